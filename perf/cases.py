@@ -13,6 +13,7 @@ job), the elements T of one intermediate value and the payload mode.  Routes:
 """
 from __future__ import annotations
 
+import itertools
 import math
 
 import torch
@@ -154,18 +155,24 @@ def _values(shape, case, g):
     return torch.empty(shape, dtype=dtype, device="cuda").normal_(0.0, case["sigma"], generator=g)
 
 
+def _inputs(case, seed):
+    """The values (or the files) [J][N][Q][T], and the model [J][Q][T] of a step from files."""
+    g = torch.Generator(device="cuda").manual_seed(int(seed))
+    J = math.comb(case["K"], case["r"] + 1) if case["route"] == "shuffle" else 1
+    V = _values((J, case["N"], case["Q"], case["T"]), case, g)
+    return V, _values((J, case["Q"], case["T"]), case, g) if case["route"] == "files" else None
+
+
 def prepare(case, seed):
     """The plan, uploaded; the values (or files and model) in device memory; the buffers a program keeps for results."""
     route = case["route"]
     plan = L.Plan(case["K"], case["r"], case["Q"], case["N"], jobs=route == "shuffle", compression=route == "uncoded")
     plan.bind(case["T"], case["mode"]).upload()
-    g = torch.Generator(device="cuda").manual_seed(int(seed))
+    V, theta = _inputs(case, seed)
     shapes = plan.shapes()
-    V = _values(shapes["V"], case, g)
     state = {"plan": plan, "route": route, "mode": case["mode"], "V": V}
     if route == "files":
-        state["files"], state["V"] = V, torch.empty_like(V)
-        state["theta"] = _values(shapes["Phi"], case, g)
+        state["files"], state["V"], state["theta"] = V, torch.empty_like(V), theta
     kept = {"pipeline": (), "files": (), "node": (), "shuffle": ("D",), "stages": ("Vbar", "D"), "uncoded": ("Vbar",)}
     for name in ("X", "Phi") + kept[route]:
         if route == "uncoded" and name == "X":
@@ -209,4 +216,76 @@ def run(state):
     else:
         plan.node_encode(-1, V, X)
         plan.node_decode_reduce(-1, V, X, Phi)
+    return out
+
+
+# ------------------------------------------------------------------ the same pass in 64 bits
+def _schedule(case):
+    """Per round and member: the member's node, and the file (over all jobs) its batch starts at."""
+    K, r, N = case["K"], case["r"], case["N"]
+    groups = list(itertools.combinations(range(K), r + 1))
+    member, first = [], []
+    if case["route"] != "shuffle":           # one job: batch p lives on the p-th r-subset of the nodes
+        rank = {P: p for p, P in enumerate(itertools.combinations(range(K), r))}
+        m = N // len(rank)
+        for S in groups:
+            member.append(S)
+            first.append([rank[S[:b] + S[b + 1:]] * m for b in range(r + 1)])
+        return member, first
+    m = N // (r + 1)
+    job = {S: j for j, S in enumerate(groups)}
+
+    def start(S, dropped):                   # the batch of the job on S that the node `dropped` misses
+        return job[S] * N + (r - S.index(dropped)) * m
+
+    for S in groups:
+        member.append(S)
+        first.append([start(S, s) for s in S])
+        for i in range(K):                   # second stage: one round per node outside the group
+            if i not in S:
+                member.append(S)
+                first.append([start(tuple(sorted(set(S) - {s} | {i})), i) for s in S])
+    return member, first
+
+
+def exact(case, seed):
+    """Plain sums in 64 bits: outputs, pre-combined and decoded packets, and coded packets where they are numbers."""
+    if case["mode"] == "u32":
+        return None                          # whole numbers: compared bit for bit
+    route, K, r, Q, N, T = (case[k] for k in ("route", "K", "r", "Q", "N", "T"))
+    V, theta = _inputs(case, seed)
+    V = V.double() if theta is None else theta.double().unsqueeze(1) - V.double()
+    out = {"Phi": V.sum(1)}
+    W, files = Q // K * T, V.reshape(-1, K, Q // K * T)
+    if route == "files":
+        out["V"] = V
+    if route == "uncoded":
+        num, den = (r, K) if 2 * r <= K else (1, 2)
+        nb, per = -(-den // num), N * num // den
+        batch = [files[t * per:(t + 1) * per if t < nb - 1 else N].sum(0) for t in range(nb)]
+        out["packets"] = torch.stack([batch[t][k] for k in range(K) for t in range(nb) if t != k % nb])
+        return out
+    coded = case["mode"] == "f32"
+    if not coded and route not in ("shuffle", "stages"):
+        out["X"] = None                      # bit patterns
+        return out
+    member, first = (torch.tensor(t, device="cuda") for t in _schedule(case))
+    m = N // (r + 1 if route == "shuffle" else math.comb(K, r))
+    ell = W // r if W % (4 * r) == 0 else (-(-W // r) + 3) // 4 * 4
+    packets, X = [], []
+    step = max(1, (1 << 27) // ((r + 1) * r * ell))
+    for u in range(0, len(member), step):
+        who, at = member[u:u + step], first[u:u + step]
+        P = sum(files[at + f, who] for f in range(m))                    # [rounds][r+1][W]
+        if route in ("shuffle", "stages"):
+            packets.append(P)
+        if coded:
+            seg = torch.nn.functional.pad(P, (0, r * ell - W)).view(-1, r + 1, r, ell)
+            X.append(torch.stack([sum(seg[:, b, a - (a > b)] for b in range(r + 1) if b != a)
+                                  for a in range(r + 1)], 1))
+    out["X"] = torch.cat(X) if coded else None
+    if packets:
+        out["D"] = torch.cat(packets)
+        if route == "stages":
+            out["Vbar"] = out["D"]
     return out
