@@ -241,8 +241,9 @@ int ccdc_shuffle_fused(const ccdc_plan_t *plan, const void *V, void *X, void *D,
  * receiver as in ccdc_decode (coded pack minus the receiver's side information)
  * and added to that receiver's output, together with the files it stores itself.
  * X equals ccdc_encode's bit for bit; Phi is bit-exact in XOR mode and, in fp32,
- * a fixed summation order different from ccdc_reduce's.  Uses the plan's
- * workspace.  CCDC_ESIZE for plans of ccdc_plan_jobs, for r > 5 and for
+ * a fixed summation order different from ccdc_reduce's.  Any value length and any
+ * element-aligned pointers take the same kernel.  Uses the plan's workspace (at
+ * most 64 MiB for this call).  CCDC_ESIZE for plans of ccdc_plan_jobs, for r > 5 and for
  * K*r > 256 (the per-lane outputs of all nodes must fit in 64 KB of LDS):
  * use ccdc_shuffle_fused + ccdc_reduce there. */
 int ccdc_pipeline_fused(const ccdc_plan_t *plan, const void *V, void *X, void *Phi, void *stream);

@@ -12,6 +12,8 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libccdc.so")
 SOURCES = ["ccdc.hip", "pipeline.hip", "node.hip", "noalloc.hip", "map.hip", "plan.cpp"]
+# pipeline.hip has hundreds of kernel instantiations: it is compiled in pieces, one per payload algebra
+PIECES = {"pipeline.hip": ("CCDC_PIPELINE_PART", 5)}
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
@@ -40,14 +42,21 @@ def build_library(verbose: bool = False) -> str:
     """Compile every source (in parallel) and link the shared library."""
     os.makedirs(OBJ, exist_ok=True)
     inc = ["-I", os.path.join(ROOT, "include"), "-I", CSRC]
-    objs = [os.path.join(OBJ, s + ".o") for s in SOURCES]
+    units = []                                      # (source, object, extra flags), the long ones first
+    for src in sorted(SOURCES, key=lambda s: s not in PIECES):
+        name, n = PIECES.get(src, ("", 0))
+        if n:
+            units += [(src, os.path.join(OBJ, f"{src}.{i}.o"), [f"-D{name}={i}"]) for i in range(n)]
+        else:
+            units.append((src, os.path.join(OBJ, src + ".o"), []))
+    objs = [obj for _, obj, _ in units]
 
-    def compile_one(pair):
-        src, obj = pair
-        _run([HIPCC] + FLAGS + inc + ["-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj], verbose)
+    def compile_one(unit):
+        src, obj, extra = unit
+        _run([HIPCC] + FLAGS + extra + inc + ["-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj], verbose)
 
-    with ThreadPoolExecutor(max_workers=len(SOURCES)) as pool:
-        list(pool.map(compile_one, zip(SOURCES, objs)))
+    with ThreadPoolExecutor(max_workers=min(len(units), 8)) as pool:
+        list(pool.map(compile_one, units))
     _run([HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-fno-gpu-rdc"] + objs + ["-o", LIB], verbose)
     return LIB
 

@@ -253,7 +253,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce_rows(const typename A::elem *
 void release_device(ccdc_plan_t *p)
 {
     if (!p) return;
-    if (p->uploaded || p->d_src_off || p->d_red_ptr || p->d_red_row || p->d_red_out || p->d_loc_row || p->d_member ||
+    if (p->uploaded || p->d_src_off || p->d_red_ptr || p->d_red_row || p->d_red_out || p->d_loc_row || p->d_pipe_row ||
         p->d_row_files || p->d_node_rows || p->d_workspace || p->ws_event) {
         int cur = -1;
         const bool sw = hipGetDevice(&cur) == hipSuccess && p->device >= 0 && cur != p->device &&
@@ -263,7 +263,7 @@ void release_device(ccdc_plan_t *p)
         (void)hipFree(p->d_red_row);
         (void)hipFree(p->d_red_out);
         (void)hipFree(p->d_loc_row);
-        (void)hipFree(p->d_member);
+        (void)hipFree(p->d_pipe_row);
         (void)hipFree(p->d_row_files);
         (void)hipFree(p->d_node_rows);
         (void)hipFree(p->d_workspace);
@@ -271,11 +271,11 @@ void release_device(ccdc_plan_t *p)
         if (sw) (void)hipSetDevice(cur);
     }
     p->d_src_off = p->d_red_ptr = p->d_red_row = p->d_red_out = p->d_loc_row = nullptr;
-    p->d_member = nullptr;
+    p->d_pipe_row = nullptr;
     p->d_row_files = nullptr;
     p->d_node_rows = nullptr;
     p->d_workspace = nullptr;
-    p->pipe_chunks[0] = p->pipe_chunks[1] = p->pipe_chunks[2] = 0;
+    p->pipe_chunks = 0;
     p->ws_event = nullptr;
     p->ws_stream = nullptr;
     p->ws_used = false;
@@ -450,7 +450,7 @@ int ccdc_plan_upload(ccdc_plan_t *plan)
     if (rc == CCDC_OK) rc = to_device(plan->red_row, &plan->d_red_row);
     if (rc == CCDC_OK) rc = to_device(plan->red_out, &plan->d_red_out);
     if (rc == CCDC_OK) rc = to_device(plan->loc_row, &plan->d_loc_row);
-    if (rc == CCDC_OK) rc = to_device(plan->round_member, &plan->d_member);
+    if (rc == CCDC_OK) rc = to_device(plan->pipe_row, &plan->d_pipe_row);
     if (rc == CCDC_OK && !plan->row_files.empty()) rc = to_device(plan->row_files, &plan->d_row_files);
     if (rc == CCDC_OK && !plan->node_rows.empty()) rc = to_device(plan->node_rows, &plan->d_node_rows);
     if (rc == CCDC_OK && plan->workspace_bytes > 0 &&

@@ -23,6 +23,7 @@ struct SumF32 {                       // real numbers throughout
     static constexpr bool fixed_order = false;
     static __device__ __forceinline__ elem zero() { return 0.0f; }
     static __device__ __forceinline__ acc azero() { return 0.0f; }
+    static __device__ __forceinline__ acc identity() { return -0.0f; }
     static __device__ __forceinline__ acc widen(elem a) { return a; }
     static __device__ __forceinline__ elem narrow(acc a) { return a; }
     static __device__ __forceinline__ acc add(acc a, acc b) { return a + b; }
@@ -36,6 +37,7 @@ struct XorU32 {                       // the field F_{2^T} throughout
     static constexpr bool fixed_order = false;
     static __device__ __forceinline__ elem zero() { return 0u; }
     static __device__ __forceinline__ acc azero() { return 0u; }
+    static __device__ __forceinline__ acc identity() { return 0u; }
     static __device__ __forceinline__ acc widen(elem a) { return a; }
     static __device__ __forceinline__ elem narrow(acc a) { return a; }
     static __device__ __forceinline__ acc add(acc a, acc b) { return a ^ b; }
@@ -49,6 +51,7 @@ struct HybF32 {                       // numbers are summed, packets are XOR-cod
     static constexpr bool fixed_order = true;
     static __device__ __forceinline__ elem zero() { return 0.0f; }    // all-zero bits: also the XOR identity
     static __device__ __forceinline__ acc azero() { return 0.0f; }
+    static __device__ __forceinline__ acc identity() { return -0.0f; }
     static __device__ __forceinline__ acc widen(elem a) { return a; }
     static __device__ __forceinline__ elem narrow(acc a) { return a; }
     static __device__ __forceinline__ acc add(acc a, acc b) { return a + b; }
@@ -72,6 +75,7 @@ struct Hyb16 {
     static constexpr bool fixed_order = true;
     static __device__ __forceinline__ elem zero() { return 0; }
     static __device__ __forceinline__ acc azero() { return 0.0f; }
+    static __device__ __forceinline__ acc identity() { return -0.0f; }
     static __device__ __forceinline__ acc widen(elem a)
     {
         if constexpr (BF) {
@@ -132,6 +136,13 @@ struct Ops {
         Q z;
 #pragma unroll
         for (int i = 0; i < VEC; i++) z.v[i] = A::azero();
+        return z;
+    }
+    static __device__ __forceinline__ Q identity()         // identity + a is a, pattern for pattern
+    {
+        Q z;
+#pragma unroll
+        for (int i = 0; i < VEC; i++) z.v[i] = A::identity();
         return z;
     }
     static __device__ __forceinline__ Q widen(P a)
@@ -222,6 +233,59 @@ __device__ __forceinline__ void store_stream(void *p, const P &v)
 #else
     *reinterpret_cast<P *>(p) = v;
 #endif
+}
+
+// The same for packs of E elements that are only aligned to E: global memory serves
+// unaligned dwords and vectors of them in one instruction.
+template <class P, class E>
+struct AnyBits {
+    typedef typename Bits<sizeof(P)>::type type __attribute__((aligned(sizeof(E))));
+};
+template <class P, class E>
+__device__ __forceinline__ P load_stream_any(const void *p)
+{
+    using B = typename AnyBits<P, E>::type;
+    const B b = __builtin_nontemporal_load(reinterpret_cast<const B *>(p));
+    P out;
+    __builtin_memcpy(&out, &b, sizeof(P));
+    return out;
+}
+template <class P, class E>
+__device__ __forceinline__ void store_stream_any(void *p, const P &v)
+{
+    using B = typename AnyBits<P, E>::type;
+    B b;
+    __builtin_memcpy(&b, &v, sizeof(P));
+    __builtin_nontemporal_store(b, reinterpret_cast<B *>(p));
+}
+template <class P, class E>
+__device__ __forceinline__ void store_any(void *p, const P &v)
+{
+    using B = typename AnyBits<P, E>::type;
+    B b;
+    __builtin_memcpy(&b, &v, sizeof(P));
+    *reinterpret_cast<B *>(p) = b;
+}
+
+// A value that is the same in all lanes of a wavefront, told to the compiler as such.
+__device__ __forceinline__ uint32_t wave_uniform(uint32_t v)
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+#else
+    return v;
+#endif
+}
+
+// A lane's 32-bit byte offset, made anew where it is used: the compiler then sees next to the
+// access that it is 32 bits wide and adds it to the (uniform) row address in the access itself
+// instead of in two registers a row.
+__device__ __forceinline__ uint32_t lane_offset(uint32_t v)
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    asm volatile("" : "+v"(v));
+#endif
+    return v;
 }
 
 constexpr int kBlock = 256;

@@ -1,4 +1,6 @@
 // One-pass pipeline kernel (combine + encode + decode + reduce) and its entry point.
+#include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "common.hpp"
@@ -7,52 +9,70 @@ namespace {
 using namespace ccdc;
 
 // ------------------------------------------------- whole path in one pass
-// combine + encode + decode + reduce for a single-job plan.  A workgroup is one
-// wavefront; lane = in-segment pack x; the workgroup walks a chunk of rounds.
+// combine + encode + decode + reduce for a single-job plan.  A workgroup is up to
+// eight wavefronts on one tile of columns (lane = in-segment pack x); each walks
+// its share of the rounds and of the files that nodes store themselves.
 // For a round it reads the r packs of each of the r+1 packets that sit at
 // x (every needed element of V once), forms each sender's coded pack (written
 // to X), decodes it for each receiver exactly as k_decode does, and adds the
 // decoded pack to the receiver's running output.  Those running outputs (K nodes
-// x r segments per lane) live in LDS, one private slot per lane: no atomics, no
-// barriers, and since only the owning lane touches a slot the summation order is
-// program order.  (LDS float atomics were measured several times slower than
-// this read-add-write of the round's slots.)
-// The files a node stores itself are added from V the same way.  With more than
-// one chunk the per-chunk outputs go to the workspace and k_reduce_final adds
+// x r segments per lane) live in LDS, one private slot per lane of every wavefront:
+// no atomics, one barrier at the end, and since only the owning lane touches a slot
+// the summation order is program order.  (LDS float atomics were measured several
+// times slower than this read-add-write of the round's slots.)
+// The wavefronts' outputs are added in wavefront order; with more than one chunk
+// the per-chunk outputs go to the workspace and k_reduce_final adds
 // them in chunk order.  Running outputs and chunk outputs are sums in the making
 // (the algebra's acc type); they are narrowed to elements once, when Phi is written.
 //
-// LDS capacity, not registers, bounds how many wavefronts fit on a compute
-// unit, so the loads of the next PF rounds are kept in flight in registers
-// while the current round is decoded.  The round loop is branch-free so that
-// the hardware load counter can be waited on partially: a short or empty last
-// segment (RAGGED) is read at a clamped position and replaced by zeros.
-// MULTI (a batch has more than one file) adds the file loop and gives up the
-// prefetch.
-#ifndef CCDC_PIPE_PREFETCH_REGS
-#define CCDC_PIPE_PREFETCH_REGS 160               // registers a lane may spend on rounds in flight
-#endif
-#ifndef CCDC_PIPE_PREFETCH_MAX
-#define CCDC_PIPE_PREFETCH_MAX 8
-#endif
-#ifndef CCDC_PIPE_VMCNT_BUDGET
-#define CCDC_PIPE_VMCNT_BUDGET 56                 // outstanding loads+stores; the counter has 6 bits
-#endif
-template <int VEC, int R1>
+// What bounds it: bytes on large inputs (the 8-node gradient shape, 4.04 GB of
+// traffic, runs at 5.4 TB/s); waiting on small ones and on large K*r, where LDS
+// capacity, not registers, bounds how many wavefronts fit on a compute unit.  So
+// the loads of the next PF steps are kept in flight in registers while a round is
+// decoded.  A step is a round, or (MULTI: a batch has m > 1 files) one file of it:
+// the packs of the m files are added up as they arrive.  Walking the files step
+// by step in the same pipeline took the 8-node shape with 10 files a batch
+// (h32, T = 25000) from 236 to 93 us; the kernel before read a round, waited, and
+// went on.
+// Packs are loaded and stored at element alignment, so any value length runs with
+// wide packs (7 nodes, r = 3, f32, T = 100003: 38.4 us with one-element packs, 29.3 with four).
+template <class A, int VEC, int R1, bool MULTI>
 constexpr int prefetch_depth()
 {
-    constexpr int by_regs = CCDC_PIPE_PREFETCH_REGS / (VEC * R1 * (R1 - 1));
-    constexpr int by_cnt = CCDC_PIPE_VMCNT_BUDGET / (R1 * (R1 - 1) + R1);
+    constexpr int packs = R1 * (R1 - 1);
+    constexpr int regs = packs * ((VEC * (int)sizeof(typename A::elem) + 3) / 4);
+    constexpr int by_regs = (MULTI ? 80 : 120) / regs;       // registers a lane spends on rounds in flight
+    constexpr int by_cnt = 56 / (packs + R1);                //  the counter of outstanding loads and stores has 6 bits
+        constexpr int most = R1 == 2 ? 6 : 4;
     constexpr int d = by_regs < by_cnt ? by_regs : by_cnt;
-    return d < 1 ? 1 : (d > CCDC_PIPE_PREFETCH_MAX ? CCDC_PIPE_PREFETCH_MAX : d);
+    return d < 1 ? 1 : (d > most ? most : d);
 }
 
-template <class A, int VEC, int R1, bool MULTI, bool RAGGED>
-__global__ __launch_bounds__(ccdc::kPipeLanes) void k_pipeline(
-    const typename A::elem *__restrict__ V, typename A::elem *__restrict__ X, typename A::elem *__restrict__ Phi,
-    typename A::acc *__restrict__ part, const int64_t *__restrict__ src_off, const int32_t *__restrict__ member, const int64_t *__restrict__ loc_row,
-    int K, uint32_t Lv, uint32_t Wv, int m, int64_t file_stride, uint32_t R, uint32_t tiles, uint32_t chunks,
-    uint32_t n_loc, int64_t chunk_stride)
+// How a packet's last segment ends, at a given pack width.
+enum Tail {
+    kWhole = 0,                       // r segments of ell elements, whole packs everywhere
+    kShort = 1,                       // the last segment is short or empty, but a pack is either in it or past its end
+    kSplit = 2,                       // some pack would straddle the end of the packet
+};
+
+struct PipeArgs {
+    int K, m;
+    uint32_t W, ell;                  // elements of a packet and of a segment
+    uint32_t R, n_loc;
+    uint32_t tiles, chunks, waves;
+    bool even;                        // how the work is shared out, see walk()
+    uint32_t cols;                    // packs the wide columns cover (kSplit: the rest is the last tile's)
+    int64_t file_stride, chunk_stride;
+};
+
+// One wavefront's share of the pass on one tile of columns: lane = VEC elements
+// from in-segment position x on, rounds and own files of the wavefront's range.
+template <class A, int VEC, int R1, bool MULTI, bool SHORT>
+__device__ __forceinline__ void walk(const typename A::elem *__restrict__ V, typename A::elem *__restrict__ X,
+                                     typename A::elem *__restrict__ Phi, typename A::acc *__restrict__ part,
+                                     const int64_t *__restrict__ rows, const int64_t *__restrict__ own,
+                                     const PipeArgs &p, unsigned char *smem, uint32_t chunk, uint32_t wave,
+                                     uint32_t lane, uint32_t x, bool active)
 {
     using E = typename A::elem;
     using O = Ops<A, VEC>;
@@ -60,11 +80,277 @@ __global__ __launch_bounds__(ccdc::kPipeLanes) void k_pipeline(
     using Q = typename O::Q;
     constexpr int r = R1 - 1;
     constexpr int LANES = ccdc::kPipeLanes;
-    constexpr int PF = MULTI ? 1 : prefetch_depth<VEC, R1>();
+    constexpr int PF = prefetch_depth<A, VEC, R1, MULTI>();
     constexpr int PFL = PF * R1;                     // own-file rows in flight (r packs each)
-    extern __shared__ __align__(16) unsigned char smem[];
-    Q *acc = reinterpret_cast<Q *>(smem) + threadIdx.x;      // slot i of this lane: acc[i * LANES]
+    const int K = p.K, slots = K * r;
+    Q *all = reinterpret_cast<Q *>(smem) + lane;     // slot i of wavefront g, this lane: all[(g * slots + i) * LANES]
+    Q *acc = all + (size_t)wave * slots * LANES;
 
+    if (active) {
+        bool valid[r];                // does segment rho reach position x (short / empty tail)
+        uint32_t offb[r];             // byte offset of pack x of segment rho inside a packet
+#pragma unroll
+        for (int rho = 0; rho < r; rho++) {
+            const uint32_t pos = rho * p.ell + x;
+            valid[rho] = !SHORT || pos < p.W;
+            offb[rho] = (valid[rho] ? pos : p.W - VEC) * (uint32_t)sizeof(E);
+        }
+        const uint32_t xb = x * (uint32_t)sizeof(E);
+        auto pack_at = [](const E *row, uint32_t byte_off) -> P {
+            return load_stream_any<P, E>(reinterpret_cast<const char *>(row) + byte_off);
+        };
+        for (int i = 0; i < slots; i++) acc[i * LANES] = O::azero();
+
+        struct Row {                  // a round's table entries (wave-uniform): (element offset << 12) | node
+            int64_t e[R1];
+        };
+        struct Stage {
+            P w[R1][r];               // w[b][rho]: pack x of segment rho of packet b (of one file of its batch)
+            int slot[R1];             // first slot of the node packet b is for
+        };
+        auto fetch = [&](uint32_t u) {
+            Row t;
+#pragma unroll
+            for (int b = 0; b < R1; b++) t.e[b] = rows[(size_t)u * R1 + b];
+            return t;
+        };
+        auto issue = [&](const Row &t, int f, Stage &s) {
+            uint32_t at[r];
+#pragma unroll
+            for (int rho = 0; rho < r; rho++) at[rho] = lane_offset(offb[rho]);
+#pragma unroll
+            for (int b = 0; b < R1; b++) {
+                const E *row = V + (t.e[b] >> 12);
+                if constexpr (MULTI) row += f * p.file_stride;
+                s.slot[b] = (int)(t.e[b] & 4095) * r;
+#pragma unroll
+                for (int rho = 0; rho < r; rho++) s.w[b][rho] = pack_at(row, at[rho]);
+            }
+        };
+        // Decode one round and add the r(r+1) decoded packs to their owners' outputs.
+        // The slots of a round are distinct (receiver b, segment rank(a,b)), so they are
+        // read ahead of the writes: all of them where registers allow (one LDS wait a round).
+        auto finish = [&](uint32_t u, const P (&w)[R1][r], const int (&slot)[R1]) {
+            constexpr int AHEAD = R1 * r * VEC <= 64 ? R1 : 2;       // senders whose slots are held at a time
+            Q cur[AHEAD][R1];         // cur[a % AHEAD][b]: running output that sender a's pack for b goes to
+            auto read = [&](int a) {
+#pragma unroll
+                for (int b = 0; b < R1; b++)
+                    if (b != a) cur[a % AHEAD][b] = acc[(slot[b] + a - (a > b ? 1 : 0)) * LANES];
+            };
+#pragma unroll
+            for (int a = 0; a + 1 < AHEAD; a++) read(a);
+#pragma unroll
+            for (int a = 0; a < R1; a++) {
+                if (a + AHEAD - 1 < R1) read(a + AHEAD - 1);
+                P coded = O::zero();
+#pragma unroll
+                for (int b = 0; b < R1; b++)
+                    if (b != a) coded = O::code(coded, w[b][a - (a > b ? 1 : 0)]);
+                store_stream_any<P, E>(reinterpret_cast<char *>(X + ((size_t)u * R1 + a) * p.ell) + lane_offset(xb), coded);
+#pragma unroll
+                for (int b = 0; b < R1; b++) {
+                    if (b == a) continue;
+                    P d = coded;
+#pragma unroll
+                    for (int b2 = 0; b2 < R1; b2++)
+                        if (b2 != a && b2 != b) d = O::uncode(d, w[b2][a - (a > b2 ? 1 : 0)]);
+                    // a slot past a short segment collects zeros and is never written out
+                    acc[(slot[b] + a - (a > b ? 1 : 0)) * LANES] = O::accum(cur[a % AHEAD][b], d);
+                }
+            }
+        };
+        auto clip = [&](P v, int rho) -> P {
+            if constexpr (SHORT) v = O::select(valid[rho], v, O::zero());
+            return v;
+        };
+
+        // This wavefront's rounds [u0, u1) and own rows [i0, i1): the j-th of n equal shares of
+        // each (even), or of the list of rounds (m files of r+1 rows each) followed by the own
+        // rows, so that a wavefront with little to do mostly has one kind and one wait for it.
+        const uint32_t j = chunk * p.waves + wave, n = p.chunks * p.waves;
+        uint32_t u0, u1, i0, i1;
+        if (p.even) {
+            u0 = (uint32_t)((uint64_t)p.R * j / n);
+            u1 = (uint32_t)((uint64_t)p.R * (j + 1) / n);
+            i0 = (uint32_t)((uint64_t)p.n_loc * j / n);
+            i1 = (uint32_t)((uint64_t)p.n_loc * (j + 1) / n);
+        } else {
+            const uint64_t per_round = (uint64_t)R1 * (uint32_t)p.m, in_rounds = per_round * p.R;
+            const uint64_t total = in_rounds + p.n_loc;
+            const uint64_t lo = total * j / n, hi = total * (j + 1) / n;
+            u0 = lo < in_rounds ? (uint32_t)(lo / per_round) : p.R;
+            u1 = hi < in_rounds ? (uint32_t)(hi / per_round) : p.R;
+            i0 = lo < in_rounds ? 0 : (uint32_t)(lo - in_rounds);
+            i1 = hi < in_rounds ? 0 : (uint32_t)(hi - in_rounds);
+        }
+
+        // Rounds: a step is one file of a round's batches (MULTI) or the whole round.
+        // PF steps are in flight; the main loop has no condition on what to load.
+        if (u1 > u0) {
+            const uint32_t steps = MULTI ? (u1 - u0) * (uint32_t)p.m : u1 - u0;
+            Stage st[PF];
+            uint32_t iu = u0, cu = u0;               // round and file of the next step to load / to use
+            int jf = 0, cf = 0;
+            Q sum[MULTI ? R1 : 1][r];
+            if constexpr (MULTI) {
+#pragma unroll
+                for (int b = 0; b < R1; b++)
+#pragma unroll
+                    for (int rho = 0; rho < r; rho++) sum[b][rho] = O::identity();
+            }
+            auto load = [&](const Row &t, Stage &s) {
+                issue(t, jf, s);
+                if constexpr (MULTI) {
+                    if (++jf == p.m) { jf = 0; iu++; }
+                } else {
+                    iu++;
+                }
+            };
+            auto use = [&](Stage &s) {
+                if constexpr (MULTI) {
+#pragma unroll
+                    for (int b = 0; b < R1; b++)
+#pragma unroll
+                        for (int rho = 0; rho < r; rho++) sum[b][rho] = O::accum(sum[b][rho], s.w[b][rho]);
+                    if (++cf == p.m) {
+                        P w[R1][r];
+#pragma unroll
+                        for (int b = 0; b < R1; b++)
+#pragma unroll
+                            for (int rho = 0; rho < r; rho++) {
+                                w[b][rho] = clip(O::narrow(sum[b][rho]), rho);
+                                sum[b][rho] = O::identity();
+                            }
+                        finish(cu, w, s.slot);
+                        cf = 0;
+                        cu++;
+                    }
+                } else {
+                    if constexpr (SHORT) {
+#pragma unroll
+                        for (int b = 0; b < R1; b++)
+#pragma unroll
+                            for (int rho = 0; rho < r; rho++) s.w[b][rho] = clip(s.w[b][rho], rho);
+                    }
+                    finish(cu, s.w, s.slot);
+                    cu++;
+                }
+            };
+            // The table row of a load is asked for a turn ahead, behind the loads of the turn before:
+            // it arrives while those of the stage in hand are waited for.  (One row more than there
+            // are rounds may be asked for; the table has it.)
+            Row ahead;
+            auto turn = [&](Stage &s) {
+                use(s);
+                load(ahead, s);
+                ahead = fetch(iu);
+            };
+            // The compiler waits for a stage by counting the loads and stores issued after it,
+            // and counts the least that any way into the code may have issued: the first turn
+            // is taken out of the loop (no X store lies between its loads), and short ranges
+            // fill the stages on a way of their own.
+            uint32_t i = 0;
+            if (steps >= 3 * PF) {
+#pragma unroll
+                for (int s = 0; s < PF; s++) {
+                    load(fetch(iu), st[s]);
+                }
+                ahead = fetch(iu);
+#pragma unroll
+                for (int s = 0; s < PF; s++) turn(st[s]);
+                for (i = PF; i + 2 * PF <= steps; i += PF) {
+#pragma unroll
+                    for (int s = 0; s < PF; s++) turn(st[s]);
+                }
+            } else {
+#pragma unroll
+                for (int s = 0; s < PF; s++)
+                    if ((uint32_t)s < steps) load(fetch(iu), st[s]);
+            }
+            for (; i < steps; i += PF) {
+#pragma unroll
+                for (int s = 0; s < PF; s++)
+                    if (i + s < steps) {
+                        use(st[s]);
+                        if (i + s + PF < steps) load(fetch(iu), st[s]);
+                    }
+            }
+        }
+
+        // the files each node stores itself; table entries as above
+        if (i1 > i0) {
+            struct Own {
+                P w[r];
+                int slot;
+            };
+            auto load = [&](int64_t e, Own &s) {
+                s.slot = (int)(e & 4095) * r;
+                const E *row = V + (e >> 12);
+#pragma unroll
+                for (int rho = 0; rho < r; rho++) s.w[rho] = pack_at(row, lane_offset(offb[rho]));
+            };
+            auto use = [&](const Own &s) {
+                Q cur[r];
+#pragma unroll
+                for (int rho = 0; rho < r; rho++) cur[rho] = acc[(s.slot + rho) * LANES];
+#pragma unroll
+                for (int rho = 0; rho < r; rho++) acc[(s.slot + rho) * LANES] = O::accum(cur[rho], clip(s.w[rho], rho));
+            };
+            Own ow[PFL];
+            uint32_t i = i0;
+            if (i1 - i0 >= 2 * PFL) {
+#pragma unroll
+                for (int s = 0; s < PFL; s++) load(own[i0 + s], ow[s]);
+                for (; i + 2 * PFL <= i1; i += PFL) {
+                    int64_t e[PFL];
+#pragma unroll
+                    for (int s = 0; s < PFL; s++) e[s] = own[i + s + PFL];
+#pragma unroll
+                    for (int s = 0; s < PFL; s++) {
+                        use(ow[s]);
+                        load(e[s], ow[s]);
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int s = 0; s < PFL; s++)
+                    if (i0 + s < i1) load(own[i0 + s], ow[s]);
+            }
+            for (; i < i1; i += PFL) {
+#pragma unroll
+                for (int s = 0; s < PFL; s++)
+                    if (i + s < i1) {
+                        use(ow[s]);
+                        if (i + s + PFL < i1) load(own[i + s + PFL], ow[s]);
+                    }
+            }
+        }
+    }
+
+    // the outputs of the workgroup's wavefronts are added in wavefront order and written, the
+    // only chunk's straight to Phi, else to the chunk's slice of the workspace
+    if (p.waves > 1) __syncthreads();
+    if (!active) return;
+    typename A::acc *dst = part + (int64_t)chunk * p.chunk_stride;
+    for (uint32_t i = wave; i < (uint32_t)slots; i += p.waves) {
+        const uint32_t k = i / r, pos = (i - k * r) * p.ell + x;
+        if (SHORT && pos >= p.W) continue;
+        Q v = all[i * LANES];
+        for (uint32_t g = 1; g < p.waves; g++) v = O::add(v, all[((size_t)g * slots + i) * LANES]);
+        const int64_t at = (int64_t)k * p.W + pos;               // element index in [K][W]
+        if (p.chunks == 1) store_any<P, E>(Phi + at, O::narrow(v));
+        else store_any<Q, typename A::acc>(dst + at, v);
+    }
+}
+
+template <class A, int VEC, int R1, bool MULTI, int TAIL>
+__global__ __launch_bounds__(ccdc::kPipeLanes *ccdc::kPipeMaxWaves) void k_pipeline(
+    const typename A::elem *__restrict__ V, typename A::elem *__restrict__ X, typename A::elem *__restrict__ Phi,
+    typename A::acc *__restrict__ part, const int64_t *__restrict__ rows, const int64_t *__restrict__ own, PipeArgs p)
+{
+    constexpr uint32_t LANES = ccdc::kPipeLanes;
+    extern __shared__ __align__(16) unsigned char smem[];
     // Workgroups are handed to the 8 XCDs round-robin.  When the rounds are cut
     // into chunks, renumber them so that each XCD gets a contiguous range of
     // (chunk, tile) pairs: the tiles of one chunk (adjacent pieces of the same
@@ -75,201 +361,62 @@ __global__ __launch_bounds__(ccdc::kPipeLanes) void k_pipeline(
     const uint32_t nb = gridDim.x, q = nb / XCDS, rem = nb % XCDS;
     const uint32_t xcd = blockIdx.x % XCDS, j = blockIdx.x / XCDS;
     const uint32_t logical =
-        chunks > 1 ? (xcd < rem ? xcd * (q + 1) : rem * (q + 1) + (xcd - rem) * q) + j : blockIdx.x;
-    const uint32_t tile = logical % tiles, chunk = logical / tiles;
-    const uint32_t x = tile * LANES + threadIdx.x;
-    if (x >= Lv) return;
-
-    bool valid[r];                    // does segment rho reach position x (short / empty tail)
-    uint32_t offb[r];                 // byte offset of pack x of segment rho inside a packet
-#pragma unroll
-    for (int rho = 0; rho < r; rho++) {
-        const uint32_t pos = rho * Lv + x;
-        valid[rho] = !RAGGED || pos < Wv;
-        offb[rho] = (valid[rho] ? pos : Wv - 1) * (uint32_t)(VEC * sizeof(E));
-    }
-    auto pack_at = [](const E *row, uint32_t byte_off) -> P {
-        return load_stream<P>(reinterpret_cast<const char *>(row) + byte_off);
-    };
-    for (int i = 0; i < K * r; i++) acc[i * LANES] = O::azero();
-
-    struct Row {                      // one round's table entries (wave-uniform)
-        int64_t src[R1];              // element offset in V of packet b's first file
-        int node[R1];                 // s_b
-    };
-    struct Stage {
-        P w[R1][r];                   // w[b][rho]: pack x of segment rho of Vbar[u][b]
-        int node[R1];
-    };
-    auto fetch_row = [&](uint32_t u, Row &t) {
-        const int64_t *src = src_off + (size_t)u * R1;
-        const int32_t *mem = member + (size_t)u * R1;
-#pragma unroll
-        for (int b = 0; b < R1; b++) {
-            t.src[b] = src[b];
-            t.node[b] = mem[b];
-        }
-    };
-    auto issue = [&](const Row &t, Stage &s) {
-#pragma unroll
-        for (int b = 0; b < R1; b++) {
-            s.node[b] = t.node[b];
-            const E *row = V + t.src[b];
-#pragma unroll
-            for (int rho = 0; rho < r; rho++) {
-                P v = pack_at(row, offb[rho]);
-                if constexpr (MULTI) {
-                    Q sum = O::widen(v);
-                    for (int f = 1; f < m; f++) sum = O::accum(sum, pack_at(row + f * file_stride, offb[rho]));
-                    v = O::narrow(sum);
-                }
-                if constexpr (RAGGED) v = O::select(valid[rho], v, O::zero());
-                s.w[b][rho] = v;
-            }
-        }
-    };
-    // Decode one round and add the r(r+1) decoded packs to their owners' outputs.
-    // The r(r+1) slots of a round are distinct (receiver b, segment rank(a,b)), so
-    // they are read together, updated, and written together: one LDS wait a round.
-    auto consume = [&](uint32_t u, const Stage &s) {
-        Q cur[R1][r];                 // cur[b][rho]: running output of node s_b, segment rho
-#pragma unroll
-        for (int b = 0; b < R1; b++)
-#pragma unroll
-            for (int rho = 0; rho < r; rho++) cur[b][rho] = acc[(s.node[b] * r + rho) * LANES];
-#pragma unroll
-        for (int a = 0; a < R1; a++) {
-            P coded = O::zero();
-#pragma unroll
-            for (int b = 0; b < R1; b++)
-                if (b != a) coded = O::code(coded, s.w[b][a - (a > b ? 1 : 0)]);
-            store_stream(reinterpret_cast<P *>(X) + ((size_t)u * R1 + a) * Lv + x, coded);
-#pragma unroll
-            for (int b = 0; b < R1; b++) {
-                if (b == a) continue;
-                const int rho = a - (a > b ? 1 : 0);
-                P d = coded;
-#pragma unroll
-                for (int b2 = 0; b2 < R1; b2++)
-                    if (b2 != a && b2 != b) d = O::uncode(d, s.w[b2][a - (a > b2 ? 1 : 0)]);
-                // a slot past a short segment collects zeros and is never written out
-                cur[b][rho] = O::accum(cur[b][rho], d);
-            }
-        }
-#pragma unroll
-        for (int b = 0; b < R1; b++)
-#pragma unroll
-            for (int rho = 0; rho < r; rho++) acc[(s.node[b] * r + rho) * LANES] = cur[b][rho];
-    };
-
-    const uint32_t u0 = (uint32_t)((uint64_t)R * chunk / chunks);
-    const uint32_t u1 = (uint32_t)((uint64_t)R * (chunk + 1) / chunks);
-    const uint32_t n = u1 - u0;
-    if (n > 0) {
-        Stage st[PF];
-#pragma unroll
-        for (int s = 0; s < PF; s++) {
-            Row t;
-            fetch_row(u0 + ((uint32_t)s < n ? s : n - 1), t);
-            issue(t, st[s]);
-        }
-        // Full groups of PF rounds with no branch inside (a branch makes the
-        // compiler drain every outstanding load); the remainder is handled after
-        // the loop.  Past the end the last round is read again (never consumed).
-        // The table row is requested before decoding so that it arrives meanwhile.
-        const uint32_t full = n / PF;
-        for (uint32_t g = 0; g < full; g++) {
-#pragma unroll
-            for (int s = 0; s < PF; s++) {
-                const uint32_t i = g * PF + s, nxt = i + PF;
-                Row t;
-                fetch_row(u0 + (nxt < n ? nxt : n - 1), t);
-                consume(u0 + i, st[s]);
-                issue(t, st[s]);
-            }
-        }
-#pragma unroll
-        for (int s = 0; s < PF; s++)
-            if (full * PF + s < n) consume(u0 + full * PF + s, st[s]);
-    }
-
-    // the files each node stores itself; a table entry is (element offset << 12) | node
-    struct Own {
-        P w[r];
-        int k;
-    };
-    auto issue_own = [&](int64_t e, Own &s) {
-        s.k = (int)(e & 4095);
-        const E *row = V + (e >> 12);
-#pragma unroll
-        for (int rho = 0; rho < r; rho++) {
-            P t = pack_at(row, offb[rho]);
-            if constexpr (RAGGED) t = O::select(valid[rho], t, O::zero());
-            s.w[rho] = t;
-        }
-    };
-    auto consume_own = [&](const Own &s) {
-        Q cur[r];
-#pragma unroll
-        for (int rho = 0; rho < r; rho++) cur[rho] = acc[(s.k * r + rho) * LANES];
-#pragma unroll
-        for (int rho = 0; rho < r; rho++) acc[(s.k * r + rho) * LANES] = O::accum(cur[rho], s.w[rho]);
-    };
-    const uint32_t i0 = (uint32_t)((uint64_t)n_loc * chunk / chunks);
-    const uint32_t i1 = (uint32_t)((uint64_t)n_loc * (chunk + 1) / chunks);
-    const uint32_t nl = i1 - i0;
-    if (nl > 0) {
-        Own ow[PFL];
-#pragma unroll
-        for (int s = 0; s < PFL; s++) issue_own(loc_row[i0 + ((uint32_t)s < nl ? s : nl - 1)], ow[s]);
-        const uint32_t full = nl / PFL;
-        for (uint32_t g = 0; g < full; g++) {
-#pragma unroll
-            for (int s = 0; s < PFL; s++) {
-                const uint32_t nxt = g * PFL + s + PFL;
-                const int64_t e = loc_row[i0 + (nxt < nl ? nxt : nl - 1)];
-                consume_own(ow[s]);
-                issue_own(e, ow[s]);
-            }
-        }
-#pragma unroll
-        for (int s = 0; s < PFL; s++)
-            if (full * PFL + s < nl) consume_own(ow[s]);
-    }
-
-    // write the chunk's outputs: the only chunk straight to Phi, else to its slice of the workspace
-    const int64_t W = (int64_t)Wv * VEC;
-    typename A::acc *dst = part + (int64_t)chunk * chunk_stride;
-    for (int k = 0; k < K; k++) {
-#pragma unroll
-        for (int rho = 0; rho < r; rho++) {
-            if (!valid[rho]) continue;
-            const int64_t pos = k * W + (int64_t)(offb[rho] / sizeof(E));        // element index in [K][W]
-            const Q v = acc[(k * r + rho) * LANES];
-            if (chunks == 1) *reinterpret_cast<P *>(Phi + pos) = O::narrow(v);
-            else *reinterpret_cast<Q *>(dst + pos) = v;
+        p.chunks > 1 ? (xcd < rem ? xcd * (q + 1) : rem * (q + 1) + (xcd - rem) * q) + j : blockIdx.x;
+    const uint32_t tile = logical % p.tiles, chunk = logical / p.tiles;
+    const uint32_t lane = threadIdx.x % LANES, wave = wave_uniform(threadIdx.x / LANES);
+    if constexpr (TAIL == kSplit) {
+        if (tile + 1 == p.tiles) {                   // what the wide columns leave: a few elements of every segment
+            const uint32_t x = p.cols * VEC + lane;
+            walk<A, 1, R1, MULTI, true>(V, X, Phi, part, rows, own, p, smem, chunk, wave, lane, x, x < p.ell);
+            return;
         }
     }
+    const uint32_t c = tile * LANES + lane;
+    walk<A, VEC, R1, MULTI, TAIL == kShort>(V, X, Phi, part, rows, own, p, smem, chunk, wave, lane, c * VEC, c < p.cols);
 }
 
 // Every k_pipeline<A, VEC, R1, *, *> has this signature.
 template <class A>
 using PipeKernel = void (*)(const typename A::elem *, typename A::elem *, typename A::elem *, typename A::acc *,
-                            const int64_t *, const int32_t *, const int64_t *, int, uint32_t, uint32_t, int, int64_t,
-                            uint32_t, uint32_t, uint32_t, uint32_t, int64_t);
+                            const int64_t *, const int64_t *, PipeArgs);
 
-// The instantiation a plan runs: MULTI when a batch has several files, RAGGED
-// when the last segment is short or empty.  Null for an r the kernel is not
-// unrolled for.
+template <int VEC>
+Tail tail_kind(const ccdc_plan_t *p)
+{
+    if (p->ell * p->r == p->W) return kWhole;
+    return p->W % VEC == 0 ? kShort : kSplit;       // ell is a multiple of 4 then
+}
+
+// Packs of a segment that the wide columns cover.  kSplit: those that every segment has whole; at
+// most 4r + 2 elements are left (r*ell - W <= 4r - 1; when the last segment is empty ell itself is
+// below 4r), which one wavefront of one-element packs covers.
+template <int VEC>
+uint32_t pipeline_cols(const ccdc_plan_t *p)
+{
+    if (tail_kind<VEC>(p) != kSplit) return (uint32_t)(p->ell / VEC);
+    const int64_t last = p->W - (p->r - 1) * p->ell;
+    return last > 0 ? (uint32_t)(last / VEC) : 0;
+}
+
+template <int VEC>
+uint32_t pipeline_tiles(const ccdc_plan_t *p)
+{
+    return cdiv(pipeline_cols<VEC>(p), ccdc::kPipeLanes) + (tail_kind<VEC>(p) == kSplit ? 1 : 0);
+}
+
+// The instantiation a plan runs.  Null for an r the kernel is not unrolled for.
 template <class A, int VEC>
 PipeKernel<A> pipeline_kernel(const ccdc_plan_t *p)
 {
-    const bool ragged = p->ell * p->r != p->W;
+    const Tail tail = tail_kind<VEC>(p);
     auto of = [&](auto r1) -> PipeKernel<A> {
         constexpr int R1 = decltype(r1)::value;
-        if (p->m > 1) return k_pipeline<A, VEC, R1, true, true>;
-        if (ragged) return k_pipeline<A, VEC, R1, false, true>;
-        return k_pipeline<A, VEC, R1, false, false>;
+        if constexpr (VEC > 1) {
+            if (tail == kSplit) return p->m > 1 ? k_pipeline<A, VEC, R1, true, kSplit> : k_pipeline<A, VEC, R1, false, kSplit>;
+        }
+        if (p->m > 1) return k_pipeline<A, VEC, R1, true, kShort>;
+        if (tail == kShort) return k_pipeline<A, VEC, R1, false, kShort>;
+        return k_pipeline<A, VEC, R1, false, kWhole>;
     };
     switch (p->r + 1) {
     case 2: return of(std::integral_constant<int, 2>());
@@ -281,66 +428,116 @@ PipeKernel<A> pipeline_kernel(const ccdc_plan_t *p)
     }
 }
 
+template <class A, int VEC, bool MULTI>
+int pipeline_depth(int r)
+{
+    switch (r) {
+    case 1: return prefetch_depth<A, VEC, 2, MULTI>();
+    case 2: return prefetch_depth<A, VEC, 3, MULTI>();
+    case 3: return prefetch_depth<A, VEC, 4, MULTI>();
+    case 4: return prefetch_depth<A, VEC, 5, MULTI>();
+    default: return prefetch_depth<A, VEC, 6, MULTI>();
+    }
+}
+
 template <int VEC>
-size_t pipeline_lds(const ccdc_plan_t *p)
+size_t pipeline_lds(const ccdc_plan_t *p)           // one wavefront's running outputs
 {
     return (size_t)p->K * p->r * ccdc::kPipeLanes * VEC * sizeof(float);     // every algebra sums in 4 bytes
 }
 
-template <int VEC>
-uint32_t pipeline_tiles(const ccdc_plan_t *p)
-{
-    return cdiv((uint64_t)(p->ell / VEC), ccdc::kPipeLanes);
-}
+// The launch geometry of a plan: pack width, wavefronts of a workgroup (they share a tile of columns
+// and add their outputs in LDS, so they cost no workspace traffic), chunks of rounds (they fill the
+// chip where tiles are few, at the price of a second kernel and of writing and reading a copy of all
+// outputs per chunk).  No single threshold on sizes separates the good from the bad: the time of a
+// candidate is estimated and the least taken.  The constants are fitted to measured passes of 54
+// shapes (K 4..24, r 1..5, 64 KB..3.3 GB, every mode, 30 to 70 geometries each); on those the choice
+// is 5 % slower than each shape's best geometry on average, 36 % at the worst, and 1.47 times as fast
+// on average as the one-wavefront workgroups with at most N/8 chunks that it replaces.
+struct Candidate {
+    int vec, waves, chunks;
+    bool even;
+    double us;
+};
 
-// Round chunks for a launch with VEC-element packs: when there are fewer column
-// tiles than wavefront slots on the device, the rounds are cut so that the grid
-// is one resident wave of equally loaded workgroups (bounded by the workspace).
 template <class A, int VEC>
-int chunks_for(const ccdc_plan_t *p)
+void consider(const ccdc_plan_t *p, Candidate *best)
 {
+    constexpr int elem = (int)sizeof(typename A::elem);
     PipeKernel<A> kernel = pipeline_kernel<A, VEC>(p);
-    if (!kernel || p->ell % VEC != 0 || p->T % VEC != 0) return 1;
-    int per_cu = 0, cus = 0, dev = 0;
+    const size_t lds = pipeline_lds<VEC>(p);
+    const bool narrowest = VEC == 1;
+    if (!kernel || lds > (size_t)ccdc::kPipeMaxLds || (!narrowest && p->ell < VEC)) return;
+    int limit = 0, cus = 0, dev = 0;                 // wavefronts a compute unit holds as far as registers go
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, ccdc::kPipeLanes, pipeline_lds<VEC>(p)) !=
-            hipSuccess ||
-        per_cu < 1 || cus < 1) {
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&limit, kernel, ccdc::kPipeLanes, 0) != hipSuccess || limit < 1 ||
+        cus < 1) {
         (void)hipGetLastError();
-        return 1;
+        limit = cus = 1;
     }
-    int64_t chunks = (int64_t)per_cu * cus / pipeline_tiles<VEC>(p);
-    if (chunks < 1) chunks = 1;
-    if (chunks > p->pipe_max_chunks) chunks = p->pipe_max_chunks;
-    return (int)chunks;
-}
-
-template <class A>
-void prepare(ccdc_plan_t *p)
-{
-    p->pipe_chunks[0] = chunks_for<A, 1>(p);
-    p->pipe_chunks[1] = p->pipe_vec >= 2 ? chunks_for<A, 2>(p) : 1;
-    p->pipe_chunks[2] = p->pipe_vec >= 4 ? chunks_for<A, 4>(p) : 1;
+    const double r1 = p->r + 1, R = (double)p->nround, m = p->m, own = (double)p->K * p->pipe_local_rows;
+    const double rows = R * r1 * m + own;            // rows of r packs a tile reads
+    const double tiles = pipeline_tiles<VEC>(p), bytes =
+        ((double)p->N * p->Q * p->T + (double)p->nrows * p->ell + (double)p->Q * p->T) * elem;
+    const int depth = p->m > 1 ? pipeline_depth<A, VEC, true>(p->r) : pipeline_depth<A, VEC, false>(p->r);
+    const double flight = depth * r1 * p->r * ccdc::kPipeLanes * VEC * elem;       // bytes a wavefront has on the way
+    double peak = VEC * elem >= 16 ? 6.5e6 : VEC * elem == 8 ? 5.3e6 : VEC * elem == 4 ? 4.2e6 : 3.2e6;   // B/us
+    if (p->T * elem % 8) peak *= 1 - 0.4 * std::min(1.0, 8.0 / (VEC * elem));    // rows start anywhere: more lines an access
+    for (int waves = 1; waves <= ccdc::kPipeMaxWaves && waves * lds <= (size_t)ccdc::kPipeMaxLds; waves++) {
+        const int by_lds = (int)(ccdc::kCuLds / (waves * lds)), by_regs = limit / waves;
+        const int per_cu = std::max(1, std::min(by_lds, by_regs));
+        const double room = (double)cus * per_cu * waves;                            // wavefronts in flight at most
+        int64_t last = 0;
+        for (int part = 8; part >= 0; part = part > 1 ? part / 2 : part - 1) {        // 1/8 .. 1 of what fills the chip, and 1 chunk
+            int64_t chunks = part ? (int64_t)((double)cus * per_cu / (part * tiles)) : 1;
+            chunks = std::max<int64_t>(1, std::min<int64_t>(chunks, p->pipe_max_chunks));
+            if (chunks == last) continue;
+            last = chunks;
+            const double shares = (double)chunks * waves, per = R / shares;
+            Candidate c{VEC, waves, (int)chunks, shares == 1 || per >= 32, 0};
+            const double w = tiles * shares, fill = w / room, gens = std::max(1.0, fill);
+            // rounds (and rounds' worth of own rows) the busiest wavefront walks
+            const double steps = c.even ? std::ceil(per) * m + own / shares / r1 : std::ceil(rows / shares / (r1 * m)) * m;
+            double rate = 1 / (0.8 / (std::min(w, room) * flight) + 1 / peak);
+            rate *= std::sqrt(gens / std::ceil(gens));                                // a last generation that is not full
+            const double stream = bytes / rate * std::pow(steps / (rows / r1 / shares), 0.08);
+            const double chain = 0.8 * gens * (steps / depth + 1);                    // waits one after the other
+            c.us = std::sqrt(stream * stream + chain * chain) + 0.007 * gens * p->K * p->r * 4 * VEC;
+            if (chunks > 1) c.us += 4 + 2.0 * chunks * p->K * p->W * 4 / 1.8e6;
+            if (best->vec == 0 || c.us < best->us) *best = c;
+        }
+    }
 }
 
 // One launch of the pass with `chunks` round chunks; partial outputs of the
 // chunks go to `part` (chunks * K * W sums) and k_reduce_final adds them.
 template <class A, int VEC>
-int run_pipeline(const ccdc_plan_t *p, const void *V, void *X, void *Phi, void *part, int chunks, bool wide_final,
-                 hipStream_t st)
+int run_pipeline(const ccdc_plan_t *p, const void *V, void *X, void *Phi, void *part, bool wide_final, hipStream_t st)
 {
     using E = typename A::elem;
     using Acc = typename A::acc;
     PipeKernel<A> kernel = pipeline_kernel<A, VEC>(p);
     if (!kernel) return CCDC_ESIZE;
-    const uint32_t Wv = (uint32_t)(p->W / VEC), Lv = (uint32_t)(p->ell / VEC);
+    const int chunks = p->pipe_chunks;
     const uint32_t tiles = pipeline_tiles<VEC>(p);
     if (!fits_launch((uint64_t)tiles * (uint64_t)chunks) || !fits_launch((uint64_t)p->K * (uint64_t)p->W)) return CCDC_ESIZE;
-    kernel<<<tiles * (uint32_t)chunks, ccdc::kPipeLanes, pipeline_lds<VEC>(p), st>>>(
-        (const E *)V, (E *)X, (E *)Phi, (Acc *)part, p->d_src_off, p->d_member, p->d_loc_row, p->K, Lv, Wv, p->m,
-        (int64_t)p->Q * p->T, (uint32_t)p->nround, tiles, (uint32_t)chunks, (uint32_t)(p->K * p->pipe_local_rows),
-        (int64_t)p->K * p->W);
+    PipeArgs args;
+    args.K = p->K;
+    args.m = p->m;
+    args.W = (uint32_t)p->W;
+    args.ell = (uint32_t)p->ell;
+    args.R = (uint32_t)p->nround;
+    args.n_loc = (uint32_t)(p->K * p->pipe_local_rows);
+    args.tiles = tiles;
+    args.chunks = (uint32_t)chunks;
+    args.waves = (uint32_t)p->pipe_waves;
+    args.even = p->pipe_even;
+    args.cols = pipeline_cols<VEC>(p);
+    args.file_stride = (int64_t)p->Q * p->T;
+    args.chunk_stride = (int64_t)p->K * p->W;
+    kernel<<<tiles * (uint32_t)chunks, ccdc::kPipeLanes * p->pipe_waves, pipeline_lds<VEC>(p) * p->pipe_waves, st>>>(
+        (const E *)V, (E *)X, (E *)Phi, (Acc *)part, p->d_pipe_row, p->d_loc_row, args);
     int rc = launched();
     if (rc != CCDC_OK || chunks == 1) return rc;
     const int64_t n = (int64_t)p->K * p->W;
@@ -360,6 +557,56 @@ int run_pipeline(const ccdc_plan_t *p, const void *V, void *X, void *Phi, void *
 
 namespace ccdc {
 
+template <class A>
+int pipeline_run(const ccdc_plan_t *p, const void *V, void *X, void *Phi, void *part, bool wide_final, hipStream_t st)
+{
+    if (p->pipe_vec == 4) return run_pipeline<A, 4>(p, V, X, Phi, part, wide_final, st);
+    if (p->pipe_vec == 2) return run_pipeline<A, 2>(p, V, X, Phi, part, wide_final, st);
+    return run_pipeline<A, 1>(p, V, X, Phi, part, wide_final, st);
+}
+
+template <class A>
+void pipeline_geometry(ccdc_plan_t *p)
+{
+    Candidate best{0, 1, 1, true, 0};
+    consider<A, 4>(p, &best);
+    consider<A, 2>(p, &best);
+    consider<A, 1>(p, &best);
+    p->pipe_vec = best.vec;
+    p->pipe_waves = best.waves;
+    p->pipe_chunks = best.chunks;
+    p->pipe_even = best.even;
+}
+
+// The kernel's instantiations take minutes to compile in one piece: with CCDC_PIPELINE_PART set, this
+// file is one of five pieces, each with one algebra (and the first with the entry points).
+#ifdef CCDC_PIPELINE_PART
+#define CCDC_PIECE(A)                                                                                            \
+    template int pipeline_run<A>(const ccdc_plan_t *, const void *, void *, void *, void *, bool, hipStream_t); \
+    template void pipeline_geometry<A>(ccdc_plan_t *)
+#if CCDC_PIPELINE_PART == 0
+CCDC_PIECE(SumF32);
+#elif CCDC_PIPELINE_PART == 1
+CCDC_PIECE(XorU32);
+#elif CCDC_PIPELINE_PART == 2
+CCDC_PIECE(HybF32);
+#elif CCDC_PIPELINE_PART == 3
+CCDC_PIECE(HybBF16);
+#else
+CCDC_PIECE(HybF16);
+#endif
+#if CCDC_PIPELINE_PART == 0
+#define CCDC_ELSEWHERE(A)                                                                                               \
+    extern template int pipeline_run<A>(const ccdc_plan_t *, const void *, void *, void *, void *, bool, hipStream_t); \
+    extern template void pipeline_geometry<A>(ccdc_plan_t *)
+CCDC_ELSEWHERE(XorU32);
+CCDC_ELSEWHERE(HybF32);
+CCDC_ELSEWHERE(HybBF16);
+CCDC_ELSEWHERE(HybF16);
+#endif
+#endif
+#if !defined(CCDC_PIPELINE_PART) || CCDC_PIPELINE_PART == 0
+
 // ccdc_pipeline_fused: checks, pack width, dispatch on the algebra.  The partial
 // outputs of round chunks go to the plan's workspace, or, when the caller brings
 // a buffer (own_part, of own_part_bytes bytes), to that one; a launch whose
@@ -372,13 +619,8 @@ int pipeline_entry(const ccdc_plan_t *plan, const void *V, void *X, void *Phi, v
     if (plan->compression) return CCDC_ESTATE;       // nothing is coded in that scheme
     if (!plan->pipe_ok) return CCDC_ESIZE;
     if ((rc = pick_vec(plan, &vec_any, V, (const void *)X, (const void *)Phi)) != CCDC_OK) return rc;
-    // widest pack allowed by the plan's LDS budget (the running outputs take 4 bytes
-    // an element in every mode) and by the pointers
-    const size_t eb = (size_t)elem_bytes(plan->mode);
-    int vec = plan->pipe_vec;
-    while (vec > 1 && !(aligned(V, eb * vec) && aligned(X, eb * vec) && aligned(Phi, eb * vec))) vec /= 2;
     const bool wide_final = vec_any >= 4;            // Phi can be written four elements at a time
-    const int chunks = plan->pipe_chunks[vec == 4 ? 2 : (vec == 2 ? 1 : 0)];
+    const int chunks = plan->pipe_chunks;
     if (chunks < 1) return CCDC_ESTATE;
     void *part = plan->d_workspace;
     if (own_part) {
@@ -388,46 +630,33 @@ int pipeline_entry(const ccdc_plan_t *plan, const void *V, void *X, void *Phi, v
     }
     hipStream_t st = (hipStream_t)stream;
     WorkspaceOrder order(plan, st, !own_part && chunks > 1);
-    if (plan->mode == CCDC_F32_SUM) {
-        if (vec == 4) return run_pipeline<SumF32, 4>(plan, V, X, Phi, part, chunks, wide_final, st);
-        if (vec == 2) return run_pipeline<SumF32, 2>(plan, V, X, Phi, part, chunks, wide_final, st);
-        return run_pipeline<SumF32, 1>(plan, V, X, Phi, part, chunks, wide_final, st);
+    switch (plan->mode) {
+    case CCDC_F32_SUM: return pipeline_run<SumF32>(plan, V, X, Phi, part, wide_final, st);
+    case CCDC_F32_SUM_XOR: return pipeline_run<HybF32>(plan, V, X, Phi, part, wide_final, st);
+    case CCDC_BF16_SUM_XOR: return pipeline_run<HybBF16>(plan, V, X, Phi, part, wide_final, st);
+    case CCDC_F16_SUM_XOR: return pipeline_run<HybF16>(plan, V, X, Phi, part, wide_final, st);
+    default: return pipeline_run<XorU32>(plan, V, X, Phi, part, wide_final, st);
     }
-    if (plan->mode == CCDC_F32_SUM_XOR) {
-        if (vec == 4) return run_pipeline<HybF32, 4>(plan, V, X, Phi, part, chunks, wide_final, st);
-        if (vec == 2) return run_pipeline<HybF32, 2>(plan, V, X, Phi, part, chunks, wide_final, st);
-        return run_pipeline<HybF32, 1>(plan, V, X, Phi, part, chunks, wide_final, st);
-    }
-    if (plan->mode == CCDC_BF16_SUM_XOR) {
-        if (vec == 4) return run_pipeline<HybBF16, 4>(plan, V, X, Phi, part, chunks, wide_final, st);
-        if (vec == 2) return run_pipeline<HybBF16, 2>(plan, V, X, Phi, part, chunks, wide_final, st);
-        return run_pipeline<HybBF16, 1>(plan, V, X, Phi, part, chunks, wide_final, st);
-    }
-    if (plan->mode == CCDC_F16_SUM_XOR) {
-        if (vec == 4) return run_pipeline<HybF16, 4>(plan, V, X, Phi, part, chunks, wide_final, st);
-        if (vec == 2) return run_pipeline<HybF16, 2>(plan, V, X, Phi, part, chunks, wide_final, st);
-        return run_pipeline<HybF16, 1>(plan, V, X, Phi, part, chunks, wide_final, st);
-    }
-    if (vec == 4) return run_pipeline<XorU32, 4>(plan, V, X, Phi, part, chunks, wide_final, st);
-    if (vec == 2) return run_pipeline<XorU32, 2>(plan, V, X, Phi, part, chunks, wide_final, st);
-    return run_pipeline<XorU32, 1>(plan, V, X, Phi, part, chunks, wide_final, st);
 }
 
 void pipeline_prepare(ccdc_plan_t *p)
 {
-    p->pipe_chunks[0] = p->pipe_chunks[1] = p->pipe_chunks[2] = 1;
+    p->pipe_chunks = p->pipe_waves = p->pipe_vec = 1;
     if (!p->pipe_ok) return;
     switch (p->mode) {
-    case CCDC_F32_SUM: prepare<SumF32>(p); break;
-    case CCDC_F32_SUM_XOR: prepare<HybF32>(p); break;
-    case CCDC_BF16_SUM_XOR: prepare<HybBF16>(p); break;
-    case CCDC_F16_SUM_XOR: prepare<HybF16>(p); break;
-    default: prepare<XorU32>(p); break;
+    case CCDC_F32_SUM: pipeline_geometry<SumF32>(p); break;
+    case CCDC_F32_SUM_XOR: pipeline_geometry<HybF32>(p); break;
+    case CCDC_BF16_SUM_XOR: pipeline_geometry<HybBF16>(p); break;
+    case CCDC_F16_SUM_XOR: pipeline_geometry<HybF16>(p); break;
+    default: pipeline_geometry<XorU32>(p); break;
     }
 }
 
+#endif
+
 }  // namespace ccdc
 
+#if !defined(CCDC_PIPELINE_PART) || CCDC_PIPELINE_PART == 0
 extern "C" {
 
 int ccdc_pipeline_fused(const ccdc_plan_t *plan, const void *V, void *X, void *Phi, void *stream)
@@ -436,3 +665,4 @@ int ccdc_pipeline_fused(const ccdc_plan_t *plan, const void *V, void *X, void *P
 }
 
 }  // extern "C"
+#endif

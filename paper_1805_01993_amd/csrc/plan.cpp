@@ -338,6 +338,7 @@ int bind_compression(ccdc_plan_t *p, int64_t T, int mode)
         p->workspace_bytes = split > 1 ? (size_t)split * (size_t)p->Q * (size_t)T * 4 : 0;
         p->pipe_ok = false;
         p->loc_row.clear();
+        p->pipe_row.clear();
         p->bound = true;
     } catch (const std::bad_alloc &) {
         return CCDC_ENOMEM;
@@ -439,21 +440,12 @@ int bind_plan(ccdc_plan_t *p, int64_t T, int mode)
         // several wavefronts per compute unit is preferred.
         bool pipe_ok = !p->paper_jobs && r1 <= kPipeMaxR1 && W < (1LL << 29) &&   // 32-bit byte offsets in a packet
                        (int64_t)p->K * r * 4 * kPipeLanes <= kPipeMaxLds;
-        int pipe_vec = 1;
         int64_t pipe_cap = 1, local_rows = 0;
-        std::vector<int64_t> loc;
+        std::vector<int64_t> loc, pipe;
         if (pipe_ok) {
-            // Small inputs are bound by how many wavefronts share the rounds: four-element
-            // packs only while six of them fit on a compute unit.  Large inputs are bound
-            // by the memory system, which is served better by wide accesses from three
-            // wavefronts than by narrow ones from six (both measured).
-            const bool large = v_elems * 4.0 >= (double)kPipeLargeInput;
-            const int64_t lds4 = large ? kPipeGoodLdsHalf : kPipeGoodLds;
-            if (T % 4 == 0 && (int64_t)p->K * r * 16 * kPipeLanes <= lds4) pipe_vec = 4;
-            else if (T % 2 == 0 && (int64_t)p->K * r * 8 * kPipeLanes <= kPipeGoodLdsHalf) pipe_vec = 2;
             // chunk partials are written and read once more: keep them under ~1/4 of |V|
-            const double v = (double)p->N * p->Q * (double)T, kw = (double)p->K * (double)W;
-            pipe_cap = std::max<int64_t>(1, std::min<int64_t>({(int64_t)1024, p->nround, (int64_t)(0.125 * v / kw)}));
+            const double kw = (double)p->K * (double)W;
+            pipe_cap = std::max<int64_t>(1, std::min<int64_t>({(int64_t)1024, p->nround, (int64_t)((64 << 20) / (4 * kw))}));
             // rows of V each node adds from its own files: the V entries of its
             // reduce list (the same count for every node of a single job)
             for (int64_t i = cnt[0]; i < cnt[1]; i++) local_rows += !(rows_tab[i] & 1);
@@ -468,14 +460,16 @@ int bind_plan(ccdc_plan_t *p, int64_t T, int mode)
                     }
                 if (w != local_rows) pipe_ok = false;
             }
+            pipe.resize(src.size() + r1, 0);         // and one row that is read but not used
+            for (size_t i = 0; i < src.size(); i++) pipe[i] = (src[i] << 12) | p->round_member[i];
         }
 
         p->T = T; p->W = W; p->ell = ell; p->mode = mode;
         p->pipe_ok = pipe_ok;
-        p->pipe_vec = pipe_vec;
         p->pipe_max_chunks = (int)pipe_cap;
         p->pipe_local_rows = pipe_ok ? local_rows : 0;
         p->loc_row.swap(loc);
+        p->pipe_row.swap(pipe);
         p->packet_len.swap(plen);
         p->scheduled = per_round * p->nround;
         p->src_off.swap(src);

@@ -59,24 +59,24 @@ struct ccdc_plan_s {
     // whole path in one pass (single-job plans): the partial outputs of all K
     // nodes are accumulated in LDS, one private slot per (node, segment, lane)
     bool pipe_ok = false;               // shape supported by ccdc_pipeline_fused
-    int pipe_vec = 1;                   // widest pack the LDS budget allows
     int pipe_max_chunks = 1;            // upper bound on round chunks (sizes the workspace)
     int64_t pipe_local_rows = 0;        // rows of V every node adds from its own files
-    std::vector<int64_t> loc_row;       // [K][pipe_local_rows] element offsets in V
+    std::vector<int64_t> loc_row;       // [K][pipe_local_rows] (element offset in V << 12) | node
+    std::vector<int64_t> pipe_row;      // [nround][r+1] (src_off << 12) | member
 
     // device side, set by ccdc_plan_upload
     bool uploaded = false;
     int device = -1;
     int64_t *d_src_off = nullptr, *d_red_ptr = nullptr, *d_red_row = nullptr, *d_red_out = nullptr;
-    int64_t *d_loc_row = nullptr;
-    int32_t *d_member = nullptr;
+    int64_t *d_loc_row = nullptr, *d_pipe_row = nullptr;
     int32_t *d_row_files = nullptr;     // null when every packet adds m files
     int32_t *d_node_rows = nullptr;
     void *d_workspace = nullptr;
 
-    // round chunks of the one-pass kernel on this device for packs of 1, 2 and 4
-    // elements (index log2 of the width), from an occupancy query at upload time
-    int pipe_chunks[3] = {0, 0, 0};
+    // launch geometry of the one-pass kernel on this device, fixed at upload time: elements of a
+    // pack, wavefronts of a workgroup (they share a tile of columns) and chunks of rounds
+    int pipe_vec = 1, pipe_waves = 1, pipe_chunks = 0;
+    bool pipe_even = true;              // every wavefront takes a share of the rounds and one of the own rows
 
     // Order of the calls that use the workspace, across streams: the last such call
     // recorded ws_event (a hipEvent_t made by ccdc_plan_upload) on ws_stream.
@@ -94,21 +94,10 @@ int build_compression_plan(int K, int r, int Q, int N, ccdc_plan_t **out);
 int bind_plan(ccdc_plan_t *p, int64_t T, int mode);
 
 // Limits of the one-pass pipeline kernel.
-constexpr int kPipeLanes = 64;                 // one wavefront per workgroup
+constexpr int kPipeLanes = 64;                 // columns of a tile: one wavefront wide
+constexpr int kPipeMaxWaves = 8;               // wavefronts of a workgroup
 constexpr int kPipeMaxLds = 64 * 1024;         // bytes of LDS one workgroup may take
-// LDS a wavefront may take for its running outputs before a narrower pack is
-// preferred (measured): four-element packs only while >= 6 wavefronts fit on a
-// compute unit, unless the input is large, then down to 3 wavefronts like
-// two-element packs (narrow accesses cost more than the lost occupancy).
-#ifndef CCDC_PIPE_GOOD_LDS
-#define CCDC_PIPE_GOOD_LDS (26 * 1024)
-#endif
-#ifndef CCDC_PIPE_GOOD_LDS_HALF
-#define CCDC_PIPE_GOOD_LDS_HALF (50 * 1024)
-#endif
-constexpr int kPipeGoodLds = CCDC_PIPE_GOOD_LDS;
-constexpr int kPipeGoodLdsHalf = CCDC_PIPE_GOOD_LDS_HALF;
-constexpr int64_t kPipeLargeInput = 256LL << 20;   // bytes of V (at 4 bytes an element) from which an input counts as large
+constexpr int kCuLds = 160 * 1024;             // bytes of LDS of a compute unit
 constexpr int kPipeMaxR1 = 6;                  // r+1 the kernel is unrolled for
 
 // One-pass pipeline (pipeline.hip): fills p->pipe_chunks for the current device.

@@ -1,0 +1,92 @@
+"""ccdc_pipeline_fused where its launch geometry and its packs have edges: value lengths that no pack
+width divides, packets shorter than a pack or a segment, several files per batch with more and fewer
+steps than the pipeline is deep, one to many column tiles, pointers that are only element-aligned.
+X against ccdc_encode's bit for bit, Phi against eq. (1) from the oracle.  Needs a GPU."""
+from math import comb
+
+import numpy as np
+import pytest
+
+import oracle as O
+from workloads import generate_numpy
+
+pytestmark = pytest.mark.gpu
+
+# K, r, c, files per batch, T
+SHAPES = [
+    (4, 2, 1, 2, 1), (4, 3, 1, 1, 2), (7, 5, 1, 1, 3), (5, 4, 2, 3, 7),            # packets shorter than their segments
+    (5, 1, 1, 1, 255), (5, 1, 1, 7, 257), (6, 2, 1, 1, 513), (6, 2, 2, 10, 258),    # a tile and one pack more or less
+    (7, 3, 1, 1, 1543), (7, 3, 1, 2, 1030), (8, 4, 1, 1, 4097), (7, 5, 1, 3, 1287),
+    (12, 4, 1, 1, 66), (16, 5, 1, 1, 131), (16, 3, 1, 1, 1021), (24, 2, 1, 1, 70),  # few columns, many rounds
+    (5, 2, 1, 1, 70001), (4, 1, 1, 2, 200003),                                       # many tiles, one chunk
+]
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    torch.cuda.set_device(0)
+    return torch
+
+
+@pytest.mark.parametrize("mode", ["f32", "u32", "h32"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "-".join(map(str, s)))
+@pytest.mark.parametrize("shift", [0, 1], ids=["aligned", "element-aligned"])
+def test_pipeline_edges(torch, shape, mode, shift):
+    import paper_1805_01993_amd as L
+    K, r, c, m, T = shape
+    Q, N = c * K, m * comb(K, r)
+    plan = L.ccdc_plan(K, r, Q, N).bind(T, mode).upload()
+    sh = plan.shapes()
+    Vh = generate_numpy(1, N, Q, T, 5, "u32" if mode == "u32" else "f32")
+    host = torch.from_numpy(Vh.view(np.int32) if mode == "u32" else Vh)
+    poison = -1 if mode == "u32" else float("nan")
+
+    def buf(key):                       # the buffer starts `shift` elements past an aligned address, poison around it
+        n = int(np.prod(sh[key]))
+        t = torch.full((n + 2 * shift + 8,), poison, dtype=host.dtype, device="cuda")
+        return t, t[shift:shift + n].view(sh[key])
+
+    (Vall, V), (Xall, X), (Pall, Phi), (_, Vbar), (_, want_X) = map(buf, ("V", "X", "Phi", "Vbar", "X"))
+    V.copy_(host.view(sh["V"]))
+    plan.combine(V, Vbar)
+    plan.encode(Vbar, want_X)
+    plan.pipeline_fused(V, X, Phi)
+    torch.cuda.synchronize()
+    assert torch.equal(X.view(torch.int32), want_X.view(torch.int32)), "X differs from ccdc_encode's"
+    want = O.direct(O.build_plan(K, r, Q, N), T, Vh).reshape(-1)
+    got = Phi.cpu().numpy().reshape(-1)
+    if mode == "u32":
+        assert np.array_equal(got.view(np.uint32), want)
+    else:
+        assert np.abs(got.astype(np.float64) - want).max() <= 1e-5 * np.abs(want).max()
+    # nothing outside the outputs was written
+    for whole, inner in ((Xall, X), (Pall, Phi)):
+        edge = torch.cat([whole[:shift], whole[shift + inner.numel():]])
+        assert bool((edge == -1).all() if mode == "u32" else torch.isnan(edge).all())
+    plan.close()
+
+
+@pytest.mark.parametrize("mode", ["bf16", "f16"])
+@pytest.mark.parametrize("shape", [s for s in SHAPES if s[4] > 1], ids=lambda s: "-".join(map(str, s)))
+def test_pipeline_edges_16bit(torch, shape, mode):
+    """Buffers at odd element offsets (2-byte alignment); the outputs are small whole numbers, exact in every order."""
+    import paper_1805_01993_amd as L
+    K, r, c, m, T = shape
+    Q, N = c * K, m * comb(K, r)
+    plan = L.ccdc_plan(K, r, Q, N).bind(T, mode).upload()
+    sh = plan.shapes()
+    dt = torch.bfloat16 if mode == "bf16" else torch.float16
+    new = lambda key: torch.full((int(np.prod(sh[key])) + 1,), float("nan"), dtype=dt, device="cuda")[1:].view(sh[key])
+    V, X, Phi, Vbar, want_X = map(new, ("V", "X", "Phi", "Vbar", "X"))
+    g = torch.Generator(device="cuda").manual_seed(9)
+    V.copy_((torch.rand(sh["V"], device="cuda", generator=g) < 8.0 / N).to(dt))      # sums stay far below 2^8
+    plan.combine(V, Vbar)
+    plan.encode(Vbar, want_X)
+    plan.pipeline_fused(V, X, Phi)
+    torch.cuda.synchronize()
+    assert torch.equal(X.view(torch.int16), want_X.view(torch.int16)), "X differs from ccdc_encode's"
+    assert torch.equal(Phi.double(), V.double().sum(1))
+    plan.close()
