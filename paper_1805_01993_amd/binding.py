@@ -106,14 +106,31 @@ def _dev_ptr(t, name, elem_bytes=4):
         raise ValueError(f"{name}: need a contiguous device tensor")
     if t.element_size() != elem_bytes:
         raise ValueError(f"{name}: need {elem_bytes}-byte elements, got {t.dtype}")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+_current_stream = None
+
+
+def _make_current_stream():
+    """A function that returns the handle of torch's current stream on the current device.  The raw
+    handle where torch gives it: a small call is bound by what the host does, and the stream object
+    that torch.cuda.current_stream() makes costs more than the rest of the marshalling (3.2 us of the
+    8.1 us of a pipeline_fused call; 0.3 of 5.5 this way).  Callers hold device tensors: CUDA is up."""
+    import torch
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw is None or device is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    return lambda: raw(device())
 
 
 def _stream_ptr(stream):
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+        global _current_stream
+        if _current_stream is None:
+            _current_stream = _make_current_stream()
+        return _current_stream()
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 class Plan:
@@ -250,7 +267,8 @@ class Plan:
         return self._shapes
 
     def _need(self, t, key, name):
-        self.shapes()
+        if self._shapes is None:
+            self.shapes()
         want = self._numel[key]
         if t.numel() != want:
             raise ValueError(f"{name}: need {want} elements, got {t.numel()}")
