@@ -3,6 +3,8 @@
 // Run for every node it is the emulation in which no result is shared between
 // nodes: each of the r nodes that store a batch pre-combines it for itself,
 // as a real cluster would.
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace {
@@ -107,23 +109,182 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
     else reinterpret_cast<P *>(out + red_out[o])[e] = O::narrow(acc);
 }
 
-// Adds the chunk sums of the selected output blocks in chunk order.
+// The same two, with a wavefront on 64 consecutive packs of ONE segment: sender, receiver, batch
+// rows and segment are then the same for all lanes, so the index tables are read with scalar
+// loads, nothing is divided per lane and the packs of several rows are asked for before the first
+// is used.  The lane-packed kernels above spend more time on addresses and on waiting for one row
+// after the other than on data.  A pass of both calls, lane-packed -> this: 16 nodes r = 3 T = 4096
+// h32 107 -> 98 us (most of it cache traffic: every V pack is read by up to r nodes), 16 nodes r = 4
+// T = 512 f32 113 -> 57, 12 nodes r = 3 T = 3000 bf16 with two files a batch 60 -> 38, 20 nodes r = 2
+// T = 352 h32 64 -> 18 (there the chunk sums, added by one thread per output before, were most).
+// The lane-packed kernels stay for segments that would leave over a quarter of the lanes idle.
+constexpr int kWave = 64;
+constexpr int kWaves = kBlock / kWave;
+
+// Segments fill the wavefronts of a tile row to at least 3/4.
+inline bool fills_wavefronts(uint32_t Lv)
+{
+    const uint64_t lanes = (uint64_t)cdiv(Lv, kWave) * kWave;
+    return (uint64_t)Lv * 4 >= lanes * 3;
+}
+
+template <class A, int VEC, int R1, bool MULTI>
+__global__ __launch_bounds__(kBlock) void k_node_encode_wave(const typename A::elem *__restrict__ V,
+                                                             typename A::elem *__restrict__ X,
+                                                             const int64_t *__restrict__ src_off,
+                                                             const int32_t *__restrict__ rows, uint32_t Lv,
+                                                             uint32_t Wv, int m, int64_t file_stride, uint32_t tiles,
+                                                             uint32_t units)
+{
+    using O = Ops<A, VEC>;
+    using P = typename O::P;
+    const uint32_t unit = blockIdx.x * kWaves + wave_uniform(threadIdx.x / kWave);
+    if (unit >= units) return;
+    const uint32_t j = unit / tiles, x = (unit - j * tiles) * kWave + threadIdx.x % kWave;
+    if (x >= Lv) return;
+    const uint32_t i = rows ? (uint32_t)rows[j] : j;
+    const uint32_t u = i / R1;
+    const int a = (int)(i - u * R1);
+    const int64_t *src = src_off + (size_t)u * R1;
+    P part[R1 - 1];
+#pragma unroll
+    for (int k = 0; k < R1 - 1; k++) {
+        const int b = k + (k >= a ? 1 : 0);
+        const uint32_t pos = segment_rank(a, b) * Lv + x;
+        part[k] = O::zero();
+        if (pos < Wv) part[k] = combined_pack<A, VEC>(V, src[b], pos, MULTI ? m : 1, file_stride);
+    }
+    P coded = O::zero();
+#pragma unroll
+    for (int k = 0; k < R1 - 1; k++) coded = O::code(coded, part[k]);
+    store_stream(reinterpret_cast<P *>(X) + (size_t)i * Lv + x, coded);
+}
+
+template <class A, int VEC, int R1, bool MULTI>
+__global__ __launch_bounds__(kBlock) void k_node_decode_reduce_wave(
+    const typename A::elem *__restrict__ V, const typename A::elem *__restrict__ X, typename A::elem *__restrict__ out,
+    typename A::acc *__restrict__ part, const int64_t *__restrict__ red_ptr, const int64_t *__restrict__ red_row,
+    const int64_t *__restrict__ red_out, const int64_t *__restrict__ src_off, uint32_t Lv, uint32_t Wv,
+    double per_row, int m, int64_t file_stride, uint32_t tiles, int split, int64_t chunk_stride, uint32_t o_first,
+    uint32_t o_step, uint32_t units)
+{
+    using O = Ops<A, VEC>;
+    using P = typename O::P;
+    constexpr int r = R1 - 1;
+    constexpr int AHEAD = MULTI ? 1 : (R1 <= 3 ? 4 : 2);     // received packets asked for together
+    const uint32_t unit = blockIdx.x * kWaves + wave_uniform(threadIdx.x / kWave);
+    if (unit >= units) return;
+    const uint32_t seg = unit / tiles, oc = seg / r;         // unit = ((output block, chunk), segment, tile)
+    const int rho = (int)(seg - oc * r);
+    const uint32_t x = (unit - seg * tiles) * kWave + threadIdx.x % kWave;
+    const uint32_t oi = oc / split;
+    const int s = (int)(oc - oi * split);
+    const uint32_t o = o_first + oi * o_step;
+    const uint32_t e = rho * Lv + x;
+    if (x >= Lv || e >= Wv) return;
+    const int64_t first = red_ptr[o], n = red_ptr[o + 1] - first;
+    const int64_t lo = first + n * s / split, hi = first + n * (s + 1) / split;
+    typename O::Q acc = O::azero();
+    int64_t i = lo;
+    // the files the node stores come first in the list
+    auto own = [&](int64_t row) { return load_stream<P>(reinterpret_cast<const P *>(V + (row >> 1)) + e); };
+    for (; i + 4 <= hi; i += 4) {
+        const int64_t row[4] = {red_row[i], red_row[i + 1], red_row[i + 2], red_row[i + 3]};
+        if (row[3] & 1) break;
+        const P v[4] = {own(row[0]), own(row[1]), own(row[2]), own(row[3])};
+#pragma unroll
+        for (int t = 0; t < 4; t++) acc = O::accum(acc, v[t]);
+    }
+    for (; i < hi && !(red_row[i] & 1); i++) acc = O::accum(acc, own(red_row[i]));
+    struct Packet {
+        P coded, side[r > 1 ? r - 1 : 1];
+    };
+    auto load = [&](int64_t at, Packet &k) {
+        // the entry is the packet's first element: packet number = element / W, exact in fp64
+        const uint32_t pk = wave_uniform((uint32_t)((double)(red_row[at] >> 1) * per_row + 0.5));
+        const uint32_t u = pk / R1;
+        const int b = (int)(pk - u * R1);
+        const int a = rho < b ? rho : rho + 1;
+        const int low = a < b ? a : b, high = a < b ? b : a;
+        const int64_t *src = src_off + (size_t)u * R1;
+        k.coded = load_stream<P>(reinterpret_cast<const P *>(X) + ((size_t)u * R1 + a) * Lv + x);
+#pragma unroll
+        for (int q = 0; q < r - 1; q++) {
+            int b2 = q + (q >= low ? 1 : 0);                 // the q-th member that is neither a nor b
+            b2 += b2 >= high ? 1 : 0;
+            const uint32_t pos = segment_rank(a, b2) * Lv + x;
+            k.side[q] = O::zero();
+            if (pos < Wv) k.side[q] = combined_pack<A, VEC>(V, src[b2], pos, MULTI ? m : 1, file_stride);
+        }
+    };
+    auto use = [&](const Packet &k) {
+        P d = k.coded;
+#pragma unroll
+        for (int q = 0; q < r - 1; q++) d = O::uncode(d, k.side[q]);
+        acc = O::accum(acc, d);
+    };
+    for (; i + AHEAD <= hi; i += AHEAD) {
+        Packet k[AHEAD];
+#pragma unroll
+        for (int t = 0; t < AHEAD; t++) load(i + t, k[t]);
+#pragma unroll
+        for (int t = 0; t < AHEAD; t++) use(k[t]);
+    }
+    for (; i < hi; i++) {
+        Packet k;
+        load(i, k);
+        use(k);
+    }
+    if (split > 1) reinterpret_cast<typename O::Q *>(part + (int64_t)s * chunk_stride + red_out[o])[e] = acc;
+    else reinterpret_cast<P *>(out + red_out[o])[e] = O::narrow(acc);
+}
+
+// Adds the chunk sums of one node's output blocks, in k_reduce_final's order for the same G, so
+// that a node's outputs do not depend on whether it was run alone.
 template <class A, int VEC>
 __global__ __launch_bounds__(kBlock) void k_node_final(const typename A::acc *__restrict__ part,
                                                        typename A::elem *__restrict__ Phi,
                                                        const int64_t *__restrict__ red_out, uint32_t Wv, int split,
                                                        int64_t chunk_stride, uint32_t o_first, uint32_t o_step,
-                                                       uint32_t items)
+                                                       uint32_t items, int G)
 {
     using O = Ops<A, VEC>;
-    const uint32_t idx = blockIdx.x * kBlock + threadIdx.x;
-    if (idx >= items) return;
+    using Q = typename O::Q;
+    __shared__ Q sums[kBlock];
+    const int per_block = kBlock / G;
+    const int at = threadIdx.x % per_block, g = threadIdx.x / per_block;
+    const uint32_t idx = blockIdx.x * per_block + at;
     const uint32_t oi = idx / Wv, e = idx - oi * Wv;
-    const int64_t base = red_out[o_first + oi * o_step];
-    typename O::Q acc = O::azero();
-    for (int s = 0; s < split; s++)
-        acc = O::add(acc, reinterpret_cast<const typename O::Q *>(part + (int64_t)s * chunk_stride + base)[e]);
-    reinterpret_cast<typename O::P *>(Phi + base)[e] = O::narrow(acc);
+    const int64_t base = idx < items ? red_out[o_first + oi * o_step] : 0;
+    Q acc = O::azero();
+    if (idx < items) {
+#pragma unroll 4
+        for (int s = g; s < split; s += G)
+            acc = O::add(acc, reinterpret_cast<const Q *>(part + (int64_t)s * chunk_stride + base)[e]);
+    }
+    sums[threadIdx.x] = acc;
+    __syncthreads();
+    if (g == 0 && idx < items) {
+        for (int k = 1; k < G; k++) acc = O::add(acc, sums[k * per_block + at]);
+        reinterpret_cast<typename O::P *>(Phi + base)[e] = O::narrow(acc);
+    }
+}
+
+// Calls launch(r+1, several files a batch) with both as compile-time constants, r <= 5.
+template <class F>
+void by_shape(const ccdc_plan_t *p, F launch)
+{
+    auto files = [&](auto r1) {
+        if (p->m > 1) launch(r1, std::true_type());
+        else launch(r1, std::false_type());
+    };
+    switch (p->r) {
+    case 1: files(std::integral_constant<int, 2>()); break;
+    case 2: files(std::integral_constant<int, 3>()); break;
+    case 3: files(std::integral_constant<int, 4>()); break;
+    case 4: files(std::integral_constant<int, 5>()); break;
+    default: files(std::integral_constant<int, 6>()); break;
+    }
 }
 
 template <class A, int VEC>
@@ -136,6 +297,18 @@ int run_node_encode(const ccdc_plan_t *p, int node, const void *V, void *X, hipS
     if (items == 0) return CCDC_OK;
     if (!fits_launch(items)) return CCDC_ESIZE;
     const int32_t *list = node < 0 ? nullptr : p->d_node_rows + (size_t)node * p->rows_per_node;
+    const uint32_t wave_tiles = cdiv(Lv, kWave);
+    const uint64_t units = (uint64_t)rows * wave_tiles;
+    if (p->r <= 5 && fills_wavefronts(Lv) && fits_launch(units + kWaves)) {
+        auto launch = [&](auto r1, auto multi) {
+            constexpr int R1 = decltype(r1)::value;
+            constexpr bool MULTI = decltype(multi)::value;
+            k_node_encode_wave<A, VEC, R1, MULTI><<<cdiv(units, kWaves), kBlock, 0, st>>>(
+                (const E *)V, (E *)X, p->d_src_off, list, Lv, Wv, p->m, (int64_t)p->Q * p->T, wave_tiles, (uint32_t)units);
+        };
+        by_shape(p, launch);
+        return launched();
+    }
     k_node_encode<A, VEC><<<cdiv(items, kBlock), kBlock, 0, st>>>((const E *)V, (E *)X, p->d_src_off, list, p->r + 1,
                                                                    Lv, Wv, p->m, (int64_t)p->Q * p->T,
                                                                    (uint32_t)items);
@@ -154,16 +327,37 @@ int run_node_decode_reduce(const ccdc_plan_t *p, int node, const void *V, const 
     const uint32_t o_first = node < 0 ? 0u : (uint32_t)node, o_step = node < 0 ? 1u : (uint32_t)p->K;
     const int64_t chunk_stride = (int64_t)p->J * p->Q * p->T;
     const uint64_t blocks = (uint64_t)count * split * tiles;
-    if (!fits_launch(blocks) || !fits_launch((uint64_t)count * Wv)) return CCDC_ESIZE;
+    if (!fits_launch(blocks) || !fits_launch((uint64_t)chunk_stride / VEC)) return CCDC_ESIZE;
     WorkspaceOrder order(p, st, split > 1);
-    k_node_decode_reduce<A, VEC><<<(uint32_t)blocks, kBlock, 0, st>>>(
-        (const E *)V, (const E *)X, (E *)Phi, (Acc *)p->d_workspace, p->d_red_ptr, p->d_red_row, p->d_red_out,
-        p->d_src_off, p->r + 1, Lv, Wv, p->W, p->m, (int64_t)p->Q * p->T, tiles, split, chunk_stride, o_first, o_step);
+    const uint32_t wave_tiles = cdiv(Lv, kWave);
+    const uint64_t units = (uint64_t)count * split * p->r * wave_tiles;
+    if (p->r <= 5 && fills_wavefronts(Lv) && fits_launch(units + kWaves)) {
+        auto launch = [&](auto r1, auto multi) {
+            constexpr int R1 = decltype(r1)::value;
+            constexpr bool MULTI = decltype(multi)::value;
+            k_node_decode_reduce_wave<A, VEC, R1, MULTI><<<cdiv(units, kWaves), kBlock, 0, st>>>(
+                (const E *)V, (const E *)X, (E *)Phi, (Acc *)p->d_workspace, p->d_red_ptr, p->d_red_row, p->d_red_out,
+                p->d_src_off, Lv, Wv, 1.0 / (double)p->W, p->m, (int64_t)p->Q * p->T, wave_tiles, split, chunk_stride,
+                o_first, o_step, (uint32_t)units);
+        };
+        by_shape(p, launch);
+    } else {
+        k_node_decode_reduce<A, VEC><<<(uint32_t)blocks, kBlock, 0, st>>>(
+            (const E *)V, (const E *)X, (E *)Phi, (Acc *)p->d_workspace, p->d_red_ptr, p->d_red_row, p->d_red_out,
+            p->d_src_off, p->r + 1, Lv, Wv, p->W, p->m, (int64_t)p->Q * p->T, tiles, split, chunk_stride, o_first, o_step);
+    }
     int rc = launched();
     if (rc != CCDC_OK || split == 1) return rc;
     const uint64_t items = (uint64_t)count * Wv;
-    k_node_final<A, VEC><<<cdiv(items, kBlock), kBlock, 0, st>>>((const Acc *)p->d_workspace, (E *)Phi, p->d_red_out, Wv,
-                                                                  split, chunk_stride, o_first, o_step, (uint32_t)items);
+    const uint64_t all = (uint64_t)chunk_stride / VEC;
+    const int G = reduce_final_groups((int64_t)all, split);
+    if (node < 0)                                            // every block: Phi from end to end, as in ccdc_reduce
+        k_reduce_final<A, VEC><<<cdiv(all, kBlock / G), kBlock, 0, st>>>((const Acc *)p->d_workspace, (E *)Phi, split,
+                                                                          chunk_stride / VEC, (uint32_t)all, G);
+    else
+        k_node_final<A, VEC><<<cdiv(items, kBlock / G), kBlock, 0, st>>>((const Acc *)p->d_workspace, (E *)Phi, p->d_red_out,
+                                                                          Wv, split, chunk_stride, o_first, o_step,
+                                                                          (uint32_t)items, G);
     return launched();
 }
 
