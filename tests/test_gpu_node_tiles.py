@@ -36,7 +36,7 @@ def test_node_calls_at_tile_edges(torch, K, r, m, packs, mode):
     plan.reduce(V, D, Phi)
     plan.node_encode(-1, V, Xn)
     plan.node_decode_reduce(-1, V, Xn, Phin)
-    assert torch.equal(Xn, X)
+    assert torch.equal(Xn.view(torch.int16), X.view(torch.int16))       # packets are bit patterns
     assert torch.equal(Phin, Phi)
     one = new("Phi")
     k = K - 1
