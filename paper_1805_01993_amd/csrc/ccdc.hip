@@ -11,29 +11,6 @@
 namespace {
 using namespace ccdc;
 
-// The packet's pack from its first file's pack and the packs of the other files, ascending.  Three are
-// asked for before the first is added, in short batches (a 12-node plan with two files a batch, f16:
-// 15 -> 14 us; long ones keep enough loads going by themselves: 77 files, 500 us plain, 504 in threes).
-template <class A, int VEC>
-__device__ __forceinline__ typename Ops<A, VEC>::P add_files(typename Ops<A, VEC>::P first,
-                                                             const typename A::elem *__restrict__ src, int files,
-                                                             int64_t file_stride)
-{
-    using O = Ops<A, VEC>;
-    using P = typename O::P;
-    typename O::Q acc = O::widen(first);
-    int f = 1;
-    for (; files <= 16 && f + 3 <= files; f += 3) {
-        P p[3];
-#pragma unroll
-        for (int k = 0; k < 3; k++) p[k] = load_stream<P>(src + (f + k) * file_stride);
-#pragma unroll
-        for (int k = 0; k < 3; k++) acc = O::accum(acc, p[k]);
-    }
-    for (; f < files; f++) acc = O::accum(acc, load_stream<P>(src + f * file_stride));
-    return O::narrow(acc);
-}
-
 // ------------------------------------------------------------------ combine
 // Sec. IV-B pre-combining.  One work item = one pack of one packet Vbar[u][b]:
 // it adds the same pack of the files of the served batch (m of them, or
@@ -57,7 +34,9 @@ __global__ __launch_bounds__(kBlock) void k_combine(const typename A::elem *__re
         reinterpret_cast<P *>(Vbar)[idx] = first;
         return;
     }
-    reinterpret_cast<P *>(Vbar)[idx] = add_files<A, VEC>(first, src, files, file_stride);
+    typename O::Q acc = O::widen(first);
+    for (int f = 1; f < files; f++) acc = O::accum(acc, load_stream<P>(src + f * file_stride));
+    reinterpret_cast<P *>(Vbar)[idx] = O::narrow(acc);
 }
 
 // Pre-combining for short packets and long batches (few packs per packet, many
@@ -229,7 +208,9 @@ __global__ __launch_bounds__(kBlock) void k_shuffle_fused(const typename A::elem
         const typename A::elem *s = V + src[b] + (int64_t)pos * VEC;
         const P first = load_stream<P>(s);
         if (m == 1) return first;                     // a one-file batch is sent as it is
-        return add_files<A, VEC>(first, s, m, file_stride);
+        typename O::Q acc = O::widen(first);
+        for (int f = 1; f < m; f++) acc = O::accum(acc, load_stream<P>(s + f * file_stride));
+        return O::narrow(acc);
     };
 
     P *Drows = reinterpret_cast<P *>(D) + (size_t)u * r1 * Wv;
