@@ -481,8 +481,10 @@ void consider(const ccdc_plan_t *p, Candidate *best)
     const double tiles = pipeline_tiles<VEC>(p), bytes =
         ((double)p->N * p->Q * p->T + (double)p->nrows * p->ell + (double)p->Q * p->T) * elem;
     const int depth = p->m > 1 ? pipeline_depth<A, VEC, true>(p->r) : pipeline_depth<A, VEC, false>(p->r);
-    const double flight = depth * r1 * p->r * ccdc::kPipeLanes * VEC * elem;       // bytes a wavefront has on the way
+    const double used = (double)(p->ell / VEC) / (cdiv(p->ell / VEC, ccdc::kPipeLanes) * ccdc::kPipeLanes);    // share of lanes with work
+    const double flight = depth * r1 * p->r * ccdc::kPipeLanes * VEC * elem * used;                // bytes a wavefront has on the way
     double peak = VEC * elem >= 16 ? 6.5e6 : VEC * elem == 8 ? 5.3e6 : VEC * elem == 4 ? 4.2e6 : 3.2e6;   // B/us
+    peak *= std::pow(used, 0.3);
     if (p->T * elem % 8) peak *= 1 - 0.4 * std::min(1.0, 8.0 / (VEC * elem));    // rows start anywhere: more lines an access
     for (int waves = 1; waves <= ccdc::kPipeMaxWaves && waves * lds <= (size_t)ccdc::kPipeMaxLds; waves++) {
         const int by_lds = (int)(ccdc::kCuLds / (waves * lds)), by_regs = limit / waves;
