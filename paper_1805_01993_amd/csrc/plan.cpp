@@ -436,14 +436,15 @@ int bind_plan(ccdc_plan_t *p, int64_t T, int mode)
         if (items * split > kMaxItems) return CCDC_ESIZE;
 
         // One-pass pipeline: single job, unrolled r, accumulators of K nodes x r
-        // segments per lane must fit in LDS.  The widest pack that still leaves
-        // several wavefronts per compute unit is preferred.
+        // segments per lane must fit in LDS.  Pack width, wavefronts and chunks are
+        // chosen at upload, when the device is known.
         bool pipe_ok = !p->paper_jobs && r1 <= kPipeMaxR1 && W < (1LL << 29) &&   // 32-bit byte offsets in a packet
                        (int64_t)p->K * r * 4 * kPipeLanes <= kPipeMaxLds;
         int64_t pipe_cap = 1, local_rows = 0;
         std::vector<int64_t> loc, pipe;
         if (pipe_ok) {
-            // chunk partials are written and read once more: keep them under ~1/4 of |V|
+            // The chunks' outputs are kept under 64 MiB: what ccdc_pipeline_fused_noalloc's array
+            // holds, and no workgroups are short of work at outputs large enough to feel it.
             const double kw = (double)p->K * (double)W;
             pipe_cap = std::max<int64_t>(1, std::min<int64_t>({(int64_t)1024, p->nround, (int64_t)((64 << 20) / (4 * kw))}));
             // rows of V each node adds from its own files: the V entries of its

@@ -100,7 +100,7 @@ constexpr int kPipeMaxLds = 64 * 1024;         // bytes of LDS one workgroup may
 constexpr int kCuLds = 160 * 1024;             // bytes of LDS of a compute unit
 constexpr int kPipeMaxR1 = 6;                  // r+1 the kernel is unrolled for
 
-// One-pass pipeline (pipeline.hip): fills p->pipe_chunks for the current device.
+// One-pass pipeline (pipeline.hip): fixes the launch geometry (pipe_vec .. pipe_even) for the current device.
 void pipeline_prepare(ccdc_plan_t *p);
 // Body of ccdc_pipeline_fused.  own_part = null: partial outputs of round chunks go
 // to the plan's workspace; else to the caller's buffer of own_part_bytes bytes
