@@ -382,11 +382,13 @@ int run_decode(const ccdc_plan_t *p, const void *X, const void *Vbar, void *D, h
     using E = typename A::elem;
     const uint32_t Wv = (uint32_t)(p->W / VEC), Lv = (uint32_t)(p->ell / VEC);
     const uint64_t items = (uint64_t)p->nround * (p->r + 1) * Wv;
-    if (!fits_launch(items) || !fits_launch((uint64_t)p->nround * (p->r + 1) * Lv)) return CCDC_ESIZE;
-    const uint32_t by_sender = (uint32_t)((uint64_t)p->nround * (p->r + 1) * Lv);
-    const uint32_t blocks = cdiv(by_sender, kBlock);
+    if (!fits_launch(items)) return CCDC_ESIZE;
+    // By sender where the packs of the padded segments can be numbered too (packets of fewer than four
+    // elements have more of those than of their own); k_decode takes whatever the packets' packs allow.
+    const uint64_t packs = (uint64_t)p->nround * (p->r + 1) * Lv;
+    const uint32_t by_sender = (uint32_t)packs, blocks = cdiv(packs, kBlock);
     const E *x = (const E *)X, *v = (const E *)Vbar;
-    switch (p->r + 1) {
+    switch (fits_launch(packs) ? p->r + 1 : 0) {
     case 2: k_decode_sender<A, VEC, 2><<<blocks, kBlock, 0, st>>>(x, v, (E *)D, Lv, Wv, by_sender); break;
     case 3: k_decode_sender<A, VEC, 3><<<blocks, kBlock, 0, st>>>(x, v, (E *)D, Lv, Wv, by_sender); break;
     case 4: k_decode_sender<A, VEC, 4><<<blocks, kBlock, 0, st>>>(x, v, (E *)D, Lv, Wv, by_sender); break;

@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "ccdc.h"
+#include "plan.hpp"
 
 #define CHECK(call)                                                                              \
     do {                                                                                         \
@@ -65,6 +66,22 @@ static int limits()
     // a value length past what any pack width indexes is refused when the plan is bound
     bad += ccdc_plan_bind(p, (int64_t)1 << 38, CCDC_U32_XOR) != CCDC_ESIZE;
     ccdc_plan_destroy(p);
+
+    // Launches that are only checked and counted.  Counts that would need tables of gigabytes are
+    // written into the plan: no kernel runs.
+    shim::dry_run = true;
+    {   // packets of one element, padded segments of four: the packets' packs can be numbered, the segments' cannot
+        CHECK(ccdc_plan(4, 3, 4, 4, &p));
+        CHECK(ccdc_plan_bind(p, 1, CCDC_U32_XOR));
+        CHECK(ccdc_plan_upload(p));
+        const int64_t rounds = p->nround;
+        p->nround = 150000000;
+        const long at = shim::launches.load();
+        bad += ccdc_decode(p, a, b, c, nullptr) != CCDC_OK || shim::launches.load() != at + 1;
+        bad += ccdc_encode(p, b, a, nullptr) != CCDC_ESIZE;
+        p->nround = rounds;
+        ccdc_plan_destroy(p);
+    }
     std::printf(bad ? "limits FAILED (%d)\n" : "limits ok\n", bad);
     return bad ? 1 : 0;
 }

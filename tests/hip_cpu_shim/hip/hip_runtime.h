@@ -55,6 +55,7 @@ extern int compute_units;                               // what the device attri
 extern int blocks_per_cu;                               // what the occupancy query answers
 extern size_t max_dynamic_lds;                          // launches asking for more are refused
 extern std::atomic<long> launches;
+extern bool dry_run;                                     // launches are checked and counted, not run
 void barrier_wait();                                    // __syncthreads()
 void *block_static(size_t bytes);                       // the running workgroup's static __shared__ array
 uint32_t shuffle_xor(uint32_t v, int mask);             // all lanes of the workgroup call it together

@@ -13,6 +13,7 @@ int compute_units = 8;
 int blocks_per_cu = 4;
 size_t max_dynamic_lds = 64 * 1024;
 std::atomic<long> launches{0};
+bool dry_run = false;
 
 namespace {
 // State of one workgroup of the running launch.  The lanes (one OS thread each, kept for the
@@ -85,11 +86,13 @@ void *block_static(size_t bytes)
 void launch(dim3 grid, dim3 block, size_t lds, const std::function<void()> &body)
 {
     launches++;
-    if (grid.x == 0 || block.x == 0 || block.x > 1024 || lds > max_dynamic_lds) {
+    // a launch of 2^32 work items or more is refused, as the HIP runtime does
+    if (grid.x == 0 || block.x == 0 || block.x > 1024 || lds > max_dynamic_lds || ((uint64_t)grid.x * block.x) >> 32) {
         std::fprintf(stderr, "shim: launch refused (grid %u, block %u, lds %zu)\n", grid.x, block.x, lds);
         last_error = hipErrorInvalidValue;
         return;
     }
+    if (dry_run) return;
     const int n = (int)block.x;
     cur.blocks.reset(new Block[grid.x]);
     cur.lanes = n;
