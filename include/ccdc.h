@@ -91,7 +91,7 @@ enum ccdc_query {
     CCDC_Q_CLOSED_FORM_NUM,  /* R*(r+1)*c*T  (Sec. IV-B: r+1 packets of c*T/r per round) */
     CCDC_Q_CLOSED_FORM_DEN,  /* r */
     CCDC_Q_V_ELEMS, CCDC_Q_VBAR_ELEMS, CCDC_Q_X_ELEMS, CCDC_Q_D_ELEMS, CCDC_Q_PHI_ELEMS,
-    CCDC_Q_WORKSPACE_BYTES,  /* device bytes ccdc_plan_upload allocates besides tables */
+    CCDC_Q_WORKSPACE_BYTES,  /* device bytes ccdc_plan_upload allocates besides tables; before it: the most it may */
     CCDC_Q_PACKET_LEN = 64,  /* int64_t[r+1]      true packet length of sender a        */
     CCDC_Q_BATCH_JOB,        /* int32_t[NBATCH]    job of the batch                     */
     CCDC_Q_BATCH_FILE0,      /* int32_t[NBATCH]    first file (index inside its job)    */

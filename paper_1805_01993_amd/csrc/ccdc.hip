@@ -4,6 +4,7 @@
 // work item moves one pack (16 bytes when the value length allows it, else 8
 // bytes or one element) per operand, consecutive lanes touch consecutive packs of the same
 // row, and there is no reuse across work items, so no LDS tiling and no MFMA.
+#include <algorithm>
 #include <new>
 
 #include "common.hpp"
@@ -497,6 +498,10 @@ int ccdc_plan_upload(ccdc_plan_t *plan)
         return CCDC_EHIP;
     }
     plan->device = dev;
+    ccdc::pipeline_prepare(plan);                 // launch geometry of the one-pass kernel on this device
+    plan->workspace_bytes = plan->red_workspace_bytes;
+    if (plan->pipe_chunks > 1)
+        plan->workspace_bytes = std::max(plan->workspace_bytes, (size_t)plan->pipe_chunks * (size_t)plan->K * (size_t)plan->W * 4);
     int rc = to_device(plan->src_off, &plan->d_src_off);
     if (rc == CCDC_OK) rc = to_device(plan->red_ptr, &plan->d_red_ptr);
     if (rc == CCDC_OK) rc = to_device(plan->red_row, &plan->d_red_row);
@@ -523,7 +528,6 @@ int ccdc_plan_upload(ccdc_plan_t *plan)
         release_device(plan);
         return rc;
     }
-    ccdc::pipeline_prepare(plan);                 // launch geometry of the one-pass kernel on this device
     (void)ccdc::scratch_address(nullptr);         // set-up for ccdc_pipeline_fused_noalloc, which reports a failure itself
     plan->uploaded = true;
     return CCDC_OK;

@@ -335,7 +335,7 @@ int bind_compression(ccdc_plan_t *p, int64_t T, int mode)
         p->red_out.swap(outs);
         p->nout = nout;
         p->red_split = (int)split;
-        p->workspace_bytes = split > 1 ? (size_t)split * (size_t)p->Q * (size_t)T * 4 : 0;
+        p->workspace_bytes = p->red_workspace_bytes = split > 1 ? (size_t)split * (size_t)p->Q * (size_t)T * 4 : 0;
         p->pipe_ok = false;
         p->loc_row.clear();
         p->pipe_row.clear();
@@ -479,7 +479,8 @@ int bind_plan(ccdc_plan_t *p, int64_t T, int mode)
         p->red_out.swap(outs);
         p->nout = nout;
         p->red_split = (int)split;
-        p->workspace_bytes = split > 1 ? (size_t)split * (size_t)p->J * p->Q * (size_t)T * 4 : 0;
+        p->red_workspace_bytes = split > 1 ? (size_t)split * (size_t)p->J * p->Q * (size_t)T * 4 : 0;
+        p->workspace_bytes = p->red_workspace_bytes;         // until upload has fixed the chunks: the most it can be
         if (pipe_ok && pipe_cap > 1)
             p->workspace_bytes = std::max(p->workspace_bytes, (size_t)pipe_cap * (size_t)p->K * (size_t)W * 4);
         p->bound = true;

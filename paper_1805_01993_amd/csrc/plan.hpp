@@ -54,12 +54,13 @@ struct ccdc_plan_s {
     std::vector<int64_t> red_out;       // [nout] element offset of the output block in Phi
     int64_t nout = 0;                   // J * K output blocks of W elements
     int red_split = 1;                  // the row list of an output is summed in this many chunks
-    size_t workspace_bytes = 0;
+    size_t red_workspace_bytes = 0;     // partial sums of the split reductions
+    size_t workspace_bytes = 0;         // what those and the one-pass kernel's chunks need; exact once uploaded
 
     // whole path in one pass (single-job plans): the partial outputs of all K
     // nodes are accumulated in LDS, one private slot per (node, segment, lane)
     bool pipe_ok = false;               // shape supported by ccdc_pipeline_fused
-    int pipe_max_chunks = 1;            // upper bound on round chunks (sizes the workspace)
+    int pipe_max_chunks = 1;            // upper bound on round chunks
     int64_t pipe_local_rows = 0;        // rows of V every node adds from its own files
     std::vector<int64_t> loc_row;       // [K][pipe_local_rows] (element offset in V << 12) | node
     std::vector<int64_t> pipe_row;      // [nround][r+1] (src_off << 12) | member

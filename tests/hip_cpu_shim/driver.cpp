@@ -5,6 +5,7 @@
 // Test infrastructure only.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <vector>
@@ -86,8 +87,35 @@ static int limits()
     return bad ? 1 : 0;
 }
 
+// The workspace holds the partial sums that calls on the uploaded plan write, and no more.
+static int workspace()
+{
+    const int64_t shapes[][5] = {{7, 3, 7, 35, 100003}, {8, 2, 8, 28, 65536}, {10, 3, 10, 120, 4096}, {4, 1, 4, 4, 1 << 22}};
+    int bad = 0;
+    shim::compute_units = 256;
+    shim::blocks_per_cu = 16;
+    for (const auto &s : shapes) {
+        ccdc_plan_t *p = nullptr;
+        CHECK(ccdc_plan((int)s[0], (int)s[1], (int)s[2], (int)s[3], &p));
+        CHECK(ccdc_plan_bind(p, s[4], CCDC_F32_SUM));
+        const int64_t most = query(p, CCDC_Q_WORKSPACE_BYTES);
+        for (int again = 0; again < 2; again++) {
+            CHECK(ccdc_plan_upload(p));
+            const int64_t phi = query(p, CCDC_Q_PHI_ELEMS) * 4, red = p->red_split > 1 ? p->red_split * phi : 0;
+            const int64_t pipe = p->pipe_chunks > 1 ? p->pipe_chunks * phi : 0, got = query(p, CCDC_Q_WORKSPACE_BYTES);
+            std::printf("K=%d r=%d T=%lld: %d chunks, split %d, workspace %lld\n", p->K, p->r, (long long)p->T, p->pipe_chunks,
+                        p->red_split, (long long)got);
+            bad += got != std::max(red, pipe) || got > most;
+        }
+        ccdc_plan_destroy(p);
+    }
+    std::printf(bad ? "workspace FAILED (%d)\n" : "workspace ok\n", bad);
+    return bad ? 1 : 0;
+}
+
 int main(int argc, char **argv)
 {
+    if (argc == 2 && std::strcmp(argv[1], "workspace") == 0) return workspace();
     if (argc == 2 && std::strcmp(argv[1], "limits") == 0) return limits();
     if (argc < 8) return 64;
     const int K = atoi(argv[1]), r = atoi(argv[2]), Q = atoi(argv[3]), N = atoi(argv[4]);

@@ -81,3 +81,9 @@ def test_narrow_pack_fallback_is_refused_before_launch(kernel_driver):
     res = subprocess.run([kernel_driver, "limits"], capture_output=True, text=True, env=ENV, timeout=600)
     assert res.returncode == 0, res.stdout + res.stderr
     assert "limits ok" in res.stdout, res.stdout
+
+
+def test_workspace_is_what_the_calls_write(kernel_driver):
+    res = subprocess.run([kernel_driver, "workspace"], capture_output=True, text=True, env=ENV, timeout=600)
+    assert res.returncode == 0, res.stdout + res.stderr
+    assert "workspace ok" in res.stdout, res.stdout
