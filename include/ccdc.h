@@ -111,7 +111,11 @@ enum ccdc_query {
      * placement is BATCH_FIRST + NODE_BATCH).  A file is numbered job*N + n. */
     CCDC_Q_FILE_NODES,       /* int32_t[J*N][r]    the r nodes that store the file, ascending         */
     CCDC_Q_FILES_PER_NODE,   /* |M_k|: files every node stores, r*J*N/K (= mu*J*N, Sec. IV-A)         */
-    CCDC_Q_NODE_FILES        /* int32_t[K][FILES_PER_NODE] the set M_k: files node k stores, ascending */
+    CCDC_Q_NODE_FILES,       /* int32_t[K][FILES_PER_NODE] the set M_k: files node k stores, ascending */
+    CCDC_Q_PIPELINE_LAUNCH   /* int32_t[4] what ccdc_plan_upload fixed for ccdc_pipeline_fused: elements of a pack,
+                              *   wavefronts of a workgroup, chunks of rounds, flags (1: every wavefront takes an
+                              *   equal share of the rounds and one of the own files).  CCDC_ESTATE before
+                              *   ccdc_plan_upload and for plans that call answers CCDC_ESIZE or CCDC_ESTATE for */
 };
 
 /*

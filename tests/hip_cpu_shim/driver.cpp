@@ -1,7 +1,9 @@
 // Runs every entry point of the library, compiled for the host against the HIP stand-in, on
 // small shapes, under AddressSanitizer / UBSan.  Checks the outputs against the plain sum of
 // eq. (1) of the paper and the coded packets of the different paths against each other.
-// Usage: driver K r Q N T mode jobs [cus blocks_per_cu]      (mode: 0 f32, 1 u32, 2 h32, 3 bf16, 4 f16)
+// Usage: driver K r Q N T mode jobs [cus blocks_per_cu [geometry ...]]  (mode: 0 f32, 1 u32, 2 h32, 3 bf16, 4 f16)
+// A geometry is pack,wavefronts,chunks,flags as in CCDC_Q_PIPELINE_LAUNCH: only the one-pass kernel runs then,
+// as uploaded and with each geometry forced into the plan, against ccdc_combine + ccdc_encode and the plain sum.
 // Test infrastructure only.
 #include <hip/hip_runtime.h>
 
@@ -85,6 +87,24 @@ static int limits()
     }
     std::printf(bad ? "limits FAILED (%d)\n" : "limits ok\n", bad);
     return bad ? 1 : 0;
+}
+
+// Gives an uploaded plan another launch geometry for the one-pass kernel, with an exact-size workspace.
+static bool force_geometry(ccdc_plan_t *p, const char *text)
+{
+    int pack, waves, chunks, flags;
+    if (std::sscanf(text, "%d,%d,%d,%d", &pack, &waves, &chunks, &flags) != 4) return false;
+    if ((pack != 1 && pack != 2 && pack != 4) || p->ell < pack || chunks < 1 || chunks > p->pipe_max_chunks || waves < 1 ||
+        waves > ccdc::kPipeMaxWaves || p->K * p->r * ccdc::kPipeLanes * pack * 4 * waves > ccdc::kPipeMaxLds)
+        return false;
+    p->pipe_vec = pack;
+    p->pipe_waves = waves;
+    p->pipe_chunks = chunks;
+    p->pipe_even = flags & 1;
+    (void)hipFree(p->d_workspace);
+    p->workspace_bytes = std::max(p->red_workspace_bytes, chunks > 1 ? (size_t)chunks * p->K * p->W * 4 : 0);
+    p->d_workspace = nullptr;
+    return p->workspace_bytes == 0 || hipMalloc(&p->d_workspace, p->workspace_bytes) == hipSuccess;
 }
 
 // The workspace holds the partial sums that calls on the uploaded plan write, and no more.
@@ -228,16 +248,19 @@ int main(int argc, char **argv)
     }
     CHECK(ccdc_combine(p, V, Vbar, nullptr));
     CHECK(ccdc_encode(p, Vbar, X, nullptr));
-    CHECK(ccdc_decode(p, X, Vbar, D, nullptr));
-    CHECK(ccdc_reduce(p, V, D, Phi, nullptr));
-    check_phi(Phi, "staged Phi");
-    same(D, Vbar, nd, "decoded packets vs pre-combined packets");
+    const bool only_pipeline = argc > 10;
+    if (!only_pipeline) {
+        CHECK(ccdc_decode(p, X, Vbar, D, nullptr));
+        CHECK(ccdc_reduce(p, V, D, Phi, nullptr));
+        check_phi(Phi, "staged Phi");
+        same(D, Vbar, nd, "decoded packets vs pre-combined packets");
 
-    CHECK(ccdc_shuffle_fused(p, V, X2, D2, nullptr));
-    CHECK(ccdc_reduce(p, V, D2, Phi2, nullptr));
-    same(X2, X, nx, "fused X");
-    same(D2, D, nd, "fused D");
-    check_phi(Phi2, "fused Phi");
+        CHECK(ccdc_shuffle_fused(p, V, X2, D2, nullptr));
+        CHECK(ccdc_reduce(p, V, D2, Phi2, nullptr));
+        same(X2, X, nx, "fused X");
+        same(D2, D, nd, "fused D");
+        check_phi(Phi2, "fused Phi");
+    }
 
     const int rc = ccdc_pipeline_fused(p, V, X3, Phi3, nullptr);
     if (rc == CCDC_OK) {
@@ -251,13 +274,35 @@ int main(int argc, char **argv)
         return 2;
     }
 
-    CHECK(ccdc_node_encode(p, -1, V, X5, nullptr));
-    CHECK(ccdc_node_decode_reduce(p, -1, V, X5, Phi5, nullptr));
-    same(X5, X, nx, "node-local X");
-    check_phi(Phi5, "node-local Phi");
+    if (rc == CCDC_OK) {
+        int32_t launch[4];
+        CHECK(ccdc_plan_query(p, CCDC_Q_PIPELINE_LAUNCH, launch, sizeof launch));
+        std::printf("launch %d,%d,%d,%d\n", launch[0], launch[1], launch[2], launch[3]);
+    }
+    for (int i = 10; i < argc; i++) {
+        if (!force_geometry(p, argv[i])) {
+            std::fprintf(stderr, "geometry %s does not fit the plan\n", argv[i]);
+            return 3;
+        }
+        std::memset(X3, 0xA5, (size_t)nx * eb);
+        std::memset(Phi3, 0xA5, (size_t)nphi * eb);
+        CHECK(ccdc_pipeline_fused(p, V, X3, Phi3, nullptr));
+        same(X3, X, nx, argv[i]);
+        check_phi(Phi3, argv[i]);
+        CHECK(ccdc_pipeline_fused_noalloc(p, V, X4, Phi4, nullptr));
+        same(X4, X, nx, argv[i]);
+        same(Phi4, Phi3, nphi, argv[i]);
+    }
+
+    if (!only_pipeline) {
+        CHECK(ccdc_node_encode(p, -1, V, X5, nullptr));
+        CHECK(ccdc_node_decode_reduce(p, -1, V, X5, Phi5, nullptr));
+        same(X5, X, nx, "node-local X");
+        check_phi(Phi5, "node-local Phi");
+    }
 
     // Map stand-in: out = theta - files (XOR in the field), separate buffer and in place
-    {
+    if (!only_pipeline) {
         unsigned char *theta = dev(nphi), *out = dev(nv), *inpl = dev(nv);
         for (int64_t i = 0; i < nphi; i++) std::memcpy(theta + i * eb, V + ((i * 7) % nv) * eb, eb);   // any valid patterns
         std::memcpy(inpl, V, (size_t)nv * eb);

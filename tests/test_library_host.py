@@ -285,6 +285,15 @@ def test_state_and_argument_errors(lib):
     assert B.strerror(B.ESIZE) and B.strerror(-99) == "unknown status"
 
 
+def test_pipeline_launch_needs_an_uploaded_plan(lib):
+    out = (C.c_int32 * 4)()
+    p = B.ccdc_plan(4, 2, 4, 12)
+    assert lib.ccdc_plan_query(p._h, B.Q_PIPELINE_LAUNCH, out, 16) == B.ESTATE
+    p.bind(16, "f32")
+    assert lib.ccdc_plan_query(p._h, B.Q_PIPELINE_LAUNCH, out, 16) == B.ESTATE
+    p.close()
+
+
 def test_payload_modes(lib):
     p = B.ccdc_plan(4, 2, 4, 12)
     for name, code in B.MODES.items():

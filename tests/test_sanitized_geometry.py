@@ -1,9 +1,12 @@
 """The one-pass kernel's launch geometries and the node-local kernels' two forms on the CPU build of the kernels, under
 ASan and UBSan (see test_sanitized_host_code.py): every path's outputs against the plain sum and the paths' packets
-against each other, where packs straddle the end of a packet, batches have several files, workgroups several
-wavefronts and a segment a wavefront or more of packs."""
+against each other.  CASES run every path as the library launches it.  The forms of the one-pass kernel (pack width,
+end of a packet, several files a batch, wavefronts, chunks, how the rounds are shared out, more and fewer steps than
+the kernel keeps in flight) are not left to what the library would choose: FORMS forces each into the plan."""
 import os
 import subprocess
+from concurrent.futures import ThreadPoolExecutor
+from math import comb
 
 import pytest
 
@@ -11,10 +14,10 @@ from test_sanitized_host_code import ENV, kernel_driver  # noqa: F401  (the fixt
 
 # K, r, Q, N, T, mode (0 f32, 1 u32, 2 h32, 3 bf16, 4 f16), jobs, compute units, wavefronts a unit holds
 CASES = [
-    (5, 1, 5, 15, 259, 0, 0, 8, 8),       # r = 1, three files a batch, three elements past the last wide pack
-    (6, 2, 6, 30, 517, 2, 0, 2, 8),       # two files a batch, odd length, few compute units: several generations
-    (7, 3, 7, 35, 1023, 1, 0, 256, 8),    # chunks of single rounds
-    (6, 4, 12, 15, 401, 3, 0, 40, 8),     # 16-bit packs at 2-byte alignment, two functions a node
+    (5, 1, 5, 15, 259, 0, 0, 8, 8),       # r = 1, three files a batch, odd length
+    (6, 2, 6, 30, 517, 2, 0, 2, 8),       # two files a batch, odd length, two compute units
+    (7, 3, 7, 35, 1023, 1, 0, 256, 8),    # odd length, many compute units
+    (6, 4, 12, 15, 401, 3, 0, 40, 8),     # 16-bit, two functions a node
     (7, 5, 7, 42, 333, 4, 0, 8, 4),       # r = 5, two files a batch
     (5, 4, 5, 5, 3, 0, 0, 8, 8),          # a packet shorter than its segments
     (5, 2, 5, 10, 512, 1, 0, 8, 8),       # node-local: segments of exactly one wavefront of packs
@@ -29,3 +32,35 @@ def test_geometries_under_sanitizers(kernel_driver, case):  # noqa: F811
                          env=dict(os.environ, **ENV), timeout=600)
     assert res.returncode == 0, res.stdout + res.stderr
     assert " 0 mismatches" in res.stdout, res.stdout
+
+
+# Value lengths, per r: whole segments of 264 elements (66 four-element packs: a full column tile and a part one), a
+# last segment four elements short, one that no pack width divides.
+LENGTHS = {"whole": lambda r: 264 * r, "short": lambda r: 264 * r - 4 if r > 1 else 260, "split": lambda r: 264 * r - 3}
+# pack, wavefronts, chunks, flags (1: equal shares)
+FORMS = ["4,1,1,1", "4,1,1,0", "4,2,1,1", "4,1,3,0", "2,1,1,1", "2,3,1,0", "2,2,2,1", "2,1,5,0", "1,1,1,1", "1,6,1,0", "1,2,3,1"]
+
+
+@pytest.mark.parametrize("m", [1, 3])
+@pytest.mark.parametrize("r", [1, 2, 3, 4, 5])
+def test_forms_of_the_one_pass_kernel(kernel_driver, r, m):  # noqa: F811
+    """C(7, r+1) rounds: one wavefront alone has 7 to 35 rounds, or 21 to 105 steps of one file, one of six has one or
+    two rounds; up to six steps are in flight."""
+    K = 7
+
+    def run(k, end):
+        T, mode = LENGTHS[end](r), (r + k + m) % 5
+        forms = []
+        for f in FORMS:
+            pack, waves, chunks, _ = map(int, f.split(","))
+            if K * r * 256 * pack * waves <= 65536 and chunks <= comb(K, r + 1):
+                forms.append(f)
+        assert any(f[0] == "4" for f in forms) and any(f[0] == "2" for f in forms)
+        args = (K, r, K, m * comb(K, r), T, mode, 0, 8, 8)
+        return subprocess.run([kernel_driver] + [str(v) for v in args] + forms, capture_output=True, text=True,
+                              env=dict(os.environ, **ENV), timeout=600)
+
+    with ThreadPoolExecutor(3) as pool:
+        for res in pool.map(run, range(3), LENGTHS):
+            assert res.returncode == 0, res.stdout + res.stderr
+            assert " 0 mismatches" in res.stdout, res.stdout

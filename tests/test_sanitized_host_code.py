@@ -53,8 +53,8 @@ def kernel_driver(tmp_path_factory):
 
 # K, r, Q, N, T, mode (0 f32, 1 u32, 2 h32, 3 bf16, 4 f16), jobs, compute units, workgroups per unit
 KERNEL_CASES = [
-    (4, 2, 4, 12, 256, 0, 0, 8, 4),       # the tiny workload: m = 2, rounds cut into chunks
-    (4, 2, 4, 12, 256, 1, 0, 1, 1),       # same, one chunk
+    (4, 2, 4, 12, 256, 0, 0, 8, 4),       # the tiny workload: m = 2
+    (4, 2, 4, 12, 256, 1, 0, 1, 1),       # same, one compute unit
     (5, 3, 10, 20, 100, 2, 0, 8, 4),      # c = 2, m = 2, r does not divide W: short last segment
     (4, 2, 4, 12, 7, 1, 0, 8, 4),         # one-element packs, ragged tail
     (4, 3, 4, 4, 1, 0, 0, 8, 4),          # W = 1: all but the first segment empty
@@ -64,9 +64,9 @@ KERNEL_CASES = [
     (4, 2, 4, 6, 64, 0, 1, 8, 4),         # the paper's four-job schedule
     (5, 2, 10, 6, 30, 1, 1, 8, 4),        # ten jobs, c = 2, two-element alignment only
     (4, 2, 4, 240, 12, 0, 0, 8, 4),       # 40 files a batch: wavefront-wide combiner
-    (10, 3, 10, 120, 512, 0, 0, 256, 5),  # the 10-node plan, ragged split, chunked as on the device
-    (8, 2, 8, 28, 4096, 3, 0, 1, 1),      # the gradient shape's plan, bfloat16, a single chunk, several column tiles
-    (8, 4, 8, 70, 2048, 1, 0, 256, 3),    # r = 4 with the many-node shape's value length: two-element packs
+    (10, 3, 10, 120, 512, 0, 0, 256, 5),  # the 10-node plan, ragged split, the device's compute units
+    (8, 2, 8, 28, 4096, 3, 0, 1, 1),      # the gradient shape's plan, bfloat16, several column tiles
+    (8, 4, 8, 70, 2048, 1, 0, 256, 3),    # r = 4 with the many-node shape's value length
 ]
 
 
