@@ -42,8 +42,8 @@ constexpr int prefetch_depth()
     constexpr int packs = R1 * (R1 - 1);
     constexpr int regs = packs * ((VEC * (int)sizeof(typename A::elem) + 3) / 4);
     constexpr int by_regs = (MULTI ? 80 : 120) / regs;       // registers a lane spends on rounds in flight
-    constexpr int by_cnt = 56 / (packs + R1);                //  the counter of outstanding loads and stores has 6 bits
-        constexpr int most = R1 == 2 ? 6 : 4;
+    constexpr int by_cnt = 56 / (packs + R1);                // the counter of outstanding loads and stores has 6 bits
+    constexpr int most = R1 == 2 ? 6 : 4;
     constexpr int d = by_regs < by_cnt ? by_regs : by_cnt;
     return d < 1 ? 1 : (d > most ? most : d);
 }
@@ -404,17 +404,25 @@ uint32_t pipeline_tiles(const ccdc_plan_t *p)
     return cdiv(pipeline_cols<VEC>(p), ccdc::kPipeLanes) + (tail_kind<VEC>(p) == kSplit ? 1 : 0);
 }
 
-// The instantiation a plan runs.  Null for an r the kernel is not unrolled for.
+// The instantiation a plan runs.  Null for an r the kernel is not unrolled for, and where it would spill.
 template <class A, int VEC>
 PipeKernel<A> pipeline_kernel(const ccdc_plan_t *p)
 {
     const Tail tail = tail_kind<VEC>(p);
     auto of = [&](auto r1) -> PipeKernel<A> {
         constexpr int R1 = decltype(r1)::value;
-        if constexpr (VEC > 1) {
-            if (tail == kSplit) return p->m > 1 ? k_pipeline<A, VEC, R1, true, kSplit> : k_pipeline<A, VEC, R1, false, kSplit>;
+        if (p->m > 1) {
+            // Five segments of six packets, their sums and the file on the way do not fit the registers at four
+            // elements a pack: those kernels spilled up to 112 of them.  Narrower packs were faster in 19 of 20
+            // shapes measured (eight nodes, four files a batch, T = 60000 f32: 101 us at the best geometry of
+            // four-element packs, 82 with two, 73 with one), the twentieth 4 % slower.
+            if constexpr (VEC == 4 && R1 == 6) return nullptr;
+            else if constexpr (VEC == 1) return k_pipeline<A, VEC, R1, true, kShort>;
+            else return tail == kSplit ? k_pipeline<A, VEC, R1, true, kSplit> : k_pipeline<A, VEC, R1, true, kShort>;
         }
-        if (p->m > 1) return k_pipeline<A, VEC, R1, true, kShort>;
+        if constexpr (VEC > 1) {
+            if (tail == kSplit) return k_pipeline<A, VEC, R1, false, kSplit>;
+        }
         if (tail == kShort) return k_pipeline<A, VEC, R1, false, kShort>;
         return k_pipeline<A, VEC, R1, false, kWhole>;
     };

@@ -53,9 +53,10 @@ def test_forms_of_the_one_pass_kernel(kernel_driver, r, m):  # noqa: F811
         forms = []
         for f in FORMS:
             pack, waves, chunks, _ = map(int, f.split(","))
-            if K * r * 256 * pack * waves <= 65536 and chunks <= comb(K, r + 1):
-                forms.append(f)
-        assert any(f[0] == "4" for f in forms) and any(f[0] == "2" for f in forms)
+            if K * r * 256 * pack * waves <= 65536 and chunks <= comb(K, r + 1) and not (pack == 4 and r == 5 and m > 1):
+                forms.append(f)                              # (r = 5 with several files has no four-element packs)
+        assert any(f[0] == "4" for f in forms) or (r == 5 and m > 1)
+        assert any(f[0] == "2" for f in forms)
         args = (K, r, K, m * comb(K, r), T, mode, 0, 8, 8)
         return subprocess.run([kernel_driver] + [str(v) for v in args] + forms, capture_output=True, text=True,
                               env=dict(os.environ, **ENV), timeout=600)
