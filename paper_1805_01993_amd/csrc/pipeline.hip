@@ -457,16 +457,25 @@ size_t pipeline_lds(const ccdc_plan_t *p)           // one wavefront's running o
 // The launch geometry of a plan: pack width, wavefronts of a workgroup (they share a tile of columns
 // and add their outputs in LDS, so they cost no workspace traffic), chunks of rounds (they fill the
 // chip where tiles are few, at the price of a second kernel and of writing and reading a copy of all
-// outputs per chunk).  No single threshold on sizes separates the good from the bad: the time of a
-// candidate is estimated and the least taken.  The constants are fitted to measured passes of 54
-// shapes (K 4..24, r 1..5, 64 KB..3.3 GB, every mode, 30 to 70 geometries each); on those the choice
-// is 5 % slower than each shape's best geometry on average, 36 % at the worst, and 1.47 times as fast
-// on average as the one-wavefront workgroups with at most N/8 chunks that it replaces.
+// outputs per chunk).  No single threshold on sizes separates the good from the bad: the candidates are
+// ranked by an estimate of their time and the least is taken.  Its constants are fitted to measured
+// passes of several hundred shapes (K 4..24, r 1..5, 64 KB..3.2 GB, every mode, 25 to 200 geometries
+// each): they rank; as a time the estimate is up to twice the measured one.  Two sets of them, because
+// what ranks the candidates differs between small inputs (waits, the second kernel, lanes in flight) and
+// large ones (the loads a compute unit can issue, bytes, full generations).  With the first set alone 31
+// of 143 shapes with one file a batch, r >= 3 and 200 MB or more ran 3 to 34 % slower than one wavefront a
+// workgroup and at most N/8 chunks, the geometry before either set; with the second 12 do, by at most
+// 10 %, and on average they take 0.97 of the time (11 nodes, r = 4, T = 138064 u32: 545 -> 478 us; 22 nodes,
+// r = 4, T = 344 h32: 101 -> 77).  It also serves r = 5 with several files, where four-element packs are
+// missing (0.94 of the time over 20 shapes).  Elsewhere it gave nothing: with r <= 2 1.00 of the time over
+// 72 shapes, three of them 9 to 18 % slower; below 200 MB 1.00; with several files and r = 4 up to 20 % slower.
 struct Candidate {
     int vec, waves, chunks;
     bool even;
     double us;
 };
+
+constexpr double kLargeInput = 200e6;              // bytes a pass moves
 
 template <class A, int VEC>
 void consider(const ccdc_plan_t *p, Candidate *best)
@@ -491,9 +500,13 @@ void consider(const ccdc_plan_t *p, Candidate *best)
     const int depth = p->m > 1 ? pipeline_depth<A, VEC, true>(p->r) : pipeline_depth<A, VEC, false>(p->r);
     const double used = (double)(p->ell / VEC) / (cdiv(p->ell / VEC, ccdc::kPipeLanes) * ccdc::kPipeLanes);    // share of lanes with work
     const double flight = depth * r1 * p->r * ccdc::kPipeLanes * VEC * elem * used;                // bytes a wavefront has on the way
-    double peak = VEC * elem >= 16 ? 6.5e6 : VEC * elem == 8 ? 5.3e6 : VEC * elem == 4 ? 4.2e6 : 3.2e6;   // B/us
-    peak *= std::pow(used, 0.3);
-    if (p->T * elem % 8) peak *= 1 - 0.4 * std::min(1.0, 8.0 / (VEC * elem));    // rows start anywhere: more lines an access
+    const bool large = bytes >= kLargeInput && (p->m == 1 ? p->r >= 3 : p->r == 5);
+    constexpr int width = VEC * elem >= 16 ? 3 : VEC * elem == 8 ? 2 : VEC * elem == 4 ? 1 : 0;
+    constexpr double peaks[2][4] = {{3.2e6, 4.2e6, 5.3e6, 6.5e6}, {4.2e6, 4.8e6, 6.2e6, 9.0e6}};        // B/us
+    double peak = peaks[large][width] * (large ? used : std::pow(used, 0.3));
+    if (p->T * elem % 8)                             // rows start anywhere: more lines an access
+        peak *= 1 - (!large ? 0.4 : width == 0 ? 0.45 : 0.25) * std::min(1.0, 8.0 / (VEC * elem));
+    const double issue = tiles * (rows * p->r + R * r1) * 0.012 / cus;       // us a compute unit takes to issue the loads and stores
     for (int waves = 1; waves <= ccdc::kPipeMaxWaves && waves * lds <= (size_t)ccdc::kPipeMaxLds; waves++) {
         const int by_lds = (int)(ccdc::kCuLds / (waves * lds)), by_regs = limit / waves;
         const int per_cu = std::max(1, std::min(by_lds, by_regs));
@@ -505,16 +518,25 @@ void consider(const ccdc_plan_t *p, Candidate *best)
             if (chunks == last) continue;
             last = chunks;
             const double shares = (double)chunks * waves, per = R / shares;
-            Candidate c{VEC, waves, (int)chunks, shares == 1 || per >= 32, 0};
+            // equal shares of rounds and own rows: 2 % faster on large inputs, 3 % slower on small ones
+            Candidate c{VEC, waves, (int)chunks, shares == 1 || per >= (large ? 2 : 32), 0};
             const double w = tiles * shares, fill = w / room, gens = std::max(1.0, fill);
             // rounds (and rounds' worth of own rows) the busiest wavefront walks
             const double steps = c.even ? std::ceil(per) * m + own / shares / r1 : std::ceil(rows / shares / (r1 * m)) * m;
-            double rate = 1 / (0.8 / (std::min(w, room) * flight) + 1 / peak);
-            rate *= std::sqrt(gens / std::ceil(gens));                                // a last generation that is not full
-            const double stream = bytes / rate * std::pow(steps / (rows / r1 / shares), 0.08);
-            const double chain = 0.8 * gens * (steps / depth + 1);                    // waits one after the other
-            c.us = std::sqrt(stream * stream + chain * chain) + 0.007 * gens * p->K * p->r * 4 * VEC;
-            if (chunks > 1) c.us += 4 + 2.0 * chunks * p->K * p->W * 4 / 1.8e6;
+            const double uneven = steps / (rows / r1 / shares), full = gens / std::ceil(gens);    // how full the generations are
+            const double slots = gens * p->K * p->r * 4 * VEC, outputs = 2.0 * chunks * p->K * p->W * 4;
+            const double rate = 1 / ((large ? 0.2 : 0.8) / (std::min(w, room) * flight) + 1 / peak);
+            if (large) {
+                const double stream = bytes / (rate * full) * std::pow(uneven, 0.36);
+                const double chain = 2.2 * gens * (steps / depth + 1);                // waits one after the other
+                c.us = std::max({stream, chain, issue}) + 0.018 * slots;
+                if (chunks > 1) c.us += 2 + outputs / 4.6e6;
+            } else {
+                const double stream = bytes / (rate * std::sqrt(full)) * std::pow(uneven, 0.08);
+                const double chain = 0.8 * gens * (steps / depth + 1);
+                c.us = std::sqrt(stream * stream + chain * chain) + 0.007 * slots;
+                if (chunks > 1) c.us += 4 + outputs / 1.8e6;
+            }
             if (best->vec == 0 || c.us < best->us) *best = c;
         }
     }

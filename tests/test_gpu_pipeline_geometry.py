@@ -90,3 +90,24 @@ def test_pipeline_edges_16bit(torch, shape, mode):
     assert torch.equal(X.view(torch.int16), want_X.view(torch.int16)), "X differs from ccdc_encode's"
     assert torch.equal(Phi.double(), V.double().sum(1))
     plan.close()
+
+
+# Large shapes that ran slower than with one wavefront a workgroup and at most N/8 chunks, and the geometry each gets
+# since (pack, wavefronts, chunks), with the measured times.
+LAUNCHES = [
+    ((22, 4, 1, 1, 344), "h32", (2, 1, 768)),        # 101 -> 77 us
+    ((8, 5, 1, 1, 111788), "u32", (2, 3, 2)),        # 66 -> 57
+    ((11, 4, 1, 1, 138064), "u32", (4, 1, 5)),       # 545 -> 478
+    ((10, 4, 1, 1, 132616), "f32", (4, 1, 7)),       # 321 -> 282
+    ((9, 5, 1, 1, 100000), "f32", (4, 1, 9)),        # 113 -> 104
+    ((22, 4, 1, 1, 2139), "f16", (2, 1, 128)),       # odd length: two-byte accesses would be 317 us, these are 242
+]
+
+
+@pytest.mark.parametrize("shape,mode,want", LAUNCHES, ids=lambda v: "-".join(map(str, v)) if isinstance(v, tuple) else v)
+def test_launch_of_large_inputs(torch, shape, mode, want):
+    import paper_1805_01993_amd as L
+    K, r, c, m, T = shape
+    plan = L.ccdc_plan(K, r, c * K, m * comb(K, r)).bind(T, mode).upload()
+    assert plan.pipeline_launch()[:3] == want
+    plan.close()
