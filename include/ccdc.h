@@ -114,8 +114,9 @@ enum ccdc_query {
     CCDC_Q_NODE_FILES,       /* int32_t[K][FILES_PER_NODE] the set M_k: files node k stores, ascending */
     CCDC_Q_PIPELINE_LAUNCH   /* int32_t[4] what ccdc_plan_upload fixed for ccdc_pipeline_fused: elements of a pack,
                               *   wavefronts of a workgroup, chunks of rounds, flags (1: every wavefront takes an
-                              *   equal share of the rounds and one of the own files).  CCDC_ESTATE before
-                              *   ccdc_plan_upload and for plans that call answers CCDC_ESIZE or CCDC_ESTATE for */
+                              *   equal share of the rounds and one of the own files; 2: one step of the rounds
+                              *   in flight).  CCDC_ESTATE before ccdc_plan_upload and for plans that call
+                              *   answers CCDC_ESIZE or CCDC_ESTATE for */
 };
 
 /*

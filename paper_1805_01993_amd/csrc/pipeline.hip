@@ -48,6 +48,21 @@ constexpr int prefetch_depth()
     return d < 1 ? 1 : (d > most ? most : d);
 }
 
+// With r = 1 and several files a batch, a packet long enough to make wavefronts of 16-byte packs for
+// all of the chip runs faster with ONE step in flight: every wavefront then stays close to the same row
+// of V, where deeper prefetch lets them drift apart and read from many rows at once.  Nine nodes, two
+// functions each, four files a batch, T = 313700 f32 (1.0 GB): 220 us with six steps in flight, 205 with
+// one; 11 nodes, two files, T = 892808 (1.3 GB): 278, 256; six nodes, two files, T = 2671248: 250, 208;
+// two or three steps in flight are no better than six.  With shorter packets, or so many nodes that LDS
+// holds fewer than eight wavefronts a compute unit, there is too little on the way with one step (23
+// nodes, two functions, two files, T = 119076: 317 and 416 us).
+template <class A, int VEC, int R1, bool MULTI>
+constexpr bool can_be_shallow()
+{
+    return MULTI && R1 == 2 && VEC * sizeof(typename A::elem) == 16;
+}
+constexpr int64_t kLongPacket = 1200 * 1024;               // bytes: 1200 tiles of columns
+
 // How a packet's last segment ends, at a given pack width.
 enum Tail {
     kWhole = 0,                       // r segments of ell elements, whole packs everywhere
@@ -61,6 +76,7 @@ struct PipeArgs {
     uint32_t R, n_loc;
     uint32_t tiles, chunks, waves;
     bool even;                        // how the work is shared out, see walk()
+    bool shallow;                     // one step in flight, see long_packets()
     uint32_t cols;                    // packs the wide columns cover (kSplit: the rest is the last tile's)
     int64_t file_stride, chunk_stride;
 };
@@ -251,7 +267,15 @@ __device__ __forceinline__ void walk(const typename A::elem *__restrict__ V, typ
             // is taken out of the loop (no X store lies between its loads), and short ranges
             // fill the stages on a way of their own.
             uint32_t i = 0;
-            if (steps >= 3 * PF) {
+            bool shallow = false;
+            if constexpr (can_be_shallow<A, VEC, R1, MULTI>()) shallow = p.shallow;
+            if (shallow) {
+                load(fetch(iu), st[0]);
+                ahead = fetch(iu);
+                for (; i + 1 < steps; i++) turn(st[0]);
+                use(st[0]);
+                i = steps;
+            } else if (steps >= 3 * PF) {
 #pragma unroll
                 for (int s = 0; s < PF; s++) {
                     load(fetch(iu), st[s]);
@@ -454,6 +478,13 @@ size_t pipeline_lds(const ccdc_plan_t *p)           // one wavefront's running o
     return (size_t)p->K * p->r * ccdc::kPipeLanes * VEC * sizeof(float);     // every algebra sums in 4 bytes
 }
 
+// Whether four-element packs of this plan run with one step in flight (see kLongPacket).
+bool long_packets(const ccdc_plan_t *p)
+{
+    return p->r == 1 && p->m > 1 && elem_bytes(p->mode) == 4 && p->W * 4 >= kLongPacket &&
+           8 * pipeline_lds<4>(p) <= (size_t)ccdc::kCuLds;
+}
+
 // The launch geometry of a plan: pack width, wavefronts of a workgroup (they share a tile of columns
 // and add their outputs in LDS, so they cost no workspace traffic), chunks of rounds (they fill the
 // chip where tiles are few, at the price of a second kernel and of writing and reading a copy of all
@@ -467,11 +498,11 @@ size_t pipeline_lds(const ccdc_plan_t *p)           // one wavefront's running o
 // workgroup and at most N/8 chunks, the geometry before either set; with the second 12 do, by at most
 // 10 %, and on average they take 0.97 of the time (11 nodes, r = 4, T = 138064 u32: 545 -> 478 us; 22 nodes,
 // r = 4, T = 344 h32: 101 -> 77).  It also serves r = 5 with several files, where four-element packs are
-// missing (0.94 of the time over 20 shapes).  Elsewhere it gave nothing: with r <= 2 1.00 of the time over
+// missing (0.94 of the time over 20 shapes), and r = 1 with several files and long packets (see kLongPacket).  Elsewhere it gave nothing: with r <= 2 1.00 of the time over
 // 72 shapes, three of them 9 to 18 % slower; below 200 MB 1.00; with several files and r = 4 up to 20 % slower.
 struct Candidate {
     int vec, waves, chunks;
-    bool even;
+    bool even, shallow;
     double us;
 };
 
@@ -497,10 +528,11 @@ void consider(const ccdc_plan_t *p, Candidate *best)
     const double rows = R * r1 * m + own;            // rows of r packs a tile reads
     const double tiles = pipeline_tiles<VEC>(p), bytes =
         ((double)p->N * p->Q * p->T + (double)p->nrows * p->ell + (double)p->Q * p->T) * elem;
+    const bool longp = bytes >= kLargeInput && long_packets(p), shallow = can_be_shallow<A, VEC, 2, true>() && longp;
+    const bool large = bytes >= kLargeInput && (p->m == 1 ? p->r >= 3 : p->r == 5 || longp);
     const int depth = p->m > 1 ? pipeline_depth<A, VEC, true>(p->r) : pipeline_depth<A, VEC, false>(p->r);
     const double used = (double)(p->ell / VEC) / (cdiv(p->ell / VEC, ccdc::kPipeLanes) * ccdc::kPipeLanes);    // share of lanes with work
-    const double flight = depth * r1 * p->r * ccdc::kPipeLanes * VEC * elem * used;                // bytes a wavefront has on the way
-    const bool large = bytes >= kLargeInput && (p->m == 1 ? p->r >= 3 : p->r == 5);
+    const double flight = (shallow ? 1 : depth) * r1 * p->r * ccdc::kPipeLanes * VEC * elem * used;                // bytes a wavefront has on the way
     constexpr int width = VEC * elem >= 16 ? 3 : VEC * elem == 8 ? 2 : VEC * elem == 4 ? 1 : 0;
     constexpr double peaks[2][4] = {{3.2e6, 4.2e6, 5.3e6, 6.5e6}, {4.2e6, 4.8e6, 6.2e6, 9.0e6}};        // B/us
     double peak = peaks[large][width] * (large ? used : std::pow(used, 0.3));
@@ -508,7 +540,8 @@ void consider(const ccdc_plan_t *p, Candidate *best)
         peak *= 1 - (!large ? 0.4 : width == 0 ? 0.45 : 0.25) * std::min(1.0, 8.0 / (VEC * elem));
     const double issue = tiles * (rows * p->r + R * r1) * 0.012 / cus;       // us a compute unit takes to issue the loads and stores
     for (int waves = 1; waves <= ccdc::kPipeMaxWaves && waves * lds <= (size_t)ccdc::kPipeMaxLds; waves++) {
-        const int by_lds = (int)(ccdc::kCuLds / (waves * lds)), by_regs = limit / waves;
+        const size_t granule = large ? ccdc::kLdsGranule : 1;
+        const int by_lds = (int)(ccdc::kCuLds / ((waves * lds + granule - 1) / granule * granule)), by_regs = limit / waves;
         const int per_cu = std::max(1, std::min(by_lds, by_regs));
         const double room = (double)cus * per_cu * waves;                            // wavefronts in flight at most
         int64_t last = 0;
@@ -519,20 +552,21 @@ void consider(const ccdc_plan_t *p, Candidate *best)
             last = chunks;
             const double shares = (double)chunks * waves, per = R / shares;
             // equal shares of rounds and own rows: 2 % faster on large inputs, 3 % slower on small ones
-            Candidate c{VEC, waves, (int)chunks, shares == 1 || per >= (large ? 2 : 32), 0};
+            Candidate c{VEC, waves, (int)chunks, shares == 1 || per >= (large ? 2 : 32), shallow, 0};
             const double w = tiles * shares, fill = w / room, gens = std::max(1.0, fill);
             // rounds (and rounds' worth of own rows) the busiest wavefront walks
             const double steps = c.even ? std::ceil(per) * m + own / shares / r1 : std::ceil(rows / shares / (r1 * m)) * m;
             const double uneven = steps / (rows / r1 / shares), full = gens / std::ceil(gens);    // how full the generations are
             const double slots = gens * p->K * p->r * 4 * VEC, outputs = 2.0 * chunks * p->K * p->W * 4;
-            const double rate = 1 / ((large ? 0.2 : 0.8) / (std::min(w, room) * flight) + 1 / peak);
+            const double latency = !large ? 0.8 : longp ? 0.1 : 0.2;                  // us
+            const double rate = std::sqrt(full) / (latency / (std::min(w, room) * flight) + 1 / peak);
             if (large) {
-                const double stream = bytes / (rate * full) * std::pow(uneven, 0.36);
+                const double stream = bytes / rate * std::pow(uneven, 0.36);
                 const double chain = 2.2 * gens * (steps / depth + 1);                // waits one after the other
                 c.us = std::max({stream, chain, issue}) + 0.018 * slots;
                 if (chunks > 1) c.us += 2 + outputs / 4.6e6;
             } else {
-                const double stream = bytes / (rate * std::sqrt(full)) * std::pow(uneven, 0.08);
+                const double stream = bytes / rate * std::pow(uneven, 0.08);
                 const double chain = 0.8 * gens * (steps / depth + 1);
                 c.us = std::sqrt(stream * stream + chain * chain) + 0.007 * slots;
                 if (chunks > 1) c.us += 4 + outputs / 1.8e6;
@@ -565,6 +599,7 @@ int run_pipeline(const ccdc_plan_t *p, const void *V, void *X, void *Phi, void *
     args.chunks = (uint32_t)chunks;
     args.waves = (uint32_t)p->pipe_waves;
     args.even = p->pipe_even;
+    args.shallow = p->pipe_shallow;
     args.cols = pipeline_cols<VEC>(p);
     args.file_stride = (int64_t)p->Q * p->T;
     args.chunk_stride = (int64_t)p->K * p->W;
@@ -600,7 +635,7 @@ int pipeline_run(const ccdc_plan_t *p, const void *V, void *X, void *Phi, void *
 template <class A>
 void pipeline_geometry(ccdc_plan_t *p)
 {
-    Candidate best{0, 1, 1, true, 0};
+    Candidate best{0, 1, 1, true, false, 0};
     consider<A, 4>(p, &best);
     consider<A, 2>(p, &best);
     consider<A, 1>(p, &best);
@@ -608,6 +643,7 @@ void pipeline_geometry(ccdc_plan_t *p)
     p->pipe_waves = best.waves;
     p->pipe_chunks = best.chunks;
     p->pipe_even = best.even;
+    p->pipe_shallow = best.shallow;
 }
 
 // The kernel's instantiations take minutes to compile in one piece: with CCDC_PIPELINE_PART set, this

@@ -78,6 +78,7 @@ struct ccdc_plan_s {
     // pack, wavefronts of a workgroup (they share a tile of columns) and chunks of rounds
     int pipe_vec = 1, pipe_waves = 1, pipe_chunks = 0;
     bool pipe_even = true;              // every wavefront takes a share of the rounds and one of the own rows
+    bool pipe_shallow = false;          // one step of the rounds in flight (r = 1, several files a batch)
 
     // Order of the calls that use the workspace, across streams: the last such call
     // recorded ws_event (a hipEvent_t made by ccdc_plan_upload) on ws_stream.
@@ -99,9 +100,10 @@ constexpr int kPipeLanes = 64;                 // columns of a tile: one wavefro
 constexpr int kPipeMaxWaves = 8;               // wavefronts of a workgroup
 constexpr int kPipeMaxLds = 64 * 1024;         // bytes of LDS one workgroup may take
 constexpr int kCuLds = 160 * 1024;             // bytes of LDS of a compute unit
+constexpr int kLdsGranule = 1280;              // bytes it is given out in
 constexpr int kPipeMaxR1 = 6;                  // r+1 the kernel is unrolled for
 
-// One-pass pipeline (pipeline.hip): fixes the launch geometry (pipe_vec .. pipe_even) for the current device.
+// One-pass pipeline (pipeline.hip): fixes the launch geometry (pipe_vec .. pipe_shallow) for the current device.
 void pipeline_prepare(ccdc_plan_t *p);
 // Body of ccdc_pipeline_fused.  own_part = null: partial outputs of round chunks go
 // to the plan's workspace; else to the caller's buffer of own_part_bytes bytes

@@ -101,6 +101,7 @@ static bool force_geometry(ccdc_plan_t *p, const char *text)
     p->pipe_waves = waves;
     p->pipe_chunks = chunks;
     p->pipe_even = flags & 1;
+    p->pipe_shallow = flags & 2;
     (void)hipFree(p->d_workspace);
     p->workspace_bytes = std::max(p->red_workspace_bytes, chunks > 1 ? (size_t)chunks * p->K * p->W * 4 : 0);
     p->d_workspace = nullptr;

@@ -101,7 +101,10 @@ LAUNCHES = [
     ((10, 4, 1, 1, 132616), "f32", (4, 1, 7)),       # 321 -> 282
     ((9, 5, 1, 1, 100000), "f32", (4, 1, 9)),        # 113 -> 104
     ((22, 4, 1, 1, 2139), "f16", (2, 1, 128)),       # odd length: two-byte accesses would be 317 us, these are 242
+    ((11, 1, 1, 2, 892808), "f32", (4, 1, 1)),       # 278 -> 256, with one step in flight
+    ((12, 1, 1, 2, 426920), "u32", (4, 1, 1)),       # 154 -> 140, the same
 ]
+ONE_STEP = 2                                         # flag of pipeline_launch()
 
 
 @pytest.mark.parametrize("shape,mode,want", LAUNCHES, ids=lambda v: "-".join(map(str, v)) if isinstance(v, tuple) else v)
@@ -110,4 +113,31 @@ def test_launch_of_large_inputs(torch, shape, mode, want):
     K, r, c, m, T = shape
     plan = L.ccdc_plan(K, r, c * K, m * comb(K, r)).bind(T, mode).upload()
     assert plan.pipeline_launch()[:3] == want
+    assert bool(plan.pipeline_launch()[3] & ONE_STEP) == (r == 1)
+    plan.close()
+
+
+@pytest.mark.parametrize("mode", ["f32", "u32", "h32"])
+@pytest.mark.parametrize("T", [310003, 310004])
+def test_one_step_in_flight(torch, T, mode):
+    """r = 1, ten files a batch, packets long enough for the form with one step in flight, with and without an end
+    that a pack straddles.  Whole numbers of a small range: sums are exact in every order."""
+    import paper_1805_01993_amd as L
+    plan = L.ccdc_plan(4, 1, 4, 40).bind(T, mode).upload()
+    assert plan.pipeline_launch()[0] == 4 and plan.pipeline_launch()[3] & ONE_STEP
+    sh, dt = plan.shapes(), torch.int32 if mode == "u32" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(4)
+    V = torch.randint(-8, 9, sh["V"], device="cuda", generator=g).to(dt)
+    X, Phi, Vbar, want_X = (torch.full(sh[key], 77, dtype=dt, device="cuda") for key in ("X", "Phi", "Vbar", "X"))
+    plan.combine(V, Vbar)
+    plan.encode(Vbar, want_X)
+    plan.pipeline_fused(V, X, Phi)
+    assert torch.equal(X.view(torch.int32), want_X.view(torch.int32)), "X differs from ccdc_encode's"
+    if mode == "u32":
+        want = V[:, 0].clone()
+        for n in range(1, V.shape[1]):
+            want ^= V[:, n]
+    else:
+        want = V.sum(1)
+    assert torch.equal(Phi, want)
     plan.close()

@@ -37,8 +37,8 @@ def test_geometries_under_sanitizers(kernel_driver, case):  # noqa: F811
 # Value lengths, per r: whole segments of 264 elements (66 four-element packs: a full column tile and a part one), a
 # last segment four elements short, one that no pack width divides.
 LENGTHS = {"whole": lambda r: 264 * r, "short": lambda r: 264 * r - 4 if r > 1 else 260, "split": lambda r: 264 * r - 3}
-# pack, wavefronts, chunks, flags (1: equal shares)
-FORMS = ["4,1,1,1", "4,1,1,0", "4,2,1,1", "4,1,3,0", "2,1,1,1", "2,3,1,0", "2,2,2,1", "2,1,5,0", "1,1,1,1", "1,6,1,0", "1,2,3,1"]
+# pack, wavefronts, chunks, flags (1: equal shares, 2: one step in flight where the kernel has that form)
+FORMS = ["4,1,1,3", "4,2,3,2", "4,1,1,1", "4,1,1,0", "4,2,1,1", "4,1,3,0", "2,1,1,1", "2,3,1,0", "2,2,2,1", "2,1,5,0", "1,1,1,1", "1,6,1,0", "1,2,3,1"]
 
 
 @pytest.mark.parametrize("m", [1, 3])
