@@ -305,7 +305,7 @@ def test_one_plan_on_two_streams_is_put_in_order(torch, L):
     exactly what it gives alone."""
     K, r, Q, N, T = 10, 3, 10, 120, 32768
     plan = L.ccdc_plan(K, r, Q, N).bind(T, "f32").upload()
-    assert plan.workspace_bytes > 0
+    assert plan.workspace_bytes > 0 and plan.pipeline_launch()[2] > 1        # both calls write chunk outputs there
     sh = plan.shapes()
     Va = generate_torch(1, N, Q, T, 11, "f32", device="cuda")
     Vb = generate_torch(1, N, Q, T, 12, "f32", device="cuda")

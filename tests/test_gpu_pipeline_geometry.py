@@ -1,7 +1,9 @@
-"""ccdc_pipeline_fused where its launch geometry and its packs have edges: value lengths that no pack
-width divides, packets shorter than a pack or a segment, several files per batch with more and fewer
-steps than the pipeline is deep, one to many column tiles, pointers that are only element-aligned.
-X against ccdc_encode's bit for bit, Phi against eq. (1) from the oracle.  Needs a GPU."""
+"""ccdc_pipeline_fused where its launch geometry and its packs have edges.  SHAPES: value lengths that no
+pack width divides, packets shorter than a pack or a segment, several files per batch, one to many column
+tiles, pointers that are only element-aligned; nearly all of them run one-element packs.  X against
+ccdc_encode's bit for bit, Phi against eq. (1) from the oracle.  WIDE: shapes that the library sends to
+wide packs, each with the geometry that makes it one of the kernel's forms.  (The CPU build runs every form
+by force, test_sanitized_geometry.py.)  Needs a GPU."""
 from math import comb
 
 import numpy as np
@@ -15,7 +17,7 @@ pytestmark = pytest.mark.gpu
 # K, r, c, files per batch, T
 SHAPES = [
     (4, 2, 1, 2, 1), (4, 3, 1, 1, 2), (7, 5, 1, 1, 3), (5, 4, 2, 3, 7),            # packets shorter than their segments
-    (5, 1, 1, 1, 255), (5, 1, 1, 7, 257), (6, 2, 1, 1, 513), (6, 2, 2, 10, 258),    # a tile and one pack more or less
+    (5, 1, 1, 1, 255), (5, 1, 1, 7, 257), (6, 2, 1, 1, 513), (6, 2, 2, 10, 258),    # a tile and an element more or less
     (7, 3, 1, 1, 1543), (7, 3, 1, 2, 1030), (8, 4, 1, 1, 4097), (7, 5, 1, 3, 1287),
     (12, 4, 1, 1, 66), (16, 5, 1, 1, 131), (16, 3, 1, 1, 1021), (24, 2, 1, 1, 70),  # few columns, many rounds
     (5, 2, 1, 1, 70001), (4, 1, 1, 2, 200003),                                       # many tiles, one chunk
@@ -114,6 +116,54 @@ def test_launch_of_large_inputs(torch, shape, mode, want):
     plan = L.ccdc_plan(K, r, c * K, m * comb(K, r)).bind(T, mode).upload()
     assert plan.pipeline_launch()[:3] == want
     assert bool(plan.pipeline_launch()[3] & ONE_STEP) == (r == 1)
+    plan.close()
+
+
+# shape, mode, (pack, wavefronts, chunks, flags): what makes it a form of its own
+WIDE = [
+    ((7, 3, 1, 1, 100003), "f32", (4, 3, 1, 0)),     # a pack straddles the packet's end, r = 3, one chunk
+    ((10, 2, 1, 1, 20001), "u32", (4, 3, 3, 0)),     # the same with chunks, and more rounds than three times those in flight
+    ((10, 3, 1, 1, 10001), "h32", (2, 4, 9, 0)),     # two-element packs, chunks
+    ((6, 4, 1, 1, 60001), "f32", (2, 5, 1, 0)),      # r = 4
+    ((6, 5, 1, 1, 150001), "u32", (2, 4, 1, 0)),     # r = 5; wavefronts without a round
+    ((9, 4, 1, 1, 20002), "f32", (2, 3, 6, 0)),      # last segment short, whole packs
+    ((9, 4, 1, 1, 20002), "f16", (2, 3, 6, 0)),
+    ((9, 2, 1, 3, 20001), "f32", (4, 3, 6, 0)),      # three files a batch, 14 steps a wavefront, three in flight
+    ((9, 2, 1, 3, 20001), "bf16", (2, 7, 3, 0)),
+    ((6, 1, 1, 12, 60002), "h32", (4, 8, 1, 0)),     # r = 1, 22 steps, six in flight
+    ((5, 2, 1, 8, 60001), "bf16", (4, 6, 1, 0)),
+    ((8, 5, 1, 1, 111788), "f32", (2, 3, 2, 1)),     # equal shares of the rounds
+    ((9, 5, 1, 1, 100000), "u32", (4, 1, 9, 1)),
+]
+
+
+@pytest.mark.parametrize("shape,mode,want", WIDE, ids=lambda v: "-".join(map(str, v)) if isinstance(v, tuple) else v)
+def test_wide_packs(torch, shape, mode, want):
+    """Whole numbers of a small range: sums are exact in every order (in 16 bits: sparse ones, sums far below 2^8)."""
+    import paper_1805_01993_amd as L
+    K, r, c, m, T = shape
+    N = m * comb(K, r)
+    plan = L.ccdc_plan(K, r, c * K, N).bind(T, mode).upload()
+    assert plan.pipeline_launch() == want
+    sh, dt = plan.shapes(), {"u32": torch.int32, "bf16": torch.bfloat16, "f16": torch.float16}.get(mode, torch.float32)
+    g = torch.Generator(device="cuda").manual_seed(6)
+    if dt.itemsize == 2:
+        V = (torch.rand(sh["V"], device="cuda", generator=g) < 8.0 / N).to(dt)
+    else:
+        V = torch.randint(-8, 9, sh["V"], device="cuda", generator=g).to(dt)
+    X, Phi, Vbar, want_X = (torch.full(sh[key], 77, dtype=dt, device="cuda") for key in ("X", "Phi", "Vbar", "X"))
+    plan.combine(V, Vbar)
+    plan.encode(Vbar, want_X)
+    plan.pipeline_fused(V, X, Phi)
+    bits = torch.int16 if dt.itemsize == 2 else torch.int32
+    assert torch.equal(X.view(bits), want_X.view(bits)), "X differs from ccdc_encode's"
+    if mode == "u32":
+        total = V[:, 0].clone()
+        for n in range(1, N):
+            total ^= V[:, n]
+        assert torch.equal(Phi, total)
+    else:
+        assert torch.equal(Phi.float(), V.float().sum(1))
     plan.close()
 
 
