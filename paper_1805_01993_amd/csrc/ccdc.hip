@@ -258,7 +258,7 @@ __global__ __launch_bounds__(kBlock) void k_shuffle_fused(const typename A::elem
 // c functions of one job) is the sum of a list of W-long rows, some in V (files
 // the node stores), some in D (packets it decoded).  The list is cut into
 // `split` chunks; work item = (o, chunk, pack).  With split > 1 the chunk sums
-// go, not yet narrowed, to the workspace and k_reduce_final adds them in chunk order.
+// go, not yet narrowed, to the workspace and k_reduce_final adds them in its fixed order.
 template <class A, int VEC>
 __global__ __launch_bounds__(kBlock) void k_reduce_rows(const typename A::elem *__restrict__ V,
                                                         const typename A::elem *__restrict__ D,

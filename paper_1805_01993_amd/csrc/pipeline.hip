@@ -22,7 +22,7 @@ using namespace ccdc;
 // times slower than this read-add-write of the round's slots.)
 // The wavefronts' outputs are added in wavefront order; with more than one chunk
 // the per-chunk outputs go to the workspace and k_reduce_final adds
-// them in chunk order.  Running outputs and chunk outputs are sums in the making
+// them in its fixed order.  Running outputs and chunk outputs are sums in the making
 // (the algebra's acc type); they are narrowed to elements once, when Phi is written.
 //
 // What bounds it: bytes on large inputs (the 8-node gradient shape, 4.04 GB of

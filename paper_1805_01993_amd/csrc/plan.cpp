@@ -429,7 +429,7 @@ int bind_plan(ccdc_plan_t *p, int64_t T, int mode)
 
         // Few, long outputs (small T, many rounds) would leave the chip idle: cut
         // each row list into red_split chunks summed by different workgroups and
-        // added up, in chunk order, by a second pass.
+        // added up, in a fixed order, by a second pass.
         const int64_t items = nout * ((W + vec - 1) / vec);
         int64_t split = 1;
         if (items < (1 << 18)) split = std::min<int64_t>({(int64_t)256, std::max<int64_t>(1, min_rows), ((1 << 19) + items - 1) / items});
