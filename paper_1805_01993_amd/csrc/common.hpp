@@ -96,7 +96,7 @@ struct Hyb16 {
             // v_cvt_pk_bf16_f32 rounds to nearest even, subnormals and overflow to infinity included (all 2^32 patterns
             // compared with the integer form below).  The integer form's ten instructions an element kept the Map kernel
             // busy for half of its time: 28 files of 25.6 M bf16 values 532 us, as the 32-bit modes 505; with the
-            // conversion 482.
+            // conversion 510.
             const __bf16 h = (__bf16)a;
             elem out;
             __builtin_memcpy(&out, &h, 2);
@@ -297,6 +297,15 @@ __device__ __forceinline__ uint32_t lane_offset(uint32_t v)
     asm volatile("" : "+v"(v));
 #endif
     return v;
+}
+
+// Workgroups are handed to the 8 XCDs round-robin.  This numbers them so that each XCD gets a contiguous
+// range of the work, behind its own L2.
+__device__ __forceinline__ uint32_t xcd_contiguous(uint32_t block, uint32_t blocks)
+{
+    constexpr uint32_t XCDS = 8;
+    const uint32_t q = blocks / XCDS, rem = blocks % XCDS, xcd = block % XCDS, j = block / XCDS;
+    return (xcd < rem ? xcd * (q + 1) : rem * (q + 1) + (xcd - rem) * q) + j;
 }
 
 constexpr int kBlock = 256;

@@ -375,17 +375,12 @@ __global__ __launch_bounds__(ccdc::kPipeLanes *ccdc::kPipeMaxWaves) void k_pipel
 {
     constexpr uint32_t LANES = ccdc::kPipeLanes;
     extern __shared__ __align__(16) unsigned char smem[];
-    // Workgroups are handed to the 8 XCDs round-robin.  When the rounds are cut
-    // into chunks, renumber them so that each XCD gets a contiguous range of
+    // When the rounds are cut into chunks, each XCD gets a contiguous range of
     // (chunk, tile) pairs: the tiles of one chunk (adjacent pieces of the same
     // rows, the same table entries) then run next to each other in time behind one
     // L2.  With a single chunk the hardware order is kept: all XCDs then sweep the
     // same window of every row together (measured: 2 % either way).
-    constexpr uint32_t XCDS = 8;
-    const uint32_t nb = gridDim.x, q = nb / XCDS, rem = nb % XCDS;
-    const uint32_t xcd = blockIdx.x % XCDS, j = blockIdx.x / XCDS;
-    const uint32_t logical =
-        p.chunks > 1 ? (xcd < rem ? xcd * (q + 1) : rem * (q + 1) + (xcd - rem) * q) + j : blockIdx.x;
+    const uint32_t logical = p.chunks > 1 ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x;
     const uint32_t tile = logical % p.tiles, chunk = logical / p.tiles;
     const uint32_t lane = threadIdx.x % LANES, wave = wave_uniform(threadIdx.x / LANES);
     if constexpr (TAIL == kSplit) {

@@ -106,3 +106,17 @@ def test_gradient_workload_from_files(torch, L):
     got = Phi.cpu().numpy().astype(np.float64)
     assert np.abs(got - full).max() <= 1e-5 * np.abs(full).max()
     plan.close()
+
+
+@pytest.mark.parametrize("N,tiles", [(2, 1), (7, 1), (3, 3), (8, 5), (9, 17), (5, 300), (2, 513)])
+def test_every_tile_of_every_file_is_mapped_once(torch, L, N, tiles):
+    """Fewer workgroups than XCDs, a multiple of them, remainders; one and several groups of tiles (the last one short).
+    One subtraction in fp32: bit for bit."""
+    T = tiles * 256 * 4 // 2 - 4                                      # Q = 2 functions: the last tile is short
+    plan = L.Plan(2, 1, 2, N * 2).bind(T, "f32").upload()
+    g = torch.Generator(device="cuda").manual_seed(N * 1000 + tiles)
+    files = torch.randn((1, 2 * N, 2, T), device="cuda", generator=g)
+    theta = torch.randn((1, 2, T), device="cuda", generator=g)
+    V = torch.full_like(files, float("nan"))
+    plan.map(files, theta, V)
+    assert torch.equal(V, theta.unsqueeze(1) - files)
