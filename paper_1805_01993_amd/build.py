@@ -12,8 +12,8 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libccdc.so")
 SOURCES = ["ccdc.hip", "pipeline.hip", "node.hip", "noalloc.hip", "map.hip", "plan.cpp"]
-# pipeline.hip has hundreds of kernel instantiations: it is compiled in pieces, one per payload algebra
-PIECES = {"pipeline.hip": ("CCDC_PIPELINE_PART", 5)}
+# pipeline.hip has hundreds of kernel instantiations: it is compiled in pieces, two per payload algebra
+PIECES = {"pipeline.hip": ("CCDC_PIPELINE_PART", 10)}
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "ccdc.h"
 #include "plan.hpp"
@@ -261,6 +262,26 @@ __device__ __forceinline__ P load_stream_any(const void *p)
     __builtin_memcpy(&out, &b, sizeof(P));
     return out;
 }
+// Through the caches instead: KEPT loads are ordinary ones (see kKeptBytes).
+template <bool KEPT, class P>
+__device__ __forceinline__ P load_pack(const void *p)
+{
+    if constexpr (KEPT) return *reinterpret_cast<const P *>(p);
+    else return load_stream<P>(p);
+}
+template <bool KEPT, class P, class E>
+__device__ __forceinline__ P load_pack_any(const void *p)
+{
+    if constexpr (KEPT) {
+        using B = typename AnyBits<P, E>::type;
+        const B b = *reinterpret_cast<const B *>(p);
+        P out;
+        __builtin_memcpy(&out, &b, sizeof(P));
+        return out;
+    } else {
+        return load_stream_any<P, E>(p);
+    }
+}
 template <class P, class E>
 __device__ __forceinline__ void store_stream_any(void *p, const P &v)
 {
@@ -371,6 +392,32 @@ inline int ready(const ccdc_plan_t *p)
 }
 
 inline int elem_bytes(int mode) { return (mode == CCDC_BF16_SUM_XOR || mode == CCDC_F16_SUM_XOR) ? 2 : 4; }
+
+// Non-temporal loads pass the last-level cache (256 MB) by, ordinary ones leave the data there.  A call whose
+// inputs and outputs take no more than this therefore reads with ordinary loads: its inputs are then often still
+// there from the call that made them.  Measured with three sets of buffers used in turn.  One-pass kernel, 8 nodes,
+// r = 2, one file a batch, f32: 64 MB a pass 14.5 -> 12.6 us, 129 MB 24.1 -> 23.4, but 194 MB 43.1 -> 46.2 and 1 GB
+// 190 -> 199.  The calls of single stages share the cache with what the other stages make: two functions a node,
+// uncoded, 13 nodes, T = 780 u32 (17 MB of values) 23.5 -> 18.3 us, six nodes, T = 24256 u32 (50 MB a call) 33 -> 24,
+// a step from files on 24 nodes (43 MB read) 47 -> 41, but the four stages at 87 MB a call (12 nodes, T = 6000 f16)
+// 43.7 -> 46.4.
+constexpr double kKeptBytes = 128e6, kKeptStageBytes = 64e6;
+
+// The bytes a call that reads V moves, with `elements` of other inputs and outputs.
+inline double moved_bytes(const ccdc_plan_t *p, double elements)
+{
+    return ((double)p->J * p->N * p->Q * (double)p->T + elements) * elem_bytes(p->mode);
+}
+
+// Calls launch(kept) with that as a compile-time constant.  One-element packs always keep their reads: rows then
+// begin anywhere in a cache line, and neighbours share the line (six nodes, uncoded, T = 729266 f32, 2.5 GB of
+// values: 604 -> 577 us).
+template <int VEC, class F>
+void by_reads(bool kept, F launch)
+{
+    if (VEC == 1 || kept) launch(std::true_type());
+    else if constexpr (VEC > 1) launch(std::false_type());
+}
 
 // Pack width (elements) for this call: 16 bytes when the value length, the
 // segment length and every pointer allow it; for 2-byte elements else 8 bytes;

@@ -61,7 +61,7 @@ constexpr bool can_be_shallow()
 {
     return MULTI && R1 == 2 && VEC * sizeof(typename A::elem) == 16;
 }
-constexpr int64_t kLongPacket = 1200 * 1024;               // bytes: 1200 tiles of columns
+[[maybe_unused]] constexpr int64_t kLongPacket = 1200 * 1024;               // bytes: 1200 tiles of columns
 
 // How a packet's last segment ends, at a given pack width.
 enum Tail {
@@ -70,6 +70,9 @@ enum Tail {
     kSplit = 2,                       // some pack would straddle the end of the packet
 };
 
+}  // namespace
+
+namespace ccdc {
 struct PipeArgs {
     int K, m;
     uint32_t W, ell;                  // elements of a packet and of a segment
@@ -77,13 +80,17 @@ struct PipeArgs {
     uint32_t tiles, chunks, waves;
     bool even;                        // how the work is shared out, see walk()
     bool shallow;                     // one step in flight, see long_packets()
+    bool by_xcd;                      // each XCD works on a contiguous range of (chunk, tile) pairs
     uint32_t cols;                    // packs the wide columns cover (kSplit: the rest is the last tile's)
     int64_t file_stride, chunk_stride;
 };
+}  // namespace ccdc
+
+namespace {
 
 // One wavefront's share of the pass on one tile of columns: lane = VEC elements
 // from in-segment position x on, rounds and own files of the wavefront's range.
-template <class A, int VEC, int R1, bool MULTI, bool SHORT>
+template <class A, int VEC, int R1, bool MULTI, bool SHORT, bool KEPT>
 __device__ __forceinline__ void walk(const typename A::elem *__restrict__ V, typename A::elem *__restrict__ X,
                                      typename A::elem *__restrict__ Phi, typename A::acc *__restrict__ part,
                                      const int64_t *__restrict__ rows, const int64_t *__restrict__ own,
@@ -113,7 +120,7 @@ __device__ __forceinline__ void walk(const typename A::elem *__restrict__ V, typ
         }
         const uint32_t xb = x * (uint32_t)sizeof(E);
         auto pack_at = [](const E *row, uint32_t byte_off) -> P {
-            return load_stream_any<P, E>(reinterpret_cast<const char *>(row) + byte_off);
+            return load_pack_any<KEPT, P, E>(reinterpret_cast<const char *>(row) + byte_off);
         };
         for (int i = 0; i < slots; i++) acc[i * LANES] = O::azero();
 
@@ -368,36 +375,37 @@ __device__ __forceinline__ void walk(const typename A::elem *__restrict__ V, typ
     }
 }
 
-template <class A, int VEC, int R1, bool MULTI, int TAIL>
+template <class A, int VEC, int R1, bool MULTI, int TAIL, bool KEPT>
 __global__ __launch_bounds__(ccdc::kPipeLanes *ccdc::kPipeMaxWaves) void k_pipeline(
     const typename A::elem *__restrict__ V, typename A::elem *__restrict__ X, typename A::elem *__restrict__ Phi,
     typename A::acc *__restrict__ part, const int64_t *__restrict__ rows, const int64_t *__restrict__ own, PipeArgs p)
 {
     constexpr uint32_t LANES = ccdc::kPipeLanes;
     extern __shared__ __align__(16) unsigned char smem[];
-    // When the rounds are cut into chunks, each XCD gets a contiguous range of
-    // (chunk, tile) pairs: the tiles of one chunk (adjacent pieces of the same
-    // rows, the same table entries) then run next to each other in time behind one
-    // L2.  With a single chunk the hardware order is kept: all XCDs then sweep the
-    // same window of every row together (measured: 2 % either way).
-    const uint32_t logical = p.chunks > 1 ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x;
+    const uint32_t logical = p.by_xcd ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x;
     const uint32_t tile = logical % p.tiles, chunk = logical / p.tiles;
     const uint32_t lane = threadIdx.x % LANES, wave = wave_uniform(threadIdx.x / LANES);
     if constexpr (TAIL == kSplit) {
         if (tile + 1 == p.tiles) {                   // what the wide columns leave: a few elements of every segment
             const uint32_t x = p.cols * VEC + lane;
-            walk<A, 1, R1, MULTI, true>(V, X, Phi, part, rows, own, p, smem, chunk, wave, lane, x, x < p.ell);
+            walk<A, 1, R1, MULTI, true, KEPT>(V, X, Phi, part, rows, own, p, smem, chunk, wave, lane, x, x < p.ell);
             return;
         }
     }
     const uint32_t c = tile * LANES + lane;
-    walk<A, VEC, R1, MULTI, TAIL == kShort>(V, X, Phi, part, rows, own, p, smem, chunk, wave, lane, c * VEC, c < p.cols);
+    walk<A, VEC, R1, MULTI, TAIL == kShort, KEPT>(V, X, Phi, part, rows, own, p, smem, chunk, wave, lane, c * VEC, c < p.cols);
 }
 
-// Every k_pipeline<A, VEC, R1, *, *> has this signature.
+}  // namespace
+
+namespace ccdc {
+// Every k_pipeline<A, VEC, R1, *, *, *> has this signature.
 template <class A>
 using PipeKernel = void (*)(const typename A::elem *, typename A::elem *, typename A::elem *, typename A::acc *,
                             const int64_t *, const int64_t *, PipeArgs);
+}  // namespace ccdc
+
+namespace {
 
 template <int VEC>
 Tail tail_kind(const ccdc_plan_t *p)
@@ -423,9 +431,28 @@ uint32_t pipeline_tiles(const ccdc_plan_t *p)
     return cdiv(pipeline_cols<VEC>(p), ccdc::kPipeLanes) + (tail_kind<VEC>(p) == kSplit ? 1 : 0);
 }
 
-// The instantiation a plan runs.  Null for an r the kernel is not unrolled for, and where it would spill.
+// Whether the kernel reads V with ordinary loads (KEPT) or past the caches.  Ordinary ones where a pass is small
+// (kKeptBytes), and where rows of V or segments begin inside a cache line: the two tiles on either side of a line
+// then both want it, and with non-temporal loads each fetched it from memory.  One file a batch, 8 nodes, r = 2,
+// past the caches -> kept (with by_xcd, below): T = 800008 bf16 134 -> 110 us, f32 223 -> 212; 16 nodes, r = 3,
+// T = 6148 bf16 49.0 -> 45.0, f32 76 -> 74.  With rows on whole lines, T = 800000, f32 190 -> 199, bf16 98 -> 103.
+// Sixteen-byte packs of four-byte elements on whole sectors (32 bytes) do as well past the caches (T = 800032 f32
+// 201, kept 203), narrower ones do not (16 nodes, r = 3, T = 4096 f32 53.3 -> 50.9; 8 nodes, T = 800064 bf16,
+// segments half a line off, 107.5 -> 103).  Nor does it help with r <= 2 and long batches of wide packs in chunks:
+// each XCD reads few long rows then, and finds the shared lines in its L2 anyway (six nodes, r = 2, 12 files a batch,
+// T = 33592 f32 past the caches 30.8, kept 33.4; 40 files 90, 98).
 template <class A, int VEC>
-PipeKernel<A> pipeline_kernel(const ccdc_plan_t *p)
+bool reads_kept(const ccdc_plan_t *p)
+{
+    if (moved_bytes(p, (double)p->nrows * p->ell + (double)p->Q * p->T) <= kKeptBytes) return true;
+    constexpr int64_t eb = sizeof(typename A::elem), unit = VEC * eb >= 16 ? 32 : 128;
+    if (VEC * eb >= 16 && p->r <= 2 && p->m >= 8 && p->pipe_chunks > 1) return false;
+    return p->W * eb % unit != 0 || p->ell * eb % unit != 0;
+}
+
+// The instantiation a plan runs.  Null for an r the kernel is not unrolled for, and where it would spill.
+template <class A, int VEC, bool KEPT>
+PipeKernel<A> kernel_of(const ccdc_plan_t *p)
 {
     const Tail tail = tail_kind<VEC>(p);
     auto of = [&](auto r1) -> PipeKernel<A> {
@@ -436,14 +463,14 @@ PipeKernel<A> pipeline_kernel(const ccdc_plan_t *p)
             // shapes measured (eight nodes, four files a batch, T = 60000 f32: 101 us at the best geometry of
             // four-element packs, 82 with two, 73 with one), the twentieth 4 % slower.
             if constexpr (VEC == 4 && R1 == 6) return nullptr;
-            else if constexpr (VEC == 1) return k_pipeline<A, VEC, R1, true, kShort>;
-            else return tail == kSplit ? k_pipeline<A, VEC, R1, true, kSplit> : k_pipeline<A, VEC, R1, true, kShort>;
+            else if constexpr (VEC == 1) return k_pipeline<A, VEC, R1, true, kShort, KEPT>;
+            else return tail == kSplit ? k_pipeline<A, VEC, R1, true, kSplit, KEPT> : k_pipeline<A, VEC, R1, true, kShort, KEPT>;
         }
         if constexpr (VEC > 1) {
-            if (tail == kSplit) return k_pipeline<A, VEC, R1, false, kSplit>;
+            if (tail == kSplit) return k_pipeline<A, VEC, R1, false, kSplit, KEPT>;
         }
-        if (tail == kShort) return k_pipeline<A, VEC, R1, false, kShort>;
-        return k_pipeline<A, VEC, R1, false, kWhole>;
+        if (tail == kShort) return k_pipeline<A, VEC, R1, false, kShort, KEPT>;
+        return k_pipeline<A, VEC, R1, false, kWhole, KEPT>;
     };
     switch (p->r + 1) {
     case 2: return of(std::integral_constant<int, 2>());
@@ -453,6 +480,41 @@ PipeKernel<A> pipeline_kernel(const ccdc_plan_t *p)
     case 6: return of(std::integral_constant<int, 6>());
     default: return nullptr;
     }
+}
+
+}  // namespace
+
+namespace ccdc {
+
+// The kernels that keep their reads, as kernel_of<A, VEC, true>; compiled in pieces of their own.
+template <class A>
+PipeKernel<A> pipeline_kernel_kept(const ccdc_plan_t *p, int vec)
+{
+    if (vec == 4) return kernel_of<A, 4, true>(p);
+    if (vec == 2) return kernel_of<A, 2, true>(p);
+    return kernel_of<A, 1, true>(p);
+}
+
+}  // namespace ccdc
+
+#if !defined(CCDC_PIPELINE_PART) || CCDC_PIPELINE_PART < 5
+namespace {
+
+// When the rounds are cut into chunks, each XCD gets a contiguous range of (chunk, tile) pairs: the tiles of one
+// chunk (adjacent pieces of the same rows, the same table entries) then run next to each other in time behind one
+// L2.  The same with a single chunk where adjacent tiles share lines (8 nodes, r = 2, T = 800008 bf16 in the
+// hardware's order 120 us, this way 110; f32 216, 212).  Else the hardware's order is kept: all XCDs then sweep the
+// same window of every row together (2 % better).
+template <class A, int VEC>
+bool by_xcd(const ccdc_plan_t *p)
+{
+    return p->pipe_chunks > 1 || reads_kept<A, VEC>(p);
+}
+
+template <class A, int VEC>
+PipeKernel<A> pipeline_kernel(const ccdc_plan_t *p)
+{
+    return reads_kept<A, VEC>(p) ? pipeline_kernel_kept<A>(p, VEC) : kernel_of<A, VEC, false>(p);
 }
 
 template <class A, int VEC, bool MULTI>
@@ -595,6 +657,7 @@ int run_pipeline(const ccdc_plan_t *p, const void *V, void *X, void *Phi, void *
     args.waves = (uint32_t)p->pipe_waves;
     args.even = p->pipe_even;
     args.shallow = p->pipe_shallow;
+    args.by_xcd = by_xcd<A, VEC>(p);
     args.cols = pipeline_cols<VEC>(p);
     args.file_stride = (int64_t)p->Q * p->T;
     args.chunk_stride = (int64_t)p->K * p->W;
@@ -641,22 +704,34 @@ void pipeline_geometry(ccdc_plan_t *p)
     p->pipe_shallow = best.shallow;
 }
 
+}  // namespace ccdc
+#endif
+
 // The kernel's instantiations take minutes to compile in one piece: with CCDC_PIPELINE_PART set, this
-// file is one of five pieces, each with one algebra (and the first with the entry points).
+// file is one of ten pieces, two for each algebra: its kernels that read past the caches with the code that
+// launches them (the first with the entry points), and those that keep their reads.
+namespace ccdc {
 #ifdef CCDC_PIPELINE_PART
-#define CCDC_PIECE(A)                                                                                            \
+#define CCDC_RUN(A)                                                                                              \
     template int pipeline_run<A>(const ccdc_plan_t *, const void *, void *, void *, void *, bool, hipStream_t); \
     template void pipeline_geometry<A>(ccdc_plan_t *)
-#if CCDC_PIPELINE_PART == 0
-CCDC_PIECE(SumF32);
-#elif CCDC_PIPELINE_PART == 1
-CCDC_PIECE(XorU32);
-#elif CCDC_PIPELINE_PART == 2
-CCDC_PIECE(HybF32);
-#elif CCDC_PIPELINE_PART == 3
-CCDC_PIECE(HybBF16);
+#define CCDC_KEPT(A) template PipeKernel<A> pipeline_kernel_kept<A>(const ccdc_plan_t *, int)
+#if CCDC_PIPELINE_PART % 5 == 0
+using PieceAlgebra = SumF32;
+#elif CCDC_PIPELINE_PART % 5 == 1
+using PieceAlgebra = XorU32;
+#elif CCDC_PIPELINE_PART % 5 == 2
+using PieceAlgebra = HybF32;
+#elif CCDC_PIPELINE_PART % 5 == 3
+using PieceAlgebra = HybBF16;
 #else
-CCDC_PIECE(HybF16);
+using PieceAlgebra = HybF16;
+#endif
+#if CCDC_PIPELINE_PART < 5
+extern CCDC_KEPT(PieceAlgebra);
+CCDC_RUN(PieceAlgebra);
+#else
+CCDC_KEPT(PieceAlgebra);
 #endif
 #if CCDC_PIPELINE_PART == 0
 #define CCDC_ELSEWHERE(A)                                                                                               \
