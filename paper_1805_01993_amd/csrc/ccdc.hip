@@ -16,7 +16,7 @@ using namespace ccdc;
 // Sec. IV-B pre-combining.  One work item = one pack of one packet Vbar[u][b]:
 // it adds the same pack of the files of the served batch (m of them, or
 // row_files[row] when batches differ in size).
-template <class A, int VEC>
+template <class A, int VEC, bool KEPT>
 __global__ __launch_bounds__(kBlock) void k_combine(const typename A::elem *__restrict__ V,
                                                     typename A::elem *__restrict__ Vbar,
                                                     const int64_t *__restrict__ src_off,
@@ -30,13 +30,13 @@ __global__ __launch_bounds__(kBlock) void k_combine(const typename A::elem *__re
     const uint32_t row = idx / Wv, e = idx - row * Wv;
     const typename A::elem *src = V + src_off[row] + (int64_t)e * VEC;
     const int files = row_files ? row_files[row] : m;
-    const P first = load_stream<P>(src);
+    const P first = load_pack<KEPT, P>(src);
     if (files == 1) {                                 // not a sum: the packet is the file's values as they are
         reinterpret_cast<P *>(Vbar)[idx] = first;
         return;
     }
     typename O::Q acc = O::widen(first);
-    for (int f = 1; f < files; f++) acc = O::accum(acc, load_stream<P>(src + f * file_stride));
+    for (int f = 1; f < files; f++) acc = O::accum(acc, load_pack<KEPT, P>(src + f * file_stride));
     reinterpret_cast<P *>(Vbar)[idx] = O::narrow(acc);
 }
 
@@ -48,7 +48,7 @@ __global__ __launch_bounds__(kBlock) void k_combine(const typename A::elem *__re
 // exchanges.  The order of additions is fixed by (m, SEG), not by timing; it
 // differs from k_combine's file order, so the algebras whose packets are coded
 // bit patterns (fixed_order) do not use it.
-template <class A, int VEC>
+template <class A, int VEC, bool KEPT>
 __global__ __launch_bounds__(64) void k_combine_wave(const typename A::elem *__restrict__ V,
                                                      typename A::elem *__restrict__ Vbar,
                                                      const int64_t *__restrict__ src_off, uint32_t Wv, int seg,
@@ -64,7 +64,7 @@ __global__ __launch_bounds__(64) void k_combine_wave(const typename A::elem *__r
     const E *src = V + src_off[row] + (int64_t)e * VEC;
     typename O::Q acc = O::azero();
     if ((uint32_t)e < Wv)
-        for (int f = g; f < m; f += G) acc = O::accum(acc, load_stream<P>(src + f * file_stride));
+        for (int f = g; f < m; f += G) acc = O::accum(acc, load_pack<KEPT, P>(src + f * file_stride));
     // segmented butterfly: after the step with distance d, lane l holds the sum of
     // the segments whose index differs from its own only in the bits below d/seg
     for (int d = seg; d < 64; d <<= 1) {
@@ -185,7 +185,7 @@ __global__ __launch_bounds__(kBlock) void k_decode_sender(const typename A::elem
 // pack of its own packet by removing the other r-1 from the coded pack.
 // R1 = r+1 at compile time keeps the r combined packs in registers; R1 = 0 is
 // the any-r fallback that re-reads them (cache hits) instead.
-template <class A, int VEC, int R1>
+template <class A, int VEC, int R1, bool KEPT>
 __global__ __launch_bounds__(kBlock) void k_shuffle_fused(const typename A::elem *__restrict__ V,
                                                           typename A::elem *__restrict__ X,
                                                           typename A::elem *__restrict__ D,
@@ -207,10 +207,10 @@ __global__ __launch_bounds__(kBlock) void k_shuffle_fused(const typename A::elem
         const uint32_t pos = segment_rank(a, b) * Lv + x;
         if (pos >= Wv) return O::zero();
         const typename A::elem *s = V + src[b] + (int64_t)pos * VEC;
-        const P first = load_stream<P>(s);
+        const P first = load_pack<KEPT, P>(s);
         if (m == 1) return first;                     // a one-file batch is sent as it is
         typename O::Q acc = O::widen(first);
-        for (int f = 1; f < m; f++) acc = O::accum(acc, load_stream<P>(s + f * file_stride));
+        for (int f = 1; f < m; f++) acc = O::accum(acc, load_pack<KEPT, P>(s + f * file_stride));
         return O::narrow(acc);
     };
 
@@ -259,7 +259,7 @@ __global__ __launch_bounds__(kBlock) void k_shuffle_fused(const typename A::elem
 // the node stores), some in D (packets it decoded).  The list is cut into
 // `split` chunks; work item = (o, chunk, pack).  With split > 1 the chunk sums
 // go, not yet narrowed, to the workspace and k_reduce_final adds them in its fixed order.
-template <class A, int VEC>
+template <class A, int VEC, bool KEPT>
 __global__ __launch_bounds__(kBlock) void k_reduce_rows(const typename A::elem *__restrict__ V,
                                                         const typename A::elem *__restrict__ D,
                                                         typename A::elem *__restrict__ out,
@@ -284,7 +284,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce_rows(const typename A::elem *
     for (int64_t i = lo; i < hi; i++) {
         const int64_t row = red_row[i];
         const typename A::elem *base = (row & 1) ? D : V;
-        acc = O::accum(acc, load_stream<P>(reinterpret_cast<const P *>(base + (row >> 1)) + e));
+        acc = O::accum(acc, load_pack<KEPT, P>(reinterpret_cast<const P *>(base + (row >> 1)) + e));
     }
     if (split > 1) reinterpret_cast<typename O::Q *>(part + (int64_t)s * chunk_stride + red_out[o])[e] = acc;
     else reinterpret_cast<P *>(out + red_out[o])[e] = O::narrow(acc);
@@ -346,6 +346,7 @@ int run_combine(const ccdc_plan_t *p, const void *V, void *Vbar, hipStream_t st)
     const uint64_t items = (uint64_t)p->nrows * Wv;
     if (items == 0) return CCDC_OK;
     if (!fits_launch(items)) return CCDC_ESIZE;
+    const bool kept = moved_bytes(p, (double)p->nrows * p->W) <= kKeptStageBytes;        // V and Vbar
     // short packets, long batches: a wavefront per packet with a cross-lane reduction
 #ifndef CCDC_COMBINE_WAVE_MIN_FILES
 #define CCDC_COMBINE_WAVE_MIN_FILES 8
@@ -355,13 +356,17 @@ int run_combine(const ccdc_plan_t *p, const void *V, void *Vbar, hipStream_t st)
             int seg = 1;
             while ((uint32_t)seg < Wv) seg <<= 1;
             const uint32_t rows = (uint32_t)p->nrows;
-            k_combine_wave<A, VEC><<<rows, 64, 0, st>>>((const E *)V, (E *)Vbar, p->d_src_off, Wv, seg, p->m,
-                                                        (int64_t)p->Q * p->T, rows);
+            by_reads<VEC>(kept, [&](auto k) {
+                k_combine_wave<A, VEC, decltype(k)::value><<<rows, 64, 0, st>>>(
+                    (const E *)V, (E *)Vbar, p->d_src_off, Wv, seg, p->m, (int64_t)p->Q * p->T, rows);
+            });
             return launched();
         }
     }
-    k_combine<A, VEC><<<cdiv(items, kBlock), kBlock, 0, st>>>((const E *)V, (E *)Vbar, p->d_src_off, p->d_row_files,
-                                                               Wv, p->m, (int64_t)p->Q * p->T, (uint32_t)items);
+    by_reads<VEC>(kept, [&](auto k) {
+        k_combine<A, VEC, decltype(k)::value><<<cdiv(items, kBlock), kBlock, 0, st>>>(
+            (const E *)V, (E *)Vbar, p->d_src_off, p->d_row_files, Wv, p->m, (int64_t)p->Q * p->T, (uint32_t)items);
+    });
     return launched();
 }
 
@@ -408,8 +413,11 @@ void launch_shuffle(const ccdc_plan_t *p, const void *V, void *X, void *D, hipSt
     using E = typename A::elem;
     const uint32_t Wv = (uint32_t)(p->W / VEC), Lv = (uint32_t)(p->ell / VEC);
     const uint64_t items = (uint64_t)p->nround * (p->r + 1) * Lv;
-    k_shuffle_fused<A, VEC, R1><<<cdiv(items, kBlock), kBlock, 0, st>>>(
-        (const E *)V, (E *)X, (E *)D, p->d_src_off, p->r + 1, Lv, Wv, p->m, (int64_t)p->Q * p->T, (uint32_t)items);
+    const bool kept = moved_bytes(p, (double)p->nrows * (p->W + p->ell)) <= kKeptStageBytes;        // V, X and D
+    by_reads<VEC>(kept, [&](auto k) {
+        k_shuffle_fused<A, VEC, R1, decltype(k)::value><<<cdiv(items, kBlock), kBlock, 0, st>>>(
+            (const E *)V, (E *)X, (E *)D, p->d_src_off, p->r + 1, Lv, Wv, p->m, (int64_t)p->Q * p->T, (uint32_t)items);
+    });
 }
 
 template <class A, int VEC>
@@ -441,9 +449,12 @@ int run_reduce(const ccdc_plan_t *p, const void *V, const void *D, void *Phi, hi
     if (!fits_launch(blocks) || !fits_launch((uint64_t)chunk_stride / VEC)) return CCDC_ESIZE;
     using Acc = typename A::acc;
     WorkspaceOrder order(p, st, split > 1);
-    k_reduce_rows<A, VEC><<<(uint32_t)blocks, kBlock, 0, st>>>((const E *)V, (const E *)D, (E *)Phi,
-                                                                (Acc *)p->d_workspace, p->d_red_ptr, p->d_red_row,
-                                                                p->d_red_out, Wv, tiles, split, chunk_stride);
+    const bool kept = moved_bytes(p, (double)p->nrows * p->W + (double)chunk_stride) <= kKeptStageBytes;        // V, D, Phi
+    by_reads<VEC>(kept, [&](auto k) {
+        k_reduce_rows<A, VEC, decltype(k)::value><<<(uint32_t)blocks, kBlock, 0, st>>>(
+            (const E *)V, (const E *)D, (E *)Phi, (Acc *)p->d_workspace, p->d_red_ptr, p->d_red_row, p->d_red_out, Wv, tiles,
+            split, chunk_stride);
+    });
     int rc = launched();
     if (rc != CCDC_OK || split == 1) return rc;
     const uint64_t items = (uint64_t)chunk_stride / VEC;

@@ -25,7 +25,7 @@ using namespace ccdc;
 // the XCDs in turn (480 with groups of 64), 461 this way (6.3 TB/s); 28 files of 25.6 M bf16 values 510, 463.  Four files a work
 // item were 2 % faster on 28 files of 25.6 M bf16 values and up to 8 % slower elsewhere.
 constexpr uint32_t kMapGroup = 256;
-template <class A, int VEC>
+template <class A, int VEC, bool KEPT>
 __global__ __launch_bounds__(kBlock) void k_map(const typename A::elem *files,      // may be V itself
                                                 const typename A::elem *__restrict__ theta,
                                                 typename A::elem *V, uint32_t model_packs, uint32_t tiles,
@@ -42,7 +42,7 @@ __global__ __launch_bounds__(kBlock) void k_map(const typename A::elem *files,  
     if (e >= model_packs) return;
     const uint32_t job = row / files_per_job;
     const size_t at = (size_t)row * model_packs + e;
-    const P data = load_stream<P>(reinterpret_cast<const P *>(files) + at);
+    const P data = load_pack<KEPT, P>(reinterpret_cast<const P *>(files) + at);
     const P model = reinterpret_cast<const P *>(theta)[(size_t)job * model_packs + e];
     store_stream(reinterpret_cast<P *>(V) + at, O::gradient(model, data));
 }
@@ -56,9 +56,12 @@ int run_map(const ccdc_plan_t *p, const void *files, const void *theta, void *V,
     const uint64_t tiles = (model_packs + kBlock - 1) / kBlock, groups = (tiles + kMapGroup - 1) / kMapGroup;
     if (!fits_launch(rows * groups * kMapGroup)) return CCDC_ESIZE;
     const uint64_t group_tiles = (tiles + groups - 1) / groups;      // equal groups: no workgroups without work
-    k_map<A, VEC><<<(uint32_t)(rows * groups * group_tiles), kBlock, 0, st>>>(
-        (const E *)files, (const E *)theta, (E *)V, (uint32_t)model_packs, (uint32_t)tiles, (uint32_t)rows, (uint32_t)p->N,
-        (uint32_t)group_tiles);
+    const bool kept = moved_bytes(p, (double)p->J * p->Q * p->T) <= kKeptStageBytes;        // files and models
+    by_reads<VEC>(kept, [&](auto k) {
+        k_map<A, VEC, decltype(k)::value><<<(uint32_t)(rows * groups * group_tiles), kBlock, 0, st>>>(
+            (const E *)files, (const E *)theta, (E *)V, (uint32_t)model_packs, (uint32_t)tiles, (uint32_t)rows,
+            (uint32_t)p->N, (uint32_t)group_tiles);
+    });
     return launched();
 }
 
