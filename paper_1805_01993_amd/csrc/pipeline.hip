@@ -557,6 +557,11 @@ bool long_packets(const ccdc_plan_t *p)
 // r = 4, T = 344 h32: 101 -> 77).  It also serves r = 5 with several files, where four-element packs are
 // missing (0.94 of the time over 20 shapes), and r = 1 with several files and long packets (see kLongPacket).  Elsewhere it gave nothing: with r <= 2 1.00 of the time over
 // 72 shapes, three of them 9 to 18 % slower; below 200 MB 1.00; with several files and r = 4 up to 20 % slower.
+// The third set is for what the second leaves of r >= 3 and more than 40 running outputs a lane, where LDS holds few
+// wavefronts; fitted with reads kept or not and with workgroups of up to 160 KB of LDS.  Over 116 shapes 0.92 of the
+// first set's time, 95 of them over 3 % faster, the slowest 5 % slower (16 nodes, r = 4, T = 257 bf16, six files a batch
+// 61 -> 34 us; 16 nodes, r = 3, T = 4096 f32 50.7 -> 46.7).  With 40 outputs and fewer it gave 0.96, with r <= 2 0.98,
+// some shapes over 20 % slower.
 struct Candidate {
     int vec, waves, chunks;
     bool even, shallow;
@@ -591,14 +596,23 @@ void consider(const ccdc_plan_t *p, Candidate *best)
     const double used = (double)(p->ell / VEC) / (cdiv(p->ell / VEC, ccdc::kPipeLanes) * ccdc::kPipeLanes);    // share of lanes with work
     const double flight = (shallow ? 1 : depth) * r1 * p->r * ccdc::kPipeLanes * VEC * elem * used;                // bytes a wavefront has on the way
     constexpr int width = VEC * elem >= 16 ? 3 : VEC * elem == 8 ? 2 : VEC * elem == 4 ? 1 : 0;
-    constexpr double peaks[2][4] = {{3.2e6, 4.2e6, 5.3e6, 6.5e6}, {4.2e6, 4.8e6, 6.2e6, 9.0e6}};        // B/us
-    double peak = peaks[large][width] * (large ? used : std::pow(used, 0.3));
+    const bool deep = !large && p->r >= 3 && p->K * p->r > 40;       // the third set of constants
+    constexpr double peaks[4][4] = {                 // B/us
+        {3.2e6, 4.2e6, 5.3e6, 6.5e6}, {4.2e6, 4.8e6, 6.2e6, 9.0e6},
+        {3.6e6, 4.0e6, 5.65e6, 13.8e6}, {3.3e6, 5.85e6, 8.45e6, 23.7e6}};                // deep: past the caches, through them
+    double peak = peaks[large ? 1 : !deep ? 0 : reads_kept<A, VEC>(p) ? 3 : 2][width];
+    peak *= large ? used : std::pow(used, deep ? 0.25 : 0.3);
     if (p->T * elem % 8)                             // rows start anywhere: more lines an access
-        peak *= 1 - (!large ? 0.4 : width == 0 ? 0.45 : 0.25) * std::min(1.0, 8.0 / (VEC * elem));
+        peak *= 1 - (deep ? 0.2 : !large ? 0.4 : width == 0 ? 0.45 : 0.25) * std::min(1.0, 8.0 / (VEC * elem));
+    // A workgroup may take most of a compute unit's LDS where the third set ranks, and with r = 2 on large inputs (18
+    // nodes, two functions each, T = 45440 f16 150 -> 133 us).  Elsewhere 64 KB stay the limit: with r = 1 (22 nodes,
+    // T = 240608 bf16 89 -> 106), on small inputs (9 nodes, r = 2, T = 21340 f32 12.0 -> 16.1) and where the second
+    // set ranks (9 nodes, r = 5, T = 697096 bf16 322 -> 441).
+    const size_t most_lds = deep || (p->r == 2 && bytes >= kLargeInput) ? ccdc::kPipeGroupLds : ccdc::kPipeMaxLds;
     const double issue = tiles * (rows * p->r + R * r1) * 0.012 / cus;       // us a compute unit takes to issue the loads and stores
-    for (int waves = 1; waves <= ccdc::kPipeMaxWaves && waves * lds <= (size_t)ccdc::kPipeMaxLds; waves++) {
-        const size_t granule = large ? ccdc::kLdsGranule : 1;
-        const int by_lds = (int)(ccdc::kCuLds / ((waves * lds + granule - 1) / granule * granule)), by_regs = limit / waves;
+    for (int waves = 1; waves <= ccdc::kPipeMaxWaves && waves * lds <= most_lds; waves++) {
+        const size_t granule = large || deep ? ccdc::kLdsGranule : 1, group_lds = (waves * lds + granule - 1) / granule * granule;
+        const int by_lds = (int)(ccdc::kCuLds / group_lds), by_regs = limit / waves;
         const int per_cu = std::max(1, std::min(by_lds, by_regs));
         const double room = (double)cus * per_cu * waves;                            // wavefronts in flight at most
         int64_t last = 0;
@@ -615,13 +629,19 @@ void consider(const ccdc_plan_t *p, Candidate *best)
             const double steps = c.even ? std::ceil(per) * m + own / shares / r1 : std::ceil(rows / shares / (r1 * m)) * m;
             const double uneven = steps / (rows / r1 / shares), full = gens / std::ceil(gens);    // how full the generations are
             const double slots = gens * p->K * p->r * 4 * VEC, outputs = 2.0 * chunks * p->K * p->W * 4;
-            const double latency = !large ? 0.8 : longp ? 0.1 : 0.2;                  // us
-            const double rate = std::sqrt(full) / (latency / (std::min(w, room) * flight) + 1 / peak);
+            const double latency = deep ? 0.7 : !large ? 0.8 : longp ? 0.1 : 0.2;      // us
+            const double rate = std::pow(full, deep ? 1.8 : 0.5) / (latency / (std::min(w, room) * flight) + 1 / peak);
             if (large) {
                 const double stream = bytes / rate * std::pow(uneven, 0.36);
                 const double chain = 2.2 * gens * (steps / depth + 1);                // waits one after the other
                 c.us = std::max({stream, chain, issue}) + 0.018 * slots;
                 if (chunks > 1) c.us += 2 + outputs / 4.6e6;
+            } else if (deep) {
+                const double stream = bytes / rate * std::pow(uneven, 0.25);
+                const double chain = 0.83 * gens * (steps / depth + 0.8);
+                c.us = std::pow(std::pow(stream, 1.44) + std::pow(chain, 1.44), 1 / 1.44) + 0.053 * slots;
+                c.us += 0.42 * (double)group_lds / 65536 * std::ceil(gens);           // slots to clear and add up, a group after the other
+                if (chunks > 1) c.us += 3.8 + outputs / 1.34e6;
             } else {
                 const double stream = bytes / rate * std::pow(uneven, 0.08);
                 const double chain = 0.8 * gens * (steps / depth + 1);

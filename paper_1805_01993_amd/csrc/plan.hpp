@@ -98,7 +98,12 @@ int bind_plan(ccdc_plan_t *p, int64_t T, int mode);
 // Limits of the one-pass pipeline kernel.
 constexpr int kPipeLanes = 64;                 // columns of a tile: one wavefront wide
 constexpr int kPipeMaxWaves = 8;               // wavefronts of a workgroup
-constexpr int kPipeMaxLds = 64 * 1024;         // bytes of LDS one workgroup may take
+constexpr int kPipeMaxLds = 64 * 1024;         // bytes of LDS one wavefront may take
+#ifdef __HIP__
+constexpr int kPipeGroupLds = 160 * 1024;      // bytes of LDS one workgroup may take: all that gfx950 has
+#else
+constexpr int kPipeGroupLds = 64 * 1024;       // what the CPU build of the kernels grants
+#endif
 constexpr int kCuLds = 160 * 1024;             // bytes of LDS of a compute unit
 constexpr int kLdsGranule = 1280;              // bytes it is given out in
 constexpr int kPipeMaxR1 = 6;                  // r+1 the kernel is unrolled for
