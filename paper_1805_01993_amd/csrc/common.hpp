@@ -393,7 +393,7 @@ inline int ready(const ccdc_plan_t *p)
 
 inline int elem_bytes(int mode) { return (mode == CCDC_BF16_SUM_XOR || mode == CCDC_F16_SUM_XOR) ? 2 : 4; }
 
-// Non-temporal loads pass the last-level cache (256 MB) by, ordinary ones leave the data there.  A call whose
+// kKeptBytes, kKeptStageBytes: non-temporal loads pass the last-level cache (256 MB) by, ordinary ones leave the data there.  A call whose
 // inputs and outputs take no more than this therefore reads with ordinary loads: its inputs are then often still
 // there from the call that made them.  Measured with three sets of buffers used in turn.  One-pass kernel, 8 nodes,
 // r = 2, one file a batch, f32: 64 MB a pass 14.5 -> 12.6 us, 129 MB 24.1 -> 23.4, but 194 MB 43.1 -> 46.2 and 1 GB
@@ -401,7 +401,6 @@ inline int elem_bytes(int mode) { return (mode == CCDC_BF16_SUM_XOR || mode == C
 // uncoded, 13 nodes, T = 780 u32 (17 MB of values) 23.5 -> 18.3 us, six nodes, T = 24256 u32 (50 MB a call) 33 -> 24,
 // a step from files on 24 nodes (43 MB read) 47 -> 41, but the four stages at 87 MB a call (12 nodes, T = 6000 f16)
 // 43.7 -> 46.4.
-constexpr double kKeptBytes = 128e6, kKeptStageBytes = 64e6;
 
 // The bytes a call that reads V moves, with `elements` of other inputs and outputs.
 inline double moved_bytes(const ccdc_plan_t *p, double elements)

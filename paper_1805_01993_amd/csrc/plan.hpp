@@ -99,14 +99,19 @@ int bind_plan(ccdc_plan_t *p, int64_t T, int mode);
 constexpr int kPipeLanes = 64;                 // columns of a tile: one wavefront wide
 constexpr int kPipeMaxWaves = 8;               // wavefronts of a workgroup
 constexpr int kPipeMaxLds = 64 * 1024;         // bytes of LDS one wavefront may take
-#ifdef __HIP__
 constexpr int kPipeGroupLds = 160 * 1024;      // bytes of LDS one workgroup may take: all that gfx950 has
-#else
-constexpr int kPipeGroupLds = 64 * 1024;       // what the CPU build of the kernels grants
-#endif
 constexpr int kCuLds = 160 * 1024;             // bytes of LDS of a compute unit
 constexpr int kLdsGranule = 1280;              // bytes it is given out in
 constexpr int kPipeMaxR1 = 6;                  // r+1 the kernel is unrolled for
+
+// Bytes up to which a call reads with ordinary loads (the rules that use them, with both sides measured, are in
+// common.hpp and pipeline.hip).  The CPU build of the kernels makes variables of them, to run either side on small inputs.
+#ifdef CCDC_VARIABLE_READ_LIMITS
+#define CCDC_READ_LIMIT inline double
+#else
+#define CCDC_READ_LIMIT constexpr double
+#endif
+CCDC_READ_LIMIT kKeptBytes = 128e6, kKeptStageBytes = 64e6;
 
 // One-pass pipeline (pipeline.hip): fixes the launch geometry (pipe_vec .. pipe_shallow) for the current device.
 void pipeline_prepare(ccdc_plan_t *p);

@@ -4,6 +4,8 @@
 // Usage: driver K r Q N T mode jobs [cus blocks_per_cu [geometry ...]]  (mode: 0 f32, 1 u32, 2 h32, 3 bf16, 4 f16)
 // A geometry is pack,wavefronts,chunks,flags as in CCDC_Q_PIPELINE_LAUNCH: only the one-pass kernel runs then,
 // as uploaded and with each geometry forced into the plan, against ccdc_combine + ccdc_encode and the plain sum.
+// SHIM_PAST=1: no input is small enough to be read through the caches for its size.  "streamed C n" says that call C made
+// n non-temporal loads.
 // Test infrastructure only.
 #include <hip/hip_runtime.h>
 
@@ -95,7 +97,8 @@ static bool force_geometry(ccdc_plan_t *p, const char *text)
     int pack, waves, chunks, flags;
     if (std::sscanf(text, "%d,%d,%d,%d", &pack, &waves, &chunks, &flags) != 4) return false;
     if ((pack != 1 && pack != 2 && pack != 4) || p->ell < pack || chunks < 1 || chunks > p->pipe_max_chunks || waves < 1 ||
-        waves > ccdc::kPipeMaxWaves || p->K * p->r * ccdc::kPipeLanes * pack * 4 * waves > ccdc::kPipeMaxLds)
+        waves > ccdc::kPipeMaxWaves || p->K * p->r * ccdc::kPipeLanes * pack * 4 * waves > ccdc::kPipeGroupLds ||
+        p->K * p->r * ccdc::kPipeLanes * pack * 4 > ccdc::kPipeMaxLds)
         return false;
     p->pipe_vec = pack;
     p->pipe_waves = waves;
@@ -146,6 +149,7 @@ int main(int argc, char **argv)
         shim::compute_units = atoi(argv[8]);
         shim::blocks_per_cu = atoi(argv[9]);
     }
+    if (std::getenv("SHIM_PAST")) ccdc::kKeptBytes = ccdc::kKeptStageBytes = 0;
     const bool half = mode >= 3, real = mode != 1;
     const size_t eb = half ? 2 : 4;
 
@@ -235,6 +239,8 @@ int main(int argc, char **argv)
         }
     };
 
+    auto streamed = [&](const char *name) { std::printf("streamed %s %ld\n", name, shim::streaming_loads.exchange(0)); };
+
     // SHIM_ONLY_PIPELINE=1: only the one-pass pipeline, checked against the plain sum (for shapes
     // at which the staged kernels, one emulated thread per work item, would take too long)
     if (std::getenv("SHIM_ONLY_PIPELINE")) {
@@ -248,22 +254,28 @@ int main(int argc, char **argv)
         return bad ? 1 : 0;
     }
     CHECK(ccdc_combine(p, V, Vbar, nullptr));
+    streamed("combine");
     CHECK(ccdc_encode(p, Vbar, X, nullptr));
     const bool only_pipeline = argc > 10;
     if (!only_pipeline) {
         CHECK(ccdc_decode(p, X, Vbar, D, nullptr));
+        shim::streaming_loads = 0;
         CHECK(ccdc_reduce(p, V, D, Phi, nullptr));
+        streamed("reduce");
         check_phi(Phi, "staged Phi");
         same(D, Vbar, nd, "decoded packets vs pre-combined packets");
 
         CHECK(ccdc_shuffle_fused(p, V, X2, D2, nullptr));
+        streamed("shuffle");
         CHECK(ccdc_reduce(p, V, D2, Phi2, nullptr));
         same(X2, X, nx, "fused X");
         same(D2, D, nd, "fused D");
         check_phi(Phi2, "fused Phi");
     }
 
+    shim::streaming_loads = 0;
     const int rc = ccdc_pipeline_fused(p, V, X3, Phi3, nullptr);
+    if (rc == CCDC_OK) streamed("pipeline");
     if (rc == CCDC_OK) {
         same(X3, X, nx, "pipeline X");
         check_phi(Phi3, "pipeline Phi");
@@ -287,7 +299,9 @@ int main(int argc, char **argv)
         }
         std::memset(X3, 0xA5, (size_t)nx * eb);
         std::memset(Phi3, 0xA5, (size_t)nphi * eb);
+        shim::streaming_loads = 0;
         CHECK(ccdc_pipeline_fused(p, V, X3, Phi3, nullptr));
+        streamed(argv[i]);
         same(X3, X, nx, argv[i]);
         check_phi(Phi3, argv[i]);
         CHECK(ccdc_pipeline_fused_noalloc(p, V, X4, Phi4, nullptr));
@@ -296,8 +310,11 @@ int main(int argc, char **argv)
     }
 
     if (!only_pipeline) {
+        shim::streaming_loads = 0;
         CHECK(ccdc_node_encode(p, -1, V, X5, nullptr));
+        streamed("node-encode");
         CHECK(ccdc_node_decode_reduce(p, -1, V, X5, Phi5, nullptr));
+        streamed("node-decode");
         same(X5, X, nx, "node-local X");
         check_phi(Phi5, "node-local Phi");
     }
@@ -307,7 +324,9 @@ int main(int argc, char **argv)
         unsigned char *theta = dev(nphi), *out = dev(nv), *inpl = dev(nv);
         for (int64_t i = 0; i < nphi; i++) std::memcpy(theta + i * eb, V + ((i * 7) % nv) * eb, eb);   // any valid patterns
         std::memcpy(inpl, V, (size_t)nv * eb);
+        shim::streaming_loads = 0;
         CHECK(ccdc_map(p, V, theta, out, nullptr));
+        streamed("map");
         CHECK(ccdc_map(p, inpl, theta, inpl, nullptr));
         same(inpl, out, nv, "map in place");
         for (int64_t j = 0; j < J; j++)

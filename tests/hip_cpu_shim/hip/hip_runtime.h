@@ -55,11 +55,18 @@ extern int compute_units;                               // what the device attri
 extern int blocks_per_cu;                               // what the occupancy query answers
 extern size_t max_dynamic_lds;                          // launches asking for more are refused
 extern std::atomic<long> launches;
+extern std::atomic<long> streaming_loads;               // non-temporal loads the kernels made
 extern bool dry_run;                                     // launches are checked and counted, not run
 void barrier_wait();                                    // __syncthreads()
 void *block_static(size_t bytes);                       // the running workgroup's static __shared__ array
 uint32_t shuffle_xor(uint32_t v, int mask);             // all lanes of the workgroup call it together
 void launch(dim3 grid, dim3 block, size_t lds, const std::function<void()> &body);
+template <class B>
+__attribute__((always_inline)) inline auto streaming_load(const B *p)
+{
+    streaming_loads.fetch_add(1, std::memory_order_relaxed);
+    return __builtin_nontemporal_load(p);
+}
 }  // namespace shim
 
 inline void __syncthreads() { shim::barrier_wait(); }

@@ -11,8 +11,8 @@ namespace shim {
 thread_local unsigned char *dyn_smem = nullptr;
 int compute_units = 8;
 int blocks_per_cu = 4;
-size_t max_dynamic_lds = 64 * 1024;
-std::atomic<long> launches{0};
+size_t max_dynamic_lds = 160 * 1024;
+std::atomic<long> launches{0}, streaming_loads{0};
 bool dry_run = false;
 
 namespace {

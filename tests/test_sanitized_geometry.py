@@ -23,6 +23,8 @@ CASES = [
     (5, 2, 5, 10, 512, 1, 0, 8, 8),       # node-local: segments of exactly one wavefront of packs
     (6, 3, 6, 20, 804, 2, 0, 8, 8),       # node-local: one pack past a wavefront (lane-packed kernels)
     (4, 2, 4, 6, 400, 0, 1, 8, 8),        # the J-job schedule: node-local kernels over several jobs
+    (9, 5, 9, 126, 333, 0, 0, 256, 8),    # more than 40 running outputs a lane
+    (14, 3, 14, 364, 192, 3, 0, 256, 8),
 ]
 
 
@@ -35,18 +37,21 @@ def test_geometries_under_sanitizers(kernel_driver, case):  # noqa: F811
 
 
 # Value lengths, per r: whole segments of 264 elements (66 four-element packs: a full column tile and a part one), a
-# last segment four elements short, one that no pack width divides.
-LENGTHS = {"whole": lambda r: 264 * r, "short": lambda r: 264 * r - 4 if r > 1 else 260, "split": lambda r: 264 * r - 3}
+# last segment four elements short, one that no pack width divides, whole segments on whole cache lines.
+LENGTHS = {"whole": lambda r: 264 * r, "short": lambda r: 264 * r - 4 if r > 1 else 260, "split": lambda r: 264 * r - 3,
+           "lines": lambda r: 320 * r}
 # pack, wavefronts, chunks, flags (1: equal shares, 2: one step in flight where the kernel has that form)
 FORMS = ["4,1,1,3", "4,2,3,2", "4,1,1,1", "4,1,1,0", "4,2,1,1", "4,1,3,0", "2,1,1,1", "2,3,1,0", "2,2,2,1", "2,1,5,0", "1,1,1,1", "1,6,1,0", "1,2,3,1"]
 
 
+@pytest.mark.parametrize("past", [False, True], ids=["kept", "past"])
 @pytest.mark.parametrize("m", [1, 3])
 @pytest.mark.parametrize("r", [1, 2, 3, 4, 5])
-def test_forms_of_the_one_pass_kernel(kernel_driver, r, m):  # noqa: F811
+def test_forms_of_the_one_pass_kernel(kernel_driver, r, m, past):  # noqa: F811
     """C(7, r+1) rounds: one wavefront alone has 7 to 35 rounds, or 21 to 105 steps of one file, one of six has one or
-    two rounds; up to six steps are in flight."""
+    two rounds; up to six steps are in flight.  As small inputs are read and as large ones are."""
     K = 7
+    env = dict(os.environ, **ENV, **({"SHIM_PAST": "1"} if past else {}))
 
     def run(k, end):
         T, mode = LENGTHS[end](r), (r + k + m) % 5
@@ -58,10 +63,37 @@ def test_forms_of_the_one_pass_kernel(kernel_driver, r, m):  # noqa: F811
         assert any(f[0] == "4" for f in forms) or (r == 5 and m > 1)
         assert any(f[0] == "2" for f in forms)
         args = (K, r, K, m * comb(K, r), T, mode, 0, 8, 8)
-        return subprocess.run([kernel_driver] + [str(v) for v in args] + forms, capture_output=True, text=True,
-                              env=dict(os.environ, **ENV), timeout=600)
+        res = subprocess.run([kernel_driver] + [str(v) for v in args] + forms, capture_output=True, text=True,
+                             env=env, timeout=600)
+        assert res.returncode == 0, res.stdout + res.stderr
+        assert " 0 mismatches" in res.stdout, res.stdout
+        streamed = {l.split()[1]: int(l.split()[2]) for l in res.stdout.splitlines() if l.startswith("streamed")}
+        for f in forms:
+            if not past:
+                assert streamed[f] == 0
+            elif end == "lines":
+                assert streamed[f] > 0
 
-    with ThreadPoolExecutor(3) as pool:
-        for res in pool.map(run, range(3), LENGTHS):
-            assert res.returncode == 0, res.stdout + res.stderr
-            assert " 0 mismatches" in res.stdout, res.stdout
+    with ThreadPoolExecutor(4) as pool:
+        list(pool.map(run, range(4), LENGTHS))
+
+
+# Workgroups of 64 to 160 KB of LDS
+LARGE_GROUPS = [
+    ((9, 5, 9, 126, 5 * 264 - 3, 0), ["4,2,1,0", "4,3,2,1", "2,6,1,0", "2,7,3,1"]),
+    ((9, 5, 9, 252, 5 * 264 - 4, 1), ["2,3,1,0", "2,7,2,0"]),
+    ((14, 3, 14, 364, 3 * 264, 4), ["4,2,3,0", "4,3,1,1", "2,7,1,0"]),
+    ((14, 3, 14, 728, 3 * 264 - 3, 2), ["4,3,2,0", "2,4,1,0"]),
+]
+
+
+@pytest.mark.parametrize("args,forms", LARGE_GROUPS, ids=lambda v: "-".join(map(str, v)))
+def test_large_workgroups_under_sanitizers(kernel_driver, args, forms):  # noqa: F811
+    K, r = args[:2]
+    for f in forms:
+        pack, waves, _, _ = map(int, f.split(","))
+        assert 65536 < K * r * 256 * pack * waves <= 160 * 1024
+    res = subprocess.run([kernel_driver] + [str(v) for v in args + (0, 8, 8)] + forms, capture_output=True, text=True,
+                         env=dict(os.environ, **ENV), timeout=600)
+    assert res.returncode == 0, res.stdout + res.stderr
+    assert " 0 mismatches" in res.stdout, res.stdout
