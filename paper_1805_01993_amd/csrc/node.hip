@@ -10,24 +10,26 @@
 namespace {
 using namespace ccdc;
 
-// All reads here are ordinary loads: each of the r nodes that store a file, or receive a coded packet, reads it again,
-// and a segment shares lines with its neighbours.  A pass of both calls, past the caches -> through them: 16 nodes,
-// r = 3, T = 4096 h32 102 -> 89 us; nine nodes, r = 5, T = 17728 f32 111 -> 90; eight nodes, r = 3, T = 664680 f16
-// (0.6 GB of values) 317 -> 297; 22 nodes, r = 1, T = 192358 u32 316 -> 310.
+// What a call reads with ordinary loads, through the caches; the rest goes past them.
+enum Reads {
+    kPast = 0,                        // nothing
+    kCoded = 1,                       // the coded packets
+    kAll = 2,                         // and the files
+};
 
 // Pack `pos` of the packet pre-combined for a round member from the batch that
 // starts at element offset `src` of V (files ascending, narrowed once).
-template <class A, int VEC>
+template <class A, int VEC, bool KEPT>
 __device__ __forceinline__ typename Ops<A, VEC>::P combined_pack(const typename A::elem *__restrict__ V, int64_t src,
                                                                  uint32_t pos, int m, int64_t file_stride)
 {
     using O = Ops<A, VEC>;
     using P = typename O::P;
     const typename A::elem *s = V + src + (int64_t)pos * VEC;
-    const P first = load_pack<true, P>(s);
+    const P first = load_pack<KEPT, P>(s);
     if (m == 1) return first;                         // a one-file batch is sent as it is
     typename O::Q acc = O::widen(first);
-    for (int f = 1; f < m; f++) acc = O::accum(acc, load_pack<true, P>(s + f * file_stride));
+    for (int f = 1; f < m; f++) acc = O::accum(acc, load_pack<KEPT, P>(s + f * file_stride));
     return O::narrow(acc);
 }
 
@@ -36,7 +38,7 @@ __device__ __forceinline__ typename Ops<A, VEC>::P combined_pack(const typename 
 // node sends; null = every packet).  One work item = one pack of X[u][a]: the
 // sender pre-combines, for each other member b, the segment of b's packet that
 // carries the sender's label; it stores all those batches.
-template <class A, int VEC>
+template <class A, int VEC, int READS>
 __global__ __launch_bounds__(kBlock) void k_node_encode(const typename A::elem *__restrict__ V,
                                                         typename A::elem *__restrict__ X,
                                                         const int64_t *__restrict__ src_off,
@@ -56,7 +58,7 @@ __global__ __launch_bounds__(kBlock) void k_node_encode(const typename A::elem *
     for (int b = 0; b < r1; b++) {
         if (b == a) continue;
         const uint32_t pos = segment_rank(a, b) * Lv + x;
-        if (pos < Wv) coded = O::code(coded, combined_pack<A, VEC>(V, src[b], pos, m, file_stride));
+        if (pos < Wv) coded = O::code(coded, combined_pack<A, VEC, READS == kAll>(V, src[b], pos, m, file_stride));
     }
     store_stream(reinterpret_cast<P *>(X) + (size_t)i * Lv + x, coded);
 }
@@ -70,7 +72,7 @@ __global__ __launch_bounds__(kBlock) void k_node_encode(const typename A::elem *
 // is recovered here as that sender's coded pack minus the packs of the other
 // members' packets in it, which the receiver pre-combines from its own files.
 // The list is cut into `split` chunks as in ccdc_reduce.
-template <class A, int VEC>
+template <class A, int VEC, int READS>
 __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
     const typename A::elem *__restrict__ V, const typename A::elem *__restrict__ X, typename A::elem *__restrict__ out,
     typename A::acc *__restrict__ part, const int64_t *__restrict__ red_ptr, const int64_t *__restrict__ red_row,
@@ -94,7 +96,7 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
     for (int64_t i = lo; i < hi; i++) {
         const int64_t row = red_row[i];
         if (!(row & 1)) {                                    // a file the node stores
-            acc = O::accum(acc, load_pack<true, P>(reinterpret_cast<const P *>(V + (row >> 1)) + e));
+            acc = O::accum(acc, load_pack<READS == kAll, P>(reinterpret_cast<const P *>(V + (row >> 1)) + e));
             continue;
         }
         const int64_t pk = (row >> 1) / W;                   // packet u*(r+1)+b meant for this node
@@ -102,11 +104,11 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
         const int b = (int)(pk - (int64_t)u * r1);
         const int a = (int)rho < b ? (int)rho : (int)rho + 1;
         const int64_t *src = src_off + (size_t)u * r1;
-        P d = load_pack<true, P>(reinterpret_cast<const P *>(X) + ((size_t)u * r1 + a) * Lv + x);
+        P d = load_pack<READS != kPast, P>(reinterpret_cast<const P *>(X) + ((size_t)u * r1 + a) * Lv + x);
         for (int b2 = 0; b2 < r1; b2++) {
             if (b2 == a || b2 == b) continue;
             const uint32_t pos = segment_rank(a, b2) * Lv + x;
-            if (pos < Wv) d = O::uncode(d, combined_pack<A, VEC>(V, src[b2], pos, m, file_stride));
+            if (pos < Wv) d = O::uncode(d, combined_pack<A, VEC, READS == kAll>(V, src[b2], pos, m, file_stride));
         }
         acc = O::accum(acc, d);
     }
@@ -133,7 +135,7 @@ inline bool fills_wavefronts(uint32_t Lv)
     return (uint64_t)Lv * 4 >= lanes * 3;
 }
 
-template <class A, int VEC, int R1, bool MULTI>
+template <class A, int VEC, int R1, bool MULTI, int READS>
 __global__ __launch_bounds__(kBlock) void k_node_encode_wave(const typename A::elem *__restrict__ V,
                                                              typename A::elem *__restrict__ X,
                                                              const int64_t *__restrict__ src_off,
@@ -157,7 +159,7 @@ __global__ __launch_bounds__(kBlock) void k_node_encode_wave(const typename A::e
         const int b = k + (k >= a ? 1 : 0);
         const uint32_t pos = segment_rank(a, b) * Lv + x;
         part[k] = O::zero();
-        if (pos < Wv) part[k] = combined_pack<A, VEC>(V, src[b], pos, MULTI ? m : 1, file_stride);
+        if (pos < Wv) part[k] = combined_pack<A, VEC, READS == kAll>(V, src[b], pos, MULTI ? m : 1, file_stride);
     }
     P coded = O::zero();
 #pragma unroll
@@ -165,7 +167,7 @@ __global__ __launch_bounds__(kBlock) void k_node_encode_wave(const typename A::e
     store_stream(reinterpret_cast<P *>(X) + (size_t)i * Lv + x, coded);
 }
 
-template <class A, int VEC, int R1, bool MULTI>
+template <class A, int VEC, int R1, bool MULTI, int READS>
 __global__ __launch_bounds__(kBlock) void k_node_decode_reduce_wave(
     const typename A::elem *__restrict__ V, const typename A::elem *__restrict__ X, typename A::elem *__restrict__ out,
     typename A::acc *__restrict__ part, const int64_t *__restrict__ red_ptr, const int64_t *__restrict__ red_row,
@@ -192,7 +194,7 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce_wave(
     typename O::Q acc = O::azero();
     int64_t i = lo;
     // the files the node stores come first in the list
-    auto own = [&](int64_t row) { return load_pack<true, P>(reinterpret_cast<const P *>(V + (row >> 1)) + e); };
+    auto own = [&](int64_t row) { return load_pack<READS == kAll, P>(reinterpret_cast<const P *>(V + (row >> 1)) + e); };
     for (; i + 4 <= hi; i += 4) {
         const int64_t row[4] = {red_row[i], red_row[i + 1], red_row[i + 2], red_row[i + 3]};
         if (row[3] & 1) break;
@@ -212,14 +214,14 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce_wave(
         const int a = rho < b ? rho : rho + 1;
         const int low = a < b ? a : b, high = a < b ? b : a;
         const int64_t *src = src_off + (size_t)u * R1;
-        k.coded = load_pack<true, P>(reinterpret_cast<const P *>(X) + ((size_t)u * R1 + a) * Lv + x);
+        k.coded = load_pack<READS != kPast, P>(reinterpret_cast<const P *>(X) + ((size_t)u * R1 + a) * Lv + x);
 #pragma unroll
         for (int q = 0; q < r - 1; q++) {
             int b2 = q + (q >= low ? 1 : 0);                 // the q-th member that is neither a nor b
             b2 += b2 >= high ? 1 : 0;
             const uint32_t pos = segment_rank(a, b2) * Lv + x;
             k.side[q] = O::zero();
-            if (pos < Wv) k.side[q] = combined_pack<A, VEC>(V, src[b2], pos, MULTI ? m : 1, file_stride);
+            if (pos < Wv) k.side[q] = combined_pack<A, VEC, READS == kAll>(V, src[b2], pos, MULTI ? m : 1, file_stride);
         }
     };
     auto use = [&](const Packet &k) {
@@ -292,6 +294,42 @@ void by_shape(const ccdc_plan_t *p, F launch)
     }
 }
 
+// Whether V and X are read through the caches.  A call for one node reads each value once; one for all nodes reads a coded
+// packet r times and a value that is side information r - 1 times, a job's nodes after each other.  All of it with
+// ordinary loads up to a size of a job's values that grows with r - 1 (kKeptNodeBytes is the last-level cache's size), where
+// both ways measure the same.  Beyond it V goes past the caches; the coded packets stay.  A pass of both calls in us,
+// everything kept / V past the caches / everything past them:
+//   r = 2, 8 nodes f32    179 MB of values 95 / 95 / 97, 358 MB 179 / 172 / 181, 717 MB 360 / 329 / 353, 2.9 GB 1455 / 1357 / 1390
+//   r = 3, 10 nodes f32   115 MB 69 / 74 / 77, 461 MB 257 / 259 / 276, 922 MB 499 / 479 / 505, 1.8 GB 1044 / 956 / 1021
+//   r = 5, 9 nodes f32    186 MB 90 / 120 / 116, 743 MB 347 / 361 / 379, 1.0 GB 533 / 531 / 567, 1.5 GB 812 / 747 / 798
+//   15 jobs, r = 3, 6 nodes u32, 1.2 GB (77 MB a job) 463 / 495 / 528
+// With r = 1 nothing is read twice: 12 nodes f32, 35 MB 35 / 38 / 39, 72 MB 51 / 50 / 49, 288 MB 154 / 154 / 150, 1.2 GB
+// 576 / 571 / 547.  One-element packs and the lane-packed kernels share lines with their neighbours and gain nothing past the
+// caches (8 nodes, r = 4, T = 1024001 f32 1343 / 1335 / 1455; 24 nodes, r = 4, T = 200 f32 248 / 300 / 300).
+//   One node, its two calls for every node of the cluster in turn, everything kept / everything past: 6 nodes, r = 3, ten files
+// a batch, h32: 96 MB 343 / 495, 480 MB 662 / 702; 8 nodes, r = 6, f32: 358 MB 329 / 375, 1.4 GB 665 / 619; 10 nodes, r = 3,
+// f32, 1.8 GB 1130 / 994; 24 nodes, r = 4, T = 2047 f32 (2.1 GB, one-element packs) 17580 / 14570.
+template <int VEC>
+Reads node_reads(const ccdc_plan_t *p, int node, bool by_wavefront)
+{
+    const double values = moved_bytes(p, 0);
+    if (node >= 0) return values <= kKeptOneNodeBytes ? kAll : kPast;
+    if (!by_wavefront || VEC == 1) return kAll;
+    if (p->r == 1) return values <= kKeptStageBytes ? kAll : kPast;
+    return values / p->J <= (p->r - 1) * kKeptNodeBytes ? kAll : kCoded;
+}
+
+// Calls launch(reads) with that as a compile-time constant.  CODED: whether kCoded is one of the answers there are.
+template <bool CODED, class F>
+void by_node_reads(Reads reads, F launch)
+{
+    if (reads == kAll) return launch(std::integral_constant<int, kAll>());
+    if constexpr (CODED) {
+        if (reads == kCoded) return launch(std::integral_constant<int, kCoded>());
+    }
+    launch(std::integral_constant<int, kPast>());
+}
+
 template <class A, int VEC>
 int run_node_encode(const ccdc_plan_t *p, int node, const void *V, void *X, hipStream_t st)
 {
@@ -308,15 +346,19 @@ int run_node_encode(const ccdc_plan_t *p, int node, const void *V, void *X, hipS
         auto launch = [&](auto r1, auto multi) {
             constexpr int R1 = decltype(r1)::value;
             constexpr bool MULTI = decltype(multi)::value;
-            k_node_encode_wave<A, VEC, R1, MULTI><<<cdiv(units, kWaves), kBlock, 0, st>>>(
-                (const E *)V, (E *)X, p->d_src_off, list, Lv, Wv, p->m, (int64_t)p->Q * p->T, wave_tiles, (uint32_t)units);
+            by_node_reads<false>(node_reads<VEC>(p, node, true), [&](auto reads) {
+                k_node_encode_wave<A, VEC, R1, MULTI, decltype(reads)::value><<<cdiv(units, kWaves), kBlock, 0, st>>>(
+                    (const E *)V, (E *)X, p->d_src_off, list, Lv, Wv, p->m, (int64_t)p->Q * p->T, wave_tiles,
+                    (uint32_t)units);
+            });
         };
         by_shape(p, launch);
         return launched();
     }
-    k_node_encode<A, VEC><<<cdiv(items, kBlock), kBlock, 0, st>>>((const E *)V, (E *)X, p->d_src_off, list, p->r + 1,
-                                                                   Lv, Wv, p->m, (int64_t)p->Q * p->T,
-                                                                   (uint32_t)items);
+    by_node_reads<false>(node_reads<VEC>(p, node, false), [&](auto reads) {
+        k_node_encode<A, VEC, decltype(reads)::value><<<cdiv(items, kBlock), kBlock, 0, st>>>(
+            (const E *)V, (E *)X, p->d_src_off, list, p->r + 1, Lv, Wv, p->m, (int64_t)p->Q * p->T, (uint32_t)items);
+    });
     return launched();
 }
 
@@ -340,16 +382,21 @@ int run_node_decode_reduce(const ccdc_plan_t *p, int node, const void *V, const 
         auto launch = [&](auto r1, auto multi) {
             constexpr int R1 = decltype(r1)::value;
             constexpr bool MULTI = decltype(multi)::value;
-            k_node_decode_reduce_wave<A, VEC, R1, MULTI><<<cdiv(units, kWaves), kBlock, 0, st>>>(
-                (const E *)V, (const E *)X, (E *)Phi, (Acc *)p->d_workspace, p->d_red_ptr, p->d_red_row, p->d_red_out,
-                p->d_src_off, Lv, Wv, 1.0 / (double)p->W, p->m, (int64_t)p->Q * p->T, wave_tiles, split, chunk_stride,
-                o_first, o_step, (uint32_t)units);
+            by_node_reads<(VEC > 1 && R1 > 2)>(node_reads<VEC>(p, node, true), [&](auto reads) {
+                k_node_decode_reduce_wave<A, VEC, R1, MULTI, decltype(reads)::value><<<cdiv(units, kWaves), kBlock, 0, st>>>(
+                    (const E *)V, (const E *)X, (E *)Phi, (Acc *)p->d_workspace, p->d_red_ptr, p->d_red_row, p->d_red_out,
+                    p->d_src_off, Lv, Wv, 1.0 / (double)p->W, p->m, (int64_t)p->Q * p->T, wave_tiles, split, chunk_stride,
+                    o_first, o_step, (uint32_t)units);
+            });
         };
         by_shape(p, launch);
     } else {
-        k_node_decode_reduce<A, VEC><<<(uint32_t)blocks, kBlock, 0, st>>>(
-            (const E *)V, (const E *)X, (E *)Phi, (Acc *)p->d_workspace, p->d_red_ptr, p->d_red_row, p->d_red_out,
-            p->d_src_off, p->r + 1, Lv, Wv, p->W, p->m, (int64_t)p->Q * p->T, tiles, split, chunk_stride, o_first, o_step);
+        by_node_reads<false>(node_reads<VEC>(p, node, false), [&](auto reads) {
+            k_node_decode_reduce<A, VEC, decltype(reads)::value><<<(uint32_t)blocks, kBlock, 0, st>>>(
+                (const E *)V, (const E *)X, (E *)Phi, (Acc *)p->d_workspace, p->d_red_ptr, p->d_red_row, p->d_red_out,
+                p->d_src_off, p->r + 1, Lv, Wv, p->W, p->m, (int64_t)p->Q * p->T, tiles, split, chunk_stride, o_first,
+                o_step);
+        });
     }
     int rc = launched();
     if (rc != CCDC_OK || split == 1) return rc;

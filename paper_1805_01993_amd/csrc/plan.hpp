@@ -105,13 +105,13 @@ constexpr int kLdsGranule = 1280;              // bytes it is given out in
 constexpr int kPipeMaxR1 = 6;                  // r+1 the kernel is unrolled for
 
 // Bytes up to which a call reads with ordinary loads (the rules that use them, with both sides measured, are in
-// common.hpp and pipeline.hip).  The CPU build of the kernels makes variables of them, to run either side on small inputs.
+// common.hpp, node.hip and pipeline.hip).  The CPU build of the kernels makes variables of them, to run either side on small inputs.
 #ifdef CCDC_VARIABLE_READ_LIMITS
 #define CCDC_READ_LIMIT inline double
 #else
 #define CCDC_READ_LIMIT constexpr double
 #endif
-CCDC_READ_LIMIT kKeptBytes = 128e6, kKeptStageBytes = 64e6;
+CCDC_READ_LIMIT kKeptBytes = 128e6, kKeptStageBytes = 64e6, kKeptNodeBytes = 256e6, kKeptOneNodeBytes = 640e6;
 
 // One-pass pipeline (pipeline.hip): fixes the launch geometry (pipe_vec .. pipe_shallow) for the current device.
 void pipeline_prepare(ccdc_plan_t *p);

@@ -149,7 +149,7 @@ int main(int argc, char **argv)
         shim::compute_units = atoi(argv[8]);
         shim::blocks_per_cu = atoi(argv[9]);
     }
-    if (std::getenv("SHIM_PAST")) ccdc::kKeptBytes = ccdc::kKeptStageBytes = 0;
+    if (std::getenv("SHIM_PAST")) ccdc::kKeptBytes = ccdc::kKeptStageBytes = ccdc::kKeptNodeBytes = ccdc::kKeptOneNodeBytes = 0;
     const bool half = mode >= 3, real = mode != 1;
     const size_t eb = half ? 2 : 4;
 
@@ -317,6 +317,15 @@ int main(int argc, char **argv)
         streamed("node-decode");
         same(X5, X, nx, "node-local X");
         check_phi(Phi5, "node-local Phi");
+        // each node on its own: the same packets, and the outputs of the call for all of them
+        std::memset(X5, 0xA5, (size_t)nx * eb);
+        for (int k = 0; k < K; k++) CHECK(ccdc_node_encode(p, k, V, X5, nullptr));
+        streamed("one-node-encode");
+        same(X5, X, nx, "one node's X");
+        std::memset(Phi4, 0xA5, (size_t)nphi * eb);
+        for (int k = 0; k < K; k++) CHECK(ccdc_node_decode_reduce(p, k, V, X5, Phi4, nullptr));
+        streamed("one-node-decode");
+        same(Phi4, Phi5, nphi, "one node's Phi");
     }
 
     // Map stand-in: out = theta - files (XOR in the field), separate buffer and in place
