@@ -320,15 +320,6 @@ __device__ __forceinline__ uint32_t lane_offset(uint32_t v)
     return v;
 }
 
-// Workgroups are handed to the 8 XCDs round-robin.  This numbers them so that each XCD gets a contiguous
-// range of the work, behind its own L2.
-__device__ __forceinline__ uint32_t xcd_contiguous(uint32_t block, uint32_t blocks)
-{
-    constexpr uint32_t XCDS = 8;
-    const uint32_t q = blocks / XCDS, rem = blocks % XCDS, xcd = block % XCDS, j = block / XCDS;
-    return (xcd < rem ? xcd * (q + 1) : rem * (q + 1) + (xcd - rem) * q) + j;
-}
-
 constexpr int kBlock = 256;
 // Work items (and workgroups) of one launch are numbered in 32 bits.  ccdc_plan_bind checks the
 // counts for the widest packs a shape allows; a call that has to fall back to narrower packs

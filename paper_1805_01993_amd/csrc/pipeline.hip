@@ -70,6 +70,13 @@ enum Tail {
     kSplit = 2,                       // some pack would straddle the end of the packet
 };
 
+// Which (chunk, tile) pair a workgroup works on, see order_of().
+enum Order {
+    kInTurn = 0,                      // neighbouring tiles on different XCDs, as workgroups are handed out
+    kContiguous = 1,                  // each XCD on a contiguous range of pairs
+    kRuns = 2,                        // the XCDs on runs of neighbouring tiles in turn
+};
+
 }  // namespace
 
 namespace ccdc {
@@ -80,7 +87,7 @@ struct PipeArgs {
     uint32_t tiles, chunks, waves;
     bool even;                        // how the work is shared out, see walk()
     bool shallow;                     // one step in flight, see long_packets()
-    bool by_xcd;                      // each XCD works on a contiguous range of (chunk, tile) pairs
+    int order;                        // of the workgroups: an Order
     uint32_t cols;                    // packs the wide columns cover (kSplit: the rest is the last tile's)
     int64_t file_stride, chunk_stride;
 };
@@ -382,7 +389,9 @@ __global__ __launch_bounds__(ccdc::kPipeLanes *ccdc::kPipeMaxWaves) void k_pipel
 {
     constexpr uint32_t LANES = ccdc::kPipeLanes;
     extern __shared__ __align__(16) unsigned char smem[];
-    const uint32_t logical = p.by_xcd ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x;
+    const uint32_t logical = p.order == kRuns         ? xcd_runs(blockIdx.x, gridDim.x)
+                             : p.order == kContiguous ? xcd_contiguous(blockIdx.x, gridDim.x)
+                                                      : blockIdx.x;
     const uint32_t tile = logical % p.tiles, chunk = logical / p.tiles;
     const uint32_t lane = threadIdx.x % LANES, wave = wave_uniform(threadIdx.x / LANES);
     if constexpr (TAIL == kSplit) {
@@ -434,7 +443,7 @@ uint32_t pipeline_tiles(const ccdc_plan_t *p)
 // Whether the kernel reads V with ordinary loads (KEPT) or past the caches.  Ordinary ones where a pass is small
 // (kKeptBytes), and where rows of V or segments begin inside a cache line: the two tiles on either side of a line
 // then both want it, and with non-temporal loads each fetched it from memory.  One file a batch, 8 nodes, r = 2,
-// past the caches -> kept (with by_xcd, below): T = 800008 bf16 134 -> 110 us, f32 223 -> 212; 16 nodes, r = 3,
+// past the caches -> kept (with order_of, below): T = 800008 bf16 134 -> 110 us, f32 223 -> 212; 16 nodes, r = 3,
 // T = 6148 bf16 49.0 -> 45.0, f32 76 -> 74.  With rows on whole lines, T = 800000, f32 190 -> 199, bf16 98 -> 103.
 // Sixteen-byte packs of four-byte elements on whole sectors (32 bytes) do as well past the caches (T = 800032 f32
 // 201, kept 203), narrower ones do not (16 nodes, r = 3, T = 4096 f32 53.3 -> 50.9; 8 nodes, T = 800064 bf16,
@@ -502,13 +511,20 @@ namespace {
 
 // When the rounds are cut into chunks, each XCD gets a contiguous range of (chunk, tile) pairs: the tiles of one
 // chunk (adjacent pieces of the same rows, the same table entries) then run next to each other in time behind one
-// L2.  The same with a single chunk where adjacent tiles share lines (8 nodes, r = 2, T = 800008 bf16 in the
-// hardware's order 120 us, this way 110; f32 216, 212).  Else the hardware's order is kept: all XCDs then sweep the
-// same window of every row together (2 % better).
+// L2.  The same with a single chunk where reads are kept, since adjacent tiles then share lines (8 nodes, r = 2, T = 800008
+// bf16 in the hardware's order 122 us, this way 112; f32 216, 212) or the input is small (0.93 of the time over 11 shapes
+// that share lines, 0.995 over 23 that do not).  With r = 1 and one file a batch some plans run a fifth slower that way,
+// as if the XCDs' eight windows of each row got in each other's way (six nodes, T = 4746660 f32 in the hardware's order
+// 334 us, contiguous ranges 410; seven nodes, T = 2080360 174, 203): there the XCDs take runs of 16 tiles in turn, all in
+// the same window (308, 172; nine nodes, T = 3043714 477, 444, runs 449).  With r > 1 no such plan was found, and ranges
+// are the better order (seven nodes, r = 3, T = 1815201 u32 536, 467, runs 536).  Else the hardware's order is kept: all
+// XCDs then sweep the same window of every row together (2 to 3 % better).
 template <class A, int VEC>
-bool by_xcd(const ccdc_plan_t *p)
+Order order_of(const ccdc_plan_t *p)
 {
-    return p->pipe_chunks > 1 || reads_kept<A, VEC>(p);
+    if (p->pipe_chunks > 1) return kContiguous;
+    if (!reads_kept<A, VEC>(p)) return kInTurn;
+    return p->r == 1 && p->m == 1 ? kRuns : kContiguous;
 }
 
 template <class A, int VEC>
@@ -677,7 +693,7 @@ int run_pipeline(const ccdc_plan_t *p, const void *V, void *X, void *Phi, void *
     args.waves = (uint32_t)p->pipe_waves;
     args.even = p->pipe_even;
     args.shallow = p->pipe_shallow;
-    args.by_xcd = by_xcd<A, VEC>(p);
+    args.order = order_of<A, VEC>(p);
     args.cols = pipeline_cols<VEC>(p);
     args.file_stride = (int64_t)p->Q * p->T;
     args.chunk_stride = (int64_t)p->K * p->W;

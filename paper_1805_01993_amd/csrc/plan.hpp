@@ -125,6 +125,24 @@ int pipeline_entry(const ccdc_plan_t *plan, const void *V, void *X, void *Phi, v
 // current device (noalloc.hip); out may be null to only look it up ahead of time.
 int scratch_address(void **out);
 
+// Workgroups are handed to the 8 XCDs round-robin.  This numbers them so that each XCD gets a contiguous
+// range of the work, behind its own L2.
+constexpr uint32_t kXcds = 8;
+constexpr uint32_t xcd_contiguous(uint32_t block, uint32_t blocks)
+{
+    const uint32_t q = blocks / kXcds, rem = blocks % kXcds, xcd = block % kXcds, j = block / kXcds;
+    return (xcd < rem ? xcd * (q + 1) : rem * (q + 1) + (xcd - rem) * q) + j;
+}
+
+// The same within every kXcdRun workgroups an XCD: the XCDs take runs of neighbours in turn, and all of them stay in the
+// same part of the work.
+constexpr uint32_t kXcdRun = 16;
+constexpr uint32_t xcd_runs(uint32_t block, uint32_t blocks)
+{
+    const uint32_t span = kXcds * kXcdRun, first = block / span * span, left = blocks - first;
+    return first + xcd_contiguous(block - first, left < span ? left : span);
+}
+
 // Rank of sender a's label among the members other than b.
 inline int label_rank(int a, int b) { return a - (a > b ? 1 : 0); }
 

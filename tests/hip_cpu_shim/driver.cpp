@@ -137,8 +137,27 @@ static int workspace()
     return bad ? 1 : 0;
 }
 
+// The numberings of workgroups take every number below their count once, and runs of neighbours stay on an XCD.
+static int numberings()
+{
+    int bad = 0;
+    for (uint32_t n = 1; n <= 1500; n++) {
+        std::vector<int> whole(n), runs(n), xcd(n);
+        for (uint32_t b = 0; b < n; b++) {
+            const uint32_t w = ccdc::xcd_contiguous(b, n), r = ccdc::xcd_runs(b, n);
+            if (w >= n || r >= n || whole[w]++ || runs[r]++) return std::printf("numberings FAILED (%u of %u)\n", b, n), 1;
+            xcd[r] = b % 8;
+        }
+        for (uint32_t i = 0; i + 16 <= n / 128 * 128; i += 16)
+            for (uint32_t j = 0; j < 16; j++) bad += xcd[i + j] != xcd[i];
+    }
+    std::printf(bad ? "numberings FAILED (%d)\n" : "numberings ok\n", bad);
+    return bad ? 1 : 0;
+}
+
 int main(int argc, char **argv)
 {
+    if (argc == 2 && std::strcmp(argv[1], "numberings") == 0) return numberings();
     if (argc == 2 && std::strcmp(argv[1], "workspace") == 0) return workspace();
     if (argc == 2 && std::strcmp(argv[1], "limits") == 0) return limits();
     if (argc < 8) return 64;

@@ -87,3 +87,9 @@ def test_workspace_is_what_the_calls_write(kernel_driver):
     res = subprocess.run([kernel_driver, "workspace"], capture_output=True, text=True, env=ENV, timeout=600)
     assert res.returncode == 0, res.stdout + res.stderr
     assert "workspace ok" in res.stdout, res.stdout
+
+
+def test_numberings_of_workgroups(kernel_driver):
+    res = subprocess.run([kernel_driver, "numberings"], capture_output=True, text=True, env=ENV, timeout=600)
+    assert res.returncode == 0, res.stdout + res.stderr
+    assert "numberings ok" in res.stdout, res.stdout
