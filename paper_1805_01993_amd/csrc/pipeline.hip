@@ -440,23 +440,34 @@ uint32_t pipeline_tiles(const ccdc_plan_t *p)
     return cdiv(pipeline_cols<VEC>(p), ccdc::kPipeLanes) + (tail_kind<VEC>(p) == kSplit ? 1 : 0);
 }
 
+// Whether rows of V or segments begin inside a sector (16-byte packs) or a cache line (narrower ones): two neighbouring
+// tiles then both want what lies across their border.
+template <class A, int VEC>
+bool shares_lines(const ccdc_plan_t *p)
+{
+    constexpr int64_t eb = sizeof(typename A::elem), unit = VEC * eb >= 16 ? 32 : 128;
+    return p->W * eb % unit != 0 || p->ell * eb % unit != 0;
+}
+
 // Whether the kernel reads V with ordinary loads (KEPT) or past the caches.  Ordinary ones where a pass is small
-// (kKeptBytes), and where rows of V or segments begin inside a cache line: the two tiles on either side of a line
-// then both want it, and with non-temporal loads each fetched it from memory.  One file a batch, 8 nodes, r = 2,
-// past the caches -> kept (with order_of, below): T = 800008 bf16 134 -> 110 us, f32 223 -> 212; 16 nodes, r = 3,
-// T = 6148 bf16 49.0 -> 45.0, f32 76 -> 74.  With rows on whole lines, T = 800000, f32 190 -> 199, bf16 98 -> 103.
-// Sixteen-byte packs of four-byte elements on whole sectors (32 bytes) do as well past the caches (T = 800032 f32
-// 201, kept 203), narrower ones do not (16 nodes, r = 3, T = 4096 f32 53.3 -> 50.9; 8 nodes, T = 800064 bf16,
-// segments half a line off, 107.5 -> 103).  Nor does it help with r <= 2 and long batches of wide packs in chunks:
-// each XCD reads few long rows then, and finds the shared lines in its L2 anyway (six nodes, r = 2, 12 files a batch,
-// T = 33592 f32 past the caches 30.8, kept 33.4; 40 files 90, 98).
+// (kKeptBytes), and where tiles share lines, which non-temporal loads fetch from memory for each: with packs of less than
+// 16 bytes on inputs of any size, with wider ones, which cross the borders in fewer places, from kKeptWideBytes on.  Below
+// that, wide packs share what they need in the L2 of an XCD that works on neighbouring tiles (order_of) and read past the
+// caches up to 8 % faster; 63 shapes of 0.13 to 1.2 GB with one chunk take 0.94 of the time of such reads in the hardware's
+// order, ordinary ones 0.96, 42 shapes with chunks 1.00 and 1.02 (six nodes, r = 5, T = 1841604 f32 in the hardware's order
+// 64 us, so 60, kept 69; five nodes, r = 4, T = 3000004 75, 70, 79; six nodes, r = 3, ten files a batch, T = 125001 h32
+// 117, 117, 123).  Larger inputs are read faster through the caches, by 2 to 3 % on average and up to 8 (five nodes, r = 2,
+// T = 6485985 f32, 1.8 GB, 428, 392, 367; eight nodes, r = 1, T = 5811425, 3.0 GB, 728, 734, 674); why is not known.
+// Narrow packs, past the caches -> kept: 8 nodes, r = 2, T = 800008 bf16 134 -> 110 us; 16 nodes, r = 3, T = 6148 bf16
+// 49.0 -> 45.0, T = 4096 f32 53.3 -> 50.9; 8 nodes, T = 800064 bf16, segments half a line off, 107.5 -> 103; in chunks with
+// ten and more files a batch 0.90 to 1.07 of the time (12 nodes, r = 3, T = 2817 bf16 0.90, 8 nodes, r = 3, T = 20928 u32
+// 1.07).  On whole lines ordinary loads are slower, T = 800000, f32 190 -> 199, bf16 98 -> 103.
 template <class A, int VEC>
 bool reads_kept(const ccdc_plan_t *p)
 {
-    if (moved_bytes(p, (double)p->nrows * p->ell + (double)p->Q * p->T) <= kKeptBytes) return true;
-    constexpr int64_t eb = sizeof(typename A::elem), unit = VEC * eb >= 16 ? 32 : 128;
-    if (VEC * eb >= 16 && p->r <= 2 && p->m >= 8 && p->pipe_chunks > 1) return false;
-    return p->W * eb % unit != 0 || p->ell * eb % unit != 0;
+    const double bytes = moved_bytes(p, (double)p->nrows * p->ell + (double)p->Q * p->T);
+    if (bytes <= kKeptBytes) return true;
+    return shares_lines<A, VEC>(p) && (VEC * sizeof(typename A::elem) < 16 || bytes >= kKeptWideBytes);
 }
 
 // The instantiation a plan runs.  Null for an r the kernel is not unrolled for, and where it would spill.
@@ -511,9 +522,9 @@ namespace {
 
 // When the rounds are cut into chunks, each XCD gets a contiguous range of (chunk, tile) pairs: the tiles of one
 // chunk (adjacent pieces of the same rows, the same table entries) then run next to each other in time behind one
-// L2.  The same with a single chunk where reads are kept, since adjacent tiles then share lines (8 nodes, r = 2, T = 800008
-// bf16 in the hardware's order 122 us, this way 112; f32 216, 212) or the input is small (0.93 of the time over 11 shapes
-// that share lines, 0.995 over 23 that do not).  With r = 1 and one file a batch some plans run a fifth slower that way,
+// L2.  The same with a single chunk where adjacent tiles share lines (8 nodes, r = 2, T = 800008 bf16 in the hardware's
+// order 122 us, this way 112; f32 216, 212) or the input is small (0.93 of the time over 11 shapes that share lines, 0.995
+// over 23 that do not).  With r = 1 and one file a batch some plans run a fifth slower that way,
 // as if the XCDs' eight windows of each row got in each other's way (six nodes, T = 4746660 f32 in the hardware's order
 // 334 us, contiguous ranges 410; seven nodes, T = 2080360 174, 203): there the XCDs take runs of 16 tiles in turn, all in
 // the same window (308, 172; nine nodes, T = 3043714 477, 444, runs 449).  With r > 1 no such plan was found, and ranges
@@ -523,7 +534,7 @@ template <class A, int VEC>
 Order order_of(const ccdc_plan_t *p)
 {
     if (p->pipe_chunks > 1) return kContiguous;
-    if (!reads_kept<A, VEC>(p)) return kInTurn;
+    if (!reads_kept<A, VEC>(p) && !shares_lines<A, VEC>(p)) return kInTurn;
     return p->r == 1 && p->m == 1 ? kRuns : kContiguous;
 }
 

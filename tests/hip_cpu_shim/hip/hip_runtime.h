@@ -61,13 +61,10 @@ void barrier_wait();                                    // __syncthreads()
 void *block_static(size_t bytes);                       // the running workgroup's static __shared__ array
 uint32_t shuffle_xor(uint32_t v, int mask);             // all lanes of the workgroup call it together
 void launch(dim3 grid, dim3 block, size_t lds, const std::function<void()> &body);
-template <class B>
-__attribute__((always_inline)) inline auto streaming_load(const B *p)
-{
-    streaming_loads.fetch_add(1, std::memory_order_relaxed);
-    return __builtin_nontemporal_load(p);
-}
 }  // namespace shim
+
+#define SHIM_STREAMING_LOAD(...) \
+    (shim::streaming_loads.fetch_add(1, std::memory_order_relaxed), __builtin_nontemporal_load(__VA_ARGS__))
 
 inline void __syncthreads() { shim::barrier_wait(); }
 inline int __shfl_xor(int v, int mask, int /*width*/) { return (int)shim::shuffle_xor((uint32_t)v, mask); }

@@ -1,7 +1,7 @@
 """Rewrite HIP sources so that a host C++ compiler accepts them (test infrastructure only).
 
 Three constructs have no host spelling: the triple-chevron launch and the two LDS
-declarations.  Non-temporal loads have one, but become `shim::streaming_load(p)`, which counts them.  `K<<<grid, block, lds, stream>>>(args);` becomes
+declarations.  Non-temporal loads have one, but become `SHIM_STREAMING_LOAD(p)`, which counts them.  `K<<<grid, block, lds, stream>>>(args);` becomes
 `shim::launch(grid, block, lds, [&] { K(args); });`,
 `extern __shared__ ... name[];` becomes `unsigned char *name = shim::dyn_smem;` and
 `__shared__ T name[N];` becomes a per-workgroup heap block, `T *name = ...block_static(...)`.
@@ -62,7 +62,7 @@ def translate(text):
     text = re.sub(r"extern\s+__shared__[^;]*?\b(\w+)\[\];", r"unsigned char *\1 = shim::dyn_smem;", text)
     text = re.sub(r"(?<!extern )__shared__\s+([\w:<>]+)\s+(\w+)\[([^\]]+)\];",
                   r"\1 *\2 = static_cast<\1 *>(shim::block_static(sizeof(\1) * (\3)));", text)
-    text = text.replace("__builtin_nontemporal_load(", "shim::streaming_load(")
+    text = text.replace("__builtin_nontemporal_load(", "SHIM_STREAMING_LOAD(")
     out, pos = "", 0
     while True:
         i = text.find("<<<", pos)

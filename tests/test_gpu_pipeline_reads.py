@@ -57,3 +57,46 @@ def run(K, r, m, T, mode):
 def test_orders_of_the_workgroups(K, r, m, T, mode):
     _, launch, _ = run(K, r, m, T, mode)
     assert launch[2] == 1                 # one chunk
+
+
+# K, r, files a batch, T, mode, whether packs of 16 bytes; each moves more than the 128 MB that are always read through the caches
+PAST = [
+    (8, 2, 1, 400_000, "f32", True),      # rows on whole lines
+    (7, 3, 1, 480_000, "u32", True),
+    (7, 4, 1, 409_600, "h32", True),
+    (6, 5, 1, 1_041_600, "f32", True),
+    (4, 1, 10, 320_000, "f32", True),     # one step in flight
+    (6, 2, 4, 320_000, "u32", True),
+    (5, 3, 12, 409_152, "h32", True),
+    (8, 2, 1, 300_002, "h32", True),      # wide packs whose tiles share sectors, up to 1.4 GB
+    (7, 3, 1, 300_001, "f32", True),
+    (5, 4, 1, 3_000_004, "u32", True),
+    (6, 5, 1, 1_841_604, "f32", True),
+    (9, 5, 1, 100_003, "u32", True),      # the same in chunks
+    (6, 3, 10, 125_001, "h32", True),
+    (6, 2, 12, 70_002, "f32", True),
+    (8, 2, 1, 800_000, "bf16", False),    # narrow packs on whole lines
+    (7, 3, 1, 480_000, "f16", False),
+    (8, 4, 1, 320_000, "bf16", False),
+    (7, 5, 1, 800_000, "f16", False),
+    (6, 3, 8, 96_000, "bf16", False),
+    (6, 1, 4, 704_000, "f16", False),
+    (10, 4, 8, 2048, "f32", False),
+]
+KEPT = [
+    (8, 2, 1, 400_001, "bf16", False),    # narrow packs whose tiles share lines
+    (7, 3, 1, 480_004, "f16", False),
+    (6, 3, 8, 96_001, "bf16", False),
+    (9, 4, 8, 4100, "u32", False),
+    (5, 2, 1, 6_485_985, "f32", True),    # wide ones from 1.4 GB on
+    (7, 3, 1, 1_380_769, "u32", True),
+]
+
+
+@pytest.mark.parametrize("K,r,m,T,mode,wide", PAST + KEPT)
+def test_large_inputs(K, r, m, T, mode, wide):
+    sh, launch, eb = run(K, r, m, T, mode)
+    assert (launch[0] * eb == 16) == wide
+    size, shares = moved(sh, eb), T * eb % (32 if wide else 128) or sh["X"][2] * eb % (32 if wide else 128)
+    assert size > 128e6
+    assert ((K, r, m, T, mode, wide) in KEPT) == bool(shares and (not wide or size >= 1.4e9))
