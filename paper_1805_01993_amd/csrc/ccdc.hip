@@ -346,7 +346,9 @@ int run_combine(const ccdc_plan_t *p, const void *V, void *Vbar, hipStream_t st)
     const uint64_t items = (uint64_t)p->nrows * Wv;
     if (items == 0) return CCDC_OK;
     if (!fits_launch(items)) return CCDC_ESIZE;
-    const bool kept = moved_bytes(p, (double)p->nrows * p->W) <= kKeptStageBytes;        // V and Vbar
+    const double packets = (double)p->nrows * p->W;
+    const bool kept = moved_bytes(p, packets) <= kKeptStageBytes ||                      // V and Vbar
+                      (VEC == 1 && packets * sizeof(E) <= kKeptPacketBytes);
     // short packets, long batches: a wavefront per packet with a cross-lane reduction
 #ifndef CCDC_COMBINE_WAVE_MIN_FILES
 #define CCDC_COMBINE_WAVE_MIN_FILES 8
@@ -356,14 +358,14 @@ int run_combine(const ccdc_plan_t *p, const void *V, void *Vbar, hipStream_t st)
             int seg = 1;
             while ((uint32_t)seg < Wv) seg <<= 1;
             const uint32_t rows = (uint32_t)p->nrows;
-            by_reads<VEC>(kept, [&](auto k) {
+            by_reads<false>(kept, [&](auto k) {
                 k_combine_wave<A, VEC, decltype(k)::value><<<rows, 64, 0, st>>>(
                     (const E *)V, (E *)Vbar, p->d_src_off, Wv, seg, p->m, (int64_t)p->Q * p->T, rows);
             });
             return launched();
         }
     }
-    by_reads<VEC>(kept, [&](auto k) {
+    by_reads<false>(kept, [&](auto k) {
         k_combine<A, VEC, decltype(k)::value><<<cdiv(items, kBlock), kBlock, 0, st>>>(
             (const E *)V, (E *)Vbar, p->d_src_off, p->d_row_files, Wv, p->m, (int64_t)p->Q * p->T, (uint32_t)items);
     });
@@ -414,7 +416,7 @@ void launch_shuffle(const ccdc_plan_t *p, const void *V, void *X, void *D, hipSt
     const uint32_t Wv = (uint32_t)(p->W / VEC), Lv = (uint32_t)(p->ell / VEC);
     const uint64_t items = (uint64_t)p->nround * (p->r + 1) * Lv;
     const bool kept = moved_bytes(p, (double)p->nrows * (p->W + p->ell)) <= kKeptStageBytes;        // V, X and D
-    by_reads<VEC>(kept, [&](auto k) {
+    by_reads<VEC == 1>(kept, [&](auto k) {
         k_shuffle_fused<A, VEC, R1, decltype(k)::value><<<cdiv(items, kBlock), kBlock, 0, st>>>(
             (const E *)V, (E *)X, (E *)D, p->d_src_off, p->r + 1, Lv, Wv, p->m, (int64_t)p->Q * p->T, (uint32_t)items);
     });
@@ -450,7 +452,7 @@ int run_reduce(const ccdc_plan_t *p, const void *V, const void *D, void *Phi, hi
     using Acc = typename A::acc;
     WorkspaceOrder order(p, st, split > 1);
     const bool kept = moved_bytes(p, (double)p->nrows * p->W + (double)chunk_stride) <= kKeptStageBytes;        // V, D, Phi
-    by_reads<VEC>(kept, [&](auto k) {
+    by_reads<VEC == 1>(kept, [&](auto k) {
         k_reduce_rows<A, VEC, decltype(k)::value><<<(uint32_t)blocks, kBlock, 0, st>>>(
             (const E *)V, (const E *)D, (E *)Phi, (Acc *)p->d_workspace, p->d_red_ptr, p->d_red_row, p->d_red_out, Wv, tiles,
             split, chunk_stride);

@@ -399,15 +399,22 @@ inline double moved_bytes(const ccdc_plan_t *p, double elements)
     return ((double)p->J * p->N * p->Q * (double)p->T + elements) * elem_bytes(p->mode);
 }
 
-// Calls launch(kept) with that as a compile-time constant.  One-element packs always keep their reads: rows then
-// begin anywhere in a cache line, and neighbours share the line (six nodes, uncoded, T = 729266 f32, 2.5 GB of
-// values: 604 -> 577 us).
-template <int VEC, class F>
+// Calls launch(kept) with that as a compile-time constant.  ALWAYS: only true is asked for.
+template <bool ALWAYS, class F>
 void by_reads(bool kept, F launch)
 {
-    if (VEC == 1 || kept) launch(std::true_type());
-    else if constexpr (VEC > 1) launch(std::false_type());
+    if (ALWAYS || kept) launch(std::true_type());
+    else if constexpr (!ALWAYS) launch(std::false_type());
 }
+
+// One-element packs mean rows that begin anywhere in a cache line, and neighbours that share lines.  ccdc_shuffle_fused and
+// ccdc_reduce always keep the reads of those (a pass of both, past the caches -> kept: 56 jobs on 8 nodes, r = 2, T = 150001
+// u32, 2.4 GB of values, 1162 -> 1140 us; 7 nodes, r = 2, T = 9001 f32 46.3 -> 43.8; reduce alone at most 1 % slower in a
+// pass of the four stages), ccdc_combine while its packets take up to kKeptPacketBytes: beyond that, V in the caches pushes out
+// the packets that the next call reads (the four stages, 9 nodes, r = 2, T = 150001 f32, 151 MB of packets, 311 -> 327; 10
+// nodes, r = 3, T = 100001 bf16, 168 MB, 473 -> 490; but the uncoded scheme, 22 nodes, T = 85615 u32, 79 MB, 392 -> 383).
+// For ccdc_map, which reads each line once, they are packs like others (62 MB and less 0.73 to 0.82 of the time, more
+// 1.00 to 1.04).
 
 // Pack width (elements) for this call: 16 bytes when the value length, the
 // segment length and every pointer allow it; for 2-byte elements else 8 bytes;

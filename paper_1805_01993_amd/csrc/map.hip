@@ -56,8 +56,8 @@ int run_map(const ccdc_plan_t *p, const void *files, const void *theta, void *V,
     const uint64_t tiles = (model_packs + kBlock - 1) / kBlock, groups = (tiles + kMapGroup - 1) / kMapGroup;
     if (!fits_launch(rows * groups * kMapGroup)) return CCDC_ESIZE;
     const uint64_t group_tiles = (tiles + groups - 1) / groups;      // equal groups: no workgroups without work
-    const bool kept = moved_bytes(p, (double)p->J * p->Q * p->T) <= kKeptStageBytes;        // files and models
-    by_reads<VEC>(kept, [&](auto k) {
+    const bool kept = moved_bytes(p, (double)p->J * p->Q * p->T) <= kKeptStageBytes;        // files and models: what it reads
+    by_reads<false>(kept, [&](auto k) {
         k_map<A, VEC, decltype(k)::value><<<(uint32_t)(rows * groups * group_tiles), kBlock, 0, st>>>(
             (const E *)files, (const E *)theta, (E *)V, (uint32_t)model_packs, (uint32_t)tiles, (uint32_t)rows,
             (uint32_t)p->N, (uint32_t)group_tiles);
