@@ -108,9 +108,11 @@ def test_gradient_workload_from_files(torch, L):
     plan.close()
 
 
-@pytest.mark.parametrize("N,tiles", [(2, 1), (7, 1), (3, 3), (8, 5), (9, 17), (5, 300), (2, 513)])
+@pytest.mark.parametrize("N,tiles", [(2, 1), (7, 1), (3, 3), (8, 5), (9, 17), (5, 300), (2, 513),
+                                     (3, 257), (4, 514)])
 def test_every_tile_of_every_file_is_mapped_once(torch, L, N, tiles):
-    """Fewer workgroups than XCDs, a multiple of them, remainders; one and several groups of tiles (the last one short).
+    """Fewer workgroups than XCDs, a multiple of them, remainders; one and several groups of tiles, the last one short with 257
+    tiles (groups of 129 and 128) and 514 (two of 172, one of 170).
     One subtraction in fp32: bit for bit."""
     T = tiles * 256 * 4 // 2 - 4                                      # Q = 2 functions: the last tile is short
     plan = L.Plan(2, 1, 2, N * 2).bind(T, "f32").upload()
