@@ -477,19 +477,25 @@ PipeKernel<A> kernel_of(const ccdc_plan_t *p)
     const Tail tail = tail_kind<VEC>(p);
     auto of = [&](auto r1) -> PipeKernel<A> {
         constexpr int R1 = decltype(r1)::value;
+        // Narrow packs go past the caches where W and ell are whole lines.  r * ell exceeds W by less than 4r elements, that
+        // is by less than a line, so then not at all: there are no other ends.
+        constexpr bool ALL_ENDS = KEPT || VEC * sizeof(typename A::elem) >= 16;
+        if (!ALL_ENDS && tail != kWhole) return nullptr;
         if (p->m > 1) {
             // Five segments of six packets, their sums and the file on the way do not fit the registers at four
             // elements a pack: those kernels spilled up to 112 of them.  Narrower packs were faster in 19 of 20
             // shapes measured (eight nodes, four files a batch, T = 60000 f32: 101 us at the best geometry of
             // four-element packs, 82 with two, 73 with one), the twentieth 4 % slower.
             if constexpr (VEC == 4 && R1 == 6) return nullptr;
-            else if constexpr (VEC == 1) return k_pipeline<A, VEC, R1, true, kShort, KEPT>;
+            else if constexpr (VEC == 1 || !ALL_ENDS) return k_pipeline<A, VEC, R1, true, kShort, KEPT>;
             else return tail == kSplit ? k_pipeline<A, VEC, R1, true, kSplit, KEPT> : k_pipeline<A, VEC, R1, true, kShort, KEPT>;
         }
-        if constexpr (VEC > 1) {
+        if constexpr (VEC > 1 && ALL_ENDS) {
             if (tail == kSplit) return k_pipeline<A, VEC, R1, false, kSplit, KEPT>;
         }
-        if (tail == kShort) return k_pipeline<A, VEC, R1, false, kShort, KEPT>;
+        if constexpr (ALL_ENDS) {
+            if (tail == kShort) return k_pipeline<A, VEC, R1, false, kShort, KEPT>;
+        }
         return k_pipeline<A, VEC, R1, false, kWhole, KEPT>;
     };
     switch (p->r + 1) {

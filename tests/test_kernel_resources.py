@@ -2,6 +2,7 @@
 registers or keeps anything in scratch memory."""
 import os
 import re
+import shutil
 import struct
 import subprocess
 
@@ -10,6 +11,7 @@ import pytest
 from paper_1805_01993_amd import binding as B
 
 READELF = "/opt/rocm/lib/llvm/bin/llvm-readelf"
+CXXFILT = shutil.which("c++filt")
 MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
 
 
@@ -30,10 +32,12 @@ def code_objects(path):
         at = data.find(MAGIC, at + 1)
 
 
-def test_no_kernel_uses_scratch_memory(tmp_path):
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """Per kernel: bytes of scratch memory, spilled vector and scalar registers."""
     if not os.path.exists(READELF):
         pytest.skip("no llvm-readelf")
-    kernels = {}
+    tmp_path, kernels = tmp_path_factory.mktemp("objects"), {}
     for i, obj in enumerate(code_objects(B.LIB_PATH)):
         path = tmp_path / f"{i}.o"
         path.write_bytes(obj)
@@ -42,6 +46,24 @@ def test_no_kernel_uses_scratch_memory(tmp_path):
             name = re.search(r"\.symbol:\s+'?(\S+?)\.kd", kernel).group(1)
             kernels[name] = [int(re.search(rf"\.{key}:\s+(\d+)", kernel).group(1))
                              for key in ("private_segment_fixed_size", "vgpr_spill_count", "sgpr_spill_count")]
+    return kernels
+
+
+def test_no_kernel_uses_scratch_memory(kernels):
     assert sum("k_pipeline" in name for name in kernels) >= 300
     assert any("k_map" in name for name in kernels) and any("k_node_encode" in name for name in kernels)
     assert {name: v for name, v in kernels.items() if any(v)} == {}
+
+
+def test_one_pass_kernels_past_the_caches_have_ends_that_occur(kernels):
+    """Packs of less than 16 bytes are read past the caches only where a packet and its segments are whole cache lines:
+    the last segment is whole then (end 0; the kernels for several files a batch have 1, which takes that too)."""
+    if not CXXFILT:
+        pytest.skip("no c++filt")
+    names = subprocess.run([CXXFILT], input="\n".join(kernels), capture_output=True, text=True, check=True).stdout
+    found = re.findall(r"k_pipeline<ccdc::(\w+)(?:<\w+>)?, (\d), (\d), (true|false), (\d), (true|false)>", names)
+    assert len(found) == sum("k_pipeline" in name for name in kernels)
+    past = [(int(vec) * (2 if algebra == "Hyb16" else 4), multi, end) for algebra, vec, _, multi, end, kept in found
+            if kept == "false"]
+    assert {end for size, _, end in past if size == 16} == {"0", "1", "2"}
+    assert {(multi, end) for size, multi, end in past if size < 16} == {("false", "0"), ("true", "1")}
