@@ -637,11 +637,14 @@ void consider(const ccdc_plan_t *p, Candidate *best)
     peak *= large ? used : std::pow(used, deep ? 0.25 : 0.3);
     if (p->T * elem % 8)                             // rows start anywhere: more lines an access
         peak *= 1 - (deep ? 0.2 : !large ? 0.4 : width == 0 ? 0.45 : 0.25) * std::min(1.0, 8.0 / (VEC * elem));
-    // A workgroup may take most of a compute unit's LDS where the third set ranks, and with r = 2 on large inputs (18
-    // nodes, two functions each, T = 45440 f16 150 -> 133 us).  Elsewhere 64 KB stay the limit: with r = 1 (22 nodes,
-    // T = 240608 bf16 89 -> 106), on small inputs (9 nodes, r = 2, T = 21340 f32 12.0 -> 16.1) and where the second
-    // set ranks (9 nodes, r = 5, T = 697096 bf16 322 -> 441).
-    const size_t most_lds = deep || (p->r == 2 && bytes >= kLargeInput) ? ccdc::kPipeGroupLds : ccdc::kPipeMaxLds;
+    // A workgroup may take most of a compute unit's LDS where the third set ranks, and with r = 2 on large inputs that have
+    // fewer tiles than there are compute units: larger workgroups then save chunks.  Over 138 shapes 0.95 of the time with 64
+    // KB, the slowest 9 % slower (18 nodes, two functions each, T = 45440 f16 150 -> 133 us); with a tile for every compute
+    // unit they only gave some 0.96, others up to 1.16 (13 nodes, T = 502358 bf16 289 -> 336; eight nodes, T = 2068872 bf16
+    // 280 -> 302).  Elsewhere 64 KB stay the limit: with r = 1 (22 nodes, T = 240608 bf16 89 -> 106), on small inputs (9
+    // nodes, r = 2, T = 21340 f32 12.0 -> 16.1) and where the second set ranks (9 nodes, r = 5, T = 697096 bf16 322 -> 441).
+    const bool few_tiles = p->r == 2 && bytes >= kLargeInput && tiles < cus;
+    const size_t most_lds = deep || few_tiles ? ccdc::kPipeGroupLds : ccdc::kPipeMaxLds;
     const double issue = tiles * (rows * p->r + R * r1) * 0.012 / cus;       // us a compute unit takes to issue the loads and stores
     for (int waves = 1; waves <= ccdc::kPipeMaxWaves && waves * lds <= most_lds; waves++) {
         const size_t granule = large || deep ? ccdc::kLdsGranule : 1, group_lds = (waves * lds + granule - 1) / granule * granule;

@@ -54,3 +54,13 @@ def test_workgroups_over_64_kilobytes(K, r, c, m, T, mode):
         assert torch.equal(Phi.float(), V.float().sum(1))
     assert torch.equal(Phi2, Phi)
     plan.close()
+
+
+@pytest.mark.parametrize("K,r,m,T,mode", [(13, 2, 1, 502358, "bf16"), (8, 2, 6, 247552, "bf16"), (8, 2, 1, 2068872, "bf16")])
+def test_r2_with_a_tile_for_every_compute_unit_keeps_to_64_kilobytes(K, r, m, T, mode):
+    """Larger workgroups were up to 16 % slower there."""
+    plan = L.ccdc_plan(K, r, K, m * comb(K, r)).bind(T, mode).upload()
+    pack, waves = plan.pipeline_launch()[:2]
+    assert -(-(T // r) // (64 * pack)) >= torch.cuda.get_device_properties(0).multi_processor_count
+    assert waves * pack * K * r * 256 <= 64 * 1024
+    plan.close()
