@@ -581,7 +581,7 @@ bool long_packets(const ccdc_plan_t *p)
 // outputs per chunk).  No single threshold on sizes separates the good from the bad: the candidates are
 // ranked by an estimate of their time and the least is taken.  Its constants are fitted to measured
 // passes of several hundred shapes (K 4..24, r 1..5, 64 KB..3.2 GB, every mode, 25 to 200 geometries
-// each): they rank; as a time the estimate is up to twice the measured one.  Two sets of them, because
+// each): they rank; as a time the estimate is up to twice the measured one.  Three sets of them, because
 // what ranks the candidates differs between small inputs (waits, the second kernel, lanes in flight) and
 // large ones (the loads a compute unit can issue, bytes, full generations).  With the first set alone 31
 // of 143 shapes with one file a batch, r >= 3 and 200 MB or more ran 3 to 34 % slower than one wavefront a
@@ -590,11 +590,13 @@ bool long_packets(const ccdc_plan_t *p)
 // r = 4, T = 344 h32: 101 -> 77).  It also serves r = 5 with several files, where four-element packs are
 // missing (0.94 of the time over 20 shapes), and r = 1 with several files and long packets (see kLongPacket).  Elsewhere it gave nothing: with r <= 2 1.00 of the time over
 // 72 shapes, three of them 9 to 18 % slower; below 200 MB 1.00; with several files and r = 4 up to 20 % slower.
-// The third set is for what the second leaves of r >= 3 and more than 40 running outputs a lane, where LDS holds few
-// wavefronts; fitted with reads kept or not and with workgroups of up to 160 KB of LDS.  Over 116 shapes 0.92 of the
-// first set's time, 95 of them over 3 % faster, the slowest 5 % slower (16 nodes, r = 4, T = 257 bf16, six files a batch
-// 61 -> 34 us; 16 nodes, r = 3, T = 4096 f32 50.7 -> 46.7).  With 40 outputs and fewer it gave 0.96, with r <= 2 0.98,
-// some shapes over 20 % slower.
+// The third set is for what the second leaves of r >= 3 where a compute unit's LDS holds fewer than 16 wavefronts even with
+// one-element packs (four a SIMD: over 40 running outputs a lane); fitted with reads kept or not and with workgroups of up to
+// 160 KB of LDS.  Against the first set's choice: 340 shapes below 200 MB 0.90 of the time, three of them over 3 % slower,
+// the slowest 8 % (16 nodes, r = 4, T = 257 bf16, six files a batch 60 -> 34 us; 16 nodes, r = 3, T = 4096 f32 49 -> 46; 13
+// nodes, r = 4, T = 688 h32 13.5 -> 14.0); 300 shapes with several files and 200 MB or more 0.92, five over 3 % slower, the
+// slowest 10 %.  Where LDS holds 16 and more it gave 0.98 over 61 shapes, 11 of them over 3 % slower, up to 26 %; with r <= 2
+// 0.98, some over 20 % slower.
 struct Candidate {
     int vec, waves, chunks;
     bool even, shallow;
@@ -629,12 +631,17 @@ void consider(const ccdc_plan_t *p, Candidate *best)
     const double used = (double)(p->ell / VEC) / (cdiv(p->ell / VEC, ccdc::kPipeLanes) * ccdc::kPipeLanes);    // share of lanes with work
     const double flight = (shallow ? 1 : depth) * r1 * p->r * ccdc::kPipeLanes * VEC * elem * used;                // bytes a wavefront has on the way
     constexpr int width = VEC * elem >= 16 ? 3 : VEC * elem == 8 ? 2 : VEC * elem == 4 ? 1 : 0;
-    const bool deep = !large && p->r >= 3 && p->K * p->r > 40;       // the third set of constants
+    const bool deep = !large && p->r >= 3 && ccdc::kCuLds / pipeline_lds<1>(p) < 16;       // the third set of constants
     constexpr double peaks[4][4] = {                 // B/us
         {3.2e6, 4.2e6, 5.3e6, 6.5e6}, {4.2e6, 4.8e6, 6.2e6, 9.0e6},
         {3.6e6, 4.0e6, 5.65e6, 13.8e6}, {3.3e6, 5.85e6, 8.45e6, 23.7e6}};                // deep: past the caches, through them
     double peak = peaks[large ? 1 : !deep ? 0 : reads_kept<A, VEC>(p) ? 3 : 2][width];
-    peak *= large ? used : std::pow(used, deep ? 0.25 : 0.3);
+    // Lanes without work cost the third set little while the last-level cache holds the input, and much beyond: a last tile that
+    // is nearly empty then shares its lines with a neighbour that has long gone on (24 nodes, r = 3, eight files a batch, T =
+    // 448 bf16 as two tiles of two-element packs, 64 and 12 lanes, 205 us, as three of one element 141; 22 nodes, r = 4, six
+    // files, T = 576 f16 535, 306).  Over 241 shapes of 16 bits 0.92 -> 0.91 of the first set's time, 11 -> 5 of them over 3 %
+    // slower, the slowest 53 -> 10 %; over 59 of 32 bits 0.95 -> 0.94, the slowest 12 -> 1 %.
+    peak *= large ? used : std::pow(used, !deep ? 0.3 : bytes >= kLargeInput ? 3 : 0.25);
     if (p->T * elem % 8)                             // rows start anywhere: more lines an access
         peak *= 1 - (deep ? 0.2 : !large ? 0.4 : width == 0 ? 0.45 : 0.25) * std::min(1.0, 8.0 / (VEC * elem));
     // A workgroup may take most of a compute unit's LDS where the third set ranks, and with r = 2 on large inputs that have

@@ -64,3 +64,13 @@ def test_r2_with_a_tile_for_every_compute_unit_keeps_to_64_kilobytes(K, r, m, T,
     assert -(-(T // r) // (64 * pack)) >= torch.cuda.get_device_properties(0).multi_processor_count
     assert waves * pack * K * r * 256 <= 64 * 1024
     plan.close()
+
+
+@pytest.mark.parametrize("K,r,m,T,mode", [(24, 3, 8, 432, "bf16"), (24, 3, 12, 448, "bf16"), (22, 4, 6, 576, "f16"), (19, 4, 4, 600, "f16")])
+def test_large_inputs_avoid_a_nearly_empty_second_tile(K, r, m, T, mode):
+    """As two tiles of two-element packs, the second with 8 to 12 of 64 lanes at work, these ran up to 1.8 times as long."""
+    plan = L.ccdc_plan(K, r, K, m * comb(K, r)).bind(T, mode).upload()
+    pack = plan.pipeline_launch()[0]
+    lanes = plan.seg_len // pack
+    assert lanes % 64 == 0 or lanes % 64 > 12
+    plan.close()
