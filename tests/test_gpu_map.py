@@ -122,3 +122,24 @@ def test_every_tile_of_every_file_is_mapped_once(torch, L, N, tiles):
     V = torch.full_like(files, float("nan"))
     plan.map(files, theta, V)
     assert torch.equal(V, theta.unsqueeze(1) - files)
+
+
+def test_rounding_of_every_difference_of_two_bf16_values(torch, L):
+    """All 2^32 pairs of patterns: the hardware's conversion against rounding to nearest even on the bits of the fp32
+    difference (subnormals, ties, the carry into the exponent and into infinity); every NaN is the canonical one."""
+    N = 2048
+    plan = L.Plan(2, 1, 2, N).bind(1 << 15, "bf16").upload()
+    every = torch.arange(1 << 16, device="cuda", dtype=torch.int32)
+    theta = every.to(torch.int16).view(1, 2, 1 << 15)
+    wide = (every << 16).view(torch.float32)                          # the same values in fp32
+    V = torch.empty((1, N, 2, 1 << 15), dtype=torch.int16, device="cuda")
+    for first in range(0, 1 << 16, N):
+        files = theta.reshape(-1)[first:first + N].view(1, N, 1, 1).expand(1, N, 2, 1 << 15).contiguous()
+        plan.map(files, theta, V)
+        a = (wide - wide[first:first + N, None])
+        nan = a.isnan()
+        b = a.view(torch.int32)
+        want = (b + 0x7FFF + ((b >> 16) & 1)) >> 16                   # no carry past the sign: NaN apart, b is at most infinity
+        want = torch.where(nan, 0x7FC0, want).to(torch.int16)
+        assert torch.equal(V.view(N, -1), want), f"files from pattern {first:#x} on"
+    plan.close()
