@@ -384,8 +384,9 @@ inline int ready(const ccdc_plan_t *p)
 
 inline int elem_bytes(int mode) { return (mode == CCDC_BF16_SUM_XOR || mode == CCDC_F16_SUM_XOR) ? 2 : 4; }
 
-// kKeptBytes, kKeptStageBytes: non-temporal loads pass the last-level cache (256 MB) by, ordinary ones leave the data there.  A call whose
-// inputs and outputs take no more than this therefore reads with ordinary loads: its inputs are then often still
+// kKeptBytes, kKeptStageBytes: non-temporal loads pass the last-level cache (256 MB) by, ordinary ones leave the data
+// there.  A call whose inputs and outputs take no more than this (ccdc_map: what it reads; V, as large again, is only written)
+// therefore reads with ordinary loads: its inputs are then often still
 // there from the call that made them.  Measured with three sets of buffers used in turn.  One-pass kernel, 8 nodes,
 // r = 2, one file a batch, f32: 64 MB a pass 14.5 -> 12.6 us, 129 MB 24.1 -> 23.4, but 194 MB 43.1 -> 46.2 and 1 GB
 // 190 -> 199.  The calls of single stages share the cache with what the other stages make: two functions a node,

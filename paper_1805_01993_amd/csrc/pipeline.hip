@@ -592,7 +592,7 @@ bool long_packets(const ccdc_plan_t *p)
 // 72 shapes, three of them 9 to 18 % slower; below 200 MB 1.00; with several files and r = 4 up to 20 % slower.
 // The third set is for what the second leaves of r >= 3 where a compute unit's LDS holds fewer than 16 wavefronts even with
 // one-element packs (four a SIMD: over 40 running outputs a lane); fitted with reads kept or not and with workgroups of up to
-// 160 KB of LDS.  Against the first set's choice: 340 shapes below 200 MB 0.90 of the time, three of them over 3 % slower,
+// 160 KB of LDS.  Against the first set's choice: 335 shapes below 200 MB 0.90 of the time, four of them over 3 % slower,
 // the slowest 8 % (16 nodes, r = 4, T = 257 bf16, six files a batch 60 -> 34 us; 16 nodes, r = 3, T = 4096 f32 49 -> 46; 13
 // nodes, r = 4, T = 688 h32 13.5 -> 14.0); 300 shapes with several files and 200 MB or more 0.92, five over 3 % slower, the
 // slowest 10 %.  Where LDS holds 16 and more it gave 0.98 over 61 shapes, 11 of them over 3 % slower, up to 26 %; with r <= 2
