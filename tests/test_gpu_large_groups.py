@@ -24,6 +24,8 @@ pytestmark = pytest.mark.gpu
     (15, 5, 1, 1, 192, "f32"),
     (17, 5, 1, 1, 235, "u32"),
     (18, 2, 1, 1, 57076, "f16"),         # r = 2, a large input
+    (24, 3, 1, 8, 432, "bf16"),          # large inputs with several files
+    (22, 4, 1, 6, 576, "f16"),
 ])
 def test_workgroups_over_64_kilobytes(K, r, c, m, T, mode):
     N = m * comb(K, r)
