@@ -70,11 +70,11 @@ enum Tail {
     kSplit = 2,                       // some pack would straddle the end of the packet
 };
 
-// Which (chunk, tile) pair a workgroup works on, see order_of().
-enum Order {
-    kInTurn = 0,                      // neighbouring tiles on different XCDs, as workgroups are handed out
-    kContiguous = 1,                  // each XCD on a contiguous range of pairs
-    kRuns = 2,                        // the XCDs on runs of neighbouring tiles in turn
+// Which (chunk, tile) pair a workgroup works on: the span of xcd_spans(), see order_of().
+enum Order : uint32_t {
+    kContiguous = 0,                  // each XCD on a contiguous range of pairs
+    kInTurn = 8,                      // neighbouring tiles on different XCDs, as workgroups are handed out
+    kRuns = 128,                      // the XCDs on runs of 16 neighbouring tiles in turn
 };
 
 }  // namespace
@@ -87,7 +87,7 @@ struct PipeArgs {
     uint32_t tiles, chunks, waves;
     bool even;                        // how the work is shared out, see walk()
     bool shallow;                     // one step in flight, see long_packets()
-    int order;                        // of the workgroups: an Order
+    uint32_t order;                   // of the workgroups: an Order
     uint32_t cols;                    // packs the wide columns cover (kSplit: the rest is the last tile's)
     int64_t file_stride, chunk_stride;
 };
@@ -389,9 +389,7 @@ __global__ __launch_bounds__(ccdc::kPipeLanes *ccdc::kPipeMaxWaves) void k_pipel
 {
     constexpr uint32_t LANES = ccdc::kPipeLanes;
     extern __shared__ __align__(16) unsigned char smem[];
-    const uint32_t logical = p.order == kRuns         ? xcd_runs(blockIdx.x, gridDim.x)
-                             : p.order == kContiguous ? xcd_contiguous(blockIdx.x, gridDim.x)
-                                                      : blockIdx.x;
+    const uint32_t logical = xcd_spans(blockIdx.x, gridDim.x, p.order);
     const uint32_t tile = logical % p.tiles, chunk = logical / p.tiles;
     const uint32_t lane = threadIdx.x % LANES, wave = wave_uniform(threadIdx.x / LANES);
     if constexpr (TAIL == kSplit) {

@@ -136,13 +136,12 @@ constexpr uint32_t xcd_contiguous(uint32_t block, uint32_t blocks)
     return (xcd < rem ? xcd * (q + 1) : rem * (q + 1) + (xcd - rem) * q) + j;
 }
 
-// The same within every kXcdRun workgroups an XCD: the XCDs take runs of neighbours in turn, and all of them stay in the
-// same part of the work.
-constexpr uint32_t kXcdRun = 16;
-constexpr uint32_t xcd_runs(uint32_t block, uint32_t blocks)
+// The same within every `span` workgroups (a power of two, 0: all of them): the XCDs take runs of span / 8 neighbours in turn,
+// and all of them stay in the same part of the work.  With a span of 8 that is the order in which workgroups are handed out.
+constexpr uint32_t xcd_spans(uint32_t block, uint32_t blocks, uint32_t span)
 {
-    const uint32_t span = kXcds * kXcdRun, first = block / span * span, left = blocks - first;
-    return first + xcd_contiguous(block - first, left < span ? left : span);
+    const uint32_t first = block & (0u - span), left = blocks - first;
+    return first + xcd_contiguous(block - first, span - 1 < left - 1 ? span : left);
 }
 
 // Rank of sender a's label among the members other than b.

@@ -137,19 +137,24 @@ static int workspace()
     return bad ? 1 : 0;
 }
 
-// The numberings of workgroups take every number below their count once, and runs of neighbours stay on an XCD.
+// The numberings of workgroups take every number below their count once; a span of 8 leaves them as they are, and with a longer
+// one runs of neighbours stay on an XCD.
 static int numberings()
 {
     int bad = 0;
     for (uint32_t n = 1; n <= 1500; n++) {
-        std::vector<int> whole(n), runs(n), xcd(n);
-        for (uint32_t b = 0; b < n; b++) {
-            const uint32_t w = ccdc::xcd_contiguous(b, n), r = ccdc::xcd_runs(b, n);
-            if (w >= n || r >= n || whole[w]++ || runs[r]++) return std::printf("numberings FAILED (%u of %u)\n", b, n), 1;
-            xcd[r] = b % 8;
+        for (uint32_t span : {0u, 8u, 16u, 128u, 512u}) {
+            std::vector<int> seen(n), xcd(n);
+            for (uint32_t b = 0; b < n; b++) {
+                const uint32_t w = ccdc::xcd_spans(b, n, span);
+                if (w >= n || seen[w]++) return std::printf("numberings FAILED (%u of %u, %u)\n", b, n, span), 1;
+                if ((span == 8 && w != b) || (span == 0 && w != ccdc::xcd_contiguous(b, n))) bad++;
+                xcd[w] = b % 8;
+            }
+            const uint32_t run = span / 8;
+            for (uint32_t i = 0; span && i + run <= n / span * span; i += run)
+                for (uint32_t j = 0; j < run; j++) bad += xcd[i + j] != xcd[i];
         }
-        for (uint32_t i = 0; i + 16 <= n / 128 * 128; i += 16)
-            for (uint32_t j = 0; j < 16; j++) bad += xcd[i + j] != xcd[i];
     }
     std::printf(bad ? "numberings FAILED (%d)\n" : "numberings ok\n", bad);
     return bad ? 1 : 0;
