@@ -454,7 +454,9 @@ bool shares_lines(const ccdc_plan_t *p)
 // caches up to 8 % faster; 63 shapes of 0.13 to 1.2 GB with one chunk take 0.94 of the time of such reads in the hardware's
 // order, ordinary ones 0.96, 42 shapes with chunks 1.00 and 1.02 (six nodes, r = 5, T = 1841604 f32 in the hardware's order
 // 64 us, so 60, kept 69; five nodes, r = 4, T = 3000004 75, 70, 79; six nodes, r = 3, ten files a batch, T = 125001 h32
-// 117, 117, 123).  Larger inputs are read faster through the caches, by 2 to 3 % on average and up to 8 (five nodes, r = 2,
+// 117, 117, 123).  With r <= 2 and up to kKeptSharedBytes the cache still holds enough: 13 shapes of 128 to 200 MB past the
+// caches 1.04 of the time of ordinary loads (18 nodes, r = 1, T = 51921 f32 29.1, 24.0; 24 nodes, r = 2, T = 3373 u32 46.0,
+// 39.5), 15 shapes of 200 to 300 MB 0.98; with r >= 3 nothing was lost there.  Larger inputs are read faster through the caches, by 2 to 3 % on average and up to 8 (five nodes, r = 2,
 // T = 6485985 f32, 1.8 GB, 428, 392, 367; eight nodes, r = 1, T = 5811425, 3.0 GB, 728, 734, 674); why is not known.
 // Narrow packs, past the caches -> kept: 8 nodes, r = 2, T = 800008 bf16 134 -> 110 us; 16 nodes, r = 3, T = 6148 bf16
 // 49.0 -> 45.0, T = 4096 f32 53.3 -> 50.9; 8 nodes, T = 800064 bf16, segments half a line off, 107.5 -> 103; in chunks with
@@ -465,7 +467,8 @@ bool reads_kept(const ccdc_plan_t *p)
 {
     const double bytes = moved_bytes(p, (double)p->nrows * p->ell + (double)p->Q * p->T);
     if (bytes <= kKeptBytes) return true;
-    return shares_lines<A, VEC>(p) && (VEC * sizeof(typename A::elem) < 16 || bytes >= kKeptWideBytes);
+    if (!shares_lines<A, VEC>(p)) return false;
+    return VEC * sizeof(typename A::elem) < 16 || bytes >= kKeptWideBytes || (p->r <= 2 && bytes <= kKeptSharedBytes);
 }
 
 // The instantiation a plan runs.  Null for an r the kernel is not unrolled for, and where it would spill.
@@ -590,7 +593,7 @@ bool long_packets(const ccdc_plan_t *p)
 // 72 shapes, three of them 9 to 18 % slower; below 200 MB 1.00; with several files and r = 4 up to 20 % slower.
 // The third set is for what the second leaves of r >= 3 where a compute unit's LDS holds fewer than 16 wavefronts even with
 // one-element packs (four a SIMD: over 40 running outputs a lane); fitted with reads kept or not and with workgroups of up to
-// 160 KB of LDS.  Against the first set's choice: 335 shapes below 200 MB 0.90 of the time, four of them over 3 % slower,
+// 160 KB of LDS.  Against the first set's choice: 334 shapes below 200 MB 0.90 of the time, four of them over 3 % slower,
 // the slowest 8 % (16 nodes, r = 4, T = 257 bf16, six files a batch 60 -> 34 us; 16 nodes, r = 3, T = 4096 f32 49 -> 46; 13
 // nodes, r = 4, T = 688 h32 13.5 -> 14.0); 300 shapes with several files and 200 MB or more 0.92, five over 3 % slower, the
 // slowest 10 %.  Where LDS holds 16 and more it gave 0.98 over 61 shapes, 11 of them over 3 % slower, up to 26 %; with r <= 2

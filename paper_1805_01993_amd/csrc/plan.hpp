@@ -112,7 +112,7 @@ constexpr int kPipeMaxR1 = 6;                  // r+1 the kernel is unrolled for
 #define CCDC_READ_LIMIT constexpr double
 #endif
 CCDC_READ_LIMIT kKeptBytes = 128e6, kKeptStageBytes = 64e6, kKeptNodeBytes = 256e6, kKeptOneNodeBytes = 640e6;
-CCDC_READ_LIMIT kKeptPacketBytes = 100e6;
+CCDC_READ_LIMIT kKeptPacketBytes = 100e6, kKeptSharedBytes = 200e6;
 CCDC_READ_LIMIT kKeptWideBytes = 1.4e9;        // from these on
 
 // One-pass pipeline (pipeline.hip): fixes the launch geometry (pipe_vec .. pipe_shallow) for the current device.

@@ -174,7 +174,7 @@ int main(int argc, char **argv)
         shim::blocks_per_cu = atoi(argv[9]);
     }
     if (std::getenv("SHIM_PAST")) ccdc::kKeptBytes = ccdc::kKeptStageBytes = ccdc::kKeptNodeBytes = ccdc::kKeptOneNodeBytes =
-                                       ccdc::kKeptPacketBytes = 0;
+                                       ccdc::kKeptPacketBytes = ccdc::kKeptSharedBytes = 0;
     const bool half = mode >= 3, real = mode != 1;
     const size_t eb = half ? 2 : 4;
 

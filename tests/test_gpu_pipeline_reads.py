@@ -88,6 +88,8 @@ KEPT = [
     (7, 3, 1, 480_004, "f16", False),
     (6, 3, 8, 96_001, "bf16", False),
     (9, 4, 8, 4100, "u32", False),
+    (18, 1, 1, 51_921, "f32", True),      # wide ones up to 200 MB, r <= 2
+    (24, 2, 1, 3373, "u32", True),
     (5, 2, 1, 6_485_985, "f32", True),    # wide ones from 1.4 GB on
     (7, 3, 1, 1_380_769, "u32", True),
 ]
@@ -99,4 +101,4 @@ def test_large_inputs(K, r, m, T, mode, wide):
     assert (launch[0] * eb == 16) == wide
     size, shares = moved(sh, eb), T * eb % (32 if wide else 128) or sh["X"][2] * eb % (32 if wide else 128)
     assert size > 128e6
-    assert ((K, r, m, T, mode, wide) in KEPT) == bool(shares and (not wide or size >= 1.4e9))
+    assert ((K, r, m, T, mode, wide) in KEPT) == bool(shares and (not wide or size >= 1.4e9 or r <= 2 and size <= 200e6))
