@@ -115,7 +115,8 @@ enum ccdc_query {
     CCDC_Q_PIPELINE_LAUNCH   /* int32_t[4] what ccdc_plan_upload fixed for ccdc_pipeline_fused: elements of a pack,
                               *   wavefronts of a workgroup, chunks of rounds, flags (1: every wavefront takes an
                               *   equal share of the rounds and one of the own files; 2: one step of the rounds
-                              *   in flight).  CCDC_ESTATE before ccdc_plan_upload and for plans that call
+                              *   in flight; 4: small input, a workgroup makes outputs of one node and its
+                              *   wavefronts share that node's rounds).  CCDC_ESTATE before ccdc_plan_upload and for plans that call
                               *   answers CCDC_ESIZE or CCDC_ESTATE for */
 };
 
@@ -247,7 +248,7 @@ int ccdc_shuffle_fused(const ccdc_plan_t *plan, const void *V, void *X, void *D,
  * and added to that receiver's output, together with the files it stores itself.
  * X equals ccdc_encode's bit for bit; Phi is bit-exact in XOR mode and, in fp32,
  * a fixed summation order different from ccdc_reduce's.  Any value length and any
- * element-aligned pointers take the same kernel.  Uses the plan's workspace (at
+ * element-aligned pointers take the same kernel, which the plan's sizes alone choose.  Uses the plan's workspace (at
  * most 64 MiB for this call).  CCDC_ESIZE for plans of ccdc_plan_jobs, for r > 5 and for
  * K*r > 256 (the per-lane outputs of all nodes must fit in 64 KB of LDS):
  * use ccdc_shuffle_fused + ccdc_reduce there. */

@@ -11,9 +11,9 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libccdc.so")
-SOURCES = ["ccdc.hip", "pipeline.hip", "node.hip", "noalloc.hip", "map.hip", "plan.cpp"]
-# pipeline.hip has hundreds of kernel instantiations: it is compiled in pieces, two per payload algebra
-PIECES = {"pipeline.hip": ("CCDC_PIPELINE_PART", 10)}
+SOURCES = ["ccdc.hip", "pipeline.hip", "node.hip", "noalloc.hip", "map.hip", "receive.hip", "plan.cpp"]
+# pipeline.hip has hundreds of kernel instantiations: it is compiled in pieces, two per payload algebra; receive.hip in one each
+PIECES = {"pipeline.hip": ("CCDC_PIPELINE_PART", 10), "receive.hip": ("CCDC_RECEIVE_PART", 5)}
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [

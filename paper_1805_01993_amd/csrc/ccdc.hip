@@ -591,7 +591,9 @@ int ccdc_plan_query(const ccdc_plan_t *p, int what, void *out, size_t out_bytes)
     case CCDC_Q_ROUND_BATCH: return table(p->round_batch.data(), p->round_batch.size() * 4);
     case CCDC_Q_PIPELINE_LAUNCH: {
         if (!p->uploaded || !p->pipe_ok) return CCDC_ESTATE;
-        const int32_t launch[4] = {p->pipe_vec, p->pipe_waves, p->pipe_chunks, (p->pipe_even ? 1 : 0) | (p->pipe_shallow ? 2 : 0)};
+        const bool receiver = ccdc::by_receiver(p);
+        const int32_t launch[4] = {p->pipe_vec, p->pipe_waves, receiver ? 1 : p->pipe_chunks,
+                                   receiver ? 4 : (p->pipe_even ? 1 : 0) | (p->pipe_shallow ? 2 : 0)};
         return table(launch, sizeof launch);
     }
     default: break;

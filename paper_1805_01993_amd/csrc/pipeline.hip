@@ -755,7 +755,7 @@ int pipeline_run(const ccdc_plan_t *p, const void *V, void *X, void *Phi, void *
 }
 
 template <class A>
-void pipeline_geometry(ccdc_plan_t *p)
+double pipeline_geometry(ccdc_plan_t *p)
 {
     Candidate best{0, 1, 1, true, false, 0};
     consider<A, 4>(p, &best);
@@ -766,6 +766,7 @@ void pipeline_geometry(ccdc_plan_t *p)
     p->pipe_chunks = best.chunks;
     p->pipe_even = best.even;
     p->pipe_shallow = best.shallow;
+    return best.us;
 }
 
 }  // namespace ccdc
@@ -778,7 +779,7 @@ namespace ccdc {
 #ifdef CCDC_PIPELINE_PART
 #define CCDC_RUN(A)                                                                                              \
     template int pipeline_run<A>(const ccdc_plan_t *, const void *, void *, void *, void *, bool, hipStream_t); \
-    template void pipeline_geometry<A>(ccdc_plan_t *)
+    template double pipeline_geometry<A>(ccdc_plan_t *)
 #define CCDC_KEPT(A) template PipeKernel<A> pipeline_kernel_kept<A>(const ccdc_plan_t *, int)
 #if CCDC_PIPELINE_PART % 5 == 0
 using PieceAlgebra = SumF32;
@@ -800,7 +801,7 @@ CCDC_KEPT(PieceAlgebra);
 #if CCDC_PIPELINE_PART == 0
 #define CCDC_ELSEWHERE(A)                                                                                               \
     extern template int pipeline_run<A>(const ccdc_plan_t *, const void *, void *, void *, void *, bool, hipStream_t); \
-    extern template void pipeline_geometry<A>(ccdc_plan_t *)
+    extern template double pipeline_geometry<A>(ccdc_plan_t *)
 CCDC_ELSEWHERE(XorU32);
 CCDC_ELSEWHERE(HybF32);
 CCDC_ELSEWHERE(HybBF16);
@@ -821,9 +822,9 @@ int pipeline_entry(const ccdc_plan_t *plan, const void *V, void *X, void *Phi, v
     if (plan->compression) return CCDC_ESTATE;       // nothing is coded in that scheme
     if (!plan->pipe_ok) return CCDC_ESIZE;
     if ((rc = pick_vec(plan, &vec_any, V, (const void *)X, (const void *)Phi)) != CCDC_OK) return rc;
+    if (by_receiver(plan)) return receive_entry(plan, V, X, Phi, stream);
     const bool wide_final = vec_any >= 4;            // Phi can be written four elements at a time
     const int chunks = plan->pipe_chunks;
-    if (chunks < 1) return CCDC_ESTATE;
     void *part = plan->d_workspace;
     if (own_part) {
         if (chunks > 1 && (uint64_t)chunks * (uint64_t)plan->K * (uint64_t)plan->W * 4u > (uint64_t)own_part_bytes)
@@ -845,13 +846,15 @@ void pipeline_prepare(ccdc_plan_t *p)
 {
     p->pipe_chunks = p->pipe_waves = p->pipe_vec = 1;
     if (!p->pipe_ok) return;
+    double us = 0;
     switch (p->mode) {
-    case CCDC_F32_SUM: pipeline_geometry<SumF32>(p); break;
-    case CCDC_F32_SUM_XOR: pipeline_geometry<HybF32>(p); break;
-    case CCDC_BF16_SUM_XOR: pipeline_geometry<HybBF16>(p); break;
-    case CCDC_F16_SUM_XOR: pipeline_geometry<HybF16>(p); break;
-    default: pipeline_geometry<XorU32>(p); break;
+    case CCDC_F32_SUM: us = pipeline_geometry<SumF32>(p); break;
+    case CCDC_F32_SUM_XOR: us = pipeline_geometry<HybF32>(p); break;
+    case CCDC_BF16_SUM_XOR: us = pipeline_geometry<HybBF16>(p); break;
+    case CCDC_F16_SUM_XOR: us = pipeline_geometry<HybF16>(p); break;
+    default: us = pipeline_geometry<XorU32>(p); break;
     }
+    receive_prepare(p, us);
 }
 
 #endif

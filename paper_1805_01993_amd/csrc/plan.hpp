@@ -75,7 +75,7 @@ struct ccdc_plan_s {
     void *d_workspace = nullptr;
 
     // launch geometry of the one-pass kernel on this device, fixed at upload time: elements of a
-    // pack, wavefronts of a workgroup (they share a tile of columns) and chunks of rounds
+    // pack, wavefronts of a workgroup (they share a tile of columns) and chunks of rounds (0: by receiver, receive.hip)
     int pipe_vec = 1, pipe_waves = 1, pipe_chunks = 0;
     bool pipe_even = true;              // every wavefront takes a share of the rounds and one of the own rows
     bool pipe_shallow = false;          // one step of the rounds in flight (r = 1, several files a batch)
@@ -103,6 +103,8 @@ constexpr int kPipeGroupLds = 160 * 1024;      // bytes of LDS one workgroup may
 constexpr int kCuLds = 160 * 1024;             // bytes of LDS of a compute unit
 constexpr int kLdsGranule = 1280;              // bytes it is given out in
 constexpr int kPipeMaxR1 = 6;                  // r+1 the kernel is unrolled for
+constexpr int kReceiveMaxWaves = 16;           // wavefronts of a workgroup of the form for small inputs (receive.hip)
+constexpr double kReceiveBytes = 24e6, kReceiveBytesR1 = 48e6;       // a pass of that form moves at most (r = 1: the second)
 
 // Bytes up to which a call reads with ordinary loads (the rules that use them, with both sides measured, are in
 // common.hpp, node.hip and pipeline.hip).  The CPU build of the kernels makes variables of them, to run either side on small inputs.
@@ -122,6 +124,17 @@ void pipeline_prepare(ccdc_plan_t *p);
 // (CCDC_ESIZE when they do not fit).
 int pipeline_entry(const ccdc_plan_t *plan, const void *V, void *X, void *Phi, void *stream, void *own_part,
                    size_t own_part_bytes);
+
+// The form of the pass for small inputs, by receiver (receive.hip): a plan with pipe_chunks = 0 takes it.
+struct ReceiveArgs {
+    int K, m;
+    uint32_t W, ell;                  // elements of a packet and of a segment
+    uint32_t rounds, own;             // rounds a node is in, files it stores
+    int64_t file_stride;
+};
+inline bool by_receiver(const ccdc_plan_t *p) { return p->pipe_chunks == 0; }
+void receive_prepare(ccdc_plan_t *p, double one_pass_us);
+int receive_entry(const ccdc_plan_t *p, const void *V, void *X, void *Phi, void *stream);
 
 // Device address of the fixed scratch array of ccdc_pipeline_fused_noalloc on the
 // current device (noalloc.hip); out may be null to only look it up ahead of time.

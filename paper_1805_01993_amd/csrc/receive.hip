@@ -1,0 +1,339 @@
+// ccdc_pipeline_fused for small inputs: the whole path in one launch that needs no partial outputs in memory.
+#include <algorithm>
+
+#include "common.hpp"
+
+namespace {
+using namespace ccdc;
+
+// A workgroup makes 64 packs of one segment of one node's output.  Its wavefronts share the rounds the node is in and
+// the files it stores; their sums are added in LDS, in wavefront order.  For a round the wavefront reads the r packs
+// of the coded packet that carries the node's segment, forms the coded pack, takes the r-1 packs the node can compute
+// itself back out of it and adds what is left.  Each coded pack is so formed by its r receivers; the one that follows
+// the sender in the round writes it to X.
+//
+// What bounds it: the chain kernel start, table entries, loads, sum, and then the instructions of the loads.  k_pipeline
+// (pipeline.hip) reads every value once but keeps the outputs of all nodes in every wavefront, and where there are few
+// columns it fills the chip by cutting the rounds into chunks, whose outputs a second kernel adds: that launch alone is
+// 2.5 us of host time and as much on the device.  Here values are read by up to r nodes, r times as much through the
+// L2s (an XCD works on neighbouring tiles, so memory is read once), and nothing is left to add.  Passes among others, this
+// kernel against k_pipeline: 24 nodes, r = 1, T = 376 h32 (1.7 MB) 9.2 -> 6.1 us, 21 nodes, r = 1, T = 1112 u32 (3.9 MB) 8.1 ->
+// 5.3, 7 nodes, r = 3, T = 212 f32 8.9 -> 6.1, 10 nodes, r = 2, two functions each, T = 340 f16 9.1 -> 6.1, 11 nodes, r = 2,
+// T = 5536 u32 (19 MB) 10.2 -> 6.9; about 5.5 of these are the host's.  With many nodes and r >= 3 the rounds of a node are
+// too many for one workgroup (17 nodes, r = 3, T = 134 u32: 11.2, 24.6 this way): see receive_prepare().
+// Two stages of loads are in flight, and the list entries of the next.  One stage of 16 packs was 5 to 10 % faster
+// below 4 MB and as much slower above; entries kept in the lanes and taken out with readlane cost more than scalar
+// loads (1.05 of the time over 131 shapes).
+constexpr int receive_steps(int regs, int r, bool multi)     // of a stage; regs: registers a pack takes
+{
+    const int rows = multi ? 6 : 10;                         // scalar registers: the rows of the packs
+    const int packs = 20 / regs < rows ? 20 / regs : rows;
+    return packs / r < 1 ? 1 : packs / r > 6 ? 6 : packs / r;
+}
+constexpr int receive_own(int regs) { return 16 / regs > 8 ? 8 : 16 / regs; }      // own files asked for together
+
+// SHORT: the last segment is short or empty (W is a multiple of VEC all the same).
+template <class A, int VEC, int R1, bool MULTI, bool SHORT>
+__global__ __launch_bounds__(ccdc::kPipeLanes *ccdc::kReceiveMaxWaves) void k_receive(
+    const typename A::elem *__restrict__ V, typename A::elem *__restrict__ X, typename A::elem *__restrict__ Phi,
+    const int32_t *__restrict__ node_rows, const int64_t *__restrict__ src_off, const int64_t *__restrict__ own_rows,
+    ReceiveArgs p)
+{
+    using E = typename A::elem;
+    using O = Ops<A, VEC>;
+    using P = typename O::P;
+    using Q = typename O::Q;
+    using Acc = typename A::acc;
+    constexpr int r = R1 - 1;
+    constexpr uint32_t LANES = ccdc::kPipeLanes;
+    constexpr int regs = (VEC * (int)sizeof(E) + 3) / 4;     // registers a pack takes
+    constexpr int STEPS = receive_steps(regs, r, MULTI), OWN = receive_own(regs);
+    extern __shared__ __align__(16) unsigned char smem[];
+    const uint32_t logical = xcd_contiguous(blockIdx.x, gridDim.x), outputs = (uint32_t)p.K * r;
+    const uint32_t tile = logical / outputs, kr = logical - tile * outputs;
+    const uint32_t node = kr / r, rho = kr - node * r;
+    const uint32_t lane = threadIdx.x % LANES, wave = wave_uniform(threadIdx.x / LANES), waves = blockDim.x / LANES;
+    const uint32_t x = (tile * LANES + lane) * VEC, xb = x * (uint32_t)sizeof(E);
+    Q acc = O::azero();
+
+    // Pack x of segment seg of a row.  Past the packet's end the last pack stands in; it is not used.
+    auto pack_at = [&](const E *row, uint32_t seg) {
+        if constexpr (SHORT) {
+            const uint32_t pos = seg * p.ell + x, last = p.W - VEC;
+            return load_pack_any<true, P, E>(reinterpret_cast<const char *>(row) +
+                                             lane_offset((pos < last ? pos : last) * (uint32_t)sizeof(E)));
+        } else {
+            return load_pack_any<true, P, E>(reinterpret_cast<const char *>(row + seg * p.ell) + lane_offset(xb));
+        }
+    };
+    auto clip = [&](P v, uint32_t seg) {
+        if constexpr (SHORT) v = O::select(seg * p.ell + x < p.W, v, O::zero());
+        return v;
+    };
+
+    const uint32_t back = waves - 1 - wave;
+    const uint32_t i0 = p.own * back / waves, i1 = p.own * (back + 1) / waves;
+    const uint32_t j0 = p.rounds * wave / waves, j1 = p.rounds * (wave + 1) / waves;
+    if (x < p.ell && (i1 > i0 || j1 > j0)) {
+        const int64_t *own = own_rows + (size_t)node * p.own;
+        const int32_t *mine = node_rows + (size_t)node * p.rounds;
+        P first[OWN];
+#pragma unroll
+        for (int t = 0; t < OWN; t++) first[t] = pack_at(V + (own[i0 + t < p.own ? i0 + t : p.own - 1] >> 12), rho);
+
+        // Rounds: a step is a round, or (MULTI) one file of it.  Two stages of steps are in flight, and the entries of the
+        // list that the next one starts from.
+        const uint32_t steps = MULTI ? (j1 - j0) * (uint32_t)p.m : j1 - j0;
+        struct Stage {
+            P w[STEPS][r];
+            uint32_t packet[STEPS];
+        };
+        uint32_t next[STEPS], nf[STEPS], j = j0, f = 0, cf = 0;
+        Q sum[r];
+#pragma unroll
+        for (int q = 0; q < r; q++) sum[q] = O::identity();
+        auto ask = [&] {
+#pragma unroll
+            for (int t = 0; t < STEPS; t++) {
+                next[t] = (uint32_t)mine[j < j1 ? j : j1 - 1];
+                nf[t] = f;
+                if constexpr (MULTI) {
+                    if (++f == (uint32_t)p.m) { f = 0; j++; }
+                } else {
+                    j++;
+                }
+            }
+        };
+        auto load = [&](Stage &s) {
+#pragma unroll
+            for (int t = 0; t < STEPS; t++) {
+                s.packet[t] = next[t];
+                const uint32_t u = next[t] / R1, b = next[t] - u * R1, a = rho < b ? rho : rho + 1;
+                const int64_t *src = src_off + (size_t)u * R1;
+#pragma unroll
+                for (int q = 0; q < r; q++) {
+                    const uint32_t over = (uint32_t)q >= a ? 1 : 0;
+                    const E *row = V + src[q + over];
+                    if constexpr (MULTI) row += nf[t] * p.file_stride;
+                    s.w[t][q] = pack_at(row, a - 1 + over);
+                }
+            }
+            ask();
+        };
+        auto use = [&](Stage &s, uint32_t left) {
+#pragma unroll
+            for (int t = 0; t < STEPS; t++) {
+                if ((uint32_t)t >= left) break;
+                P w[r];
+                if constexpr (MULTI) {
+#pragma unroll
+                    for (int q = 0; q < r; q++) sum[q] = O::accum(sum[q], s.w[t][q]);
+                    if (++cf < (uint32_t)p.m) continue;
+                    cf = 0;
+#pragma unroll
+                    for (int q = 0; q < r; q++) {
+                        w[q] = O::narrow(sum[q]);
+                        sum[q] = O::identity();
+                    }
+                } else {
+#pragma unroll
+                    for (int q = 0; q < r; q++) w[q] = s.w[t][q];
+                }
+                const uint32_t u = s.packet[t] / R1, b = s.packet[t] - u * R1, a = rho < b ? rho : rho + 1;
+                P coded = O::zero();
+#pragma unroll
+                for (int q = 0; q < r; q++) {
+                    w[q] = clip(w[q], a - 1 + ((uint32_t)q >= a ? 1 : 0));
+                    coded = O::code(coded, w[q]);
+                }
+                const uint32_t me = b - (b > a ? 1 : 0);
+                P d = coded;
+#pragma unroll
+                for (int k = 0; k < r; k++) {
+                    if (me != (uint32_t)k) continue;
+#pragma unroll
+                    for (int q = 0; q < r; q++)
+                        if (q != k) d = O::uncode(d, w[q]);
+                }
+                acc = O::accum(acc, d);
+                if (b == (a + 1 == R1 ? 0 : a + 1))
+                    store_any<P, E>(reinterpret_cast<char *>(X + ((size_t)u * R1 + a) * p.ell) + lane_offset(xb), coded);
+            }
+        };
+        if (steps > 0) {
+            Stage even, odd;
+            uint32_t left = steps;
+            ask();
+            load(even);
+            for (;;) {
+                if (left <= STEPS) {
+                    use(even, left);
+                    break;
+                }
+                load(odd);
+                use(even, STEPS);
+                left -= STEPS;
+                if (left <= STEPS) {
+                    use(odd, left);
+                    break;
+                }
+                load(even);
+                use(odd, STEPS);
+                left -= STEPS;
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < OWN; t++)
+            if (i0 + t < i1) acc = O::accum(acc, first[t]);
+        for (uint32_t i = i0 + OWN; i < i1; i += OWN) {
+            P w[OWN];
+#pragma unroll
+            for (int t = 0; t < OWN; t++) w[t] = pack_at(V + (own[i + t < i1 ? i + t : i1 - 1] >> 12), rho);
+#pragma unroll
+            for (int t = 0; t < OWN; t++)
+                if (i + t < i1) acc = O::accum(acc, w[t]);
+        }
+    }
+    reinterpret_cast<Q *>(smem)[threadIdx.x] = acc;
+    __syncthreads();
+    for (uint32_t e = threadIdx.x; e < LANES * VEC; e += blockDim.x) {
+        const uint32_t at = tile * LANES * VEC + e, pos = rho * p.ell + at;
+        if (at >= p.ell || pos >= p.W) continue;
+        const Acc *parts = reinterpret_cast<const Acc *>(smem) + e;
+        Acc v = parts[0];
+        for (uint32_t g = 1; g < waves; g++) v = A::add(v, parts[g * LANES * VEC]);
+        Phi[(size_t)node * p.W + pos] = A::narrow(v);
+    }
+}
+
+template <class A, int VEC, int R1, bool MULTI>
+int launch_receive(const ccdc_plan_t *p, const void *V, void *X, void *Phi, hipStream_t st)
+{
+    using E = typename A::elem;
+    ReceiveArgs args;
+    args.K = p->K;
+    args.m = p->m;
+    args.W = (uint32_t)p->W;
+    args.ell = (uint32_t)p->ell;
+    args.rounds = (uint32_t)p->rows_per_node;
+    args.own = (uint32_t)p->pipe_local_rows;
+    args.file_stride = (int64_t)p->Q * p->T;
+    const uint64_t groups = (uint64_t)p->K * p->r * cdiv((uint64_t)(p->ell / VEC), ccdc::kPipeLanes);
+    if (!fits_launch(groups)) return CCDC_ESIZE;
+    const int threads = ccdc::kPipeLanes * p->pipe_waves;
+    const size_t lds = (size_t)threads * VEC * sizeof(typename A::acc);
+    if (p->ell * p->r == p->W)
+        k_receive<A, VEC, R1, MULTI, false><<<(uint32_t)groups, threads, lds, st>>>(
+            (const E *)V, (E *)X, (E *)Phi, p->d_node_rows, p->d_src_off, p->d_loc_row, args);
+    else
+        k_receive<A, VEC, R1, MULTI, true><<<(uint32_t)groups, threads, lds, st>>>(
+            (const E *)V, (E *)X, (E *)Phi, p->d_node_rows, p->d_src_off, p->d_loc_row, args);
+    return launched();
+}
+
+template <class A, int VEC, int R1>
+int run_files(const ccdc_plan_t *p, const void *V, void *X, void *Phi, hipStream_t st)
+{
+    return p->m > 1 ? launch_receive<A, VEC, R1, true>(p, V, X, Phi, st) : launch_receive<A, VEC, R1, false>(p, V, X, Phi, st);
+}
+
+template <class A, int VEC>
+int run_receive(const ccdc_plan_t *p, const void *V, void *X, void *Phi, hipStream_t st)
+{
+    switch (p->r) {
+    case 1: return run_files<A, VEC, 2>(p, V, X, Phi, st);
+    case 2: return run_files<A, VEC, 3>(p, V, X, Phi, st);
+    case 3: return run_files<A, VEC, 4>(p, V, X, Phi, st);
+    case 4: return run_files<A, VEC, 5>(p, V, X, Phi, st);
+    default: return run_files<A, VEC, 6>(p, V, X, Phi, st);
+    }
+}
+
+}  // namespace
+
+namespace ccdc {
+
+template <class A>
+int receive_run(const ccdc_plan_t *p, const void *V, void *X, void *Phi, hipStream_t st)
+{
+    if (p->pipe_vec == 4) return run_receive<A, 4>(p, V, X, Phi, st);
+    if (p->pipe_vec == 2) return run_receive<A, 2>(p, V, X, Phi, st);
+    return run_receive<A, 1>(p, V, X, Phi, st);
+}
+
+// Compiled in five pieces, one for each algebra, the first with the entry.
+#ifdef CCDC_RECEIVE_PART
+#define CCDC_RECEIVE(A) template int receive_run<A>(const ccdc_plan_t *, const void *, void *, void *, hipStream_t)
+#if CCDC_RECEIVE_PART == 0
+CCDC_RECEIVE(SumF32);
+extern CCDC_RECEIVE(XorU32);
+extern CCDC_RECEIVE(HybF32);
+extern CCDC_RECEIVE(HybBF16);
+extern CCDC_RECEIVE(HybF16);
+#elif CCDC_RECEIVE_PART == 1
+CCDC_RECEIVE(XorU32);
+#elif CCDC_RECEIVE_PART == 2
+CCDC_RECEIVE(HybF32);
+#elif CCDC_RECEIVE_PART == 3
+CCDC_RECEIVE(HybBF16);
+#else
+CCDC_RECEIVE(HybF16);
+#endif
+#endif
+
+#if !defined(CCDC_RECEIVE_PART) || CCDC_RECEIVE_PART == 0
+// Gives the plan this kernel where an estimate of its time (us) is below the one-pass kernel's, one_pass_us.  Both are
+// fitted to passes of 475 shapes of the sizes below (K 4..24, r 1..5, every mode), each with the one-pass kernel's
+// geometry and with 15 of this one's: 305 of them take this kernel, all 475 then take 0.867 of the time before, and
+// would take 0.843 with the best choice each time.  Of 500 other shapes of 64 KB to 50 MB 251 take it, in 0.81 of the time
+// before; two are over 3 % slower, the slowest 5 % (8 nodes, r = 1, T = 40000 f32 5.6 -> 5.9).  Without the margin of
+// a twentieth seven of the 475 were, the slowest 27 %.
+// Above kReceiveBytes it gains little more (24 to 48 MB, r = 2: 0.94 with the best choice each time, r >= 3 0.98; but r = 1,
+// where no value is read twice, 0.82, and 0.93 from 48 to 96 MB).
+void receive_prepare(ccdc_plan_t *p, double one_pass_us)
+{
+    const int eb = elem_bytes(p->mode), r = p->r;
+    const double bytes = moved_bytes(p, (double)p->nrows * p->ell + (double)p->Q * p->T);
+    if (bytes > kKeptBytes || bytes > (r == 1 ? kReceiveBytesR1 : kReceiveBytes)) return;
+    int cus = 0, dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        cus < 1) {
+        (void)hipGetLastError();
+        return;
+    }
+    const int64_t rounds = p->rows_per_node, own = p->pipe_local_rows;
+    double least = 0.95 * (5.9 + (p->m > 1 ? 0.34 : 0.26) * one_pass_us + (p->pipe_chunks > 1 ? 1.1 : 0));
+    for (int vec = 1; vec <= 4; vec *= 2) {
+        if (p->W % vec != 0 || p->ell < vec) break;
+        const int regs = (vec * eb + 3) / 4;
+        const double groups = (double)p->K * r * cdiv((uint64_t)(p->ell / vec), kPipeLanes), fill = std::min(1.0, groups / cus);
+        for (int waves : {2, 4, 8, 12, 16}) {
+            const double gens = std::max(1.0, groups / (cus * std::max(1.0, 14.0 / waves)));
+            const int64_t steps = (rounds + waves - 1) / waves * p->m, files = (own + waves - 1) / waves;
+            const int at_once = receive_steps(regs, r, p->m > 1), own_at_once = receive_own(regs);
+            const double waits = (double)((steps + at_once - 1) / at_once + std::max<int64_t>(0, (files - 1) / own_at_once));
+            const double issue = groups * (double)(rounds * p->m * r + own) / cus * (regs == 4 ? 0.0031 : 0.0097) / fill;
+            const double us = 4.1 + gens * (0.39 * waits + 0.087 * waves) + issue + bytes / 11e6;
+            if (us >= least) continue;
+            least = us;
+            p->pipe_vec = vec;
+            p->pipe_waves = waves;
+            p->pipe_chunks = 0;
+        }
+    }
+}
+
+int receive_entry(const ccdc_plan_t *p, const void *V, void *X, void *Phi, void *stream)
+{
+    hipStream_t st = (hipStream_t)stream;
+    switch (p->mode) {
+    case CCDC_F32_SUM: return receive_run<SumF32>(p, V, X, Phi, st);
+    case CCDC_F32_SUM_XOR: return receive_run<HybF32>(p, V, X, Phi, st);
+    case CCDC_BF16_SUM_XOR: return receive_run<HybBF16>(p, V, X, Phi, st);
+    case CCDC_F16_SUM_XOR: return receive_run<HybF16>(p, V, X, Phi, st);
+    default: return receive_run<XorU32>(p, V, X, Phi, st);
+    }
+}
+#endif
+
+}  // namespace ccdc

@@ -4,6 +4,7 @@
 // Usage: driver K r Q N T mode jobs [cus blocks_per_cu [geometry ...]]  (mode: 0 f32, 1 u32, 2 h32, 3 bf16, 4 f16)
 // A geometry is pack,wavefronts,chunks,flags as in CCDC_Q_PIPELINE_LAUNCH: only the one-pass kernel runs then,
 // as uploaded and with each geometry forced into the plan, against ccdc_combine + ccdc_encode and the plain sum.
+// No chunks (0): the form for small inputs.
 // SHIM_PAST=1: no input is small enough to be read through the caches for its size.  "streamed C n" says that call C made
 // n non-temporal loads.
 // Test infrastructure only.
@@ -96,9 +97,10 @@ static bool force_geometry(ccdc_plan_t *p, const char *text)
 {
     int pack, waves, chunks, flags;
     if (std::sscanf(text, "%d,%d,%d,%d", &pack, &waves, &chunks, &flags) != 4) return false;
-    if ((pack != 1 && pack != 2 && pack != 4) || p->ell < pack || chunks < 1 || chunks > p->pipe_max_chunks || waves < 1 ||
-        waves > ccdc::kPipeMaxWaves || p->K * p->r * ccdc::kPipeLanes * pack * 4 * waves > ccdc::kPipeGroupLds ||
-        p->K * p->r * ccdc::kPipeLanes * pack * 4 > ccdc::kPipeMaxLds)
+    if (chunks == 0 && (p->W % pack != 0 || waves > ccdc::kReceiveMaxWaves)) return false;
+    if ((pack != 1 && pack != 2 && pack != 4) || p->ell < pack || chunks < 0 || chunks > p->pipe_max_chunks || waves < 1 ||
+        (chunks > 0 && (waves > ccdc::kPipeMaxWaves || p->K * p->r * ccdc::kPipeLanes * pack * 4 * waves > ccdc::kPipeGroupLds ||
+                        p->K * p->r * ccdc::kPipeLanes * pack * 4 > ccdc::kPipeMaxLds)))
         return false;
     p->pipe_vec = pack;
     p->pipe_waves = waves;

@@ -124,3 +124,26 @@ def test_large_workgroups_under_sanitizers(kernel_driver, args, forms):  # noqa:
                          env=dict(os.environ, **ENV), timeout=600)
     assert res.returncode == 0, res.stdout + res.stderr
     assert " 0 mismatches" in res.stdout, res.stdout
+
+
+# The form for small inputs, by receiver: pack, wavefronts, no chunks, flags
+RECEIVER = ["1,1,0,0", "1,3,0,0", "2,2,0,0", "2,5,0,0", "4,2,0,0", "4,3,0,0"]
+
+
+@pytest.mark.parametrize("m", [1, 3])
+@pytest.mark.parametrize("r", [1, 2, 3, 4, 5])
+def test_forms_by_receiver(kernel_driver, r, m):  # noqa: F811
+    """As above, one tile of 64 packs and a part of one, ends of a packet that the packs divide, packets shorter than their
+    segments; 6 to 20 rounds a node, one and several stages of them and of own files, wavefronts without any."""
+    K = 7
+
+    def run(k, T):
+        args = (K, r, K, m * comb(K, r), T, (r + k + m) % 5, 0, 8, 8)
+        forms = [f for f in RECEIVER if T % int(f[0]) == 0 and T >= int(f[0])] if T > 3 else ["1,2,0,0", "1,16,0,0"]
+        res = subprocess.run([kernel_driver] + [str(v) for v in args] + forms, capture_output=True, text=True,
+                             env=dict(os.environ, **ENV), timeout=600)
+        assert res.returncode == 0, res.stdout + res.stderr
+        assert " 0 mismatches" in res.stdout, res.stdout
+
+    with ThreadPoolExecutor(4) as pool:
+        list(pool.map(run, range(5), [264 * r, 264 * r - 4 if r > 1 else 260, 264 * r - 2, 68 * r - 3, 3]))
