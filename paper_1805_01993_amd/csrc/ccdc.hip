@@ -290,6 +290,74 @@ __global__ __launch_bounds__(kBlock) void k_reduce_rows(const typename A::elem *
     else reinterpret_cast<P *>(out + red_out[o])[e] = O::narrow(acc);
 }
 
+// The same in one launch: the wavefronts of a workgroup share the row list of 64 packs of an output and add up in LDS.
+// Bound by the launch and the chain list entry, load, sum; the second launch of the split form and the partial sums that
+// it reads back were 2.5 to 5 us of its time.  Which plans: plan_groups() in plan.cpp.  14 nodes, r = 1, T = 952 u32 8.0 -> 5.6 us,
+// 12 nodes, r = 3, two files, T = 6000 f16 (40 MB) 17.3 -> 11.1 to 12, uncoded, 13 nodes, T = 48768 f32 17.8 -> 11; with one stage
+// of rows in flight 3 % slower over 282 plans.
+template <class A, int VEC, bool KEPT>
+__global__ __launch_bounds__(kGroupLanes *kGroupMaxWaves) void k_reduce_group(
+    const typename A::elem *__restrict__ V, const typename A::elem *__restrict__ D, typename A::elem *__restrict__ out,
+    const int64_t *__restrict__ red_ptr, const int64_t *__restrict__ red_row, const int64_t *__restrict__ red_out,
+    uint32_t Wv, uint32_t tiles)
+{
+    using E = typename A::elem;
+    using O = Ops<A, VEC>;
+    using P = typename O::P;
+    constexpr int AHEAD = 8;                              // rows asked for together, two such stages in flight
+    extern __shared__ __align__(16) unsigned char smem[];
+    const uint32_t o = blockIdx.x / tiles, tile = blockIdx.x - o * tiles;
+    const uint32_t lane = threadIdx.x % kGroupLanes, wave = wave_uniform(threadIdx.x / kGroupLanes), waves = blockDim.x / kGroupLanes;
+    const uint32_t e = tile * kGroupLanes + lane;
+    const int64_t first = red_ptr[o], n = red_ptr[o + 1] - first;
+    const int64_t lo = first + n * wave / waves, hi = first + n * (wave + 1) / waves;
+    typename O::Q acc = O::azero();
+    if (e < Wv && hi > lo) {
+        const uint32_t offset = e * (uint32_t)sizeof(P);
+        struct Stage {
+            P v[AHEAD];
+        };
+        int64_t next = lo;
+        auto load = [&](Stage &s) {
+#pragma unroll
+            for (int t = 0; t < AHEAD; t++) {
+                const int64_t row = red_row[next + t < hi ? next + t : hi - 1];
+                const E *base = (row & 1) ? D : V;
+                s.v[t] = load_pack<KEPT, P>(reinterpret_cast<const char *>(base + (row >> 1)) + lane_offset(offset));
+            }
+            next += AHEAD;
+        };
+        auto use = [&](const Stage &s, int64_t left) {
+#pragma unroll
+            for (int t = 0; t < AHEAD; t++)
+                if (t < left) acc = O::accum(acc, s.v[t]);
+        };
+        Stage even, odd;
+        int64_t left = hi - lo;
+        load(even);
+        for (;;) {
+            if (left <= AHEAD) {
+                use(even, left);
+                break;
+            }
+            load(odd);
+            use(even, AHEAD);
+            left -= AHEAD;
+            if (left <= AHEAD) {
+                use(odd, left);
+                break;
+            }
+            load(even);
+            use(odd, AHEAD);
+            left -= AHEAD;
+        }
+    }
+    add_wavefronts<A, VEC>(smem, acc, waves, [&](uint32_t i, typename A::acc v) {
+        const uint32_t at = tile * kGroupLanes * VEC + i;
+        if (at < Wv * VEC) out[red_out[o] + at] = A::narrow(v);
+    });
+}
+
 void release_device(ccdc_plan_t *p)
 {
     if (!p) return;
@@ -440,6 +508,22 @@ int run_shuffle(const ccdc_plan_t *p, const void *V, void *X, void *D, hipStream
 }
 
 template <class A, int VEC>
+void reduce_in_groups(const ccdc_plan_t *p, const void *V, const void *D, void *Phi, bool kept, hipStream_t st)
+{
+    using E = typename A::elem;
+    // the widest packs that make enough workgroups, else those of four bytes
+    if constexpr (VEC > 1 && VEC * sizeof(E) > 4) {
+        if (p->nout * cdiv((uint64_t)(p->W / VEC), kGroupLanes) < kGroupsWanted)
+            return reduce_in_groups<A, VEC / 2>(p, V, D, Phi, kept, st);
+    }
+    const uint32_t Wv = (uint32_t)(p->W / VEC), tiles = cdiv(Wv, kGroupLanes), threads = kGroupLanes * p->red_waves;
+    by_reads<VEC == 1>(kept, [&](auto k) {
+        k_reduce_group<A, VEC, decltype(k)::value><<<(uint32_t)p->nout * tiles, threads, threads * VEC * 4, st>>>(
+            (const E *)V, (const E *)D, (E *)Phi, p->d_red_ptr, p->d_red_row, p->d_red_out, Wv, tiles);
+    });
+}
+
+template <class A, int VEC>
 int run_reduce(const ccdc_plan_t *p, const void *V, const void *D, void *Phi, hipStream_t st)
 {
     using E = typename A::elem;
@@ -450,8 +534,12 @@ int run_reduce(const ccdc_plan_t *p, const void *V, const void *D, void *Phi, hi
     const int64_t chunk_stride = (int64_t)p->J * p->Q * p->T;
     if (!fits_launch(blocks) || !fits_launch((uint64_t)chunk_stride / VEC)) return CCDC_ESIZE;
     using Acc = typename A::acc;
-    WorkspaceOrder order(p, st, split > 1);
     const bool kept = moved_bytes(p, (double)p->nrows * p->W + (double)chunk_stride) <= kKeptStageBytes;        // V, D, Phi
+    if (p->red_waves > 0) {
+        reduce_in_groups<A, VEC>(p, V, D, Phi, kept, st);
+        return launched();
+    }
+    WorkspaceOrder order(p, st, split > 1);
     by_reads<VEC == 1>(kept, [&](auto k) {
         k_reduce_rows<A, VEC, decltype(k)::value><<<(uint32_t)blocks, kBlock, 0, st>>>(
             (const E *)V, (const E *)D, (E *)Phi, (Acc *)p->d_workspace, p->d_red_ptr, p->d_red_row, p->d_red_out, Wv, tiles,

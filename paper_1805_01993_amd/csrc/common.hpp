@@ -368,6 +368,22 @@ inline int reduce_final_groups(int64_t items, int split)
     return G;
 }
 
+// Sums of the wavefronts of one workgroup, every lane's acc: added in LDS (smem, 64 packs of sums a wavefront) in
+// wavefront order; write(i, sum) gets element i of the 64 packs.
+template <class A, int VEC, class F>
+__device__ __forceinline__ void add_wavefronts(unsigned char *smem, const typename Ops<A, VEC>::Q &acc, uint32_t waves, F write)
+{
+    using Acc = typename A::acc;
+    reinterpret_cast<typename Ops<A, VEC>::Q *>(smem)[threadIdx.x] = acc;
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < kGroupLanes * VEC; i += blockDim.x) {
+        const Acc *parts = reinterpret_cast<const Acc *>(smem) + i;
+        Acc v = parts[0];
+        for (uint32_t g = 1; g < waves; g++) v = A::add(v, parts[g * kGroupLanes * VEC]);
+        write(i, v);
+    }
+}
+
 // ------------------------------------------------------------ host helpers
 inline bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
 inline uint32_t cdiv(uint64_t a, uint64_t b) { return (uint32_t)((a + b - 1) / b); }

@@ -293,6 +293,25 @@ int build_compression_plan(int K, int r, int Q, int N, ccdc_plan_t **out)
 
 namespace {
 
+// Wavefronts of a workgroup that sums a whole row list (ccdc_reduce in one launch), 0 where the list is better split over
+// workgroups and added by a second kernel.  Only for plans whose outputs are too few to fill the chip with whole lists
+// (split > 1).  Measured over 282 such plans of 64 KB to 400 MB (every scheme and mode): the one launch takes 0.657 of the
+// split form's time (up to 4 MB 0.68, 4 to 48 MB 0.59, above 0.84), with the best pack and count of wavefronts each time
+// 0.645; one is over 3 % slower (5 %).  A wavefront for two rows is the best share (four 0.659), in all at most 3072.
+// Lists of over 640 rows are left to the split: 16 nodes, r = 4, T = 728 f32 (1820 rows) 24 us, in one launch 28 to 45; 14
+// nodes, r = 5, T = 1227 f16 (2002) 26, 39; and so are inputs past the last-level cache.
+int plan_groups(int64_t nout, int64_t rows, int64_t W, int vec, int64_t split, double bytes)
+{
+    if (split <= 1 || rows > 640 * nout || bytes > 256e6) return 0;
+    int64_t tiles = 0;
+    for (; vec > 0; vec /= 2) {
+        tiles = (W / vec + kGroupLanes - 1) / kGroupLanes;
+        if (nout * tiles >= kGroupsWanted) break;
+    }
+    const int64_t wanted = std::max<int64_t>(2, std::min<int64_t>(kGroupMaxWaves, rows / (2 * nout)));
+    return (int)std::max<int64_t>(2, std::min<int64_t>(wanted, 3072 / (nout * tiles)));
+}
+
 // ccdc_plan_bind for the compression-only scheme: the packet is sent whole (no
 // segments), so ell = W, and every packet is both what is transmitted and what
 // the receiver adds.
@@ -335,6 +354,7 @@ int bind_compression(ccdc_plan_t *p, int64_t T, int mode)
         p->red_out.swap(outs);
         p->nout = nout;
         p->red_split = (int)split;
+        p->red_waves = plan_groups(nout, (int64_t)p->red_row.size(), W, vec, split, ((double)p->N * p->Q * (double)T) * 4);
         p->workspace_bytes = p->red_workspace_bytes = split > 1 ? (size_t)split * (size_t)p->Q * (size_t)T * 4 : 0;
         p->pipe_ok = false;
         p->loc_row.clear();
@@ -479,6 +499,7 @@ int bind_plan(ccdc_plan_t *p, int64_t T, int mode)
         p->red_out.swap(outs);
         p->nout = nout;
         p->red_split = (int)split;
+        p->red_waves = plan_groups(nout, (int64_t)p->red_row.size(), W, vec, split, v_elems * (mode >= CCDC_BF16_SUM_XOR ? 2 : 4));
         p->red_workspace_bytes = split > 1 ? (size_t)split * (size_t)p->J * p->Q * (size_t)T * 4 : 0;
         p->workspace_bytes = p->red_workspace_bytes;         // until upload has fixed the chunks: the most it can be
         if (pipe_ok && pipe_cap > 1)

@@ -54,6 +54,7 @@ struct ccdc_plan_s {
     std::vector<int64_t> red_out;       // [nout] element offset of the output block in Phi
     int64_t nout = 0;                   // J * K output blocks of W elements
     int red_split = 1;                  // the row list of an output is summed in this many chunks
+    int red_waves = 0;                  // > 0: ccdc_reduce sums it in one workgroup of that many wavefronts instead
     size_t red_workspace_bytes = 0;     // partial sums of the split reductions
     size_t workspace_bytes = 0;         // what those and the one-pass kernel's chunks need; exact once uploaded
 
@@ -105,6 +106,11 @@ constexpr int kLdsGranule = 1280;              // bytes it is given out in
 constexpr int kPipeMaxR1 = 6;                  // r+1 the kernel is unrolled for
 constexpr int kReceiveMaxWaves = 16;           // wavefronts of a workgroup of the form for small inputs (receive.hip)
 constexpr double kReceiveBytes = 24e6, kReceiveBytesR1 = 48e6;       // a pass of that form moves at most (r = 1: the second)
+
+// Reductions in one launch: 64 packs of an output a workgroup.
+constexpr uint32_t kGroupLanes = 64;
+constexpr uint32_t kGroupMaxWaves = 16;
+constexpr int64_t kGroupsWanted = 128;         // a workgroup for every second compute unit
 
 // Bytes up to which a call reads with ordinary loads (the rules that use them, with both sides measured, are in
 // common.hpp, node.hip and pipeline.hip).  The CPU build of the kernels makes variables of them, to run either side on small inputs.
