@@ -284,9 +284,8 @@ int ccdc_pipeline_fused_noalloc(const ccdc_plan_t *plan, const void *V, void *X,
  * ccdc_node_decode_reduce writes the node's c outputs of every job,
  *   Phi[job][node*c*T ...]: its own files plus, for every round it is in, the
  *   packet it decodes from the other members' coded packets; the decoded packet
- *   is never stored.  Same row order as ccdc_reduce; uses the plan's workspace
- *   when the sum is split (chunk sums are added as in ccdc_reduce, in groups, in
- *   the same order for one node as for all).
+ *   is never stored.  The rows are added in an order that the plan fixes, the same
+ *   for one node as for all; uses the plan's workspace when the sum is split.
  * Call ccdc_node_encode for all senders of a round before a receiver decodes it.
  * Errors as the stage calls; CCDC_EINVAL for node outside -1..K-1, CCDC_ESTATE
  * for plans of ccdc_plan_compression.

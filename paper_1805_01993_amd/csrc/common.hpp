@@ -398,6 +398,14 @@ inline int ready(const ccdc_plan_t *p)
     return CCDC_OK;
 }
 
+constexpr int kWave = 64;
+// Segments fill the wavefronts of a tile row to at least 3/4.
+inline bool fills_wavefronts(uint32_t Lv)
+{
+    const uint64_t lanes = (uint64_t)cdiv(Lv, kWave) * kWave;
+    return (uint64_t)Lv * 4 >= lanes * 3;
+}
+
 inline int elem_bytes(int mode) { return (mode == CCDC_BF16_SUM_XOR || mode == CCDC_F16_SUM_XOR) ? 2 : 4; }
 
 // kKeptBytes, kKeptStageBytes: non-temporal loads pass the last-level cache (256 MB) by, ordinary ones leave the data

@@ -125,15 +125,7 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
 // T = 512 f32 113 -> 57, 12 nodes r = 3 T = 3000 bf16 with two files a batch 60 -> 38, 20 nodes r = 2
 // T = 352 h32 64 -> 18 (there the chunk sums, added by one thread per output before, were most).
 // The lane-packed kernels stay for segments that would leave over a quarter of the lanes idle.
-constexpr int kWave = 64;
 constexpr int kWaves = kBlock / kWave;
-
-// Segments fill the wavefronts of a tile row to at least 3/4.
-inline bool fills_wavefronts(uint32_t Lv)
-{
-    const uint64_t lanes = (uint64_t)cdiv(Lv, kWave) * kWave;
-    return (uint64_t)Lv * 4 >= lanes * 3;
-}
 
 template <class A, int VEC, int R1, bool MULTI, int READS>
 __global__ __launch_bounds__(kBlock) void k_node_encode_wave(const typename A::elem *__restrict__ V,
@@ -440,6 +432,7 @@ int ccdc_node_decode_reduce(const ccdc_plan_t *plan, int node, const void *V, co
     int rc = node_ready(plan, node), vec = 1;
     if (rc != CCDC_OK) return rc;
     if ((rc = pick_vec(plan, &vec, V, X, (const void *)Phi)) != CCDC_OK) return rc;
+    if (plan->node_waves > 0) return receive_coded(plan, node, V, X, Phi, stream);
     hipStream_t st = (hipStream_t)stream;
     CCDC_DISPATCH(plan, vec, (run_node_decode_reduce<A, VEC>(plan, node, V, X, Phi, st)));
 }

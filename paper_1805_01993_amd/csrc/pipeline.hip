@@ -845,6 +845,7 @@ int pipeline_entry(const ccdc_plan_t *plan, const void *V, void *X, void *Phi, v
 void pipeline_prepare(ccdc_plan_t *p)
 {
     p->pipe_chunks = p->pipe_waves = p->pipe_vec = 1;
+    p->node_waves = 0;
     if (!p->pipe_ok) return;
     double us = 0;
     switch (p->mode) {
@@ -855,6 +856,7 @@ void pipeline_prepare(ccdc_plan_t *p)
     default: us = pipeline_geometry<XorU32>(p); break;
     }
     receive_prepare(p, us);
+    receive_node_prepare(p);
 }
 
 #endif

@@ -81,6 +81,9 @@ struct ccdc_plan_s {
     bool pipe_even = true;              // every wavefront takes a share of the rounds and one of the own rows
     bool pipe_shallow = false;          // one step of the rounds in flight (r = 1, several files a batch)
 
+    // ccdc_node_decode_reduce by receiver: elements of a pack and wavefronts of a workgroup, 0 for its other kernels
+    int node_vec = 1, node_waves = 0;
+
     // Order of the calls that use the workspace, across streams: the last such call
     // recorded ws_event (a hipEvent_t made by ccdc_plan_upload) on ws_stream.
     mutable std::mutex ws_mutex;
@@ -106,6 +109,7 @@ constexpr int kLdsGranule = 1280;              // bytes it is given out in
 constexpr int kPipeMaxR1 = 6;                  // r+1 the kernel is unrolled for
 constexpr int kReceiveMaxWaves = 16;           // wavefronts of a workgroup of the form for small inputs (receive.hip)
 constexpr double kReceiveBytes = 24e6, kReceiveBytesR1 = 48e6;       // a pass of that form moves at most (r = 1: the second)
+constexpr double kReceiveNodeBytes = 48e6;     // inputs and outputs of a node-local decoding of that form
 
 // Reductions in one launch: 64 packs of an output a workgroup.
 constexpr uint32_t kGroupLanes = 64;
@@ -133,14 +137,16 @@ int pipeline_entry(const ccdc_plan_t *plan, const void *V, void *X, void *Phi, v
 
 // The form of the pass for small inputs, by receiver (receive.hip): a plan with pipe_chunks = 0 takes it.
 struct ReceiveArgs {
-    int K, m;
+    int first_node, nodes, m;
     uint32_t W, ell;                  // elements of a packet and of a segment
     uint32_t rounds, own;             // rounds a node is in, files it stores
     int64_t file_stride;
 };
 inline bool by_receiver(const ccdc_plan_t *p) { return p->pipe_chunks == 0; }
 void receive_prepare(ccdc_plan_t *p, double one_pass_us);
+void receive_node_prepare(ccdc_plan_t *p);
 int receive_entry(const ccdc_plan_t *p, const void *V, void *X, void *Phi, void *stream);
+int receive_coded(const ccdc_plan_t *p, int node, const void *V, const void *X, void *Phi, void *stream);
 
 // Device address of the fixed scratch array of ccdc_pipeline_fused_noalloc on the
 // current device (noalloc.hip); out may be null to only look it up ahead of time.

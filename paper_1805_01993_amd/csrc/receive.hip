@@ -1,4 +1,4 @@
-// ccdc_pipeline_fused for small inputs: the whole path in one launch that needs no partial outputs in memory.
+// ccdc_pipeline_fused and ccdc_node_decode_reduce for small inputs: one launch that needs no partial outputs in memory.
 #include <algorithm>
 
 #include "common.hpp"
@@ -33,7 +33,8 @@ constexpr int receive_steps(int regs, int r, bool multi)     // of a stage; regs
 constexpr int receive_own(int regs) { return 16 / regs > 8 ? 8 : 16 / regs; }      // own files asked for together
 
 // SHORT: the last segment is short or empty (W is a multiple of VEC all the same).
-template <class A, int VEC, int R1, bool MULTI, bool SHORT>
+// CODED: the coded packs are read from X, which other nodes sent (ccdc_node_decode_reduce), not formed.
+template <class A, int VEC, int R1, bool MULTI, bool SHORT, bool CODED>
 __global__ __launch_bounds__(ccdc::kPipeLanes *ccdc::kReceiveMaxWaves) void k_receive(
     const typename A::elem *__restrict__ V, typename A::elem *__restrict__ X, typename A::elem *__restrict__ Phi,
     const int32_t *__restrict__ node_rows, const int64_t *__restrict__ src_off, const int64_t *__restrict__ own_rows,
@@ -49,9 +50,9 @@ __global__ __launch_bounds__(ccdc::kPipeLanes *ccdc::kReceiveMaxWaves) void k_re
     constexpr int regs = (VEC * (int)sizeof(E) + 3) / 4;     // registers a pack takes
     constexpr int STEPS = receive_steps(regs, r, MULTI), OWN = receive_own(regs);
     extern __shared__ __align__(16) unsigned char smem[];
-    const uint32_t logical = xcd_contiguous(blockIdx.x, gridDim.x), outputs = (uint32_t)p.K * r;
+    const uint32_t logical = xcd_contiguous(blockIdx.x, gridDim.x), outputs = (uint32_t)p.nodes * r;
     const uint32_t tile = logical / outputs, kr = logical - tile * outputs;
-    const uint32_t node = kr / r, rho = kr - node * r;
+    const uint32_t node = (uint32_t)p.first_node + kr / r, rho = kr % r;
     const uint32_t lane = threadIdx.x % LANES, wave = wave_uniform(threadIdx.x / LANES), waves = blockDim.x / LANES;
     const uint32_t x = (tile * LANES + lane) * VEC, xb = x * (uint32_t)sizeof(E);
     Q acc = O::azero();
@@ -115,7 +116,13 @@ __global__ __launch_bounds__(ccdc::kPipeLanes *ccdc::kReceiveMaxWaves) void k_re
                     const uint32_t over = (uint32_t)q >= a ? 1 : 0;
                     const E *row = V + src[q + over];
                     if constexpr (MULTI) row += nf[t] * p.file_stride;
-                    s.w[t][q] = pack_at(row, a - 1 + over);
+                    uint32_t seg = a - 1 + over;
+                    if constexpr (CODED) {                   // in place of the pack to be decoded
+                        const bool coded = q + over == b;
+                        row = coded ? X + ((size_t)u * R1 + a) * p.ell : row;
+                        seg = coded ? 0 : seg;
+                    }
+                    s.w[t][q] = pack_at(row, seg);
                 }
             }
             ask();
@@ -140,13 +147,14 @@ __global__ __launch_bounds__(ccdc::kPipeLanes *ccdc::kReceiveMaxWaves) void k_re
                     for (int q = 0; q < r; q++) w[q] = s.w[t][q];
                 }
                 const uint32_t u = s.packet[t] / R1, b = s.packet[t] - u * R1, a = rho < b ? rho : rho + 1;
+                const uint32_t me = b - (b > a ? 1 : 0);
                 P coded = O::zero();
 #pragma unroll
                 for (int q = 0; q < r; q++) {
                     w[q] = clip(w[q], a - 1 + ((uint32_t)q >= a ? 1 : 0));
-                    coded = O::code(coded, w[q]);
+                    if constexpr (CODED) coded = O::select((uint32_t)q == me, s.w[t][q], coded);
+                    else coded = O::code(coded, w[q]);
                 }
-                const uint32_t me = b - (b > a ? 1 : 0);
                 P d = coded;
 #pragma unroll
                 for (int k = 0; k < r; k++) {
@@ -156,7 +164,7 @@ __global__ __launch_bounds__(ccdc::kPipeLanes *ccdc::kReceiveMaxWaves) void k_re
                         if (q != k) d = O::uncode(d, w[q]);
                 }
                 acc = O::accum(acc, d);
-                if (b == (a + 1 == R1 ? 0 : a + 1))
+                if (!CODED && b == (a + 1 == R1 ? 0 : a + 1))
                     store_any<P, E>(reinterpret_cast<char *>(X + ((size_t)u * R1 + a) * p.ell) + lane_offset(xb), coded);
             }
         };
@@ -206,46 +214,49 @@ __global__ __launch_bounds__(ccdc::kPipeLanes *ccdc::kReceiveMaxWaves) void k_re
     }
 }
 
-template <class A, int VEC, int R1, bool MULTI>
-int launch_receive(const ccdc_plan_t *p, const void *V, void *X, void *Phi, hipStream_t st)
+// For all nodes (node < 0) or one.  CODED: X is read.
+template <class A, int VEC, int R1, bool MULTI, bool CODED>
+int launch_receive(const ccdc_plan_t *p, int node, int waves, const void *V, const void *X, void *Phi, hipStream_t st)
 {
     using E = typename A::elem;
     ReceiveArgs args;
-    args.K = p->K;
+    args.first_node = node < 0 ? 0 : node;
+    args.nodes = node < 0 ? p->K : 1;
     args.m = p->m;
     args.W = (uint32_t)p->W;
     args.ell = (uint32_t)p->ell;
     args.rounds = (uint32_t)p->rows_per_node;
     args.own = (uint32_t)p->pipe_local_rows;
     args.file_stride = (int64_t)p->Q * p->T;
-    const uint64_t groups = (uint64_t)p->K * p->r * cdiv((uint64_t)(p->ell / VEC), ccdc::kPipeLanes);
+    const uint64_t groups = (uint64_t)args.nodes * p->r * cdiv((uint64_t)(p->ell / VEC), ccdc::kPipeLanes);
     if (!fits_launch(groups)) return CCDC_ESIZE;
-    const int threads = ccdc::kPipeLanes * p->pipe_waves;
+    const int threads = ccdc::kPipeLanes * waves;
     const size_t lds = (size_t)threads * VEC * sizeof(typename A::acc);
     if (p->ell * p->r == p->W)
-        k_receive<A, VEC, R1, MULTI, false><<<(uint32_t)groups, threads, lds, st>>>(
+        k_receive<A, VEC, R1, MULTI, false, CODED><<<(uint32_t)groups, threads, lds, st>>>(
             (const E *)V, (E *)X, (E *)Phi, p->d_node_rows, p->d_src_off, p->d_loc_row, args);
     else
-        k_receive<A, VEC, R1, MULTI, true><<<(uint32_t)groups, threads, lds, st>>>(
+        k_receive<A, VEC, R1, MULTI, true, CODED><<<(uint32_t)groups, threads, lds, st>>>(
             (const E *)V, (E *)X, (E *)Phi, p->d_node_rows, p->d_src_off, p->d_loc_row, args);
     return launched();
 }
 
-template <class A, int VEC, int R1>
-int run_files(const ccdc_plan_t *p, const void *V, void *X, void *Phi, hipStream_t st)
+template <class A, int VEC, int R1, bool CODED>
+int run_files(const ccdc_plan_t *p, int node, int waves, const void *V, const void *X, void *Phi, hipStream_t st)
 {
-    return p->m > 1 ? launch_receive<A, VEC, R1, true>(p, V, X, Phi, st) : launch_receive<A, VEC, R1, false>(p, V, X, Phi, st);
+    return p->m > 1 ? launch_receive<A, VEC, R1, true, CODED>(p, node, waves, V, X, Phi, st)
+                    : launch_receive<A, VEC, R1, false, CODED>(p, node, waves, V, X, Phi, st);
 }
 
-template <class A, int VEC>
-int run_receive(const ccdc_plan_t *p, const void *V, void *X, void *Phi, hipStream_t st)
+template <class A, int VEC, bool CODED>
+int run_receive(const ccdc_plan_t *p, int node, int waves, const void *V, const void *X, void *Phi, hipStream_t st)
 {
     switch (p->r) {
-    case 1: return run_files<A, VEC, 2>(p, V, X, Phi, st);
-    case 2: return run_files<A, VEC, 3>(p, V, X, Phi, st);
-    case 3: return run_files<A, VEC, 4>(p, V, X, Phi, st);
-    case 4: return run_files<A, VEC, 5>(p, V, X, Phi, st);
-    default: return run_files<A, VEC, 6>(p, V, X, Phi, st);
+    case 1: return run_files<A, VEC, 2, CODED>(p, node, waves, V, X, Phi, st);
+    case 2: return run_files<A, VEC, 3, CODED>(p, node, waves, V, X, Phi, st);
+    case 3: return run_files<A, VEC, 4, CODED>(p, node, waves, V, X, Phi, st);
+    case 4: return run_files<A, VEC, 5, CODED>(p, node, waves, V, X, Phi, st);
+    default: return run_files<A, VEC, 6, CODED>(p, node, waves, V, X, Phi, st);
     }
 }
 
@@ -253,23 +264,26 @@ int run_receive(const ccdc_plan_t *p, const void *V, void *X, void *Phi, hipStre
 
 namespace ccdc {
 
-template <class A>
-int receive_run(const ccdc_plan_t *p, const void *V, void *X, void *Phi, hipStream_t st)
+template <class A, bool CODED>
+int receive_run(const ccdc_plan_t *p, int node, int vec, int waves, const void *V, const void *X, void *Phi, hipStream_t st)
 {
-    if (p->pipe_vec == 4) return run_receive<A, 4>(p, V, X, Phi, st);
-    if (p->pipe_vec == 2) return run_receive<A, 2>(p, V, X, Phi, st);
-    return run_receive<A, 1>(p, V, X, Phi, st);
+    if (vec == 4) return run_receive<A, 4, CODED>(p, node, waves, V, X, Phi, st);
+    if (vec == 2) return run_receive<A, 2, CODED>(p, node, waves, V, X, Phi, st);
+    return run_receive<A, 1, CODED>(p, node, waves, V, X, Phi, st);
 }
 
 // Compiled in five pieces, one for each algebra, the first with the entry.
 #ifdef CCDC_RECEIVE_PART
-#define CCDC_RECEIVE(A) template int receive_run<A>(const ccdc_plan_t *, const void *, void *, void *, hipStream_t)
+#define CCDC_RECEIVE_FORM(A, CODED) \
+    template int receive_run<A, CODED>(const ccdc_plan_t *, int, int, int, const void *, const void *, void *, hipStream_t)
+#define CCDC_RECEIVE(A) CCDC_RECEIVE_FORM(A, false); CCDC_RECEIVE_FORM(A, true)
+#define CCDC_ELSEWHERE(A) extern CCDC_RECEIVE_FORM(A, false); extern CCDC_RECEIVE_FORM(A, true)
 #if CCDC_RECEIVE_PART == 0
 CCDC_RECEIVE(SumF32);
-extern CCDC_RECEIVE(XorU32);
-extern CCDC_RECEIVE(HybF32);
-extern CCDC_RECEIVE(HybBF16);
-extern CCDC_RECEIVE(HybF16);
+CCDC_ELSEWHERE(XorU32);
+CCDC_ELSEWHERE(HybF32);
+CCDC_ELSEWHERE(HybBF16);
+CCDC_ELSEWHERE(HybF16);
 #elif CCDC_RECEIVE_PART == 1
 CCDC_RECEIVE(XorU32);
 #elif CCDC_RECEIVE_PART == 2
@@ -282,6 +296,43 @@ CCDC_RECEIVE(HybF16);
 #endif
 
 #if !defined(CCDC_RECEIVE_PART) || CCDC_RECEIVE_PART == 0
+// The pack width and wavefronts of a workgroup of least estimated time: a start, for every generation of workgroups the waits
+// of a wavefront and its own start, the loads a compute unit issues (of less than 16 bytes, of 16) and the bytes.
+struct Shape {
+    int vec, waves;
+    double us;
+};
+struct Costs {
+    double start, wait, load, load16, bytes_per_us;
+};
+Shape best_shape(const ccdc_plan_t *p, const Costs &c, double bytes)
+{
+    Shape best{1, 8, 1e30};
+    int cus = 0, dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        cus < 1) {
+        (void)hipGetLastError();
+        return best;
+    }
+    const int eb = elem_bytes(p->mode), r = p->r;
+    const int64_t rounds = p->rows_per_node, own = p->pipe_local_rows;
+    for (int vec = 1; vec <= 4; vec *= 2) {
+        if (p->W % vec != 0 || p->ell < vec) break;
+        const int regs = (vec * eb + 3) / 4;
+        const double groups = (double)p->K * r * cdiv((uint64_t)(p->ell / vec), kPipeLanes), fill = std::min(1.0, groups / cus);
+        for (int waves : {2, 4, 8, 12, 16}) {
+            const double gens = std::max(1.0, groups / (cus * std::max(1.0, 14.0 / waves)));
+            const int64_t steps = (rounds + waves - 1) / waves * p->m, files = (own + waves - 1) / waves;
+            const int at_once = receive_steps(regs, r, p->m > 1), own_at_once = receive_own(regs);
+            const double waits = (double)((steps + at_once - 1) / at_once + std::max<int64_t>(0, (files - 1) / own_at_once));
+            const double issue = groups * (double)(rounds * p->m * r + own) / cus * (regs == 4 ? c.load16 : c.load) / fill;
+            const double us = c.start + gens * (c.wait * waits + 0.088 * waves) + issue + bytes / c.bytes_per_us;
+            if (us < best.us) best = {vec, waves, us};
+        }
+    }
+    return best;
+}
+
 // Gives the plan this kernel where an estimate of its time (us) is below the one-pass kernel's, one_pass_us.  Both are
 // fitted to passes of 475 shapes of the sizes below (K 4..24, r 1..5, every mode), each with the one-pass kernel's
 // geometry and with 15 of this one's: 305 of them take this kernel, all 475 then take 0.867 of the time before, and
@@ -292,47 +343,60 @@ CCDC_RECEIVE(HybF16);
 // where no value is read twice, 0.82, and 0.93 from 48 to 96 MB).
 void receive_prepare(ccdc_plan_t *p, double one_pass_us)
 {
-    const int eb = elem_bytes(p->mode), r = p->r;
     const double bytes = moved_bytes(p, (double)p->nrows * p->ell + (double)p->Q * p->T);
-    if (bytes > kKeptBytes || bytes > (r == 1 ? kReceiveBytesR1 : kReceiveBytes)) return;
-    int cus = 0, dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        cus < 1) {
-        (void)hipGetLastError();
-        return;
-    }
-    const int64_t rounds = p->rows_per_node, own = p->pipe_local_rows;
-    double least = 0.95 * (5.9 + (p->m > 1 ? 0.34 : 0.26) * one_pass_us + (p->pipe_chunks > 1 ? 1.1 : 0));
-    for (int vec = 1; vec <= 4; vec *= 2) {
-        if (p->W % vec != 0 || p->ell < vec) break;
-        const int regs = (vec * eb + 3) / 4;
-        const double groups = (double)p->K * r * cdiv((uint64_t)(p->ell / vec), kPipeLanes), fill = std::min(1.0, groups / cus);
-        for (int waves : {2, 4, 8, 12, 16}) {
-            const double gens = std::max(1.0, groups / (cus * std::max(1.0, 14.0 / waves)));
-            const int64_t steps = (rounds + waves - 1) / waves * p->m, files = (own + waves - 1) / waves;
-            const int at_once = receive_steps(regs, r, p->m > 1), own_at_once = receive_own(regs);
-            const double waits = (double)((steps + at_once - 1) / at_once + std::max<int64_t>(0, (files - 1) / own_at_once));
-            const double issue = groups * (double)(rounds * p->m * r + own) / cus * (regs == 4 ? 0.0031 : 0.0097) / fill;
-            const double us = 4.1 + gens * (0.39 * waits + 0.087 * waves) + issue + bytes / 11e6;
-            if (us >= least) continue;
-            least = us;
-            p->pipe_vec = vec;
-            p->pipe_waves = waves;
-            p->pipe_chunks = 0;
-        }
+    if (bytes > kKeptBytes || bytes > (p->r == 1 ? kReceiveBytesR1 : kReceiveBytes)) return;
+    const double other = 5.9 + (p->m > 1 ? 0.34 : 0.26) * one_pass_us + (p->pipe_chunks > 1 ? 1.1 : 0);
+    const Shape best = best_shape(p, {4.1, 0.39, 0.0097, 0.0031, 11e6}, bytes);
+    if (best.us >= 0.95 * other) return;
+    p->pipe_vec = best.vec;
+    p->pipe_waves = best.waves;
+    p->pipe_chunks = 0;
+}
+
+// The same for ccdc_node_decode_reduce, against its other kernels: two launches where the row lists are split, a chain of rows
+// each, and lanes without work where segments do not fill wavefronts.  188 plans of 64 KB to 48 MB: 125 take this kernel, all
+// take 0.775 of the time before (best choice each time 0.752), two are over 3 % slower (16 nodes, r = 3, T = 1020 f32, 46 MB 22.8 ->
+// 26.7).  15 nodes, r = 1, T = 680 u32 9.7 -> 6.6 us, 9 nodes, r = 2, T = 8128 f16 13.1 -> 7.0, 6 nodes, r = 4, six files, T = 19264 f16
+// 35.0 -> 10.2.  Above, up to 500 MB, 0.86 of the time to 100 MB and 0.97 beyond, but some up to 1.46.
+void receive_node_prepare(ccdc_plan_t *p)
+{
+    const int eb = elem_bytes(p->mode), r = p->r;
+    const double bytes = moved_bytes(p, (double)p->nrows * p->ell + (double)p->Q * p->T), values = moved_bytes(p, 0);
+    if (bytes > kReceiveNodeBytes || values > (r == 1 ? kKeptStageBytes : (r - 1) * kKeptNodeBytes)) return;
+    const int vec = eb == 4 ? (p->T % 4 == 0 ? 4 : 1) : p->T % 8 == 0 && p->ell % 8 == 0 ? 8 : p->T % 4 == 0 ? 4 : 1;
+    const bool fills = fills_wavefronts((uint32_t)(p->ell / vec));
+    const double rounds = (double)p->rows_per_node, per_round = 1 + (r - 1.0) * p->m, own = (double)p->pipe_local_rows;
+    const double rows = p->K * (rounds * per_round + own) * (double)p->W;                    // elements that are read
+    const double chain = (rounds * per_round / (fills ? 2 : 1) + own / 4) / p->red_split;
+    const double other = 1.7 + (p->red_split > 1 ? 7.3 : 0) + (fills ? 0 : 0.0098 / 256 / 64 * rows / vec) +
+                         0.118e-6 * rows * eb + 0.62 * chain;
+    const Shape best = best_shape(p, {4.05, 0.55, 0.0099, 0.0022, 19e6}, bytes);
+    if (best.us >= 0.9 * other) return;
+    p->node_vec = best.vec;
+    p->node_waves = best.waves;
+}
+
+template <bool CODED>
+int receive_any(const ccdc_plan_t *p, int node, int vec, int waves, const void *V, const void *X, void *Phi, void *stream)
+{
+    hipStream_t st = (hipStream_t)stream;
+    switch (p->mode) {
+    case CCDC_F32_SUM: return receive_run<SumF32, CODED>(p, node, vec, waves, V, X, Phi, st);
+    case CCDC_F32_SUM_XOR: return receive_run<HybF32, CODED>(p, node, vec, waves, V, X, Phi, st);
+    case CCDC_BF16_SUM_XOR: return receive_run<HybBF16, CODED>(p, node, vec, waves, V, X, Phi, st);
+    case CCDC_F16_SUM_XOR: return receive_run<HybF16, CODED>(p, node, vec, waves, V, X, Phi, st);
+    default: return receive_run<XorU32, CODED>(p, node, vec, waves, V, X, Phi, st);
     }
 }
 
 int receive_entry(const ccdc_plan_t *p, const void *V, void *X, void *Phi, void *stream)
 {
-    hipStream_t st = (hipStream_t)stream;
-    switch (p->mode) {
-    case CCDC_F32_SUM: return receive_run<SumF32>(p, V, X, Phi, st);
-    case CCDC_F32_SUM_XOR: return receive_run<HybF32>(p, V, X, Phi, st);
-    case CCDC_BF16_SUM_XOR: return receive_run<HybBF16>(p, V, X, Phi, st);
-    case CCDC_F16_SUM_XOR: return receive_run<HybF16>(p, V, X, Phi, st);
-    default: return receive_run<XorU32>(p, V, X, Phi, st);
-    }
+    return receive_any<false>(p, -1, p->pipe_vec, p->pipe_waves, V, X, Phi, stream);
+}
+
+int receive_coded(const ccdc_plan_t *p, int node, const void *V, const void *X, void *Phi, void *stream)
+{
+    return receive_any<true>(p, node, p->node_vec, p->node_waves, V, X, Phi, stream);
 }
 #endif
 

@@ -1,5 +1,5 @@
-"""ccdc_pipeline_fused on small inputs, where a workgroup makes outputs of one node.  Packets against ccdc_encode's bit for
-bit, outputs against ccdc_shuffle_fused + ccdc_reduce on whole numbers of a small range (field elements; sparse ones in 16
+"""ccdc_pipeline_fused and ccdc_node_decode_reduce on small inputs, where a workgroup makes outputs of one node.  Packets
+against ccdc_shuffle_fused's bit for bit, outputs against ccdc_shuffle_fused + ccdc_reduce on whole numbers of a small range (field elements; sparse ones in 16
 bits), which are exact in every order; and the lines between this form and the one-pass kernel.  Needs a GPU."""
 from math import comb
 
@@ -40,6 +40,13 @@ def run(K, r, c, m, T, mode, shift=0):
         call(V, X, Phi)
         assert torch.equal(X.view(bits), want_X.view(bits)), "X differs"
         assert torch.equal(Phi, want), "Phi differs"
+    Phi.fill_(55)
+    plan.node_decode_reduce(-1, V, want_X, Phi)
+    assert torch.equal(Phi, want), "node-local Phi differs"
+    Phi.fill_(55)
+    for k in range(K):                               # each node reads its own files and the packets sent to it
+        plan.node_decode_reduce(k, V, want_X, Phi)
+    assert torch.equal(Phi, want), "one node's Phi differs"
     for whole, inner in ((Xall, X), (Pall, Phi)):    # nothing outside the outputs was written
         assert bool((whole[:shift] == 77).all()) and bool((whole[shift + inner.numel():] == 77).all())
     plan.close()
