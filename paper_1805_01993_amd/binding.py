@@ -35,6 +35,15 @@ EXPORTS = [
 ]
 
 
+# What the native marshalling (csrc/marshal.cpp) calls: entry point, whether a node number comes first, its tensors.
+_CALLS = [("ccdc_pipeline_fused", False, "V X Phi"), ("ccdc_pipeline_fused_noalloc", False, "V X Phi"),
+          ("ccdc_map", False, "V Phi V"), ("ccdc_combine", False, "V Vbar"), ("ccdc_encode", False, "Vbar X"),
+          ("ccdc_decode", False, "X Vbar D"), ("ccdc_reduce", False, "V D Phi"), ("ccdc_shuffle_fused", False, "V X D"),
+          ("ccdc_node_encode", True, "V X"), ("ccdc_node_decode_reduce", True, "V X Phi")]
+(_PIPELINE, _PIPELINE_NOALLOC, _MAP, _COMBINE, _ENCODE, _DECODE, _REDUCE, _SHUFFLE, _NODE_ENCODE,
+ _NODE_DECODE) = range(len(_CALLS))
+
+
 class CcdcError(RuntimeError):
     def __init__(self, status, where):
         self.status = status
@@ -42,6 +51,7 @@ class CcdcError(RuntimeError):
 
 
 _lib = None
+_marshal = None
 
 
 def load_library():
@@ -87,8 +97,26 @@ def load_library():
         fn = getattr(lib, name)
         fn.restype = C.c_int
         fn.argtypes = [vp, C.c_int] + [vp] * nptr + [vp]
+    _load_marshal(lib)
     _lib = lib
     return lib
+
+
+def _load_marshal(lib):
+    """The native marshalling, built with the library.  Without it every call takes the longer way through ctypes."""
+    global _marshal
+    path = os.path.join(_HERE, "_marshal.so")
+    if os.path.exists(path):
+        import torch  # noqa: F401  (its libraries have to be there)
+        from importlib.machinery import ExtensionFileLoader
+        from importlib.util import module_from_spec, spec_from_loader
+        loader = ExtensionFileLoader("_marshal", path)
+        module = module_from_spec(spec_from_loader("_marshal", loader))
+        loader.exec_module(module)
+        buffers = ("V", "Vbar", "X", "D", "Phi")
+        module.calls([(C.cast(getattr(lib, name), C.c_void_p).value, node, tuple(buffers.index(k) for k in keys.split()))
+                      for name, node, keys in _CALLS])
+        _marshal = module
 
 
 def strerror(status):
@@ -133,8 +161,19 @@ def _stream_ptr(stream):
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
+def _not_here(*args):
+    return None
+
+
+def _failed(status, call):
+    _check(status, _CALLS[call][0])
+
+
 class Plan:
-    """Owns one ccdc_plan_t.  Methods mirror the C entry points."""
+    """Owns one ccdc_plan_t.  Methods mirror the C entry points.
+
+    A call on plain tensors and torch's current stream goes through the native marshalling, which answers None for
+    anything else; the checks and messages below are then what they are without it."""
 
     def __init__(self, K, r, Q, N, jobs=False, compression=False, gamma=1):
         lib = load_library()
@@ -150,8 +189,10 @@ class Plan:
         self.compression = bool(compression)
         self._lib = lib
         self._shapes = None
+        self._quick = None
 
     def close(self):
+        self._quick = None
         if getattr(self, "_h", None):
             self._lib.ccdc_plan_destroy(self._h)
             self._h = None
@@ -167,6 +208,7 @@ class Plan:
         mode = MODES.get(mode, mode)
         _check(self._lib.ccdc_plan_bind(self._h, int(T), mode), "ccdc_plan_bind")
         self._shapes = None
+        self._quick = None
         self._elem_bytes = ELEM_BYTES[mode]
         return self
 
@@ -279,48 +321,77 @@ class Plan:
             raise ValueError(f"{name}: need {want} elements, got {t.numel()}")
         return _dev_ptr(t, name, self._elem_bytes)
 
+    def _quickly(self):
+        """The native marshalling of this plan's calls, once it is bound and open."""
+        if self._shapes is None or not self._h:
+            return _not_here
+        n = self._numel
+        self._quick = _not_here if _marshal is None else _marshal.Marshal(
+            self._h.value, _failed, self._elem_bytes, n["V"], n["Vbar"], n["X"], n["D"], n["Phi"])
+        return self._quick
+
     # ---- Map stand-in: V = theta - files (V may be the files tensor itself)
     def map(self, files, theta, V, stream=None):
+        if stream is None and (self._quick or self._quickly())(_MAP, files, theta, V) == OK:
+            return
         _check(self._lib.ccdc_map(self._h, self._need(files, "V", "files"), self._need(theta, "Phi", "theta"),
                                   self._need(V, "V", "V"), _stream_ptr(stream)), "ccdc_map")
 
     # ---- stages (asynchronous on `stream`, default torch's current stream)
     def combine(self, V, Vbar, stream=None):
+        if stream is None and (self._quick or self._quickly())(_COMBINE, V, Vbar) == OK:
+            return
         _check(self._lib.ccdc_combine(self._h, self._need(V, "V", "V"), self._need(Vbar, "Vbar", "Vbar"),
                                       _stream_ptr(stream)), "ccdc_combine")
 
     def encode(self, Vbar, X, stream=None):
+        if stream is None and (self._quick or self._quickly())(_ENCODE, Vbar, X) == OK:
+            return
         _check(self._lib.ccdc_encode(self._h, self._need(Vbar, "Vbar", "Vbar"), self._need(X, "X", "X"),
                                      _stream_ptr(stream)), "ccdc_encode")
 
     def decode(self, X, Vbar, D, stream=None):
+        if stream is None and (self._quick or self._quickly())(_DECODE, X, Vbar, D) == OK:
+            return
         _check(self._lib.ccdc_decode(self._h, self._need(X, "X", "X"), self._need(Vbar, "Vbar", "Vbar"),
                                      self._need(D, "D", "D"), _stream_ptr(stream)), "ccdc_decode")
 
     def reduce(self, V, D, Phi, stream=None):
+        if stream is None and (self._quick or self._quickly())(_REDUCE, V, D, Phi) == OK:
+            return
         _check(self._lib.ccdc_reduce(self._h, self._need(V, "V", "V"), self._need(D, "D", "D"),
                                      self._need(Phi, "Phi", "Phi"), _stream_ptr(stream)), "ccdc_reduce")
 
     def shuffle_fused(self, V, X, D, stream=None):
+        if stream is None and (self._quick or self._quickly())(_SHUFFLE, V, X, D) == OK:
+            return
         _check(self._lib.ccdc_shuffle_fused(self._h, self._need(V, "V", "V"), self._need(X, "X", "X"),
                                             self._need(D, "D", "D"), _stream_ptr(stream)), "ccdc_shuffle_fused")
 
     def pipeline_fused(self, V, X, Phi, stream=None):
+        if stream is None and (self._quick or self._quickly())(_PIPELINE, V, X, Phi) == OK:
+            return
         _check(self._lib.ccdc_pipeline_fused(self._h, self._need(V, "V", "V"), self._need(X, "X", "X"),
                                              self._need(Phi, "Phi", "Phi"), _stream_ptr(stream)),
                "ccdc_pipeline_fused")
 
     def pipeline_fused_noalloc(self, V, X, Phi, stream=None):
+        if stream is None and (self._quick or self._quickly())(_PIPELINE_NOALLOC, V, X, Phi) == OK:
+            return
         _check(self._lib.ccdc_pipeline_fused_noalloc(self._h, self._need(V, "V", "V"), self._need(X, "X", "X"),
                                                      self._need(Phi, "Phi", "Phi"), _stream_ptr(stream)),
                "ccdc_pipeline_fused_noalloc")
 
     # ---- the node-local form: node = -1 runs every node
     def node_encode(self, node, V, X, stream=None):
+        if stream is None and (self._quick or self._quickly())(_NODE_ENCODE, node, V, X) == OK:
+            return
         _check(self._lib.ccdc_node_encode(self._h, int(node), self._need(V, "V", "V"), self._need(X, "X", "X"),
                                           _stream_ptr(stream)), "ccdc_node_encode")
 
     def node_decode_reduce(self, node, V, X, Phi, stream=None):
+        if stream is None and (self._quick or self._quickly())(_NODE_DECODE, node, V, X, Phi) == OK:
+            return
         _check(self._lib.ccdc_node_decode_reduce(self._h, int(node), self._need(V, "V", "V"), self._need(X, "X", "X"),
                                                  self._need(Phi, "Phi", "Phi"), _stream_ptr(stream)),
                "ccdc_node_decode_reduce")

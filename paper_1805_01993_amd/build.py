@@ -11,6 +11,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libccdc.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 SOURCES = ["ccdc.hip", "pipeline.hip", "node.hip", "noalloc.hip", "map.hip", "receive.hip", "plan.cpp"]
 # pipeline.hip has hundreds of kernel instantiations: it is compiled in pieces, two per payload algebra; receive.hip in one each
 PIECES = {"pipeline.hip": ("CCDC_PIPELINE_PART", 10), "receive.hip": ("CCDC_RECEIVE_PART", 5)}
@@ -38,6 +39,20 @@ def _run(cmd, verbose):
         print(out, flush=True)
 
 
+def build_marshal(verbose: bool = False) -> str:
+    """Compile the native argument marshalling (a CPython module over torch's C++ tensors)."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    flags = ["-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-DUSE_ROCM=1", "-D__HIP_PLATFORM_AMD__=1",
+             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+    inc = [f for d in cpp_extension.include_paths() + [sysconfig.get_paths()["include"], "/opt/rocm/include"] for f in ("-isystem", d)]
+    libs = [f for d in cpp_extension.library_paths() for f in ("-L" + d,)] + ["-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    _run(["g++"] + flags + inc + [os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL] + libs, verbose)
+    return MARSHAL
+
+
 def build_library(verbose: bool = False) -> str:
     """Compile every source (in parallel) and link the shared library."""
     os.makedirs(OBJ, exist_ok=True)
@@ -55,8 +70,10 @@ def build_library(verbose: bool = False) -> str:
         src, obj, extra = unit
         _run([HIPCC] + FLAGS + extra + inc + ["-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj], verbose)
 
-    with ThreadPoolExecutor(max_workers=min(len(units), 8)) as pool:
+    with ThreadPoolExecutor(max_workers=min(len(units) + 1, 8)) as pool:
+        marshal = pool.submit(build_marshal, verbose)
         list(pool.map(compile_one, units))
+        marshal.result()
     _run([HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-fno-gpu-rdc"] + objs + ["-o", LIB], verbose)
     return LIB
 
