@@ -16,7 +16,7 @@ using namespace ccdc;
 // Sec. IV-B pre-combining.  One work item = one pack of one packet Vbar[u][b]:
 // it adds the same pack of the files of the served batch (m of them, or
 // row_files[row] when batches differ in size).
-template <class A, int VEC, bool KEPT>
+template <class A, int VEC, bool KEPT, bool TOGETHER>
 __global__ __launch_bounds__(kBlock) void k_combine(const typename A::elem *__restrict__ V,
                                                     typename A::elem *__restrict__ Vbar,
                                                     const int64_t *__restrict__ src_off,
@@ -35,9 +35,7 @@ __global__ __launch_bounds__(kBlock) void k_combine(const typename A::elem *__re
         reinterpret_cast<P *>(Vbar)[idx] = first;
         return;
     }
-    typename O::Q acc = O::widen(first);
-    for (int f = 1; f < files; f++) acc = O::accum(acc, load_pack<KEPT, P>(src + f * file_stride));
-    reinterpret_cast<P *>(Vbar)[idx] = O::narrow(acc);
+    reinterpret_cast<P *>(Vbar)[idx] = O::narrow(sum_files<O, KEPT, TOGETHER>(first, src, files, file_stride));
 }
 
 // Pre-combining for short packets and long batches (few packs per packet, many
@@ -185,7 +183,9 @@ __global__ __launch_bounds__(kBlock) void k_decode_sender(const typename A::elem
 // pack of its own packet by removing the other r-1 from the coded pack.
 // R1 = r+1 at compile time keeps the r combined packs in registers; R1 = 0 is
 // the any-r fallback that re-reads them (cache hits) instead.
-template <class A, int VEC, int R1, bool KEPT>
+// MULTI: several files a batch (a kernel of their own: their sums in the making take registers that the other would pay for
+// with fewer wavefronts).
+template <class A, int VEC, int R1, bool KEPT, bool MULTI>
 __global__ __launch_bounds__(kBlock) void k_shuffle_fused(const typename A::elem *__restrict__ V,
                                                           typename A::elem *__restrict__ X,
                                                           typename A::elem *__restrict__ D,
@@ -209,13 +209,37 @@ __global__ __launch_bounds__(kBlock) void k_shuffle_fused(const typename A::elem
         const typename A::elem *s = V + src[b] + (int64_t)pos * VEC;
         const P first = load_pack<KEPT, P>(s);
         if (m == 1) return first;                     // a one-file batch is sent as it is
-        typename O::Q acc = O::widen(first);
-        for (int f = 1; f < m; f++) acc = O::accum(acc, load_pack<KEPT, P>(s + f * file_stride));
-        return O::narrow(acc);
+        return O::narrow(sum_files<O, KEPT, files_together<O>()>(first, s, m, file_stride));
     };
 
     P *Drows = reinterpret_cast<P *>(D) + (size_t)u * r1 * Wv;
-    if constexpr (R1 > 0) {
+    if constexpr (R1 > 0 && packets_together<O, R1 - 1>()) {
+        P v[R1 - 1];                                  // of the members other than a
+        const typename A::elem *at[R1 - 1];
+        bool there[R1 - 1];
+#pragma unroll
+        for (int k = 0; k < R1 - 1; k++) {
+            const int b = k + (k >= a ? 1 : 0);
+            const uint32_t pos = segment_rank(a, b) * Lv + x;
+            there[k] = pos < Wv;
+            at[k] = V + src[b] + (int64_t)(there[k] ? pos : 0) * VEC;
+        }
+        sum_packets<O, KEPT>(v, at, there, MULTI ? m : 1, file_stride);
+        P coded = O::zero();
+#pragma unroll
+        for (int k = 0; k < R1 - 1; k++) coded = O::code(coded, v[k]);
+        store_stream(reinterpret_cast<P *>(X) + idx, coded);
+#pragma unroll
+        for (int k = 0; k < R1 - 1; k++) {
+            if (!there[k]) continue;
+            const int b = k + (k >= a ? 1 : 0);
+            P acc = coded;
+#pragma unroll
+            for (int k2 = 0; k2 < R1 - 1; k2++)
+                if (k2 != k) acc = O::uncode(acc, v[k2]);
+            store_stream(Drows + (size_t)b * Wv + segment_rank(a, b) * Lv + x, acc);
+        }
+    } else if constexpr (R1 > 0) {
         P v[R1];
 #pragma unroll
         for (int b = 0; b < R1; b++)
@@ -436,8 +460,10 @@ int run_combine(const ccdc_plan_t *p, const void *V, void *Vbar, hipStream_t st)
         }
     }
     by_reads<false>(kept, [&](auto k) {
-        k_combine<A, VEC, decltype(k)::value><<<cdiv(items, kBlock), kBlock, 0, st>>>(
-            (const E *)V, (E *)Vbar, p->d_src_off, p->d_row_files, Wv, p->m, (int64_t)p->Q * p->T, (uint32_t)items);
+        by_files<Ops<A, VEC>>(p->m > 2 || p->d_row_files, [&](auto together) {
+            k_combine<A, VEC, decltype(k)::value, decltype(together)::value><<<cdiv(items, kBlock), kBlock, 0, st>>>(
+                (const E *)V, (E *)Vbar, p->d_src_off, p->d_row_files, Wv, p->m, (int64_t)p->Q * p->T, (uint32_t)items);
+        });
     });
     return launched();
 }
@@ -486,10 +512,14 @@ void launch_shuffle(const ccdc_plan_t *p, const void *V, void *X, void *D, hipSt
     const uint32_t Wv = (uint32_t)(p->W / VEC), Lv = (uint32_t)(p->ell / VEC);
     const uint64_t items = (uint64_t)p->nround * (p->r + 1) * Lv;
     const bool kept = moved_bytes(p, (double)p->nrows * (p->W + p->ell)) <= kKeptStageBytes;        // V, X and D
-    by_reads<VEC == 1>(kept, [&](auto k) {
-        k_shuffle_fused<A, VEC, R1, decltype(k)::value><<<cdiv(items, kBlock), kBlock, 0, st>>>(
-            (const E *)V, (E *)X, (E *)D, p->d_src_off, p->r + 1, Lv, Wv, p->m, (int64_t)p->Q * p->T, (uint32_t)items);
-    });
+    auto launch = [&](auto multi) {
+        by_reads<VEC == 1>(kept, [&](auto k) {
+            k_shuffle_fused<A, VEC, R1, decltype(k)::value, decltype(multi)::value><<<cdiv(items, kBlock), kBlock, 0, st>>>(
+                (const E *)V, (E *)X, (E *)D, p->d_src_off, p->r + 1, Lv, Wv, p->m, (int64_t)p->Q * p->T, (uint32_t)items);
+        });
+    };
+    if (R1 > 0 && p->m == 1) launch(std::false_type());
+    else launch(std::true_type());
 }
 
 template <class A, int VEC>

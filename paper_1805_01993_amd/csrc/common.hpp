@@ -282,6 +282,102 @@ __device__ __forceinline__ P load_pack_any(const void *p)
         return load_stream_any<P, E>(p);
     }
 }
+
+// Batches of several files.  Asked for one after the other, the files of a batch are as many waits; with packs of less than 16
+// bytes, of which a wavefront has few bytes in flight, several files are asked for together.  Packs of 16 bytes stay with one
+// at a time: past the caches that gives nothing (56 jobs on 8 nodes, r = 2, three files, T = 150000 u32 483 -> 491 us), and sums of
+// eight elements take the registers of other wavefronts (12 nodes, r = 3, two files, T = 6000 f16, node-local decoding 33 -> 38).
+// Two files alone stay too where they are a lane's only packs in flight: combine (6 nodes, r = 4, T = 634231 f32 129 -> 136)
+// and the kernels of node.hip that pack lanes (17 nodes, r = 4, T = 99 h32 46 -> 56).  141 inputs of 20 MB to 2.5 GB: combine
+// down to 0.60 of the time, the fused shuffle 0.42, node-local encoding 0.43, decoding 0.38 (9 nodes, r = 3, T = 36845 bf16, nine
+// files, 0.61, 0.42, 0.45, 0.56).
+template <class O>
+constexpr bool files_together()
+{
+    return sizeof(typename O::P) < 16;
+}
+
+// Calls launch(together) with it as a compile-time constant.
+template <class O, class F>
+void by_files(bool together, F launch)
+{
+    if constexpr (files_together<O>()) {
+        if (together) return launch(std::true_type());
+    }
+    launch(std::false_type());
+}
+
+// The sum of the same pack of `files` files, ascending: `first` is the first one's, at s.
+template <class O, bool KEPT, bool TOGETHER, class E>
+__device__ __forceinline__ typename O::Q sum_files(const typename O::P &first, const E *s, int files, int64_t file_stride)
+{
+    using P = typename O::P;
+    typename O::Q acc = O::widen(first);
+    int f = 1;
+    if constexpr (TOGETHER) {
+        for (; f + 4 <= files; f += 4) {
+            P v[4];
+#pragma unroll
+            for (int t = 0; t < 4; t++) v[t] = load_pack<KEPT, P>(s + (f + t) * file_stride);
+#pragma unroll
+            for (int t = 0; t < 4; t++) acc = O::accum(acc, v[t]);
+        }
+        if (f + 2 <= files) {
+            const P v0 = load_pack<KEPT, P>(s + f * file_stride), v1 = load_pack<KEPT, P>(s + (f + 1) * file_stride);
+            acc = O::accum(O::accum(acc, v0), v1);
+            f += 2;
+        }
+    }
+    for (; f < files; f++) acc = O::accum(acc, load_pack<KEPT, P>(s + f * file_stride));
+    return acc;
+}
+
+// Where the same file of N packets is asked for together: as far as the registers of their sums allow (beyond, wavefronts are
+// lost: eight elements a pack, r = 4, 11 files 43 -> 56 us).
+template <class O, int N>
+constexpr bool packets_together()
+{
+    return files_together<O>() && N * sizeof(typename O::Q) / 4 <= 12;
+}
+
+// The same for the packs s[k] of N packets, narrowed, a file or two of all of them at a time; zeros where there is none (not
+// valid[k]; s[k] can be read all the same).
+template <class O, bool KEPT, int N, class E>
+__device__ __forceinline__ void sum_packets(typename O::P (&v)[N], const E *const (&s)[N], const bool (&valid)[N], int files,
+                                            int64_t file_stride)
+{
+    using P = typename O::P;
+#pragma unroll
+    for (int k = 0; k < N; k++) v[k] = load_pack<KEPT, P>(s[k]);
+    if (files > 1) {                                      // else not sums: the files' values as they are
+        typename O::Q acc[N];
+#pragma unroll
+        for (int k = 0; k < N; k++) acc[k] = O::widen(v[k]);
+        int f = 1;
+        auto some = [&](auto count) {
+            constexpr int C = decltype(count)::value;
+            P w[C][N];
+#pragma unroll
+            for (int t = 0; t < C; t++)
+#pragma unroll
+                for (int k = 0; k < N; k++) w[t][k] = load_pack<KEPT, P>(s[k] + (f + t) * file_stride);
+#pragma unroll
+            for (int t = 0; t < C; t++)
+#pragma unroll
+                for (int k = 0; k < N; k++) acc[k] = O::accum(acc[k], w[t][k]);
+            f += C;
+        };
+        if constexpr (N * sizeof(typename O::Q) / 4 <= 8) {
+            while (f + 2 <= files) some(std::integral_constant<int, 2>());
+        }
+        while (f < files) some(std::integral_constant<int, 1>());
+#pragma unroll
+        for (int k = 0; k < N; k++) v[k] = O::narrow(acc[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < N; k++) v[k] = O::select(valid[k], v[k], O::zero());
+}
+
 template <class P, class E>
 __device__ __forceinline__ void store_stream_any(void *p, const P &v)
 {

@@ -19,7 +19,7 @@ enum Reads {
 
 // Pack `pos` of the packet pre-combined for a round member from the batch that
 // starts at element offset `src` of V (files ascending, narrowed once).
-template <class A, int VEC, bool KEPT>
+template <class A, int VEC, bool KEPT, bool TOGETHER>
 __device__ __forceinline__ typename Ops<A, VEC>::P combined_pack(const typename A::elem *__restrict__ V, int64_t src,
                                                                  uint32_t pos, int m, int64_t file_stride)
 {
@@ -28,9 +28,7 @@ __device__ __forceinline__ typename Ops<A, VEC>::P combined_pack(const typename 
     const typename A::elem *s = V + src + (int64_t)pos * VEC;
     const P first = load_pack<KEPT, P>(s);
     if (m == 1) return first;                         // a one-file batch is sent as it is
-    typename O::Q acc = O::widen(first);
-    for (int f = 1; f < m; f++) acc = O::accum(acc, load_pack<KEPT, P>(s + f * file_stride));
-    return O::narrow(acc);
+    return O::narrow(sum_files<O, KEPT, TOGETHER>(first, s, m, file_stride));
 }
 
 // ------------------------------------------------------- a sender's packets
@@ -38,7 +36,7 @@ __device__ __forceinline__ typename Ops<A, VEC>::P combined_pack(const typename 
 // node sends; null = every packet).  One work item = one pack of X[u][a]: the
 // sender pre-combines, for each other member b, the segment of b's packet that
 // carries the sender's label; it stores all those batches.
-template <class A, int VEC, int READS>
+template <class A, int VEC, int READS, bool TOGETHER>
 __global__ __launch_bounds__(kBlock) void k_node_encode(const typename A::elem *__restrict__ V,
                                                         typename A::elem *__restrict__ X,
                                                         const int64_t *__restrict__ src_off,
@@ -58,7 +56,7 @@ __global__ __launch_bounds__(kBlock) void k_node_encode(const typename A::elem *
     for (int b = 0; b < r1; b++) {
         if (b == a) continue;
         const uint32_t pos = segment_rank(a, b) * Lv + x;
-        if (pos < Wv) coded = O::code(coded, combined_pack<A, VEC, READS == kAll>(V, src[b], pos, m, file_stride));
+        if (pos < Wv) coded = O::code(coded, combined_pack<A, VEC, READS == kAll, TOGETHER>(V, src[b], pos, m, file_stride));
     }
     store_stream(reinterpret_cast<P *>(X) + (size_t)i * Lv + x, coded);
 }
@@ -72,7 +70,7 @@ __global__ __launch_bounds__(kBlock) void k_node_encode(const typename A::elem *
 // is recovered here as that sender's coded pack minus the packs of the other
 // members' packets in it, which the receiver pre-combines from its own files.
 // The list is cut into `split` chunks as in ccdc_reduce.
-template <class A, int VEC, int READS>
+template <class A, int VEC, int READS, bool TOGETHER>
 __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
     const typename A::elem *__restrict__ V, const typename A::elem *__restrict__ X, typename A::elem *__restrict__ out,
     typename A::acc *__restrict__ part, const int64_t *__restrict__ red_ptr, const int64_t *__restrict__ red_row,
@@ -108,7 +106,7 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
         for (int b2 = 0; b2 < r1; b2++) {
             if (b2 == a || b2 == b) continue;
             const uint32_t pos = segment_rank(a, b2) * Lv + x;
-            if (pos < Wv) d = O::uncode(d, combined_pack<A, VEC, READS == kAll>(V, src[b2], pos, m, file_stride));
+            if (pos < Wv) d = O::uncode(d, combined_pack<A, VEC, READS == kAll, TOGETHER>(V, src[b2], pos, m, file_stride));
         }
         acc = O::accum(acc, d);
     }
@@ -127,7 +125,10 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
 // The lane-packed kernels stay for segments that would leave over a quarter of the lanes idle.
 constexpr int kWaves = kBlock / kWave;
 
-template <class A, int VEC, int R1, bool MULTI, int READS>
+// FILES: the files of a batch, one, several in turn or together.
+enum Files { kOneFile, kInTurn, kTogether };
+
+template <class A, int VEC, int R1, int FILES, int READS>
 __global__ __launch_bounds__(kBlock) void k_node_encode_wave(const typename A::elem *__restrict__ V,
                                                              typename A::elem *__restrict__ X,
                                                              const int64_t *__restrict__ src_off,
@@ -146,12 +147,25 @@ __global__ __launch_bounds__(kBlock) void k_node_encode_wave(const typename A::e
     const int a = (int)(i - u * R1);
     const int64_t *src = src_off + (size_t)u * R1;
     P part[R1 - 1];
+    if constexpr (FILES == kTogether && packets_together<O, R1 - 1>()) {
+        const typename A::elem *at[R1 - 1];
+        bool there[R1 - 1];
 #pragma unroll
-    for (int k = 0; k < R1 - 1; k++) {
-        const int b = k + (k >= a ? 1 : 0);
-        const uint32_t pos = segment_rank(a, b) * Lv + x;
-        part[k] = O::zero();
-        if (pos < Wv) part[k] = combined_pack<A, VEC, READS == kAll>(V, src[b], pos, MULTI ? m : 1, file_stride);
+        for (int k = 0; k < R1 - 1; k++) {
+            const int b = k + (k >= a ? 1 : 0);
+            const uint32_t pos = segment_rank(a, b) * Lv + x;
+            there[k] = pos < Wv;
+            at[k] = V + src[b] + (int64_t)(there[k] ? pos : 0) * VEC;
+        }
+        sum_packets<O, READS == kAll>(part, at, there, m, file_stride);
+    } else {
+#pragma unroll
+        for (int k = 0; k < R1 - 1; k++) {
+            const int b = k + (k >= a ? 1 : 0);
+            const uint32_t pos = segment_rank(a, b) * Lv + x;
+            part[k] = O::zero();
+            if (pos < Wv) part[k] = combined_pack<A, VEC, READS == kAll, FILES == kTogether>(V, src[b], pos, FILES == kOneFile ? 1 : m, file_stride);
+        }
     }
     P coded = O::zero();
 #pragma unroll
@@ -160,7 +174,7 @@ __global__ __launch_bounds__(kBlock) void k_node_encode_wave(const typename A::e
 }
 
 // BY_TILE: how the units are numbered, see neighbours_share().
-template <class A, int VEC, int R1, bool MULTI, int READS, bool BY_TILE>
+template <class A, int VEC, int R1, int FILES, int READS, bool BY_TILE>
 __global__ __launch_bounds__(kBlock) void k_node_decode_reduce_wave(
     const typename A::elem *__restrict__ V, const typename A::elem *__restrict__ X, typename A::elem *__restrict__ out,
     typename A::acc *__restrict__ part, const int64_t *__restrict__ red_ptr, const int64_t *__restrict__ red_row,
@@ -171,7 +185,7 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce_wave(
     using O = Ops<A, VEC>;
     using P = typename O::P;
     constexpr int r = R1 - 1;
-    constexpr int AHEAD = MULTI ? 1 : (R1 <= 3 ? 4 : 2);     // received packets asked for together
+    constexpr int AHEAD = FILES != kOneFile ? 1 : (R1 <= 3 ? 4 : 2);     // received packets asked for together
     const uint32_t unit = (BY_TILE ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x) * kWaves + wave_uniform(threadIdx.x / kWave);
     if (unit >= units) return;
     uint32_t tile, oi;
@@ -220,13 +234,30 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce_wave(
         const int low = a < b ? a : b, high = a < b ? b : a;
         const int64_t *src = src_off + (size_t)u * R1;
         k.coded = load_pack<READS != kPast, P>(reinterpret_cast<const P *>(X) + ((size_t)u * R1 + a) * Lv + x);
-#pragma unroll
-        for (int q = 0; q < r - 1; q++) {
-            int b2 = q + (q >= low ? 1 : 0);                 // the q-th member that is neither a nor b
+        auto position = [&](int q, int &b2) {                // of the q-th member that is neither a nor b
+            b2 = q + (q >= low ? 1 : 0);
             b2 += b2 >= high ? 1 : 0;
-            const uint32_t pos = segment_rank(a, b2) * Lv + x;
-            k.side[q] = O::zero();
-            if (pos < Wv) k.side[q] = combined_pack<A, VEC, READS == kAll>(V, src[b2], pos, MULTI ? m : 1, file_stride);
+            return segment_rank(a, b2) * Lv + x;
+        };
+        if constexpr (FILES == kTogether && r > 2 && packets_together<O, r - 1>()) {
+            const typename A::elem *from[r - 1];
+            bool there[r - 1];
+#pragma unroll
+            for (int q = 0; q < r - 1; q++) {
+                int b2;
+                const uint32_t pos = position(q, b2);
+                there[q] = pos < Wv;
+                from[q] = V + src[b2] + (int64_t)(there[q] ? pos : 0) * VEC;
+            }
+            sum_packets<O, READS == kAll>(k.side, from, there, m, file_stride);
+        } else {
+#pragma unroll
+            for (int q = 0; q < r - 1; q++) {
+                int b2;
+                const uint32_t pos = position(q, b2);
+                k.side[q] = O::zero();
+                if (pos < Wv) k.side[q] = combined_pack<A, VEC, READS == kAll, FILES == kTogether>(V, src[b2], pos, FILES == kOneFile ? 1 : m, file_stride);
+            }
         }
     };
     auto use = [&](const Packet &k) {
@@ -282,13 +313,13 @@ __global__ __launch_bounds__(kBlock) void k_node_final(const typename A::acc *__
     }
 }
 
-// Calls launch(r+1, several files a batch) with both as compile-time constants, r <= 5.
-template <class F>
-void by_shape(const ccdc_plan_t *p, F launch)
+// Calls launch(r+1, files of a batch) with both as compile-time constants, r <= 5.
+template <class O, class F>
+void by_shape(const ccdc_plan_t *p, bool together, F launch)
 {
     auto files = [&](auto r1) {
-        if (p->m > 1) launch(r1, std::true_type());
-        else launch(r1, std::false_type());
+        if (p->m == 1) return launch(r1, std::integral_constant<int, kOneFile>());
+        by_files<O>(together, [&](auto t) { launch(r1, std::integral_constant<int, decltype(t)::value ? kTogether : kInTurn>()); });
     };
     switch (p->r) {
     case 1: files(std::integral_constant<int, 2>()); break;
@@ -356,21 +387,23 @@ int run_node_encode(const ccdc_plan_t *p, int node, const void *V, void *X, hipS
     const uint32_t wave_tiles = cdiv(Lv, kWave);
     const uint64_t units = (uint64_t)rows * wave_tiles;
     if (p->r <= 5 && fills_wavefronts(Lv) && fits_launch(units + kWaves)) {
-        auto launch = [&](auto r1, auto multi) {
+        auto launch = [&](auto r1, auto files) {
             constexpr int R1 = decltype(r1)::value;
-            constexpr bool MULTI = decltype(multi)::value;
+            constexpr int FILES = decltype(files)::value;
             by_node_reads<false>(node_reads<VEC>(p, node, true), [&](auto reads) {
-                k_node_encode_wave<A, VEC, R1, MULTI, decltype(reads)::value><<<cdiv(units, kWaves), kBlock, 0, st>>>(
+                k_node_encode_wave<A, VEC, R1, FILES, decltype(reads)::value><<<cdiv(units, kWaves), kBlock, 0, st>>>(
                     (const E *)V, (E *)X, p->d_src_off, list, Lv, Wv, p->m, (int64_t)p->Q * p->T, wave_tiles,
                     (uint32_t)units);
             });
         };
-        by_shape(p, launch);
+        by_shape<Ops<A, VEC>>(p, true, launch);
         return launched();
     }
     by_node_reads<false>(node_reads<VEC>(p, node, false), [&](auto reads) {
-        k_node_encode<A, VEC, decltype(reads)::value><<<cdiv(items, kBlock), kBlock, 0, st>>>(
-            (const E *)V, (E *)X, p->d_src_off, list, p->r + 1, Lv, Wv, p->m, (int64_t)p->Q * p->T, (uint32_t)items);
+        by_files<Ops<A, VEC>>(p->m > 2, [&](auto together) {
+            k_node_encode<A, VEC, decltype(reads)::value, decltype(together)::value><<<cdiv(items, kBlock), kBlock, 0, st>>>(
+                (const E *)V, (E *)X, p->d_src_off, list, p->r + 1, Lv, Wv, p->m, (int64_t)p->Q * p->T, (uint32_t)items);
+        });
     });
     return launched();
 }
@@ -392,12 +425,12 @@ int run_node_decode_reduce(const ccdc_plan_t *p, int node, const void *V, const 
     const uint32_t wave_tiles = cdiv(Lv, kWave);
     const uint64_t units = (uint64_t)count * split * p->r * wave_tiles;
     if (p->r <= 5 && fills_wavefronts(Lv) && fits_launch(units + kWaves)) {
-        auto launch = [&](auto r1, auto multi) {
+        auto launch = [&](auto r1, auto files) {
             constexpr int R1 = decltype(r1)::value;
-            constexpr bool MULTI = decltype(multi)::value;
+            constexpr int FILES = decltype(files)::value;
             by_node_reads<(VEC > 1 && R1 > 2)>(node_reads<VEC>(p, node, true), [&](auto reads) {
                 auto numbered = [&](auto by_tile) {
-                    k_node_decode_reduce_wave<A, VEC, R1, MULTI, decltype(reads)::value, decltype(by_tile)::value><<<cdiv(units, kWaves), kBlock, 0, st>>>(
+                    k_node_decode_reduce_wave<A, VEC, R1, FILES, decltype(reads)::value, decltype(by_tile)::value><<<cdiv(units, kWaves), kBlock, 0, st>>>(
                         (const E *)V, (const E *)X, (E *)Phi, (Acc *)p->d_workspace, p->d_red_ptr, p->d_red_row, p->d_red_out,
                         p->d_src_off, Lv, Wv, 1.0 / (double)p->W, p->m, (int64_t)p->Q * p->T, wave_tiles, split, chunk_stride,
                         o_first, o_step, (uint32_t)units);
@@ -408,13 +441,15 @@ int run_node_decode_reduce(const ccdc_plan_t *p, int node, const void *V, const 
                 numbered(std::false_type());
             });
         };
-        by_shape(p, launch);
+        by_shape<Ops<A, VEC>>(p, p->m > 2 || p->r > 2, launch);     // r = 2: one packet in the making, as in combine
     } else {
         by_node_reads<false>(node_reads<VEC>(p, node, false), [&](auto reads) {
-            k_node_decode_reduce<A, VEC, decltype(reads)::value><<<(uint32_t)blocks, kBlock, 0, st>>>(
-                (const E *)V, (const E *)X, (E *)Phi, (Acc *)p->d_workspace, p->d_red_ptr, p->d_red_row, p->d_red_out,
-                p->d_src_off, p->r + 1, Lv, Wv, p->W, p->m, (int64_t)p->Q * p->T, tiles, split, chunk_stride, o_first,
-                o_step);
+            by_files<Ops<A, VEC>>(p->m > 2, [&](auto together) {
+                k_node_decode_reduce<A, VEC, decltype(reads)::value, decltype(together)::value><<<(uint32_t)blocks, kBlock, 0, st>>>(
+                    (const E *)V, (const E *)X, (E *)Phi, (Acc *)p->d_workspace, p->d_red_ptr, p->d_red_row, p->d_red_out,
+                    p->d_src_off, p->r + 1, Lv, Wv, p->W, p->m, (int64_t)p->Q * p->T, tiles, split, chunk_stride, o_first,
+                    o_step);
+            });
         });
     }
     int rc = launched();
