@@ -86,11 +86,11 @@ TRAFFIC = {
 # Sources that define the kernels and the launch geometry of each path: a recorded traffic
 # figure holds as long as these files are what they were when it was recorded.
 PATH_SOURCES = {
-    "pipeline": ["pipeline.hip", "common.hpp", "plan.hpp", "plan.cpp"],
+    "pipeline": ["pipeline.hip", "receive.hip", "common.hpp", "plan.hpp", "plan.cpp"],
     "shuffle+reduce": ["ccdc.hip", "common.hpp", "plan.hpp", "plan.cpp"],
     "combine+reduce": ["ccdc.hip", "common.hpp", "plan.hpp", "plan.cpp"],
-    "node": ["node.hip", "common.hpp", "plan.hpp", "plan.cpp"],
-    "map+pipeline": ["map.hip", "pipeline.hip", "common.hpp", "plan.hpp", "plan.cpp"],
+    "node": ["node.hip", "receive.hip", "common.hpp", "plan.hpp", "plan.cpp"],
+    "map+pipeline": ["map.hip", "pipeline.hip", "receive.hip", "common.hpp", "plan.hpp", "plan.cpp"],
 }
 
 
