@@ -45,40 +45,40 @@ ALSO = [
 # is recorded with them; for any other source `traffic` is null.
 TRAFFIC = {
     ("cfg3_gradient", "f32", "pipeline"): {
-        "source_hash": "8bda9cfba8bc5e37", "fetch_kib": 1400178.1, "write_kib": 1150000.0, "fetch_scale": 2.0, "write_scale": 1.0,
+        "source_hash": "cc7f84f09b1c36da", "fetch_kib": 1400192.8, "write_kib": 1150000.1, "fetch_scale": 2.0, "write_scale": 1.0,
         "profile": "profiles/pipeline_fused_cfg3_gradient_f32.md"},
     ("cfg5_k24", "f32", "pipeline"): {
-        "source_hash": "8bda9cfba8bc5e37", "fetch_kib": 1040711.3, "write_kib": 462096.0, "fetch_scale": 2.0, "write_scale": 1.0,
+        "source_hash": "cc7f84f09b1c36da", "fetch_kib": 1040715.1, "write_kib": 462096.0, "fetch_scale": 2.0, "write_scale": 1.0,
         "profile": "profiles/pipeline_fused_cfg5_k24_f32.md"},
     ("cfg5_k24", "u32", "pipeline"): {
-        "source_hash": "8bda9cfba8bc5e37", "fetch_kib": 1040695.3, "write_kib": 462096.0, "fetch_scale": 2.0, "write_scale": 1.0,
+        "source_hash": "cc7f84f09b1c36da", "fetch_kib": 1040699.1, "write_kib": 462096.0, "fetch_scale": 2.0, "write_scale": 1.0,
         "profile": "profiles/pipeline_fused_cfg5_k24_u32.md"},
     ("cfg3_gradient", "bf16", "pipeline"): {
-        "source_hash": "8bda9cfba8bc5e37", "fetch_kib": 700199.0, "write_kib": 575000.0, "fetch_scale": 2.0, "write_scale": 1.0,
+        "source_hash": "cc7f84f09b1c36da", "fetch_kib": 700202.1, "write_kib": 575000.0, "fetch_scale": 2.0, "write_scale": 1.0,
         "profile": "profiles/pipeline_fused_cfg3_gradient_bf16.md"},
     ("cfg5_k24", "bf16", "pipeline"): {
-        "source_hash": "8bda9cfba8bc5e37", "fetch_kib": 530669.8, "write_kib": 249480.0, "fetch_scale": 2.0, "write_scale": 1.0,
+        "source_hash": "cc7f84f09b1c36da", "fetch_kib": 530670.9, "write_kib": 249480.0, "fetch_scale": 2.0, "write_scale": 1.0,
         "profile": "profiles/pipeline_fused_cfg5_k24_bf16.md"},
     ("cfg3_gradient", "f32", "shuffle+reduce"): {
-        "source_hash": "23069ef4134f30f1", "fetch_kib": 1050020.2, "write_kib": 3150275.3, "fetch_scale": 2.0, "write_scale": 1.0,
+        "source_hash": "d114ca885f8faf99", "fetch_kib": 1050033.5, "write_kib": 3150258.9, "fetch_scale": 2.0, "write_scale": 1.0,
         "profile": "profiles/shuffle_fused_reduce_cfg3_gradient_f32.md"},
     ("jobs_k8", "f32", "shuffle+reduce"): {
-        "source_hash": "23069ef4134f30f1", "fetch_kib": 909448.6, "write_kib": 892623.5, "fetch_scale": 2.0, "write_scale": 1.0,
+        "source_hash": "d114ca885f8faf99", "fetch_kib": 909384.6, "write_kib": 892648.8, "fetch_scale": 2.0, "write_scale": 1.0,
         "profile": "profiles/shuffle_fused_reduce_jobs_k8_f32.md"},
     ("comp_gradient", "f32", "combine+reduce"): {
-        "source_hash": "23069ef4134f30f1", "fetch_kib": 1050013.9, "write_kib": 300000.0, "fetch_scale": 2.0, "write_scale": 1.0,
+        "source_hash": "d114ca885f8faf99", "fetch_kib": 1050015.7, "write_kib": 300000.0, "fetch_scale": 2.0, "write_scale": 1.0,
         "profile": "profiles/combine_reduce_comp_gradient_f32.md"},
     ("cfg3_gradient", "f32", "node"): {
-        "source_hash": "3e8006ad95aff6d0", "fetch_kib": 2450069.8, "write_kib": 100000.0, "fetch_scale": 2.0, "write_scale": 1.0,
+        "source_hash": "25b14d05b2e4c33e", "fetch_kib": 1948853.6, "write_kib": 100000.0, "fetch_scale": 2.0, "write_scale": 1.0,
         "profile": "profiles/node_encode_decode_reduce_cfg3_gradient_f32.md"},
     ("cfg3_gradient", "f32", "map+pipeline"): {
-        "source_hash": "c6c550f9a2ea1063", "fetch_kib": 1453085.1, "write_kib": 2800000.0, "fetch_scale": 2.0, "write_scale": 1.0,
+        "source_hash": "683a1dc319a77fb4", "fetch_kib": 1453095.0, "write_kib": 2800000.0, "fetch_scale": 2.0, "write_scale": 1.0,
         "profile": "profiles/map_pipeline_fused_cfg3_gradient_f32.md"},
     ("cfg2_k10", "f32", "pipeline"): {
-        "source_hash": "8bda9cfba8bc5e37", "fetch_kib": 10789.8, "write_kib": 6884.5, "fetch_scale": 2.0, "write_scale": 1.0,
+        "source_hash": "cc7f84f09b1c36da", "fetch_kib": 10790.8, "write_kib": 6861.4, "fetch_scale": 2.0, "write_scale": 1.0,
         "profile": "profiles/pipeline_fused_cfg2_k10_f32.md"},
     ("cfg4_k16", "f32", "pipeline"): {
-        "source_hash": "8bda9cfba8bc5e37", "fetch_kib": 75482.0, "write_kib": 44564.4, "fetch_scale": 2.0, "write_scale": 1.0,
+        "source_hash": "cc7f84f09b1c36da", "fetch_kib": 75497.0, "write_kib": 44520.0, "fetch_scale": 2.0, "write_scale": 1.0,
         "profile": "profiles/pipeline_fused_cfg4_k16_f32.md"},
 }
 
