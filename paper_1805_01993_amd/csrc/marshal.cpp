@@ -57,7 +57,7 @@ PyObject *marshal_call(PyObject *self, PyObject *const *args, size_t nargsf, PyO
     if (e.node) {
         if (!PyLong_CheckExact(args[1])) Py_RETURN_NONE;
         const long v = PyLong_AsLong(args[1]);
-        if (v < -1 || v > INT32_MAX) {
+        if (v < -1 || v > INT32_MAX || (v == -1 && PyErr_Occurred())) {       // no long either: -1 and an exception
             PyErr_Clear();
             Py_RETURN_NONE;
         }

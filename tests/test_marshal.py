@@ -24,6 +24,19 @@ def test_it_leaves_what_is_not_ordinary():
     assert plan._quick is None
 
 
+@pytest.mark.parametrize("node", [1 << 31, (1 << 63) - 1, 1 << 63, 1 << 64, -(1 << 63), -(1 << 63) - 1])
+def test_node_numbers_that_do_not_fit_are_left(node):
+    plan = L.ccdc_plan(4, 2, 4, 12).bind(16, "f32")
+    sh = plan.shapes()
+    V, X, Phi = (torch.zeros(sh[k]) for k in ("V", "X", "Phi"))
+    assert plan._quickly()(B._NODE_ENCODE, node, V, X) is None
+    with pytest.raises(ValueError, match="V: need a contiguous device tensor"):
+        plan.node_encode(node, V, X)
+    with pytest.raises(ValueError, match="V: need a contiguous device tensor"):
+        plan.node_decode_reduce(node, V, X, Phi)
+    plan.close()
+
+
 def test_unbound_plans_answer_as_before():
     plan = L.ccdc_plan(4, 2, 4, 12)
     with pytest.raises(B.CcdcError):
