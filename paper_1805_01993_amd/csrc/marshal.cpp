@@ -1,13 +1,15 @@
 // Native argument marshalling for binding.py (the module _marshal): checks the tensors of a call, takes their addresses and
 // torch's current stream, and calls the C entry point.  A small pass is bound by what the host does between two launches: a
 // one-launch call took 4.8 us through ctypes and tensor attributes read from Python, 1.5 of them before the library was
-// entered.  Only the ordinary case is taken: plain torch tensors that fit.  Everything else is answered with
+// entered.  Only the ordinary case is taken: plain torch tensors that fit, and no mode that wants to see what is asked of
+// tensors (torch.overrides.TorchFunctionMode).  Everything else is answered with
 // None, and binding.py goes its own way, which accepts what it accepted and raises what it raised.
 #include <Python.h>
 
 #include <cstddef>
 #include <cstdint>
 
+#include <ATen/PythonTorchFunctionTLS.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -44,7 +46,7 @@ PyObject *marshal_call(PyObject *self, PyObject *const *args, size_t nargsf, PyO
 {
     const Marshal *m = reinterpret_cast<const Marshal *>(self);
     const Py_ssize_t n = PyVectorcall_NARGS(nargsf);
-    if (kwnames || n < 1) Py_RETURN_NONE;
+    if (kwnames || n < 1 || at::impl::torch_function_mode_enabled()) Py_RETURN_NONE;
     const long id = PyLong_AsLong(args[0]);
     if (id < 0 || id >= entries) {
         PyErr_Clear();

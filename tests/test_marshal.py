@@ -79,6 +79,27 @@ def test_calls_reach_the_library():
 
 
 @pytest.mark.gpu
+def test_modes_that_intercept_calls_see_the_tensors():
+    class Seen(torch.overrides.TorchFunctionMode):
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            names.append(getattr(func, "__name__", ""))
+            return func(*args, **(kwargs or {}))
+
+    names = []
+    plan = L.ccdc_plan(4, 2, 4, 12).bind(16, "f32").upload()
+    sh = plan.shapes()
+    V = torch.ones(sh["V"], device="cuda")
+    X, Phi, Phi2 = (torch.zeros(sh[k], device="cuda") for k in ("X", "Phi", "Phi"))
+    plan.pipeline_fused(V, X, Phi)
+    assert type(plan._quick).__name__ == "Marshal"
+    with Seen():
+        plan.pipeline_fused(V, X, Phi2)
+    assert names.count("numel") == names.count("data_ptr") == 3       # of V, X and Phi, in the checks in Python
+    assert torch.equal(Phi, Phi2) and bool((Phi == 12).all())
+    plan.close()
+
+
+@pytest.mark.gpu
 def test_refusals_are_those_of_the_checks():
     plan = L.ccdc_plan(4, 2, 4, 12).bind(16, "f32").upload()
     sh = plan.shapes()
