@@ -14,7 +14,8 @@ namespace ccdc {
 // ----------------------------------------------------------------- algebras
 // elem: what V, Vbar, X, D and Phi hold.  acc: what sums are carried in.
 // widen / add / narrow: pre-combining and the final reduction (a sum is
-// narrowed once, when it is stored as an elem).  code / uncode: forming a coded
+// narrowed once, when it is stored as an elem).  next_file: add, for the files of a
+// batch.  code / uncode: forming a coded
 // packet and cancelling side information from it.  fixed_order: the bits of a
 // pre-combined packet are part of the result (they are XOR-coded), so every
 // kernel adds a batch's files in ascending order.
@@ -28,6 +29,7 @@ struct SumF32 {                       // real numbers throughout
     static __device__ __forceinline__ acc widen(elem a) { return a; }
     static __device__ __forceinline__ elem narrow(acc a) { return a; }
     static __device__ __forceinline__ acc add(acc a, acc b) { return a + b; }
+    static __device__ __forceinline__ acc next_file(acc a, acc b) { return a + b; }
     static __device__ __forceinline__ elem code(elem a, elem b) { return a + b; }
     static __device__ __forceinline__ elem uncode(elem a, elem b) { return a - b; }
     static __device__ __forceinline__ elem gradient(elem theta, elem data) { return theta - data; }
@@ -42,6 +44,7 @@ struct XorU32 {                       // the field F_{2^T} throughout
     static __device__ __forceinline__ acc widen(elem a) { return a; }
     static __device__ __forceinline__ elem narrow(acc a) { return a; }
     static __device__ __forceinline__ acc add(acc a, acc b) { return a ^ b; }
+    static __device__ __forceinline__ acc next_file(acc a, acc b) { return a ^ b; }
     static __device__ __forceinline__ elem code(elem a, elem b) { return a ^ b; }
     static __device__ __forceinline__ elem uncode(elem a, elem b) { return a ^ b; }
     static __device__ __forceinline__ elem gradient(elem theta, elem data) { return theta ^ data; }   // - is XOR in F_{2^T}
@@ -56,6 +59,19 @@ struct HybF32 {                       // numbers are summed, packets are XOR-cod
     static __device__ __forceinline__ acc widen(elem a) { return a; }
     static __device__ __forceinline__ elem narrow(acc a) { return a; }
     static __device__ __forceinline__ acc add(acc a, acc b) { return a + b; }
+    // Of two NaNs the addition hands on its first operand, and the compiler may exchange operands: a sum with two NaNs
+    // of different patterns then differs from kernel to kernel, and a receiver that takes its own form of it out of a coded
+    // packet is left with the difference of the two in place of another packet's number.  Here the sum so far comes first.
+    static __device__ __forceinline__ acc next_file(acc a, acc b)
+    {
+#ifdef __HIP_DEVICE_COMPILE__
+        acc sum;
+        asm("v_add_f32 %0, %1, %2" : "=v"(sum) : "v"(a), "v"(b));
+        return sum;
+#else
+        return a + b;
+#endif
+    }
     static __device__ __forceinline__ elem code(elem a, elem b)
     {
         return __uint_as_float(__float_as_uint(a) ^ __float_as_uint(b));
@@ -118,6 +134,7 @@ struct Hyb16 {
         }
     }
     static __device__ __forceinline__ acc add(acc a, acc b) { return a + b; }
+    static __device__ __forceinline__ acc next_file(acc a, acc b) { return a + b; }     // narrow() makes every NaN the same
     static __device__ __forceinline__ elem code(elem a, elem b) { return (elem)(a ^ b); }
     static __device__ __forceinline__ elem uncode(elem a, elem b) { return (elem)(a ^ b); }
     // the difference of the two values in fp32 (one rounding), rounded once more to the format
@@ -178,6 +195,12 @@ struct Ops {
         return a;
     }
     static __device__ __forceinline__ Q accum(Q a, P b) { return add(a, widen(b)); }
+    static __device__ __forceinline__ Q accum_file(Q a, P b)
+    {
+#pragma unroll
+        for (int i = 0; i < VEC; i++) a.v[i] = A::next_file(a.v[i], A::widen(b.v[i]));
+        return a;
+    }
     static __device__ __forceinline__ P code(P a, P b)
     {
 #pragma unroll
@@ -320,15 +343,15 @@ __device__ __forceinline__ typename O::Q sum_files(const typename O::P &first, c
 #pragma unroll
             for (int t = 0; t < 4; t++) v[t] = load_pack<KEPT, P>(s + (f + t) * file_stride);
 #pragma unroll
-            for (int t = 0; t < 4; t++) acc = O::accum(acc, v[t]);
+            for (int t = 0; t < 4; t++) acc = O::accum_file(acc, v[t]);
         }
         if (f + 2 <= files) {
             const P v0 = load_pack<KEPT, P>(s + f * file_stride), v1 = load_pack<KEPT, P>(s + (f + 1) * file_stride);
-            acc = O::accum(O::accum(acc, v0), v1);
+            acc = O::accum_file(O::accum_file(acc, v0), v1);
             f += 2;
         }
     }
-    for (; f < files; f++) acc = O::accum(acc, load_pack<KEPT, P>(s + f * file_stride));
+    for (; f < files; f++) acc = O::accum_file(acc, load_pack<KEPT, P>(s + f * file_stride));
     return acc;
 }
 
@@ -364,7 +387,7 @@ __device__ __forceinline__ void sum_packets(typename O::P (&v)[N], const E *cons
 #pragma unroll
             for (int t = 0; t < C; t++)
 #pragma unroll
-                for (int k = 0; k < N; k++) acc[k] = O::accum(acc[k], w[t][k]);
+                for (int k = 0; k < N; k++) acc[k] = O::accum_file(acc[k], w[t][k]);
             f += C;
         };
         if constexpr (N * sizeof(typename O::Q) / 4 <= 8) {

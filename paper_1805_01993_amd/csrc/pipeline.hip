@@ -242,7 +242,7 @@ __device__ __forceinline__ void walk(const typename A::elem *__restrict__ V, typ
 #pragma unroll
                     for (int b = 0; b < R1; b++)
 #pragma unroll
-                        for (int rho = 0; rho < r; rho++) sum[b][rho] = O::accum(sum[b][rho], s.w[b][rho]);
+                        for (int rho = 0; rho < r; rho++) sum[b][rho] = O::accum_file(sum[b][rho], s.w[b][rho]);
                     if (++cf == p.m) {
                         P w[R1][r];
 #pragma unroll

@@ -134,7 +134,7 @@ __global__ __launch_bounds__(ccdc::kPipeLanes *ccdc::kReceiveMaxWaves) void k_re
                 P w[r];
                 if constexpr (MULTI) {
 #pragma unroll
-                    for (int q = 0; q < r; q++) sum[q] = O::accum(sum[q], s.w[t][q]);
+                    for (int q = 0; q < r; q++) sum[q] = O::accum_file(sum[q], s.w[t][q]);
                     if (++cf < (uint32_t)p.m) continue;
                     cf = 0;
 #pragma unroll

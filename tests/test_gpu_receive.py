@@ -78,3 +78,34 @@ def test_by_receiver(K, r, c, m, T, mode, shift):
 ])
 def test_where_the_line_lies(K, r, c, T, mode, receiver):
     assert bool(run(K, r, c, 1, T, mode)[3] & BY_RECEIVER) == receiver
+
+
+# files a batch are summed; a plan by receiver in both calls or in neither, packs of one and of four elements
+@pytest.mark.parametrize("K,r,m,T", [(5, 2, 2, 64), (6, 3, 3, 256), (4, 1, 5, 640), (7, 4, 2, 260), (5, 2, 2, 37), (6, 2, 9, 259),
+                                     (7, 3, 2, 40000), (6, 2, 5, 60001)])
+def test_numbers_beside_nans(K, r, m, T):
+    """h32: a batch may sum NaNs of several patterns.  Every call codes the same pattern for it, so it comes out of a coded packet
+    whole and what is decoded beside it stays the number that it is."""
+    N = m * comb(K, r)
+    plan = L.ccdc_plan(K, r, K, N).bind(T, "h32").upload()
+    sh = plan.shapes()
+    g = torch.Generator(device="cuda").manual_seed(T)
+    V = torch.randint(-8, 9, sh["V"], device="cuda", generator=g).float()
+    bits, pick = V.view(torch.int32), torch.rand(sh["V"], device="cuda", generator=g)
+    for i, pattern in enumerate((0x7FC12345, 0x7F800001, 0xFFC54321 - (1 << 32), 0x7FC00000, 0x80000000 - (1 << 32))):
+        bits[(pick >= 0.01 * i) & (pick < 0.01 * (i + 1))] = pattern
+    Vbar, X, X2, X3, X4, D, D2, P1, P2, P3, P4 = (torch.empty(sh[k], device="cuda")
+                                                  for k in "Vbar X X X X D D Phi Phi Phi Phi".split())
+    same = lambda a, b: torch.equal(a.view(torch.int32), b.view(torch.int32))  # noqa: E731
+    plan.combine(V, Vbar), plan.encode(Vbar, X), plan.decode(X, Vbar, D), plan.reduce(V, D, P1)
+    plan.shuffle_fused(V, X2, D2), plan.pipeline_fused(V, X3, P2)
+    plan.node_encode(-1, V, X4), plan.node_decode_reduce(-1, V, X, P3)
+    for k in range(K):
+        plan.node_decode_reduce(k, V, X, P4)
+    assert same(D, Vbar) and same(D2, Vbar)
+    assert same(X2, X) and same(X4, X) and same(X3, X)
+    nan = V.isnan().any(1)
+    want = V.sum(1)
+    for Phi in (P1, P2, P3, P4):
+        assert torch.equal(Phi.isnan(), nan) and torch.equal(Phi[~nan], want[~nan])
+    plan.close()
