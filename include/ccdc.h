@@ -112,12 +112,17 @@ enum ccdc_query {
     CCDC_Q_FILE_NODES,       /* int32_t[J*N][r]    the r nodes that store the file, ascending         */
     CCDC_Q_FILES_PER_NODE,   /* |M_k|: files every node stores, r*J*N/K (= mu*J*N, Sec. IV-A)         */
     CCDC_Q_NODE_FILES,       /* int32_t[K][FILES_PER_NODE] the set M_k: files node k stores, ascending */
-    CCDC_Q_PIPELINE_LAUNCH   /* int32_t[4] what ccdc_plan_upload fixed for ccdc_pipeline_fused: elements of a pack,
+    CCDC_Q_PIPELINE_LAUNCH,  /* int32_t[4] what ccdc_plan_upload fixed for ccdc_pipeline_fused: elements of a pack,
                               *   wavefronts of a workgroup, chunks of rounds, flags (1: every wavefront takes an
                               *   equal share of the rounds and one of the own files; 2: one step of the rounds
                               *   in flight; 4: small input, a workgroup makes outputs of one node and its
                               *   wavefronts share that node's rounds).  CCDC_ESTATE before ccdc_plan_upload and for plans that call
                               *   answers CCDC_ESIZE or CCDC_ESTATE for */
+    CCDC_Q_REDUCE_LAUNCH     /* int32_t[4] the same for the calls that sum row lists: chunks that ccdc_reduce and
+                              *   ccdc_node_decode_reduce cut a list into; wavefronts that sum a whole list in one
+                              *   launch of ccdc_reduce instead (0: none); elements of a pack and wavefronts of
+                              *   ccdc_node_decode_reduce where a workgroup makes outputs of one node, as above, in
+                              *   place of the chunks (0, 0: it does not).  CCDC_ESTATE before ccdc_plan_upload */
 };
 
 /*

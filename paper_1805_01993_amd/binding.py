@@ -25,7 +25,8 @@ ELEM_BYTES = {F32_SUM: 4, U32_XOR: 4, F32_SUM_XOR: 4, BF16_SUM_XOR: 2, F16_SUM_X
  Q_D_ELEMS, Q_PHI_ELEMS, Q_WORKSPACE_BYTES) = range(22)
 (Q_PACKET_LEN, Q_BATCH_JOB, Q_BATCH_FILE0, Q_BATCH_LABEL, Q_ROUND_MEMBER, Q_ROUND_BATCH) = range(64, 70)
 (Q_NROWS, Q_SCHEME, Q_BATCH_FIRST, Q_NODE_BATCH, Q_PACKET_RECV, Q_PACKET_BATCH, Q_PACKET_SEND,
- Q_ROWS_PER_NODE, Q_NODE_ROWS, Q_FILE_NODES, Q_FILES_PER_NODE, Q_NODE_FILES, Q_PIPELINE_LAUNCH) = range(128, 141)
+ Q_ROWS_PER_NODE, Q_NODE_ROWS, Q_FILE_NODES, Q_FILES_PER_NODE, Q_NODE_FILES, Q_PIPELINE_LAUNCH,
+ Q_REDUCE_LAUNCH) = range(128, 142)
 
 EXPORTS = [
     "ccdc_plan", "ccdc_plan_jobs", "ccdc_plan_jobs_repeated", "ccdc_plan_compression", "ccdc_plan_destroy", "ccdc_plan_bind", "ccdc_plan_upload",
@@ -286,6 +287,11 @@ class Plan:
         """What upload() fixed for pipeline_fused: (elements of a pack, wavefronts of a workgroup, chunks of
         rounds, flags)."""
         return tuple(int(v) for v in self.query_table(Q_PIPELINE_LAUNCH, (4,), np.int32))
+
+    def reduce_launch(self):
+        """What upload() fixed for reduce and node_decode_reduce: (chunks of a row list, wavefronts of a whole list in
+        one launch of reduce or 0, and for node_decode_reduce by receiver elements of a pack and wavefronts, or 0, 0)."""
+        return tuple(int(v) for v in self.query_table(Q_REDUCE_LAUNCH, (4,), np.int32))
 
     def packet_len(self):
         return self.query_table(Q_PACKET_LEN, (1 if self.compression else self.r + 1,), np.int64)

@@ -717,6 +717,11 @@ int ccdc_plan_query(const ccdc_plan_t *p, int what, void *out, size_t out_bytes)
                                    receiver ? 4 : (p->pipe_even ? 1 : 0) | (p->pipe_shallow ? 2 : 0)};
         return table(launch, sizeof launch);
     }
+    case CCDC_Q_REDUCE_LAUNCH: {
+        if (!p->uploaded) return CCDC_ESTATE;
+        const int32_t launch[4] = {p->red_split, p->red_waves, p->node_waves > 0 ? p->node_vec : 0, p->node_waves};
+        return table(launch, sizeof launch);
+    }
     default: break;
     }
     if (!p->bound) {

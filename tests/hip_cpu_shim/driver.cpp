@@ -5,6 +5,8 @@
 // A geometry is pack,wavefronts,chunks,flags as in CCDC_Q_PIPELINE_LAUNCH: only the one-pass kernel runs then,
 // as uploaded and with each geometry forced into the plan, against ccdc_combine + ccdc_encode and the plain sum.
 // No chunks (0): the form for small inputs.
+// "reduce a,b,c,d" says what CCDC_Q_REDUCE_LAUNCH does.  SHIM_REDUCE=waves and SHIM_NODE=pack,waves force the form of ccdc_reduce and of
+// ccdc_node_decode_reduce (no wavefronts: their other kernels).
 // SHIM_PAST=1: no input is small enough to be read through the caches for its size.  "streamed C n" says that call C made
 // n non-temporal loads.
 // Test infrastructure only.
@@ -92,6 +94,32 @@ static int limits()
     return bad ? 1 : 0;
 }
 
+// The workspace that the plan's launches need now, exact.
+static bool resize_workspace(ccdc_plan_t *p)
+{
+    (void)hipFree(p->d_workspace);
+    p->d_workspace = nullptr;
+    p->workspace_bytes = std::max(p->red_workspace_bytes, p->pipe_chunks > 1 ? (size_t)p->pipe_chunks * p->K * p->W * 4 : 0);
+    return p->workspace_bytes == 0 || hipMalloc(&p->d_workspace, p->workspace_bytes) == hipSuccess;
+}
+
+// Forces the forms that SHIM_REDUCE and SHIM_NODE name.
+static bool force_reductions(ccdc_plan_t *p)
+{
+    if (const char *text = std::getenv("SHIM_REDUCE")) {
+        p->red_waves = std::atoi(text);
+        if (p->red_waves < 0 || p->red_waves > (int)ccdc::kGroupMaxWaves) return false;
+    }
+    if (const char *text = std::getenv("SHIM_NODE")) {
+        if (std::sscanf(text, "%d,%d", &p->node_vec, &p->node_waves) != 2) return false;
+        const int pack = p->node_vec, waves = p->node_waves;
+        if (waves != 0 && (!p->pipe_ok || (pack != 1 && pack != 2 && pack != 4) || p->W % pack != 0 || p->ell < pack || waves < 1 ||
+                           waves > ccdc::kReceiveMaxWaves))
+            return false;
+    }
+    return resize_workspace(p);
+}
+
 // Gives an uploaded plan another launch geometry for the one-pass kernel, with an exact-size workspace.
 static bool force_geometry(ccdc_plan_t *p, const char *text)
 {
@@ -107,10 +135,7 @@ static bool force_geometry(ccdc_plan_t *p, const char *text)
     p->pipe_chunks = chunks;
     p->pipe_even = flags & 1;
     p->pipe_shallow = flags & 2;
-    (void)hipFree(p->d_workspace);
-    p->workspace_bytes = std::max(p->red_workspace_bytes, chunks > 1 ? (size_t)chunks * p->K * p->W * 4 : 0);
-    p->d_workspace = nullptr;
-    return p->workspace_bytes == 0 || hipMalloc(&p->d_workspace, p->workspace_bytes) == hipSuccess;
+    return resize_workspace(p);
 }
 
 // The workspace holds the partial sums that calls on the uploaded plan write, and no more.
@@ -184,6 +209,13 @@ int main(int argc, char **argv)
     CHECK(jobs ? ccdc_plan_jobs(K, r, Q, N, &p) : ccdc_plan(K, r, Q, N, &p));
     CHECK(ccdc_plan_bind(p, T, mode));
     CHECK(ccdc_plan_upload(p));
+    if (!force_reductions(p)) {
+        std::fprintf(stderr, "the form of a reduction does not fit the plan\n");
+        return 3;
+    }
+    int32_t sums[4];
+    CHECK(ccdc_plan_query(p, CCDC_Q_REDUCE_LAUNCH, sums, sizeof sums));
+    std::printf("reduce %d,%d,%d,%d\n", sums[0], sums[1], sums[2], sums[3]);
     const int64_t nv = query(p, CCDC_Q_V_ELEMS), nvb = query(p, CCDC_Q_VBAR_ELEMS), nx = query(p, CCDC_Q_X_ELEMS),
                   nd = query(p, CCDC_Q_D_ELEMS), nphi = query(p, CCDC_Q_PHI_ELEMS), J = query(p, CCDC_Q_J);
 

@@ -289,8 +289,10 @@ def test_pipeline_launch_needs_an_uploaded_plan(lib):
     out = (C.c_int32 * 4)()
     p = B.ccdc_plan(4, 2, 4, 12)
     assert lib.ccdc_plan_query(p._h, B.Q_PIPELINE_LAUNCH, out, 16) == B.ESTATE
+    assert lib.ccdc_plan_query(p._h, B.Q_REDUCE_LAUNCH, out, 16) == B.ESTATE
     p.bind(16, "f32")
     assert lib.ccdc_plan_query(p._h, B.Q_PIPELINE_LAUNCH, out, 16) == B.ESTATE
+    assert lib.ccdc_plan_query(p._h, B.Q_REDUCE_LAUNCH, out, 16) == B.ESTATE
     p.close()
 
 
