@@ -1,5 +1,6 @@
 // ccdc_pipeline_fused and ccdc_node_decode_reduce for small inputs: one launch that needs no partial outputs in memory.
 #include <algorithm>
+#include <cmath>
 
 #include "common.hpp"
 
@@ -296,6 +297,33 @@ CCDC_RECEIVE(HybF16);
 #endif
 
 #if !defined(CCDC_RECEIVE_PART) || CCDC_RECEIVE_PART == 0
+// What a launch for `nodes` of the nodes is made of: generations of workgroups, the waits of a wavefront one after the other, and
+// the loads that a compute unit issues.
+struct Load {
+    double gens, waits, issue;
+    bool wide;                        // packs of 16 bytes
+};
+Load load_of(const ccdc_plan_t *p, int cus, int nodes, int vec, int waves)
+{
+    const int regs = (vec * elem_bytes(p->mode) + 3) / 4, r = p->r;
+    const int64_t rounds = p->rows_per_node, own = p->pipe_local_rows;
+    const double groups = (double)nodes * r * cdiv((uint64_t)(p->ell / vec), kPipeLanes), fill = std::min(1.0, groups / cus);
+    const int64_t steps = (rounds + waves - 1) / waves * p->m, files = (own + waves - 1) / waves;
+    const int at_once = receive_steps(regs, r, p->m > 1), own_at_once = receive_own(regs);
+    return {std::max(1.0, groups / (cus * std::max(1.0, 14.0 / waves))),
+            (double)((steps + at_once - 1) / at_once + std::max<int64_t>(0, (files - 1) / own_at_once)),
+            groups * (double)(rounds * p->m * r + own) / cus / fill, regs == 4};
+}
+
+int compute_units()
+{
+    int cus = 0, dev = 0;
+    if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess)
+        return cus;
+    (void)hipGetLastError();
+    return 0;
+}
+
 // The pack width and wavefronts of a workgroup of least estimated time: a start, for every generation of workgroups the waits
 // of a wavefront and its own start, the loads a compute unit issues (of less than 16 bytes, of 16) and the bytes.
 struct Shape {
@@ -305,28 +333,15 @@ struct Shape {
 struct Costs {
     double start, wait, load, load16, bytes_per_us;
 };
-Shape best_shape(const ccdc_plan_t *p, const Costs &c, double bytes)
+Shape best_shape(const ccdc_plan_t *p, int cus, const Costs &c, double bytes)
 {
     Shape best{1, 8, 1e30};
-    int cus = 0, dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        cus < 1) {
-        (void)hipGetLastError();
-        return best;
-    }
-    const int eb = elem_bytes(p->mode), r = p->r;
-    const int64_t rounds = p->rows_per_node, own = p->pipe_local_rows;
     for (int vec = 1; vec <= 4; vec *= 2) {
         if (p->W % vec != 0 || p->ell < vec) break;
-        const int regs = (vec * eb + 3) / 4;
-        const double groups = (double)p->K * r * cdiv((uint64_t)(p->ell / vec), kPipeLanes), fill = std::min(1.0, groups / cus);
         for (int waves : {2, 4, 8, 12, 16}) {
-            const double gens = std::max(1.0, groups / (cus * std::max(1.0, 14.0 / waves)));
-            const int64_t steps = (rounds + waves - 1) / waves * p->m, files = (own + waves - 1) / waves;
-            const int at_once = receive_steps(regs, r, p->m > 1), own_at_once = receive_own(regs);
-            const double waits = (double)((steps + at_once - 1) / at_once + std::max<int64_t>(0, (files - 1) / own_at_once));
-            const double issue = groups * (double)(rounds * p->m * r + own) / cus * (regs == 4 ? c.load16 : c.load) / fill;
-            const double us = c.start + gens * (c.wait * waits + 0.088 * waves) + issue + bytes / c.bytes_per_us;
+            const Load l = load_of(p, cus, p->K, vec, waves);
+            const double us = c.start + l.gens * (c.wait * l.waits + 0.088 * waves) + l.issue * (l.wide ? c.load16 : c.load) +
+                              bytes / c.bytes_per_us;
             if (us < best.us) best = {vec, waves, us};
         }
     }
@@ -346,7 +361,9 @@ void receive_prepare(ccdc_plan_t *p, double one_pass_us)
     const double bytes = moved_bytes(p, (double)p->nrows * p->ell + (double)p->Q * p->T);
     if (bytes > kKeptBytes || bytes > (p->r == 1 ? kReceiveBytesR1 : kReceiveBytes)) return;
     const double other = 5.9 + (p->m > 1 ? 0.34 : 0.26) * one_pass_us + (p->pipe_chunks > 1 ? 1.1 : 0);
-    const Shape best = best_shape(p, {4.1, 0.39, 0.0097, 0.0031, 11e6}, bytes);
+    const int cus = compute_units();
+    if (cus < 1) return;
+    const Shape best = best_shape(p, cus, {4.1, 0.39, 0.0097, 0.0031, 11e6}, bytes);
     if (best.us >= 0.95 * other) return;
     p->pipe_vec = best.vec;
     p->pipe_waves = best.waves;
@@ -354,24 +371,36 @@ void receive_prepare(ccdc_plan_t *p, double one_pass_us)
 }
 
 // The same for ccdc_node_decode_reduce, against its other kernels: two launches where the row lists are split, a chain of rows
-// each, and lanes without work where segments do not fill wavefronts.  188 plans of 64 KB to 48 MB: 125 take this kernel, all
-// take 0.775 of the time before (best choice each time 0.752), two are over 3 % slower (16 nodes, r = 3, T = 1020 f32, 46 MB 22.8 ->
-// 26.7).  15 nodes, r = 1, T = 680 u32 9.7 -> 6.6 us, 9 nodes, r = 2, T = 8128 f16 13.1 -> 7.0, 6 nodes, r = 4, six files, T = 19264 f16
-// 35.0 -> 10.2.  Above, up to 500 MB, 0.86 of the time to 100 MB and 0.97 beyond, but some up to 1.46.
+// each, and lanes without work where segments do not fill wavefronts.  A node's outputs are the same bits alone as with all
+// nodes, so one form serves both calls, and it is this one only where it gains for both: the workgroups of one node are few, and where a
+// node is in many rounds its other form spreads them over hundreds (12 nodes, r = 4, T = 1624 f32, 330 rounds: one node 9.2 us, by
+// receiver 26.0; all nodes 20.6, 27.5).
+// Both estimates are fitted to 16411 plans of 64 KB to 48 MB with either form forced, for one node and for all, and to 5800 more that
+// kept the other.  Of 6314 other plans 2930 take this kernel: all nodes 0.565 of the time, one node 0.623; three are over 3 % slower
+// for all nodes (worst 1.19: 7 nodes, r = 5, twelve files, T = 96 h32 13.8 -> 16.3), nine for one (1.18).  Chosen by all nodes
+// alone, one node took up to 3.2 of its time, over 10 % more on one plan in ten; plans that are given up for that would have
+// run all nodes in 0.76 of the time.  15 nodes, r = 1, T = 680 u32 9.7 -> 6.6 us, 9 nodes, r = 2, T = 8128 f16 13.1 -> 7.0, 6 nodes, r = 4, six files,
+// T = 19264 f16 35.0 -> 10.2.  Above kReceiveNodeBytes, up to 500 MB, 0.86 of the time to 100 MB and 0.97 beyond, but some up to 1.46.
 void receive_node_prepare(ccdc_plan_t *p)
 {
-    const int eb = elem_bytes(p->mode), r = p->r;
+    const int eb = elem_bytes(p->mode), r = p->r, cus = compute_units();
     const double bytes = moved_bytes(p, (double)p->nrows * p->ell + (double)p->Q * p->T), values = moved_bytes(p, 0);
-    if (bytes > kReceiveNodeBytes || values > (r == 1 ? kKeptStageBytes : (r - 1) * kKeptNodeBytes)) return;
+    if (cus < 1 || bytes > kReceiveNodeBytes || values > (r == 1 ? kKeptStageBytes : (r - 1) * kKeptNodeBytes)) return;
     const int vec = eb == 4 ? (p->T % 4 == 0 ? 4 : 1) : p->T % 8 == 0 && p->ell % 8 == 0 ? 8 : p->T % 4 == 0 ? 4 : 1;
     const bool fills = fills_wavefronts((uint32_t)(p->ell / vec));
     const double rounds = (double)p->rows_per_node, per_round = 1 + (r - 1.0) * p->m, own = (double)p->pipe_local_rows;
-    const double rows = p->K * (rounds * per_round + own) * (double)p->W;                    // elements that are read
-    const double chain = (rounds * per_round / (fills ? 2 : 1) + own / 4) / p->red_split;
-    const double other = 1.7 + (p->red_split > 1 ? 7.3 : 0) + (fills ? 0 : 0.0098 / 256 / 64 * rows / vec) +
-                         0.118e-6 * rows * eb + 0.62 * chain;
-    const Shape best = best_shape(p, {4.05, 0.55, 0.0099, 0.0022, 19e6}, bytes);
-    if (best.us >= 0.9 * other) return;
+    const double longest = std::ceil((rounds + own) / p->red_split);                         // rows of a chunk
+    const double chain = std::min(longest, rounds) * per_round / (fills ? 2 : 1) + std::max(0.0, longest - rounds) / 4;
+    const Shape best = best_shape(p, cus, {4.05, 0.55, 0.0099, 0.0022, 19e6}, bytes);
+    for (int nodes : {1, p->K}) {
+        const Load l = load_of(p, cus, nodes, best.vec, best.waves);
+        const double us = 3.44 + 0.277 * l.gens * l.waits + (l.wide ? 0.0109 : 0.0132) * l.issue + bytes * nodes / p->K / 30e6;
+        const double rows = nodes * (rounds * per_round + own) * (double)p->W;               // elements that are read
+        const double parts = p->red_split > 1 ? (double)p->red_split * nodes * r * (double)p->ell : 0;
+        const double other = 3.08 + (p->red_split > 1 ? 3.31 : 0) + 1.53e-6 * parts + (fills ? 0 : 1.59e-6 * rows / vec) +
+                             0.115e-6 * rows * eb + 0.194 * chain;
+        if (us >= 0.85 * other) return;
+    }
     p->node_vec = best.vec;
     p->node_waves = best.waves;
 }

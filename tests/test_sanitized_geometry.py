@@ -147,3 +147,25 @@ def test_forms_by_receiver(kernel_driver, r, m):  # noqa: F811
 
     with ThreadPoolExecutor(4) as pool:
         list(pool.map(run, range(5), [264 * r, 264 * r - 4 if r > 1 else 260, 264 * r - 2, 68 * r - 3, 3]))
+
+
+def choices(kernel_driver, K, r, N, T, mode):
+    """What a plan takes on 256 compute units: CCDC_Q_PIPELINE_LAUNCH and CCDC_Q_REDUCE_LAUNCH."""
+    res = subprocess.run([kernel_driver] + [str(v) for v in (K, r, K, N, T, mode, 0, 256, 16)], capture_output=True, text=True,
+                         env=dict(os.environ, SHIM_PLAN_ONLY="1", **ENV), timeout=600)
+    assert res.returncode == 0, res.stdout + res.stderr
+    said = dict(l.split() for l in res.stdout.splitlines())
+    return [[int(v) for v in said[k].split(",")] for k in ("launch", "reduce")]
+
+
+# K, r, files a batch, T, mode; whether node-local decoding is by receiver, for one node as for all
+@pytest.mark.parametrize("K,r,m,T,mode,receiver", [
+    (15, 1, 1, 680, 1, True), (9, 2, 1, 8128, 4, True), (6, 4, 6, 7200, 0, True), (20, 1, 1, 64, 0, True),
+    (12, 4, 1, 1624, 0, False),        # one node 9.2 us with its rounds spread over 108 chunks, by receiver 26
+    (15, 3, 1, 1104, 2, False),        # 11.6 and 20.0
+    (13, 4, 1, 1048, 1, False),        # 15.0 and 47.3
+    (20, 3, 1, 388, 3, False),
+    (18, 2, 1, 64, 1, False),          # 6.8 and 9.4; all nodes 8.0 and 11.3
+])
+def test_node_local_form_fits_one_node_and_all(kernel_driver, K, r, m, T, mode, receiver):  # noqa: F811
+    assert (choices(kernel_driver, K, r, m * comb(K, r), T, mode)[1][3] > 0) == receiver
