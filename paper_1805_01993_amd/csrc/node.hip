@@ -356,12 +356,20 @@ Reads node_reads(const ccdc_plan_t *p, int node, bool by_wavefront)
 }
 
 // Whether k_node_decode_reduce_wave numbers its units by tile, an XCD on a contiguous range of them, so that the nodes that read
-// the same packs run next to each other behind one L2; else the tiles of one output are neighbours, on all XCDs.  For
-// all nodes of one job, packs of 16 bytes and 16 tiles or more: 20 plans of 50 MB to 2 GB take 0.92 of the time, one is over 4 %
-// slower (6 nodes, r = 3, T = 554384 f32 85 -> 68 us, 12 nodes, r = 2, two functions each, T = 155840 u32 271 -> 249).  With fewer tiles the
-// rows of one are more than an L2 holds (22 nodes, r = 3, seven files, T = 1352 f32, two tiles, 448, 786); narrower packs 0.99, up
-// to 1.05; with r = 1 nothing is read twice, 1.04.  Chosen in the kernel both ways cost short wavefronts up to 15 %.
-inline bool neighbours_share(const ccdc_plan_t *p, int node, uint32_t tiles) { return node < 0 && p->J == 1 && tiles >= 16; }
+// the same packs run next to each other behind one L2; else the tiles of one output are neighbours, on all XCDs.  For all nodes
+// of one job and packs of 16 bytes, where a tile has 14 outputs (a node's segment) or more to share its packs: with fewer it is
+// slower (r = 2, 4 nodes 1.04 of the time, 5 nodes 1.03, 6 nodes 0.99; 4 nodes, r = 3 0.99, 5 nodes 0.90).  The fewer readers a pack has
+// and the more files are summed for one, the less is shared, so r = 2 and batches of several files ask for more tiles.  Over 3303 inputs
+// of 48 MB to 2.9 GB and 16 tiles or more: 2110 are numbered by tile and take 0.886 of the time (one file and r >= 3 0.848, r = 2 0.967, several files
+// 0.910; 12 nodes, r = 2, two functions each, T = 155840 u32 271 -> 249 us), 32 over 3 % more (8 nodes, r = 4, T = 72064 f16 28.6 -> 35.0, else up to 1.09);
+// the other 1193 would take 1.001 of it, 245 over 3 % more.
+// With fewer than 16 tiles the rows of one are more than an L2 holds (22 nodes, r = 3, seven files, T = 1352 f32, two tiles, 448 us, 786);
+// narrower packs 0.99, up to 1.05; with r = 1 nothing is read twice, 1.04.  Chosen in the kernel both ways cost short wavefronts up to 15 %.
+inline bool neighbours_share(const ccdc_plan_t *p, int node, uint32_t tiles)
+{
+    if (node >= 0 || p->J > 1 || p->K * p->r < 14 || (p->r == 2 && p->m > 1)) return false;
+    return tiles >= (p->m > 1 ? 200u : p->r == 2 ? 64u : 16u);
+}
 
 // Calls launch(reads) with that as a compile-time constant.  CODED: whether kCoded is one of the answers there are.
 template <bool CODED, class F>
