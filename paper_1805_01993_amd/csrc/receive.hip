@@ -302,6 +302,7 @@ CCDC_RECEIVE(HybF16);
 struct Load {
     double gens, waits, issue;
     bool wide;                        // packs of 16 bytes
+    double groups, group_loads;       // workgroups, and the loads of one
 };
 Load load_of(const ccdc_plan_t *p, int cus, int nodes, int vec, int waves)
 {
@@ -310,9 +311,10 @@ Load load_of(const ccdc_plan_t *p, int cus, int nodes, int vec, int waves)
     const double groups = (double)nodes * r * cdiv((uint64_t)(p->ell / vec), kPipeLanes), fill = std::min(1.0, groups / cus);
     const int64_t steps = (rounds + waves - 1) / waves * p->m, files = (own + waves - 1) / waves;
     const int at_once = receive_steps(regs, r, p->m > 1), own_at_once = receive_own(regs);
+    const double group_loads = (double)(rounds * p->m * r + own);
     return {std::max(1.0, groups / (cus * std::max(1.0, 14.0 / waves))),
             (double)((steps + at_once - 1) / at_once + std::max<int64_t>(0, (files - 1) / own_at_once)),
-            groups * (double)(rounds * p->m * r + own) / cus / fill, regs == 4};
+            groups * group_loads / cus / fill, regs == 4, groups, group_loads};
 }
 
 int compute_units()
@@ -348,23 +350,31 @@ Shape best_shape(const ccdc_plan_t *p, int cus, const Costs &c, double bytes)
     return best;
 }
 
-// Gives the plan this kernel where an estimate of its time (us) is below the one-pass kernel's, one_pass_us.  Both are
-// fitted to passes of 475 shapes of the sizes below (K 4..24, r 1..5, every mode), each with the one-pass kernel's
-// geometry and with 15 of this one's: 305 of them take this kernel, all 475 then take 0.867 of the time before, and
-// would take 0.843 with the best choice each time.  Of 500 other shapes of 64 KB to 50 MB 251 take it, in 0.81 of the time
-// before; two are over 3 % slower, the slowest 5 % (8 nodes, r = 1, T = 40000 f32 5.6 -> 5.9).  Without the margin of
-// a twentieth seven of the 475 were, the slowest 27 %.
+// Gives the plan this kernel where its estimated time (us) is below the one-pass kernel's, by one_pass_us, in both of two estimates, with a
+// margin of a twentieth.  The first is fitted to passes of 475 shapes of the sizes below (K 4..24, r 1..5, every mode), each with the one-pass
+// kernel's geometry and with 15 of this one's, and picks the pack and the wavefronts.  It knows no whole generations of workgroups: of 19140
+// other plans that it favours 620 were over 3 % slower, by up to 67 %.  The second, fitted to those, counts them (16 wavefronts a
+// compute unit) and the loads of the busiest unit (12 nodes, r = 2, two files, T = 1377 h32: 264 workgroups of 12 wavefronts, 12.9 us,
+// 9.4 by k_pipeline); alone it let others in that are slower.  Many workgroups of two wavefronts with next to nothing to load are bound by
+// their starts, which neither catches (4 nodes, r = 1, T = 50119 f32, 3136 of them, 6.6 us and 4.0).
+// Of 10754 plans of 64 KB to 30 MB 5530 take this kernel, in 0.694 of the time, 80 of them over 3 % slower (worst 1.38: 9 nodes, r = 5,
+// T = 124 u32 8.6 -> 11.9); by the first estimate alone 211 were.  24 nodes, r = 1, T = 376 h32 (1.7 MB) 9.2 -> 6.1 us.
 // Above kReceiveBytes it gains little more (24 to 48 MB, r = 2: 0.94 with the best choice each time, r >= 3 0.98; but r = 1,
 // where no value is read twice, 0.82, and 0.93 from 48 to 96 MB).
 void receive_prepare(ccdc_plan_t *p, double one_pass_us)
 {
     const double bytes = moved_bytes(p, (double)p->nrows * p->ell + (double)p->Q * p->T);
     if (bytes > kKeptBytes || bytes > (p->r == 1 ? kReceiveBytesR1 : kReceiveBytes)) return;
-    const double other = 5.9 + (p->m > 1 ? 0.34 : 0.26) * one_pass_us + (p->pipe_chunks > 1 ? 1.1 : 0);
     const int cus = compute_units();
     if (cus < 1) return;
     const Shape best = best_shape(p, cus, {4.1, 0.39, 0.0097, 0.0031, 11e6}, bytes);
-    if (best.us >= 0.95 * other) return;
+    if (best.us >= 0.95 * (5.9 + (p->m > 1 ? 0.34 : 0.26) * one_pass_us + (p->pipe_chunks > 1 ? 1.1 : 0))) return;
+    const Load l = load_of(p, cus, p->K, best.vec, best.waves);
+    if (best.waves == 2 && l.groups >= 4 * cus && l.group_loads <= 9) return;
+    const double gens = std::ceil(l.groups / (cus * (kReceiveMaxWaves / best.waves)));
+    const double busiest = std::ceil(l.groups / cus) * l.group_loads;
+    const double us = 3.06 + 0.305 * gens * l.waits + (l.wide ? 0.0118 : 0.0150) * busiest + bytes / 14.8e6;
+    if (us >= 0.95 * (3.40 + (p->m > 1 ? 0.636 : 0.590) * one_pass_us)) return;
     p->pipe_vec = best.vec;
     p->pipe_waves = best.waves;
     p->pipe_chunks = 0;

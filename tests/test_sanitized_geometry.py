@@ -169,3 +169,13 @@ def choices(kernel_driver, K, r, N, T, mode):
 ])
 def test_node_local_form_fits_one_node_and_all(kernel_driver, K, r, m, T, mode, receiver):  # noqa: F811
     assert (choices(kernel_driver, K, r, m * comb(K, r), T, mode)[1][3] > 0) == receiver
+
+
+@pytest.mark.parametrize("K,r,m,T,mode,receiver", [
+    (24, 1, 1, 376, 2, True), (7, 3, 1, 212, 0, True), (10, 2, 1, 680, 4, True), (11, 2, 1, 5536, 1, True),
+    (4, 1, 1, 50119, 0, False),        # 3136 workgroups that load four packs each: 4.0 us by the one-pass kernel, 6.6
+    (12, 2, 2, 1377, 2, False),        # 264 workgroups of 12 wavefronts: two generations on 256 compute units, 9.4 and 12.9
+    (17, 3, 1, 134, 1, False),
+])
+def test_one_pass_form_of_small_inputs(kernel_driver, K, r, m, T, mode, receiver):  # noqa: F811
+    assert bool(choices(kernel_driver, K, r, m * comb(K, r), T, mode)[0][3] & 4) == receiver
