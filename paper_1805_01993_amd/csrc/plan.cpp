@@ -297,19 +297,23 @@ namespace {
 // workgroups and added by a second kernel.  Only for plans whose outputs are too few to fill the chip with whole lists
 // (split > 1).  Measured over 282 such plans of 64 KB to 400 MB (every scheme and mode): the one launch takes 0.657 of the
 // split form's time (up to 4 MB 0.68, 4 to 48 MB 0.59, above 0.84), with the best pack and count of wavefronts each time
-// 0.645; one is over 3 % slower (5 %).  A wavefront for two rows is the best share (four 0.659), in all at most 3072.
+// 0.645.  A wavefront for two rows is the best share (four 0.659), in all at most 3072, with the workgroups counted in packs of up to four
+// elements: by the packs of eight that 16-bit rows are summed in, 462 of 2998 such plans get more wavefronts and take 1.035 of the time.
 // Lists of over 640 rows are left to the split: 16 nodes, r = 4, T = 728 f32 (1820 rows) 24 us, in one launch 28 to 45; 14
-// nodes, r = 5, T = 1227 f16 (2002) 26, 39; and so are inputs past the last-level cache.
-int plan_groups(int64_t nout, int64_t rows, int64_t W, int vec, int64_t split, double bytes)
+// nodes, r = 5, T = 1227 f16 (2002) 26, 39; so are inputs past the last-level cache, and one-element packs of 16 bits with over 64
+// rows a wavefront, 1.04 of the time over 31 plans (14 nodes, r = 3, T = 6735 f16 24.0, 29.8; of 2998 16-bit plans 24 were over 3 % slower, 18 of them these).
+int plan_groups(int64_t nout, int64_t rows, int64_t W, int vec, int elem, int64_t split, double bytes)
 {
     if (split <= 1 || rows > 640 * nout || bytes > 256e6) return 0;
+    const bool narrow = elem == 2 && vec == 1;
     int64_t tiles = 0;
     for (; vec > 0; vec /= 2) {
         tiles = (W / vec + kGroupLanes - 1) / kGroupLanes;
         if (nout * tiles >= kGroupsWanted) break;
     }
     const int64_t wanted = std::max<int64_t>(2, std::min<int64_t>(kGroupMaxWaves, rows / (2 * nout)));
-    return (int)std::max<int64_t>(2, std::min<int64_t>(wanted, 3072 / (nout * tiles)));
+    const int64_t waves = std::max<int64_t>(2, std::min<int64_t>(wanted, 3072 / (nout * tiles)));
+    return narrow && rows > 64 * nout * waves ? 0 : (int)waves;
 }
 
 // ccdc_plan_bind for the compression-only scheme: the packet is sent whole (no
@@ -354,7 +358,7 @@ int bind_compression(ccdc_plan_t *p, int64_t T, int mode)
         p->red_out.swap(outs);
         p->nout = nout;
         p->red_split = (int)split;
-        p->red_waves = plan_groups(nout, (int64_t)p->red_row.size(), W, vec, split, ((double)p->N * p->Q * (double)T) * 4);
+        p->red_waves = plan_groups(nout, (int64_t)p->red_row.size(), W, vec, 4, split, ((double)p->N * p->Q * (double)T) * 4);
         p->workspace_bytes = p->red_workspace_bytes = split > 1 ? (size_t)split * (size_t)p->Q * (size_t)T * 4 : 0;
         p->pipe_ok = false;
         p->loc_row.clear();
@@ -499,7 +503,8 @@ int bind_plan(ccdc_plan_t *p, int64_t T, int mode)
         p->red_out.swap(outs);
         p->nout = nout;
         p->red_split = (int)split;
-        p->red_waves = plan_groups(nout, (int64_t)p->red_row.size(), W, vec, split, v_elems * (mode >= CCDC_BF16_SUM_XOR ? 2 : 4));
+        const int elem = mode >= CCDC_BF16_SUM_XOR ? 2 : 4;
+        p->red_waves = plan_groups(nout, (int64_t)p->red_row.size(), W, vec, elem, split, v_elems * elem);
         p->red_workspace_bytes = split > 1 ? (size_t)split * (size_t)p->J * p->Q * (size_t)T * 4 : 0;
         p->workspace_bytes = p->red_workspace_bytes;         // until upload has fixed the chunks: the most it can be
         if (pipe_ok && pipe_cap > 1)

@@ -179,3 +179,10 @@ def test_node_local_form_fits_one_node_and_all(kernel_driver, K, r, m, T, mode, 
 ])
 def test_one_pass_form_of_small_inputs(kernel_driver, K, r, m, T, mode, receiver):  # noqa: F811
     assert bool(choices(kernel_driver, K, r, m * comb(K, r), T, mode)[0][3] & 4) == receiver
+
+
+@pytest.mark.parametrize("K,r,T,mode,waves", [(12, 3, 6000, 4, 10), (14, 3, 6735, 1, 2), (14, 3, 6735, 4, 0), (14, 3, 6736, 4, 8)])
+def test_reduce_of_narrow_packs(kernel_driver, K, r, T, mode, waves):  # noqa: F811
+    """One-element packs of 16 bits with over 64 rows a wavefront keep the split form."""
+    m = 2 if K == 12 else 1
+    assert choices(kernel_driver, K, r, m * comb(K, r), T, mode)[1][1] == waves
