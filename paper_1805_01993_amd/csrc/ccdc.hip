@@ -459,8 +459,9 @@ int run_combine(const ccdc_plan_t *p, const void *V, void *Vbar, hipStream_t st)
             return launched();
         }
     }
+    const int files = p->compression ? p->batch_first[1] : p->m;        // of a batch, uncoded plans: of the largest
     by_reads<false>(kept, [&](auto k) {
-        by_files<Ops<A, VEC>>(p->m > 2 || p->d_row_files, [&](auto together) {
+        by_files<Ops<A, VEC>>(files > 2, [&](auto together) {
             k_combine<A, VEC, decltype(k)::value, decltype(together)::value><<<cdiv(items, kBlock), kBlock, 0, st>>>(
                 (const E *)V, (E *)Vbar, p->d_src_off, p->d_row_files, Wv, p->m, (int64_t)p->Q * p->T, (uint32_t)items);
         });
