@@ -634,7 +634,9 @@ int ccdc_plan_upload(ccdc_plan_t *plan)
     }
     plan->device = dev;
     ccdc::pipeline_prepare(plan);                 // launch geometry of the one-pass kernel on this device
-    plan->workspace_bytes = plan->red_workspace_bytes;
+    // partial sums of a split row list: where ccdc_reduce or ccdc_node_decode_reduce runs that form
+    const bool split = plan->red_waves == 0 || (!plan->compression && plan->node_waves == 0);
+    plan->workspace_bytes = split ? plan->red_workspace_bytes : 0;
     if (plan->pipe_chunks > 1)
         plan->workspace_bytes = std::max(plan->workspace_bytes, (size_t)plan->pipe_chunks * (size_t)plan->K * (size_t)plan->W * 4);
     int rc = to_device(plan->src_off, &plan->d_src_off);

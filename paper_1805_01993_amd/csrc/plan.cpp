@@ -359,7 +359,7 @@ int bind_compression(ccdc_plan_t *p, int64_t T, int mode)
         p->nout = nout;
         p->red_split = (int)split;
         p->red_waves = plan_groups(nout, (int64_t)p->red_row.size(), W, vec, 4, split, ((double)p->N * p->Q * (double)T) * 4);
-        p->workspace_bytes = p->red_workspace_bytes = split > 1 ? (size_t)split * (size_t)p->Q * (size_t)T * 4 : 0;
+        p->workspace_bytes = p->red_workspace_bytes = split > 1 && p->red_waves == 0 ? (size_t)split * (size_t)p->Q * (size_t)T * 4 : 0;
         p->pipe_ok = false;
         p->loc_row.clear();
         p->pipe_row.clear();

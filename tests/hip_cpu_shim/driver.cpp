@@ -118,7 +118,7 @@ static bool force_reductions(ccdc_plan_t *p)
                            waves > ccdc::kReceiveMaxWaves))
             return false;
     }
-    return resize_workspace(p);
+    return (!std::getenv("SHIM_REDUCE") && !std::getenv("SHIM_NODE")) || resize_workspace(p);
 }
 
 // Gives an uploaded plan another launch geometry for the one-pass kernel, with an exact-size workspace.
@@ -142,7 +142,9 @@ static bool force_geometry(ccdc_plan_t *p, const char *text)
 // The workspace holds the partial sums that calls on the uploaded plan write, and no more.
 static int workspace()
 {
-    const int64_t shapes[][5] = {{7, 3, 7, 35, 100003}, {8, 2, 8, 28, 65536}, {10, 3, 10, 120, 4096}, {4, 1, 4, 4, 1 << 22}};
+    // the last three: lists are split by no call, without and with chunks of rounds, and by both
+    const int64_t shapes[][5] = {{7, 3, 7, 35, 100003}, {8, 2, 8, 28, 65536}, {10, 3, 10, 120, 4096}, {4, 1, 4, 4, 1 << 22},
+                                 {15, 1, 15, 15, 680}, {12, 2, 12, 66, 5536}, {9, 5, 9, 1512, 64}};
     int bad = 0;
     shim::compute_units = 256;
     shim::blocks_per_cu = 16;
@@ -153,10 +155,13 @@ static int workspace()
         const int64_t most = query(p, CCDC_Q_WORKSPACE_BYTES);
         for (int again = 0; again < 2; again++) {
             CHECK(ccdc_plan_upload(p));
-            const int64_t phi = query(p, CCDC_Q_PHI_ELEMS) * 4, red = p->red_split > 1 ? p->red_split * phi : 0;
+            int32_t sums[4];
+            CHECK(ccdc_plan_query(p, CCDC_Q_REDUCE_LAUNCH, sums, sizeof sums));
+            const int64_t phi = query(p, CCDC_Q_PHI_ELEMS) * 4;
+            const int64_t red = sums[0] > 1 && (sums[1] == 0 || sums[3] == 0) ? sums[0] * phi : 0;
             const int64_t pipe = p->pipe_chunks > 1 ? p->pipe_chunks * phi : 0, got = query(p, CCDC_Q_WORKSPACE_BYTES);
-            std::printf("K=%d r=%d T=%lld: %d chunks, split %d, workspace %lld\n", p->K, p->r, (long long)p->T, p->pipe_chunks,
-                        p->red_split, (long long)got);
+            std::printf("K=%d r=%d T=%lld: %d chunks, split %d, %d and %d in one launch, workspace %lld\n", p->K, p->r, (long long)p->T,
+                        p->pipe_chunks, sums[0], sums[1], sums[3], (long long)got);
             bad += got != std::max(red, pipe) || got > most;
         }
         ccdc_plan_destroy(p);
