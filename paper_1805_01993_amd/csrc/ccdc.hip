@@ -183,8 +183,8 @@ __global__ __launch_bounds__(kBlock) void k_decode_sender(const typename A::elem
 // pack of its own packet by removing the other r-1 from the coded pack.
 // R1 = r+1 at compile time keeps the r combined packs in registers; R1 = 0 is
 // the any-r fallback that re-reads them (cache hits) instead.
-// MULTI: several files a batch (a kernel of their own: their sums in the making take registers that the other would pay for
-// with fewer wavefronts).
+// MULTI: several files a batch, where their packets are asked for together (a kernel of their own: their sums in the making take
+// registers that the other would pay for with fewer wavefronts); elsewhere the one kernel looks at m.
 template <class A, int VEC, int R1, bool KEPT, bool MULTI>
 __global__ __launch_bounds__(kBlock) void k_shuffle_fused(const typename A::elem *__restrict__ V,
                                                           typename A::elem *__restrict__ X,
@@ -519,8 +519,10 @@ void launch_shuffle(const ccdc_plan_t *p, const void *V, void *X, void *D, hipSt
                 (const E *)V, (E *)X, (E *)D, p->d_src_off, p->r + 1, Lv, Wv, p->m, (int64_t)p->Q * p->T, (uint32_t)items);
         });
     };
-    if (R1 > 0 && p->m == 1) launch(std::false_type());
-    else launch(std::true_type());
+    if constexpr (R1 > 0 && packets_together<Ops<A, VEC>, R1 - 1>()) {
+        if (p->m == 1) return launch(std::false_type());
+    }
+    launch(std::true_type());
 }
 
 template <class A, int VEC>
