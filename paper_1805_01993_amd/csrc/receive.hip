@@ -45,7 +45,6 @@ __global__ __launch_bounds__(ccdc::kPipeLanes *ccdc::kReceiveMaxWaves) void k_re
     using O = Ops<A, VEC>;
     using P = typename O::P;
     using Q = typename O::Q;
-    using Acc = typename A::acc;
     constexpr int r = R1 - 1;
     constexpr uint32_t LANES = ccdc::kPipeLanes;
     constexpr int regs = (VEC * (int)sizeof(E) + 3) / 4;     // registers a pack takes
@@ -203,16 +202,10 @@ __global__ __launch_bounds__(ccdc::kPipeLanes *ccdc::kReceiveMaxWaves) void k_re
                 if (i + t < i1) acc = O::accum(acc, w[t]);
         }
     }
-    reinterpret_cast<Q *>(smem)[threadIdx.x] = acc;
-    __syncthreads();
-    for (uint32_t e = threadIdx.x; e < LANES * VEC; e += blockDim.x) {
+    add_wavefronts<A, VEC>(smem, acc, waves, [&](uint32_t e, typename A::acc v) {
         const uint32_t at = tile * LANES * VEC + e, pos = rho * p.ell + at;
-        if (at >= p.ell || pos >= p.W) continue;
-        const Acc *parts = reinterpret_cast<const Acc *>(smem) + e;
-        Acc v = parts[0];
-        for (uint32_t g = 1; g < waves; g++) v = A::add(v, parts[g * LANES * VEC]);
-        Phi[(size_t)node * p.W + pos] = A::narrow(v);
-    }
+        if (at < p.ell && pos < p.W) Phi[(size_t)node * p.W + pos] = A::narrow(v);
+    });
 }
 
 // For all nodes (node < 0) or one.  CODED: X is read.
