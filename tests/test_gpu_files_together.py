@@ -1,9 +1,8 @@
 """Batches of several files whose packs are asked for together (packs of less than 16 bytes): every count of files around the
 steps of four, two and one, segments that fill wavefronts and that do not, one output pack more or less.  Whole numbers of a
 small range, exact in every order: decoded packets against combined ones, coded packets of the three calls that make them
-against each other, outputs against the sum of V over the files.  Needs a GPU."""
-from math import comb
-
+against each other, outputs against the sum of V over the files.  Plans of several jobs, which never decode by receiver.  Needs a
+GPU."""
 import pytest
 import torch
 
@@ -28,13 +27,17 @@ def values(sh, mode):
     return V.to(dt), V.sum(1).to(dt)
 
 
-@pytest.mark.parametrize("mode", ["u32", "f32", "h32", "bf16", "f16"])
-@pytest.mark.parametrize("T", [1, 2, 71, 259, 646, 1030, 2049])
-@pytest.mark.parametrize("r,m", [(1, 2), (1, 7), (2, 2), (2, 3), (2, 6), (3, 2), (3, 5), (4, 2), (4, 3), (4, 9), (5, 2), (5, 4),
-                                 (6, 3)])
-def test_coded_plans(r, m, T, mode):
-    K = r + 2
-    plan = L.ccdc_plan(K, r, K, m * comb(K, r)).bind(T, mode).upload()
+MODES = ["u32", "f32", "h32", "bf16", "f16"]
+LENGTHS = [1, 2, 71, 259, 646, 1030, 2049]
+FILES = [(1, 2), (1, 7), (2, 2), (2, 3), (2, 6), (3, 2), (3, 5), (4, 2), (4, 3), (4, 9), (5, 2), (5, 4), (6, 3)]      # r, files a batch
+
+
+@pytest.mark.parametrize("T", LENGTHS)
+@pytest.mark.parametrize("r,m", FILES)
+def test_coded_plans(r, m, T):
+    K, mode = r + 2, MODES[(FILES.index((r, m)) + LENGTHS.index(T)) % 5]
+    plan = L.ccdc_plan_jobs(K, r, K, m * (r + 1)).bind(T, mode).upload()
+    assert plan.reduce_launch()[2:] == (0, 0)
     sh = plan.shapes()
     V, want = values(sh, mode)
     new = lambda key: torch.full(sh[key], 55, dtype=V.dtype, device="cuda")  # noqa: E731

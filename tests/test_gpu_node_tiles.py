@@ -1,8 +1,7 @@
-"""The node-local calls at the edges of their tiles: segments of a few packs, of one wavefront, one pack more or less,
-and where the rule between the two kernels changes.  Packets against ccdc_encode's and outputs against
+"""The node-local calls' kernels by wavefront and by packed lanes at the edges of their tiles: segments of a few packs, of one
+wavefront, one pack more or less, and where the rule between the two changes.  Plans of the J-job
+schedule, which never decode by receiver.  Packets against ccdc_encode's and outputs against
 ccdc_reduce's, whose row order they share (XOR: bit for bit).  Needs a GPU."""
-from math import comb
-
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -18,13 +17,14 @@ def torch():
 
 
 @pytest.mark.parametrize("mode", ["u32", "f32", "bf16"])
-@pytest.mark.parametrize("K,r,m", [(5, 1, 1), (6, 2, 3), (6, 3, 1), (7, 4, 2), (7, 5, 1), (8, 6, 1)])
+@pytest.mark.parametrize("K,r,m", [(2, 1, 1), (6, 2, 3), (4, 3, 1), (7, 4, 2), (6, 5, 1), (7, 6, 1)])
 @pytest.mark.parametrize("packs", [1, 47, 48, 64, 65, 96, 97, 130])
 def test_node_calls_at_tile_edges(torch, K, r, m, packs, mode):
     import paper_1805_01993_amd as L
     lanes = 8 if mode == "bf16" else 4
-    N, T = m * comb(K, r), r * packs * lanes
-    plan = L.ccdc_plan(K, r, K, N).bind(T, mode).upload()
+    T = r * packs * lanes
+    plan = L.ccdc_plan_jobs(K, r, K, m * (r + 1)).bind(T, mode).upload()
+    assert plan.reduce_launch()[2:] == (0, 0)
     sh = plan.shapes()
     dt = {"u32": torch.int32, "f32": torch.float32, "bf16": torch.bfloat16}[mode]
     g = torch.Generator(device="cuda").manual_seed(3)

@@ -326,7 +326,12 @@ def test_one_plan_on_two_streams_is_put_in_order(torch, L):
         for i, (X, Phi) in enumerate(outs):
             assert torch.equal(X, alone[i % 2][0]), (rep, i)
             assert torch.equal(Phi, alone[i % 2][1]), (rep, i)
-    # the separate reduction and the node-local reduction use the same workspace
+    # the separate reduction and the node-local reduction use the same workspace where both split their lists
+    T = 100000
+    plan.bind(T, "f32").upload()
+    split, whole, _, by_receiver = plan.reduce_launch()
+    assert split > 1 and whole == 0 and by_receiver == 0
+    sh, Va = plan.shapes(), generate_torch(1, N, Q, T, 11, "f32", device="cuda")
     D = dev_empty(torch, sh["D"], "f32", float("nan"))
     X = dev_empty(torch, sh["X"], "f32", float("nan"))
     plan.shuffle_fused(Va, X, D)

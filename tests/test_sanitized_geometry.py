@@ -1,6 +1,7 @@
 """The one-pass kernel's launch geometries and the node-local kernels' two forms on the CPU build of the kernels, under
 ASan and UBSan (see test_sanitized_host_code.py): every path's outputs against the plain sum and the paths' packets
-against each other.  CASES run every path as the library launches it.  The forms of the one-pass kernel (pack width,
+against each other.  CASES run every path as the library launches it, and with row lists split and decoded by node.hip's kernels, which
+small inputs do not take.  The forms of the one-pass kernel (pack width,
 end of a packet, several files a batch, wavefronts, chunks, how the rounds are shared out, more and fewer steps than
 the kernel keeps in flight) are not left to what the library would choose: FORMS forces each into the plan."""
 import os
@@ -28,12 +29,18 @@ CASES = [
 ]
 
 
+SPLIT = {"SHIM_NODE": "0,0", "SHIM_REDUCE": "0"}
+
+
+@pytest.mark.parametrize("forms", [{}, SPLIT], ids=["chosen", "split"])
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(map(str, c)))
-def test_geometries_under_sanitizers(kernel_driver, case):  # noqa: F811
+def test_geometries_under_sanitizers(kernel_driver, case, forms):  # noqa: F811
     res = subprocess.run([kernel_driver] + [str(v) for v in case], capture_output=True, text=True,
-                         env=dict(os.environ, **ENV), timeout=600)
+                         env=dict(os.environ, **ENV, **forms), timeout=600)
     assert res.returncode == 0, res.stdout + res.stderr
     assert " 0 mismatches" in res.stdout, res.stdout
+    if forms:
+        assert ",0,0,0\n" in res.stdout[res.stdout.index("reduce "):], res.stdout
 
 
 # Value lengths, per r: whole segments of 264 elements (66 four-element packs: a full column tile and a part one), a
@@ -147,6 +154,28 @@ def test_forms_by_receiver(kernel_driver, r, m):  # noqa: F811
 
     with ThreadPoolExecutor(4) as pool:
         list(pool.map(run, range(5), [264 * r, 264 * r - 4 if r > 1 else 260, 264 * r - 2, 68 * r - 3, 3]))
+
+
+# Node-local decoding by receiver (pack, wavefronts) and lists summed whole (wavefronts)
+@pytest.mark.parametrize("m", [1, 3])
+@pytest.mark.parametrize("r", [1, 2, 3, 4, 5])
+def test_forms_of_the_reductions(kernel_driver, r, m):  # noqa: F811
+    """K = r+2; for all nodes and for each alone; the ends of a packet as above, one and several stages of rounds, own files and rows,
+    wavefronts without any."""
+    K = r + 2
+    ends = [(260 if r == 1 else 264 * r - 4, "4,3", "3"), (264 * r - 2, "2,2", "16"), (68 * r - 3, "1,16", "2"), (3, "1,2", "5")]
+
+    def run(k, case):
+        T, node, waves = case
+        args = (K, r, K, m * comb(K, r), T, (r + k + m) % 5, 0, 8, 8)
+        res = subprocess.run([kernel_driver] + [str(v) for v in args], capture_output=True, text=True,
+                             env=dict(os.environ, SHIM_NODE=node, SHIM_REDUCE=waves, **ENV), timeout=600)
+        assert res.returncode == 0, res.stdout + res.stderr
+        assert " 0 mismatches" in res.stdout, res.stdout
+        assert f",{waves},{node}\n" in res.stdout, res.stdout
+
+    with ThreadPoolExecutor(4) as pool:
+        list(pool.map(run, range(4), ends))
 
 
 def choices(kernel_driver, K, r, N, T, mode):
