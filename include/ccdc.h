@@ -247,14 +247,14 @@ int ccdc_shuffle_fused(const ccdc_plan_t *plan, const void *V, void *X, void *D,
 
 /* The whole path of Sec. IV-B in one pass for single-job plans (ccdc_plan):
  * pre-combining, the coded-packet equation, the decoding paragraph and the final
- * reduction of its last paragraphs; every element of V is read once, X and Phi are written,
- * neither Vbar nor D is materialised.  Each coded pack is decoded for each
+ * reduction of its last paragraphs; every element of V is read once (on small inputs by up
+ * to r workgroups), X and Phi are written, neither Vbar nor D is materialised.  Each coded pack is decoded for each
  * receiver as in ccdc_decode (coded pack minus the receiver's side information)
  * and added to that receiver's output, together with the files it stores itself.
  * X equals ccdc_encode's bit for bit; Phi is bit-exact in XOR mode and, in fp32,
  * a fixed summation order different from ccdc_reduce's.  Any value length and any
- * element-aligned pointers take the same kernel, which the plan's sizes alone choose.  Uses the plan's workspace (at
- * most 64 MiB for this call).  CCDC_ESIZE for plans of ccdc_plan_jobs, for r > 5 and for
+ * element-aligned pointers take the same kernel, which ccdc_plan_upload chooses by the plan's sizes, the payload mode
+ * and the device.  Uses the plan's workspace (at most 64 MiB for this call).  CCDC_ESIZE for plans of ccdc_plan_jobs, for r > 5 and for
  * K*r > 256 (the per-lane outputs of all nodes must fit in 64 KB of LDS):
  * use ccdc_shuffle_fused + ccdc_reduce there. */
 int ccdc_pipeline_fused(const ccdc_plan_t *plan, const void *V, void *X, void *Phi, void *stream);

@@ -310,8 +310,8 @@ __device__ __forceinline__ P load_pack_any(const void *p)
 // bytes, of which a wavefront has few bytes in flight, several files are asked for together.  Packs of 16 bytes stay with one
 // at a time: past the caches that gives nothing (56 jobs on 8 nodes, r = 2, three files, T = 150000 u32 483 -> 491 us), and sums of
 // eight elements take the registers of other wavefronts (12 nodes, r = 3, two files, T = 6000 f16, node-local decoding 33 -> 38).
-// Two files alone stay too where they are a lane's only packs in flight: combine (6 nodes, r = 4, T = 634231 f32 129 -> 136)
-// and the kernels of node.hip that pack lanes (17 nodes, r = 4, T = 99 h32 46 -> 56).  141 inputs of 20 MB to 2.5 GB: combine
+// Two files alone stay too where they are a lane's only packs in flight: combine (6 nodes, r = 4, T = 634231 f32 129 -> 136,
+// uncoded, 12 nodes, r = 1, T = 1278647 f32 548 -> 580) and the kernels of node.hip that pack lanes (17 nodes, r = 4, T = 99 h32 46 -> 56).  141 inputs of 20 MB to 2.5 GB: combine
 // down to 0.60 of the time, the fused shuffle 0.42, node-local encoding 0.43, decoding 0.38 (9 nodes, r = 3, T = 36845 bf16, nine
 // files, 0.61, 0.42, 0.45, 0.56).
 template <class O>

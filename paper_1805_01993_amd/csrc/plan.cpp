@@ -298,7 +298,8 @@ namespace {
 // (split > 1).  Measured over 282 such plans of 64 KB to 400 MB (every scheme and mode): the one launch takes 0.657 of the
 // split form's time (up to 4 MB 0.68, 4 to 48 MB 0.59, above 0.84), with the best pack and count of wavefronts each time
 // 0.645.  A wavefront for two rows is the best share (four 0.659), in all at most 3072, with the workgroups counted in packs of up to four
-// elements: by the packs of eight that 16-bit rows are summed in, 462 of 2998 such plans get more wavefronts and take 1.035 of the time.
+// elements: by the packs of eight that 16-bit rows are summed in, 462 of 2998 such plans get more wavefronts and take 1.035 of the time.  (A call with
+// pointers that are not aligned for wide packs has more workgroups of the same count.)
 // Lists of over 640 rows are left to the split: 16 nodes, r = 4, T = 728 f32 (1820 rows) 24 us, in one launch 28 to 45; 14
 // nodes, r = 5, T = 1227 f16 (2002) 26, 39; so are inputs past the last-level cache, and one-element packs of 16 bits with over 64
 // rows a wavefront, 1.04 of the time over 31 plans (14 nodes, r = 3, T = 6735 f16 24.0, 29.8; of 2998 16-bit plans 24 were over 3 % slower, 18 of them these).

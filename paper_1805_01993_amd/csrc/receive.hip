@@ -351,9 +351,10 @@ Shape best_shape(const ccdc_plan_t *p, int cus, const Costs &c, double bytes)
 // 9.4 by k_pipeline); alone it let others in that are slower.  Many workgroups of two wavefronts with next to nothing to load are bound by
 // their starts, which neither catches (4 nodes, r = 1, T = 50119 f32, 3136 of them, 6.6 us and 4.0).
 // Of 10754 plans of 64 KB to 30 MB 5530 take this kernel, in 0.694 of the time, 80 of them over 3 % slower (worst 1.38: 9 nodes, r = 5,
-// T = 124 u32 8.6 -> 11.9); by the first estimate alone 211 were.  24 nodes, r = 1, T = 376 h32 (1.7 MB) 9.2 -> 6.1 us.
-// Above kReceiveBytes it gains little more (24 to 48 MB, r = 2: 0.94 with the best choice each time, r >= 3 0.98; but r = 1,
-// where no value is read twice, 0.82, and 0.93 from 48 to 96 MB).
+// T = 124 u32 8.6 -> 11.9); by the first estimate alone 211 were.
+// Above kReceiveBytes it gains little more on average (24 to 48 MB, r = 2: 0.94 with the best choice each time, r >= 3 0.98; but r = 1,
+// where no value is read twice, 0.82, and 0.93 from 48 to 96 MB), though single plans just above that line would: 10 nodes, r = 3,
+// T = 4096 u32 (24.4 MB) 11.4 us, by receiver 8.9.
 void receive_prepare(ccdc_plan_t *p, double one_pass_us)
 {
     const double bytes = moved_bytes(p, (double)p->nrows * p->ell + (double)p->Q * p->T);
