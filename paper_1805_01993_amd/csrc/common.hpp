@@ -505,7 +505,6 @@ __device__ __forceinline__ void add_wavefronts(unsigned char *smem, const typena
 
 // ------------------------------------------------------------ host helpers
 inline bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
-inline uint32_t cdiv(uint64_t a, uint64_t b) { return (uint32_t)((a + b - 1) / b); }
 
 inline int ready(const ccdc_plan_t *p)
 {
@@ -515,14 +514,6 @@ inline int ready(const ccdc_plan_t *p)
     if (hipGetDevice(&dev) != hipSuccess) return CCDC_EHIP;
     if (dev != p->device) return CCDC_ESTATE;
     return CCDC_OK;
-}
-
-constexpr int kWave = 64;
-// Segments fill the wavefronts of a tile row to at least 3/4.
-inline bool fills_wavefronts(uint32_t Lv)
-{
-    const uint64_t lanes = (uint64_t)cdiv(Lv, kWave) * kWave;
-    return (uint64_t)Lv * 4 >= lanes * 3;
 }
 
 inline int elem_bytes(int mode) { return (mode == CCDC_BF16_SUM_XOR || mode == CCDC_F16_SUM_XOR) ? 2 : 4; }

@@ -73,7 +73,7 @@ __global__ __launch_bounds__(kBlock) void k_node_encode(const typename A::elem *
 template <class A, int VEC, int READS, bool TOGETHER>
 __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
     const typename A::elem *__restrict__ V, const typename A::elem *__restrict__ X, typename A::elem *__restrict__ out,
-    typename A::acc *__restrict__ part, const int64_t *__restrict__ red_ptr, const int64_t *__restrict__ red_row,
+    typename A::acc *__restrict__ part, const int64_t *__restrict__ node_ptr, const int64_t *__restrict__ node_row,
     const int64_t *__restrict__ red_out, const int64_t *__restrict__ src_off, int r1, uint32_t Lv, uint32_t Wv,
     int64_t W, int m, int64_t file_stride, uint32_t tiles, int split, int64_t chunk_stride, uint32_t o_first,
     uint32_t o_step)
@@ -88,11 +88,10 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
     const uint32_t e = tile * kBlock + threadIdx.x;
     if (e >= Wv) return;
     const uint32_t rho = e / Lv, x = e - rho * Lv;
-    const int64_t first = red_ptr[o], n = red_ptr[o + 1] - first;
-    const int64_t lo = first + n * s / split, hi = first + n * (s + 1) / split;
+    const int64_t lo = node_ptr[o * split + s], hi = node_ptr[o * split + s + 1];
     typename O::Q acc = O::azero();
     for (int64_t i = lo; i < hi; i++) {
-        const int64_t row = red_row[i];
+        const int64_t row = node_row[i];
         if (!(row & 1)) {                                    // a file the node stores
             acc = O::accum(acc, load_pack<READS == kAll, P>(reinterpret_cast<const P *>(V + (row >> 1)) + e));
             continue;
@@ -173,11 +172,17 @@ __global__ __launch_bounds__(kBlock) void k_node_encode_wave(const typename A::e
     store_stream(reinterpret_cast<P *>(X) + (size_t)i * Lv + x, coded);
 }
 
-// BY_TILE: how the units are numbered, see neighbours_share().
-template <class A, int VEC, int R1, int FILES, int READS, bool BY_TILE>
+// How the units are numbered.
+enum Numbering {
+    kByOutput,                        // ((output block, chunk), segment, tile), as workgroups are handed out
+    kByTile,                          // (tile, ((chunk, output block), segment)), an XCD on a contiguous range: neighbours_share()
+    kByChunk,                         // (chunk, (output block, segment, tile)), an XCD on a contiguous range: lists_by_round()
+};
+
+template <class A, int VEC, int R1, int FILES, int READS, int NUMBERING>
 __global__ __launch_bounds__(kBlock) void k_node_decode_reduce_wave(
     const typename A::elem *__restrict__ V, const typename A::elem *__restrict__ X, typename A::elem *__restrict__ out,
-    typename A::acc *__restrict__ part, const int64_t *__restrict__ red_ptr, const int64_t *__restrict__ red_row,
+    typename A::acc *__restrict__ part, const int64_t *__restrict__ node_ptr, const int64_t *__restrict__ node_row,
     const int64_t *__restrict__ red_out, const int64_t *__restrict__ src_off, uint32_t Lv, uint32_t Wv,
     double per_row, int m, int64_t file_stride, uint32_t tiles, int split, int64_t chunk_stride, uint32_t o_first,
     uint32_t o_step, uint32_t units)
@@ -186,18 +191,24 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce_wave(
     using P = typename O::P;
     constexpr int r = R1 - 1;
     constexpr int AHEAD = FILES != kOneFile ? 1 : (R1 <= 3 ? 4 : 2);     // received packets asked for together
-    const uint32_t unit = (BY_TILE ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x) * kWaves + wave_uniform(threadIdx.x / kWave);
+    const uint32_t unit = (NUMBERING == kByOutput ? blockIdx.x : xcd_contiguous(blockIdx.x, gridDim.x)) * kWaves + wave_uniform(threadIdx.x / kWave);
     if (unit >= units) return;
     uint32_t tile, oi;
     int rho, s;
-    if constexpr (BY_TILE) {                                 // unit = (tile, ((chunk, output block), segment))
+    if constexpr (NUMBERING == kByChunk) {
+        const uint32_t per_chunk = units / split, in = unit % per_chunk, seg = in / tiles;
+        s = (int)(unit / per_chunk);
+        tile = in - seg * tiles;
+        oi = seg / r;
+        rho = (int)(seg - oi * r);
+    } else if constexpr (NUMBERING == kByTile) {
         const uint32_t per_tile = units / tiles, blocks = per_tile / (r * split);
         tile = unit / per_tile;
         const uint32_t seg = unit - tile * per_tile, oc = seg / r;
         rho = (int)(seg - oc * r);
         s = (int)(oc / blocks);
         oi = oc - s * blocks;
-    } else {                                                 // unit = ((output block, chunk), segment, tile)
+    } else {
         const uint32_t seg = unit / tiles, oc = seg / r;
         rho = (int)(seg - oc * r);
         tile = unit - seg * tiles;
@@ -208,26 +219,25 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce_wave(
     const uint32_t o = o_first + oi * o_step;
     const uint32_t e = rho * Lv + x;
     if (x >= Lv || e >= Wv) return;
-    const int64_t first = red_ptr[o], n = red_ptr[o + 1] - first;
-    const int64_t lo = first + n * s / split, hi = first + n * (s + 1) / split;
+    const int64_t lo = node_ptr[o * split + s], hi = node_ptr[o * split + s + 1];
     typename O::Q acc = O::azero();
     int64_t i = lo;
     // the files the node stores come first in the list
     auto own = [&](int64_t row) { return load_pack<READS == kAll, P>(reinterpret_cast<const P *>(V + (row >> 1)) + e); };
     for (; i + 4 <= hi; i += 4) {
-        const int64_t row[4] = {red_row[i], red_row[i + 1], red_row[i + 2], red_row[i + 3]};
+        const int64_t row[4] = {node_row[i], node_row[i + 1], node_row[i + 2], node_row[i + 3]};
         if (row[3] & 1) break;
         const P v[4] = {own(row[0]), own(row[1]), own(row[2]), own(row[3])};
 #pragma unroll
         for (int t = 0; t < 4; t++) acc = O::accum(acc, v[t]);
     }
-    for (; i < hi && !(red_row[i] & 1); i++) acc = O::accum(acc, own(red_row[i]));
+    for (; i < hi && !(node_row[i] & 1); i++) acc = O::accum(acc, own(node_row[i]));
     struct Packet {
         P coded, side[r > 1 ? r - 1 : 1];
     };
     auto load = [&](int64_t at, Packet &k) {
         // the entry is the packet's first element: packet number = element / W, exact in fp64
-        const uint32_t pk = wave_uniform((uint32_t)((double)(red_row[at] >> 1) * per_row + 0.5));
+        const uint32_t pk = wave_uniform((uint32_t)((double)(node_row[at] >> 1) * per_row + 0.5));
         const uint32_t u = pk / R1;
         const int b = (int)(pk - u * R1);
         const int a = rho < b ? rho : rho + 1;
@@ -352,23 +362,8 @@ Reads node_reads(const ccdc_plan_t *p, int node, bool by_wavefront)
     if (node >= 0) return values <= kKeptOneNodeBytes ? kAll : kPast;
     if (!by_wavefront || VEC == 1) return kAll;
     if (p->r == 1) return values <= kKeptStageBytes ? kAll : kPast;
+    if (!p->node_row.empty()) return kAll;           // read together, see lists_by_round()
     return values / p->J <= (p->r - 1) * kKeptNodeBytes ? kAll : kCoded;
-}
-
-// Whether k_node_decode_reduce_wave numbers its units by tile, an XCD on a contiguous range of them, so that the nodes that read
-// the same packs run next to each other behind one L2; else the tiles of one output are neighbours, on all XCDs.  For all nodes
-// of one job and packs of 16 bytes, where a tile has 14 outputs (a node's segment) or more to share its packs: with fewer it is
-// slower (r = 2, 4 nodes 1.04 of the time, 5 nodes 1.03, 6 nodes 0.99; 4 nodes, r = 3 0.99, 5 nodes 0.90).  The fewer readers a pack has
-// and the more files are summed for one, the less is shared, so r = 2 and batches of several files ask for more tiles.  Over 3303 inputs
-// of 48 MB to 2.9 GB and 16 tiles or more: 2110 are numbered by tile and take 0.886 of the time (one file and r >= 3 0.848, r = 2 0.967, several files
-// 0.910; 12 nodes, r = 2, two functions each, T = 155840 u32 271 -> 249 us), 32 over 3 % more (8 nodes, r = 4, T = 72064 f16 28.6 -> 35.0, else up to 1.09);
-// the other 1193 would take 1.001 of it, 245 over 3 % more.
-// With fewer than 16 tiles the rows of one are more than an L2 holds (22 nodes, r = 3, seven files, T = 1352 f32, two tiles, 448 us, 786);
-// narrower packs 0.99, up to 1.05; with r = 1 nothing is read twice, 1.04.  Chosen in the kernel both ways cost short wavefronts up to 15 %.
-inline bool neighbours_share(const ccdc_plan_t *p, int node, uint32_t tiles)
-{
-    if (node >= 0 || p->J > 1 || p->K * p->r < 14 || (p->r == 2 && p->m > 1)) return false;
-    return tiles >= (p->m > 1 ? 200u : p->r == 2 ? 64u : 16u);
 }
 
 // Calls launch(reads) with that as a compile-time constant.  CODED: whether kCoded is one of the answers there are.
@@ -424,6 +419,7 @@ int run_node_decode_reduce(const ccdc_plan_t *p, int node, const void *V, const 
     const uint32_t Wv = (uint32_t)(p->W / VEC), Lv = (uint32_t)(p->ell / VEC);
     const uint32_t tiles = cdiv(Wv, kBlock);
     const int split = p->red_split;
+    const int64_t *rows = p->node_row.empty() ? p->d_red_row : p->d_node_row;
     const uint32_t count = node < 0 ? (uint32_t)p->nout : (uint32_t)p->J;
     const uint32_t o_first = node < 0 ? 0u : (uint32_t)node, o_step = node < 0 ? 1u : (uint32_t)p->K;
     const int64_t chunk_stride = (int64_t)p->J * p->Q * p->T;
@@ -437,16 +433,19 @@ int run_node_decode_reduce(const ccdc_plan_t *p, int node, const void *V, const 
             constexpr int R1 = decltype(r1)::value;
             constexpr int FILES = decltype(files)::value;
             by_node_reads<(VEC > 1 && R1 > 2)>(node_reads<VEC>(p, node, true), [&](auto reads) {
-                auto numbered = [&](auto by_tile) {
-                    k_node_decode_reduce_wave<A, VEC, R1, FILES, decltype(reads)::value, decltype(by_tile)::value><<<cdiv(units, kWaves), kBlock, 0, st>>>(
-                        (const E *)V, (const E *)X, (E *)Phi, (Acc *)p->d_workspace, p->d_red_ptr, p->d_red_row, p->d_red_out,
+                auto numbered = [&](auto numbering) {
+                    k_node_decode_reduce_wave<A, VEC, R1, FILES, decltype(reads)::value, decltype(numbering)::value><<<cdiv(units, kWaves), kBlock, 0, st>>>(
+                        (const E *)V, (const E *)X, (E *)Phi, (Acc *)p->d_workspace, p->d_node_ptr, rows, p->d_red_out,
                         p->d_src_off, Lv, Wv, 1.0 / (double)p->W, p->m, (int64_t)p->Q * p->T, wave_tiles, split, chunk_stride,
                         o_first, o_step, (uint32_t)units);
                 };
-                if constexpr (VEC * sizeof(E) >= 16 && R1 > 2) {
-                    if (neighbours_share(p, node, wave_tiles)) return numbered(std::true_type());
+                if constexpr (R1 > 3 && decltype(reads)::value == kAll) {
+                    if (node < 0 && !p->node_row.empty()) return numbered(std::integral_constant<int, kByChunk>());
                 }
-                numbered(std::false_type());
+                if constexpr (VEC * sizeof(E) >= 16 && R1 > 2) {
+                    if (node < 0 && neighbours_share(p, wave_tiles)) return numbered(std::integral_constant<int, kByTile>());
+                }
+                numbered(std::integral_constant<int, kByOutput>());
             });
         };
         by_shape<Ops<A, VEC>>(p, p->m > 2 || p->r > 2, launch);     // r = 2: one packet in the making, as in combine
@@ -454,7 +453,7 @@ int run_node_decode_reduce(const ccdc_plan_t *p, int node, const void *V, const 
         by_node_reads<false>(node_reads<VEC>(p, node, false), [&](auto reads) {
             by_files<Ops<A, VEC>>(p->m > 2, [&](auto together) {
                 k_node_decode_reduce<A, VEC, decltype(reads)::value, decltype(together)::value><<<(uint32_t)blocks, kBlock, 0, st>>>(
-                    (const E *)V, (const E *)X, (E *)Phi, (Acc *)p->d_workspace, p->d_red_ptr, p->d_red_row, p->d_red_out,
+                    (const E *)V, (const E *)X, (E *)Phi, (Acc *)p->d_workspace, p->d_node_ptr, rows, p->d_red_out,
                     p->d_src_off, p->r + 1, Lv, Wv, p->W, p->m, (int64_t)p->Q * p->T, tiles, split, chunk_stride, o_first,
                     o_step);
             });

@@ -317,6 +317,36 @@ int plan_groups(int64_t nout, int64_t rows, int64_t W, int vec, int elem, int64_
     return narrow && rows > 64 * nout * waves ? 0 : (int)waves;
 }
 
+// The row lists of ccdc_node_decode_reduce and the chunks they are cut into.  A coded packet is read by its r receivers and a value
+// that is side information by r - 1, so lists are best cut by rounds: chunk s of every list then has the packets of the
+// same rounds, s, s + split, s + 2 split, .. (a chunk of neighbouring rounds would have all of the first node's),
+// and units that are numbered by chunk (node.hip) read them together, behind one L2.  The price is chunks of unequal length, and
+// a chunk is a chain of waits: false where the longest is over `most` times the mean.
+bool lists_by_round(const ccdc_plan_t *p, const std::vector<int64_t> &ptr, const std::vector<int64_t> &rows, int64_t split, int64_t W,
+                    double most, std::vector<int64_t> *cut, std::vector<int64_t> *list)
+{
+    const int64_t nout = (int64_t)ptr.size() - 1;
+    const int r1 = p->r + 1;
+    std::vector<int64_t> at((size_t)(nout * split) + 1, 0), own((size_t)nout, 0);
+    for (int64_t o = 0; o < nout; o++) {
+        while (own[o] < ptr[o + 1] - ptr[o] && !(rows[ptr[o] + own[o]] & 1)) own[o]++;
+        for (int64_t s = 0; s < split; s++) at[o * split + s + 1] = own[o] * (s + 1) / split - own[o] * s / split;
+    }
+    for (int64_t u = 0; u < p->nround; u++)
+        for (int b = 0; b < r1; b++) at[p->round_member[u * r1 + b] * split + u % split + 1]++;
+    const int64_t longest = *std::max_element(at.begin(), at.end());
+    if ((double)longest * (double)(nout * split) > most * (double)ptr[nout]) return false;
+    for (int64_t i = 0; i < nout * split; i++) at[i + 1] += at[i];
+    cut->assign(at.begin(), at.end());
+    list->resize((size_t)at.back());
+    for (int64_t o = 0; o < nout; o++)
+        for (int64_t s = 0; s < split; s++)
+            for (int64_t i = own[o] * s / split; i < own[o] * (s + 1) / split; i++) (*list)[at[o * split + s]++] = rows[ptr[o] + i];
+    for (int64_t u = 0; u < p->nround; u++)
+        for (int b = 0; b < r1; b++) (*list)[at[p->round_member[u * r1 + b] * split + u % split]++] = (((u * r1 + b) * W) << 1) | 1;
+    return true;
+}
+
 // ccdc_plan_bind for the compression-only scheme: the packet is sent whole (no
 // segments), so ell = W, and every packet is both what is transmitted and what
 // the receiver adds.
@@ -490,7 +520,32 @@ int bind_plan(ccdc_plan_t *p, int64_t T, int mode)
             for (size_t i = 0; i < src.size(); i++) pipe[i] = (src[i] << 12) | p->round_member[i];
         }
 
+        std::vector<int64_t> node_ptr, node_row;
+        const int elem = mode >= CCDC_BF16_SUM_XOR ? 2 : 4;
+        // elements of the packs of a call with aligned pointers
+        const int node_vec = elem == 4 || T % 4 != 0 ? vec : (T % 8 == 0 && ell % 8 == 0 ? 8 : 4);
+        // Lists by round: where a value has two readers or more besides its owner's output (r >= 3; r = 2 0.94 to 1.08 of the
+        // time), with a wavefront on one segment and units that are not shared by tile already.  Over 95 such inputs of 3 MB to
+        // 2 GB 0.83 of the time of equal cuts, the least 0.28 (8 nodes, r = 5, twelve files, T = 19008 f32 410 -> 113 us; 16
+        // nodes, r = 3, T = 4096 h32 60.5 -> 50.5).  Chunks may be up to twice as long as the mean: seven inputs beyond that took
+        // 0.95 to 1.06 of the time, 13 nodes, r = 3, T = 1280 bf16 13.3 -> 14.1 at 2.7 times.  One-element packs share lines with
+        // their neighbours anyway: half as long again at most (18 nodes, r = 3, T = 1973 bf16 62 -> 66 at 1.64 times), and in few
+        // chunks only while the values' readers can find them in the last-level cache (21 nodes, r = 3, T = 4711 f32, 1.3
+        // GB, six chunks, 281 -> 295).
+        const bool wide = node_vec > 1;
+        const bool by_round = split > 1 && p->J == 1 && r >= 3 && r <= 5 && fills_wavefronts((uint32_t)(ell / node_vec)) &&
+                              (wide || split >= 8 || v_elems * elem <= (r - 1) * kKeptNodeBytes) &&
+                              !(node_vec * elem == 16 && neighbours_share(p, cdiv((uint64_t)(ell / node_vec), kPipeLanes)));
+        if (!by_round || !lists_by_round(p, cnt, rows_tab, split, W, wide ? 2 : 1.5, &node_ptr, &node_row)) {
+            node_ptr.resize((size_t)(nout * split) + 1);
+            for (int64_t o = 0; o < nout; o++)
+                for (int64_t s = 0; s < split; s++) node_ptr[o * split + s] = cnt[o] + (cnt[o + 1] - cnt[o]) * s / split;
+            node_ptr.back() = cnt[nout];
+        }
+
         p->T = T; p->W = W; p->ell = ell; p->mode = mode;
+        p->node_ptr.swap(node_ptr);
+        p->node_row.swap(node_row);
         p->pipe_ok = pipe_ok;
         p->pipe_max_chunks = (int)pipe_cap;
         p->pipe_local_rows = pipe_ok ? local_rows : 0;
@@ -504,7 +559,6 @@ int bind_plan(ccdc_plan_t *p, int64_t T, int mode)
         p->red_out.swap(outs);
         p->nout = nout;
         p->red_split = (int)split;
-        const int elem = mode >= CCDC_BF16_SUM_XOR ? 2 : 4;
         p->red_waves = plan_groups(nout, (int64_t)p->red_row.size(), W, vec, elem, split, v_elems * elem);
         p->red_workspace_bytes = split > 1 ? (size_t)split * (size_t)p->J * p->Q * (size_t)T * 4 : 0;
         p->workspace_bytes = p->red_workspace_bytes;         // until upload has fixed the chunks: the most it can be

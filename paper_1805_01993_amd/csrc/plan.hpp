@@ -53,6 +53,8 @@ struct ccdc_plan_s {
     std::vector<int64_t> red_row;       // rows: (element offset << 1) | (1 = in D, 0 = in V)
     std::vector<int64_t> red_out;       // [nout] element offset of the output block in Phi
     int64_t nout = 0;                   // J * K output blocks of W elements
+    std::vector<int64_t> node_ptr;      // [nout*red_split+1] bounds of the chunks ccdc_node_decode_reduce cuts the lists into
+    std::vector<int64_t> node_row;      // their rows, as red_row, where they are cut by rounds; empty: red_row
     int red_split = 1;                  // the row list of an output is summed in this many chunks
     int red_waves = 0;                  // > 0: ccdc_reduce sums it in one workgroup of that many wavefronts instead
     size_t red_workspace_bytes = 0;     // partial sums of the split reductions
@@ -71,6 +73,7 @@ struct ccdc_plan_s {
     int device = -1;
     int64_t *d_src_off = nullptr, *d_red_ptr = nullptr, *d_red_row = nullptr, *d_red_out = nullptr;
     int64_t *d_loc_row = nullptr, *d_pipe_row = nullptr;
+    int64_t *d_node_ptr = nullptr, *d_node_row = nullptr;       // node_row empty: null
     int32_t *d_row_files = nullptr;     // null when every packet adds m files
     int32_t *d_node_rows = nullptr;
     void *d_workspace = nullptr;
@@ -167,6 +170,32 @@ constexpr uint32_t xcd_spans(uint32_t block, uint32_t blocks, uint32_t span)
 {
     const uint32_t first = block & (0u - span), left = blocks - first;
     return first + xcd_contiguous(block - first, span - 1 < left - 1 ? span : left);
+}
+
+inline uint32_t cdiv(uint64_t a, uint64_t b) { return (uint32_t)((a + b - 1) / b); }
+
+constexpr int kWave = 64;
+// Segments fill the wavefronts of a tile row to at least 3/4.
+inline bool fills_wavefronts(uint32_t Lv)
+{
+    const uint64_t lanes = (uint64_t)cdiv(Lv, kWave) * kWave;
+    return (uint64_t)Lv * 4 >= lanes * 3;
+}
+
+// Whether k_node_decode_reduce_wave numbers its units by tile, an XCD on a contiguous range of them, so that the nodes that read
+// the same packs run next to each other behind one L2; else the tiles of one output are neighbours, on all XCDs.  For all nodes
+// of one job and packs of 16 bytes, where a tile has 14 outputs (a node's segment) or more to share its packs: with fewer it is
+// slower (r = 2, 4 nodes 1.04 of the time, 5 nodes 1.03, 6 nodes 0.99; 4 nodes, r = 3 0.99, 5 nodes 0.90).  The fewer readers a pack has
+// and the more files are summed for one, the less is shared, so r = 2 and batches of several files ask for more tiles.  Over 3303 inputs
+// of 48 MB to 2.9 GB and 16 tiles or more: 2110 are numbered by tile and take 0.886 of the time (one file and r >= 3 0.848, r = 2 0.967, several files
+// 0.910; 12 nodes, r = 2, two functions each, T = 155840 u32 271 -> 249 us), 32 over 3 % more (8 nodes, r = 4, T = 72064 f16 28.6 -> 35.0, else up to 1.09);
+// the other 1193 would take 1.001 of it, 245 over 3 % more.
+// With fewer than 16 tiles the rows of one are more than an L2 holds (22 nodes, r = 3, seven files, T = 1352 f32, two tiles, 448 us, 786);
+// narrower packs 0.99, up to 1.05; with r = 1 nothing is read twice, 1.04.  Chosen in the kernel both ways cost short wavefronts up to 15 %.
+inline bool neighbours_share(const ccdc_plan_t *p, uint32_t tiles)
+{
+    if (p->J > 1 || p->K * p->r < 14 || (p->r == 2 && p->m > 1)) return false;
+    return tiles >= (p->m > 1 ? 200u : p->r == 2 ? 64u : 16u);
 }
 
 // Rank of sender a's label among the members other than b.

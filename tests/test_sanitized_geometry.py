@@ -215,3 +215,23 @@ def test_reduce_of_narrow_packs(kernel_driver, K, r, T, mode, waves):  # noqa: F
     """One-element packs of 16 bits with over 64 rows a wavefront keep the split form."""
     m = 2 if K == 12 else 1
     assert choices(kernel_driver, K, r, m * comb(K, r), T, mode)[1][1] == waves
+
+
+# K, r, m, T, mode, whether node-local lists are cut by rounds: edges of the rule (replication, how unequal the chunks
+# are, one-element packs, segments that leave lanes idle, a list that is not cut)
+BY_ROUND = [
+    (7, 3, 2, 768, 2, 1), (7, 4, 1, 1024, 0, 1), (7, 5, 3, 1280, 1, 1), (8, 3, 3, 1536, 3, 1), (9, 3, 1, 765, 1, 0),
+    (7, 3, 9, 759, 0, 0), (8, 2, 1, 512, 2, 0), (7, 3, 2, 804, 2, 0), (6, 5, 1, 4100, 4, 1),
+]
+
+
+@pytest.mark.parametrize("case", BY_ROUND, ids=lambda c: "-".join(map(str, c)))
+def test_lists_by_round(kernel_driver, case):  # noqa: F811
+    """Every row once, whatever the chunks: the sums are whole numbers, and a node alone has the bits of all nodes."""
+    K, r, m, T, mode, by_round = case
+    args = (K, r, K, m * comb(K, r), T, mode, 0, 256, 8)
+    res = subprocess.run([kernel_driver] + [str(v) for v in args], capture_output=True, text=True,
+                         env=dict(os.environ, **ENV, SHIM_NODE="0,0", SHIM_REDUCE="0"), timeout=600)
+    assert res.returncode == 0, res.stdout + res.stderr
+    assert f"lists by round {by_round}\n" in res.stdout, res.stdout
+    assert " 0 mismatches" in res.stdout, res.stdout
