@@ -12,6 +12,25 @@
 namespace {
 using namespace ccdc;
 
+// On large inputs, packs of more than one element, the XCDs take runs of span / 8 neighbouring workgroups in turn, so that an L2
+// sees whole stretches of the rows; small ones and packs that share lines keep the order in which workgroups are handed out.  Over 110
+// passes of 60 MB to 4 GB by ccdc_combine with the calls after it, ccdc_shuffle_fused and ccdc_reduce, and the uncoded scheme, with these
+// runs 0.981 of the time, of 300 MB and more 0.980, with the stores past the caches 0.970 (56 jobs on 8 nodes, r = 2, T = 150000 u32 731 -> 702 us; uncoded,
+// 22 nodes, T = 39296 u32, the packets 301 -> 263, 23 nodes, T = 14300 f32 67 -> 58).  A call alone: ccdc_combine in runs of 8
+// to 512 workgroups 0.988 to 0.966 of the time over 25 inputs, with one-element packs 1.01 to 1.03; ccdc_reduce in runs of 8 to 32 0.98 over
+// 65; ccdc_shuffle_fused from a gigabyte on 0.984 over six, below it 0.99 to 1.02.
+constexpr uint32_t kCombineSpan = 1024, kReduceSpan = 128, kShuffleSpan = 256;
+constexpr double kShuffleRunsBytes = 1e9;
+// From here on ccdc_combine's sums are stored past the caches: 24 inputs of over a gigabyte 0.965 of the time, ordinary
+// stores 0.988.  Below it the next call still finds part of the packets (15 nodes, r = 4, four files, T = 376 f32, 248 MB, a pass
+// of the four stages 53.1 -> 53.5; 23 nodes, r = 4, three files, T = 64 bf16 60.6 -> 61.9).
+constexpr double kPastStoreBytes = 500e6;
+template <bool LARGE>
+__device__ __forceinline__ uint32_t in_runs(uint32_t span)
+{
+    return LARGE ? xcd_spans(blockIdx.x, gridDim.x, span) : blockIdx.x;
+}
+
 // ------------------------------------------------------------------ combine
 // Sec. IV-B pre-combining.  One work item = one pack of one packet Vbar[u][b]:
 // it adds the same pack of the files of the served batch (m of them, or
@@ -21,11 +40,12 @@ __global__ __launch_bounds__(kBlock) void k_combine(const typename A::elem *__re
                                                     typename A::elem *__restrict__ Vbar,
                                                     const int64_t *__restrict__ src_off,
                                                     const int32_t *__restrict__ row_files, uint32_t Wv, int m,
-                                                    int64_t file_stride, uint32_t items)
+                                                    int64_t file_stride, uint32_t items, bool past)
 {
     using O = Ops<A, VEC>;
     using P = typename O::P;
-    const uint32_t idx = blockIdx.x * kBlock + threadIdx.x;
+    constexpr bool LARGE = !KEPT && VEC > 1;          // see in_runs()
+    const uint32_t idx = in_runs<LARGE>(kCombineSpan) * kBlock + threadIdx.x;
     if (idx >= items) return;
     const uint32_t row = idx / Wv, e = idx - row * Wv;
     const typename A::elem *src = V + src_off[row] + (int64_t)e * VEC;
@@ -35,7 +55,9 @@ __global__ __launch_bounds__(kBlock) void k_combine(const typename A::elem *__re
         reinterpret_cast<P *>(Vbar)[idx] = first;
         return;
     }
-    reinterpret_cast<P *>(Vbar)[idx] = O::narrow(sum_files<O, KEPT, TOGETHER>(first, src, files, file_stride));
+    const P sum = O::narrow(sum_files<O, KEPT, TOGETHER>(first, src, files, file_stride));
+    if (LARGE && past) store_stream(reinterpret_cast<P *>(Vbar) + idx, sum);
+    else reinterpret_cast<P *>(Vbar)[idx] = sum;
 }
 
 // Pre-combining for short packets and long batches (few packs per packet, many
@@ -191,12 +213,12 @@ __global__ __launch_bounds__(kBlock) void k_shuffle_fused(const typename A::elem
                                                           typename A::elem *__restrict__ D,
                                                           const int64_t *__restrict__ src_off, int r1_rt,
                                                           uint32_t Lv, uint32_t Wv, int m, int64_t file_stride,
-                                                          uint32_t items)
+                                                          uint32_t items, uint32_t span)
 {
     using O = Ops<A, VEC>;
     using P = typename O::P;
     const int r1 = R1 > 0 ? R1 : r1_rt;
-    const uint32_t idx = blockIdx.x * kBlock + threadIdx.x;
+    const uint32_t idx = in_runs<!KEPT && (VEC > 1)>(span) * kBlock + threadIdx.x;
     if (idx >= items) return;
     const uint32_t ua = idx / Lv, x = idx - ua * Lv;
     const uint32_t u = ua / r1;
@@ -295,8 +317,10 @@ __global__ __launch_bounds__(kBlock) void k_reduce_rows(const typename A::elem *
 {
     using O = Ops<A, VEC>;
     using P = typename O::P;
-    const uint32_t tile = blockIdx.x % tiles;
-    const uint32_t oc = blockIdx.x / tiles;
+    constexpr bool LARGE = !KEPT && VEC > 1;          // see in_runs()
+    const uint32_t block = in_runs<LARGE>(kReduceSpan);
+    const uint32_t tile = block % tiles;
+    const uint32_t oc = block / tiles;
     const uint32_t o = oc / split;
     const int s = (int)(oc - o * split);
     const uint32_t e = tile * kBlock + threadIdx.x;
@@ -304,13 +328,27 @@ __global__ __launch_bounds__(kBlock) void k_reduce_rows(const typename A::elem *
     const int64_t first = red_ptr[o], n = red_ptr[o + 1] - first;
     const int64_t lo = first + n * s / split, hi = first + n * (s + 1) / split;
     typename O::Q acc = O::azero();
-#pragma unroll 4
-    for (int64_t i = lo; i < hi; i++) {
-        const int64_t row = red_row[i];
+    int64_t i = lo;
+    auto row_pack = [&](int64_t at) {
+        const int64_t row = red_row[at];
         const typename A::elem *base = (row & 1) ? D : V;
-        acc = O::accum(acc, load_pack<KEPT, P>(reinterpret_cast<const P *>(base + (row >> 1)) + e));
+        return load_pack<KEPT, P>(reinterpret_cast<const P *>(base + (row >> 1)) + e);
+    };
+    // One-element packs are few bytes in flight: eight rows at a time.  16 lists of 22 rows and more 0.93 of the time with four (12
+    // nodes, r = 5, T = 27763 bf16 153 -> 110 us); wide packs 0.99 to 1.08.
+    if constexpr (VEC == 1) {
+        for (; i + 8 <= hi; i += 8) {
+            P v[8];
+#pragma unroll
+            for (int t = 0; t < 8; t++) v[t] = row_pack(i + t);
+#pragma unroll
+            for (int t = 0; t < 8; t++) acc = O::accum(acc, v[t]);
+        }
     }
+#pragma unroll 4
+    for (; i < hi; i++) acc = O::accum(acc, row_pack(i));
     if (split > 1) reinterpret_cast<typename O::Q *>(part + (int64_t)s * chunk_stride + red_out[o])[e] = acc;
+    else if constexpr (LARGE) store_stream(reinterpret_cast<P *>(out + red_out[o]) + e, O::narrow(acc));
     else reinterpret_cast<P *>(out + red_out[o])[e] = O::narrow(acc);
 }
 
@@ -463,10 +501,11 @@ int run_combine(const ccdc_plan_t *p, const void *V, void *Vbar, hipStream_t st)
         }
     }
     const int files = p->compression ? p->batch_first[1] : p->m;        // of a batch, uncoded plans: of the largest
+    const bool past = moved_bytes(p, packets) >= kPastStoreBytes;
     by_reads<false>(kept, [&](auto k) {
         by_files<Ops<A, VEC>>(files > 2, [&](auto together) {
             k_combine<A, VEC, decltype(k)::value, decltype(together)::value><<<cdiv(items, kBlock), kBlock, 0, st>>>(
-                (const E *)V, (E *)Vbar, p->d_src_off, p->d_row_files, Wv, p->m, (int64_t)p->Q * p->T, (uint32_t)items);
+                (const E *)V, (E *)Vbar, p->d_src_off, p->d_row_files, Wv, p->m, (int64_t)p->Q * p->T, (uint32_t)items, past);
         });
     });
     return launched();
@@ -515,11 +554,13 @@ void launch_shuffle(const ccdc_plan_t *p, const void *V, void *X, void *D, hipSt
     using E = typename A::elem;
     const uint32_t Wv = (uint32_t)(p->W / VEC), Lv = (uint32_t)(p->ell / VEC);
     const uint64_t items = (uint64_t)p->nround * (p->r + 1) * Lv;
-    const bool kept = moved_bytes(p, (double)p->nrows * (p->W + p->ell)) <= kKeptStageBytes;        // V, X and D
+    const double bytes = moved_bytes(p, (double)p->nrows * (p->W + p->ell));                         // V, X and D
+    const bool kept = bytes <= kKeptStageBytes;
+    const uint32_t span = bytes >= kShuffleRunsBytes ? kShuffleSpan : kXcds;
     auto launch = [&](auto multi) {
         by_reads<VEC == 1>(kept, [&](auto k) {
             k_shuffle_fused<A, VEC, R1, decltype(k)::value, decltype(multi)::value><<<cdiv(items, kBlock), kBlock, 0, st>>>(
-                (const E *)V, (E *)X, (E *)D, p->d_src_off, p->r + 1, Lv, Wv, p->m, (int64_t)p->Q * p->T, (uint32_t)items);
+                (const E *)V, (E *)X, (E *)D, p->d_src_off, p->r + 1, Lv, Wv, p->m, (int64_t)p->Q * p->T, (uint32_t)items, span);
         });
     };
     if constexpr (R1 > 0 && packets_together<Ops<A, VEC>, R1 - 1>()) {
