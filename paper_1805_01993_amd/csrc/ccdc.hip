@@ -426,7 +426,7 @@ void release_device(ccdc_plan_t *p)
 {
     if (!p) return;
     if (p->uploaded || p->d_src_off || p->d_red_ptr || p->d_red_row || p->d_red_out || p->d_loc_row || p->d_pipe_row ||
-        p->d_row_files || p->d_node_rows || p->d_node_ptr || p->d_node_row || p->d_workspace || p->ws_event) {
+        p->d_row_files || p->d_node_rows || p->d_node_row || p->d_workspace || p->ws_event) {
         int cur = -1;
         const bool sw = hipGetDevice(&cur) == hipSuccess && p->device >= 0 && cur != p->device &&
                         hipSetDevice(p->device) == hipSuccess;
@@ -438,7 +438,6 @@ void release_device(ccdc_plan_t *p)
         (void)hipFree(p->d_pipe_row);
         (void)hipFree(p->d_row_files);
         (void)hipFree(p->d_node_rows);
-        (void)hipFree(p->d_node_ptr);
         (void)hipFree(p->d_node_row);
         (void)hipFree(p->d_workspace);
         if (p->ws_event) (void)hipEventDestroy((hipEvent_t)p->ws_event);
@@ -448,7 +447,7 @@ void release_device(ccdc_plan_t *p)
     p->d_pipe_row = nullptr;
     p->d_row_files = nullptr;
     p->d_node_rows = nullptr;
-    p->d_node_ptr = p->d_node_row = nullptr;
+    p->d_node_row = nullptr;
     p->d_workspace = nullptr;
     p->pipe_chunks = 0;
     p->ws_event = nullptr;
@@ -693,7 +692,6 @@ int ccdc_plan_upload(ccdc_plan_t *plan)
     if (rc == CCDC_OK) rc = to_device(plan->pipe_row, &plan->d_pipe_row);
     if (rc == CCDC_OK && !plan->row_files.empty()) rc = to_device(plan->row_files, &plan->d_row_files);
     if (rc == CCDC_OK && !plan->node_rows.empty()) rc = to_device(plan->node_rows, &plan->d_node_rows);
-    if (rc == CCDC_OK && !plan->node_ptr.empty()) rc = to_device(plan->node_ptr, &plan->d_node_ptr);
     if (rc == CCDC_OK && !plan->node_row.empty()) rc = to_device(plan->node_row, &plan->d_node_row);
     if (rc == CCDC_OK && plan->workspace_bytes > 0 &&
         hipMalloc(&plan->d_workspace, plan->workspace_bytes) != hipSuccess) {

@@ -61,6 +61,17 @@ __global__ __launch_bounds__(kBlock) void k_node_encode(const typename A::elem *
     store_stream(reinterpret_cast<P *>(X) + (size_t)i * Lv + x, coded);
 }
 
+// Bounds of chunk s of output block o's row list: in a table where lists are cut by rounds, else an equal part of the list.
+struct Rows {
+    int64_t lo, hi;
+};
+__device__ __forceinline__ Rows chunk_of(const int64_t *__restrict__ ptr, bool by_round, uint32_t o, int s, int split)
+{
+    if (by_round) return {ptr[o * split + s], ptr[o * split + s + 1]};
+    const int64_t first = ptr[o], n = ptr[o + 1] - first;
+    return {first + n * s / split, first + n * (s + 1) / split};
+}
+
 // --------------------------------------------- a receiver's decoding + output
 // Decoding and final reduction of Sec. IV-B for the output blocks o_first,
 // o_first + o_step, ... (one node's block in every job, or all blocks).  The
@@ -73,7 +84,7 @@ __global__ __launch_bounds__(kBlock) void k_node_encode(const typename A::elem *
 template <class A, int VEC, int READS, bool TOGETHER>
 __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
     const typename A::elem *__restrict__ V, const typename A::elem *__restrict__ X, typename A::elem *__restrict__ out,
-    typename A::acc *__restrict__ part, const int64_t *__restrict__ node_ptr, const int64_t *__restrict__ node_row,
+    typename A::acc *__restrict__ part, const int64_t *__restrict__ node_ptr, bool by_round, const int64_t *__restrict__ node_row,
     const int64_t *__restrict__ red_out, const int64_t *__restrict__ src_off, int r1, uint32_t Lv, uint32_t Wv,
     int64_t W, int m, int64_t file_stride, uint32_t tiles, int split, int64_t chunk_stride, uint32_t o_first,
     uint32_t o_step)
@@ -88,7 +99,7 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
     const uint32_t e = tile * kBlock + threadIdx.x;
     if (e >= Wv) return;
     const uint32_t rho = e / Lv, x = e - rho * Lv;
-    const int64_t lo = node_ptr[o * split + s], hi = node_ptr[o * split + s + 1];
+    const auto [lo, hi] = chunk_of(node_ptr, by_round, o, s, split);
     typename O::Q acc = O::azero();
     for (int64_t i = lo; i < hi; i++) {
         const int64_t row = node_row[i];
@@ -182,7 +193,7 @@ enum Numbering {
 template <class A, int VEC, int R1, int FILES, int READS, int NUMBERING>
 __global__ __launch_bounds__(kBlock) void k_node_decode_reduce_wave(
     const typename A::elem *__restrict__ V, const typename A::elem *__restrict__ X, typename A::elem *__restrict__ out,
-    typename A::acc *__restrict__ part, const int64_t *__restrict__ node_ptr, const int64_t *__restrict__ node_row,
+    typename A::acc *__restrict__ part, const int64_t *__restrict__ node_ptr, bool by_round, const int64_t *__restrict__ node_row,
     const int64_t *__restrict__ red_out, const int64_t *__restrict__ src_off, uint32_t Lv, uint32_t Wv,
     double per_row, int m, int64_t file_stride, uint32_t tiles, int split, int64_t chunk_stride, uint32_t o_first,
     uint32_t o_step, uint32_t units)
@@ -219,7 +230,7 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce_wave(
     const uint32_t o = o_first + oi * o_step;
     const uint32_t e = rho * Lv + x;
     if (x >= Lv || e >= Wv) return;
-    const int64_t lo = node_ptr[o * split + s], hi = node_ptr[o * split + s + 1];
+    const auto [lo, hi] = chunk_of(node_ptr, by_round, o, s, split);
     typename O::Q acc = O::azero();
     int64_t i = lo;
     // the files the node stores come first in the list
@@ -419,7 +430,9 @@ int run_node_decode_reduce(const ccdc_plan_t *p, int node, const void *V, const 
     const uint32_t Wv = (uint32_t)(p->W / VEC), Lv = (uint32_t)(p->ell / VEC);
     const uint32_t tiles = cdiv(Wv, kBlock);
     const int split = p->red_split;
-    const int64_t *rows = p->node_row.empty() ? p->d_red_row : p->d_node_row;
+    const bool by_round = p->d_node_row != nullptr;
+    const int64_t *bounds = by_round ? p->d_node_row : p->d_red_ptr;
+    const int64_t *rows = by_round ? p->d_node_row + (size_t)p->nout * split + 1 : p->d_red_row;
     const uint32_t count = node < 0 ? (uint32_t)p->nout : (uint32_t)p->J;
     const uint32_t o_first = node < 0 ? 0u : (uint32_t)node, o_step = node < 0 ? 1u : (uint32_t)p->K;
     const int64_t chunk_stride = (int64_t)p->J * p->Q * p->T;
@@ -435,12 +448,12 @@ int run_node_decode_reduce(const ccdc_plan_t *p, int node, const void *V, const 
             by_node_reads<(VEC > 1 && R1 > 2)>(node_reads<VEC>(p, node, true), [&](auto reads) {
                 auto numbered = [&](auto numbering) {
                     k_node_decode_reduce_wave<A, VEC, R1, FILES, decltype(reads)::value, decltype(numbering)::value><<<cdiv(units, kWaves), kBlock, 0, st>>>(
-                        (const E *)V, (const E *)X, (E *)Phi, (Acc *)p->d_workspace, p->d_node_ptr, rows, p->d_red_out,
+                        (const E *)V, (const E *)X, (E *)Phi, (Acc *)p->d_workspace, bounds, by_round, rows, p->d_red_out,
                         p->d_src_off, Lv, Wv, 1.0 / (double)p->W, p->m, (int64_t)p->Q * p->T, wave_tiles, split, chunk_stride,
                         o_first, o_step, (uint32_t)units);
                 };
                 if constexpr (R1 > 3 && decltype(reads)::value == kAll) {
-                    if (node < 0 && !p->node_row.empty()) return numbered(std::integral_constant<int, kByChunk>());
+                    if (node < 0 && by_round) return numbered(std::integral_constant<int, kByChunk>());
                 }
                 if constexpr (VEC * sizeof(E) >= 16 && R1 > 2) {
                     if (node < 0 && neighbours_share(p, wave_tiles)) return numbered(std::integral_constant<int, kByTile>());
@@ -453,7 +466,7 @@ int run_node_decode_reduce(const ccdc_plan_t *p, int node, const void *V, const 
         by_node_reads<false>(node_reads<VEC>(p, node, false), [&](auto reads) {
             by_files<Ops<A, VEC>>(p->m > 2, [&](auto together) {
                 k_node_decode_reduce<A, VEC, decltype(reads)::value, decltype(together)::value><<<(uint32_t)blocks, kBlock, 0, st>>>(
-                    (const E *)V, (const E *)X, (E *)Phi, (Acc *)p->d_workspace, p->d_node_ptr, rows, p->d_red_out,
+                    (const E *)V, (const E *)X, (E *)Phi, (Acc *)p->d_workspace, bounds, by_round, rows, p->d_red_out,
                     p->d_src_off, p->r + 1, Lv, Wv, p->W, p->m, (int64_t)p->Q * p->T, tiles, split, chunk_stride, o_first,
                     o_step);
             });

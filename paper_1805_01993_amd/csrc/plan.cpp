@@ -321,9 +321,9 @@ int plan_groups(int64_t nout, int64_t rows, int64_t W, int vec, int elem, int64_
 // that is side information by r - 1, so lists are best cut by rounds: chunk s of every list then has the packets of the
 // same rounds, s, s + split, s + 2 split, .. (a chunk of neighbouring rounds would have all of the first node's),
 // and units that are numbered by chunk (node.hip) read them together, behind one L2.  The price is chunks of unequal length, and
-// a chunk is a chain of waits: false where the longest is over `most` times the mean.
-bool lists_by_round(const ccdc_plan_t *p, const std::vector<int64_t> &ptr, const std::vector<int64_t> &rows, int64_t split, int64_t W,
-                    double most, std::vector<int64_t> *cut, std::vector<int64_t> *list)
+// a chunk is a chain of waits: no such lists where the longest is over `most` times the mean.
+void lists_by_round(const ccdc_plan_t *p, const std::vector<int64_t> &ptr, const std::vector<int64_t> &rows, int64_t split, int64_t W,
+                    double most, std::vector<int64_t> *lists)
 {
     const int64_t nout = (int64_t)ptr.size() - 1;
     const int r1 = p->r + 1;
@@ -335,16 +335,17 @@ bool lists_by_round(const ccdc_plan_t *p, const std::vector<int64_t> &ptr, const
     for (int64_t u = 0; u < p->nround; u++)
         for (int b = 0; b < r1; b++) at[p->round_member[u * r1 + b] * split + u % split + 1]++;
     const int64_t longest = *std::max_element(at.begin(), at.end());
-    if ((double)longest * (double)(nout * split) > most * (double)ptr[nout]) return false;
+    if ((double)longest * (double)(nout * split) > most * (double)ptr[nout]) return;
     for (int64_t i = 0; i < nout * split; i++) at[i + 1] += at[i];
-    cut->assign(at.begin(), at.end());
-    list->resize((size_t)at.back());
+    lists->reserve(at.size() + (size_t)at.back());
+    lists->assign(at.begin(), at.end());
+    lists->resize(at.size() + (size_t)at.back());
+    int64_t *list = lists->data() + at.size();
     for (int64_t o = 0; o < nout; o++)
         for (int64_t s = 0; s < split; s++)
-            for (int64_t i = own[o] * s / split; i < own[o] * (s + 1) / split; i++) (*list)[at[o * split + s]++] = rows[ptr[o] + i];
+            for (int64_t i = own[o] * s / split; i < own[o] * (s + 1) / split; i++) list[at[o * split + s]++] = rows[ptr[o] + i];
     for (int64_t u = 0; u < p->nround; u++)
-        for (int b = 0; b < r1; b++) (*list)[at[p->round_member[u * r1 + b] * split + u % split]++] = (((u * r1 + b) * W) << 1) | 1;
-    return true;
+        for (int b = 0; b < r1; b++) list[at[p->round_member[u * r1 + b] * split + u % split]++] = (((u * r1 + b) * W) << 1) | 1;
 }
 
 // ccdc_plan_bind for the compression-only scheme: the packet is sent whole (no
@@ -520,7 +521,7 @@ int bind_plan(ccdc_plan_t *p, int64_t T, int mode)
             for (size_t i = 0; i < src.size(); i++) pipe[i] = (src[i] << 12) | p->round_member[i];
         }
 
-        std::vector<int64_t> node_ptr, node_row;
+        std::vector<int64_t> node_row;
         const int elem = mode >= CCDC_BF16_SUM_XOR ? 2 : 4;
         // elements of the packs of a call with aligned pointers
         const int node_vec = elem == 4 || T % 4 != 0 ? vec : (T % 8 == 0 && ell % 8 == 0 ? 8 : 4);
@@ -536,15 +537,9 @@ int bind_plan(ccdc_plan_t *p, int64_t T, int mode)
         const bool by_round = split > 1 && p->J == 1 && r >= 3 && r <= 5 && fills_wavefronts((uint32_t)(ell / node_vec)) &&
                               (wide || split >= 8 || v_elems * elem <= (r - 1) * kKeptNodeBytes) &&
                               !(node_vec * elem == 16 && neighbours_share(p, cdiv((uint64_t)(ell / node_vec), kPipeLanes)));
-        if (!by_round || !lists_by_round(p, cnt, rows_tab, split, W, wide ? 2 : 1.5, &node_ptr, &node_row)) {
-            node_ptr.resize((size_t)(nout * split) + 1);
-            for (int64_t o = 0; o < nout; o++)
-                for (int64_t s = 0; s < split; s++) node_ptr[o * split + s] = cnt[o] + (cnt[o + 1] - cnt[o]) * s / split;
-            node_ptr.back() = cnt[nout];
-        }
+        if (by_round) lists_by_round(p, cnt, rows_tab, split, W, wide ? 2 : 1.5, &node_row);
 
         p->T = T; p->W = W; p->ell = ell; p->mode = mode;
-        p->node_ptr.swap(node_ptr);
         p->node_row.swap(node_row);
         p->pipe_ok = pipe_ok;
         p->pipe_max_chunks = (int)pipe_cap;

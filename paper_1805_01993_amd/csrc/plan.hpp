@@ -53,8 +53,8 @@ struct ccdc_plan_s {
     std::vector<int64_t> red_row;       // rows: (element offset << 1) | (1 = in D, 0 = in V)
     std::vector<int64_t> red_out;       // [nout] element offset of the output block in Phi
     int64_t nout = 0;                   // J * K output blocks of W elements
-    std::vector<int64_t> node_ptr;      // [nout*red_split+1] bounds of the chunks ccdc_node_decode_reduce cuts the lists into
-    std::vector<int64_t> node_row;      // their rows, as red_row, where they are cut by rounds; empty: red_row
+    std::vector<int64_t> node_row;      // the lists of ccdc_node_decode_reduce where they are cut by rounds (else empty):
+                                        //   [nout*red_split+1] bounds of the chunks, then the rows, as red_row
     int red_split = 1;                  // the row list of an output is summed in this many chunks
     int red_waves = 0;                  // > 0: ccdc_reduce sums it in one workgroup of that many wavefronts instead
     size_t red_workspace_bytes = 0;     // partial sums of the split reductions
@@ -73,7 +73,7 @@ struct ccdc_plan_s {
     int device = -1;
     int64_t *d_src_off = nullptr, *d_red_ptr = nullptr, *d_red_row = nullptr, *d_red_out = nullptr;
     int64_t *d_loc_row = nullptr, *d_pipe_row = nullptr;
-    int64_t *d_node_ptr = nullptr, *d_node_row = nullptr;       // node_row empty: null
+    int64_t *d_node_row = nullptr;      // node_row empty: null
     int32_t *d_row_files = nullptr;     // null when every packet adds m files
     int32_t *d_node_rows = nullptr;
     void *d_workspace = nullptr;
