@@ -13,8 +13,8 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libccdc.so")
 MARSHAL = os.path.join(HERE, "_marshal.so")
 SOURCES = ["ccdc.hip", "pipeline.hip", "node.hip", "noalloc.hip", "map.hip", "receive.hip", "plan.cpp"]
-# pipeline.hip has hundreds of kernel instantiations: it is compiled in pieces, two per payload algebra; receive.hip in one each
-PIECES = {"pipeline.hip": ("CCDC_PIPELINE_PART", 10), "receive.hip": ("CCDC_RECEIVE_PART", 5)}
+# pipeline.hip has hundreds of kernel instantiations: it is compiled in pieces, two per payload algebra; receive.hip and node.hip in one each
+PIECES = {"pipeline.hip": ("CCDC_PIPELINE_PART", 10), "receive.hip": ("CCDC_RECEIVE_PART", 5), "node.hip": ("CCDC_NODE_PART", 5)}
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [

@@ -487,6 +487,59 @@ int run_node_decode_reduce(const ccdc_plan_t *p, int node, const void *V, const 
     return launched();
 }
 
+}  // namespace
+
+namespace ccdc {
+
+// The calls for one algebra, at a pack width that pick_vec() gives.
+template <class A>
+int node_encode(const ccdc_plan_t *p, int vec, int node, const void *V, void *X, hipStream_t st)
+{
+    if constexpr (sizeof(typename A::elem) == 2) {
+        if (vec == 8) return run_node_encode<A, 8>(p, node, V, X, st);
+    }
+    return vec == 4 ? run_node_encode<A, 4>(p, node, V, X, st) : run_node_encode<A, 1>(p, node, V, X, st);
+}
+
+template <class A>
+int node_decode_reduce(const ccdc_plan_t *p, int vec, int node, const void *V, const void *X, void *Phi, hipStream_t st)
+{
+    if constexpr (sizeof(typename A::elem) == 2) {
+        if (vec == 8) return run_node_decode_reduce<A, 8>(p, node, V, X, Phi, st);
+    }
+    return vec == 4 ? run_node_decode_reduce<A, 4>(p, node, V, X, Phi, st) : run_node_decode_reduce<A, 1>(p, node, V, X, Phi, st);
+}
+
+// Compiled in five pieces, one for each algebra, the first with the entry points.
+#ifdef CCDC_NODE_PART
+#define CCDC_NODE(A)                                                                                 \
+    template int node_encode<A>(const ccdc_plan_t *, int, int, const void *, void *, hipStream_t); \
+    template int node_decode_reduce<A>(const ccdc_plan_t *, int, int, const void *, const void *, void *, hipStream_t)
+#define CCDC_ELSEWHERE(A)                                                                                   \
+    extern template int node_encode<A>(const ccdc_plan_t *, int, int, const void *, void *, hipStream_t); \
+    extern template int node_decode_reduce<A>(const ccdc_plan_t *, int, int, const void *, const void *, void *, hipStream_t)
+#if CCDC_NODE_PART == 0
+CCDC_NODE(SumF32);
+CCDC_ELSEWHERE(XorU32);
+CCDC_ELSEWHERE(HybF32);
+CCDC_ELSEWHERE(HybBF16);
+CCDC_ELSEWHERE(HybF16);
+#elif CCDC_NODE_PART == 1
+CCDC_NODE(XorU32);
+#elif CCDC_NODE_PART == 2
+CCDC_NODE(HybF32);
+#elif CCDC_NODE_PART == 3
+CCDC_NODE(HybBF16);
+#else
+CCDC_NODE(HybF16);
+#endif
+#endif
+
+}  // namespace ccdc
+
+#if !defined(CCDC_NODE_PART) || CCDC_NODE_PART == 0
+namespace {
+
 int node_ready(const ccdc_plan_t *plan, int node)
 {
     const int rc = ready(plan);
@@ -506,7 +559,13 @@ int ccdc_node_encode(const ccdc_plan_t *plan, int node, const void *V, void *X, 
     if (rc != CCDC_OK) return rc;
     if ((rc = pick_vec(plan, &vec, V, (const void *)X)) != CCDC_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
-    CCDC_DISPATCH(plan, vec, (run_node_encode<A, VEC>(plan, node, V, X, st)));
+    switch (plan->mode) {
+    case CCDC_F32_SUM: return node_encode<SumF32>(plan, vec, node, V, X, st);
+    case CCDC_F32_SUM_XOR: return node_encode<HybF32>(plan, vec, node, V, X, st);
+    case CCDC_BF16_SUM_XOR: return node_encode<HybBF16>(plan, vec, node, V, X, st);
+    case CCDC_F16_SUM_XOR: return node_encode<HybF16>(plan, vec, node, V, X, st);
+    default: return node_encode<XorU32>(plan, vec, node, V, X, st);
+    }
 }
 
 int ccdc_node_decode_reduce(const ccdc_plan_t *plan, int node, const void *V, const void *X, void *Phi, void *stream)
@@ -516,7 +575,14 @@ int ccdc_node_decode_reduce(const ccdc_plan_t *plan, int node, const void *V, co
     if ((rc = pick_vec(plan, &vec, V, X, (const void *)Phi)) != CCDC_OK) return rc;
     if (plan->node_waves > 0) return receive_coded(plan, node, V, X, Phi, stream);
     hipStream_t st = (hipStream_t)stream;
-    CCDC_DISPATCH(plan, vec, (run_node_decode_reduce<A, VEC>(plan, node, V, X, Phi, st)));
+    switch (plan->mode) {
+    case CCDC_F32_SUM: return node_decode_reduce<SumF32>(plan, vec, node, V, X, Phi, st);
+    case CCDC_F32_SUM_XOR: return node_decode_reduce<HybF32>(plan, vec, node, V, X, Phi, st);
+    case CCDC_BF16_SUM_XOR: return node_decode_reduce<HybBF16>(plan, vec, node, V, X, Phi, st);
+    case CCDC_F16_SUM_XOR: return node_decode_reduce<HybF16>(plan, vec, node, V, X, Phi, st);
+    default: return node_decode_reduce<XorU32>(plan, vec, node, V, X, Phi, st);
+    }
 }
 
 }  // extern "C"
+#endif
