@@ -35,29 +35,31 @@ __device__ __forceinline__ uint32_t in_runs(uint32_t span)
 // Sec. IV-B pre-combining.  One work item = one pack of one packet Vbar[u][b]:
 // it adds the same pack of the files of the served batch (m of them, or
 // row_files[row] when batches differ in size).
-template <class A, int VEC, bool KEPT, bool TOGETHER>
+template <class A, int VEC, bool KEPT, bool TOGETHER, bool ANY>
 __global__ __launch_bounds__(kBlock) void k_combine(const typename A::elem *__restrict__ V,
                                                     typename A::elem *__restrict__ Vbar,
                                                     const int64_t *__restrict__ src_off,
-                                                    const int32_t *__restrict__ row_files, uint32_t Wv, int m,
+                                                    const int32_t *__restrict__ row_files, uint32_t Wv, uint32_t W, int m,
                                                     int64_t file_stride, uint32_t items, bool past)
 {
+    using E = typename A::elem;
     using O = Ops<A, VEC>;
     using P = typename O::P;
     constexpr bool LARGE = !KEPT && VEC > 1;          // see in_runs()
     const uint32_t idx = in_runs<LARGE>(kCombineSpan) * kBlock + threadIdx.x;
     if (idx >= items) return;
-    const uint32_t row = idx / Wv, e = idx - row * Wv;
-    const typename A::elem *src = V + src_off[row] + (int64_t)e * VEC;
+    const uint32_t row = idx / Wv, e = column<ANY, VEC>(idx - row * Wv, W);
+    const E *src = V + src_off[row] + e;
+    E *to = Vbar + (size_t)row * W + e;
     const int files = row_files ? row_files[row] : m;
-    const P first = load_pack<KEPT, P>(src);
+    const P first = load_at<KEPT, ANY, P, E>(src);
     if (files == 1) {                                 // not a sum: the packet is the file's values as they are
-        reinterpret_cast<P *>(Vbar)[idx] = first;
+        store_at<false, ANY, P, E>(to, first);
         return;
     }
-    const P sum = O::narrow(sum_files<O, KEPT, TOGETHER>(first, src, files, file_stride));
-    if (LARGE && past) store_stream(reinterpret_cast<P *>(Vbar) + idx, sum);
-    else reinterpret_cast<P *>(Vbar)[idx] = sum;
+    const P sum = O::narrow(sum_files<O, KEPT, TOGETHER, ANY>(first, src, files, file_stride));
+    if (LARGE && past) store_at<true, ANY, P, E>(to, sum);
+    else store_at<false, ANY, P, E>(to, sum);
 }
 
 // Pre-combining for short packets and long batches (few packs per packet, many
@@ -106,26 +108,27 @@ __global__ __launch_bounds__(64) void k_combine_wave(const typename A::elem *__r
 // Sec. IV-B coded packet.  One work item = one pack of X[u][a]: the sum over
 // the other members b of segment segment_rank(a,b) of Vbar[u][b] at the same
 // in-segment position; positions past the end of a short segment add nothing.
-template <class A, int VEC>
+template <class A, int VEC, bool ANY>
 __global__ __launch_bounds__(kBlock) void k_encode(const typename A::elem *__restrict__ Vbar,
                                                    typename A::elem *__restrict__ X, int r1, uint32_t Lv,
-                                                   uint32_t Wv, uint32_t items)
+                                                   uint32_t ell, uint32_t W, uint32_t items)
 {
+    using E = typename A::elem;
     using O = Ops<A, VEC>;
     using P = typename O::P;
     const uint32_t idx = blockIdx.x * kBlock + threadIdx.x;
     if (idx >= items) return;
-    const uint32_t ua = idx / Lv, x = idx - ua * Lv;
+    const uint32_t ua = idx / Lv, x = column<ANY, VEC>(idx - ua * Lv, ell);
     const uint32_t u = ua / r1;
     const int a = (int)(ua - u * r1);
-    const P *rows = reinterpret_cast<const P *>(Vbar) + (size_t)u * r1 * Wv;
+    const E *rows = Vbar + (size_t)u * r1 * W;
     P acc = O::zero();
     for (int b = 0; b < r1; b++) {
         if (b == a) continue;
-        const uint32_t pos = segment_rank(a, b) * Lv + x;
-        if (pos < Wv) acc = O::code(acc, rows[(size_t)b * Wv + pos]);
+        const uint32_t pos = segment_rank(a, b) * ell + x;
+        if (pos < W) acc = O::code(acc, packet_pack<O, true, false, ANY>(rows + (size_t)b * W, pos, W, 1, 0));
     }
-    reinterpret_cast<P *>(X)[idx] = acc;
+    store_at<false, ANY, P, E>(X + (size_t)ua * ell + x, acc);
 }
 
 // ------------------------------------------------------------------- decode
@@ -163,38 +166,38 @@ __global__ __launch_bounds__(kBlock) void k_decode(const typename A::elem *__res
 // it, one for each receiver.  The r packs of Vbar it holds are read once and used for r-1 receivers
 // each, where k_decode reads X r times and Vbar r-1 times (from cache) and is bound by that.  R1 = r+1
 // at compile time (k_decode serves r > 5).  12 nodes, r = 3, T = 6000, f16: 15.3 -> 7.9 us, 55 MB.
-template <class A, int VEC, int R1>
+template <class A, int VEC, int R1, bool ANY>
 __global__ __launch_bounds__(kBlock) void k_decode_sender(const typename A::elem *__restrict__ X,
                                                           const typename A::elem *__restrict__ Vbar,
-                                                          typename A::elem *__restrict__ D, uint32_t Lv, uint32_t Wv,
-                                                          uint32_t items)
+                                                          typename A::elem *__restrict__ D, uint32_t Lv, uint32_t ell,
+                                                          uint32_t W, uint32_t items)
 {
+    using E = typename A::elem;
     using O = Ops<A, VEC>;
     using P = typename O::P;
     const uint32_t idx = blockIdx.x * kBlock + threadIdx.x;
     if (idx >= items) return;
-    const uint32_t ua = idx / Lv, x = idx - ua * Lv;
+    const uint32_t ua = idx / Lv, x = column<ANY, VEC>(idx - ua * Lv, ell);
     const uint32_t u = ua / R1;
     const int a = (int)(ua - u * R1);
-    const P *rows = reinterpret_cast<const P *>(Vbar) + (size_t)u * R1 * Wv;
-    P *out = reinterpret_cast<P *>(D) + (size_t)u * R1 * Wv;
-    const P coded = reinterpret_cast<const P *>(X)[idx];
+    const E *rows = Vbar + (size_t)u * R1 * W;
+    E *out = D + (size_t)u * R1 * W;
+    const P coded = load_at<true, ANY, P, E>(X + (size_t)ua * ell + x);
     P side[R1];
 #pragma unroll
     for (int b = 0; b < R1; b++) {
-        const uint32_t pos = segment_rank(a, b) * Lv + x;
+        const uint32_t pos = segment_rank(a, b) * ell + x;
         side[b] = O::zero();
-        if (b != a && pos < Wv) side[b] = rows[(size_t)b * Wv + pos];
+        if (b != a && pos < W) side[b] = packet_pack<O, true, false, ANY>(rows + (size_t)b * W, pos, W, 1, 0);
     }
 #pragma unroll
     for (int b = 0; b < R1; b++) {
-        const uint32_t pos = segment_rank(a, b) * Lv + x;
-        if (b == a || pos >= Wv) continue;
+        if (b == a) continue;
         P d = coded;
 #pragma unroll
         for (int b2 = 0; b2 < R1; b2++)
             if (b2 != b && b2 != a) d = O::uncode(d, side[b2]);
-        out[(size_t)b * Wv + pos] = d;
+        store_in_row<O, false, ANY>(out + (size_t)b * W, segment_rank(a, b) * ell + x, W, d);
     }
 }
 
@@ -207,50 +210,46 @@ __global__ __launch_bounds__(kBlock) void k_decode_sender(const typename A::elem
 // the any-r fallback that re-reads them (cache hits) instead.
 // MULTI: several files a batch, where their packets are asked for together (a kernel of their own: their sums in the making take
 // registers that the other would pay for with fewer wavefronts); elsewhere the one kernel looks at m.
-template <class A, int VEC, int R1, bool KEPT, bool MULTI>
+template <class A, int VEC, int R1, bool KEPT, bool MULTI, bool ANY>
 __global__ __launch_bounds__(kBlock) void k_shuffle_fused(const typename A::elem *__restrict__ V,
                                                           typename A::elem *__restrict__ X,
                                                           typename A::elem *__restrict__ D,
                                                           const int64_t *__restrict__ src_off, int r1_rt,
-                                                          uint32_t Lv, uint32_t Wv, int m, int64_t file_stride,
+                                                          uint32_t Lv, uint32_t ell, uint32_t W, int m, int64_t file_stride,
                                                           uint32_t items, uint32_t span)
 {
+    using E = typename A::elem;
     using O = Ops<A, VEC>;
     using P = typename O::P;
     const int r1 = R1 > 0 ? R1 : r1_rt;
     const uint32_t idx = in_runs<!KEPT && (VEC > 1)>(span) * kBlock + threadIdx.x;
     if (idx >= items) return;
-    const uint32_t ua = idx / Lv, x = idx - ua * Lv;
+    const uint32_t ua = idx / Lv, x = column<ANY, VEC>(idx - ua * Lv, ell);
     const uint32_t u = ua / r1;
     const int a = (int)(ua - u * r1);
     const int64_t *src = src_off + (size_t)u * r1;
+    E *to = X + (size_t)ua * ell + x, *Drows = D + (size_t)u * r1 * W;
 
     auto combined = [&](int b) -> P {       // pack of Vbar[u][b] that sender a carries
-        const uint32_t pos = segment_rank(a, b) * Lv + x;
-        if (pos >= Wv) return O::zero();
-        const typename A::elem *s = V + src[b] + (int64_t)pos * VEC;
-        const P first = load_pack<KEPT, P>(s);
-        if (m == 1) return first;                     // a one-file batch is sent as it is
-        return O::narrow(sum_files<O, KEPT, files_together<O>()>(first, s, m, file_stride));
+        return packet_pack<O, KEPT, files_together<O, ANY>(), ANY>(V + src[b], segment_rank(a, b) * ell + x, W, m, file_stride);
     };
 
-    P *Drows = reinterpret_cast<P *>(D) + (size_t)u * r1 * Wv;
     if constexpr (R1 > 0 && packets_together<O, R1 - 1>()) {
         P v[R1 - 1];                                  // of the members other than a
-        const typename A::elem *at[R1 - 1];
+        const E *at[R1 - 1];
         bool there[R1 - 1];
 #pragma unroll
         for (int k = 0; k < R1 - 1; k++) {
             const int b = k + (k >= a ? 1 : 0);
-            const uint32_t pos = segment_rank(a, b) * Lv + x;
-            there[k] = pos < Wv;
-            at[k] = V + src[b] + (int64_t)(there[k] ? pos : 0) * VEC;
+            const uint32_t pos = segment_rank(a, b) * ell + x;
+            there[k] = pos < W;
+            at[k] = V + src[b] + (there[k] ? pos : 0);
         }
         sum_packets<O, KEPT>(v, at, there, MULTI ? m : 1, file_stride);
         P coded = O::zero();
 #pragma unroll
         for (int k = 0; k < R1 - 1; k++) coded = O::code(coded, v[k]);
-        store_stream(reinterpret_cast<P *>(X) + idx, coded);
+        store_at<true, ANY, P, E>(to, coded);
 #pragma unroll
         for (int k = 0; k < R1 - 1; k++) {
             if (!there[k]) continue;
@@ -259,7 +258,7 @@ __global__ __launch_bounds__(kBlock) void k_shuffle_fused(const typename A::elem
 #pragma unroll
             for (int k2 = 0; k2 < R1 - 1; k2++)
                 if (k2 != k) acc = O::uncode(acc, v[k2]);
-            store_stream(Drows + (size_t)b * Wv + segment_rank(a, b) * Lv + x, acc);
+            store_stream(Drows + (size_t)b * W + segment_rank(a, b) * ell + x, acc);
         }
     } else if constexpr (R1 > 0) {
         P v[R1];
@@ -270,31 +269,27 @@ __global__ __launch_bounds__(kBlock) void k_shuffle_fused(const typename A::elem
 #pragma unroll
         for (int b = 0; b < R1; b++)
             if (b != a) coded = O::code(coded, v[b]);
-        store_stream(reinterpret_cast<P *>(X) + idx, coded);
+        store_at<true, ANY, P, E>(to, coded);
 #pragma unroll
         for (int b = 0; b < R1; b++) {
             if (b == a) continue;
-            const uint32_t pos = segment_rank(a, b) * Lv + x;
-            if (pos >= Wv) continue;
             P acc = coded;
 #pragma unroll
             for (int b2 = 0; b2 < R1; b2++)
                 if (b2 != a && b2 != b) acc = O::uncode(acc, v[b2]);
-            store_stream(Drows + (size_t)b * Wv + pos, acc);
+            store_in_row<O, !ANY, ANY>(Drows + (size_t)b * W, segment_rank(a, b) * ell + x, W, acc);
         }
     } else {
         P coded = O::zero();
         for (int b = 0; b < r1; b++)
             if (b != a) coded = O::code(coded, combined(b));
-        store_stream(reinterpret_cast<P *>(X) + idx, coded);
+        store_at<true, ANY, P, E>(to, coded);
         for (int b = 0; b < r1; b++) {
             if (b == a) continue;
-            const uint32_t pos = segment_rank(a, b) * Lv + x;
-            if (pos >= Wv) continue;
             P acc = coded;
             for (int b2 = 0; b2 < r1; b2++)
                 if (b2 != a && b2 != b) acc = O::uncode(acc, combined(b2));
-            store_stream(Drows + (size_t)b * Wv + pos, acc);
+            store_in_row<O, true, ANY>(Drows + (size_t)b * W, segment_rank(a, b) * ell + x, W, acc);
         }
     }
 }
@@ -305,16 +300,17 @@ __global__ __launch_bounds__(kBlock) void k_shuffle_fused(const typename A::elem
 // the node stores), some in D (packets it decoded).  The list is cut into
 // `split` chunks; work item = (o, chunk, pack).  With split > 1 the chunk sums
 // go, not yet narrowed, to the workspace and k_reduce_final adds them in its fixed order.
-template <class A, int VEC, bool KEPT>
+template <class A, int VEC, bool KEPT, bool ANY>
 __global__ __launch_bounds__(kBlock) void k_reduce_rows(const typename A::elem *__restrict__ V,
                                                         const typename A::elem *__restrict__ D,
                                                         typename A::elem *__restrict__ out,
                                                         typename A::acc *__restrict__ part,
                                                         const int64_t *__restrict__ red_ptr,
                                                         const int64_t *__restrict__ red_row,
-                                                        const int64_t *__restrict__ red_out, uint32_t Wv,
+                                                        const int64_t *__restrict__ red_out, uint32_t Wv, uint32_t W,
                                                         uint32_t tiles, int split, int64_t chunk_stride)
 {
+    using E = typename A::elem;
     using O = Ops<A, VEC>;
     using P = typename O::P;
     constexpr bool LARGE = !KEPT && VEC > 1;          // see in_runs()
@@ -323,16 +319,16 @@ __global__ __launch_bounds__(kBlock) void k_reduce_rows(const typename A::elem *
     const uint32_t oc = block / tiles;
     const uint32_t o = oc / split;
     const int s = (int)(oc - o * split);
-    const uint32_t e = tile * kBlock + threadIdx.x;
-    if (e >= Wv) return;
+    const uint32_t pack = tile * kBlock + threadIdx.x;
+    if (pack >= Wv) return;
+    const uint32_t e = column<ANY, VEC>(pack, W);
     const int64_t first = red_ptr[o], n = red_ptr[o + 1] - first;
     const int64_t lo = first + n * s / split, hi = first + n * (s + 1) / split;
     typename O::Q acc = O::azero();
     int64_t i = lo;
     auto row_pack = [&](int64_t at) {
         const int64_t row = red_row[at];
-        const typename A::elem *base = (row & 1) ? D : V;
-        return load_pack<KEPT, P>(reinterpret_cast<const P *>(base + (row >> 1)) + e);
+        return load_at<KEPT, ANY, P, E>(((row & 1) ? D : V) + (row >> 1) + e);
     };
     // One-element packs are few bytes in flight: eight rows at a time.  16 lists of 22 rows and more 0.93 of the time with four (12
     // nodes, r = 5, T = 27763 bf16 153 -> 110 us); wide packs 0.99 to 1.08.
@@ -347,9 +343,8 @@ __global__ __launch_bounds__(kBlock) void k_reduce_rows(const typename A::elem *
     }
 #pragma unroll 4
     for (; i < hi; i++) acc = O::accum(acc, row_pack(i));
-    if (split > 1) reinterpret_cast<typename O::Q *>(part + (int64_t)s * chunk_stride + red_out[o])[e] = acc;
-    else if constexpr (LARGE) store_stream(reinterpret_cast<P *>(out + red_out[o]) + e, O::narrow(acc));
-    else reinterpret_cast<P *>(out + red_out[o])[e] = O::narrow(acc);
+    if (split > 1) store_at<false, ANY, typename O::Q, typename A::acc>(part + (int64_t)s * chunk_stride + red_out[o] + e, acc);
+    else store_at<LARGE, ANY, P, E>(out + red_out[o] + e, O::narrow(acc));
 }
 
 // The same in one launch: the wavefronts of a workgroup share the row list of 64 packs of an output and add up in LDS.
@@ -357,11 +352,11 @@ __global__ __launch_bounds__(kBlock) void k_reduce_rows(const typename A::elem *
 // it reads back were 2.5 to 5 us of its time.  Which plans: plan_groups() in plan.cpp.  14 nodes, r = 1, T = 952 u32 8.0 -> 5.6 us,
 // 12 nodes, r = 3, two files, T = 6000 f16 (40 MB) 17.3 -> 11.1 to 12, uncoded, 13 nodes, T = 48768 f32 17.8 -> 11; with one stage
 // of rows in flight 3 % slower over 282 plans.
-template <class A, int VEC, bool KEPT>
+template <class A, int VEC, bool KEPT, bool ANY>
 __global__ __launch_bounds__(kGroupLanes *kGroupMaxWaves) void k_reduce_group(
     const typename A::elem *__restrict__ V, const typename A::elem *__restrict__ D, typename A::elem *__restrict__ out,
     const int64_t *__restrict__ red_ptr, const int64_t *__restrict__ red_row, const int64_t *__restrict__ red_out,
-    uint32_t Wv, uint32_t tiles)
+    uint32_t Wv, uint32_t W, uint32_t tiles)
 {
     using E = typename A::elem;
     using O = Ops<A, VEC>;
@@ -370,12 +365,12 @@ __global__ __launch_bounds__(kGroupLanes *kGroupMaxWaves) void k_reduce_group(
     extern __shared__ __align__(16) unsigned char smem[];
     const uint32_t o = blockIdx.x / tiles, tile = blockIdx.x - o * tiles;
     const uint32_t lane = threadIdx.x % kGroupLanes, wave = wave_uniform(threadIdx.x / kGroupLanes), waves = blockDim.x / kGroupLanes;
-    const uint32_t e = tile * kGroupLanes + lane;
+    const uint32_t pack = tile * kGroupLanes + lane;
     const int64_t first = red_ptr[o], n = red_ptr[o + 1] - first;
     const int64_t lo = first + n * wave / waves, hi = first + n * (wave + 1) / waves;
     typename O::Q acc = O::azero();
-    if (e < Wv && hi > lo) {
-        const uint32_t offset = e * (uint32_t)sizeof(P);
+    if (pack < Wv && hi > lo) {
+        const uint32_t offset = column<ANY, VEC>(pack, W) * (uint32_t)sizeof(E);
         struct Stage {
             P v[AHEAD];
         };
@@ -387,7 +382,7 @@ __global__ __launch_bounds__(kGroupLanes *kGroupMaxWaves) void k_reduce_group(
             for (int t = 0; t < AHEAD; t++) {
                 const int64_t row = red_row[next + t < hi ? next + t : hi - 1];
                 const E *base = (row & 1) ? D : V;
-                s.v[t] = load_pack<KEPT, P>(reinterpret_cast<const char *>(base + (row >> 1)) + lane_offset(offset));
+                s.v[t] = load_at<KEPT, ANY, P, E>(reinterpret_cast<const char *>(base + (row >> 1)) + lane_offset(offset));
             }
             next += AHEAD;
         };
@@ -417,8 +412,8 @@ __global__ __launch_bounds__(kGroupLanes *kGroupMaxWaves) void k_reduce_group(
         }
     }
     add_wavefronts<A, VEC>(smem, acc, waves, [&](uint32_t i, typename A::acc v) {
-        const uint32_t at = tile * kGroupLanes * VEC + i;
-        if (at < Wv * VEC) out[red_out[o] + at] = A::narrow(v);
+        const uint32_t from = tile * kGroupLanes + i / VEC;
+        if (from < Wv) out[red_out[o] + column<ANY, VEC>(from, W) + i % VEC] = A::narrow(v);
     });
 }
 
@@ -471,12 +466,12 @@ int to_device(const std::vector<T> &h, T **d)
     return CCDC_OK;
 }
 
-// ---- typed launchers: A = algebra, VEC = pack width
-template <class A, int VEC>
+// ---- typed launchers: A = algebra, VEC = pack width, ANY = packs at any element
+template <class A, int VEC, bool ANY>
 int run_combine(const ccdc_plan_t *p, const void *V, void *Vbar, hipStream_t st)
 {
     using E = typename A::elem;
-    const uint32_t Wv = (uint32_t)(p->W / VEC);
+    const uint32_t Wv = cdiv(p->W, VEC), W = (uint32_t)p->W;
     const uint64_t items = (uint64_t)p->nrows * Wv;
     if (items == 0) return CCDC_OK;
     if (!fits_launch(items)) return CCDC_ESIZE;
@@ -487,7 +482,7 @@ int run_combine(const ccdc_plan_t *p, const void *V, void *Vbar, hipStream_t st)
 #ifndef CCDC_COMBINE_WAVE_MIN_FILES
 #define CCDC_COMBINE_WAVE_MIN_FILES 8
 #endif
-    if constexpr (!A::fixed_order) {
+    if constexpr (!A::fixed_order && !ANY) {
         if (Wv <= 16 && p->m >= CCDC_COMBINE_WAVE_MIN_FILES && !p->d_row_files) {
             int seg = 1;
             while ((uint32_t)seg < Wv) seg <<= 1;
@@ -502,64 +497,67 @@ int run_combine(const ccdc_plan_t *p, const void *V, void *Vbar, hipStream_t st)
     const int files = p->compression ? p->batch_first[1] : p->m;        // of a batch, uncoded plans: of the largest
     const bool past = moved_bytes(p, packets) >= kPastStoreBytes;
     by_reads<false>(kept, [&](auto k) {
-        by_files<Ops<A, VEC>>(files > 2, [&](auto together) {
-            k_combine<A, VEC, decltype(k)::value, decltype(together)::value><<<cdiv(items, kBlock), kBlock, 0, st>>>(
-                (const E *)V, (E *)Vbar, p->d_src_off, p->d_row_files, Wv, p->m, (int64_t)p->Q * p->T, (uint32_t)items, past);
+        by_files<Ops<A, VEC>, ANY>(files > 2, [&](auto together) {
+            k_combine<A, VEC, decltype(k)::value, decltype(together)::value, ANY><<<cdiv(items, kBlock), kBlock, 0, st>>>(
+                (const E *)V, (E *)Vbar, p->d_src_off, p->d_row_files, Wv, W, p->m, (int64_t)p->Q * p->T, (uint32_t)items, past);
         });
     });
     return launched();
 }
 
-template <class A, int VEC>
+template <class A, int VEC, bool ANY>
 int run_encode(const ccdc_plan_t *p, const void *Vbar, void *X, hipStream_t st)
 {
     using E = typename A::elem;
-    const uint32_t Wv = (uint32_t)(p->W / VEC), Lv = (uint32_t)(p->ell / VEC);
+    const uint32_t Lv = cdiv(p->ell, VEC);
     const uint64_t items = (uint64_t)p->nround * (p->r + 1) * Lv;
     if (!fits_launch(items)) return CCDC_ESIZE;
-    k_encode<A, VEC><<<cdiv(items, kBlock), kBlock, 0, st>>>((const E *)Vbar, (E *)X, p->r + 1, Lv, Wv,
-                                                              (uint32_t)items);
+    k_encode<A, VEC, ANY><<<cdiv(items, kBlock), kBlock, 0, st>>>((const E *)Vbar, (E *)X, p->r + 1, Lv, (uint32_t)p->ell,
+                                                                   (uint32_t)p->W, (uint32_t)items);
     return launched();
 }
 
-template <class A, int VEC>
+template <class A, int VEC, bool ANY>
 int run_decode(const ccdc_plan_t *p, const void *X, const void *Vbar, void *D, hipStream_t st)
 {
     using E = typename A::elem;
-    const uint32_t Wv = (uint32_t)(p->W / VEC), Lv = (uint32_t)(p->ell / VEC);
-    const uint64_t items = (uint64_t)p->nround * (p->r + 1) * Wv;
-    if (!fits_launch(items)) return CCDC_ESIZE;
+    const uint32_t Lv = cdiv(p->ell, VEC), ell = (uint32_t)p->ell, W = (uint32_t)p->W;
     // By sender where the packs of the padded segments can be numbered too (packets of fewer than four
     // elements have more of those than of their own); k_decode takes whatever the packets' packs allow.
     const uint64_t packs = (uint64_t)p->nround * (p->r + 1) * Lv;
     const uint32_t by_sender = (uint32_t)packs, blocks = cdiv(packs, kBlock);
     const E *x = (const E *)X, *v = (const E *)Vbar;
     switch (fits_launch(packs) ? p->r + 1 : 0) {
-    case 2: k_decode_sender<A, VEC, 2><<<blocks, kBlock, 0, st>>>(x, v, (E *)D, Lv, Wv, by_sender); break;
-    case 3: k_decode_sender<A, VEC, 3><<<blocks, kBlock, 0, st>>>(x, v, (E *)D, Lv, Wv, by_sender); break;
-    case 4: k_decode_sender<A, VEC, 4><<<blocks, kBlock, 0, st>>>(x, v, (E *)D, Lv, Wv, by_sender); break;
-    case 5: k_decode_sender<A, VEC, 5><<<blocks, kBlock, 0, st>>>(x, v, (E *)D, Lv, Wv, by_sender); break;
-    case 6: k_decode_sender<A, VEC, 6><<<blocks, kBlock, 0, st>>>(x, v, (E *)D, Lv, Wv, by_sender); break;
-    default:
-        k_decode<A, VEC><<<cdiv(items, kBlock), kBlock, 0, st>>>(x, v, (E *)D, p->r + 1, Lv, Wv, (uint32_t)items);
+    case 2: k_decode_sender<A, VEC, 2, ANY><<<blocks, kBlock, 0, st>>>(x, v, (E *)D, Lv, ell, W, by_sender); break;
+    case 3: k_decode_sender<A, VEC, 3, ANY><<<blocks, kBlock, 0, st>>>(x, v, (E *)D, Lv, ell, W, by_sender); break;
+    case 4: k_decode_sender<A, VEC, 4, ANY><<<blocks, kBlock, 0, st>>>(x, v, (E *)D, Lv, ell, W, by_sender); break;
+    case 5: k_decode_sender<A, VEC, 5, ANY><<<blocks, kBlock, 0, st>>>(x, v, (E *)D, Lv, ell, W, by_sender); break;
+    case 6: k_decode_sender<A, VEC, 6, ANY><<<blocks, kBlock, 0, st>>>(x, v, (E *)D, Lv, ell, W, by_sender); break;
+    default: {
+        constexpr int PACK = ANY ? 1 : VEC;              // k_decode walks whole packets: their packs are not moved back
+        const uint32_t Wv = (uint32_t)(p->W / PACK), Lw = (uint32_t)(p->ell / PACK);
+        const uint64_t items = (uint64_t)p->nround * (p->r + 1) * Wv;
+        if (!fits_launch(items)) return CCDC_ESIZE;
+        k_decode<A, PACK><<<cdiv(items, kBlock), kBlock, 0, st>>>(x, v, (E *)D, p->r + 1, Lw, Wv, (uint32_t)items);
         break;
+    }
     }
     return launched();
 }
 
-template <class A, int VEC, int R1>
+template <class A, int VEC, bool ANY, int R1>
 void launch_shuffle(const ccdc_plan_t *p, const void *V, void *X, void *D, hipStream_t st)
 {
     using E = typename A::elem;
-    const uint32_t Wv = (uint32_t)(p->W / VEC), Lv = (uint32_t)(p->ell / VEC);
+    const uint32_t Lv = cdiv(p->ell, VEC);
     const uint64_t items = (uint64_t)p->nround * (p->r + 1) * Lv;
     const double bytes = moved_bytes(p, (double)p->nrows * (p->W + p->ell));                         // V, X and D
     const bool kept = bytes <= kKeptStageBytes;
     const uint32_t span = bytes >= kShuffleRunsBytes ? kShuffleSpan : kXcds;
     auto launch = [&](auto multi) {
         by_reads<VEC == 1>(kept, [&](auto k) {
-            k_shuffle_fused<A, VEC, R1, decltype(k)::value, decltype(multi)::value><<<cdiv(items, kBlock), kBlock, 0, st>>>(
-                (const E *)V, (E *)X, (E *)D, p->d_src_off, p->r + 1, Lv, Wv, p->m, (int64_t)p->Q * p->T, (uint32_t)items, span);
+            k_shuffle_fused<A, VEC, R1, decltype(k)::value, decltype(multi)::value, ANY><<<cdiv(items, kBlock), kBlock, 0, st>>>(
+                (const E *)V, (E *)X, (E *)D, p->d_src_off, p->r + 1, Lv, (uint32_t)p->ell, (uint32_t)p->W, p->m, (int64_t)p->Q * p->T, (uint32_t)items, span);
         });
     };
     if constexpr (R1 > 0 && packets_together<Ops<A, VEC>, R1 - 1>()) {
@@ -568,69 +566,73 @@ void launch_shuffle(const ccdc_plan_t *p, const void *V, void *X, void *D, hipSt
     launch(std::true_type());
 }
 
-template <class A, int VEC>
+template <class A, int VEC, bool ANY>
 int run_shuffle(const ccdc_plan_t *p, const void *V, void *X, void *D, hipStream_t st)
 {
-    if (!fits_launch((uint64_t)p->nround * (p->r + 1) * (uint64_t)(p->ell / VEC))) return CCDC_ESIZE;
+    if (!fits_launch((uint64_t)p->nround * (p->r + 1) * (uint64_t)cdiv(p->ell, VEC))) return CCDC_ESIZE;
     switch (p->r + 1) {
-    case 2: launch_shuffle<A, VEC, 2>(p, V, X, D, st); break;
-    case 3: launch_shuffle<A, VEC, 3>(p, V, X, D, st); break;
-    case 4: launch_shuffle<A, VEC, 4>(p, V, X, D, st); break;
-    case 5: launch_shuffle<A, VEC, 5>(p, V, X, D, st); break;
-    case 6: launch_shuffle<A, VEC, 6>(p, V, X, D, st); break;
-    case 7: launch_shuffle<A, VEC, 7>(p, V, X, D, st); break;
-    case 8: launch_shuffle<A, VEC, 8>(p, V, X, D, st); break;
-    default: launch_shuffle<A, VEC, 0>(p, V, X, D, st); break;
+    case 2: launch_shuffle<A, VEC, ANY, 2>(p, V, X, D, st); break;
+    case 3: launch_shuffle<A, VEC, ANY, 3>(p, V, X, D, st); break;
+    case 4: launch_shuffle<A, VEC, ANY, 4>(p, V, X, D, st); break;
+    case 5: launch_shuffle<A, VEC, ANY, 5>(p, V, X, D, st); break;
+    case 6: launch_shuffle<A, VEC, ANY, 6>(p, V, X, D, st); break;
+    case 7: launch_shuffle<A, VEC, ANY, 7>(p, V, X, D, st); break;
+    case 8: launch_shuffle<A, VEC, ANY, 8>(p, V, X, D, st); break;
+    default: launch_shuffle<A, VEC, ANY, 0>(p, V, X, D, st); break;
     }
     return launched();
 }
 
+// Whether the fused shuffle takes packs at any element: one-element packs of 16 bits always gain (70 jobs on 8 nodes, r = 3, T = 105661 bf16 399 -> 297
+// us), those of 32 bits with r <= 2 on large inputs (10 jobs on 5 nodes, r = 2, T = 400097 u32 95 -> 79), else they are faster (4 nodes,
+// r = 3, T = 4015094 f32 25.0 and 27.4, 6 nodes, r = 5, T = 1690898 u32 73 and 79).
+bool shuffle_any(const ccdc_plan_t *p)
+{
+    return makes_lanes(p, p->nrows, p->ell, 4) && (elem_bytes(p->mode) == 2 || (p->r <= 2 && moved_bytes(p, 0) >= kAnyListBytes));
+}
+
 // SHARED: rows begin anywhere in a cache line, see kKeptPacketBytes.
-template <class A, int VEC, bool SHARED = VEC == 1>
+template <class A, int VEC, bool ANY, bool SHARED = VEC == 1>
 void reduce_in_groups(const ccdc_plan_t *p, const void *V, const void *D, void *Phi, bool kept, hipStream_t st)
 {
     using E = typename A::elem;
     // the widest packs that make enough workgroups, else those of four bytes
     if constexpr (VEC > 1 && VEC * sizeof(E) > 4) {
-        if (p->nout * cdiv((uint64_t)(p->W / VEC), kGroupLanes) < kGroupsWanted)
-            return reduce_in_groups<A, VEC / 2, SHARED>(p, V, D, Phi, kept, st);
+        if (p->nout * cdiv(cdiv(p->W, VEC), kGroupLanes) < kGroupsWanted)
+            return reduce_in_groups<A, VEC / 2, ANY, SHARED>(p, V, D, Phi, kept, st);
     }
-    const uint32_t Wv = (uint32_t)(p->W / VEC), tiles = cdiv(Wv, kGroupLanes), threads = kGroupLanes * p->red_waves;
+    const uint32_t Wv = cdiv(p->W, VEC), tiles = cdiv(Wv, kGroupLanes), threads = kGroupLanes * p->red_waves;
     by_reads<SHARED>(kept, [&](auto k) {
-        k_reduce_group<A, VEC, decltype(k)::value><<<(uint32_t)p->nout * tiles, threads, threads * VEC * 4, st>>>(
-            (const E *)V, (const E *)D, (E *)Phi, p->d_red_ptr, p->d_red_row, p->d_red_out, Wv, tiles);
+        k_reduce_group<A, VEC, decltype(k)::value, ANY><<<(uint32_t)p->nout * tiles, threads, threads * VEC * 4, st>>>(
+            (const E *)V, (const E *)D, (E *)Phi, p->d_red_ptr, p->d_red_row, p->d_red_out, Wv, (uint32_t)p->W, tiles);
     });
 }
 
-template <class A, int VEC>
+template <class A, int VEC, bool ANY>
 int run_reduce(const ccdc_plan_t *p, const void *V, const void *D, void *Phi, hipStream_t st)
 {
     using E = typename A::elem;
-    const uint32_t Wv = (uint32_t)(p->W / VEC);
+    const uint32_t Wv = cdiv(p->W, VEC);
     const uint32_t tiles = cdiv(Wv, kBlock);
     const int split = p->red_split;
     const uint64_t blocks = (uint64_t)p->nout * split * tiles;
     const int64_t chunk_stride = (int64_t)p->J * p->Q * p->T;
-    if (!fits_launch(blocks) || !fits_launch((uint64_t)chunk_stride / VEC)) return CCDC_ESIZE;
+    if (!fits_launch(blocks) || !fits_launch((uint64_t)chunk_stride / (ANY ? 1 : VEC))) return CCDC_ESIZE;
     using Acc = typename A::acc;
     const bool kept = moved_bytes(p, (double)p->nrows * p->W + (double)chunk_stride) <= kKeptStageBytes;        // V, D, Phi
     if (p->red_waves > 0) {
-        reduce_in_groups<A, VEC>(p, V, D, Phi, kept, st);
+        reduce_in_groups<A, VEC, ANY>(p, V, D, Phi, kept, st);
         return launched();
     }
     WorkspaceOrder order(p, st, split > 1);
     by_reads<VEC == 1>(kept, [&](auto k) {
-        k_reduce_rows<A, VEC, decltype(k)::value><<<(uint32_t)blocks, kBlock, 0, st>>>(
-            (const E *)V, (const E *)D, (E *)Phi, (Acc *)p->d_workspace, p->d_red_ptr, p->d_red_row, p->d_red_out, Wv, tiles,
-            split, chunk_stride);
+        k_reduce_rows<A, VEC, decltype(k)::value, ANY><<<(uint32_t)blocks, kBlock, 0, st>>>(
+            (const E *)V, (const E *)D, (E *)Phi, (Acc *)p->d_workspace, p->d_red_ptr, p->d_red_row, p->d_red_out, Wv, (uint32_t)p->W,
+            tiles, split, chunk_stride);
     });
     int rc = launched();
     if (rc != CCDC_OK || split == 1) return rc;
-    const uint64_t items = (uint64_t)chunk_stride / VEC;
-    const int G = reduce_final_groups((int64_t)items, split);
-    k_reduce_final<A, VEC><<<cdiv(items, kBlock / G), kBlock, 0, st>>>((const Acc *)p->d_workspace, (E *)Phi, split,
-                                                                        chunk_stride / VEC, (uint32_t)items, G);
-    return launched();
+    return reduce_chunks<A, ANY ? 1 : VEC>(p, Phi, split, chunk_stride, st);
 }
 
 }  // namespace
@@ -819,49 +821,54 @@ const char *ccdc_strerror(int status)
 int ccdc_combine(const ccdc_plan_t *plan, const void *V, void *Vbar, void *stream)
 {
     int rc = ready(plan), vec = 1;
+    bool any = false;
     if (rc != CCDC_OK) return rc;
-    if ((rc = pick_vec(plan, &vec, V, (const void *)Vbar)) != CCDC_OK) return rc;
+    if ((rc = pick_wide(plan, &vec, &any, makes_lanes(plan, plan->nrows, plan->W, plan->m == 1 ? 1 : 4), V, (const void *)Vbar)) != CCDC_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
-    CCDC_DISPATCH(plan, vec, (run_combine<A, VEC>(plan, V, Vbar, st)));
+    CCDC_DISPATCH(plan, vec, any, (run_combine<A, VEC, ANY>(plan, V, Vbar, st)));
 }
 
 int ccdc_encode(const ccdc_plan_t *plan, const void *Vbar, void *X, void *stream)
 {
     int rc = ready(plan), vec = 1;
+    bool any = false;
     if (rc != CCDC_OK) return rc;
     if (plan->compression) return CCDC_ESTATE;       // nothing is coded in that scheme
-    if ((rc = pick_vec(plan, &vec, Vbar, (const void *)X)) != CCDC_OK) return rc;
+    if ((rc = pick_wide(plan, &vec, &any, makes_lanes(plan, plan->nrows, plan->ell, 1), Vbar, (const void *)X)) != CCDC_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
-    CCDC_DISPATCH(plan, vec, (run_encode<A, VEC>(plan, Vbar, X, st)));
+    CCDC_DISPATCH(plan, vec, any, (run_encode<A, VEC, ANY>(plan, Vbar, X, st)));
 }
 
 int ccdc_decode(const ccdc_plan_t *plan, const void *X, const void *Vbar, void *D, void *stream)
 {
     int rc = ready(plan), vec = 1;
+    bool any = false;
     if (rc != CCDC_OK) return rc;
     if (plan->compression) return CCDC_ESTATE;       // nothing is coded in that scheme
-    if ((rc = pick_vec(plan, &vec, X, Vbar, (const void *)D)) != CCDC_OK) return rc;
+    if ((rc = pick_wide(plan, &vec, &any, makes_lanes(plan, plan->nrows, plan->ell, 1), X, Vbar, (const void *)D)) != CCDC_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
-    CCDC_DISPATCH(plan, vec, (run_decode<A, VEC>(plan, X, Vbar, D, st)));
+    CCDC_DISPATCH(plan, vec, any, (run_decode<A, VEC, ANY>(plan, X, Vbar, D, st)));
 }
 
 int ccdc_reduce(const ccdc_plan_t *plan, const void *V, const void *D, void *Phi, void *stream)
 {
     int rc = ready(plan), vec = 1;
+    bool any = false;
     if (rc != CCDC_OK) return rc;
-    if ((rc = pick_vec(plan, &vec, V, D, (const void *)Phi)) != CCDC_OK) return rc;
+    if ((rc = pick_wide(plan, &vec, &any, plan->wide_lists, V, D, (const void *)Phi)) != CCDC_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
-    CCDC_DISPATCH(plan, vec, (run_reduce<A, VEC>(plan, V, D, Phi, st)));
+    CCDC_DISPATCH(plan, vec, any, (run_reduce<A, VEC, ANY>(plan, V, D, Phi, st)));
 }
 
 int ccdc_shuffle_fused(const ccdc_plan_t *plan, const void *V, void *X, void *D, void *stream)
 {
     int rc = ready(plan), vec = 1;
+    bool any = false;
     if (rc != CCDC_OK) return rc;
     if (plan->compression) return CCDC_ESTATE;       // nothing is coded in that scheme
-    if ((rc = pick_vec(plan, &vec, V, (const void *)X, (const void *)D)) != CCDC_OK) return rc;
+    if ((rc = pick_wide(plan, &vec, &any, shuffle_any(plan), V, (const void *)X, (const void *)D)) != CCDC_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
-    CCDC_DISPATCH(plan, vec, (run_shuffle<A, VEC>(plan, V, X, D, st)));
+    CCDC_DISPATCH(plan, vec, any, (run_shuffle<A, VEC, ANY>(plan, V, X, D, st)));
 }
 
 }  // extern "C"

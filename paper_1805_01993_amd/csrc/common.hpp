@@ -151,6 +151,8 @@ struct alignas(sizeof(E) * VEC) Pack {
 
 template <class A, int VEC>
 struct Ops {
+    using algebra = A;
+    static constexpr int lanes = VEC;
     using P = Pack<typename A::elem, VEC>;       // as stored
     using Q = Pack<typename A::acc, VEC>;        // as summed
     static __device__ __forceinline__ P zero()
@@ -306,6 +308,92 @@ __device__ __forceinline__ P load_pack_any(const void *p)
     }
 }
 
+// ANY: aligned to its elements only.  (Told of whole packs the compiler keeps two 16-bit elements a register, else one.)
+template <bool KEPT, bool ANY, class P, class E>
+__device__ __forceinline__ P load_at(const void *p)
+{
+    if constexpr (ANY) return load_pack_any<KEPT, P, E>(p);
+    else return load_pack<KEPT, P>(p);
+}
+template <class P, class E>
+__device__ __forceinline__ void store_stream_any(void *p, const P &v)
+{
+    using B = typename AnyBits<P, E>::type;
+    B b;
+    __builtin_memcpy(&b, &v, sizeof(P));
+    __builtin_nontemporal_store(b, reinterpret_cast<B *>(p));
+}
+template <class P, class E>
+__device__ __forceinline__ void store_any(void *p, const P &v)
+{
+    using B = typename AnyBits<P, E>::type;
+    B b;
+    __builtin_memcpy(&b, &v, sizeof(P));
+    *reinterpret_cast<B *>(p) = b;
+}
+
+template <bool STREAM, bool ANY, class P, class E>
+__device__ __forceinline__ void store_at(void *p, const P &v)
+{
+    if constexpr (STREAM && ANY) store_stream_any<P, E>(p, v);
+    else if constexpr (STREAM) store_stream(p, v);
+    else if constexpr (ANY) store_any<P, E>(p, v);
+    else *reinterpret_cast<P *>(p) = v;
+}
+
+// Packs of 16 bytes also where the value length or the pointers do not divide by them (ANY): rows then begin at any element, and
+// one pack of a row may reach past its end.  Where whole rows are added, and along the columns of a segment, that pack is
+// moved back to the last whole one, so two lanes make the same elements from the same numbers (column()); a pack
+// of a packet's short last segment is made element by element (end_pack()).  One-element packs, which such calls were made of before,
+// are as many instructions and addresses for an eighth or a quarter of the bytes.  Over 260 passes of such lengths, 64 KB to 3 GB, 0.79 of
+// the time (16 bits from 100 MB on 0.35 to 0.55): 18 nodes, r = 2, T = 56286 bf16 the four stages 931 -> 350 us, 70 jobs on 8 nodes,
+// r = 3, four files, T = 105661 bf16 777 -> 477, 23 nodes, r = 2, T = 28754 f16 node-local 425 -> 185, 21 nodes, r = 3, T = 4282 f32 the stages 820 -> 529.
+// With fewer packs than fill the chip the narrow ones stay, of which there are more lanes with less each to add (pick_wide(); uncoded, 19
+// nodes, T = 4169 u32 12 and more files a packet 10.6 us, 28.7; 7 nodes, r = 5, eleven files, T = 5470 bf16 fused 5.3, 51).
+template <bool ANY, int VEC>
+__device__ __forceinline__ uint32_t column(uint32_t pack, uint32_t length)
+{
+    const uint32_t x = pack * VEC;
+    return ANY && x + VEC > length ? length - VEC : x;
+}
+
+// The elements of a row (of the sums of `files` files' rows) from pos on, zeros past its end at W.
+template <class O, class E>
+__device__ __forceinline__ typename O::P end_pack(const E *row, uint32_t pos, uint32_t W, int files, int64_t file_stride)
+{
+    using A = typename O::algebra;
+    typename O::P v = O::zero();
+#pragma unroll
+    for (int i = 0; i < O::lanes; i++) {
+        if (pos + i >= W) continue;
+        v.v[i] = row[pos + i];
+        if (files > 1) {                                      // else not a sum: the value as it is
+            typename A::acc sum = A::widen(v.v[i]);
+            for (int f = 1; f < files; f++) sum = A::next_file(sum, A::widen(row[pos + i + f * file_stride]));
+            v.v[i] = A::narrow(sum);
+        }
+    }
+    return v;
+}
+
+// The pack from element pos on of the packet pre-combined from the batch whose first file's row this is; zeros past W.
+template <class O, bool KEPT, bool TOGETHER, bool ANY, class E>
+__device__ __forceinline__ typename O::P packet_pack(const E *row, uint32_t pos, uint32_t W, int files, int64_t file_stride);
+
+// Writes the pack from element pos on of a row of W elements, as far as it lies in the row.
+template <class O, bool STREAM, bool ANY, class E>
+__device__ __forceinline__ void store_in_row(E *row, uint32_t pos, uint32_t W, const typename O::P &v)
+{
+    using P = typename O::P;
+    if (ANY && pos + O::lanes > W) {
+#pragma unroll
+        for (int i = 0; i < O::lanes; i++)
+            if (pos + i < W) row[pos + i] = v.v[i];
+    } else if (pos < W) {
+        store_at<STREAM, ANY, P, E>(row + pos, v);
+    }
+}
+
 // Batches of several files.  Asked for one after the other, the files of a batch are as many waits; with packs of less than 16
 // bytes, of which a wavefront has few bytes in flight, several files are asked for together.  Packs of 16 bytes stay with one
 // at a time: past the caches that gives nothing (56 jobs on 8 nodes, r = 2, three files, T = 150000 u32 483 -> 491 us), and sums of
@@ -314,24 +402,24 @@ __device__ __forceinline__ P load_pack_any(const void *p)
 // uncoded, 12 nodes, r = 1, T = 1278647 f32 548 -> 580) and the kernels of node.hip that pack lanes (17 nodes, r = 4, T = 99 h32 46 -> 56).  141 inputs of 20 MB to 2.5 GB: combine
 // down to 0.60 of the time, the fused shuffle 0.42, node-local encoding 0.43, decoding 0.38 (9 nodes, r = 3, T = 36845 bf16, nine
 // files, 0.61, 0.42, 0.45, 0.56).
-template <class O>
+template <class O, bool ANY = false>
 constexpr bool files_together()
 {
-    return sizeof(typename O::P) < 16;
+    return ANY || sizeof(typename O::P) < 16;
 }
 
 // Calls launch(together) with it as a compile-time constant.
-template <class O, class F>
+template <class O, bool ANY = false, class F>
 void by_files(bool together, F launch)
 {
-    if constexpr (files_together<O>()) {
+    if constexpr (files_together<O, ANY>()) {
         if (together) return launch(std::true_type());
     }
     launch(std::false_type());
 }
 
 // The sum of the same pack of `files` files, ascending: `first` is the first one's, at s.
-template <class O, bool KEPT, bool TOGETHER, class E>
+template <class O, bool KEPT, bool TOGETHER, bool ANY, class E>
 __device__ __forceinline__ typename O::Q sum_files(const typename O::P &first, const E *s, int files, int64_t file_stride)
 {
     using P = typename O::P;
@@ -341,18 +429,31 @@ __device__ __forceinline__ typename O::Q sum_files(const typename O::P &first, c
         for (; f + 4 <= files; f += 4) {
             P v[4];
 #pragma unroll
-            for (int t = 0; t < 4; t++) v[t] = load_pack<KEPT, P>(s + (f + t) * file_stride);
+            for (int t = 0; t < 4; t++) v[t] = load_at<KEPT, ANY, P, E>(s + (f + t) * file_stride);
 #pragma unroll
             for (int t = 0; t < 4; t++) acc = O::accum_file(acc, v[t]);
         }
         if (f + 2 <= files) {
-            const P v0 = load_pack<KEPT, P>(s + f * file_stride), v1 = load_pack<KEPT, P>(s + (f + 1) * file_stride);
+            const P v0 = load_at<KEPT, ANY, P, E>(s + f * file_stride), v1 = load_at<KEPT, ANY, P, E>(s + (f + 1) * file_stride);
             acc = O::accum_file(O::accum_file(acc, v0), v1);
             f += 2;
         }
     }
-    for (; f < files; f++) acc = O::accum_file(acc, load_pack<KEPT, P>(s + f * file_stride));
+    for (; f < files; f++) acc = O::accum_file(acc, load_at<KEPT, ANY, P, E>(s + f * file_stride));
     return acc;
+}
+
+template <class O, bool KEPT, bool TOGETHER, bool ANY, class E>
+__device__ __forceinline__ typename O::P packet_pack(const E *row, uint32_t pos, uint32_t W, int files, int64_t file_stride)
+{
+    using P = typename O::P;
+    const uint32_t last = W - O::lanes;
+    if (!ANY && pos >= W) return O::zero();
+    const E *s = row + (ANY && pos > last ? last : pos);      // loads without a condition: they stay in flight together
+    P v = load_at<KEPT, ANY, P, E>(s);
+    if (files > 1) v = O::narrow(sum_files<O, KEPT, TOGETHER, ANY>(v, s, files, file_stride));      // a one-file batch is sent as it is
+    if (ANY && pos > last) v = end_pack<O>(row, pos, W, files, file_stride);
+    return v;
 }
 
 // Where the same file of N packets is asked for together: as far as the registers of their sums allow (beyond, wavefronts are
@@ -399,23 +500,6 @@ __device__ __forceinline__ void sum_packets(typename O::P (&v)[N], const E *cons
     }
 #pragma unroll
     for (int k = 0; k < N; k++) v[k] = O::select(valid[k], v[k], O::zero());
-}
-
-template <class P, class E>
-__device__ __forceinline__ void store_stream_any(void *p, const P &v)
-{
-    using B = typename AnyBits<P, E>::type;
-    B b;
-    __builtin_memcpy(&b, &v, sizeof(P));
-    __builtin_nontemporal_store(b, reinterpret_cast<B *>(p));
-}
-template <class P, class E>
-__device__ __forceinline__ void store_any(void *p, const P &v)
-{
-    using B = typename AnyBits<P, E>::type;
-    B b;
-    __builtin_memcpy(&b, &v, sizeof(P));
-    *reinterpret_cast<B *>(p) = b;
 }
 
 // A value that is the same in all lanes of a wavefront, told to the compiler as such.
@@ -516,8 +600,6 @@ inline int ready(const ccdc_plan_t *p)
     return CCDC_OK;
 }
 
-inline int elem_bytes(int mode) { return (mode == CCDC_BF16_SUM_XOR || mode == CCDC_F16_SUM_XOR) ? 2 : 4; }
-
 // kKeptBytes, kKeptStageBytes: non-temporal loads pass the last-level cache (256 MB) by, ordinary ones leave the data
 // there.  A call whose inputs and outputs take no more than this (ccdc_map: what it reads; V, as large again, is only written)
 // therefore reads with ordinary loads: its inputs are then often still
@@ -576,9 +658,37 @@ int pick_vec(const ccdc_plan_t *p, int *vec, Ptr... ptrs)
     return CCDC_OK;
 }
 
+// The widest packs a call can be made of: pick_vec()'s, or packs of 16 bytes at any element (*any), where those would be one-element
+// packs and `wide` says so.
+template <class... Ptr>
+int pick_wide(const ccdc_plan_t *p, int *vec, bool *any, bool wide, Ptr... ptrs)
+{
+    const int rc = pick_vec(p, vec, ptrs...);
+    *any = rc == CCDC_OK && *vec == 1 && wide && wide_anyway(p->r, p->W, p->ell, elem_bytes(p->mode));
+    if (*any) *vec = 16 / elem_bytes(p->mode);
+    return rc;
+}
+
+// Whether `rows` rows of `length` elements make `times` kAnyLanes packs of 16 bytes.
+inline bool makes_lanes(const ccdc_plan_t *p, int64_t rows, int64_t length, double times)
+{
+    return (double)rows * (double)length * elem_bytes(p->mode) >= 16 * times * kAnyLanes;
+}
+
 inline int launched()
 {
     return hipGetLastError() == hipSuccess ? CCDC_OK : CCDC_EHIP;
+}
+
+// The second kernel of a reduction of split lists: Phi from the chunk sums in the workspace.
+template <class A, int VEC>
+int reduce_chunks(const ccdc_plan_t *p, void *Phi, int split, int64_t chunk_stride, hipStream_t st)
+{
+    const uint64_t items = (uint64_t)chunk_stride / VEC;
+    const int G = reduce_final_groups((int64_t)items, split);
+    k_reduce_final<A, VEC><<<cdiv(items, kBlock / G), kBlock, 0, st>>>((const typename A::acc *)p->d_workspace, (typename A::elem *)Phi,
+                                                                        split, chunk_stride / VEC, (uint32_t)items, G);
+    return launched();
 }
 
 // The plan's workspace holds partial sums between the two kernels of one call.
@@ -633,36 +743,25 @@ private:
 
 }  // namespace ccdc
 
-// Dispatch on (payload mode, pack width): evaluates CALL with the algebra as type A and the
-// pack width as constant VEC, inside a function that has `using namespace ccdc`.
-#define CCDC_DISPATCH(p, vec, CALL)                                   \
-    do {                                                              \
-        if ((p)->mode == CCDC_F32_SUM) {                              \
-            using A = SumF32;                                         \
-            if ((vec) == 4) { constexpr int VEC = 4; return CALL; }   \
-            constexpr int VEC = 1;                                    \
-            return CALL;                                              \
-        } else if ((p)->mode == CCDC_F32_SUM_XOR) {                   \
-            using A = HybF32;                                         \
-            if ((vec) == 4) { constexpr int VEC = 4; return CALL; }   \
-            constexpr int VEC = 1;                                    \
-            return CALL;                                              \
-        } else if ((p)->mode == CCDC_BF16_SUM_XOR) {                  \
-            using A = HybBF16;                                        \
-            if ((vec) == 8) { constexpr int VEC = 8; return CALL; }   \
-            if ((vec) == 4) { constexpr int VEC = 4; return CALL; }   \
-            constexpr int VEC = 1;                                    \
-            return CALL;                                              \
-        } else if ((p)->mode == CCDC_F16_SUM_XOR) {                   \
-            using A = HybF16;                                         \
-            if ((vec) == 8) { constexpr int VEC = 8; return CALL; }   \
-            if ((vec) == 4) { constexpr int VEC = 4; return CALL; }   \
-            constexpr int VEC = 1;                                    \
-            return CALL;                                              \
-        } else {                                                      \
-            using A = XorU32;                                         \
-            if ((vec) == 4) { constexpr int VEC = 4; return CALL; }   \
-            constexpr int VEC = 1;                                    \
-            return CALL;                                              \
-        }                                                             \
+// Dispatch on (payload mode, pack width): evaluates CALL with the algebra as type A, the pack width as constant VEC and
+// whether packs may begin at any element as constant ANY, inside a function that has `using namespace ccdc`.
+#define CCDC_DISPATCH_WIDTH(ALGEBRA, MOST, vec, any, CALL)                                    \
+    do {                                                                                      \
+        using A = ALGEBRA;                                                                    \
+        if (any) { constexpr int VEC = MOST; constexpr bool ANY = true; return CALL; }        \
+        constexpr bool ANY = false;                                                           \
+        if ((vec) == MOST) { constexpr int VEC = MOST; return CALL; }                         \
+        if ((vec) == 4) { constexpr int VEC = 4; return CALL; }                               \
+        constexpr int VEC = 1;                                                                \
+        return CALL;                                                                          \
+    } while (0)
+#define CCDC_DISPATCH(p, vec, any, CALL)                                                      \
+    do {                                                                                      \
+        switch ((p)->mode) {                                                                  \
+        case CCDC_F32_SUM: CCDC_DISPATCH_WIDTH(SumF32, 4, vec, any, CALL);                    \
+        case CCDC_F32_SUM_XOR: CCDC_DISPATCH_WIDTH(HybF32, 4, vec, any, CALL);                \
+        case CCDC_BF16_SUM_XOR: CCDC_DISPATCH_WIDTH(HybBF16, 8, vec, any, CALL);              \
+        case CCDC_F16_SUM_XOR: CCDC_DISPATCH_WIDTH(HybF16, 8, vec, any, CALL);                \
+        default: CCDC_DISPATCH_WIDTH(XorU32, 4, vec, any, CALL);                              \
+        }                                                                                     \
     } while (0)

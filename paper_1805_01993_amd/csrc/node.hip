@@ -17,37 +17,24 @@ enum Reads {
     kAll = 2,                         // and the files
 };
 
-// Pack `pos` of the packet pre-combined for a round member from the batch that
-// starts at element offset `src` of V (files ascending, narrowed once).
-template <class A, int VEC, bool KEPT, bool TOGETHER>
-__device__ __forceinline__ typename Ops<A, VEC>::P combined_pack(const typename A::elem *__restrict__ V, int64_t src,
-                                                                 uint32_t pos, int m, int64_t file_stride)
-{
-    using O = Ops<A, VEC>;
-    using P = typename O::P;
-    const typename A::elem *s = V + src + (int64_t)pos * VEC;
-    const P first = load_pack<KEPT, P>(s);
-    if (m == 1) return first;                         // a one-file batch is sent as it is
-    return O::narrow(sum_files<O, KEPT, TOGETHER>(first, s, m, file_stride));
-}
-
 // ------------------------------------------------------- a sender's packets
 // Coded-packet equation of Sec. IV-B for the packets listed in `rows` (those one
 // node sends; null = every packet).  One work item = one pack of X[u][a]: the
 // sender pre-combines, for each other member b, the segment of b's packet that
 // carries the sender's label; it stores all those batches.
-template <class A, int VEC, int READS, bool TOGETHER>
+template <class A, int VEC, int READS, bool TOGETHER, bool ANY>
 __global__ __launch_bounds__(kBlock) void k_node_encode(const typename A::elem *__restrict__ V,
                                                         typename A::elem *__restrict__ X,
                                                         const int64_t *__restrict__ src_off,
-                                                        const int32_t *__restrict__ rows, int r1, uint32_t Lv,
-                                                        uint32_t Wv, int m, int64_t file_stride, uint32_t items)
+                                                        const int32_t *__restrict__ rows, int r1, uint32_t Lv, uint32_t ell,
+                                                        uint32_t W, int m, int64_t file_stride, uint32_t items)
 {
+    using E = typename A::elem;
     using O = Ops<A, VEC>;
     using P = typename O::P;
     const uint32_t idx = blockIdx.x * kBlock + threadIdx.x;
     if (idx >= items) return;
-    const uint32_t j = idx / Lv, x = idx - j * Lv;
+    const uint32_t j = idx / Lv, x = column<ANY, VEC>(idx - j * Lv, ell);
     const uint32_t i = rows ? (uint32_t)rows[j] : j;
     const uint32_t u = i / r1;
     const int a = (int)(i - u * r1);
@@ -55,10 +42,19 @@ __global__ __launch_bounds__(kBlock) void k_node_encode(const typename A::elem *
     P coded = O::zero();
     for (int b = 0; b < r1; b++) {
         if (b == a) continue;
-        const uint32_t pos = segment_rank(a, b) * Lv + x;
-        if (pos < Wv) coded = O::code(coded, combined_pack<A, VEC, READS == kAll, TOGETHER>(V, src[b], pos, m, file_stride));
+        const uint32_t pos = segment_rank(a, b) * ell + x;
+        if (pos < W) coded = O::code(coded, packet_pack<O, READS == kAll, TOGETHER, ANY>(V + src[b], pos, W, m, file_stride));
     }
-    store_stream(reinterpret_cast<P *>(X) + (size_t)i * Lv + x, coded);
+    store_at<true, ANY, P, E>(X + (size_t)i * ell + x, coded);
+}
+
+// The element of its row that the pack at x of the segment which begins at `first` starts from.  A pack that reaches past the row's
+// end is moved back to the last whole one (*x too), as in column(); a last segment has a pack.
+template <bool ANY, int VEC>
+__device__ __forceinline__ uint32_t in_segment(uint32_t first, uint32_t W, uint32_t *x)
+{
+    if (ANY && first + *x + VEC > W) *x = W - VEC - first;
+    return first + *x;
 }
 
 // Bounds of chunk s of output block o's row list: in a table where lists are cut by rounds, else an equal part of the list.
@@ -81,14 +77,15 @@ __device__ __forceinline__ Rows chunk_of(const int64_t *__restrict__ ptr, bool b
 // is recovered here as that sender's coded pack minus the packs of the other
 // members' packets in it, which the receiver pre-combines from its own files.
 // The list is cut into `split` chunks as in ccdc_reduce.
-template <class A, int VEC, int READS, bool TOGETHER>
+template <class A, int VEC, int READS, bool TOGETHER, bool ANY>
 __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
     const typename A::elem *__restrict__ V, const typename A::elem *__restrict__ X, typename A::elem *__restrict__ out,
     typename A::acc *__restrict__ part, const int64_t *__restrict__ node_ptr, bool by_round, const int64_t *__restrict__ node_row,
-    const int64_t *__restrict__ red_out, const int64_t *__restrict__ src_off, int r1, uint32_t Lv, uint32_t Wv,
-    int64_t W, int m, int64_t file_stride, uint32_t tiles, int split, int64_t chunk_stride, uint32_t o_first,
+    const int64_t *__restrict__ red_out, const int64_t *__restrict__ src_off, int r1, uint32_t Lv, uint32_t ell,
+    uint32_t W, int m, int64_t file_stride, uint32_t tiles, int split, int64_t chunk_stride, uint32_t o_first,
     uint32_t o_step)
 {
+    using E = typename A::elem;
     using O = Ops<A, VEC>;
     using P = typename O::P;
     const uint32_t tile = blockIdx.x % tiles;
@@ -96,15 +93,16 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
     const uint32_t oi = oc / split;
     const int s = (int)(oc - oi * split);
     const uint32_t o = o_first + oi * o_step;
-    const uint32_t e = tile * kBlock + threadIdx.x;
-    if (e >= Wv) return;
-    const uint32_t rho = e / Lv, x = e - rho * Lv;
+    const uint32_t pack = tile * kBlock + threadIdx.x, rho = pack / Lv;
+    uint32_t x = column<ANY, VEC>(pack - rho * Lv, ell);
+    if (rho >= (uint32_t)r1 - 1 || rho * ell + x >= W) return;
+    const uint32_t e = in_segment<ANY, VEC>(rho * ell, W, &x);
     const auto [lo, hi] = chunk_of(node_ptr, by_round, o, s, split);
     typename O::Q acc = O::azero();
     for (int64_t i = lo; i < hi; i++) {
         const int64_t row = node_row[i];
         if (!(row & 1)) {                                    // a file the node stores
-            acc = O::accum(acc, load_pack<READS == kAll, P>(reinterpret_cast<const P *>(V + (row >> 1)) + e));
+            acc = O::accum(acc, load_at<READS == kAll, ANY, P, E>(V + (row >> 1) + e));
             continue;
         }
         const int64_t pk = (row >> 1) / W;                   // packet u*(r+1)+b meant for this node
@@ -112,16 +110,16 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
         const int b = (int)(pk - (int64_t)u * r1);
         const int a = (int)rho < b ? (int)rho : (int)rho + 1;
         const int64_t *src = src_off + (size_t)u * r1;
-        P d = load_pack<READS != kPast, P>(reinterpret_cast<const P *>(X) + ((size_t)u * r1 + a) * Lv + x);
+        P d = load_at<READS != kPast, ANY, P, E>(X + ((size_t)u * r1 + a) * ell + x);
         for (int b2 = 0; b2 < r1; b2++) {
             if (b2 == a || b2 == b) continue;
-            const uint32_t pos = segment_rank(a, b2) * Lv + x;
-            if (pos < Wv) d = O::uncode(d, combined_pack<A, VEC, READS == kAll, TOGETHER>(V, src[b2], pos, m, file_stride));
+            const uint32_t pos = segment_rank(a, b2) * ell + x;
+            if (pos < W) d = O::uncode(d, packet_pack<O, READS == kAll, TOGETHER, ANY>(V + src[b2], pos, W, m, file_stride));
         }
         acc = O::accum(acc, d);
     }
-    if (split > 1) reinterpret_cast<typename O::Q *>(part + (int64_t)s * chunk_stride + red_out[o])[e] = acc;
-    else reinterpret_cast<P *>(out + red_out[o])[e] = O::narrow(acc);
+    if (split > 1) store_at<false, ANY, typename O::Q, typename A::acc>(part + (int64_t)s * chunk_stride + red_out[o] + e, acc);
+    else store_at<false, ANY, P, E>(out + red_out[o] + e, O::narrow(acc));
 }
 
 // The same two, with a wavefront on 64 consecutive packs of ONE segment: sender, receiver, batch
@@ -138,49 +136,51 @@ constexpr int kWaves = kBlock / kWave;
 // FILES: the files of a batch, one, several in turn or together.
 enum Files { kOneFile, kInTurn, kTogether };
 
-template <class A, int VEC, int R1, int FILES, int READS>
+template <class A, int VEC, int R1, int FILES, int READS, bool ANY>
 __global__ __launch_bounds__(kBlock) void k_node_encode_wave(const typename A::elem *__restrict__ V,
                                                              typename A::elem *__restrict__ X,
                                                              const int64_t *__restrict__ src_off,
-                                                             const int32_t *__restrict__ rows, uint32_t Lv,
-                                                             uint32_t Wv, int m, int64_t file_stride, uint32_t tiles,
+                                                             const int32_t *__restrict__ rows, uint32_t Lv, uint32_t ell,
+                                                             uint32_t W, int m, int64_t file_stride, uint32_t tiles,
                                                              uint32_t units)
 {
+    using E = typename A::elem;
     using O = Ops<A, VEC>;
     using P = typename O::P;
     const uint32_t unit = blockIdx.x * kWaves + wave_uniform(threadIdx.x / kWave);
     if (unit >= units) return;
-    const uint32_t j = unit / tiles, x = (unit - j * tiles) * kWave + threadIdx.x % kWave;
-    if (x >= Lv) return;
+    const uint32_t j = unit / tiles, pack = (unit - j * tiles) * kWave + threadIdx.x % kWave;
+    if (pack >= Lv) return;
+    const uint32_t x = column<ANY, VEC>(pack, ell);
     const uint32_t i = rows ? (uint32_t)rows[j] : j;
     const uint32_t u = i / R1;
     const int a = (int)(i - u * R1);
     const int64_t *src = src_off + (size_t)u * R1;
     P part[R1 - 1];
     if constexpr (FILES == kTogether && packets_together<O, R1 - 1>()) {
-        const typename A::elem *at[R1 - 1];
+        const E *at[R1 - 1];
         bool there[R1 - 1];
 #pragma unroll
         for (int k = 0; k < R1 - 1; k++) {
             const int b = k + (k >= a ? 1 : 0);
-            const uint32_t pos = segment_rank(a, b) * Lv + x;
-            there[k] = pos < Wv;
-            at[k] = V + src[b] + (int64_t)(there[k] ? pos : 0) * VEC;
+            const uint32_t pos = segment_rank(a, b) * ell + x;
+            there[k] = pos < W;
+            at[k] = V + src[b] + (there[k] ? pos : 0);
         }
         sum_packets<O, READS == kAll>(part, at, there, m, file_stride);
     } else {
 #pragma unroll
         for (int k = 0; k < R1 - 1; k++) {
             const int b = k + (k >= a ? 1 : 0);
-            const uint32_t pos = segment_rank(a, b) * Lv + x;
+            const uint32_t pos = segment_rank(a, b) * ell + x;
             part[k] = O::zero();
-            if (pos < Wv) part[k] = combined_pack<A, VEC, READS == kAll, FILES == kTogether>(V, src[b], pos, FILES == kOneFile ? 1 : m, file_stride);
+            if (ANY || pos < W) part[k] = packet_pack<O, READS == kAll, FILES == kTogether, ANY>(V + src[b], pos, W, FILES == kOneFile ? 1 : m, file_stride);
         }
     }
     P coded = O::zero();
 #pragma unroll
     for (int k = 0; k < R1 - 1; k++) coded = O::code(coded, part[k]);
-    store_stream(reinterpret_cast<P *>(X) + (size_t)i * Lv + x, coded);
+    store_at<true, ANY, P, E>(X + (size_t)i * ell + x, coded);
 }
 
 // How the units are numbered.
@@ -190,14 +190,15 @@ enum Numbering {
     kByChunk,                         // (chunk, (output block, segment, tile)), an XCD on a contiguous range: lists_by_round()
 };
 
-template <class A, int VEC, int R1, int FILES, int READS, int NUMBERING>
+template <class A, int VEC, int R1, int FILES, int READS, int NUMBERING, bool ANY>
 __global__ __launch_bounds__(kBlock) void k_node_decode_reduce_wave(
     const typename A::elem *__restrict__ V, const typename A::elem *__restrict__ X, typename A::elem *__restrict__ out,
     typename A::acc *__restrict__ part, const int64_t *__restrict__ node_ptr, bool by_round, const int64_t *__restrict__ node_row,
-    const int64_t *__restrict__ red_out, const int64_t *__restrict__ src_off, uint32_t Lv, uint32_t Wv,
+    const int64_t *__restrict__ red_out, const int64_t *__restrict__ src_off, uint32_t Lv, uint32_t ell, uint32_t W,
     double per_row, int m, int64_t file_stride, uint32_t tiles, int split, int64_t chunk_stride, uint32_t o_first,
     uint32_t o_step, uint32_t units)
 {
+    using E = typename A::elem;
     using O = Ops<A, VEC>;
     using P = typename O::P;
     constexpr int r = R1 - 1;
@@ -226,15 +227,16 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce_wave(
         oi = oc / split;
         s = (int)(oc - oi * split);
     }
-    const uint32_t x = tile * kWave + threadIdx.x % kWave;
+    const uint32_t pack = tile * kWave + threadIdx.x % kWave;
     const uint32_t o = o_first + oi * o_step;
-    const uint32_t e = rho * Lv + x;
-    if (x >= Lv || e >= Wv) return;
+    uint32_t x = column<ANY, VEC>(pack, ell);
+    if (pack >= Lv || rho * ell + x >= W) return;
+    const uint32_t e = in_segment<ANY, VEC>(rho * ell, W, &x);
     const auto [lo, hi] = chunk_of(node_ptr, by_round, o, s, split);
     typename O::Q acc = O::azero();
     int64_t i = lo;
     // the files the node stores come first in the list
-    auto own = [&](int64_t row) { return load_pack<READS == kAll, P>(reinterpret_cast<const P *>(V + (row >> 1)) + e); };
+    auto own = [&](int64_t row) { return load_at<READS == kAll, ANY, P, E>(V + (row >> 1) + e); };
     for (; i + 4 <= hi; i += 4) {
         const int64_t row[4] = {node_row[i], node_row[i + 1], node_row[i + 2], node_row[i + 3]};
         if (row[3] & 1) break;
@@ -254,21 +256,21 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce_wave(
         const int a = rho < b ? rho : rho + 1;
         const int low = a < b ? a : b, high = a < b ? b : a;
         const int64_t *src = src_off + (size_t)u * R1;
-        k.coded = load_pack<READS != kPast, P>(reinterpret_cast<const P *>(X) + ((size_t)u * R1 + a) * Lv + x);
+        k.coded = load_at<READS != kPast, ANY, P, E>(X + ((size_t)u * R1 + a) * ell + x);
         auto position = [&](int q, int &b2) {                // of the q-th member that is neither a nor b
             b2 = q + (q >= low ? 1 : 0);
             b2 += b2 >= high ? 1 : 0;
-            return segment_rank(a, b2) * Lv + x;
+            return segment_rank(a, b2) * ell + x;
         };
         if constexpr (FILES == kTogether && r > 2 && packets_together<O, r - 1>()) {
-            const typename A::elem *from[r - 1];
+            const E *from[r - 1];
             bool there[r - 1];
 #pragma unroll
             for (int q = 0; q < r - 1; q++) {
                 int b2;
                 const uint32_t pos = position(q, b2);
-                there[q] = pos < Wv;
-                from[q] = V + src[b2] + (int64_t)(there[q] ? pos : 0) * VEC;
+                there[q] = pos < W;
+                from[q] = V + src[b2] + (there[q] ? pos : 0);
             }
             sum_packets<O, READS == kAll>(k.side, from, there, m, file_stride);
         } else {
@@ -277,7 +279,7 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce_wave(
                 int b2;
                 const uint32_t pos = position(q, b2);
                 k.side[q] = O::zero();
-                if (pos < Wv) k.side[q] = combined_pack<A, VEC, READS == kAll, FILES == kTogether>(V, src[b2], pos, FILES == kOneFile ? 1 : m, file_stride);
+                if (ANY || pos < W) k.side[q] = packet_pack<O, READS == kAll, FILES == kTogether, ANY>(V + src[b2], pos, W, FILES == kOneFile ? 1 : m, file_stride);
             }
         }
     };
@@ -299,8 +301,8 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce_wave(
         load(i, k);
         use(k);
     }
-    if (split > 1) reinterpret_cast<typename O::Q *>(part + (int64_t)s * chunk_stride + red_out[o])[e] = acc;
-    else reinterpret_cast<P *>(out + red_out[o])[e] = O::narrow(acc);
+    if (split > 1) store_at<false, ANY, typename O::Q, typename A::acc>(part + (int64_t)s * chunk_stride + red_out[o] + e, acc);
+    else store_at<false, ANY, P, E>(out + red_out[o] + e, O::narrow(acc));
 }
 
 // Adds the chunk sums of one node's output blocks, in k_reduce_final's order for the same G, so
@@ -335,12 +337,12 @@ __global__ __launch_bounds__(kBlock) void k_node_final(const typename A::acc *__
 }
 
 // Calls launch(r+1, files of a batch) with both as compile-time constants, r <= 5.
-template <class O, class F>
+template <class O, bool ANY, class F>
 void by_shape(const ccdc_plan_t *p, bool together, F launch)
 {
     auto files = [&](auto r1) {
         if (p->m == 1) return launch(r1, std::integral_constant<int, kOneFile>());
-        by_files<O>(together, [&](auto t) { launch(r1, std::integral_constant<int, decltype(t)::value ? kTogether : kInTurn>()); });
+        by_files<O, ANY>(together, [&](auto t) { launch(r1, std::integral_constant<int, decltype(t)::value ? kTogether : kInTurn>()); });
     };
     switch (p->r) {
     case 1: files(std::integral_constant<int, 2>()); break;
@@ -388,11 +390,11 @@ void by_node_reads(Reads reads, F launch)
     launch(std::integral_constant<int, kPast>());
 }
 
-template <class A, int VEC>
+template <class A, int VEC, bool ANY>
 int run_node_encode(const ccdc_plan_t *p, int node, const void *V, void *X, hipStream_t st)
 {
     using E = typename A::elem;
-    const uint32_t Wv = (uint32_t)(p->W / VEC), Lv = (uint32_t)(p->ell / VEC);
+    const uint32_t Lv = cdiv(p->ell, VEC), ell = (uint32_t)p->ell, W = (uint32_t)p->W;
     const int64_t rows = node < 0 ? p->nrows : p->rows_per_node;
     const uint64_t items = (uint64_t)rows * Lv;
     if (items == 0) return CCDC_OK;
@@ -405,30 +407,30 @@ int run_node_encode(const ccdc_plan_t *p, int node, const void *V, void *X, hipS
             constexpr int R1 = decltype(r1)::value;
             constexpr int FILES = decltype(files)::value;
             by_node_reads<false>(node_reads<VEC>(p, node, true), [&](auto reads) {
-                k_node_encode_wave<A, VEC, R1, FILES, decltype(reads)::value><<<cdiv(units, kWaves), kBlock, 0, st>>>(
-                    (const E *)V, (E *)X, p->d_src_off, list, Lv, Wv, p->m, (int64_t)p->Q * p->T, wave_tiles,
+                k_node_encode_wave<A, VEC, R1, FILES, decltype(reads)::value, ANY><<<cdiv(units, kWaves), kBlock, 0, st>>>(
+                    (const E *)V, (E *)X, p->d_src_off, list, Lv, ell, W, p->m, (int64_t)p->Q * p->T, wave_tiles,
                     (uint32_t)units);
             });
         };
-        by_shape<Ops<A, VEC>>(p, true, launch);
+        by_shape<Ops<A, VEC>, ANY>(p, true, launch);
         return launched();
     }
     by_node_reads<false>(node_reads<VEC>(p, node, false), [&](auto reads) {
-        by_files<Ops<A, VEC>>(p->m > 2, [&](auto together) {
-            k_node_encode<A, VEC, decltype(reads)::value, decltype(together)::value><<<cdiv(items, kBlock), kBlock, 0, st>>>(
-                (const E *)V, (E *)X, p->d_src_off, list, p->r + 1, Lv, Wv, p->m, (int64_t)p->Q * p->T, (uint32_t)items);
+        by_files<Ops<A, VEC>, ANY>(p->m > 2, [&](auto together) {
+            k_node_encode<A, VEC, decltype(reads)::value, decltype(together)::value, ANY><<<cdiv(items, kBlock), kBlock, 0, st>>>(
+                (const E *)V, (E *)X, p->d_src_off, list, p->r + 1, Lv, ell, W, p->m, (int64_t)p->Q * p->T, (uint32_t)items);
         });
     });
     return launched();
 }
 
-template <class A, int VEC>
+template <class A, int VEC, bool ANY>
 int run_node_decode_reduce(const ccdc_plan_t *p, int node, const void *V, const void *X, void *Phi, hipStream_t st)
 {
     using E = typename A::elem;
     using Acc = typename A::acc;
-    const uint32_t Wv = (uint32_t)(p->W / VEC), Lv = (uint32_t)(p->ell / VEC);
-    const uint32_t tiles = cdiv(Wv, kBlock);
+    const uint32_t Lv = cdiv(p->ell, VEC), ell = (uint32_t)p->ell, W = (uint32_t)p->W;
+    const uint32_t tiles = cdiv((uint64_t)Lv * p->r, kBlock);          // the last segment may be short
     const int split = p->red_split;
     const bool by_round = p->d_node_row != nullptr;
     const int64_t *bounds = by_round ? p->d_node_row : p->d_red_ptr;
@@ -437,7 +439,7 @@ int run_node_decode_reduce(const ccdc_plan_t *p, int node, const void *V, const 
     const uint32_t o_first = node < 0 ? 0u : (uint32_t)node, o_step = node < 0 ? 1u : (uint32_t)p->K;
     const int64_t chunk_stride = (int64_t)p->J * p->Q * p->T;
     const uint64_t blocks = (uint64_t)count * split * tiles;
-    if (!fits_launch(blocks) || !fits_launch((uint64_t)chunk_stride / VEC)) return CCDC_ESIZE;
+    if (!fits_launch(blocks) || !fits_launch((uint64_t)chunk_stride / (ANY ? 1 : VEC))) return CCDC_ESIZE;
     WorkspaceOrder order(p, st, split > 1);
     const uint32_t wave_tiles = cdiv(Lv, kWave);
     const uint64_t units = (uint64_t)count * split * p->r * wave_tiles;
@@ -447,9 +449,9 @@ int run_node_decode_reduce(const ccdc_plan_t *p, int node, const void *V, const 
             constexpr int FILES = decltype(files)::value;
             by_node_reads<(VEC > 1 && R1 > 2)>(node_reads<VEC>(p, node, true), [&](auto reads) {
                 auto numbered = [&](auto numbering) {
-                    k_node_decode_reduce_wave<A, VEC, R1, FILES, decltype(reads)::value, decltype(numbering)::value><<<cdiv(units, kWaves), kBlock, 0, st>>>(
+                    k_node_decode_reduce_wave<A, VEC, R1, FILES, decltype(reads)::value, decltype(numbering)::value, ANY><<<cdiv(units, kWaves), kBlock, 0, st>>>(
                         (const E *)V, (const E *)X, (E *)Phi, (Acc *)p->d_workspace, bounds, by_round, rows, p->d_red_out,
-                        p->d_src_off, Lv, Wv, 1.0 / (double)p->W, p->m, (int64_t)p->Q * p->T, wave_tiles, split, chunk_stride,
+                        p->d_src_off, Lv, ell, W, 1.0 / (double)p->W, p->m, (int64_t)p->Q * p->T, wave_tiles, split, chunk_stride,
                         o_first, o_step, (uint32_t)units);
                 };
                 if constexpr (R1 > 3 && decltype(reads)::value == kAll) {
@@ -461,29 +463,26 @@ int run_node_decode_reduce(const ccdc_plan_t *p, int node, const void *V, const 
                 numbered(std::integral_constant<int, kByOutput>());
             });
         };
-        by_shape<Ops<A, VEC>>(p, p->m > 2 || p->r > 2, launch);     // r = 2: one packet in the making, as in combine
+        by_shape<Ops<A, VEC>, ANY>(p, p->m > 2 || p->r > 2, launch);     // r = 2: one packet in the making, as in combine
     } else {
         by_node_reads<false>(node_reads<VEC>(p, node, false), [&](auto reads) {
-            by_files<Ops<A, VEC>>(p->m > 2, [&](auto together) {
-                k_node_decode_reduce<A, VEC, decltype(reads)::value, decltype(together)::value><<<(uint32_t)blocks, kBlock, 0, st>>>(
+            by_files<Ops<A, VEC>, ANY>(p->m > 2, [&](auto together) {
+                k_node_decode_reduce<A, VEC, decltype(reads)::value, decltype(together)::value, ANY><<<(uint32_t)blocks, kBlock, 0, st>>>(
                     (const E *)V, (const E *)X, (E *)Phi, (Acc *)p->d_workspace, bounds, by_round, rows, p->d_red_out,
-                    p->d_src_off, p->r + 1, Lv, Wv, p->W, p->m, (int64_t)p->Q * p->T, tiles, split, chunk_stride, o_first,
+                    p->d_src_off, p->r + 1, Lv, ell, W, p->m, (int64_t)p->Q * p->T, tiles, split, chunk_stride, o_first,
                     o_step);
             });
         });
     }
     int rc = launched();
     if (rc != CCDC_OK || split == 1) return rc;
+    if (node < 0) return reduce_chunks<A, ANY ? 1 : VEC>(p, Phi, split, chunk_stride, st);    // every block: Phi from end to end, as in ccdc_reduce
+    constexpr int PACK = ANY ? 1 : VEC;
+    const uint32_t Wv = W / PACK;
     const uint64_t items = (uint64_t)count * Wv;
-    const uint64_t all = (uint64_t)chunk_stride / VEC;
-    const int G = reduce_final_groups((int64_t)all, split);
-    if (node < 0)                                            // every block: Phi from end to end, as in ccdc_reduce
-        k_reduce_final<A, VEC><<<cdiv(all, kBlock / G), kBlock, 0, st>>>((const Acc *)p->d_workspace, (E *)Phi, split,
-                                                                          chunk_stride / VEC, (uint32_t)all, G);
-    else
-        k_node_final<A, VEC><<<cdiv(items, kBlock / G), kBlock, 0, st>>>((const Acc *)p->d_workspace, (E *)Phi, p->d_red_out,
-                                                                          Wv, split, chunk_stride, o_first, o_step,
-                                                                          (uint32_t)items, G);
+    const int G = reduce_final_groups(chunk_stride / PACK, split);
+    k_node_final<A, PACK><<<cdiv(items, kBlock / G), kBlock, 0, st>>>((const Acc *)p->d_workspace, (E *)Phi, p->d_red_out, Wv, split,
+                                                                       chunk_stride, o_first, o_step, (uint32_t)items, G);
     return launched();
 }
 
@@ -491,33 +490,33 @@ int run_node_decode_reduce(const ccdc_plan_t *p, int node, const void *V, const 
 
 namespace ccdc {
 
-// The calls for one algebra, at a pack width that pick_vec() gives.
+// The calls for one algebra, at a pack width that pick_wide() gives.
 template <class A>
-int node_encode(const ccdc_plan_t *p, int vec, int node, const void *V, void *X, hipStream_t st)
+int node_encode(const ccdc_plan_t *p, int vec, bool any, int node, const void *V, void *X, hipStream_t st)
 {
-    if constexpr (sizeof(typename A::elem) == 2) {
-        if (vec == 8) return run_node_encode<A, 8>(p, node, V, X, st);
-    }
-    return vec == 4 ? run_node_encode<A, 4>(p, node, V, X, st) : run_node_encode<A, 1>(p, node, V, X, st);
+    constexpr int MOST = 16 / sizeof(typename A::elem);
+    if (any) return run_node_encode<A, MOST, true>(p, node, V, X, st);
+    if (vec == MOST) return run_node_encode<A, MOST, false>(p, node, V, X, st);
+    return vec == 4 ? run_node_encode<A, 4, false>(p, node, V, X, st) : run_node_encode<A, 1, false>(p, node, V, X, st);
 }
 
 template <class A>
-int node_decode_reduce(const ccdc_plan_t *p, int vec, int node, const void *V, const void *X, void *Phi, hipStream_t st)
+int node_decode_reduce(const ccdc_plan_t *p, int vec, bool any, int node, const void *V, const void *X, void *Phi, hipStream_t st)
 {
-    if constexpr (sizeof(typename A::elem) == 2) {
-        if (vec == 8) return run_node_decode_reduce<A, 8>(p, node, V, X, Phi, st);
-    }
-    return vec == 4 ? run_node_decode_reduce<A, 4>(p, node, V, X, Phi, st) : run_node_decode_reduce<A, 1>(p, node, V, X, Phi, st);
+    constexpr int MOST = 16 / sizeof(typename A::elem);
+    if (any) return run_node_decode_reduce<A, MOST, true>(p, node, V, X, Phi, st);
+    if (vec == MOST) return run_node_decode_reduce<A, MOST, false>(p, node, V, X, Phi, st);
+    return vec == 4 ? run_node_decode_reduce<A, 4, false>(p, node, V, X, Phi, st) : run_node_decode_reduce<A, 1, false>(p, node, V, X, Phi, st);
 }
 
 // Compiled in five pieces, one for each algebra, the first with the entry points.
 #ifdef CCDC_NODE_PART
 #define CCDC_NODE(A)                                                                                 \
-    template int node_encode<A>(const ccdc_plan_t *, int, int, const void *, void *, hipStream_t); \
-    template int node_decode_reduce<A>(const ccdc_plan_t *, int, int, const void *, const void *, void *, hipStream_t)
+    template int node_encode<A>(const ccdc_plan_t *, int, bool, int, const void *, void *, hipStream_t); \
+    template int node_decode_reduce<A>(const ccdc_plan_t *, int, bool, int, const void *, const void *, void *, hipStream_t)
 #define CCDC_ELSEWHERE(A)                                                                                   \
-    extern template int node_encode<A>(const ccdc_plan_t *, int, int, const void *, void *, hipStream_t); \
-    extern template int node_decode_reduce<A>(const ccdc_plan_t *, int, int, const void *, const void *, void *, hipStream_t)
+    extern template int node_encode<A>(const ccdc_plan_t *, int, bool, int, const void *, void *, hipStream_t); \
+    extern template int node_decode_reduce<A>(const ccdc_plan_t *, int, bool, int, const void *, const void *, void *, hipStream_t)
 #if CCDC_NODE_PART == 0
 CCDC_NODE(SumF32);
 CCDC_ELSEWHERE(XorU32);
@@ -556,31 +555,33 @@ extern "C" {
 int ccdc_node_encode(const ccdc_plan_t *plan, int node, const void *V, void *X, void *stream)
 {
     int rc = node_ready(plan, node), vec = 1;
+    bool any = false;
     if (rc != CCDC_OK) return rc;
-    if ((rc = pick_vec(plan, &vec, V, (const void *)X)) != CCDC_OK) return rc;
+    if ((rc = pick_wide(plan, &vec, &any, wide_fills(plan->ell, elem_bytes(plan->mode)) && makes_lanes(plan, node < 0 ? plan->nrows : plan->rows_per_node, plan->ell, 2), V, (const void *)X)) != CCDC_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     switch (plan->mode) {
-    case CCDC_F32_SUM: return node_encode<SumF32>(plan, vec, node, V, X, st);
-    case CCDC_F32_SUM_XOR: return node_encode<HybF32>(plan, vec, node, V, X, st);
-    case CCDC_BF16_SUM_XOR: return node_encode<HybBF16>(plan, vec, node, V, X, st);
-    case CCDC_F16_SUM_XOR: return node_encode<HybF16>(plan, vec, node, V, X, st);
-    default: return node_encode<XorU32>(plan, vec, node, V, X, st);
+    case CCDC_F32_SUM: return node_encode<SumF32>(plan, vec, any, node, V, X, st);
+    case CCDC_F32_SUM_XOR: return node_encode<HybF32>(plan, vec, any, node, V, X, st);
+    case CCDC_BF16_SUM_XOR: return node_encode<HybBF16>(plan, vec, any, node, V, X, st);
+    case CCDC_F16_SUM_XOR: return node_encode<HybF16>(plan, vec, any, node, V, X, st);
+    default: return node_encode<XorU32>(plan, vec, any, node, V, X, st);
     }
 }
 
 int ccdc_node_decode_reduce(const ccdc_plan_t *plan, int node, const void *V, const void *X, void *Phi, void *stream)
 {
     int rc = node_ready(plan, node), vec = 1;
+    bool any = false;
     if (rc != CCDC_OK) return rc;
-    if ((rc = pick_vec(plan, &vec, V, X, (const void *)Phi)) != CCDC_OK) return rc;
+    if ((rc = pick_wide(plan, &vec, &any, plan->wide_lists && wide_fills(plan->ell, elem_bytes(plan->mode)), V, X, (const void *)Phi)) != CCDC_OK) return rc;
     if (plan->node_waves > 0) return receive_coded(plan, node, V, X, Phi, stream);
     hipStream_t st = (hipStream_t)stream;
     switch (plan->mode) {
-    case CCDC_F32_SUM: return node_decode_reduce<SumF32>(plan, vec, node, V, X, Phi, st);
-    case CCDC_F32_SUM_XOR: return node_decode_reduce<HybF32>(plan, vec, node, V, X, Phi, st);
-    case CCDC_BF16_SUM_XOR: return node_decode_reduce<HybBF16>(plan, vec, node, V, X, Phi, st);
-    case CCDC_F16_SUM_XOR: return node_decode_reduce<HybF16>(plan, vec, node, V, X, Phi, st);
-    default: return node_decode_reduce<XorU32>(plan, vec, node, V, X, Phi, st);
+    case CCDC_F32_SUM: return node_decode_reduce<SumF32>(plan, vec, any, node, V, X, Phi, st);
+    case CCDC_F32_SUM_XOR: return node_decode_reduce<HybF32>(plan, vec, any, node, V, X, Phi, st);
+    case CCDC_BF16_SUM_XOR: return node_decode_reduce<HybBF16>(plan, vec, any, node, V, X, Phi, st);
+    case CCDC_F16_SUM_XOR: return node_decode_reduce<HybF16>(plan, vec, any, node, V, X, Phi, st);
+    default: return node_decode_reduce<XorU32>(plan, vec, any, node, V, X, Phi, st);
     }
 }
 

@@ -293,6 +293,10 @@ int build_compression_plan(int K, int r, int Q, int N, ccdc_plan_t **out)
 
 namespace {
 
+// Whether lists are summed in packs of 16 bytes where rows do not divide by them: where those fill the chip without cutting the lists, or
+// the second launch that cut ones take is little of the time.
+bool wide_lists(int64_t nout, int64_t W, double bytes) { return (double)(nout * ((W + 3) / 4)) >= kAnyListPacks || bytes >= kAnyListBytes; }
+
 // Wavefronts of a workgroup that sums a whole row list (ccdc_reduce in one launch), 0 where the list is better split over
 // workgroups and added by a second kernel.  Only for plans whose outputs are too few to fill the chip with whole lists
 // (split > 1).  Measured over 282 such plans of 64 KB to 400 MB (every scheme and mode): the one launch takes 0.657 of the
@@ -378,9 +382,10 @@ int bind_compression(ccdc_plan_t *p, int64_t T, int mode)
             outs[k] = (int64_t)k * W;
             min_rows = std::min(min_rows, ptr[k + 1] - ptr[k]);
         }
-        const int64_t items = nout * ((W + vec - 1) / vec);
-        int64_t split = 1;
-        if (items < (1 << 18)) split = std::min<int64_t>({(int64_t)256, std::max<int64_t>(1, min_rows), ((1 << 19) + items - 1) / items});
+        const bool any = wide_anyway(p->r, W, W, 4) && wide_lists(nout, W, (double)p->N * p->Q * (double)T * 4);
+        const int pack = any ? 4 : vec;                      // elements of a call's packs
+        const int64_t items = nout * ((W + pack - 1) / pack);
+        const int64_t split = list_split(items, min_rows);
         p->T = T; p->W = W; p->ell = W; p->mode = mode;
         p->packet_len.assign(1, W);
         p->scheduled = p->nrows * W;
@@ -389,8 +394,9 @@ int bind_compression(ccdc_plan_t *p, int64_t T, int mode)
         p->red_row.swap(rows);
         p->red_out.swap(outs);
         p->nout = nout;
+        p->wide_lists = any;
         p->red_split = (int)split;
-        p->red_waves = plan_groups(nout, (int64_t)p->red_row.size(), W, vec, 4, split, ((double)p->N * p->Q * (double)T) * 4);
+        p->red_waves = plan_groups(nout, (int64_t)p->red_row.size(), W, pack, 4, split, ((double)p->N * p->Q * (double)T) * 4);
         p->workspace_bytes = p->red_workspace_bytes = split > 1 && p->red_waves == 0 ? (size_t)split * (size_t)p->Q * (size_t)T * 4 : 0;
         p->pipe_ok = false;
         p->loc_row.clear();
@@ -486,9 +492,10 @@ int bind_plan(ccdc_plan_t *p, int64_t T, int mode)
         // Few, long outputs (small T, many rounds) would leave the chip idle: cut
         // each row list into red_split chunks summed by different workgroups and
         // added up, in a fixed order, by a second pass.
-        const int64_t items = nout * ((W + vec - 1) / vec);
-        int64_t split = 1;
-        if (items < (1 << 18)) split = std::min<int64_t>({(int64_t)256, std::max<int64_t>(1, min_rows), ((1 << 19) + items - 1) / items});
+        const int elem = elem_bytes(mode);
+        const bool any = wide_anyway(r, W, ell, elem) && wide_lists(nout, W, v_elems * elem);
+        const int64_t pack = any ? 4 : vec, items = nout * ((W + pack - 1) / pack);
+        const int64_t split = list_split(items, min_rows);
         if (items * split > kMaxItems) return CCDC_ESIZE;
 
         // One-pass pipeline: single job, unrolled r, accumulators of K nodes x r
@@ -522,9 +529,7 @@ int bind_plan(ccdc_plan_t *p, int64_t T, int mode)
         }
 
         std::vector<int64_t> node_row;
-        const int elem = mode >= CCDC_BF16_SUM_XOR ? 2 : 4;
-        // elements of the packs of a call with aligned pointers
-        const int node_vec = elem == 4 || T % 4 != 0 ? vec : (T % 8 == 0 && ell % 8 == 0 ? 8 : 4);
+        const int node_vec = node_pack(any, elem, T, ell);
         // Lists by round: where a value has two readers or more besides its owner's output (r >= 3; r = 2 0.94 to 1.08 of the
         // time), with a wavefront on one segment and units that are not shared by tile already.  Over 95 such inputs of 3 MB to
         // 2 GB 0.83 of the time of equal cuts, the least 0.28 (8 nodes, r = 5, twelve files, T = 19008 f32 410 -> 113 us; 16
@@ -553,8 +558,9 @@ int bind_plan(ccdc_plan_t *p, int64_t T, int mode)
         p->red_row.swap(rows_tab);
         p->red_out.swap(outs);
         p->nout = nout;
+        p->wide_lists = any;
         p->red_split = (int)split;
-        p->red_waves = plan_groups(nout, (int64_t)p->red_row.size(), W, vec, elem, split, v_elems * elem);
+        p->red_waves = plan_groups(nout, (int64_t)p->red_row.size(), W, (int)pack, elem, split, v_elems * elem);
         p->red_workspace_bytes = split > 1 ? (size_t)split * (size_t)p->J * p->Q * (size_t)T * 4 : 0;
         p->workspace_bytes = p->red_workspace_bytes;         // until upload has fixed the chunks: the most it can be
         if (pipe_ok && pipe_cap > 1)

@@ -55,6 +55,7 @@ struct ccdc_plan_s {
     int64_t nout = 0;                   // J * K output blocks of W elements
     std::vector<int64_t> node_row;      // the lists of ccdc_node_decode_reduce where they are cut by rounds (else empty):
                                         //   [nout*red_split+1] bounds of the chunks, then the rows, as red_row
+    bool wide_lists = false;            // lists are summed in 16-byte packs at any element where rows do not divide by them
     int red_split = 1;                  // the row list of an output is summed in this many chunks
     int red_waves = 0;                  // > 0: ccdc_reduce sums it in one workgroup of that many wavefronts instead
     size_t red_workspace_bytes = 0;     // partial sums of the split reductions
@@ -130,6 +131,10 @@ CCDC_READ_LIMIT kKeptBytes = 128e6, kKeptStageBytes = 64e6, kKeptNodeBytes = 256
 CCDC_READ_LIMIT kKeptPacketBytes = 100e6, kKeptSharedBytes = 200e6;
 CCDC_READ_LIMIT kKeptWideBytes = 1.4e9;        // from these on
 
+// Packs of a segment from which on they may begin at any element, and the 16-byte packs that a call must make for it
+// (pick_wide() in common.hpp, wide_lists() in plan.cpp).
+CCDC_READ_LIMIT kAnyPacks = 32, kAnyLanes = 32e3, kAnyListPacks = 1 << 18, kAnyListBytes = 200e6;
+
 // One-pass pipeline (pipeline.hip): fixes the launch geometry (pipe_vec .. pipe_shallow) for the current device.
 void pipeline_prepare(ccdc_plan_t *p);
 // Body of ccdc_pipeline_fused.  own_part = null: partial outputs of round chunks go
@@ -172,6 +177,23 @@ constexpr uint32_t xcd_spans(uint32_t block, uint32_t blocks, uint32_t span)
     return first + xcd_contiguous(block - first, span - 1 < left - 1 ? span : left);
 }
 
+inline int elem_bytes(int mode) { return (mode == CCDC_BF16_SUM_XOR || mode == CCDC_F16_SUM_XOR) ? 2 : 4; }
+
+// Whether calls whose value length or pointers only allow one-element packs are made of 16-byte packs at any element.
+inline bool wide_anyway(int r, int64_t W, int64_t ell, int elem)
+{
+    const int64_t pack = 16 / elem;
+    return ell >= pack && (double)ell >= kAnyPacks * (double)pack && (ell == W || W - (r - 1) * ell >= pack);      // and the last segment has a pack
+}
+
+// The chunks that row lists of min_rows rows or more are cut into, `items` packs of outputs in all.
+inline int64_t list_split(int64_t items, int64_t min_rows)
+{
+    if (items >= (1 << 18)) return 1;
+    const int64_t most = min_rows < 1 ? 1 : min_rows < 256 ? min_rows : 256, wanted = ((1 << 19) + items - 1) / items;
+    return wanted < most ? wanted : most;
+}
+
 inline uint32_t cdiv(uint64_t a, uint64_t b) { return (uint32_t)((a + b - 1) / b); }
 
 constexpr int kWave = 64;
@@ -196,6 +218,21 @@ inline bool neighbours_share(const ccdc_plan_t *p, uint32_t tiles)
 {
     if (p->J > 1 || p->K * p->r < 14 || (p->r == 2 && p->m > 1)) return false;
     return tiles >= (p->m > 1 ? 200u : p->r == 2 ? 64u : 16u);
+}
+
+// Whether segments in packs of 16 bytes fill their wavefronts, or in one-element packs do not either: a node-local call whose
+// packs would leave lanes idle where one-element packs do not keeps those (14 nodes, r = 4, three files, T = 1193 f32, 75 packs a segment,
+// decoding 102 us, in lane-packed wide packs 121).
+inline bool wide_fills(int64_t ell, int elem)
+{
+    return fills_wavefronts(cdiv(ell, 16 / elem)) || !fills_wavefronts((uint32_t)ell);
+}
+
+// Elements of the packs of a node-local decoding with aligned pointers.  any: lists may be summed in packs at any element.
+inline int node_pack(bool any, int elem, int64_t T, int64_t ell)
+{
+    if (T % 4 != 0) return any && wide_fills(ell, elem) ? 16 / elem : 1;
+    return elem == 2 && T % 8 == 0 && ell % 8 == 0 ? 8 : 4;
 }
 
 // Rank of sender a's label among the members other than b.

@@ -392,16 +392,18 @@ void receive_node_prepare(ccdc_plan_t *p)
     if (cus < 1 || bytes > kReceiveNodeBytes || values > (r == 1 ? kKeptStageBytes : (r - 1) * kKeptNodeBytes)) return;
     const int vec = eb == 4 ? (p->T % 4 == 0 ? 4 : 1) : p->T % 8 == 0 && p->ell % 8 == 0 ? 8 : p->T % 4 == 0 ? 4 : 1;
     const bool fills = fills_wavefronts((uint32_t)(p->ell / vec));
+    // of the lists as they are cut for these packs (the estimates know no packs at any element, which take larger inputs on)
+    const int split = (int)list_split(p->nout * ((p->W + (p->T % 4 == 0 ? 3 : 0)) / (p->T % 4 == 0 ? 4 : 1)), p->rows_per_node + p->pipe_local_rows);
     const double rounds = (double)p->rows_per_node, per_round = 1 + (r - 1.0) * p->m, own = (double)p->pipe_local_rows;
-    const double longest = std::ceil((rounds + own) / p->red_split);                         // rows of a chunk
+    const double longest = std::ceil((rounds + own) / split);                         // rows of a chunk
     const double chain = std::min(longest, rounds) * per_round / (fills ? 2 : 1) + std::max(0.0, longest - rounds) / 4;
     const Shape best = best_shape(p, cus, {4.05, 0.55, 0.0099, 0.0022, 19e6}, bytes);
     for (int nodes : {1, p->K}) {
         const Load l = load_of(p, cus, nodes, best.vec, best.waves);
         const double us = 3.44 + 0.277 * l.gens * l.waits + (l.wide ? 0.0109 : 0.0132) * l.issue + bytes * nodes / p->K / 30e6;
         const double rows = nodes * (rounds * per_round + own) * (double)p->W;               // elements that are read
-        const double parts = p->red_split > 1 ? (double)p->red_split * nodes * r * (double)p->ell : 0;
-        const double other = 3.08 + (p->red_split > 1 ? 3.31 : 0) + 1.53e-6 * parts + (fills ? 0 : 1.59e-6 * rows / vec) +
+        const double parts = split > 1 ? (double)split * nodes * r * (double)p->ell : 0;
+        const double other = 3.08 + (split > 1 ? 3.31 : 0) + 1.53e-6 * parts + (fills ? 0 : 1.59e-6 * rows / vec) +
                              0.115e-6 * rows * eb + 0.194 * chain;
         if (us >= 0.85 * other) return;
     }

@@ -208,6 +208,7 @@ int main(int argc, char **argv)
     }
     if (std::getenv("SHIM_PAST")) ccdc::kKeptBytes = ccdc::kKeptStageBytes = ccdc::kKeptNodeBytes = ccdc::kKeptOneNodeBytes =
                                        ccdc::kKeptPacketBytes = ccdc::kKeptSharedBytes = 0;
+    if (std::getenv("SHIM_ANY")) ccdc::kAnyPacks = 1, ccdc::kAnyLanes = ccdc::kAnyListPacks = ccdc::kAnyListBytes = 0;
     const bool half = mode >= 3, real = mode != 1;
     const size_t eb = half ? 2 : 4;
 

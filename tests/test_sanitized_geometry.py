@@ -235,3 +235,22 @@ def test_lists_by_round(kernel_driver, case):  # noqa: F811
     assert res.returncode == 0, res.stdout + res.stderr
     assert f"lists by round {by_round}\n" in res.stdout, res.stdout
     assert " 0 mismatches" in res.stdout, res.stdout
+
+
+# K, r, Q, N, T, mode, jobs: lengths that no pack divides, last segments a few elements long, one pack and less
+ANY = [
+    (5, 1, 5, 15, 259, 0, 0), (6, 2, 6, 30, 517, 2, 0), (7, 3, 7, 35, 1023, 1, 0), (6, 4, 12, 15, 401, 3, 0), (7, 5, 7, 42, 333, 4, 0),
+    (5, 4, 5, 5, 3, 0, 0), (5, 2, 5, 10, 9, 3, 0), (5, 3, 5, 10, 31, 0, 0), (5, 3, 5, 30, 46, 4, 0), (4, 2, 4, 6, 401, 3, 1), (5, 2, 5, 9, 203, 0, 1),
+    (8, 6, 8, 28, 131, 0, 0), (6, 2, 6, 15, 262, 3, 0),
+]
+
+
+@pytest.mark.parametrize("reduce", ["", "0"], ids=["groups", "split"])
+@pytest.mark.parametrize("past", [False, True], ids=["kept", "past"])
+@pytest.mark.parametrize("case", ANY, ids=lambda c: "-".join(map(str, c)))
+def test_packs_at_any_element(kernel_driver, case, past, reduce):  # noqa: F811
+    """Every call in 16-byte packs where the value length does not divide by them, as small inputs are read and as large ones are."""
+    env = dict(os.environ, **ENV, SHIM_ANY="1", SHIM_NODE="0,0", **({"SHIM_PAST": "1"} if past else {}), **({"SHIM_REDUCE": "0"} if reduce else {}))
+    res = subprocess.run([kernel_driver] + [str(v) for v in case + (8, 8)], capture_output=True, text=True, env=env, timeout=600)
+    assert res.returncode == 0, res.stdout + res.stderr
+    assert " 0 mismatches" in res.stdout, res.stdout
