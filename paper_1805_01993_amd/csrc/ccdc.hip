@@ -474,7 +474,7 @@ int run_combine(const ccdc_plan_t *p, const void *V, void *Vbar, hipStream_t st)
     const uint32_t Wv = cdiv(p->W, VEC), W = (uint32_t)p->W;
     const uint64_t items = (uint64_t)p->nrows * Wv;
     if (items == 0) return CCDC_OK;
-    if (!fits_launch(items)) return CCDC_ESIZE;
+    if (!fits_rows<VEC, ANY>(p->nrows, W)) return CCDC_ESIZE;
     const double packets = (double)p->nrows * p->W;
     const bool kept = moved_bytes(p, packets) <= kKeptStageBytes ||                      // V and Vbar
                       (VEC == 1 && packets * sizeof(E) <= kKeptPacketBytes);
@@ -511,7 +511,7 @@ int run_encode(const ccdc_plan_t *p, const void *Vbar, void *X, hipStream_t st)
     using E = typename A::elem;
     const uint32_t Lv = cdiv(p->ell, VEC);
     const uint64_t items = (uint64_t)p->nround * (p->r + 1) * Lv;
-    if (!fits_launch(items)) return CCDC_ESIZE;
+    if (!fits_rows<VEC, ANY>((uint64_t)p->nround * (p->r + 1), p->ell)) return CCDC_ESIZE;
     k_encode<A, VEC, ANY><<<cdiv(items, kBlock), kBlock, 0, st>>>((const E *)Vbar, (E *)X, p->r + 1, Lv, (uint32_t)p->ell,
                                                                    (uint32_t)p->W, (uint32_t)items);
     return launched();
@@ -522,6 +522,7 @@ int run_decode(const ccdc_plan_t *p, const void *X, const void *Vbar, void *D, h
 {
     using E = typename A::elem;
     const uint32_t Lv = cdiv(p->ell, VEC), ell = (uint32_t)p->ell, W = (uint32_t)p->W;
+    if (!fits_rows<VEC, ANY>((uint64_t)p->nround * (p->r + 1), W)) return CCDC_ESIZE;
     // By sender where the packs of the padded segments can be numbered too (packets of fewer than four
     // elements have more of those than of their own); k_decode takes whatever the packets' packs allow.
     const uint64_t packs = (uint64_t)p->nround * (p->r + 1) * Lv;
@@ -537,7 +538,6 @@ int run_decode(const ccdc_plan_t *p, const void *X, const void *Vbar, void *D, h
         constexpr int PACK = ANY ? 1 : VEC;              // k_decode walks whole packets: their packs are not moved back
         const uint32_t Wv = (uint32_t)(p->W / PACK), Lw = (uint32_t)(p->ell / PACK);
         const uint64_t items = (uint64_t)p->nround * (p->r + 1) * Wv;
-        if (!fits_launch(items)) return CCDC_ESIZE;
         k_decode<A, PACK><<<cdiv(items, kBlock), kBlock, 0, st>>>(x, v, (E *)D, p->r + 1, Lw, Wv, (uint32_t)items);
         break;
     }
@@ -569,7 +569,7 @@ void launch_shuffle(const ccdc_plan_t *p, const void *V, void *X, void *D, hipSt
 template <class A, int VEC, bool ANY>
 int run_shuffle(const ccdc_plan_t *p, const void *V, void *X, void *D, hipStream_t st)
 {
-    if (!fits_launch((uint64_t)p->nround * (p->r + 1) * (uint64_t)cdiv(p->ell, VEC))) return CCDC_ESIZE;
+    if (!fits_rows<VEC, ANY>((uint64_t)p->nround * (p->r + 1), p->ell)) return CCDC_ESIZE;
     switch (p->r + 1) {
     case 2: launch_shuffle<A, VEC, ANY, 2>(p, V, X, D, st); break;
     case 3: launch_shuffle<A, VEC, ANY, 3>(p, V, X, D, st); break;
@@ -617,7 +617,7 @@ int run_reduce(const ccdc_plan_t *p, const void *V, const void *D, void *Phi, hi
     const int split = p->red_split;
     const uint64_t blocks = (uint64_t)p->nout * split * tiles;
     const int64_t chunk_stride = (int64_t)p->J * p->Q * p->T;
-    if (!fits_launch(blocks) || !fits_launch((uint64_t)chunk_stride / (ANY ? 1 : VEC))) return CCDC_ESIZE;
+    if (!fits_launch(ANY ? (uint64_t)p->nout * split * cdiv(p->W, kBlock) : blocks) || !fits_launch((uint64_t)chunk_stride / (ANY ? 1 : VEC))) return CCDC_ESIZE;
     using Acc = typename A::acc;
     const bool kept = moved_bytes(p, (double)p->nrows * p->W + (double)chunk_stride) <= kKeptStageBytes;        // V, D, Phi
     if (p->red_waves > 0) {

@@ -529,6 +529,13 @@ constexpr int kBlock = 256;
 // (pointers not aligned for the wide ones) has more items and checks again for itself.
 constexpr uint64_t kMaxLaunchItems = 2147483647ull;
 inline bool fits_launch(uint64_t items) { return items <= kMaxLaunchItems; }
+// The same for `rows` rows of `length` elements in packs; packs at any element are limited as the one-element packs that their calls
+// fall back to, whichever a call takes.
+template <int VEC, bool ANY>
+inline bool fits_rows(uint64_t rows, uint64_t length)
+{
+    return fits_launch(rows * ((length + VEC - 1) / VEC)) && (!ANY || fits_launch(rows * length));
+}
 
 // Which segment of packet b carries sender a's label: the rank of a among the members other than b.
 __device__ __forceinline__ int segment_rank(int a, int b) { return a - (a > b ? 1 : 0); }

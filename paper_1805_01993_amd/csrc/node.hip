@@ -77,17 +77,21 @@ __device__ __forceinline__ Rows chunk_of(const int64_t *__restrict__ ptr, bool b
 // is recovered here as that sender's coded pack minus the packs of the other
 // members' packets in it, which the receiver pre-combines from its own files.
 // The list is cut into `split` chunks as in ccdc_reduce.
-template <class A, int VEC, int READS, bool TOGETHER, bool ANY>
+// What bounds it: each row is a chain of table entry, rows and data.  With r+1 at compile time (R1; 0 for r > 5 and batches of
+// several files) four rows are asked for together.  Over 21 inputs of one file, r >= 3, 0.78 of the time, r = 2 0.96: 21 nodes, r = 4, T = 138 f32
+// (8 packs and less a segment) 140 -> 80 us, 16 nodes, r = 4, T = 100 h32 25.0 -> 16.6, r = 5, T = 216 bf16 52 -> 28.
+template <class A, int VEC, int R1, int READS, bool TOGETHER, bool ANY>
 __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
     const typename A::elem *__restrict__ V, const typename A::elem *__restrict__ X, typename A::elem *__restrict__ out,
     typename A::acc *__restrict__ part, const int64_t *__restrict__ node_ptr, bool by_round, const int64_t *__restrict__ node_row,
-    const int64_t *__restrict__ red_out, const int64_t *__restrict__ src_off, int r1, uint32_t Lv, uint32_t ell,
-    uint32_t W, int m, int64_t file_stride, uint32_t tiles, int split, int64_t chunk_stride, uint32_t o_first,
+    const int64_t *__restrict__ red_out, const int64_t *__restrict__ src_off, int r1_rt, uint32_t Lv, uint32_t ell,
+    uint32_t W, double per_row, int m, int64_t file_stride, uint32_t tiles, int split, int64_t chunk_stride, uint32_t o_first,
     uint32_t o_step)
 {
     using E = typename A::elem;
     using O = Ops<A, VEC>;
     using P = typename O::P;
+    const int r1 = R1 > 0 ? R1 : r1_rt;
     const uint32_t tile = blockIdx.x % tiles;
     const uint32_t oc = blockIdx.x / tiles;
     const uint32_t oi = oc / split;
@@ -99,24 +103,69 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
     const uint32_t e = in_segment<ANY, VEC>(rho * ell, W, &x);
     const auto [lo, hi] = chunk_of(node_ptr, by_round, o, s, split);
     typename O::Q acc = O::azero();
-    for (int64_t i = lo; i < hi; i++) {
-        const int64_t row = node_row[i];
-        if (!(row & 1)) {                                    // a file the node stores
-            acc = O::accum(acc, load_at<READS == kAll, ANY, P, E>(V + (row >> 1) + e));
-            continue;
+    int64_t i = lo;
+    auto own = [&](int64_t row) { return load_at<READS == kAll, ANY, P, E>(V + (row >> 1) + e); };
+    auto number = [&](int64_t row) { return (uint32_t)((double)(row >> 1) * per_row + 0.5); };      // of a packet u*(r+1)+b, exact in fp64
+    if constexpr (R1 > 0) {
+        constexpr int AHEAD = 4;
+        for (; i + AHEAD <= hi; i += AHEAD) {                    // the files the node stores come first
+            if (node_row[i + AHEAD - 1] & 1) break;
+            P v[AHEAD];
+#pragma unroll
+            for (int t = 0; t < AHEAD; t++) v[t] = own(node_row[i + t]);
+#pragma unroll
+            for (int t = 0; t < AHEAD; t++) acc = O::accum(acc, v[t]);
         }
-        const int64_t pk = (row >> 1) / W;                   // packet u*(r+1)+b meant for this node
-        const uint32_t u = (uint32_t)(pk / r1);
-        const int b = (int)(pk - (int64_t)u * r1);
-        const int a = (int)rho < b ? (int)rho : (int)rho + 1;
-        const int64_t *src = src_off + (size_t)u * r1;
-        P d = load_at<READS != kPast, ANY, P, E>(X + ((size_t)u * r1 + a) * ell + x);
-        for (int b2 = 0; b2 < r1; b2++) {
-            if (b2 == a || b2 == b) continue;
-            const uint32_t pos = segment_rank(a, b2) * ell + x;
-            if (pos < W) d = O::uncode(d, packet_pack<O, READS == kAll, TOGETHER, ANY>(V + src[b2], pos, W, m, file_stride));
+        for (; i < hi && !(node_row[i] & 1); i++) acc = O::accum(acc, own(node_row[i]));
+        for (; i < hi; i += AHEAD) {
+            P coded[AHEAD], side[AHEAD][R1];                     // side: of the members, used for those that are neither sender nor receiver
+            int from[AHEAD], to[AHEAD];
+#pragma unroll
+            for (int t = 0; t < AHEAD; t++) {                    // past the list's end the last row stands in and is not used
+                const uint32_t pk = wave_uniform(number(node_row[i + t < hi ? i + t : hi - 1])), u = pk / R1;
+                const int b = (int)(pk - u * R1), a = (int)rho < b ? (int)rho : (int)rho + 1;
+                const int64_t *src = src_off + (size_t)u * R1;
+                from[t] = a;
+                to[t] = b;
+                coded[t] = load_at<READS != kPast, ANY, P, E>(X + ((size_t)u * R1 + a) * ell + x);
+#pragma unroll
+                for (int b2 = 0; b2 < R1; b2++) {
+                    const uint32_t pos = segment_rank(a, b2) * ell + x;
+                    const bool used = b2 != a && b2 != b && pos < W;
+                    side[t][b2] = packet_pack<O, READS == kAll, false, ANY>(V + src[b2], used ? pos : 0, W, 1, 0);
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < AHEAD; t++) {
+                if (i + t >= hi) break;
+                P d = coded[t];
+#pragma unroll
+                for (int b2 = 0; b2 < R1; b2++) {
+                    const bool used = b2 != from[t] && b2 != to[t] && segment_rank(from[t], b2) * ell + x < W;
+                    d = O::select(used, O::uncode(d, side[t][b2]), d);
+                }
+                acc = O::accum(acc, d);
+            }
         }
-        acc = O::accum(acc, d);
+    } else {
+        for (; i < hi; i++) {
+            const int64_t row = node_row[i];
+            if (!(row & 1)) {                                    // a file the node stores
+                acc = O::accum(acc, own(row));
+                continue;
+            }
+            const uint32_t pk = number(row), u = pk / r1;
+            const int b = (int)(pk - u * r1);
+            const int a = (int)rho < b ? (int)rho : (int)rho + 1;
+            const int64_t *src = src_off + (size_t)u * r1;
+            P d = load_at<READS != kPast, ANY, P, E>(X + ((size_t)u * r1 + a) * ell + x);
+            for (int b2 = 0; b2 < r1; b2++) {
+                if (b2 == a || b2 == b) continue;
+                const uint32_t pos = segment_rank(a, b2) * ell + x;
+                if (pos < W) d = O::uncode(d, packet_pack<O, READS == kAll, TOGETHER, ANY>(V + src[b2], pos, W, m, file_stride));
+            }
+            acc = O::accum(acc, d);
+        }
     }
     if (split > 1) store_at<false, ANY, typename O::Q, typename A::acc>(part + (int64_t)s * chunk_stride + red_out[o] + e, acc);
     else store_at<false, ANY, P, E>(out + red_out[o] + e, O::narrow(acc));
@@ -368,15 +417,17 @@ void by_shape(const ccdc_plan_t *p, bool together, F launch)
 //   One node, its two calls for every node of the cluster in turn, everything kept / everything past: 6 nodes, r = 3, ten files
 // a batch, h32: 96 MB 343 / 495, 480 MB 662 / 702; 8 nodes, r = 6, f32: 358 MB 329 / 375, 1.4 GB 665 / 619; 10 nodes, r = 3,
 // f32, 1.8 GB 1130 / 994; 24 nodes, r = 4, T = 2047 f32 (2.1 GB, one-element packs) 17580 / 14570.
+//   Decoding by rounds, where a value's readers run together, gains through the caches also far beyond that: 28 inputs of 1.0 to 2.0 GB
+// 0.79 of the time that they take past them in equal cuts (kReadTogether times the limit: all that fit the device).
+constexpr double kReadTogether = 64;
 template <int VEC>
-Reads node_reads(const ccdc_plan_t *p, int node, bool by_wavefront)
+Reads node_reads(const ccdc_plan_t *p, int node, bool by_wavefront, bool by_round = false)
 {
     const double values = moved_bytes(p, 0);
     if (node >= 0) return values <= kKeptOneNodeBytes ? kAll : kPast;
     if (!by_wavefront || VEC == 1) return kAll;
     if (p->r == 1) return values <= kKeptStageBytes ? kAll : kPast;
-    if (!p->node_row.empty()) return kAll;           // read together, see lists_by_round()
-    return values / p->J <= (p->r - 1) * kKeptNodeBytes ? kAll : kCoded;
+    return values / p->J <= (p->r - 1) * kKeptNodeBytes * (by_round ? kReadTogether : 1) ? kAll : kCoded;
 }
 
 // Calls launch(reads) with that as a compile-time constant.  CODED: whether kCoded is one of the answers there are.
@@ -398,7 +449,7 @@ int run_node_encode(const ccdc_plan_t *p, int node, const void *V, void *X, hipS
     const int64_t rows = node < 0 ? p->nrows : p->rows_per_node;
     const uint64_t items = (uint64_t)rows * Lv;
     if (items == 0) return CCDC_OK;
-    if (!fits_launch(items)) return CCDC_ESIZE;
+    if (!fits_rows<VEC, ANY>(rows, ell)) return CCDC_ESIZE;
     const int32_t *list = node < 0 ? nullptr : p->d_node_rows + (size_t)node * p->rows_per_node;
     const uint32_t wave_tiles = cdiv(Lv, kWave);
     const uint64_t units = (uint64_t)rows * wave_tiles;
@@ -439,7 +490,7 @@ int run_node_decode_reduce(const ccdc_plan_t *p, int node, const void *V, const 
     const uint32_t o_first = node < 0 ? 0u : (uint32_t)node, o_step = node < 0 ? 1u : (uint32_t)p->K;
     const int64_t chunk_stride = (int64_t)p->J * p->Q * p->T;
     const uint64_t blocks = (uint64_t)count * split * tiles;
-    if (!fits_launch(blocks) || !fits_launch((uint64_t)chunk_stride / (ANY ? 1 : VEC))) return CCDC_ESIZE;
+    if (!fits_launch(ANY ? (uint64_t)count * split * cdiv(W, kBlock) : blocks) || !fits_launch((uint64_t)chunk_stride / (ANY ? 1 : VEC))) return CCDC_ESIZE;
     WorkspaceOrder order(p, st, split > 1);
     const uint32_t wave_tiles = cdiv(Lv, kWave);
     const uint64_t units = (uint64_t)count * split * p->r * wave_tiles;
@@ -447,7 +498,7 @@ int run_node_decode_reduce(const ccdc_plan_t *p, int node, const void *V, const 
         auto launch = [&](auto r1, auto files) {
             constexpr int R1 = decltype(r1)::value;
             constexpr int FILES = decltype(files)::value;
-            by_node_reads<(VEC > 1 && R1 > 2)>(node_reads<VEC>(p, node, true), [&](auto reads) {
+            by_node_reads<(VEC > 1 && R1 > 2)>(node_reads<VEC>(p, node, true, by_round), [&](auto reads) {
                 auto numbered = [&](auto numbering) {
                     k_node_decode_reduce_wave<A, VEC, R1, FILES, decltype(reads)::value, decltype(numbering)::value, ANY><<<cdiv(units, kWaves), kBlock, 0, st>>>(
                         (const E *)V, (const E *)X, (E *)Phi, (Acc *)p->d_workspace, bounds, by_round, rows, p->d_red_out,
@@ -466,12 +517,19 @@ int run_node_decode_reduce(const ccdc_plan_t *p, int node, const void *V, const 
         by_shape<Ops<A, VEC>, ANY>(p, p->m > 2 || p->r > 2, launch);     // r = 2: one packet in the making, as in combine
     } else {
         by_node_reads<false>(node_reads<VEC>(p, node, false), [&](auto reads) {
-            by_files<Ops<A, VEC>, ANY>(p->m > 2, [&](auto together) {
-                k_node_decode_reduce<A, VEC, decltype(reads)::value, decltype(together)::value, ANY><<<(uint32_t)blocks, kBlock, 0, st>>>(
+            auto launch = [&](auto r1, auto together) {
+                k_node_decode_reduce<A, VEC, decltype(r1)::value, decltype(reads)::value, decltype(together)::value, ANY><<<(uint32_t)blocks, kBlock, 0, st>>>(
                     (const E *)V, (const E *)X, (E *)Phi, (Acc *)p->d_workspace, bounds, by_round, rows, p->d_red_out,
-                    p->d_src_off, p->r + 1, Lv, ell, W, p->m, (int64_t)p->Q * p->T, tiles, split, chunk_stride, o_first,
-                    o_step);
-            });
+                    p->d_src_off, p->r + 1, Lv, ell, W, 1.0 / (double)p->W, p->m, (int64_t)p->Q * p->T, tiles, split, chunk_stride,
+                    o_first, o_step);
+            };
+            if (p->m > 1 || p->r > 5)
+                by_files<Ops<A, VEC>, ANY>(p->m > 2, [&](auto together) { launch(std::integral_constant<int, 0>(), together); });
+            else if (p->r == 1) launch(std::integral_constant<int, 2>(), std::false_type());
+            else if (p->r == 2) launch(std::integral_constant<int, 3>(), std::false_type());
+            else if (p->r == 3) launch(std::integral_constant<int, 4>(), std::false_type());
+            else if (p->r == 4) launch(std::integral_constant<int, 5>(), std::false_type());
+            else launch(std::integral_constant<int, 6>(), std::false_type());
         });
     }
     int rc = launched();

@@ -293,9 +293,13 @@ int build_compression_plan(int K, int r, int Q, int N, ccdc_plan_t **out)
 
 namespace {
 
-// Whether lists are summed in packs of 16 bytes where rows do not divide by them: where those fill the chip without cutting the lists, or
-// the second launch that cut ones take is little of the time.
-bool wide_lists(int64_t nout, int64_t W, double bytes) { return (double)(nout * ((W + 3) / 4)) >= kAnyListPacks || bytes >= kAnyListBytes; }
+// Whether lists are summed in packs of 16 bytes where rows do not divide by them: where those fill the chip without cutting the lists, where
+// the second launch that cut ones take is little of the time, and where one-element packs need it too and the call is not short.
+bool wide_lists(int64_t nout, int64_t W, int elem, double bytes)
+{
+    return (double)(nout * ((W + 3) / 4)) >= kAnyListPacks || bytes >= kAnyListBytes ||
+           (nout * W < (1 << 18) && bytes >= (elem == 2 ? 0.16 : 0.64) * kAnyListBytes);
+}
 
 // Wavefronts of a workgroup that sums a whole row list (ccdc_reduce in one launch), 0 where the list is better split over
 // workgroups and added by a second kernel.  Only for plans whose outputs are too few to fill the chip with whole lists
@@ -382,7 +386,7 @@ int bind_compression(ccdc_plan_t *p, int64_t T, int mode)
             outs[k] = (int64_t)k * W;
             min_rows = std::min(min_rows, ptr[k + 1] - ptr[k]);
         }
-        const bool any = wide_anyway(p->r, W, W, 4) && wide_lists(nout, W, (double)p->N * p->Q * (double)T * 4);
+        const bool any = wide_anyway(p->r, W, W, 4) && wide_lists(nout, W, 4, (double)p->N * p->Q * (double)T * 4);
         const int pack = any ? 4 : vec;                      // elements of a call's packs
         const int64_t items = nout * ((W + pack - 1) / pack);
         const int64_t split = list_split(items, min_rows);
@@ -493,7 +497,7 @@ int bind_plan(ccdc_plan_t *p, int64_t T, int mode)
         // each row list into red_split chunks summed by different workgroups and
         // added up, in a fixed order, by a second pass.
         const int elem = elem_bytes(mode);
-        const bool any = wide_anyway(r, W, ell, elem) && wide_lists(nout, W, v_elems * elem);
+        const bool any = wide_anyway(r, W, ell, elem) && wide_lists(nout, W, elem, v_elems * elem);
         const int64_t pack = any ? 4 : vec, items = nout * ((W + pack - 1) / pack);
         const int64_t split = list_split(items, min_rows);
         if (items * split > kMaxItems) return CCDC_ESIZE;
