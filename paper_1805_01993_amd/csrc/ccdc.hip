@@ -824,6 +824,8 @@ int ccdc_combine(const ccdc_plan_t *plan, const void *V, void *Vbar, void *strea
     bool any = false;
     if (rc != CCDC_OK) return rc;
     if ((rc = pick_wide(plan, &vec, &any, makes_lanes(plan, plan->nrows, plan->W, plan->m == 1 ? 1 : 4), V, (const void *)Vbar)) != CCDC_OK) return rc;
+    // (packets of up to 16 packs keep to a wavefront each)
+    if (!any && plan->W / vec > 16) narrow_files(plan, plan->compression ? plan->batch_first[1] : plan->m, plan->nrows, plan->W, &vec);
     hipStream_t st = (hipStream_t)stream;
     CCDC_DISPATCH(plan, vec, any, (run_combine<A, VEC, ANY>(plan, V, Vbar, st)));
 }
@@ -867,6 +869,7 @@ int ccdc_shuffle_fused(const ccdc_plan_t *plan, const void *V, void *X, void *D,
     if (rc != CCDC_OK) return rc;
     if (plan->compression) return CCDC_ESTATE;       // nothing is coded in that scheme
     if ((rc = pick_wide(plan, &vec, &any, shuffle_any(plan), V, (const void *)X, (const void *)D)) != CCDC_OK) return rc;
+    if (!any) narrow_files(plan, plan->m, plan->nrows, plan->ell, &vec);
     hipStream_t st = (hipStream_t)stream;
     CCDC_DISPATCH(plan, vec, any, (run_shuffle<A, VEC, ANY>(plan, V, X, D, st)));
 }

@@ -616,6 +616,7 @@ int ccdc_node_encode(const ccdc_plan_t *plan, int node, const void *V, void *X, 
     bool any = false;
     if (rc != CCDC_OK) return rc;
     if ((rc = pick_wide(plan, &vec, &any, wide_fills(plan->ell, elem_bytes(plan->mode)) && makes_lanes(plan, node < 0 ? plan->nrows : plan->rows_per_node, plan->ell, 2), V, (const void *)X)) != CCDC_OK) return rc;
+    if (!any) narrow_files(plan, plan->m, node < 0 ? plan->nrows : plan->rows_per_node, plan->ell, &vec);
     hipStream_t st = (hipStream_t)stream;
     switch (plan->mode) {
     case CCDC_F32_SUM: return node_encode<SumF32>(plan, vec, any, node, V, X, st);
