@@ -340,20 +340,30 @@ void lists_by_round(const ccdc_plan_t *p, const std::vector<int64_t> &ptr, const
         while (own[o] < ptr[o + 1] - ptr[o] && !(rows[ptr[o] + own[o]] & 1)) own[o]++;
         for (int64_t s = 0; s < split; s++) at[o * split + s + 1] = own[o] * (s + 1) / split - own[o] * s / split;
     }
-    for (int64_t u = 0; u < p->nround; u++)
-        for (int b = 0; b < r1; b++) at[p->round_member[u * r1 + b] * split + u % split + 1]++;
+    const int32_t *member = p->round_member.data();
+    for (int64_t u = 0, s = 0; u < p->nround; u++, s = s + 1 == split ? 0 : s + 1)
+        for (int b = 0; b < r1; b++) at[member[u * r1 + b] * split + s + 1]++;
     const int64_t longest = *std::max_element(at.begin(), at.end());
     if ((double)longest * (double)(nout * split) > most * (double)ptr[nout]) return;
     for (int64_t i = 0; i < nout * split; i++) at[i + 1] += at[i];
-    lists->reserve(at.size() + (size_t)at.back());
-    lists->assign(at.begin(), at.end());
     lists->resize(at.size() + (size_t)at.back());
+    std::copy(at.begin(), at.end(), lists->begin());
     int64_t *list = lists->data() + at.size();
-    for (int64_t o = 0; o < nout; o++)
+    for (int64_t o = 0; o < nout; o++) {                     // a list after the other: its chunks' ends stay in the first cache
+        int64_t *end = at.data() + o * split;
         for (int64_t s = 0; s < split; s++)
-            for (int64_t i = own[o] * s / split; i < own[o] * (s + 1) / split; i++) list[at[o * split + s]++] = rows[ptr[o] + i];
-    for (int64_t u = 0; u < p->nround; u++)
-        for (int b = 0; b < r1; b++) list[at[p->round_member[u * r1 + b] * split + u % split]++] = (((u * r1 + b) * W) << 1) | 1;
+            for (int64_t i = own[o] * s / split; i < own[o] * (s + 1) / split; i++) list[end[s]++] = rows[ptr[o] + i];
+        const int32_t *packet = p->node_rows.data() + o * p->rows_per_node;
+        uint32_t u = 0;
+        int64_t s = 0;
+        for (int64_t j = 0; j < p->rows_per_node; j++) {
+            const uint32_t next = (uint32_t)packet[j] / (uint32_t)r1, on = next - u;
+            u = next;
+            s += on < split ? on : on % split;
+            s -= s >= split ? split : 0;
+            list[end[s]++] = ((packet[j] * W) << 1) | 1;
+        }
+    }
 }
 
 // ccdc_plan_bind for the compression-only scheme: the packet is sent whole (no
@@ -468,8 +478,11 @@ int bind_plan(ccdc_plan_t *p, int64_t T, int mode)
         for (int64_t bt = 0; bt < p->nbatch; bt++)
             for (int s = 0; s < r; s++)
                 cnt[(int64_t)p->batch_job[bt] * p->K + p->batch_label[bt * r + s] + 1] += p->m;
-        for (int64_t i = 0; i < p->nround * r1; i++)
-            cnt[(int64_t)p->batch_job[p->round_batch[i]] * p->K + p->round_member[i] + 1] += 1;
+        if (p->J == 1)                                           // every node is in as many rounds
+            for (int64_t o = 0; o < nout; o++) cnt[o + 1] += p->rows_per_node;
+        else
+            for (int64_t i = 0; i < p->nround * r1; i++)
+                cnt[(int64_t)p->batch_job[p->round_batch[i]] * p->K + p->round_member[i] + 1] += 1;
         for (int64_t o = 0; o < nout; o++) cnt[o + 1] += cnt[o];
         std::vector<int64_t> rows_tab((size_t)cnt[nout]);
         std::vector<int64_t> fill(cnt.begin(), cnt.end() - 1);
@@ -482,9 +495,15 @@ int bind_plan(ccdc_plan_t *p, int64_t T, int mode)
                     rows_tab[fill[o]++] = ((file * p->Q + (int64_t)k * p->c) * T) << 1;
                 }
             }
-        for (int64_t i = 0; i < p->nround * r1; i++) {
-            const int64_t o = (int64_t)p->batch_job[p->round_batch[i]] * p->K + p->round_member[i];
-            rows_tab[fill[o]++] = ((i * W) << 1) | 1;
+        if (p->J == 1) {                                         // a list after the other
+            for (int64_t o = 0; o < nout; o++)
+                for (int64_t j = 0; j < p->rows_per_node; j++)
+                    rows_tab[fill[o] + j] = ((p->node_rows[o * p->rows_per_node + j] * W) << 1) | 1;
+        } else {
+            for (int64_t i = 0; i < p->nround * r1; i++) {
+                const int64_t o = (int64_t)p->batch_job[p->round_batch[i]] * p->K + p->round_member[i];
+                rows_tab[fill[o]++] = ((i * W) << 1) | 1;
+            }
         }
         std::vector<int64_t> outs((size_t)nout);
         int64_t min_rows = std::numeric_limits<int64_t>::max();
