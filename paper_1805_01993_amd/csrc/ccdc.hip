@@ -421,7 +421,7 @@ void release_device(ccdc_plan_t *p)
 {
     if (!p) return;
     if (p->uploaded || p->d_src_off || p->d_red_ptr || p->d_red_row || p->d_red_out || p->d_loc_row || p->d_pipe_row ||
-        p->d_row_files || p->d_node_rows || p->d_node_row || p->d_workspace || p->ws_event) {
+        p->d_row_files || p->d_node_rows || p->d_node_list || p->d_workspace || p->ws_event) {
         int cur = -1;
         const bool sw = hipGetDevice(&cur) == hipSuccess && p->device >= 0 && cur != p->device &&
                         hipSetDevice(p->device) == hipSuccess;
@@ -433,7 +433,7 @@ void release_device(ccdc_plan_t *p)
         (void)hipFree(p->d_pipe_row);
         (void)hipFree(p->d_row_files);
         (void)hipFree(p->d_node_rows);
-        (void)hipFree(p->d_node_row);
+        (void)hipFree(p->d_node_list);
         (void)hipFree(p->d_workspace);
         if (p->ws_event) (void)hipEventDestroy((hipEvent_t)p->ws_event);
         if (sw) (void)hipSetDevice(cur);
@@ -442,7 +442,7 @@ void release_device(ccdc_plan_t *p)
     p->d_pipe_row = nullptr;
     p->d_row_files = nullptr;
     p->d_node_rows = nullptr;
-    p->d_node_row = nullptr;
+    p->d_node_list = nullptr;
     p->d_workspace = nullptr;
     p->pipe_chunks = 0;
     p->ws_event = nullptr;
@@ -694,7 +694,7 @@ int ccdc_plan_upload(ccdc_plan_t *plan)
     if (rc == CCDC_OK) rc = to_device(plan->pipe_row, &plan->d_pipe_row);
     if (rc == CCDC_OK && !plan->row_files.empty()) rc = to_device(plan->row_files, &plan->d_row_files);
     if (rc == CCDC_OK && !plan->node_rows.empty()) rc = to_device(plan->node_rows, &plan->d_node_rows);
-    if (rc == CCDC_OK && !plan->node_row.empty()) rc = to_device(plan->node_row, &plan->d_node_row);
+    if (rc == CCDC_OK && !plan->node_list.empty()) rc = to_device(plan->node_list, &plan->d_node_list);
     if (rc == CCDC_OK && plan->workspace_bytes > 0 &&
         hipMalloc(&plan->d_workspace, plan->workspace_bytes) != hipSuccess) {
         plan->d_workspace = nullptr;

@@ -57,15 +57,19 @@ __device__ __forceinline__ uint32_t in_segment(uint32_t first, uint32_t W, uint3
     return first + *x;
 }
 
-// Bounds of chunk s of output block o's row list: in a table where lists are cut by rounds, else an equal part of the list.
+// Chunk s of output block o's row list: an equal part of the rows [lo, hi), files the node stores before packets it receives; or, where
+// the lists are cut by rounds, an equal part of the former (own_rows of them) and packets [first, last) of a list of their own.
 struct Rows {
     int64_t lo, hi;
+    uint32_t first, last;
 };
-__device__ __forceinline__ Rows chunk_of(const int64_t *__restrict__ ptr, bool by_round, uint32_t o, int s, int split)
+__device__ __forceinline__ Rows chunk_of(const int64_t *__restrict__ red_ptr, const int32_t *__restrict__ list, uint32_t own_rows,
+                                         uint32_t o, int s, int split)
 {
-    if (by_round) return {ptr[o * split + s], ptr[o * split + s + 1]};
-    const int64_t first = ptr[o], n = ptr[o + 1] - first;
-    return {first + n * s / split, first + n * (s + 1) / split};
+    const int64_t start = red_ptr[o], n = list ? own_rows : red_ptr[o + 1] - start;
+    const int64_t lo = start + n * s / split, hi = start + n * (s + 1) / split;
+    if (!list) return {lo, hi, 0, 0};
+    return {lo, hi, (uint32_t)list[o * split + s], (uint32_t)list[o * split + s + 1]};
 }
 
 // --------------------------------------------- a receiver's decoding + output
@@ -83,7 +87,8 @@ __device__ __forceinline__ Rows chunk_of(const int64_t *__restrict__ ptr, bool b
 template <class A, int VEC, int R1, int READS, bool TOGETHER, bool ANY>
 __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
     const typename A::elem *__restrict__ V, const typename A::elem *__restrict__ X, typename A::elem *__restrict__ out,
-    typename A::acc *__restrict__ part, const int64_t *__restrict__ node_ptr, bool by_round, const int64_t *__restrict__ node_row,
+    typename A::acc *__restrict__ part, const int64_t *__restrict__ red_ptr, const int64_t *__restrict__ red_row, const int32_t *__restrict__ list,
+    const int32_t *__restrict__ list_packets, uint32_t own_rows,
     const int64_t *__restrict__ red_out, const int64_t *__restrict__ src_off, int r1_rt, uint32_t Lv, uint32_t ell,
     uint32_t W, double per_row, int m, int64_t file_stride, uint32_t tiles, int split, int64_t chunk_stride, uint32_t o_first,
     uint32_t o_step)
@@ -101,28 +106,35 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
     uint32_t x = column<ANY, VEC>(pack - rho * Lv, ell);
     if (rho >= (uint32_t)r1 - 1 || rho * ell + x >= W) return;
     const uint32_t e = in_segment<ANY, VEC>(rho * ell, W, &x);
-    const auto [lo, hi] = chunk_of(node_ptr, by_round, o, s, split);
+    const Rows rows = chunk_of(red_ptr, list, own_rows, o, s, split);
     typename O::Q acc = O::azero();
-    int64_t i = lo;
+    int64_t i = rows.lo, hi = rows.hi;
     auto own = [&](int64_t row) { return load_at<READS == kAll, ANY, P, E>(V + (row >> 1) + e); };
-    auto number = [&](int64_t row) { return (uint32_t)((double)(row >> 1) * per_row + 0.5); };      // of a packet u*(r+1)+b, exact in fp64
+    // a packet u*(r+1)+b; a row is its first element: its number = element / W, exact in fp64
+    auto packet = [&](int64_t at) {
+        return list ? (uint32_t)list_packets[at] : (uint32_t)((double)(red_row[at] >> 1) * per_row + 0.5);
+    };
     if constexpr (R1 > 0) {
         constexpr int AHEAD = 4;
         for (; i + AHEAD <= hi; i += AHEAD) {                    // the files the node stores come first
-            if (node_row[i + AHEAD - 1] & 1) break;
+            if (red_row[i + AHEAD - 1] & 1) break;
             P v[AHEAD];
 #pragma unroll
-            for (int t = 0; t < AHEAD; t++) v[t] = own(node_row[i + t]);
+            for (int t = 0; t < AHEAD; t++) v[t] = own(red_row[i + t]);
 #pragma unroll
             for (int t = 0; t < AHEAD; t++) acc = O::accum(acc, v[t]);
         }
-        for (; i < hi && !(node_row[i] & 1); i++) acc = O::accum(acc, own(node_row[i]));
+    }
+    for (; i < hi && !(red_row[i] & 1); i++) acc = O::accum(acc, own(red_row[i]));
+    if (list) i = rows.first, hi = rows.last;
+    if constexpr (R1 > 0) {
+        constexpr int AHEAD = 4;
         for (; i < hi; i += AHEAD) {
             P coded[AHEAD], side[AHEAD][R1];                     // side: of the members, used for those that are neither sender nor receiver
             int from[AHEAD], to[AHEAD];
 #pragma unroll
             for (int t = 0; t < AHEAD; t++) {                    // past the list's end the last row stands in and is not used
-                const uint32_t pk = wave_uniform(number(node_row[i + t < hi ? i + t : hi - 1])), u = pk / R1;
+                const uint32_t pk = wave_uniform(packet(i + t < hi ? i + t : hi - 1)), u = pk / R1;
                 const int b = (int)(pk - u * R1), a = (int)rho < b ? (int)rho : (int)rho + 1;
                 const int64_t *src = src_off + (size_t)u * R1;
                 from[t] = a;
@@ -149,12 +161,7 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
         }
     } else {
         for (; i < hi; i++) {
-            const int64_t row = node_row[i];
-            if (!(row & 1)) {                                    // a file the node stores
-                acc = O::accum(acc, own(row));
-                continue;
-            }
-            const uint32_t pk = number(row), u = pk / r1;
+            const uint32_t pk = packet(i), u = pk / r1;
             const int b = (int)(pk - u * r1);
             const int a = (int)rho < b ? (int)rho : (int)rho + 1;
             const int64_t *src = src_off + (size_t)u * r1;
@@ -242,7 +249,8 @@ enum Numbering {
 template <class A, int VEC, int R1, int FILES, int READS, int NUMBERING, bool ANY>
 __global__ __launch_bounds__(kBlock) void k_node_decode_reduce_wave(
     const typename A::elem *__restrict__ V, const typename A::elem *__restrict__ X, typename A::elem *__restrict__ out,
-    typename A::acc *__restrict__ part, const int64_t *__restrict__ node_ptr, bool by_round, const int64_t *__restrict__ node_row,
+    typename A::acc *__restrict__ part, const int64_t *__restrict__ red_ptr, const int64_t *__restrict__ red_row, const int32_t *__restrict__ list,
+    const int32_t *__restrict__ list_packets, uint32_t own_rows,
     const int64_t *__restrict__ red_out, const int64_t *__restrict__ src_off, uint32_t Lv, uint32_t ell, uint32_t W,
     double per_row, int m, int64_t file_stride, uint32_t tiles, int split, int64_t chunk_stride, uint32_t o_first,
     uint32_t o_step, uint32_t units)
@@ -281,25 +289,26 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce_wave(
     uint32_t x = column<ANY, VEC>(pack, ell);
     if (pack >= Lv || rho * ell + x >= W) return;
     const uint32_t e = in_segment<ANY, VEC>(rho * ell, W, &x);
-    const auto [lo, hi] = chunk_of(node_ptr, by_round, o, s, split);
+    const Rows rows = chunk_of(red_ptr, list, own_rows, o, s, split);
     typename O::Q acc = O::azero();
-    int64_t i = lo;
+    int64_t i = rows.lo, hi = rows.hi;
     // the files the node stores come first in the list
     auto own = [&](int64_t row) { return load_at<READS == kAll, ANY, P, E>(V + (row >> 1) + e); };
     for (; i + 4 <= hi; i += 4) {
-        const int64_t row[4] = {node_row[i], node_row[i + 1], node_row[i + 2], node_row[i + 3]};
+        const int64_t row[4] = {red_row[i], red_row[i + 1], red_row[i + 2], red_row[i + 3]};
         if (row[3] & 1) break;
         const P v[4] = {own(row[0]), own(row[1]), own(row[2]), own(row[3])};
 #pragma unroll
         for (int t = 0; t < 4; t++) acc = O::accum(acc, v[t]);
     }
-    for (; i < hi && !(node_row[i] & 1); i++) acc = O::accum(acc, own(node_row[i]));
+    for (; i < hi && !(red_row[i] & 1); i++) acc = O::accum(acc, own(red_row[i]));
+    if (list) i = rows.first, hi = rows.last;
     struct Packet {
         P coded, side[r > 1 ? r - 1 : 1];
     };
     auto load = [&](int64_t at, Packet &k) {
-        // the entry is the packet's first element: packet number = element / W, exact in fp64
-        const uint32_t pk = wave_uniform((uint32_t)((double)(node_row[at] >> 1) * per_row + 0.5));
+        // a row is the packet's first element: packet number = element / W, exact in fp64
+        const uint32_t pk = list ? (uint32_t)list_packets[at] : wave_uniform((uint32_t)((double)(red_row[at] >> 1) * per_row + 0.5));
         const uint32_t u = pk / R1;
         const int b = (int)(pk - u * R1);
         const int a = rho < b ? rho : rho + 1;
@@ -483,9 +492,9 @@ int run_node_decode_reduce(const ccdc_plan_t *p, int node, const void *V, const 
     const uint32_t Lv = cdiv(p->ell, VEC), ell = (uint32_t)p->ell, W = (uint32_t)p->W;
     const uint32_t tiles = cdiv((uint64_t)Lv * p->r, kBlock);          // the last segment may be short
     const int split = p->red_split;
-    const bool by_round = p->d_node_row != nullptr;
-    const int64_t *bounds = by_round ? p->d_node_row : p->d_red_ptr;
-    const int64_t *rows = by_round ? p->d_node_row + (size_t)p->nout * split + 1 : p->d_red_row;
+    const bool by_round = p->d_node_list != nullptr;
+    const int32_t *packets = by_round ? p->d_node_list + (size_t)p->nout * split + 1 : nullptr;
+    const uint32_t own_rows = (uint32_t)(p->red_ptr[1] - p->red_ptr[0] - p->rows_per_node);      // of a node, one job
     const uint32_t count = node < 0 ? (uint32_t)p->nout : (uint32_t)p->J;
     const uint32_t o_first = node < 0 ? 0u : (uint32_t)node, o_step = node < 0 ? 1u : (uint32_t)p->K;
     const int64_t chunk_stride = (int64_t)p->J * p->Q * p->T;
@@ -501,7 +510,7 @@ int run_node_decode_reduce(const ccdc_plan_t *p, int node, const void *V, const 
             by_node_reads<(VEC > 1 && R1 > 2)>(node_reads<VEC>(p, node, true, by_round), [&](auto reads) {
                 auto numbered = [&](auto numbering) {
                     k_node_decode_reduce_wave<A, VEC, R1, FILES, decltype(reads)::value, decltype(numbering)::value, ANY><<<cdiv(units, kWaves), kBlock, 0, st>>>(
-                        (const E *)V, (const E *)X, (E *)Phi, (Acc *)p->d_workspace, bounds, by_round, rows, p->d_red_out,
+                        (const E *)V, (const E *)X, (E *)Phi, (Acc *)p->d_workspace, p->d_red_ptr, p->d_red_row, p->d_node_list, packets, own_rows, p->d_red_out,
                         p->d_src_off, Lv, ell, W, 1.0 / (double)p->W, p->m, (int64_t)p->Q * p->T, wave_tiles, split, chunk_stride,
                         o_first, o_step, (uint32_t)units);
                 };
@@ -519,7 +528,7 @@ int run_node_decode_reduce(const ccdc_plan_t *p, int node, const void *V, const 
         by_node_reads<false>(node_reads<VEC>(p, node, false), [&](auto reads) {
             auto launch = [&](auto r1, auto together) {
                 k_node_decode_reduce<A, VEC, decltype(r1)::value, decltype(reads)::value, decltype(together)::value, ANY><<<(uint32_t)blocks, kBlock, 0, st>>>(
-                    (const E *)V, (const E *)X, (E *)Phi, (Acc *)p->d_workspace, bounds, by_round, rows, p->d_red_out,
+                    (const E *)V, (const E *)X, (E *)Phi, (Acc *)p->d_workspace, p->d_red_ptr, p->d_red_row, p->d_node_list, packets, own_rows, p->d_red_out,
                     p->d_src_off, p->r + 1, Lv, ell, W, 1.0 / (double)p->W, p->m, (int64_t)p->Q * p->T, tiles, split, chunk_stride,
                     o_first, o_step);
             };

@@ -330,30 +330,27 @@ int plan_groups(int64_t nout, int64_t rows, int64_t W, int vec, int elem, int64_
 // same rounds, s, s + split, s + 2 split, .. (a chunk of neighbouring rounds would have all of the first node's),
 // and units that are numbered by chunk (node.hip) read them together, behind one L2.  The price is chunks of unequal length, and
 // a chunk is a chain of waits: no such lists where the longest is over `most` times the mean.
-void lists_by_round(const ccdc_plan_t *p, const std::vector<int64_t> &ptr, const std::vector<int64_t> &rows, int64_t split, int64_t W,
-                    double most, std::vector<int64_t> *lists)
+void lists_by_round(const ccdc_plan_t *p, int64_t local_rows, int64_t split, double most, std::vector<int32_t> *lists)
 {
-    const int64_t nout = (int64_t)ptr.size() - 1;
     const int r1 = p->r + 1;
-    std::vector<int64_t> at((size_t)(nout * split) + 1, 0), own((size_t)nout, 0);
-    for (int64_t o = 0; o < nout; o++) {
-        while (own[o] < ptr[o + 1] - ptr[o] && !(rows[ptr[o] + own[o]] & 1)) own[o]++;
-        for (int64_t s = 0; s < split; s++) at[o * split + s + 1] = own[o] * (s + 1) / split - own[o] * s / split;
-    }
+    const int64_t chunks = p->K * split;
+    std::vector<int32_t> at((size_t)chunks + 1, 0);
     const int32_t *member = p->round_member.data();
     for (int64_t u = 0, s = 0; u < p->nround; u++, s = s + 1 == split ? 0 : s + 1)
         for (int b = 0; b < r1; b++) at[member[u * r1 + b] * split + s + 1]++;
-    const int64_t longest = *std::max_element(at.begin(), at.end());
-    if ((double)longest * (double)(nout * split) > most * (double)ptr[nout]) return;
-    for (int64_t i = 0; i < nout * split; i++) at[i + 1] += at[i];
+    int64_t longest = 0;                                     // with the chunk's part of the files the node stores
+    for (int64_t i = 0; i < chunks; i++) {
+        const int64_t s = i % split;
+        longest = std::max(longest, at[i + 1] + local_rows * (s + 1) / split - local_rows * s / split);
+    }
+    if ((double)longest * (double)split > most * (double)(local_rows + p->rows_per_node)) return;
+    for (int64_t i = 0; i < chunks; i++) at[i + 1] += at[i];
     lists->resize(at.size() + (size_t)at.back());
     std::copy(at.begin(), at.end(), lists->begin());
-    int64_t *list = lists->data() + at.size();
-    for (int64_t o = 0; o < nout; o++) {                     // a list after the other: its chunks' ends stay in the first cache
-        int64_t *end = at.data() + o * split;
-        for (int64_t s = 0; s < split; s++)
-            for (int64_t i = own[o] * s / split; i < own[o] * (s + 1) / split; i++) list[end[s]++] = rows[ptr[o] + i];
-        const int32_t *packet = p->node_rows.data() + o * p->rows_per_node;
+    int32_t *list = lists->data() + at.size();
+    for (int k = 0; k < p->K; k++) {                         // a list after the other: its chunks' ends stay in the first cache
+        int32_t *end = at.data() + k * split;
+        const int32_t *packet = p->node_rows.data() + k * p->rows_per_node;
         uint32_t u = 0;
         int64_t s = 0;
         for (int64_t j = 0; j < p->rows_per_node; j++) {
@@ -361,7 +358,7 @@ void lists_by_round(const ccdc_plan_t *p, const std::vector<int64_t> &ptr, const
             u = next;
             s += on < split ? on : on % split;
             s -= s >= split ? split : 0;
-            list[end[s]++] = ((packet[j] * W) << 1) | 1;
+            list[end[s]++] = packet[j];
         }
     }
 }
@@ -551,7 +548,7 @@ int bind_plan(ccdc_plan_t *p, int64_t T, int mode)
             for (size_t i = 0; i < src.size(); i++) pipe[i] = (src[i] << 12) | p->round_member[i];
         }
 
-        std::vector<int64_t> node_row;
+        std::vector<int32_t> node_list;
         const int node_vec = node_pack(any, elem, T, ell);
         // Lists by round: where a value has two readers or more besides its owner's output (r >= 3; r = 2 0.94 to 1.08 of the
         // time), with a wavefront on one segment and units that are not shared by tile already.  Over 95 such inputs of 3 MB to
@@ -565,10 +562,10 @@ int bind_plan(ccdc_plan_t *p, int64_t T, int mode)
         const bool by_round = split > 1 && p->J == 1 && r >= 3 && r <= 5 && fills_wavefronts((uint32_t)(ell / node_vec)) &&
                               (wide || split >= 8 || v_elems * elem <= (r - 1) * kKeptNodeBytes) &&
                               !(node_vec * elem == 16 && neighbours_share(p, cdiv((uint64_t)(ell / node_vec), kPipeLanes)));
-        if (by_round) lists_by_round(p, cnt, rows_tab, split, W, wide ? 2 : 1.5, &node_row);
+        if (by_round) lists_by_round(p, cnt[1] - p->rows_per_node, split, wide ? 2 : 1.5, &node_list);
 
         p->T = T; p->W = W; p->ell = ell; p->mode = mode;
-        p->node_row.swap(node_row);
+        p->node_list.swap(node_list);
         p->pipe_ok = pipe_ok;
         p->pipe_max_chunks = (int)pipe_cap;
         p->pipe_local_rows = pipe_ok ? local_rows : 0;

@@ -53,8 +53,8 @@ struct ccdc_plan_s {
     std::vector<int64_t> red_row;       // rows: (element offset << 1) | (1 = in D, 0 = in V)
     std::vector<int64_t> red_out;       // [nout] element offset of the output block in Phi
     int64_t nout = 0;                   // J * K output blocks of W elements
-    std::vector<int64_t> node_row;      // the lists of ccdc_node_decode_reduce where they are cut by rounds (else empty):
-                                        //   [nout*red_split+1] bounds of the chunks, then the rows, as red_row
+    std::vector<int32_t> node_list;     // the packets of ccdc_node_decode_reduce's lists where those are cut by rounds (else
+                                        //   empty): [nout*red_split+1] bounds of the chunks, then packets u*(r+1)+b
     bool wide_lists = false;            // lists are summed in 16-byte packs at any element where rows do not divide by them
     int red_split = 1;                  // the row list of an output is summed in this many chunks
     int red_waves = 0;                  // > 0: ccdc_reduce sums it in one workgroup of that many wavefronts instead
@@ -74,7 +74,7 @@ struct ccdc_plan_s {
     int device = -1;
     int64_t *d_src_off = nullptr, *d_red_ptr = nullptr, *d_red_row = nullptr, *d_red_out = nullptr;
     int64_t *d_loc_row = nullptr, *d_pipe_row = nullptr;
-    int64_t *d_node_row = nullptr;      // node_row empty: null
+    int32_t *d_node_list = nullptr;     // node_list empty: null
     int32_t *d_row_files = nullptr;     // null when every packet adds m files
     int32_t *d_node_rows = nullptr;
     void *d_workspace = nullptr;

@@ -223,7 +223,7 @@ int main(int argc, char **argv)
     int32_t sums[4];
     CHECK(ccdc_plan_query(p, CCDC_Q_REDUCE_LAUNCH, sums, sizeof sums));
     std::printf("reduce %d,%d,%d,%d\n", sums[0], sums[1], sums[2], sums[3]);
-    std::printf("lists by round %d\n", p->node_row.empty() ? 0 : 1);
+    std::printf("lists by round %d\n", p->node_list.empty() ? 0 : 1);
     if (std::getenv("SHIM_PLAN_ONLY")) {
         int32_t launch[4] = {0, 0, 0, 0};
         (void)ccdc_plan_query(p, CCDC_Q_PIPELINE_LAUNCH, launch, sizeof launch);
