@@ -31,7 +31,7 @@
  * packets XOR-coded as bit patterns; decoding is bit-exact) and the same hybrid
  * for 2-byte elements, CCDC_BF16_SUM_XOR / CCDC_F16_SUM_XOR.  Every buffer of a
  * call holds elements of the bound mode's size (4 or 2 bytes) and must be
- * aligned to it; wider alignment (16 bytes) selects the wide kernels.
+ * aligned to it; wider alignment (16 bytes) selects the aligned wide kernels.
  *
  * Every function returns CCDC_OK (0) or a negative ccdc_status; nothing is
  * written to an output on error and the library never aborts or throws.
@@ -209,11 +209,12 @@ int ccdc_map(const ccdc_plan_t *plan, const void *files, const void *theta, void
  * alive until the stream has run the call; inputs are only read, outputs are
  * written in full (no accumulation into what they held).  CCDC_EINVAL for a
  * null pointer or one not aligned to the element size; pointers aligned to 16
- * bytes (with T a multiple of 4, or of 8 for 2-byte elements) take the wide
- * kernels, others the one-element kernels with the same results.  A call that
- * falls back to narrower packs has up to 8 times as many work items as
- * ccdc_plan_bind checked for: it answers CCDC_ESIZE, before anything is
- * launched, when one of its launches would pass 2^31-1 of them.
+ * bytes (with T a multiple of 4, or of 8 for 2-byte elements) take the aligned
+ * wide kernels, others wide kernels at element alignment or, for small calls,
+ * the one-element kernels, with the same results.  A call of one-element packs
+ * has up to 8 times as many work items as ccdc_plan_bind checked for: where
+ * pointers or T rule out the aligned kernels, a call answers CCDC_ESIZE, before
+ * anything is launched, when those would pass 2^31-1 in one launch.
  */
 
 /* Pre-combining (Sec. IV-B): Vbar[u][b][e] = sum over the m files n of the
