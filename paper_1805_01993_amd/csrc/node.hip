@@ -82,7 +82,7 @@ __device__ __forceinline__ Rows chunk_of(const int64_t *__restrict__ red_ptr, co
 // members' packets in it, which the receiver pre-combines from its own files.
 // The list is cut into `split` chunks as in ccdc_reduce.
 // What bounds it: each row is a chain of table entry, rows and data.  With r+1 at compile time (R1; 0 for r > 5 and batches of
-// several files) four rows are asked for together.  Over 21 inputs of one file, r >= 3, 0.78 of the time, r = 2 0.96: 21 nodes, r = 4, T = 138 f32
+// several files) two to four rows are asked for together.  With four for every r, over 21 inputs of one file, r >= 3, 0.78 of the time, r = 2 0.96: 21 nodes, r = 4, T = 138 f32
 // (8 packs and less a segment) 140 -> 80 us, 16 nodes, r = 4, T = 100 h32 25.0 -> 16.6, r = 5, T = 216 bf16 52 -> 28.
 template <class A, int VEC, int R1, int READS, bool TOGETHER, bool ANY>
 __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
     for (; i < hi && !(red_row[i] & 1); i++) acc = O::accum(acc, own(red_row[i]));
     if (list) i = rows.first, hi = rows.last;
     if constexpr (R1 > 0) {
-        constexpr int AHEAD = 4;
+        constexpr int AHEAD = R1 <= 4 ? 4 : 2;                   // four of r >= 4 take more scalar registers than there are
         for (; i < hi; i += AHEAD) {
             P coded[AHEAD], side[AHEAD][R1];                     // side: of the members, used for those that are neither sender nor receiver
             int from[AHEAD], to[AHEAD];
