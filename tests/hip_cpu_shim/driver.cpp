@@ -7,7 +7,7 @@
 // No chunks (0): the form for small inputs.
 // "reduce a,b,c,d" says what CCDC_Q_REDUCE_LAUNCH does.  SHIM_REDUCE=waves and SHIM_NODE=pack,waves force the form of ccdc_reduce and of
 // ccdc_node_decode_reduce (no wavefronts: their other kernels).
-// SHIM_PLAN_ONLY=1: says what was chosen ("launch" and "reduce") and runs nothing.
+// SHIM_PLAN_ONLY=1: says what was chosen ("launch" and "reduce", a word and a value a line) and runs nothing.
 // SHIM_PAST=1: no input is small enough to be read through the caches for its size.  "streamed C n" says that call C made
 // n non-temporal loads.
 // Test infrastructure only.
@@ -223,7 +223,6 @@ int main(int argc, char **argv)
     int32_t sums[4];
     CHECK(ccdc_plan_query(p, CCDC_Q_REDUCE_LAUNCH, sums, sizeof sums));
     std::printf("reduce %d,%d,%d,%d\n", sums[0], sums[1], sums[2], sums[3]);
-    std::printf("lists by round %d\n", p->node_list.empty() ? 0 : 1);
     if (std::getenv("SHIM_PLAN_ONLY")) {
         int32_t launch[4] = {0, 0, 0, 0};
         (void)ccdc_plan_query(p, CCDC_Q_PIPELINE_LAUNCH, launch, sizeof launch);
@@ -231,6 +230,7 @@ int main(int argc, char **argv)
         ccdc_plan_destroy(p);
         return 0;
     }
+    std::printf("lists by round %d\n", p->node_list.empty() ? 0 : 1);
     const int64_t nv = query(p, CCDC_Q_V_ELEMS), nvb = query(p, CCDC_Q_VBAR_ELEMS), nx = query(p, CCDC_Q_X_ELEMS),
                   nd = query(p, CCDC_Q_D_ELEMS), nphi = query(p, CCDC_Q_PHI_ELEMS), J = query(p, CCDC_Q_J);
 
