@@ -82,8 +82,10 @@ __device__ __forceinline__ Rows chunk_of(const int64_t *__restrict__ red_ptr, co
 // members' packets in it, which the receiver pre-combines from its own files.
 // The list is cut into `split` chunks as in ccdc_reduce.
 // What bounds it: each row is a chain of table entry, rows and data.  With r+1 at compile time (R1; 0 for r > 5 and batches of
-// several files) two to four rows are asked for together.  With four for every r, over 21 inputs of one file, r >= 3, 0.78 of the time, r = 2 0.96: 21 nodes, r = 4, T = 138 f32
-// (8 packs and less a segment) 140 -> 80 us, 16 nodes, r = 4, T = 100 h32 25.0 -> 16.6, r = 5, T = 216 bf16 52 -> 28.
+// several files) four rows are asked for together, two for r >= 4.  Against one row after the other, all nodes, one file: 17 inputs of
+// r = 3 0.80 of the time, 23 of r = 4 0.69, 15 of r = 5 0.65, r <= 2 1.02; a node alone the same.  21 nodes, r = 4, T = 138 f32 (9 packs a
+// segment) 151 -> 71 us, 16 nodes, r = 4, T = 100 h32 24.9 -> 15.6, r = 5, T = 216 bf16 52 -> 27.  Four rows for every r: r = 4 0.95 of that,
+// r = 5 1.04.
 template <class A, int VEC, int R1, int READS, bool TOGETHER, bool ANY>
 __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
     const typename A::elem *__restrict__ V, const typename A::elem *__restrict__ X, typename A::elem *__restrict__ out,
@@ -128,23 +130,27 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
     for (; i < hi && !(red_row[i] & 1); i++) acc = O::accum(acc, own(red_row[i]));
     if (list) i = rows.first, hi = rows.last;
     if constexpr (R1 > 0) {
-        constexpr int AHEAD = R1 <= 4 ? 4 : 2;                   // four of r >= 4 take more scalar registers than there are
+        constexpr int AHEAD = R1 <= 4 ? 4 : 2, r = R1 - 1;
         for (; i < hi; i += AHEAD) {
-            P coded[AHEAD], side[AHEAD][R1];                     // side: of the members, used for those that are neither sender nor receiver
-            int from[AHEAD], to[AHEAD];
+            P coded[AHEAD], side[AHEAD][r > 1 ? r - 1 : 1];      // side: of the members that are neither sender nor receiver
+            int from[AHEAD];
+            auto position = [&](int t, int q) { return (from[t] - (q < (int)rho ? 1 : 0)) * ell + x; };
 #pragma unroll
             for (int t = 0; t < AHEAD; t++) {                    // past the list's end the last row stands in and is not used
                 const uint32_t pk = wave_uniform(packet(i + t < hi ? i + t : hi - 1)), u = pk / R1;
-                const int b = (int)(pk - u * R1), a = (int)rho < b ? (int)rho : (int)rho + 1;
-                const int64_t *src = src_off + (size_t)u * R1;
-                from[t] = a;
-                to[t] = b;
-                coded[t] = load_at<READS != kPast, ANY, P, E>(X + ((size_t)u * R1 + a) * ell + x);
+                const int b = (int)(pk - u * R1);
+                from[t] = (int)rho < b ? (int)rho : (int)rho + 1;
+                coded[t] = load_at<READS != kPast, ANY, P, E>(X + ((size_t)u * R1 + from[t]) * ell + x);
+                // Of the members other than the receiver, whose batches it stores, the sender is the rho-th.  Its own batch is not
+                // one of them and is not read.
+                int64_t stored[r];
 #pragma unroll
-                for (int b2 = 0; b2 < R1; b2++) {
-                    const uint32_t pos = segment_rank(a, b2) * ell + x;
-                    const bool used = b2 != a && b2 != b && pos < W;
-                    side[t][b2] = packet_pack<O, READS == kAll, false, ANY>(V + src[b2], used ? pos : 0, W, 1, 0);
+                for (int j = 0; j < r; j++) stored[j] = src_off[(size_t)u * R1 + (j < b ? j : j + 1)];
+#pragma unroll
+                for (int q = 0; q < r - 1; q++) {
+                    const uint32_t pos = position(t, q);
+                    const int64_t src = q < (int)rho ? stored[q] : stored[q + 1];
+                    side[t][q] = packet_pack<O, READS == kAll, false, ANY>(V + src, pos < W ? pos : 0, W, 1, 0);
                 }
             }
 #pragma unroll
@@ -152,10 +158,7 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
                 if (i + t >= hi) break;
                 P d = coded[t];
 #pragma unroll
-                for (int b2 = 0; b2 < R1; b2++) {
-                    const bool used = b2 != from[t] && b2 != to[t] && segment_rank(from[t], b2) * ell + x < W;
-                    d = O::select(used, O::uncode(d, side[t][b2]), d);
-                }
+                for (int q = 0; q < r - 1; q++) d = O::select(position(t, q) < W, O::uncode(d, side[t][q]), d);
                 acc = O::accum(acc, d);
             }
         }

@@ -12,6 +12,7 @@
 // n non-temporal loads.
 // Test infrastructure only.
 #include <hip/hip_runtime.h>
+#include <sanitizer/asan_interface.h>
 
 #include <algorithm>
 #include <cmath>
@@ -391,13 +392,42 @@ int main(int argc, char **argv)
         streamed("node-decode");
         same(X5, X, nx, "node-local X");
         check_phi(Phi5, "node-local Phi");
-        // each node on its own: the same packets, and the outputs of the call for all of them
+        // each node on its own: the same packets, and the outputs of the call for all of them.  Out of its reach (reported by the
+        // sanitizer) are the files it does not store, the packets that it neither sends nor is sent, and other nodes' outputs.
+        auto only = [&](unsigned char *buf, int64_t rows, int64_t row, auto mine) {      // rows of `row` elements
+            for (int64_t i = 0; i < rows; i++)
+                if (!mine(i)) __asan_poison_memory_region(buf + (size_t)(i * row) * eb, (size_t)row * eb);
+        };
+        auto all = [&](unsigned char *buf, int64_t n) { __asan_unpoison_memory_region(buf, (size_t)n * eb); };
+        const int r1 = r + 1;
+        auto stores = [&](int k) {
+            return [&, k](int64_t file) {
+                const int32_t *held = p->node_files.data() + k * p->files_per_node;
+                return std::binary_search(held, held + p->files_per_node, (int32_t)file);
+            };
+        };
+        auto sends = [&](int k) { return [&, k](int64_t i) { return p->round_member[i] == k; }; };
+        auto is_sent = [&](int k) {
+            return [&, k](int64_t i) {
+                const int32_t *in = p->round_member.data() + i / r1 * r1;
+                return in[i % r1] != k && std::find(in, in + r1, k) != in + r1;
+            };
+        };
         std::memset(X5, 0xA5, (size_t)nx * eb);
-        for (int k = 0; k < K; k++) CHECK(ccdc_node_encode(p, k, V, X5, nullptr));
+        for (int k = 0; k < K; k++) {
+            only(V, J * N, Q * T, stores(k)), only(X5, p->nrows, p->ell, sends(k));
+            CHECK(ccdc_node_encode(p, k, V, X5, nullptr));
+            all(V, nv), all(X5, nx);
+        }
         streamed("one-node-encode");
         same(X5, X, nx, "one node's X");
         std::memset(Phi4, 0xA5, (size_t)nphi * eb);
-        for (int k = 0; k < K; k++) CHECK(ccdc_node_decode_reduce(p, k, V, X5, Phi4, nullptr));
+        for (int k = 0; k < K; k++) {
+            only(V, J * N, Q * T, stores(k)), only(X5, p->nrows, p->ell, is_sent(k));
+            only(Phi4, J * K, p->W, [&](int64_t o) { return o % K == k; });
+            CHECK(ccdc_node_decode_reduce(p, k, V, X5, Phi4, nullptr));
+            all(V, nv), all(X5, nx), all(Phi4, nphi);
+        }
         streamed("one-node-decode");
         same(Phi4, Phi5, nphi, "one node's Phi");
     }

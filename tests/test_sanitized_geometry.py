@@ -254,3 +254,24 @@ def test_packs_at_any_element(kernel_driver, case, past):  # noqa: F811
     res = subprocess.run([kernel_driver] + [str(v) for v in case + (8, 8)], capture_output=True, text=True, env=env, timeout=600)
     assert res.returncode == 0, res.stdout + res.stderr
     assert " 0 mismatches" in res.stdout, res.stdout
+
+
+# K, r, Q, N, T, jobs: segments that do not fill a wavefront's lanes and segments that do, packets shorter than their segments, one file a
+# batch and several, several jobs, r beyond what decoding is unrolled for
+ALONE = [
+    (3, 1, 3, 3, 72, 0), (6, 2, 6, 15, 64, 0), (5, 3, 5, 10, 72, 0), (5, 4, 5, 5, 400, 0), (6, 5, 6, 6, 90, 0), (5, 4, 5, 5, 3, 0),
+    (5, 2, 5, 10, 512, 0), (6, 3, 6, 20, 786, 0), (5, 3, 5, 20, 72, 0), (5, 2, 5, 6, 203, 1), (8, 6, 8, 28, 60, 0),
+]
+
+
+@pytest.mark.parametrize("any_element", [False, True], ids=["", "any"])
+@pytest.mark.parametrize("case", ALONE, ids=lambda c: "-".join(map(str, c)))
+def test_a_node_alone_keeps_to_its_files(kernel_driver, case, any_element):  # noqa: F811
+    """Calls for one node touch only the files it stores, the packets it sends or is sent and its own outputs: the driver puts the rest out of
+    reach for every call of one node, and the sanitizer reports an access to it.  The kernels of node.hip (SHIM_NODE), lists split."""
+    for mode in (1, 3):
+        K, r, Q, N, T, jobs = case
+        res = subprocess.run([kernel_driver] + [str(v) for v in (K, r, Q, N, T, mode, jobs, 8, 8)], capture_output=True, text=True,
+                             env=dict(os.environ, **ENV, **SPLIT, **({"SHIM_ANY": "1"} if any_element else {})), timeout=600)
+        assert res.returncode == 0, res.stdout + res.stderr
+        assert " 0 mismatches" in res.stdout, res.stdout
