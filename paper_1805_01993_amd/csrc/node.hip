@@ -72,6 +72,30 @@ __device__ __forceinline__ Rows chunk_of(const int64_t *__restrict__ red_ptr, co
     return {lo, hi, (uint32_t)list[o * split + s], (uint32_t)list[o * split + s + 1]};
 }
 
+// Lists are cut by rounds for r = 3, 4 and 5 only (bind_plan()); R1 = 0 is any r.
+template <int R1>
+constexpr bool kMayBeListed = R1 == 0 || R1 > 3;
+
+// Calls walk(listed) with whether there is a list of packets as a compile-time constant: looked at in every row it parts the loads that are
+// asked for together (a node alone, r = 1, 21 nodes, T = 13786 f32 3.9 -> 4.9 us).
+template <bool MAY, class F>
+__device__ __forceinline__ void by_list(const int32_t *list, F walk)
+{
+    if constexpr (MAY) {
+        if (list) return walk(std::true_type());
+    }
+    walk(std::false_type());
+}
+
+// The number u*(r+1)+b of a received packet, the same for all lanes.  A row is its first element: element / W, exact in fp64, which leaves
+// the result in a vector register and the tables that it indexes to vector loads if the compiler is not told.
+template <bool LISTED>
+__device__ __forceinline__ uint32_t packet_at(const int64_t *__restrict__ red_row, const int32_t *__restrict__ list_packets, int64_t at, double per_row)
+{
+    if constexpr (LISTED) return wave_uniform((uint32_t)list_packets[at]);
+    else return wave_uniform((uint32_t)((double)(red_row[at] >> 1) * per_row + 0.5));
+}
+
 // --------------------------------------------- a receiver's decoding + output
 // Decoding and final reduction of Sec. IV-B for the output blocks o_first,
 // o_first + o_step, ... (one node's block in every job, or all blocks).  The
@@ -83,7 +107,7 @@ __device__ __forceinline__ Rows chunk_of(const int64_t *__restrict__ red_ptr, co
 // The list is cut into `split` chunks as in ccdc_reduce.
 // What bounds it: each row is a chain of table entry, rows and data.  With r+1 at compile time (R1; 0 for r > 5 and batches of
 // several files) four rows are asked for together, two for r >= 4.  Against one row after the other, all nodes, one file: 17 inputs of
-// r = 3 0.80 of the time, 23 of r = 4 0.69, 15 of r = 5 0.65, r <= 2 1.02; a node alone the same.  21 nodes, r = 4, T = 138 f32 (9 packs a
+// r = 3 0.80 of the time, 23 of r = 4 0.69, 15 of r = 5 0.65, r <= 2 0.98; a node alone the same.  21 nodes, r = 4, T = 138 f32 (9 packs a
 // segment) 151 -> 71 us, 16 nodes, r = 4, T = 100 h32 24.9 -> 15.6, r = 5, T = 216 bf16 52 -> 27.  Four rows for every r: r = 4 0.95 of that,
 // r = 5 1.04.
 template <class A, int VEC, int R1, int READS, bool TOGETHER, bool ANY>
@@ -112,10 +136,6 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
     typename O::Q acc = O::azero();
     int64_t i = rows.lo, hi = rows.hi;
     auto own = [&](int64_t row) { return load_at<READS == kAll, ANY, P, E>(V + (row >> 1) + e); };
-    // a packet u*(r+1)+b; a row is its first element: its number = element / W, exact in fp64
-    auto packet = [&](int64_t at) {
-        return list ? (uint32_t)list_packets[at] : (uint32_t)((double)(red_row[at] >> 1) * per_row + 0.5);
-    };
     if constexpr (R1 > 0) {
         constexpr int AHEAD = 4;
         for (; i + AHEAD <= hi; i += AHEAD) {                    // the files the node stores come first
@@ -128,7 +148,12 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
         }
     }
     for (; i < hi && !(red_row[i] & 1); i++) acc = O::accum(acc, own(red_row[i]));
-    if (list) i = rows.first, hi = rows.last;
+    // (one loop for both kinds of lists: two take a quarter to a half more registers here)
+    const bool listed = kMayBeListed<R1> && list;
+    if (listed) i = rows.first, hi = rows.last;
+    auto packet = [&](int64_t at) {
+        return listed ? packet_at<true>(red_row, list_packets, at, per_row) : packet_at<false>(red_row, list_packets, at, per_row);
+    };
     if constexpr (R1 > 0) {
         constexpr int AHEAD = R1 <= 4 ? 4 : 2, r = R1 - 1;
         for (; i < hi; i += AHEAD) {
@@ -137,7 +162,7 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
             auto position = [&](int t, int q) { return (from[t] - (q < (int)rho ? 1 : 0)) * ell + x; };
 #pragma unroll
             for (int t = 0; t < AHEAD; t++) {                    // past the list's end the last row stands in and is not used
-                const uint32_t pk = wave_uniform(packet(i + t < hi ? i + t : hi - 1)), u = pk / R1;
+                const uint32_t pk = packet(i + t < hi ? i + t : hi - 1), u = pk / R1;
                 const int b = (int)(pk - u * R1);
                 from[t] = (int)rho < b ? (int)rho : (int)rho + 1;
                 coded[t] = load_at<READS != kPast, ANY, P, E>(X + ((size_t)u * R1 + from[t]) * ell + x);
@@ -305,13 +330,10 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce_wave(
         for (int t = 0; t < 4; t++) acc = O::accum(acc, v[t]);
     }
     for (; i < hi && !(red_row[i] & 1); i++) acc = O::accum(acc, own(red_row[i]));
-    if (list) i = rows.first, hi = rows.last;
     struct Packet {
         P coded, side[r > 1 ? r - 1 : 1];
     };
-    auto load = [&](int64_t at, Packet &k) {
-        // a row is the packet's first element: packet number = element / W, exact in fp64
-        const uint32_t pk = list ? (uint32_t)list_packets[at] : wave_uniform((uint32_t)((double)(red_row[at] >> 1) * per_row + 0.5));
+    auto load = [&](uint32_t pk, Packet &k) {
         const uint32_t u = pk / R1;
         const int b = (int)(pk - u * R1);
         const int a = rho < b ? rho : rho + 1;
@@ -350,18 +372,22 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce_wave(
         for (int q = 0; q < r - 1; q++) d = O::uncode(d, k.side[q]);
         acc = O::accum(acc, d);
     };
-    for (; i + AHEAD <= hi; i += AHEAD) {
-        Packet k[AHEAD];
+    auto received = [&](auto listed) {
+        if constexpr (decltype(listed)::value) i = rows.first, hi = rows.last;
+        for (; i + AHEAD <= hi; i += AHEAD) {
+            Packet k[AHEAD];
 #pragma unroll
-        for (int t = 0; t < AHEAD; t++) load(i + t, k[t]);
+            for (int t = 0; t < AHEAD; t++) load(packet_at<decltype(listed)::value>(red_row, list_packets, i + t, per_row), k[t]);
 #pragma unroll
-        for (int t = 0; t < AHEAD; t++) use(k[t]);
-    }
-    for (; i < hi; i++) {
-        Packet k;
-        load(i, k);
-        use(k);
-    }
+            for (int t = 0; t < AHEAD; t++) use(k[t]);
+        }
+        for (; i < hi; i++) {
+            Packet k;
+            load(packet_at<decltype(listed)::value>(red_row, list_packets, i, per_row), k);
+            use(k);
+        }
+    };
+    by_list<kMayBeListed<R1>>(list, received);
     if (split > 1) store_at<false, ANY, typename O::Q, typename A::acc>(part + (int64_t)s * chunk_stride + red_out[o] + e, acc);
     else store_at<false, ANY, P, E>(out + red_out[o] + e, O::narrow(acc));
 }
@@ -493,7 +519,9 @@ int run_node_decode_reduce(const ccdc_plan_t *p, int node, const void *V, const 
     using E = typename A::elem;
     using Acc = typename A::acc;
     const uint32_t Lv = cdiv(p->ell, VEC), ell = (uint32_t)p->ell, W = (uint32_t)p->W;
-    const uint32_t tiles = cdiv((uint64_t)Lv * p->r, kBlock);          // the last segment may be short
+    // the packs of a row; one shorter than r whole segments has fewer than r * Lv (18 nodes, r = 3, two functions, T = 512 f32: 256, in
+    // one tile 34.7 us, not 258, in two 41.6)
+    const uint32_t tiles = cdiv((uint64_t)(W / ell) * Lv + cdiv(W % ell, VEC), kBlock);
     const int split = p->red_split;
     const bool by_round = p->d_node_list != nullptr;
     const int32_t *packets = by_round ? p->d_node_list + (size_t)p->nout * split + 1 : nullptr;

@@ -9,7 +9,7 @@
 // ccdc_node_decode_reduce (no wavefronts: their other kernels).
 // SHIM_PLAN_ONLY=1: says what was chosen ("launch" and "reduce", a word and a value a line) and runs nothing.
 // SHIM_PAST=1: no input is small enough to be read through the caches for its size.  "streamed C n" says that call C made
-// n non-temporal loads.
+// n non-temporal loads, "workgroups node-decode n" how many the larger launch of ccdc_node_decode_reduce for all nodes has.
 // Test infrastructure only.
 #include <hip/hip_runtime.h>
 #include <sanitizer/asan_interface.h>
@@ -388,8 +388,10 @@ int main(int argc, char **argv)
         shim::streaming_loads = 0;
         CHECK(ccdc_node_encode(p, -1, V, X5, nullptr));
         streamed("node-encode");
+        shim::largest_launch = 0;
         CHECK(ccdc_node_decode_reduce(p, -1, V, X5, Phi5, nullptr));
         streamed("node-decode");
+        std::printf("workgroups node-decode %ld\n", shim::largest_launch.load());
         same(X5, X, nx, "node-local X");
         check_phi(Phi5, "node-local Phi");
         // each node on its own: the same packets, and the outputs of the call for all of them.  Out of its reach (reported by the

@@ -55,6 +55,7 @@ extern int compute_units;                               // what the device attri
 extern int blocks_per_cu;                               // what the occupancy query answers
 extern size_t max_dynamic_lds;                          // launches asking for more are refused
 extern std::atomic<long> launches;
+extern std::atomic<long> largest_launch;                // workgroups of the largest so far
 extern std::atomic<long> streaming_loads;               // non-temporal loads the kernels made
 extern bool dry_run;                                     // launches are checked and counted, not run
 void barrier_wait();                                    // __syncthreads()

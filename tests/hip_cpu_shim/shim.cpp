@@ -12,7 +12,7 @@ thread_local unsigned char *dyn_smem = nullptr;
 int compute_units = 8;
 int blocks_per_cu = 4;
 size_t max_dynamic_lds = 160 * 1024;
-std::atomic<long> launches{0}, streaming_loads{0};
+std::atomic<long> launches{0}, streaming_loads{0}, largest_launch{0};
 bool dry_run = false;
 
 namespace {
@@ -86,6 +86,7 @@ void *block_static(size_t bytes)
 void launch(dim3 grid, dim3 block, size_t lds, const std::function<void()> &body)
 {
     launches++;
+    largest_launch = std::max(largest_launch.load(), (long)grid.x);
     // a launch of 2^32 work items or more is refused, as the HIP runtime does
     if (grid.x == 0 || block.x == 0 || block.x > 1024 || lds > max_dynamic_lds || ((uint64_t)grid.x * block.x) >> 32) {
         std::fprintf(stderr, "shim: launch refused (grid %u, block %u, lds %zu)\n", grid.x, block.x, lds);

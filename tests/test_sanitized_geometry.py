@@ -256,6 +256,18 @@ def test_packs_at_any_element(kernel_driver, case, past):  # noqa: F811
     assert " 0 mismatches" in res.stdout, res.stdout
 
 
+@pytest.mark.parametrize("K,r,T,packs", [(8, 6, 1024, 256), (6, 2, 300, 75), (5, 3, 1040, 260)])
+def test_row_packs_of_lane_packed_decoding(kernel_driver, K, r, T, packs):  # noqa: F811
+    """A row has the packs of its elements, not of r whole segments: a workgroup for every 256 of them, output and chunk."""
+    args = (K, r, K, comb(K, r), T, 1, 0, 8, 8)
+    res = subprocess.run([kernel_driver] + [str(v) for v in args], capture_output=True, text=True,
+                         env=dict(os.environ, **ENV, SHIM_ANY="1", **SPLIT), timeout=600)
+    assert res.returncode == 0, res.stdout + res.stderr
+    assert " 0 mismatches" in res.stdout, res.stdout
+    split = int(res.stdout[res.stdout.index("reduce ") + 7:].split(",")[0])
+    assert split > 1 and f"workgroups node-decode {K * split * -(-packs // 256)}\n" in res.stdout, res.stdout
+
+
 # K, r, Q, N, T, jobs: segments that do not fill a wavefront's lanes and segments that do, packets shorter than their segments, one file a
 # batch and several, several jobs, r beyond what decoding is unrolled for
 ALONE = [
