@@ -329,10 +329,12 @@ int plan_groups(int64_t nout, int64_t rows, int64_t W, int vec, int elem, int64_
 // that is side information by r - 1, so lists are best cut by rounds: chunk s of every list then has the packets of the
 // same rounds, s, s + split, s + 2 split, .. (a chunk of neighbouring rounds would have all of the first node's),
 // and units that are numbered by chunk (node.hip) read them together, behind one L2.  The price is chunks of unequal length, and
-// a chunk is a chain of waits: no such lists where the longest is over `most` times the mean.
-void lists_by_round(const ccdc_plan_t *p, int64_t local_rows, int64_t split, double most, std::vector<int32_t> *lists)
+// a chunk is a chain of waits, on an XCD with the same chunk of other lists: no such lists where the longest has over kUnequalChunks
+// times the mean to load (kUnequalFileChunks with several files a batch).
+void lists_by_round(const ccdc_plan_t *p, int64_t local_rows, int64_t split, std::vector<int32_t> *lists)
 {
     const int r1 = p->r + 1;
+    const int64_t loads = 1 + (int64_t)(p->r - 1) * p->m;    // of a received packet: the coded one and the files of r - 1 batches
     const int64_t chunks = p->K * split;
     std::vector<int32_t> at((size_t)chunks + 1, 0);
     const int32_t *member = p->round_member.data();
@@ -341,9 +343,9 @@ void lists_by_round(const ccdc_plan_t *p, int64_t local_rows, int64_t split, dou
     int64_t longest = 0;                                     // with the chunk's part of the files the node stores
     for (int64_t i = 0; i < chunks; i++) {
         const int64_t s = i % split;
-        longest = std::max(longest, at[i + 1] + local_rows * (s + 1) / split - local_rows * s / split);
+        longest = std::max(longest, loads * at[i + 1] + local_rows * (s + 1) / split - local_rows * s / split);
     }
-    if ((double)longest * (double)split > most * (double)(local_rows + p->rows_per_node)) return;
+    if ((double)longest * (double)split > (p->m > 1 ? kUnequalFileChunks : kUnequalChunks) * (double)(local_rows + loads * p->rows_per_node)) return;
     for (int64_t i = 0; i < chunks; i++) at[i + 1] += at[i];
     lists->resize(at.size() + (size_t)at.back());
     std::copy(at.begin(), at.end(), lists->begin());
@@ -553,16 +555,19 @@ int bind_plan(ccdc_plan_t *p, int64_t T, int mode)
         // Lists by round: where a value has two readers or more besides its owner's output (r >= 3; r = 2 0.94 to 1.08 of the
         // time), with a wavefront on one segment and units that are not shared by tile already.  Over 95 such inputs of 3 MB to
         // 2 GB 0.83 of the time of equal cuts, the least 0.28 (8 nodes, r = 5, twelve files, T = 19008 f32 410 -> 113 us; 16
-        // nodes, r = 3, T = 4096 h32 60.5 -> 50.5).  Chunks may be up to twice as long as the mean: seven inputs beyond that took
-        // 0.95 to 1.06 of the time, 13 nodes, r = 3, T = 1280 bf16 13.3 -> 14.1 at 2.7 times.  One-element packs share lines with
-        // their neighbours anyway: half as long again at most (18 nodes, r = 3, T = 1973 bf16 62 -> 66 at 1.64 times), and in few
-        // chunks only while the values' readers can find them in the last-level cache (21 nodes, r = 3, T = 4711 f32, 1.3
-        // GB, six chunks, 281 -> 295).
+        // nodes, r = 3, T = 4096 h32 60.5 -> 50.5).  One file a batch: a chunk may have up to 1.7 times the mean to load
+        // (kUnequalChunks): 118 such plans 0.71 of the time of equal cuts for all nodes and 0.72 for a node alone, seven of those over 5 %
+        // slower; 39 up to twice the mean 0.88 and 0.97, 19 (a node alone shares nothing with others, but its lists are cut as
+        // theirs: 15 nodes, r = 3, T = 4480 h32 13.3 -> 16.0, 19 nodes, r = 3, T = 1408 h32 12.0 -> 14.3); 24 beyond 1.01 and 1.01.  Several
+        // files: equal cuts have the files that a node stores in the first chunks and all packets, of many loads, in the last, so up to twice
+        // the mean 28 plans 0.61 and 0.39, none slower; 22 beyond 0.89, three up to 1.48 (6 nodes, r = 5, ten files, T = 62272 u32: one round,
+        // whose packets are in one chunk and on one XCD).  In few chunks one-element packs gain only while the values' readers
+        // can find them in the last-level cache (21 nodes, r = 3, T = 4711 f32, 1.3 GB, six chunks, 281 -> 295).
         const bool wide = node_vec > 1;
         const bool by_round = split > 1 && p->J == 1 && r >= 3 && r <= 5 && fills_wavefronts((uint32_t)(ell / node_vec)) &&
                               (wide || split >= 8 || v_elems * elem <= (r - 1) * kKeptNodeBytes) &&
                               !(node_vec * elem == 16 && neighbours_share(p, cdiv((uint64_t)(ell / node_vec), kPipeLanes)));
-        if (by_round) lists_by_round(p, cnt[1] - p->rows_per_node, split, wide ? 2 : 1.5, &node_list);
+        if (by_round) lists_by_round(p, cnt[1] - p->rows_per_node, split, &node_list);
 
         p->T = T; p->W = W; p->ell = ell; p->mode = mode;
         p->node_list.swap(node_list);

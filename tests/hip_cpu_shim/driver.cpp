@@ -8,6 +8,7 @@
 // "reduce a,b,c,d" says what CCDC_Q_REDUCE_LAUNCH does.  SHIM_REDUCE=waves and SHIM_NODE=pack,waves force the form of ccdc_reduce and of
 // ccdc_node_decode_reduce (no wavefronts: their other kernels).
 // SHIM_PLAN_ONLY=1: says what was chosen ("launch" and "reduce", a word and a value a line) and runs nothing.
+// SHIM_ANY=1: no call is too small for packs at any element.  SHIM_ROUNDS=1: no chunks of node-local lists by round are too unequal.
 // SHIM_PAST=1: no input is small enough to be read through the caches for its size.  "streamed C n" says that call C made
 // n non-temporal loads, "workgroups node-decode n" how many the larger launch of ccdc_node_decode_reduce for all nodes has.
 // Test infrastructure only.
@@ -210,6 +211,7 @@ int main(int argc, char **argv)
     if (std::getenv("SHIM_PAST")) ccdc::kKeptBytes = ccdc::kKeptStageBytes = ccdc::kKeptNodeBytes = ccdc::kKeptOneNodeBytes =
                                        ccdc::kKeptPacketBytes = ccdc::kKeptSharedBytes = 0;
     if (std::getenv("SHIM_ANY")) ccdc::kAnyPacks = 1, ccdc::kAnyLanes = ccdc::kAnyListPacks = ccdc::kAnyListBytes = 0;
+    if (std::getenv("SHIM_ROUNDS")) ccdc::kUnequalChunks = ccdc::kUnequalFileChunks = 1e9;
     const bool half = mode >= 3, real = mode != 1;
     const size_t eb = half ? 2 : 4;
 
@@ -228,6 +230,7 @@ int main(int argc, char **argv)
         int32_t launch[4] = {0, 0, 0, 0};
         (void)ccdc_plan_query(p, CCDC_Q_PIPELINE_LAUNCH, launch, sizeof launch);
         std::printf("launch %d,%d,%d,%d\n", launch[0], launch[1], launch[2], launch[3]);
+        std::printf("by_round %d\n", p->node_list.empty() ? 0 : 1);
         ccdc_plan_destroy(p);
         return 0;
     }

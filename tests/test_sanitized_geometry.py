@@ -178,12 +178,17 @@ def test_forms_of_the_reductions(kernel_driver, r, m):  # noqa: F811
         list(pool.map(run, range(4), ends))
 
 
-def choices(kernel_driver, K, r, N, T, mode):
-    """What a plan takes on 256 compute units: CCDC_Q_PIPELINE_LAUNCH and CCDC_Q_REDUCE_LAUNCH."""
+def plan_only(kernel_driver, K, r, N, T, mode):
+    """What a plan takes on 256 compute units."""
     res = subprocess.run([kernel_driver] + [str(v) for v in (K, r, K, N, T, mode, 0, 256, 16)], capture_output=True, text=True,
                          env=dict(os.environ, SHIM_PLAN_ONLY="1", **ENV), timeout=600)
     assert res.returncode == 0, res.stdout + res.stderr
-    said = dict(l.split() for l in res.stdout.splitlines())
+    return dict(l.split() for l in res.stdout.splitlines())
+
+
+def choices(kernel_driver, K, r, N, T, mode):
+    """Of it CCDC_Q_PIPELINE_LAUNCH and CCDC_Q_REDUCE_LAUNCH."""
+    said = plan_only(kernel_driver, K, r, N, T, mode)
     return [[int(v) for v in said[k].split(",")] for k in ("launch", "reduce")]
 
 
@@ -217,11 +222,11 @@ def test_reduce_of_narrow_packs(kernel_driver, K, r, T, mode, waves):  # noqa: F
     assert choices(kernel_driver, K, r, m * comb(K, r), T, mode)[1][1] == waves
 
 
-# K, r, m, T, mode, whether node-local lists are cut by rounds: edges of the rule (replication, how unequal the chunks
-# are, one-element packs, segments that leave lanes idle, a list that is not cut)
+# K, r, m, T, mode, whether node-local lists are cut by rounds, however unequal the chunks: edges of the rest of the rule (replication,
+# one-element packs, segments that leave lanes idle, a list that is not cut)
 BY_ROUND = [
-    (7, 3, 2, 768, 2, 1), (6, 4, 1, 1024, 0, 1), (6, 5, 3, 1280, 1, 1), (6, 3, 3, 1536, 3, 1), (7, 3, 1, 765, 1, 0),
-    (7, 3, 5, 759, 0, 0), (6, 2, 1, 512, 2, 0), (7, 3, 2, 804, 2, 0), (6, 5, 1, 4100, 4, 1),
+    (7, 3, 2, 768, 2, 1), (6, 4, 1, 1024, 0, 1), (6, 5, 3, 1280, 1, 1), (6, 3, 3, 1536, 3, 1), (7, 3, 1, 765, 1, 1),
+    (7, 3, 5, 759, 0, 1), (6, 2, 1, 512, 2, 0), (7, 3, 2, 804, 2, 0), (6, 5, 1, 4100, 4, 1),
 ]
 
 
@@ -231,10 +236,23 @@ def test_lists_by_round(kernel_driver, case):  # noqa: F811
     K, r, m, T, mode, by_round = case
     args = (K, r, K, m * comb(K, r), T, mode, 0, 256, 8)
     res = subprocess.run([kernel_driver] + [str(v) for v in args], capture_output=True, text=True,
-                         env=dict(os.environ, **ENV, SHIM_NODE="0,0", SHIM_REDUCE="0"), timeout=600)
+                         env=dict(os.environ, **ENV, SHIM_NODE="0,0", SHIM_REDUCE="0", SHIM_ROUNDS="1"), timeout=600)
     assert res.returncode == 0, res.stdout + res.stderr
     assert f"lists by round {by_round}\n" in res.stdout, res.stdout
     assert " 0 mismatches" in res.stdout, res.stdout
+
+
+# The same at the sizes where it matters: chunks of up to 1.7 times the mean (several files: twice), lists that are not cut or numbered by tile
+@pytest.mark.parametrize("K,r,m,T,mode,by_round", [
+    (16, 3, 1, 4096, 2, True), (11, 5, 1, 6336, 1, True), (14, 5, 1, 281, 0, True),
+    (15, 3, 1, 4480, 2, False),        # just beyond: a node alone 13.3 us in equal cuts, by round 16.0
+    (12, 3, 1, 6464, 3, False),        # 1.93: a node alone 9.7 and 11.6
+    (19, 3, 1, 1408, 2, False),        # 1.97: 12.0 and 14.3
+    (6, 5, 10, 62272, 1, False),       # one round, whose packets are in one chunk: 36 and 53 us for all nodes
+    (4, 3, 10, 120000, 0, False), (8, 5, 12, 19008, 0, True), (9, 5, 1, 40704, 2, False), (10, 2, 1, 3544, 1, False),
+])
+def test_which_lists_are_cut_by_round(kernel_driver, K, r, m, T, mode, by_round):  # noqa: F811
+    assert plan_only(kernel_driver, K, r, m * comb(K, r), T, mode)["by_round"] == str(int(by_round))
 
 
 # K, r, Q, N, T, mode, jobs: lengths that no pack divides, last segments a few elements long, one pack and less
