@@ -132,7 +132,7 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce(
     uint32_t x = column<ANY, VEC>(pack - rho * Lv, ell);
     if (rho >= (uint32_t)r1 - 1 || rho * ell + x >= W) return;
     const uint32_t e = in_segment<ANY, VEC>(rho * ell, W, &x);
-    const Rows rows = chunk_of(red_ptr, list, own_rows, o, s, split);
+    const Rows rows = chunk_of(red_ptr, kMayBeListed<R1> ? list : nullptr, own_rows, o, s, split);
     typename O::Q acc = O::azero();
     int64_t i = rows.lo, hi = rows.hi;
     auto own = [&](int64_t row) { return load_at<READS == kAll, ANY, P, E>(V + (row >> 1) + e); };
@@ -317,7 +317,7 @@ __global__ __launch_bounds__(kBlock) void k_node_decode_reduce_wave(
     uint32_t x = column<ANY, VEC>(pack, ell);
     if (pack >= Lv || rho * ell + x >= W) return;
     const uint32_t e = in_segment<ANY, VEC>(rho * ell, W, &x);
-    const Rows rows = chunk_of(red_ptr, list, own_rows, o, s, split);
+    const Rows rows = chunk_of(red_ptr, kMayBeListed<R1> ? list : nullptr, own_rows, o, s, split);
     typename O::Q acc = O::azero();
     int64_t i = rows.lo, hi = rows.hi;
     // the files the node stores come first in the list
