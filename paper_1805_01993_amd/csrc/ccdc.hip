@@ -583,12 +583,17 @@ int run_shuffle(const ccdc_plan_t *p, const void *V, void *X, void *D, hipStream
     return launched();
 }
 
-// Whether the fused shuffle takes packs at any element: one-element packs of 16 bits always gain (70 jobs on 8 nodes, r = 3, T = 105661 bf16 399 -> 297
-// us), those of 32 bits with r <= 2 on large inputs (10 jobs on 5 nodes, r = 2, T = 400097 u32 95 -> 79), else they are faster (4 nodes,
-// r = 3, T = 4015094 f32 25.0 and 27.4, 6 nodes, r = 5, T = 1690898 u32 73 and 79).
+// Whether the fused shuffle takes packs at any element, by the 16-byte packs of its segments.  In 16 bits, one file a batch, from 512
+// thousand on (36 inputs 0.76 of the time, two over 5 % slower; 256 to 512 thousand 27 inputs 0.98, nine, 128 to 256 31 inputs 1.12); several
+// files are asked for together in one-element packs, those of all packets, so only from 256 thousand on with r = 1 (24 inputs 0.51), a million
+// with r = 2 (18 inputs 0.65; half of it 1.07), two million with r >= 3 (7 inputs 0.74; half of it 1.07, less 1.23).  32 bits gain with r <= 2 on
+// large inputs (10 jobs on 5 nodes, r = 2, T = 400097 u32 95 -> 79 us; from two million packs on 11 inputs 0.96, below 1.05), else
+// one-element packs are faster (4 nodes, r = 3, T = 4015094 f32 25.0 and 27.4, 6 nodes, r = 5, T = 1690898 u32 73 and 79).
 bool shuffle_any(const ccdc_plan_t *p)
 {
-    return makes_lanes(p, p->nrows, p->ell, 4) && (elem_bytes(p->mode) == 2 || (p->r <= 2 && moved_bytes(p, 0) >= kAnyListBytes));
+    const bool half = elem_bytes(p->mode) == 2;
+    if (!half && (p->r > 2 || moved_bytes(p, 0) < kAnyListBytes)) return false;
+    return makes_lanes(p, p->nrows, p->ell, !half ? 64 : p->m == 1 ? 16 : p->r == 1 ? 8 : p->r == 2 ? 32 : 64);
 }
 
 // SHARED: rows begin anywhere in a cache line, see kKeptPacketBytes.
@@ -836,7 +841,8 @@ int ccdc_encode(const ccdc_plan_t *plan, const void *Vbar, void *X, void *stream
     bool any = false;
     if (rc != CCDC_OK) return rc;
     if (plan->compression) return CCDC_ESTATE;       // nothing is coded in that scheme
-    if ((rc = pick_wide(plan, &vec, &any, makes_lanes(plan, plan->nrows, plan->ell, 1), Vbar, (const void *)X)) != CCDC_OK) return rc;
+    // 64 to 128 thousand packs at any element 0.84 (16 bits) and 0.97 of the time over 35 inputs, half as many 1.05 and 1.01 over 26
+    if ((rc = pick_wide(plan, &vec, &any, makes_lanes(plan, plan->nrows, plan->ell, 2), Vbar, (const void *)X)) != CCDC_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     CCDC_DISPATCH(plan, vec, any, (run_encode<A, VEC, ANY>(plan, Vbar, X, st)));
 }
@@ -847,7 +853,10 @@ int ccdc_decode(const ccdc_plan_t *plan, const void *X, const void *Vbar, void *
     bool any = false;
     if (rc != CCDC_OK) return rc;
     if (plan->compression) return CCDC_ESTATE;       // nothing is coded in that scheme
-    if ((rc = pick_wide(plan, &vec, &any, makes_lanes(plan, plan->nrows, plan->ell, 1), X, Vbar, (const void *)D)) != CCDC_OK) return rc;
+    // 16 bits: 128 to 256 thousand packs at any element 0.91 of the time (51 inputs), half as many 1.03, a quarter 1.26; 32 bits: 256
+    // to 512 thousand 0.95 (46 inputs), half as many 1.03, a quarter 1.13 (the ends of packets are made element by element)
+    const double lanes = elem_bytes(plan->mode) == 2 ? 4 : 8;
+    if ((rc = pick_wide(plan, &vec, &any, makes_lanes(plan, plan->nrows, plan->ell, lanes), X, Vbar, (const void *)D)) != CCDC_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     CCDC_DISPATCH(plan, vec, any, (run_decode<A, VEC, ANY>(plan, X, Vbar, D, st)));
 }
