@@ -682,14 +682,16 @@ inline bool makes_lanes(const ccdc_plan_t *p, int64_t rows, int64_t length, doub
     return (double)rows * (double)length * elem_bytes(p->mode) >= 16 * times * kAnyLanes;
 }
 
-// Batches of more than two files that make fewer than 128 thousand packs of 16 bytes leave the chip short of lanes, each with the files of
+// Batches of more than two files that make fewer than 128 thousand packs of 16 bytes (16 bits: 64) leave the chip short of lanes, each with the files of
 // a packet to wait for one after the other: they take one-element packs, more lanes and files asked for together.  48 such calls of
 // ccdc_combine, ccdc_shuffle_fused and ccdc_node_encode over 4 us 0.36 to 0.95 of the time (uncoded, 19 nodes, T = 4168 u32 28.7 -> 10.7 us; 7
-// nodes, r = 5, eleven files, T = 5472 bf16 fused 23.3 -> 5.5); with up to 250 thousand packs 0.78 to 1.30, beyond 0.89 to 2.1.  (Not above
-// what one-element packs can be numbered for, which is far beyond.)
+// nodes, r = 5, eleven files, T = 5472 bf16 fused 23.3 -> 5.5); with up to 250 thousand packs 0.78 to 1.30, beyond 0.89 to 2.1.  In 16 bits, eight
+// lanes for one, 64 to 128 thousand packs were 1.07, 0.84 (four of 11 over 5 % slower) and 1.06 of the time of the three (20 nodes, r = 3, two
+// functions, nine files, T = 64 bf16 node-local sending 12.8 -> 19.5), half as many 0.90, 0.74 and 0.84.  (Not above what
+// one-element packs can be numbered for, which is far beyond.)
 inline void narrow_files(const ccdc_plan_t *p, int files, int64_t rows, int64_t length, int *vec)
 {
-    if (files > 2 && !makes_lanes(p, rows, length, 4)) *vec = 1;
+    if (files > 2 && !makes_lanes(p, rows, length, elem_bytes(p->mode) == 2 ? 2 : 4)) *vec = 1;
 }
 
 inline int launched()
