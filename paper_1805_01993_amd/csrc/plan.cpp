@@ -295,8 +295,12 @@ namespace {
 
 // Whether lists are summed in packs of 16 bytes where rows do not divide by them: where those fill the chip without cutting the lists, where
 // the second launch that cut ones take is little of the time, and where one-element packs need it too and the call is not short.
-bool wide_lists(int64_t nout, int64_t W, int elem, double bytes)
+// values: bytes of V.  Where nothing is cancelled (uncoded, r = 1) a batch is read as the one packet it was combined into, and calls are as
+// long as their lists (24 nodes, r = 2, 288 files, T = 14345 u32 uncoded, 397 MB of values, 48 MB of lists, 11.3 us, as a long call 18.4; four
+// such plans 1.29 of the time).
+bool wide_lists(int r, bool coded, int64_t nout, int64_t rows, int64_t W, int elem, double values)
 {
+    const double bytes = coded && r > 1 ? values : (double)rows * (double)W * elem;
     return (double)(nout * ((W + 3) / 4)) >= kAnyListPacks || bytes >= kAnyListBytes ||
            (nout * W < (1 << 18) && bytes >= (elem == 2 ? 0.16 : 0.64) * kAnyListBytes);
 }
@@ -395,7 +399,7 @@ int bind_compression(ccdc_plan_t *p, int64_t T, int mode)
             outs[k] = (int64_t)k * W;
             min_rows = std::min(min_rows, ptr[k + 1] - ptr[k]);
         }
-        const bool any = wide_anyway(p->r, W, W, 4) && wide_lists(nout, W, 4, (double)p->N * p->Q * (double)T * 4);
+        const bool any = wide_anyway(p->r, W, W, 4) && wide_lists(p->r, false, nout, (int64_t)rows.size(), W, 4, (double)p->N * p->Q * (double)T * 4);
         const int pack = any ? 4 : vec;                      // elements of a call's packs
         const int64_t items = nout * ((W + pack - 1) / pack);
         const int64_t split = list_split(items, min_rows);
@@ -515,7 +519,7 @@ int bind_plan(ccdc_plan_t *p, int64_t T, int mode)
         // each row list into red_split chunks summed by different workgroups and
         // added up, in a fixed order, by a second pass.
         const int elem = elem_bytes(mode);
-        const bool any = wide_anyway(r, W, ell, elem) && wide_lists(nout, W, elem, v_elems * elem);
+        const bool any = wide_anyway(r, W, ell, elem) && wide_lists(r, true, nout, cnt[nout], W, elem, v_elems * elem);
         const int64_t pack = any ? 4 : vec, items = nout * ((W + pack - 1) / pack);
         const int64_t split = list_split(items, min_rows);
         if (items * split > kMaxItems) return CCDC_ESIZE;

@@ -7,7 +7,7 @@
 // No chunks (0): the form for small inputs.
 // "reduce a,b,c,d" says what CCDC_Q_REDUCE_LAUNCH does.  SHIM_REDUCE=waves and SHIM_NODE=pack,waves force the form of ccdc_reduce and of
 // ccdc_node_decode_reduce (no wavefronts: their other kernels).
-// SHIM_PLAN_ONLY=1: says what was chosen ("launch" and "reduce", a word and a value a line) and runs nothing.
+// SHIM_PLAN_ONLY=1: says what was chosen ("launch" and "reduce", a word and a value a line) and runs nothing; jobs 2 is the uncoded scheme.
 // SHIM_ANY=1: no call is too small for packs at any element.  SHIM_ROUNDS=1: no chunks of node-local lists by round are too unequal.
 // SHIM_PAST=1: no input is small enough to be read through the caches for its size.  "streamed C n" says that call C made
 // n non-temporal loads, "workgroups node-decode n" how many the larger launch of ccdc_node_decode_reduce for all nodes has.
@@ -216,7 +216,9 @@ int main(int argc, char **argv)
     const size_t eb = half ? 2 : 4;
 
     ccdc_plan_t *p = nullptr;
-    CHECK(jobs ? ccdc_plan_jobs(K, r, Q, N, &p) : ccdc_plan(K, r, Q, N, &p));
+    const bool only = std::getenv("SHIM_PLAN_ONLY");
+    if (jobs == 2 && !only) return 64;
+    CHECK(jobs == 2 ? ccdc_plan_compression(K, r, Q, N, &p) : jobs ? ccdc_plan_jobs(K, r, Q, N, &p) : ccdc_plan(K, r, Q, N, &p));
     CHECK(ccdc_plan_bind(p, T, mode));
     CHECK(ccdc_plan_upload(p));
     if (!force_reductions(p)) {
@@ -226,11 +228,12 @@ int main(int argc, char **argv)
     int32_t sums[4];
     CHECK(ccdc_plan_query(p, CCDC_Q_REDUCE_LAUNCH, sums, sizeof sums));
     std::printf("reduce %d,%d,%d,%d\n", sums[0], sums[1], sums[2], sums[3]);
-    if (std::getenv("SHIM_PLAN_ONLY")) {
+    if (only) {
         int32_t launch[4] = {0, 0, 0, 0};
         (void)ccdc_plan_query(p, CCDC_Q_PIPELINE_LAUNCH, launch, sizeof launch);
         std::printf("launch %d,%d,%d,%d\n", launch[0], launch[1], launch[2], launch[3]);
         std::printf("by_round %d\n", p->node_list.empty() ? 0 : 1);
+        std::printf("wide_lists %d\n", p->wide_lists ? 1 : 0);
         ccdc_plan_destroy(p);
         return 0;
     }

@@ -178,9 +178,9 @@ def test_forms_of_the_reductions(kernel_driver, r, m):  # noqa: F811
         list(pool.map(run, range(4), ends))
 
 
-def plan_only(kernel_driver, K, r, N, T, mode):
+def plan_only(kernel_driver, K, r, N, T, mode, jobs=0):
     """What a plan takes on 256 compute units."""
-    res = subprocess.run([kernel_driver] + [str(v) for v in (K, r, K, N, T, mode, 0, 256, 16)], capture_output=True, text=True,
+    res = subprocess.run([kernel_driver] + [str(v) for v in (K, r, K, N, T, mode, jobs, 256, 16)], capture_output=True, text=True,
                          env=dict(os.environ, SHIM_PLAN_ONLY="1", **ENV), timeout=600)
     assert res.returncode == 0, res.stdout + res.stderr
     return dict(l.split() for l in res.stdout.splitlines())
@@ -272,6 +272,20 @@ def test_packs_at_any_element(kernel_driver, case, past):  # noqa: F811
     res = subprocess.run([kernel_driver] + [str(v) for v in case + (8, 8)], capture_output=True, text=True, env=env, timeout=600)
     assert res.returncode == 0, res.stdout + res.stderr
     assert " 0 mismatches" in res.stdout, res.stdout
+
+
+# K, r, N, T, mode, jobs (2: uncoded): lengths that no pack divides
+@pytest.mark.parametrize("K,r,N,T,mode,jobs,wide", [
+    (14, 3, 364, 6735, 4, 0, True),            # 69 MB, one-element packs would be cut too
+    (14, 3, 364, 6735, 1, 0, True),
+    (14, 3, 364, 2735, 4, 0, False),           # 28 MB
+    (24, 1, 24 * 9, 3871, 3, 0, False),        # r = 1: 40 MB of values, 6 MB of lists
+    (4, 2, 6, 6700001, 1, 0, True),            # over 262144 packs
+    (24, 2, 288, 14345, 1, 2, False),          # 397 MB of values, 48 MB of lists
+    (13, 3, 26, 30001, 0, 2, False), (13, 3, 26, 90001, 0, 2, True),
+])
+def test_which_lists_are_wide(kernel_driver, K, r, N, T, mode, jobs, wide):  # noqa: F811
+    assert plan_only(kernel_driver, K, r, N, T, mode, jobs)["wide_lists"] == str(int(wide))
 
 
 @pytest.mark.parametrize("K,r,T,packs", [(8, 6, 1024, 256), (6, 2, 300, 75), (5, 3, 1040, 260)])
