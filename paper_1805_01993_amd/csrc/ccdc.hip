@@ -128,7 +128,7 @@ __global__ __launch_bounds__(kBlock) void k_encode(const typename A::elem *__res
         const uint32_t pos = segment_rank(a, b) * ell + x;
         if (pos < W) acc = O::code(acc, packet_pack<O, true, false, ANY>(rows + (size_t)b * W, pos, W, 1, 0));
     }
-    store_at<false, ANY, P, E>(X + (size_t)ua * ell + x, acc);
+    store_at<false, ANY, P, E>(X + (ANY ? (size_t)ua * ell + x : (size_t)idx * VEC), acc);
 }
 
 // ------------------------------------------------------------------- decode
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(kBlock) void k_decode_sender(const typename A::elem
     const int a = (int)(ua - u * R1);
     const E *rows = Vbar + (size_t)u * R1 * W;
     E *out = D + (size_t)u * R1 * W;
-    const P coded = load_at<true, ANY, P, E>(X + (size_t)ua * ell + x);
+    const P coded = load_at<true, ANY, P, E>(X + (ANY ? (size_t)ua * ell + x : (size_t)idx * VEC));
     P side[R1];
 #pragma unroll
     for (int b = 0; b < R1; b++) {
@@ -228,7 +228,7 @@ __global__ __launch_bounds__(kBlock) void k_shuffle_fused(const typename A::elem
     const uint32_t u = ua / r1;
     const int a = (int)(ua - u * r1);
     const int64_t *src = src_off + (size_t)u * r1;
-    E *to = X + (size_t)ua * ell + x, *Drows = D + (size_t)u * r1 * W;
+    E *to = X + (ANY ? (size_t)ua * ell + x : (size_t)idx * VEC), *Drows = D + (size_t)u * r1 * W;
 
     auto combined = [&](int b) -> P {       // pack of Vbar[u][b] that sender a carries
         return packet_pack<O, KEPT, files_together<O, ANY>(), ANY>(V + src[b], segment_rank(a, b) * ell + x, W, m, file_stride);
