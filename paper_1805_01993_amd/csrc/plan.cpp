@@ -314,7 +314,8 @@ bool wide_lists(int r, bool coded, int64_t nout, int64_t rows, int64_t W, int el
 // pointers that are not aligned for wide packs has more workgroups of the same count.)
 // Lists of over 640 rows are left to the split: 16 nodes, r = 4, T = 728 f32 (1820 rows) 24 us, in one launch 28 to 45; 14
 // nodes, r = 5, T = 1227 f16 (2002) 26, 39; so are inputs past the last-level cache, and one-element packs of 16 bits with over 64
-// rows a wavefront, 1.04 of the time over 31 plans (14 nodes, r = 3, T = 6735 f16 24.0, 29.8; of 2998 16-bit plans 24 were over 3 % slower, 18 of them these).
+// rows a wavefront, 1.04 of the time over 31 plans (of 2998 16-bit plans 24 were over 3 % slower, 18 of them these).  Rows in packs at any element
+// count as wide ones: 14 nodes, r = 3, T = 6735 f16 in one-element packs 24.0 split, 29.8 in one launch; at any element 24.1 and 21.3.
 int plan_groups(int64_t nout, int64_t rows, int64_t W, int vec, int elem, int64_t split, double bytes)
 {
     if (split <= 1 || rows > 640 * nout || bytes > 256e6) return 0;
