@@ -583,19 +583,6 @@ int run_shuffle(const ccdc_plan_t *p, const void *V, void *X, void *D, hipStream
     return launched();
 }
 
-// Whether the fused shuffle takes packs at any element, by the 16-byte packs of its segments.  In 16 bits, one file a batch, from 512
-// thousand on (36 inputs 0.76 of the time, two over 5 % slower; 256 to 512 thousand 27 inputs 0.98, nine, 128 to 256 31 inputs 1.12); several
-// files are asked for together in one-element packs, those of all packets, so only from 256 thousand on with r = 1 (24 inputs 0.51), a million
-// with r = 2 (18 inputs 0.65; half of it 1.07), two million with r >= 3 (7 inputs 0.74; half of it 1.07, less 1.23).  32 bits gain with r <= 2 on
-// large inputs (10 jobs on 5 nodes, r = 2, T = 400097 u32 95 -> 79 us; from two million packs on 11 inputs 0.96, below 1.05), else
-// one-element packs are faster (4 nodes, r = 3, T = 4015094 f32 25.0 and 27.4, 6 nodes, r = 5, T = 1690898 u32 73 and 79).
-bool shuffle_any(const ccdc_plan_t *p)
-{
-    const bool half = elem_bytes(p->mode) == 2;
-    if (!half && (p->r > 2 || moved_bytes(p, 0) < kAnyListBytes)) return false;
-    return makes_lanes(p, p->nrows, p->ell, !half ? 64 : p->m == 1 ? 16 : p->r == 1 ? 8 : p->r == 2 ? 32 : 64);
-}
-
 // SHARED: rows begin anywhere in a cache line, see kKeptPacketBytes.
 template <class A, int VEC, bool ANY, bool SHARED = VEC == 1>
 void reduce_in_groups(const ccdc_plan_t *p, const void *V, const void *D, void *Phi, bool kept, hipStream_t st)
@@ -828,8 +815,8 @@ int ccdc_combine(const ccdc_plan_t *plan, const void *V, void *Vbar, void *strea
     int rc = ready(plan), vec = 1;
     bool any = false;
     if (rc != CCDC_OK) return rc;
-    if ((rc = pick_wide(plan, &vec, &any, makes_lanes(plan, plan->nrows, plan->W, plan->m == 1 ? 1 : 4), V, (const void *)Vbar)) != CCDC_OK) return rc;
-    // (packets of up to 16 packs keep to a wavefront each)
+    if ((rc = pick_wide(plan, Call::combine, -1, &vec, &any, V, (const void *)Vbar)) != CCDC_OK) return rc;
+    // (packets of up to 16 packs are left as they are: in f32 and u32, batches of eight files and more have a wavefront each)
     if (!any && plan->W / vec > 16) narrow_files(plan, plan->compression ? plan->batch_first[1] : plan->m, plan->nrows, plan->W, &vec);
     hipStream_t st = (hipStream_t)stream;
     CCDC_DISPATCH(plan, vec, any, (run_combine<A, VEC, ANY>(plan, V, Vbar, st)));
@@ -841,8 +828,7 @@ int ccdc_encode(const ccdc_plan_t *plan, const void *Vbar, void *X, void *stream
     bool any = false;
     if (rc != CCDC_OK) return rc;
     if (plan->compression) return CCDC_ESTATE;       // nothing is coded in that scheme
-    // 64 to 128 thousand packs at any element 0.84 (16 bits) and 0.97 of the time over 35 inputs, half as many 1.05 and 1.01 over 26
-    if ((rc = pick_wide(plan, &vec, &any, makes_lanes(plan, plan->nrows, plan->ell, 2), Vbar, (const void *)X)) != CCDC_OK) return rc;
+    if ((rc = pick_wide(plan, Call::encode, -1, &vec, &any, Vbar, (const void *)X)) != CCDC_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     CCDC_DISPATCH(plan, vec, any, (run_encode<A, VEC, ANY>(plan, Vbar, X, st)));
 }
@@ -853,10 +839,7 @@ int ccdc_decode(const ccdc_plan_t *plan, const void *X, const void *Vbar, void *
     bool any = false;
     if (rc != CCDC_OK) return rc;
     if (plan->compression) return CCDC_ESTATE;       // nothing is coded in that scheme
-    // 16 bits: 128 to 256 thousand packs at any element 0.91 of the time (51 inputs), half as many 1.03, a quarter 1.26; 32 bits: 256
-    // to 512 thousand 0.95 (46 inputs), half as many 1.03, a quarter 1.13 (the ends of packets are made element by element)
-    const double lanes = elem_bytes(plan->mode) == 2 ? 4 : 8;
-    if ((rc = pick_wide(plan, &vec, &any, makes_lanes(plan, plan->nrows, plan->ell, lanes), X, Vbar, (const void *)D)) != CCDC_OK) return rc;
+    if ((rc = pick_wide(plan, Call::decode, -1, &vec, &any, X, Vbar, (const void *)D)) != CCDC_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     CCDC_DISPATCH(plan, vec, any, (run_decode<A, VEC, ANY>(plan, X, Vbar, D, st)));
 }
@@ -866,7 +849,7 @@ int ccdc_reduce(const ccdc_plan_t *plan, const void *V, const void *D, void *Phi
     int rc = ready(plan), vec = 1;
     bool any = false;
     if (rc != CCDC_OK) return rc;
-    if ((rc = pick_wide(plan, &vec, &any, plan->wide_lists, V, D, (const void *)Phi)) != CCDC_OK) return rc;
+    if ((rc = pick_wide(plan, Call::reduce, -1, &vec, &any, V, D, (const void *)Phi)) != CCDC_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     CCDC_DISPATCH(plan, vec, any, (run_reduce<A, VEC, ANY>(plan, V, D, Phi, st)));
 }
@@ -877,7 +860,7 @@ int ccdc_shuffle_fused(const ccdc_plan_t *plan, const void *V, void *X, void *D,
     bool any = false;
     if (rc != CCDC_OK) return rc;
     if (plan->compression) return CCDC_ESTATE;       // nothing is coded in that scheme
-    if ((rc = pick_wide(plan, &vec, &any, shuffle_any(plan), V, (const void *)X, (const void *)D)) != CCDC_OK) return rc;
+    if ((rc = pick_wide(plan, Call::shuffle, -1, &vec, &any, V, (const void *)X, (const void *)D)) != CCDC_OK) return rc;
     if (!any) narrow_files(plan, plan->m, plan->nrows, plan->ell, &vec);
     hipStream_t st = (hipStream_t)stream;
     CCDC_DISPATCH(plan, vec, any, (run_shuffle<A, VEC, ANY>(plan, V, X, D, st)));

@@ -617,12 +617,6 @@ inline int ready(const ccdc_plan_t *p)
 // a step from files on 24 nodes (43 MB read) 47 -> 41, but the four stages at 87 MB a call (12 nodes, T = 6000 f16)
 // 43.7 -> 46.4.
 
-// The bytes a call that reads V moves, with `elements` of other inputs and outputs.
-inline double moved_bytes(const ccdc_plan_t *p, double elements)
-{
-    return ((double)p->J * p->N * p->Q * (double)p->T + elements) * elem_bytes(p->mode);
-}
-
 // Calls launch(kept) with that as a compile-time constant.  ALWAYS: only true is asked for.
 template <bool ALWAYS, class F>
 void by_reads(bool kept, F launch)
@@ -665,21 +659,15 @@ int pick_vec(const ccdc_plan_t *p, int *vec, Ptr... ptrs)
     return CCDC_OK;
 }
 
-// The widest packs a call can be made of: pick_vec()'s, or packs of 16 bytes at any element (*any), where those would be one-element
-// packs and `wide` says so.
+// The widest packs a call (of node `node`, -1 for all) can be made of: pick_vec()'s, or packs of 16 bytes at any element (*any), where
+// those would be one-element packs and any_element() says so.
 template <class... Ptr>
-int pick_wide(const ccdc_plan_t *p, int *vec, bool *any, bool wide, Ptr... ptrs)
+int pick_wide(const ccdc_plan_t *p, Call call, int node, int *vec, bool *any, Ptr... ptrs)
 {
     const int rc = pick_vec(p, vec, ptrs...);
-    *any = rc == CCDC_OK && *vec == 1 && wide && wide_anyway(p->r, p->W, p->ell, elem_bytes(p->mode));
+    *any = rc == CCDC_OK && *vec == 1 && any_element(p, call, node);
     if (*any) *vec = 16 / elem_bytes(p->mode);
     return rc;
-}
-
-// Whether `rows` rows of `length` elements make `times` kAnyLanes packs of 16 bytes.
-inline bool makes_lanes(const ccdc_plan_t *p, int64_t rows, int64_t length, double times)
-{
-    return (double)rows * (double)length * elem_bytes(p->mode) >= 16 * times * kAnyLanes;
 }
 
 // Batches of more than two files that make fewer than 128 thousand packs of 16 bytes (16 bits: 64) leave the chip short of lanes, each with the files of

@@ -109,7 +109,7 @@ extern "C" int ccdc_map(const ccdc_plan_t *plan, const void *files, const void *
     if (rc != CCDC_OK) return rc;
     if ((rc = pick_vec(plan, &vec, files, theta, (const void *)V)) != CCDC_OK) return rc;
     const int rows_align = vec, most = 16 / elem_bytes(plan->mode);
-    const bool any = vec < most && makes_lanes(plan, (int64_t)plan->J * plan->N, (int64_t)plan->Q * plan->T, vec == 1 ? 2 : 4);
+    const bool any = vec < most && (vec == 1 ? any_element(plan, Call::map) : makes_lanes(plan, (int64_t)plan->J * plan->N, (int64_t)plan->Q * plan->T, 4));
     hipStream_t st = (hipStream_t)stream;
     CCDC_DISPATCH(plan, vec, any, (run_map<A, VEC, ANY>(plan, rows_align, files, theta, V, st)));
 }

@@ -637,19 +637,6 @@ CCDC_NODE(HybF16);
 #if !defined(CCDC_NODE_PART) || CCDC_NODE_PART == 0
 namespace {
 
-// The 16-byte packs, in kAnyLanes, from which on ccdc_node_encode makes them at any element.  One file a batch, or one packet in the making: 16 bits
-// from 64 thousand on (up to 256 thousand 39 inputs 0.86 of the time, three over 5 % slower; several files for a node alone 1.13, from 128 thousand
-// on 0.61), 32 bits from 256 thousand (29 inputs 0.85; fewer, 47 inputs, 0.94, but seven up to 1.27).  With several files and 2 <= r <= 5
-// one-element packs ask for the files of all packets together: 16 bits from half a million on (54 inputs 0.81; half of it 1.02, a quarter 1.30), 32
-// bits from four million (6 inputs 0.93; fewer, 92 inputs, 1.06).  A node alone from a quarter of a million on (10 and 13 inputs 0.74
-// and 0.88; half of it 1.08 and 1.04).
-double encode_lanes(const ccdc_plan_t *p, int node)
-{
-    const bool half = elem_bytes(p->mode) == 2;
-    if (p->m == 1 || p->r == 1 || p->r > 5) return !half ? 8 : p->m == 1 ? 2 : 4;
-    return node >= 0 ? 8 : half ? 16 : 128;
-}
-
 int node_ready(const ccdc_plan_t *plan, int node)
 {
     const int rc = ready(plan);
@@ -668,10 +655,8 @@ int ccdc_node_encode(const ccdc_plan_t *plan, int node, const void *V, void *X, 
     int rc = node_ready(plan, node), vec = 1;
     bool any = false;
     if (rc != CCDC_OK) return rc;
-    const int64_t rows = node < 0 ? plan->nrows : plan->rows_per_node;
-    const bool wide = wide_fills(plan->ell, elem_bytes(plan->mode)) && makes_lanes(plan, rows, plan->ell, encode_lanes(plan, node));
-    if ((rc = pick_wide(plan, &vec, &any, wide, V, (const void *)X)) != CCDC_OK) return rc;
-    if (!any) narrow_files(plan, plan->m, rows, plan->ell, &vec);
+    if ((rc = pick_wide(plan, Call::node_encode, node, &vec, &any, V, (const void *)X)) != CCDC_OK) return rc;
+    if (!any) narrow_files(plan, plan->m, node < 0 ? plan->nrows : plan->rows_per_node, plan->ell, &vec);
     hipStream_t st = (hipStream_t)stream;
     switch (plan->mode) {
     case CCDC_F32_SUM: return node_encode<SumF32>(plan, vec, any, node, V, X, st);
@@ -687,11 +672,7 @@ int ccdc_node_decode_reduce(const ccdc_plan_t *plan, int node, const void *V, co
     int rc = node_ready(plan, node), vec = 1;
     bool any = false;
     if (rc != CCDC_OK) return rc;
-    bool wide = plan->wide_lists && wide_fills(plan->ell, elem_bytes(plan->mode));
-    // One node of a plan whose lists are not cut has a K-th of the lanes: packs at any element from 64 thousand of its own on (32 bits, several
-    // files: 128): 31 inputs 0.77 of the time, none slower, 26 of fewer 1.14, up to 1.98.  (The width of packs does not change the order of sums.)
-    if (node >= 0 && plan->red_split == 1) wide = wide && makes_lanes(plan, plan->J, plan->W, elem_bytes(plan->mode) == 4 && plan->m > 1 ? 4 : 2);
-    if ((rc = pick_wide(plan, &vec, &any, wide, V, X, (const void *)Phi)) != CCDC_OK) return rc;
+    if ((rc = pick_wide(plan, Call::node_decode, node, &vec, &any, V, X, (const void *)Phi)) != CCDC_OK) return rc;
     if (plan->node_waves > 0) return receive_coded(plan, node, V, X, Phi, stream);
     hipStream_t st = (hipStream_t)stream;
     switch (plan->mode) {

@@ -602,4 +602,47 @@ int bind_plan(ccdc_plan_t *p, int64_t T, int mode)
     return CCDC_OK;
 }
 
+// The lines are where the one-element packs stop being faster; packs and times as there were with the calls alone, over draws of 64 KB to 3 GB.
+bool any_element(const ccdc_plan_t *p, Call call, int node)
+{
+    const int elem = elem_bytes(p->mode);
+    const bool half = elem == 2;
+    if (call == Call::map)                           // see k_map
+        return makes_lanes(p, (int64_t)p->J * p->N, (int64_t)p->Q * p->T, 2);
+    if (!wide_anyway(p->r, p->W, p->ell, elem)) return false;
+    switch (call) {
+    case Call::combine: return makes_lanes(p, p->nrows, p->W, p->m == 1 ? 1 : 4);
+    // 64 to 128 thousand packs 0.84 (16 bits) and 0.97 of the time over 35 inputs, half as many 1.05 and 1.01 over 26
+    case Call::encode: return makes_lanes(p, p->nrows, p->ell, 2);
+    // 16 bits: 128 to 256 thousand packs 0.91 of the time (51 inputs), half as many 1.03, a quarter 1.26; 32 bits: 256 to 512 thousand
+    // 0.95 (46 inputs), half as many 1.03, a quarter 1.13 (the ends of packets are made element by element)
+    case Call::decode: return makes_lanes(p, p->nrows, p->ell, half ? 4 : 8);
+    case Call::reduce: return p->wide_lists;
+    // By the packs of the segments.  In 16 bits, one file a batch, from 512 thousand on (36 inputs 0.76 of the time, two over 5 % slower; 256
+    // to 512 thousand 27 inputs 0.98, nine, 128 to 256 31 inputs 1.12); several files are asked for together in one-element packs, those of
+    // all packets, so only from 256 thousand on with r = 1 (24 inputs 0.51), a million with r = 2 (18 inputs 0.65; half of it 1.07), two
+    // million with r >= 3 (7 inputs 0.74; half of it 1.07, less 1.23).  32 bits gain with r <= 2 on large inputs (10 jobs on 5 nodes, r = 2,
+    // T = 400097 u32 95 -> 79 us; from two million packs on 11 inputs 0.96, below 1.05), else one-element packs are faster (4 nodes, r = 3, T =
+    // 4015094 f32 25.0 and 27.4, 6 nodes, r = 5, T = 1690898 u32 73 and 79).
+    case Call::shuffle:
+        if (!half && (p->r > 2 || moved_bytes(p, 0) < kAnyListBytes)) return false;
+        return makes_lanes(p, p->nrows, p->ell, !half ? 64 : p->m == 1 ? 16 : p->r == 1 ? 8 : p->r == 2 ? 32 : 64);
+    // One file a batch, or one packet in the making: 16 bits from 64 thousand on (up to 256 thousand 39 inputs 0.86 of the time, three over
+    // 5 % slower; several files for a node alone 1.13, from 128 thousand on 0.61), 32 bits from 256 thousand (29 inputs 0.85; fewer, 47
+    // inputs, 0.94, but seven up to 1.27).  With several files and 2 <= r <= 5 one-element packs ask for the files of all packets
+    // together: 16 bits from half a million on (54 inputs 0.81; half of it 1.02, a quarter 1.30), 32 bits from four million (6 inputs 0.93;
+    // fewer, 92 inputs, 1.06).  A node alone from a quarter of a million on (10 and 13 inputs 0.74 and 0.88; half of it 1.08 and 1.04).
+    case Call::node_encode: {
+        double lanes = node >= 0 ? 8 : half ? 16 : 128;
+        if (p->m == 1 || p->r == 1 || p->r > 5) lanes = !half ? 8 : p->m == 1 ? 2 : 4;
+        return wide_fills(p->ell, elem) && makes_lanes(p, node < 0 ? p->nrows : p->rows_per_node, p->ell, lanes);
+    }
+    // One node of a plan whose lists are not cut has a K-th of the lanes: from 64 thousand packs of its own on (32 bits, several files: 128)
+    // 31 inputs 0.77 of the time, none slower, 26 of fewer 1.14, up to 1.98.  (The width of packs does not change the order of sums.)
+    default:
+        if (node >= 0 && p->red_split == 1 && !makes_lanes(p, p->J, p->W, !half && p->m > 1 ? 4 : 2)) return false;
+        return p->wide_lists && wide_fills(p->ell, elem);
+    }
+}
+
 }  // namespace ccdc

@@ -132,7 +132,7 @@ CCDC_READ_LIMIT kKeptPacketBytes = 100e6, kKeptSharedBytes = 200e6;
 CCDC_READ_LIMIT kKeptWideBytes = 1.4e9;        // from these on
 
 // Packs of a segment from which on they may begin at any element, and the 16-byte packs that a call must make for it
-// (pick_wide() in common.hpp, wide_lists() in plan.cpp).
+// (any_element() and wide_lists() in plan.cpp).
 CCDC_READ_LIMIT kAnyPacks = 32, kAnyLanes = 32e3, kAnyListPacks = 1 << 18, kAnyListBytes = 200e6;
 CCDC_READ_LIMIT kUnequalChunks = 1.7, kUnequalFileChunks = 2;      // lists_by_round() in plan.cpp
 
@@ -228,6 +228,23 @@ inline bool wide_fills(int64_t ell, int elem)
 {
     return fills_wavefronts(cdiv(ell, 16 / elem)) || !fills_wavefronts((uint32_t)ell);
 }
+
+// The bytes a call that reads V moves, with `elements` of other inputs and outputs.
+inline double moved_bytes(const ccdc_plan_t *p, double elements)
+{
+    return ((double)p->J * p->N * p->Q * (double)p->T + elements) * elem_bytes(p->mode);
+}
+
+// Whether `rows` rows of `length` elements make `times` kAnyLanes packs of 16 bytes.
+inline bool makes_lanes(const ccdc_plan_t *p, int64_t rows, int64_t length, double times)
+{
+    return (double)rows * (double)length * elem_bytes(p->mode) >= 16 * times * kAnyLanes;
+}
+
+// Whether a call (of node `node`, -1 for all) whose value length or pointers only allow one-element packs is made of 16-byte packs at any
+// element.
+enum class Call { map, combine, encode, decode, reduce, shuffle, node_encode, node_decode };
+bool any_element(const ccdc_plan_t *p, Call call, int node = -1);
 
 // Elements of the packs of a node-local decoding with aligned pointers.  any: lists may be summed in packs at any element.
 inline int node_pack(bool any, int elem, int64_t T, int64_t ell)

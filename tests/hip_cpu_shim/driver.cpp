@@ -234,6 +234,11 @@ int main(int argc, char **argv)
         std::printf("launch %d,%d,%d,%d\n", launch[0], launch[1], launch[2], launch[3]);
         std::printf("by_round %d\n", p->node_list.empty() ? 0 : 1);
         std::printf("wide_lists %d\n", p->wide_lists ? 1 : 0);
+        std::printf("any_element ");                         // with pointers that are aligned to their elements only
+        using ccdc::Call;
+        for (Call c : {Call::map, Call::combine, Call::encode, Call::decode, Call::reduce, Call::shuffle, Call::node_encode, Call::node_decode})
+            std::printf("%d", ccdc::any_element(p, c) ? 1 : 0);
+        std::printf("%d%d\n", ccdc::any_element(p, Call::node_encode, 0) ? 1 : 0, ccdc::any_element(p, Call::node_decode, 0) ? 1 : 0);
         ccdc_plan_destroy(p);
         return 0;
     }
