@@ -632,7 +632,8 @@ void by_reads(bool kept, F launch)
 // the packets that the next call reads (the four stages, 9 nodes, r = 2, T = 150001 f32, 151 MB of packets, 311 -> 327; 10
 // nodes, r = 3, T = 100001 bf16, 168 MB, 473 -> 490; but the uncoded scheme, 22 nodes, T = 85615 u32, 79 MB, 392 -> 383).
 // For ccdc_map, which reads each line once, they are packs like others (62 MB and less 0.73 to 0.82 of the time, more
-// 1.00 to 1.04).
+// 1.00 to 1.04).  The lengths in these figures were all read in one-element packs; since packs at any element the rules are left with segments
+// of under 32 packs, with the fused shuffle of 32-bit values (r >= 3, or under 200 MB) and with what else any_element() says no to.
 
 // Pack width (elements) for this call: 16 bytes when the value length, the
 // segment length and every pointer allow it; for 2-byte elements else 8 bytes;

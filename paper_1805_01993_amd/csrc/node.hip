@@ -451,7 +451,8 @@ void by_shape(const ccdc_plan_t *p, bool together, F launch)
 //   15 jobs, r = 3, 6 nodes u32, 1.2 GB (77 MB a job) 463 / 495 / 528
 // With r = 1 nothing is read twice: 12 nodes f32, 35 MB 35 / 38 / 39, 72 MB 51 / 50 / 49, 288 MB 154 / 154 / 150, 1.2 GB
 // 576 / 571 / 547.  One-element packs and the lane-packed kernels share lines with their neighbours and gain nothing past the
-// caches (8 nodes, r = 4, T = 1024001 f32 1343 / 1335 / 1455; 24 nodes, r = 4, T = 200 f32 248 / 300 / 300).
+// caches (8 nodes, r = 4, T = 1024001 f32 1343 / 1335 / 1455; 24 nodes, r = 4, T = 200 f32 248 / 300 / 300; the first, like the
+// 24 nodes below, is read in packs at any element since, and one-element packs are segments of under 32 of those).
 //   One node, its two calls for every node of the cluster in turn, everything kept / everything past: 6 nodes, r = 3, ten files
 // a batch, h32: 96 MB 343 / 495, 480 MB 662 / 702; 8 nodes, r = 6, f32: 358 MB 329 / 375, 1.4 GB 665 / 619; 10 nodes, r = 3,
 // f32, 1.8 GB 1130 / 994; 24 nodes, r = 4, T = 2047 f32 (2.1 GB, one-element packs) 17580 / 14570.

@@ -33,13 +33,22 @@ def plain(torch, V, mode, dt):
     return want
 
 
-# last segments one element short of a pack, one long, of whole packs; several files; r beyond what decoding by sender is unrolled for
+# K, r, c, m, T, mode and which calls are made of 16-byte packs at any element, where pointers are aligned to their elements only: map,
+# combine, encode, decode, reduce, fused shuffle, node-local sending and decoding, those two for one node (test_sanitized_geometry.py asks the
+# library).  Lists that are not cut and cut ones, by round and in equal parts; segments that fill wavefronts and (19 nodes) that do not; last
+# segments one element short of a pack, one long, of whole packs; several files; r beyond what decoding by sender is unrolled for; a length
+# that packs divide, for the pointers alone.
+CODED = [
+    (6, 2, 1, 1, 140001, "bf16", "1111011010"), (6, 2, 1, 1, 90002, "f32", "1111001000"), (7, 3, 1, 1, 150003, "u32", "1111101100"),
+    (5, 1, 1, 1, 420003, "f16", "1111111110"), (5, 1, 2, 2, 150001, "h32", "1111101110"), (7, 4, 1, 3, 40005, "bf16", "1111000000"),
+    (8, 6, 1, 1, 60001, "bf16", "1110001000"), (13, 3, 1, 5, 6031, "bf16", "1111101101"), (14, 3, 1, 1, 6735, "f16", "1111111111"),
+    (14, 3, 1, 1, 6735, "u32", "1111101101"), (19, 4, 1, 1, 525, "u32", "1111101101"), (7, 3, 1, 2, 360003, "f16", "1111111110"),
+    (9, 5, 2, 4, 3381, "f16", "1110100101"), (6, 2, 1, 1, 140000, "f16", "1111011010"), (7, 5, 2, 1, 3011, "h32", "1100000000"),
+]
+
+
 @pytest.mark.parametrize("shift", [0, 1])
-@pytest.mark.parametrize("K,r,c,m,T,mode", [
-    (6, 2, 1, 1, 90001, "bf16"), (6, 2, 1, 1, 90002, "f32"), (7, 3, 1, 1, 40003, "u32"), (5, 1, 1, 1, 200003, "f16"),
-    (5, 1, 2, 2, 100001, "h32"), (7, 4, 1, 3, 20005, "bf16"), (7, 5, 2, 1, 30011, "h32"), (8, 6, 1, 1, 60001, "bf16"),
-    (13, 3, 1, 5, 1031, "bf16"), (6, 2, 1, 1, 90000, "f16"),
-])
+@pytest.mark.parametrize("K,r,c,m,T,mode", [case[:6] for case in CODED])
 def test_calls_of_coded_plans(K, r, c, m, T, mode, shift):
     import torch
 
@@ -75,8 +84,12 @@ def test_calls_of_coded_plans(K, r, c, m, T, mode, shift):
     plan.close()
 
 
+# K, r, N, T (f32), the same for map, combine and reduce
+UNCODED = [(13, 3, 26, 90001, "111"), (5, 1, 40, 220003, "111"), (9, 5, 18, 120002, "111"), (9, 5, 18, 50002, "100"), (24, 2, 144, 7003, "110")]
+
+
 @pytest.mark.parametrize("shift", [0, 1])
-@pytest.mark.parametrize("K,r,N,T", [(13, 3, 26, 30001), (5, 1, 40, 100003), (9, 5, 18, 50002)])
+@pytest.mark.parametrize("K,r,N,T", [case[:4] for case in UNCODED])
 def test_uncoded_plans(K, r, N, T, shift):
     import torch
 

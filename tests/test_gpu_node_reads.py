@@ -20,7 +20,8 @@ pytestmark = pytest.mark.gpu
     (5, 3, 1, 3_400_000, "u32"),          # r = 3: 512 MB; a node alone: 640 MB
     (6, 4, 1, 2_400_000, "u32"),
     (6, 5, 1, 7_700_000, "u32"),
-    (4, 2, 1, 6_700_001, "u32"),          # one-element packs, a node alone past the caches
+    (4, 2, 1, 6_700_001, "u32"),          # packs at any element, a node alone past the caches
+    (26, 4, 1, 495, "u32"),               # one-element packs (segments of under 32 packs), the same
     (7, 6, 1, 3_400_000, "u32"),          # the lane-packed kernels, the same
 ])
 def test_large_inputs(K, r, m, T, mode):

@@ -21,14 +21,15 @@ def xor(t, dim):
 # K, r, files a batch, T.  Four nodes, r = 2, one file a batch: an element of T stands for 24 of V, 12 of Vbar and D, 6 of X
 # and 4 of Phi, so the limits of 64 MB (of what a stage reads and writes, map: reads) and 128 MB (the one-pass kernel) lie at
 # T = 380952 for ccdc_shuffle_fused, 400000 for ccdc_reduce, 444444 for ccdc_combine, 571429 for ccdc_map, 941176 for
-# ccdc_pipeline_fused; that of 100 MB for one-element packets at T = 2083333.
+# ccdc_pipeline_fused.  That of 100 MB for one-element packets, which lengths take that four does not divide and whose segments
+# have under 32 packs, lies at T = 243.5 for 60 nodes (102660 packets).
 SHAPES = [(4, 2, 1, 8192), (4, 2, 1, 8190), (4, 2, 1, 8191), (4, 2, 1, 700_000), (4, 2, 1, 700_004),
           (4, 2, 1, 800_000), (4, 2, 1, 860_000), (4, 2, 1, 1_048_576), (4, 2, 1, 1_048_580),
           (4, 2, 1, 1_048_575), (4, 1, 2, 1_048_576), (4, 1, 2, 1_048_574), (4, 1, 2, 4096),
           (12, 3, 1, 8_192), (12, 3, 1, 8_196), (12, 3, 1, 8_193),
           (4, 2, 1, 380_928), (4, 2, 1, 380_960), (4, 2, 1, 399_968), (4, 2, 1, 400_032), (4, 2, 1, 444_416),
           (4, 2, 1, 444_448), (4, 2, 1, 571_424), (4, 2, 1, 571_456), (4, 2, 1, 941_152), (4, 2, 1, 941_184),
-          (4, 2, 1, 2_083_331), (4, 2, 1, 2_083_335)]
+          (60, 2, 1, 243), (60, 2, 1, 245)]
 
 
 def test_the_shapes_lie_on_both_sides():
@@ -38,7 +39,9 @@ def test_the_shapes_lie_on_both_sides():
     for per, limit in at.values():
         near = [T for T in lengths if abs(T * per * 4 / limit - 1) < 2e-4 and T % 32 == 0]
         assert {T * per * 4 <= limit for T in near} == {True, False}
-    assert {T * 12 * 4 <= 100e6 for T in lengths if T % 4 and T > 2_000_000} == {True, False}
+    one_element = [T for K, r, m, T in SHAPES if K == 60]
+    assert all(T % 4 and (-(-T // 2) + 3) // 4 < 32 for T in one_element)
+    assert {T * 3 * math.comb(60, 3) * 4 <= 100e6 for T in one_element} == {True, False}
 
 
 @pytest.mark.parametrize("K,r,m,T", SHAPES)

@@ -11,6 +11,8 @@ from math import comb
 
 import pytest
 
+import test_gpu_any_length as any_length
+import test_gpu_node_rounds as node_rounds
 from test_sanitized_host_code import ENV, kernel_driver  # noqa: F401  (the fixture)
 
 # K, r, Q, N, T, mode (0 f32, 1 u32, 2 h32, 3 bf16, 4 f16), jobs, compute units, wavefronts a unit holds
@@ -178,9 +180,9 @@ def test_forms_of_the_reductions(kernel_driver, r, m):  # noqa: F811
         list(pool.map(run, range(4), ends))
 
 
-def plan_only(kernel_driver, K, r, N, T, mode, jobs=0):
+def plan_only(kernel_driver, K, r, N, T, mode, jobs=0, c=1):
     """What a plan takes on 256 compute units."""
-    res = subprocess.run([kernel_driver] + [str(v) for v in (K, r, K, N, T, mode, jobs, 256, 16)], capture_output=True, text=True,
+    res = subprocess.run([kernel_driver] + [str(v) for v in (K, r, c * K, N, T, mode, jobs, 256, 16)], capture_output=True, text=True,
                          env=dict(os.environ, SHIM_PLAN_ONLY="1", **ENV), timeout=600)
     assert res.returncode == 0, res.stdout + res.stderr
     return dict(l.split() for l in res.stdout.splitlines())
@@ -291,6 +293,26 @@ def test_packs_at_any_element(kernel_driver, case, past):  # noqa: F811
 ])
 def test_which_lists_are_wide(kernel_driver, K, r, N, T, mode, jobs, wide):  # noqa: F811
     assert plan_only(kernel_driver, K, r, N, T, mode, jobs)["wide_lists"] == str(int(wide))
+
+
+MODES = ["f32", "u32", "h32", "bf16", "f16"]
+
+
+@pytest.mark.parametrize("K,r,c,m,T,mode,calls", any_length.CODED)
+def test_which_calls_take_packs_at_any_element(kernel_driver, K, r, c, m, T, mode, calls):  # noqa: F811
+    """The GPU test's plans lie on the sides of the lines that it says they do."""
+    assert plan_only(kernel_driver, K, r, m * comb(K, r), T, MODES.index(mode), c=c)["any_element"] == calls
+
+
+@pytest.mark.parametrize("K,r,m,T,mode,by_round", node_rounds.LISTS)
+def test_which_lists_of_the_gpu_test_are_cut_by_round(kernel_driver, K, r, m, T, mode, by_round):  # noqa: F811
+    assert plan_only(kernel_driver, K, r, m * comb(K, r), T, MODES.index(mode))["by_round"] == str(int(by_round))
+
+
+@pytest.mark.parametrize("K,r,N,T,calls", any_length.UNCODED)
+def test_which_uncoded_calls_take_packs_at_any_element(kernel_driver, K, r, N, T, calls):  # noqa: F811
+    taken = plan_only(kernel_driver, K, r, N, T, 0, jobs=2)["any_element"]
+    assert taken[:2] + taken[4] == calls
 
 
 @pytest.mark.parametrize("K,r,T,packs", [(8, 6, 1024, 256), (6, 2, 300, 75), (5, 3, 1040, 260)])
