@@ -330,9 +330,39 @@ int plan_groups(int64_t nout, int64_t rows, int64_t W, int vec, int elem, int64_
     return narrow && rows > 64 * nout * waves ? 0 : (int)waves;
 }
 
+// The chunk of the row lists that each round's packets go to: of a few, the next in turn among them, the one that is shortest where the
+// round's members have most, so that a node's packets are spread evenly whatever the order of the rounds.  (In turn alone the longest
+// chunk of 16 nodes, r = 3, 32 chunks has 1.69 times the mean, of 24 nodes, r = 4, 25 chunks 1.46; the best of two 1.34 and 1.02, of four
+// 1.20 and 1.01.)  count: [node][chunk] of packets, zeros at first.
+template <int R1>
+void spread_rounds(const int32_t *member, int64_t rounds, int split, int choices, int32_t *count, uint8_t *chunk)
+{
+    const int step = (split + choices - 1) / choices;
+    for (int64_t u = 0, turn = 0; u < rounds; u++, turn = turn + 1 == split ? 0 : turn + 1) {
+        const int32_t *in = member + u * R1;
+        int best = (int)turn;
+        int64_t least = std::numeric_limits<int64_t>::max();
+        for (int c = 0, s = (int)turn; c < choices; c++) {
+            int32_t most = 0;
+            int64_t sum = 0;
+            for (int b = 0; b < R1; b++) {
+                const int32_t n = count[in[b] * (int64_t)split + s];
+                most = std::max(most, n);
+                sum += n;
+            }
+            const int64_t cost = ((int64_t)most << 32) + sum;
+            if (cost < least) least = cost, best = s;
+            s += step;
+            if (s >= split) s -= split;
+        }
+        for (int b = 0; b < R1; b++) count[in[b] * (int64_t)split + best]++;
+        chunk[u] = (uint8_t)best;
+    }
+}
+
 // The row lists of ccdc_node_decode_reduce and the chunks they are cut into.  A coded packet is read by its r receivers and a value
 // that is side information by r - 1, so lists are best cut by rounds: chunk s of every list then has the packets of the
-// same rounds, s, s + split, s + 2 split, .. (a chunk of neighbouring rounds would have all of the first node's),
+// same rounds (not of neighbouring ones, which would be all of the first nodes'),
 // and units that are numbered by chunk (node.hip) read them together, behind one L2.  The price is chunks of unequal length, and
 // a chunk is a chain of waits, on an XCD with the same chunk of other lists: no such lists where the longest has over kUnequalChunks
 // times the mean to load (kUnequalFileChunks with several files a batch).
@@ -342,9 +372,10 @@ void lists_by_round(const ccdc_plan_t *p, int64_t local_rows, int64_t split, std
     const int64_t loads = 1 + (int64_t)(p->r - 1) * p->m;    // of a received packet: the coded one and the files of r - 1 batches
     const int64_t chunks = p->K * split;
     std::vector<int32_t> at((size_t)chunks + 1, 0);
-    const int32_t *member = p->round_member.data();
-    for (int64_t u = 0, s = 0; u < p->nround; u++, s = s + 1 == split ? 0 : s + 1)
-        for (int b = 0; b < r1; b++) at[member[u * r1 + b] * split + s + 1]++;
+    std::vector<uint8_t> chunk((size_t)p->nround);           // split <= 256
+    const int choices = p->nround > 8192 ? 2 : 4;            // many rounds are spread well enough by two, in half the time
+    auto spread = p->r == 3 ? spread_rounds<4> : p->r == 4 ? spread_rounds<5> : spread_rounds<6>;
+    spread(p->round_member.data(), p->nround, (int)split, choices, at.data() + 1, chunk.data());
     int64_t longest = 0;                                     // with the chunk's part of the files the node stores
     for (int64_t i = 0; i < chunks; i++) {
         const int64_t s = i % split;
@@ -358,15 +389,7 @@ void lists_by_round(const ccdc_plan_t *p, int64_t local_rows, int64_t split, std
     for (int k = 0; k < p->K; k++) {                         // a list after the other: its chunks' ends stay in the first cache
         int32_t *end = at.data() + k * split;
         const int32_t *packet = p->node_rows.data() + k * p->rows_per_node;
-        uint32_t u = 0;
-        int64_t s = 0;
-        for (int64_t j = 0; j < p->rows_per_node; j++) {
-            const uint32_t next = (uint32_t)packet[j] / (uint32_t)r1, on = next - u;
-            u = next;
-            s += on < split ? on : on % split;
-            s -= s >= split ? split : 0;
-            list[end[s]++] = packet[j];
-        }
+        for (int64_t j = 0; j < p->rows_per_node; j++) list[end[chunk[(uint32_t)packet[j] / (uint32_t)r1]]++] = packet[j];
     }
 }
 
@@ -558,16 +581,14 @@ int bind_plan(ccdc_plan_t *p, int64_t T, int mode)
         std::vector<int32_t> node_list;
         const int node_vec = node_pack(any, elem, T, ell);
         // Lists by round: where a value has two readers or more besides its owner's output (r >= 3; r = 2 0.94 to 1.08 of the
-        // time), with a wavefront on one segment and units that are not shared by tile already.  Over 95 such inputs of 3 MB to
-        // 2 GB 0.83 of the time of equal cuts, the least 0.28 (8 nodes, r = 5, twelve files, T = 19008 f32 410 -> 113 us; 16
-        // nodes, r = 3, T = 4096 h32 60.5 -> 50.5).  One file a batch: a chunk may have up to 1.7 times the mean to load
-        // (kUnequalChunks): 118 such plans 0.71 of the time of equal cuts for all nodes and 0.72 for a node alone, seven of those over 5 %
-        // slower; 39 up to twice the mean 0.88 and 0.97, 19 (a node alone shares nothing with others, but its lists are cut as
-        // theirs: 15 nodes, r = 3, T = 4480 h32 13.3 -> 16.0, 19 nodes, r = 3, T = 1408 h32 12.0 -> 14.3); 24 beyond 1.01 and 1.01.  Several
-        // files: equal cuts have the files that a node stores in the first chunks and all packets, of many loads, in the last, so up to twice
-        // the mean 28 plans 0.61 and 0.39, none slower; 22 beyond 0.89, three up to 1.48 (6 nodes, r = 5, ten files, T = 62272 u32: one round,
-        // whose packets are in one chunk and on one XCD).  In few chunks one-element packs gain only while the values' readers
-        // can find them in the last-level cache (21 nodes, r = 3, T = 4711 f32, 1.3 GB, six chunks, 281 -> 295).
+        // time), with a wavefront on one segment and units that are not shared by tile already.  One file a batch: a chunk may have
+        // up to 1.4 times the mean to load (kUnequalChunks): 105 such plans of 1 MB to 1.3 GB 0.75 of the time of equal cuts for all nodes and
+        // 0.74 for a node alone (16 nodes, r = 3, T = 4096 h32 61 -> 48 and 15.4 -> 14.8 us), one of them over 5 % slower, a node alone, which
+        // shares nothing with others; 16 with up to 1.7 times 0.92 and 0.94, four; 42 beyond 1.01 and 1.01.  Several files: equal cuts
+        // have the files that a node stores in the first chunks and all packets, of many loads, in the last, so up to twice the mean 29 plans
+        // 0.62 and 0.39, one of them slower (7 nodes, r = 5, eleven files, T = 142976 u32 255 -> 283); 18 beyond 1.01.  In few chunks
+        // one-element packs gain only while the values' readers can find them in the last-level cache (21 nodes, r = 3, T = 4711
+        // f32, 1.3 GB, six chunks, 281 -> 295).
         const bool wide = node_vec > 1;
         const bool by_round = split > 1 && p->J == 1 && r >= 3 && r <= 5 && fills_wavefronts((uint32_t)(ell / node_vec)) &&
                               (wide || split >= 8 || v_elems * elem <= (r - 1) * kKeptNodeBytes) &&

@@ -134,7 +134,7 @@ CCDC_READ_LIMIT kKeptWideBytes = 1.4e9;        // from these on
 // Packs of a segment from which on they may begin at any element, and the 16-byte packs that a call must make for it
 // (any_element() and wide_lists() in plan.cpp).
 CCDC_READ_LIMIT kAnyPacks = 32, kAnyLanes = 32e3, kAnyListPacks = 1 << 18, kAnyListBytes = 200e6;
-CCDC_READ_LIMIT kUnequalChunks = 1.7, kUnequalFileChunks = 2;      // lists_by_round() in plan.cpp
+CCDC_READ_LIMIT kUnequalChunks = 1.4, kUnequalFileChunks = 2;      // lists_by_round() in plan.cpp
 
 // One-pass pipeline (pipeline.hip): fixes the launch geometry (pipe_vec .. pipe_shallow) for the current device.
 void pipeline_prepare(ccdc_plan_t *p);

@@ -12,8 +12,8 @@ LISTS = [
     (16, 3, 1, 4096, "h32", True),        # 32 chunks, five tiles and a part of one
     (16, 4, 1, 1028, "f32", False),       # one pack past a wavefront's: lane-packed, equal cuts
     (11, 5, 1, 6336, "u32", True),
-    (13, 4, 7, 948, "bf16", False),       # chunks of over twice the mean
-    (13, 4, 7, 2048, "bf16", True),       # seven files' sums
+    (13, 4, 7, 948, "bf16", True),        # seven files' sums, short last segment
+    (13, 3, 1, 1280, "bf16", False),      # chunks of over twice the mean
     (14, 5, 1, 281, "f32", True),         # one-element packs
     (14, 3, 1, 6735, "f16", True),        # packs at any element
     (9, 5, 1, 40704, "h32", False),       # numbered by tile
