@@ -209,14 +209,15 @@ __global__ __launch_bounds__(kBlock) void k_decode_sender(const typename A::elem
 // R1 = r+1 at compile time keeps the r combined packs in registers; R1 = 0 is
 // the any-r fallback that re-reads them (cache hits) instead.
 // MULTI: several files a batch, where their packets are asked for together (a kernel of their own: their sums in the making take
-// registers that the other would pay for with fewer wavefronts); elsewhere the one kernel looks at m.
+// registers that the other would pay for with fewer wavefronts); elsewhere the one kernel looks at m.  What a small call reads of
+// its arguments is in their first 64 bytes.
 template <class A, int VEC, int R1, bool KEPT, bool MULTI, bool ANY>
 __global__ __launch_bounds__(kBlock) void k_shuffle_fused(const typename A::elem *__restrict__ V,
                                                           typename A::elem *__restrict__ X,
                                                           typename A::elem *__restrict__ D,
-                                                          const int64_t *__restrict__ src_off, int r1_rt,
-                                                          uint32_t Lv, uint32_t ell, uint32_t W, int m, int64_t file_stride,
-                                                          uint32_t items, uint32_t span)
+                                                          const int64_t *__restrict__ src_off, uint32_t items, uint32_t Lv,
+                                                          uint32_t ell, uint32_t W, int r1_rt, int m, int64_t file_stride,
+                                                          uint32_t span)
 {
     using E = typename A::elem;
     using O = Ops<A, VEC>;
@@ -558,7 +559,7 @@ void launch_shuffle(const ccdc_plan_t *p, const void *V, void *X, void *D, hipSt
     auto launch = [&](auto multi) {
         by_reads<VEC == 1>(kept, [&](auto k) {
             k_shuffle_fused<A, VEC, R1, decltype(k)::value, decltype(multi)::value, ANY><<<cdiv(items, kBlock), kBlock, 0, st>>>(
-                (const E *)V, (E *)X, (E *)D, p->d_src_off, p->r + 1, Lv, (uint32_t)p->ell, (uint32_t)p->W, p->m, (int64_t)p->Q * p->T, (uint32_t)items, span);
+                (const E *)V, (E *)X, (E *)D, p->d_src_off, (uint32_t)items, Lv, (uint32_t)p->ell, (uint32_t)p->W, p->r + 1, p->m, (int64_t)p->Q * p->T, span);
         });
     };
     if constexpr (R1 > 0 && packets_together<Ops<A, VEC>, R1 - 1>()) {

@@ -26,8 +26,8 @@ template <class A, int VEC, int READS, bool TOGETHER, bool ANY>
 __global__ __launch_bounds__(kBlock) void k_node_encode(const typename A::elem *__restrict__ V,
                                                         typename A::elem *__restrict__ X,
                                                         const int64_t *__restrict__ src_off,
-                                                        const int32_t *__restrict__ rows, int r1, uint32_t Lv, uint32_t ell,
-                                                        uint32_t W, int m, int64_t file_stride, uint32_t items)
+                                                        const int32_t *__restrict__ rows, uint32_t items, uint32_t Lv,
+                                                        uint32_t ell, uint32_t W, int r1, int m, int64_t file_stride)
 {
     using E = typename A::elem;
     using O = Ops<A, VEC>;
@@ -508,7 +508,7 @@ int run_node_encode(const ccdc_plan_t *p, int node, const void *V, void *X, hipS
     by_node_reads<false>(node_reads<VEC>(p, node, false), [&](auto reads) {
         by_files<Ops<A, VEC>, ANY>(p->m > 2, [&](auto together) {
             k_node_encode<A, VEC, decltype(reads)::value, decltype(together)::value, ANY><<<cdiv(items, kBlock), kBlock, 0, st>>>(
-                (const E *)V, (E *)X, p->d_src_off, list, p->r + 1, Lv, ell, W, p->m, (int64_t)p->Q * p->T, (uint32_t)items);
+                (const E *)V, (E *)X, p->d_src_off, list, (uint32_t)items, Lv, ell, W, p->r + 1, p->m, (int64_t)p->Q * p->T);
         });
     });
     return launched();
