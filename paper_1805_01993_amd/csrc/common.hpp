@@ -346,7 +346,7 @@ __device__ __forceinline__ void store_at(void *p, const P &v)
 // moved back to the last whole one, so two lanes make the same elements from the same numbers (column()); a pack
 // of a packet's short last segment is made element by element (end_pack()).  One-element packs, which such calls were made of before,
 // are as many instructions and addresses for an eighth or a quarter of the bytes.  916 calls alone of 100 plans of such lengths, 64 KB to 1.5
-// GB, 0.80 of the time, from 10 MB on 0.69, 12 of them over 5 % slower: 18 nodes, r = 2, T = 56286 bf16 the four stages 931 -> 350 us, 70 jobs on 8 nodes,
+// GB, 0.80 of the time, from 10 MB on 0.68, five of them over 5 % slower: 18 nodes, r = 2, T = 56286 bf16 the four stages 931 -> 350 us, 70 jobs on 8 nodes,
 // r = 3, four files, T = 105661 bf16 777 -> 477, 23 nodes, r = 2, T = 28754 f16 node-local 425 -> 185, 21 nodes, r = 3, T = 4282 f32 the stages 820 -> 529.
 // With fewer packs than fill the chip the narrow ones stay, of which there are more lanes with less each to add (any_element(); uncoded, 19
 // nodes, T = 4169 u32 12 and more files a packet 10.6 us, 28.7; 7 nodes, r = 5, eleven files, T = 5470 bf16 fused 5.3, 51).
