@@ -45,40 +45,40 @@ ALSO = [
 # is recorded with them; for any other source `traffic` is null.
 TRAFFIC = {
     ("cfg3_gradient", "f32", "pipeline"): {
-        "source_hash": "13a2b840da3339af", "fetch_kib": 1400192.8, "write_kib": 1150000.0, "fetch_scale": 2.0, "write_scale": 1.0,
+        "source_hash": "1e31df16c9a0125a", "fetch_kib": 1400192.8, "write_kib": 1150000.0, "fetch_scale": 2.0, "write_scale": 1.0,
         "profile": "profiles/pipeline_fused_cfg3_gradient_f32.md"},
     ("cfg5_k24", "f32", "pipeline"): {
-        "source_hash": "13a2b840da3339af", "fetch_kib": 1040715.0, "write_kib": 462096.0, "fetch_scale": 2.0, "write_scale": 1.0,
+        "source_hash": "1e31df16c9a0125a", "fetch_kib": 1040714.5, "write_kib": 462096.0, "fetch_scale": 2.0, "write_scale": 1.0,
         "profile": "profiles/pipeline_fused_cfg5_k24_f32.md"},
     ("cfg5_k24", "u32", "pipeline"): {
-        "source_hash": "13a2b840da3339af", "fetch_kib": 1040698.7, "write_kib": 462096.0, "fetch_scale": 2.0, "write_scale": 1.0,
+        "source_hash": "1e31df16c9a0125a", "fetch_kib": 1040698.6, "write_kib": 462096.0, "fetch_scale": 2.0, "write_scale": 1.0,
         "profile": "profiles/pipeline_fused_cfg5_k24_u32.md"},
     ("cfg3_gradient", "bf16", "pipeline"): {
-        "source_hash": "13a2b840da3339af", "fetch_kib": 700202.1, "write_kib": 575000.0, "fetch_scale": 2.0, "write_scale": 1.0,
+        "source_hash": "1e31df16c9a0125a", "fetch_kib": 700202.4, "write_kib": 575000.0, "fetch_scale": 2.0, "write_scale": 1.0,
         "profile": "profiles/pipeline_fused_cfg3_gradient_bf16.md"},
     ("cfg5_k24", "bf16", "pipeline"): {
-        "source_hash": "13a2b840da3339af", "fetch_kib": 530670.9, "write_kib": 249480.0, "fetch_scale": 2.0, "write_scale": 1.0,
+        "source_hash": "1e31df16c9a0125a", "fetch_kib": 530671.5, "write_kib": 249480.0, "fetch_scale": 2.0, "write_scale": 1.0,
         "profile": "profiles/pipeline_fused_cfg5_k24_bf16.md"},
     ("cfg3_gradient", "f32", "shuffle+reduce"): {
-        "source_hash": "01a6d75c2d6a4802", "fetch_kib": 1050033.5, "write_kib": 3150280.4, "fetch_scale": 2.0, "write_scale": 1.0,
+        "source_hash": "4f91aa91c18d836d", "fetch_kib": 1050034.5, "write_kib": 3150102.9, "fetch_scale": 2.0, "write_scale": 1.0,
         "profile": "profiles/shuffle_fused_reduce_cfg3_gradient_f32.md"},
     ("jobs_k8", "f32", "shuffle+reduce"): {
-        "source_hash": "01a6d75c2d6a4802", "fetch_kib": 909384.8, "write_kib": 892636.8, "fetch_scale": 2.0, "write_scale": 1.0,
+        "source_hash": "4f91aa91c18d836d", "fetch_kib": 892644.7, "write_kib": 895165.6, "fetch_scale": 2.0, "write_scale": 1.0,
         "profile": "profiles/shuffle_fused_reduce_jobs_k8_f32.md"},
     ("comp_gradient", "f32", "combine+reduce"): {
-        "source_hash": "01a6d75c2d6a4802", "fetch_kib": 1050014.1, "write_kib": 300000.0, "fetch_scale": 2.0, "write_scale": 1.0,
+        "source_hash": "4f91aa91c18d836d", "fetch_kib": 1050016.9, "write_kib": 300000.0, "fetch_scale": 2.0, "write_scale": 1.0,
         "profile": "profiles/combine_reduce_comp_gradient_f32.md"},
     ("cfg3_gradient", "f32", "node"): {
-        "source_hash": "798e1fbf5eadbabe", "fetch_kib": 1948497.8, "write_kib": 100000.0, "fetch_scale": 2.0, "write_scale": 1.0,
+        "source_hash": "b4be97eadcdd533f", "fetch_kib": 1947700.1, "write_kib": 100000.0, "fetch_scale": 2.0, "write_scale": 1.0,
         "profile": "profiles/node_encode_decode_reduce_cfg3_gradient_f32.md"},
     ("cfg3_gradient", "f32", "map+pipeline"): {
-        "source_hash": "0758b3bc4385a2f8", "fetch_kib": 1453094.8, "write_kib": 2800000.3, "fetch_scale": 2.0, "write_scale": 1.0,
+        "source_hash": "77c929e8c2745c6c", "fetch_kib": 1453095.3, "write_kib": 2800000.0, "fetch_scale": 2.0, "write_scale": 1.0,
         "profile": "profiles/map_pipeline_fused_cfg3_gradient_f32.md"},
     ("cfg2_k10", "f32", "pipeline"): {
-        "source_hash": "13a2b840da3339af", "fetch_kib": 10790.8, "write_kib": 6800.8, "fetch_scale": 2.0, "write_scale": 1.0,
+        "source_hash": "1e31df16c9a0125a", "fetch_kib": 10790.6, "write_kib": 6869.1, "fetch_scale": 2.0, "write_scale": 1.0,
         "profile": "profiles/pipeline_fused_cfg2_k10_f32.md"},
     ("cfg4_k16", "f32", "pipeline"): {
-        "source_hash": "13a2b840da3339af", "fetch_kib": 75505.2, "write_kib": 44539.4, "fetch_scale": 2.0, "write_scale": 1.0,
+        "source_hash": "1e31df16c9a0125a", "fetch_kib": 75498.4, "write_kib": 44538.2, "fetch_scale": 2.0, "write_scale": 1.0,
         "profile": "profiles/pipeline_fused_cfg4_k16_f32.md"},
 }
 
